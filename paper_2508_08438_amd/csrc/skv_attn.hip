@@ -19,7 +19,7 @@
 // pipeline over 32-key sub-tiles: the scores of sub-tile h + 1, the softmax of sub-tile h and
 // the output update with sub-tile h - 1 share a half-step, in which nothing depends on
 // anything else, so MFMAs and vector instructions alternate in the instruction stream.
-// fp32 path: one wavefront per output row, plain fp32 arithmetic (correctness configuration).
+// fp32 path: skv_attn_f32.hip.
 #include <atomic>
 
 #include "skv_internal.h"
@@ -706,89 +706,6 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
   }
 }
 
-// ---- fp32 kernel: one wavefront per (token, head) output row ----------------------------------
-template <int D>
-__global__ __launch_bounds__(64) void attn_f32_kernel(AttnParams p, int64_t max_rows) {
-  __shared__ float red[64 * (D + 1)];
-  const int lane = threadIdx.x;
-  const int64_t g = blockIdx.x;  // token row * Hq + head
-  const int h = (int)(g % p.Hq);
-  const int64_t tok = g / p.Hq;
-  if (tok >= max_rows || tok >= p.q_off[p.n_req]) return;
-  int lo = 0, hi = p.n_req;  // q_off[lo] <= tok < q_off[hi]
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (p.q_off[mid] <= tok) lo = mid; else hi = mid;
-  }
-  const int r = lo;
-  const int qbase = p.q_off[r];
-  const int i = (int)(tok - qbase);
-  const int L = p.matched_len[r] > 0 ? p.matched_len[r] & ~(SKV_BLOCK_TOKENS - 1) : 0;   // whole blocks only
-  const int n_keys = L + i + 1;
-  const int hk = h / (p.Hq / p.Hkv);
-  const float* q = (const float*)p.q + ((size_t)tok * p.Hq + h) * D;
-  float qv[D];
-#pragma unroll
-  for (int c = 0; c < D; ++c) qv[c] = q[c];
-  float m = -INFINITY, l = 0.f;
-  float acc[D];
-#pragma unroll
-  for (int c = 0; c < D; ++c) acc[c] = 0.f;
-  for (int j = lane; j < n_keys; j += 64) {
-    const float *kr = nullptr, *vr = nullptr;
-    if (j < L) {
-      const int page = p.page_table[(size_t)r * p.max_blocks + j / SKV_BLOCK_TOKENS];
-      if (page >= 0 && page < p.n_pages) {
-        const size_t off = (((size_t)page * SKV_BLOCK_TOKENS + j % SKV_BLOCK_TOKENS) * p.Hkv + hk) * D;
-        kr = (const float*)p.kpool + off;
-        vr = (const float*)p.vpool + off;
-      }
-    } else {
-      const size_t off = ((size_t)(qbase + j - L) * p.Hkv + hk) * D;
-      kr = (const float*)p.knew + off;
-      vr = (const float*)p.vnew + off;
-    }
-    float s = 0.f;
-    if (kr) {
-#pragma unroll
-      for (int c = 0; c < D; c += 4) {
-        const float4 kk = *(const float4*)(kr + c);
-        s += qv[c] * kk.x + qv[c + 1] * kk.y + qv[c + 2] * kk.z + qv[c + 3] * kk.w;
-      }
-    }
-    s *= p.scale;
-    const float m_new = fmaxf(m, s);
-    const float alpha = expf(m - m_new);
-    const float e = expf(s - m_new);
-    l = l * alpha + e;
-#pragma unroll
-    for (int c = 0; c < D; c += 4) {
-      float4 vv = {0.f, 0.f, 0.f, 0.f};
-      if (vr) vv = *(const float4*)(vr + c);
-      acc[c] = acc[c] * alpha + e * vv.x;
-      acc[c + 1] = acc[c + 1] * alpha + e * vv.y;
-      acc[c + 2] = acc[c + 2] * alpha + e * vv.z;
-      acc[c + 3] = acc[c + 3] * alpha + e * vv.w;
-    }
-    m = m_new;
-  }
-  // merge the 64 partial softmaxes
-  float mw = m;
-  for (int o = 32; o >= 1; o >>= 1) mw = fmaxf(mw, __shfl_xor(mw, o));
-  const float f = m == -INFINITY ? 0.f : expf(m - mw);
-  float lw = l * f;
-  for (int o = 32; o >= 1; o >>= 1) lw += __shfl_xor(lw, o);
-#pragma unroll
-  for (int c = 0; c < D; ++c) red[lane * (D + 1) + c] = acc[c] * f;
-  __syncthreads();
-  float* out = (float*)p.out + ((size_t)tok * p.Hq + h) * D;
-  for (int c = lane; c < D; c += 64) {
-    float sum = 0.f;
-    for (int t = 0; t < 64; ++t) sum += red[t * (D + 1) + c];
-    out[c] = sum / lw;
-  }
-}
-
 int heads_per_wg_for(int G) { return G % 4 == 0 ? 4 : (G % 2 == 0 ? 2 : 1); }  // divides kWaves
 
 int check_attn(const skv_attn_desc* d) {
@@ -854,14 +771,10 @@ static int prefill_attn_enqueue(const skv_attn_desc* desc, int32_t n_req, const 
   p.scale = skv_softmax_scale(desc);
 
   if (desc->dtype == SKV_F32) {
-    const int64_t rows = total_q_rows * desc->n_q_heads;
-    if (rows > 0x7fffffff) return SKV_ERANGE;
-    if (desc->head_dim == 64)
-      attn_f32_kernel<64><<<(int)rows, 64, 0, st>>>(p, total_q_rows);
-    else
-      attn_f32_kernel<128><<<(int)rows, 64, 0, st>>>(p, total_q_rows);
-    SKV_HIP(hipGetLastError());
-    return SKV_OK;
+    const SkvAttnF32Params f = {d_q, d_knew, d_vnew, d_kpool, d_vpool, d_out, d_q_off, d_matched_len, d_page_table,
+                                n_req, max_blocks, n_pages, desc->n_q_heads, desc->n_kv_heads, skv_softmax_scale(desc),
+                                total_q_rows};
+    return skv_attn_f32_enqueue(f, desc->head_dim, stream);
   }
 
   const int64_t max_items = max_items_for(desc, n_req, total_q_rows);
