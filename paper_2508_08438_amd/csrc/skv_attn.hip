@@ -29,6 +29,7 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
@@ -63,6 +64,8 @@ struct AttnParams {
   const int32_t* items;      // kItemInts ints per work item
   const int32_t* n_items;
   const char* zero_page;     // 16 rows of zeros: stands in for a group of keys that has no data
+  const int32_t* splits;     // kSplitInts ints per work item whose keys are split over several workgroups
+  float* partials;           // kSlotFloats floats per part and (kv head, head group); null: nothing is ever split
   int n_req, max_blocks, n_pages, Hq, Hkv;
   int heads_per_wg;          // query heads of one kv head handled by one workgroup (1, 2 or 4)
   float scale;
@@ -70,69 +73,185 @@ struct AttnParams {
 
 // ---- work list ---------------------------------------------------------------------------------
 // One workgroup.  items[] lists one 32-byte record per (request, q tile) pair -- {request, first suffix row of
-// the tile, first row of the request in Q, its suffix length S, its reused length L, end row of the tile} -- so
-// that a workgroup of the attention kernel learns everything about its piece of work from one load.  A request's
+// the tile, first row of the request in Q, its suffix length S, its reused length L, end row of the tile, first key tile,
+// part} -- so that a workgroup of the attention kernel learns everything about its piece of work from one load.  A request's
 // heaviest (last) tile first.  The q tiles of a request are cut so that L + (first row of a tile) is a multiple of the
 // 64-key tile: the first tile is short when L is not, and every later tile ends exactly where a key tile ends, so
 // no workgroup streams a key tile for the sake of a few keys of round-up -- unless the short first tile makes the
 // request one tile longer than cutting from row 0 would and the reused prefix is long (L > S / 2): a tile more costs
 // a pass over about L + S / 2 keys, the round-up one more 64-key iteration in each of the S / 64 tiles.
+//
+// Small batches leave most of the chip idle and their time is the length of one workgroup's pass over the keys (one turn
+// behind 24 k cached tokens: 80 workgroups, 0.50 ms).  Their items are split along the keys: every part is a record of its
+// own (part = (slot + 1) << kPartBits | key tiles), leaves its unnormalised output, reference and row sum in the workspace,
+// and attn_merge_kernel combines them.  The part length c is the smallest for which all parts run in one round, or in
+// two, of one workgroup per compute unit; a workgroup costs about kStartTiles key tiles before and after its loop, the
+// merge about as much again, and unless the split wins by that the items stay whole.
 constexpr int kItemInts = 8;
-__global__ void attn_schedule_kernel(int n_req, const int32_t* __restrict__ q_off,
-                                     const int32_t* __restrict__ matched_len, int pos_per_wg,
-                                     int max_items, int32_t* __restrict__ n_items, int32_t* __restrict__ items,
-                                     uint4* __restrict__ zero_page, int zero_vec) {
-  __shared__ int32_t sh[1024];
-  for (int i = threadIdx.x; i < zero_vec; i += 1024) zero_page[i] = make_uint4(0u, 0u, 0u, 0u);
+constexpr int kCus = 256;             // compute units = workgroups that run at once
+constexpr int kMaxSlots = 2 * kCus;   // parts of a split batch, over all kv heads and head groups
+constexpr int kStartTiles = 8;
+constexpr int kPartBits = 20;         // key tiles of a part
+constexpr int kSplitInts = 8;         // {first row, end row, first row of the request in Q, first slot, parts, 0, 0, 0}
+constexpr int kSlotFloats = kWaves * 64 * (64 + 2);   // per wavefront and lane: 64 of O^T, reference, row sum
+
+struct Cut {   // how one request's suffix is cut into q tiles
+  int S, L, qb, head_rows, nt;
+  __device__ void tile(int j, int pos_per_wg, int& row0, int& row1) const {   // j-th tile from the front
+    if (head_rows > 0 && j == 0) {
+      row0 = 0;
+      row1 = head_rows;
+    } else {
+      row0 = head_rows + (j - (head_rows > 0 ? 1 : 0)) * pos_per_wg;
+      row1 = min(S, row0 + pos_per_wg);
+    }
+  }
+};
+__device__ inline Cut cut_of(int r, const int32_t* q_off, const int32_t* matched_len, int pos_per_wg) {
+  Cut c;
+  c.qb = q_off[r];
+  c.S = q_off[r + 1] - c.qb;
+  c.L = matched_len[r] > 0 ? matched_len[r] & ~(SKV_BLOCK_TOKENS - 1) : 0;   // whole blocks only
+  c.head_rows = min(c.S, (kBN - c.L % kBN) % kBN);                           // rows of the short first tile (0: none)
+  c.nt = c.S > 0 ? (c.head_rows > 0 ? 1 : 0) + (c.S - c.head_rows + pos_per_wg - 1) / pos_per_wg : 0;
+  const int nt_plain = (c.S + pos_per_wg - 1) / pos_per_wg;
+  if (nt_plain < c.nt && 2 * c.L > c.S) {   // the short first tile would cost a whole extra tile: cut from row 0 instead
+    c.head_rows = 0;
+    c.nt = nt_plain;
+  }
+  return c;
+}
+// Parts an item of n key tiles is split into at part length c: every part but the first starts at a key that all of the
+// item's rows see (key tile `last` or before), so that each part has a finite row maximum from its first keys on.
+__device__ inline int parts_of(int n, int last, int c) {
+  int parts = (n + c - 1) / c;
+  while (parts > 1 && (parts - 1) * ((n + parts - 1) / parts) > last) --parts;
+  return parts;
+}
+
+constexpr int kSchedThreads = 1024;
+__global__ __launch_bounds__(kSchedThreads) void attn_schedule_kernel(
+    int n_req, const int32_t* __restrict__ q_off, const int32_t* __restrict__ matched_len, int pos_per_wg, int max_items,
+    int units /* workgroups per item */, int32_t* __restrict__ n_items /* [0] items, [1] split items */,
+    int32_t* __restrict__ items, int32_t* __restrict__ splits /* null: never split */, uint4* __restrict__ zero_page,
+    int zero_vec) {
+  __shared__ int32_t sh[kSchedThreads];
   __shared__ int32_t carry;
+  for (int i = threadIdx.x; i < zero_vec; i += kSchedThreads) zero_page[i] = make_uint4(0u, 0u, 0u, 0u);
   if (threadIdx.x == 0) carry = 0;
   __syncthreads();
-  for (int base = 0; base < n_req; base += 1024) {
+  for (int base = 0; base < n_req; base += kSchedThreads) {
     const int r = base + threadIdx.x;
-    int nt = 0, S = 0, qb = 0, L = 0, head_rows = 0;   // head_rows: rows of the short first tile (0: none)
-    if (r < n_req) {
-      qb = q_off[r];
-      S = q_off[r + 1] - qb;
-      L = matched_len[r] > 0 ? matched_len[r] & ~(SKV_BLOCK_TOKENS - 1) : 0;   // whole blocks only
-      head_rows = min(S, (kBN - L % kBN) % kBN);
-      nt = S > 0 ? (head_rows > 0 ? 1 : 0) + (S - head_rows + pos_per_wg - 1) / pos_per_wg : 0;
-      const int nt_plain = (S + pos_per_wg - 1) / pos_per_wg;
-      if (nt_plain < nt && 2 * L > S) {   // the short first tile would cost a whole extra tile: cut from row 0 instead
-        head_rows = 0;
-        nt = nt_plain;
-      }
-    }
-    sh[threadIdx.x] = nt;
+    sh[threadIdx.x] = r < n_req ? cut_of(r, q_off, matched_len, pos_per_wg).nt : 0;
     __syncthreads();
-    for (int o = 1; o < 1024; o <<= 1) {
+    for (int o = 1; o < kSchedThreads; o <<= 1) {
       int add = threadIdx.x >= o ? sh[threadIdx.x - o] : 0;
       __syncthreads();
       sh[threadIdx.x] += add;
       __syncthreads();
     }
-    const int start = carry + sh[threadIdx.x] - nt;
-    for (int k = 0; k < nt; ++k) {
-      if (start + k < max_items) {
-        int4* rec = (int4*)(items + (size_t)kItemInts * (start + k));
-        const int j = nt - 1 - k;   // tile index within the request
-        int row0, row1;
-        if (head_rows > 0 && j == 0) {
-          row0 = 0;
-          row1 = head_rows;
-        } else {
-          row0 = head_rows + (j - (head_rows > 0 ? 1 : 0)) * pos_per_wg;
-          row1 = min(S, row0 + pos_per_wg);
-        }
-        rec[0] = make_int4(r, row0, qb, S);
-        rec[1] = make_int4(L, row1, 0, 0);
-
+    // the chunk's items, one per thread and turn: the request is found in the scan
+    const int first = carry, total = sh[kSchedThreads - 1];
+    for (int it = threadIdx.x; it < total && first + it < max_items; it += kSchedThreads) {
+      int lo = 0, hi = kSchedThreads - 1;   // smallest lo with sh[lo] > it
+      while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (sh[mid] > it) hi = mid; else lo = mid + 1;
       }
+      const Cut c = cut_of(base + lo, q_off, matched_len, pos_per_wg);
+      int row0, row1;
+      c.tile(sh[lo] - 1 - it, pos_per_wg, row0, row1);   // the request's last tile first
+      int4* rec = (int4*)(items + (size_t)kItemInts * (first + it));
+      rec[0] = make_int4(base + lo, row0, c.qb, c.S);
+      rec[1] = make_int4(c.L, row1, 0, 0);
     }
     __syncthreads();
-    if (threadIdx.x == 0) carry += sh[1023];
+    if (threadIdx.x == 0) carry += total;
     __syncthreads();
   }
-  if (threadIdx.x == 0) *n_items = carry < max_items ? carry : max_items;
+  const int n = min(carry, max_items);
+  int n_out = n, n_split = 0;
+  if (splits && n > 0 && n <= kCus && n * units <= kMaxSlots) {   // few items: split their keys?  One item per thread.
+    __syncthreads();   // the records of the last chunk are read back below
+    const int i = threadIdx.x;
+    int4 a = {0, 0, 0, 0}, b = {0, 0, 0, 0};
+    int n_kt = 0, last = 0;
+    if (i < n) {
+      a = ((const int4*)(items + (size_t)kItemInts * i))[0];
+      b = ((const int4*)(items + (size_t)kItemInts * i))[1];
+      n_kt = (b.x + b.y + kBN - 1) / kBN;
+      last = (b.x + a.y) / kBN;
+    }
+    __shared__ int red[kCus / 64];
+    auto block_sum = [&](int v) {   // over the first kCus threads
+      for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
+      if (i < kCus && (i & 63) == 0) red[i >> 6] = v;
+      __syncthreads();
+      int s = 0;
+      for (int w = 0; w < kCus / 64; ++w) s += red[w];
+      __syncthreads();
+      return s;
+    };
+    int longest = n_kt;
+    for (int o = 32; o >= 1; o >>= 1) longest = max(longest, __shfl_xor(longest, o));
+    if (i < kCus && (i & 63) == 0) red[i >> 6] = longest;
+    __syncthreads();
+    longest = 0;
+    for (int w = 0; w < kCus / 64; ++w) longest = max(longest, red[w]);
+    __syncthreads();
+    const int rounds_whole = (n * units + kCus - 1) / kCus;
+    const int share = (block_sum(n_kt) * units + kCus - 1) / kCus;   // key tiles per compute unit
+    const int whole = rounds_whole == 1 ? longest : max(longest, share + longest / 2);
+    int best_c = longest, best_cost = rounds_whole * kStartTiles + whole - kStartTiles;   // (the split also merges)
+    for (int rounds = 1; rounds <= 2; ++rounds) {
+      const int room = rounds * kCus / units;
+      if (room < n) continue;
+      int lo = 1, hi = longest;   // smallest part length for which all parts have room
+      while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (block_sum(i < n ? parts_of(n_kt, last, mid) : 0) <= room) hi = mid; else lo = mid + 1;
+      }
+      if (rounds * (kStartTiles + lo) < best_cost) {
+        best_cost = rounds * (kStartTiles + lo);
+        best_c = lo;
+      }
+    }
+    const int parts = i < n ? parts_of(n_kt, last, best_c) : 0;
+    const int total = block_sum(parts);
+    if (total > n && total <= max_items) {
+      // exclusive scans of the parts (place in the list), of the parts of split items (slot) and of the split items
+      sh[i] = parts | (parts > 1 ? parts << 10 | 1 << 20 : 0);
+      __syncthreads();
+      for (int o = 1; o < kCus; o <<= 1) {
+        const int add = i >= o && i < kCus ? sh[i - o] : 0;
+        __syncthreads();
+        if (i < kCus) sh[i] += add;
+        __syncthreads();
+      }
+      if (i < n) {
+        const int before = i ? sh[i - 1] : 0;
+        const int at = before & 1023, slot = (before >> 10) & 1023, si = before >> 20;
+        const int len = (n_kt + parts - 1) / parts;
+        for (int j = 0; j < parts; ++j) {
+          const int kt0 = j * len, n_part = min(len, n_kt - kt0);
+          int4* rec = (int4*)(items + (size_t)kItemInts * (at + j));
+          rec[0] = a;
+          rec[1] = make_int4(b.x, b.y, kt0, parts > 1 ? (slot + j + 1) << kPartBits | n_part : 0);
+        }
+        if (parts > 1) {
+          int4* sp = (int4*)(splits + kSplitInts * si);
+          sp[0] = make_int4(a.y, b.y, a.z, slot);
+          sp[1] = make_int4(parts, 0, 0, 0);
+        }
+      }
+      n_out = total;
+      n_split = sh[n - 1] >> 20;
+    }
+  }
+  if (threadIdx.x == 0) {
+    n_items[0] = n_out;
+    n_items[1] = n_split;
+  }
 }
 
 // ---- bf16 MFMA kernel --------------------------------------------------------------------------
@@ -217,9 +336,13 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
   }
   // the record is read together with the item count (the grid bound keeps the index inside the list)
   const int4 rec0 = ((const int4*)(p.items + (size_t)kItemInts * item))[0];
-  const int L = __builtin_amdgcn_readfirstlane(p.items[(size_t)kItemInts * item + 4]);
-  const int row1 = __builtin_amdgcn_readfirstlane(p.items[(size_t)kItemInts * item + 5]);   // end row of the q tile
+  const int4 rec1 = ((const int4*)(p.items + (size_t)kItemInts * item))[1];
   if (item >= *p.n_items) return;
+  const int kt0 = __builtin_amdgcn_readfirstlane(rec1.z);    // first key tile of this part
+  const int part = __builtin_amdgcn_readfirstlane(rec1.w);   // 0: the whole item
+  // Everything below counts keys from the part's first one: the reused length and with it every position shifts.
+  const int L = __builtin_amdgcn_readfirstlane(rec1.x) - kt0 * kBN;                         // may be negative
+  const int row1 = __builtin_amdgcn_readfirstlane(rec1.y);                                  // end row of the q tile
   const int r = __builtin_amdgcn_readfirstlane(rec0.x);
   const int row0 = __builtin_amdgcn_readfirstlane(rec0.y);                                  // first row of the q tile
   const int qbase = __builtin_amdgcn_readfirstlane(rec0.z);
@@ -228,8 +351,10 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
 
   const int head = kvh * G + hg * p.heads_per_wg + (wave % p.heads_per_wg);
   const int pos0 = row0 + (wave / p.heads_per_wg) * kRowsPerWave;             // first row of this wave
-  const int n_tiles = (L + row1 + kBN - 1) / kBN;                             // 64-key tiles the workgroup streams
-  const int wave_key_end = pos0 < row1 ? L + min(row1, pos0 + kRowsPerWave) : 0;  // this wave needs keys [0, wave_key_end)
+  const int n_tiles = part ? part & ((1 << kPartBits) - 1) : (L + row1 + kBN - 1) / kBN;   // 64-key tiles the workgroup streams
+  const int wave_key_end = pos0 < row1 ? min(L + min(row1, pos0 + kRowsPerWave), n_tiles * kBN) : 0;  // this wave needs keys [0, wave_key_end)
+  const int32_t* const table = p.page_table + (size_t)r * p.max_blocks + kt0 * (kBN / SKV_BLOCK_TOKENS);
+  const int table_len = p.max_blocks - kt0 * (kBN / SKV_BLOCK_TOKENS);
 
   // ---- the first global reads, all in flight together: the page ids of the first two address windows (what the K/V
   // loads need first), then this wave's Q rows.  The K/V loads are issued as soon as the page ids are there; Q is
@@ -239,8 +364,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
   auto window_page = [&](int w) __attribute__((always_inline)) {
     const int gi = w * 64 + lane;
     int page = -1;
-    if (gi * SKV_BLOCK_TOKENS < L && gi < p.max_blocks)
-      page = __builtin_nontemporal_load(&p.page_table[(size_t)r * p.max_blocks + gi]);
+    if (gi * SKV_BLOCK_TOKENS < L && gi < table_len) page = __builtin_nontemporal_load(&table[gi]);
     return page;
   };
   // (the five base addresses as values: selecting between the fields of the argument block itself makes the
@@ -668,10 +792,26 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
   for (; kt < kt_mid; ++kt) iteration.template operator()<2>(kt);
   for (; kt <= n_tiles; ++kt) iteration.template operator()<0>(kt);
 
+  // ---- a part of a split item: O^T as it lies in the registers, the reference and the row sum
+  if (pos0 >= row1) return;
+  if (part) {
+    const int slot = (part >> kPartBits) - 1;
+    const int unit = kvh * n_hg + hg;
+    f32x4* dst = (f32x4*)(p.partials + ((size_t)slot * p.Hkv * n_hg + unit) * kSlotFloats + (size_t)wave * (64 * 66)) + lane;
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+      for (int i4 = 0; i4 < 4; ++i4)
+        dst[(a * 4 + i4) * 64] = f32x4{o[a][i4 * 4], o[a][i4 * 4 + 1], o[a][i4 * 4 + 2], o[a][i4 * 4 + 3]};
+    float* ml = (float*)(dst - lane + 16 * 64) + lane;
+    ml[0] = m_ref;
+    ml[64] = l_run + swap_halves(l_run);
+    return;
+  }
+
   // ---- normalise and store.  A lane holds query l32 with d = 32 a + 8 (e/4) + 4 half + e%4, i.e. sixteen 8-byte
   // pieces of one output row.  They go through the wave's staging tile, 16 rows at a time, and leave as whole
   // 256-byte rows.
-  if (pos0 >= row1) return;
   {
     const float lsum = l_run + swap_halves(l_run);
     const float inv = 1.0f / lsum;
@@ -706,6 +846,47 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
   }
 }
 
+// ---- merge of the parts of split items -----------------------------------------------------------
+// One workgroup per (split item, kv head and head group, wavefront of the attention kernel); its wavefront a combines
+// d = 32 a .. 32 a + 31 of that wavefront's 32 rows, each lane what the same lane of every part wrote: coalesced 1 KB reads.
+// Bound by those reads (16.9 KB per part).
+__global__ __launch_bounds__(256) void attn_merge_kernel(AttnParams p) {
+  const int n_hg = p.Hq / p.Hkv / p.heads_per_wg, units = p.Hkv * n_hg;
+  const int wave = blockIdx.x % kWaves, unit = blockIdx.x / kWaves % units, si = blockIdx.x / kWaves / units;
+  if (si >= p.n_items[1]) return;
+  const int4 a = ((const int4*)(p.splits + kSplitInts * si))[0];
+  const int parts = p.splits[kSplitInts * si + 4];
+  const int row0 = a.x, row1 = a.y, qbase = a.z, slot = a.w;
+  const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
+  const int pos0 = row0 + (wave / p.heads_per_wg) * kRowsPerWave;
+  if (pos0 >= row1) return;
+  const size_t stride = (size_t)units * kSlotFloats;   // from one part to the next
+  const float* src = p.partials + ((size_t)slot * units + unit) * kSlotFloats + (size_t)wave * (64 * 66);
+  float m = -INFINITY;
+  for (int j = 0; j < parts; ++j) m = fmaxf(m, src[j * stride + 64 * 64 + lane]);
+  float l = 0.f;
+  f32x4 acc[4] = {};
+#pragma unroll 4
+  for (int j = 0; j < parts; ++j) {
+    const float* s = src + j * stride;
+    const float f = __builtin_amdgcn_exp2f(s[64 * 64 + lane] - m);
+    l += f * s[64 * 65 + lane];
+#pragma unroll
+    for (int i4 = 0; i4 < 4; ++i4) acc[i4] += f * ((const f32x4*)s)[(q * 4 + i4) * 64 + lane];
+  }
+  const int row = pos0 + (lane & 31);
+  if (row >= row1) return;
+  const float inv = 1.0f / l;
+  const int head = (unit / n_hg) * (p.Hq / p.Hkv) + (unit % n_hg) * p.heads_per_wg + wave % p.heads_per_wg;
+  __bf16* dst = (__bf16*)p.out + ((size_t)(qbase + row) * p.Hq + head) * kD + 32 * q + 4 * (lane >> 5);
+#pragma unroll
+  for (int i4 = 0; i4 < 4; ++i4) {
+    const bf16x2 y0 = __builtin_convertvector((f32x2{acc[i4][0] * inv, acc[i4][1] * inv}), bf16x2);
+    const bf16x2 y1 = __builtin_convertvector((f32x2{acc[i4][2] * inv, acc[i4][3] * inv}), bf16x2);
+    *(u32x2*)(dst + 8 * i4) = u32x2{__builtin_bit_cast(uint32_t, y0), __builtin_bit_cast(uint32_t, y1)};
+  }
+}
+
 int heads_per_wg_for(int G) { return G % 4 == 0 ? 4 : (G % 2 == 0 ? 2 : 1); }  // divides kWaves
 
 int check_attn(const skv_attn_desc* d) {
@@ -723,18 +904,40 @@ int64_t max_items_for(const skv_attn_desc* d, int32_t n_req, int64_t total_q_row
   return total_q_rows / pos_per_wg + 2 * (int64_t)n_req;   // per request: a short first tile and a ragged last one
 }
 
+// Workgroups per item, and whether a batch of this bound is small enough that its items may be split along the keys
+// (with more workgroups than two rounds of the chip there is nothing to fill).
+int units_of(const skv_attn_desc* d) {
+  return d->n_kv_heads * (d->n_q_heads / d->n_kv_heads / heads_per_wg_for(d->n_q_heads / d->n_kv_heads));
+}
+int64_t max_parts_for(const skv_attn_desc* d, int64_t total_q_rows) {
+  if (d->dtype != SKV_BF16) return 0;
+  const int pos_per_wg = (kWaves / heads_per_wg_for(d->n_q_heads / d->n_kv_heads)) * kRowsPerWave;
+  const int units = units_of(d);
+  return total_q_rows / pos_per_wg * units <= kMaxSlots && units <= kCus ? kMaxSlots / units : 0;
+}
+size_t split_bytes(const skv_attn_desc* d, int64_t total_q_rows) {
+  const int64_t parts = max_parts_for(d, total_q_rows);
+  return parts ? kCus * kSplitInts * sizeof(int32_t) + (size_t)parts * units_of(d) * kSlotFloats * sizeof(float) : 0;
+}
+
 size_t zero_page_bytes(const skv_attn_desc* d) {
   return d->dtype == SKV_BF16 ? skv_align256((size_t)SKV_BLOCK_TOKENS * d->n_kv_heads * kD * 2) : 0;
 }
 
 }  // namespace
 
+// Workspace without the area for split items: what a call needs at the least.
+static size_t base_workspace(const skv_attn_desc* desc, int32_t n_req, int64_t total_q_rows) {
+  const int64_t records = max_items_for(desc, n_req, total_q_rows) + max_parts_for(desc, total_q_rows);
+  return 256 + zero_page_bytes(desc) + skv_align256((size_t)records * kItemInts * sizeof(int32_t));
+}
+
 extern "C" int skv_prefill_attn_workspace_size(const skv_attn_desc* desc, int32_t n_req,
                                                int64_t total_q_rows, size_t* bytes) {
   int rc = check_attn(desc);
   if (rc) return rc;
   if (n_req < 0 || total_q_rows < 0 || !bytes) return SKV_EINVAL;
-  *bytes = 256 + zero_page_bytes(desc) + skv_align256((size_t)max_items_for(desc, n_req, total_q_rows) * kItemInts * sizeof(int32_t));
+  *bytes = base_workspace(desc, n_req, total_q_rows) + split_bytes(desc, total_q_rows);
   return SKV_OK;
 }
 
@@ -756,7 +959,7 @@ static int prefill_attn_enqueue(const skv_attn_desc* desc, int32_t n_req, const 
                                 int64_t total_q_rows, const void* d_kpool, const void* d_vpool,
                                 int32_t n_pages, const int32_t* d_matched_len,
                                 const int32_t* d_page_table, int32_t max_blocks, void* d_out,
-                                void* d_workspace, void* stream) {
+                                void* d_workspace, bool may_split, void* stream) {
   hipStream_t st = (hipStream_t)stream;
 
   AttnParams p;
@@ -777,17 +980,25 @@ static int prefill_attn_enqueue(const skv_attn_desc* desc, int32_t n_req, const 
     return skv_attn_f32_enqueue(f, desc->head_dim, stream);
   }
 
-  const int64_t max_items = max_items_for(desc, n_req, total_q_rows);
+  const int64_t max_parts = may_split ? max_parts_for(desc, total_q_rows) : 0;
+  const int64_t max_items = max_items_for(desc, n_req, total_q_rows) + max_parts;
   const int pos_per_wg = (kWaves / p.heads_per_wg) * kRowsPerWave;
-  const int n_hg = (desc->n_q_heads / desc->n_kv_heads) / p.heads_per_wg;
-  const int64_t grid = max_items * desc->n_kv_heads * n_hg;
+  const int units = units_of(desc);
+  const int64_t grid = max_items * units;
   if (grid > 0x7fffffff || max_items > 0x3fffffff) return SKV_ERANGE;
-  attn_schedule_kernel<<<1, 1024, 0, st>>>(n_req, d_q_off, d_matched_len, pos_per_wg, (int)max_items,
-                                           (int32_t*)d_workspace, (int32_t*)p.items, (uint4*)p.zero_page,
-                                           (int)(zero_page_bytes(desc) / 16));
+  char* const split_area = (char*)d_workspace + base_workspace(desc, n_req, total_q_rows);
+  p.splits = max_parts ? (const int32_t*)split_area : nullptr;
+  p.partials = max_parts ? (float*)(split_area + kCus * kSplitInts * sizeof(int32_t)) : nullptr;
+  attn_schedule_kernel<<<1, kSchedThreads, 0, st>>>(n_req, d_q_off, d_matched_len, pos_per_wg, (int)max_items, units,
+                                                    (int32_t*)d_workspace, (int32_t*)p.items, (int32_t*)p.splits,
+                                                    (uint4*)p.zero_page, (int)(zero_page_bytes(desc) / 16));
   SKV_HIP(hipGetLastError());
   attn_bf16_kernel<<<(int)grid, kThreads, 0, st>>>(p);
   SKV_HIP(hipGetLastError());
+  if (max_parts) {   // a split item has two parts at least
+    attn_merge_kernel<<<(int)(max_parts / 2 * units * kWaves), 256, 0, st>>>(p);
+    SKV_HIP(hipGetLastError());
+  }
   return SKV_OK;
 }
 
@@ -809,7 +1020,7 @@ extern "C" int skv_prefill_attn(const skv_attn_desc* desc, int32_t n_req, const 
   if (!d_workspace || workspace_bytes < need) return SKV_ENOMEM;
   if ((uintptr_t)d_workspace & 15) return SKV_EINVAL;
   return prefill_attn_enqueue(desc, n_req, d_q, d_knew, d_vnew, d_q_off, total_q_rows, d_kpool, d_vpool, n_pages,
-                              d_matched_len, d_page_table, max_blocks, d_out, d_workspace, stream);
+                              d_matched_len, d_page_table, max_blocks, d_out, d_workspace, true, stream);
 }
 
 // ---- the same call for callers that cannot allocate ---------------------------------------------
@@ -850,16 +1061,15 @@ extern "C" int skv_prefill_attn_static(const skv_attn_desc* desc, int32_t n_req,
   rc = check_attn_buffers(d_q, d_knew, d_vnew, d_q_off, d_kpool, d_vpool, d_matched_len, d_page_table, max_blocks,
                           d_out);
   if (rc) return rc;
-  size_t need = 0;
-  skv_prefill_attn_workspace_size(desc, n_req, total_q_rows, &need);
-  if (need > (size_t)SKV_STATIC_SCRATCH_BYTES) return SKV_ERANGE;   // batch too large for the built-in scratch
+  if (base_workspace(desc, n_req, total_q_rows) > (size_t)SKV_STATIC_SCRATCH_BYTES)
+    return SKV_ERANGE;   // batch too large for the built-in scratch
   void* ws = nullptr;
   rc = scratch_of_current_device(&ws);
   if (rc) return rc;
   // the schedule kernel rewrites the item count, the page of zeros and every record it hands out on each call,
   // so nothing of the previous call's contents is read
   return prefill_attn_enqueue(desc, n_req, d_q, d_knew, d_vnew, d_q_off, total_q_rows, d_kpool, d_vpool, n_pages,
-                              d_matched_len, d_page_table, max_blocks, d_out, ws, stream);
+                              d_matched_len, d_page_table, max_blocks, d_out, ws, false, stream);
 }
 
 // ---- measurement aid: what the matrix cores sustain on given operand values ----

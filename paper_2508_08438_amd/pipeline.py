@@ -83,7 +83,7 @@ class Session:
             self.kctx = torch.zeros((n_ctx, a.n_kv_heads, a.head_dim), dtype=a.torch_dtype, device=dev)
             self.vctx = torch.zeros_like(self.kctx)
         nbytes = skv.skv_prefill_attn_workspace_size(self.desc, w.n_req, self.q.shape[0])
-        self.workspace = torch.zeros(nbytes, dtype=torch.uint8).to(dev)
+        self.workspace = torch.empty(nbytes, dtype=torch.uint8, device=dev)
         skv.skv_counters_reset(self.tree)
 
     # -- the individual stages (each only enqueues on the current stream)

@@ -50,3 +50,38 @@ def test_fp32_maxima_that_keep_moving():
     c["kpool"][:] = -1.0
     got, want = run_attn(c), oracle.attention(**c, n_threads=8)
     assert np.abs(got - want).max() <= 5 * 5 * 400 * 2.0 ** -24
+
+
+# bf16, items split along their keys (few work items behind many keys): 1, 2, 3 .. key tiles a part, parts that end before
+# and behind the reused prefix, short first row tiles, rows of several requests.  Tolerance of the unsplit kernel.
+SPLIT = [
+    (8, 2, [1], [100]), (8, 2, [137], [187]), (16, 8, [64, 5], [64, 300]), (64, 8, [263], [120]), (4, 4, [300], [90]),
+    (4, 2, [200, 1, 0, 129], [33, 250, 4, 100]), (3, 1, [70], [160]), (8, 1, [1500], [0]), (32, 8, [700], [10]),
+    (32, 8, [40] * 20, [40] * 20),
+]
+
+
+@pytest.mark.parametrize("case", range(len(SPLIT)))
+def test_bf16_split_along_the_keys(case):
+    hq, hkv, S, k = SPLIT[case]
+    c = attn_case(60 + case, len(S), hq, hkv, 128, torch.bfloat16, max(k) + 1, S, k, n_pages=sum(k) + 3)
+    got, want = run_attn(c), oracle.attention(**c, n_threads=8)
+    assert np.isfinite(got).all()
+    assert np.abs(got - want).max() <= 2e-2
+    if max(k) > 40:   # pages outside the pool read as zeros in every part
+        r = int(np.argmax(k))
+        for j in (0, k[r] // 2, k[r] - 1):
+            c["kpool"][c["page_table"][r, j]] = 0
+            c["vpool"][c["page_table"][r, j]] = 0
+        want = oracle.attention(**c, n_threads=8)
+        c["page_table"][r, [0, k[r] // 2, k[r] - 1]] = [-1, sum(k) + 3, -5]
+        assert np.abs(run_attn(c) - want).max() <= 2e-2
+
+
+def test_bf16_split_parts_with_their_own_references():
+    # scores that differ by hundreds of exp2 units between the parts: the merge keeps only the largest
+    c = attn_case(77, 1, 8, 2, 128, torch.bfloat16, 130, [100], [128], n_pages=131)
+    for j in range(128):
+        c["kpool"][c["page_table"][0, j]] *= (j % 40) * 2.0
+    got, want = run_attn(c), oracle.attention(**c, n_threads=8)
+    assert np.abs(got - want).max() <= 2e-2 * max(1.0, np.abs(want).max())   # output rounding at values above 1
