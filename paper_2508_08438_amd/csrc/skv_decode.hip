@@ -3,13 +3,15 @@
 // SafeKV Section 2.1 (the decode phase reads the cached K/V of all earlier tokens at every step; KV reuse
 // changes where those pages come from, not what is computed).  The kernel reads the same pools through the
 // same page table as the prefill kernel.  A step moves every cached K and V byte once and does 4*d flops per
-// byte pair, so it is HBM bound; the work of one (request, kv head) is split over several workgroups along
-// the keys, and a second kernel merges the partial softmax states.
+// byte pair, so it is HBM bound; every workgroup takes an equal share of the batch's key tiles, whatever requests
+// they belong to, and a second kernel merges the partial softmax states of the requests that were cut.
 //
 // Layout of the products (MFMA 16x16): S^T = K Q^T with the G query heads of the kv head as the 16 columns,
 // so one wavefront scores 16 keys for all heads with four v_mfma_f32_16x16x32_bf16; the accumulator registers
 // (lane = head, registers = 4 keys) are, after exponentiation, the B operand of O^T += V^T P^T
 // (v_mfma_f32_16x16x16_bf16), whose A operand comes from the LDS transpose load.
+#include <algorithm>
+
 #include "skv_internal.h"
 
 namespace {
@@ -31,20 +33,41 @@ constexpr int kStages = 2;
 constexpr int kKsStride = kD + 8;     // bf16 elements per K row in LDS (conflict-free b128 reads)
 constexpr int kVsStride = kD + 32;    // bf16 elements per V row in LDS (conflict-free transpose loads)
 constexpr int kMaxG = 16;             // query heads per kv head (the columns of one MFMA tile)
+constexpr int kSlots = 512;           // workgroups that run at once: two per compute unit
 constexpr float kLog2e = 1.4426950408889634f;
 
 struct DecParams {
   const void *q, *kpool, *vpool;
   void* out;
   const int32_t *ctx_len, *page_table;
-  const char* zero_page;   // 16 rows of zeros: a page id outside the pool reads as zeros
-  float *part_m, *part_l, *part_o;  // [R][Hkv][n_splits][G] (x d for part_o)
-  int n_req, max_blocks, n_pages, Hq, Hkv, G, n_splits, tiles_per_split;
+  int32_t* first_tile;              // [n_req + 1] tiles of the requests before this one
+  float *part_m, *part_l, *part_o;  // [2 * n_shares][Hkv][G] (x d for part_o)
+  int n_req, max_blocks, n_pages, Hq, Hkv, G;
+  int n_shares;                     // workgroups per kv head the tiles are dealt to; 0: one workgroup per request
   float scale;
 };
 
+__device__ inline int tiles_of(const DecParams& p, int r) {
+  return (max(0, min(p.ctx_len[r], p.max_blocks * SKV_BLOCK_TOKENS)) + kBN - 1) / kBN;
+}
+// T tiles dealt to n shares: the first T % n shares hold one tile more than the others.
+__device__ inline int share_begin(int i, int T, int n) { return i * (T / n) + min(i, T % n); }
+__device__ inline int share_of(int tile, int T, int n) {
+  const int q = T / n, big = T % n * (q + 1);
+  return tile < big ? tile / (q + 1) : T % n + (tile - big) / q;
+}
+
+// A share of a kv head is a run of the T tiles of the batch, request after request, about T / n of them: every
+// workgroup streams the same number of bytes whatever the contexts' lengths, in one round over the chip, and pays its
+// start-up once.  A request wholly inside a share is finished there; of the others every share holds one piece, and a share
+// cuts two requests at most: the one it begins in (slot 2 i) and the one it ends in (slot 2 i + 1).
+// Bound by HBM: 64 requests of 4096..16384 tokens, 8 kv heads (2.68 GB): 436 us = 6.15 TB/s; dealt by request and key range
+// in eight rounds, with most ranges of the shorter contexts empty, 487 us.  256 of 100..4000: 378 us (461).  One of 32000:
+// 31 us (53).
 __global__ __launch_bounds__(kThreads, 2) void decode_attn_kernel(DecParams p) {
   __shared__ __attribute__((aligned(16))) __bf16 smem[kStages * kBN * (kKsStride + kVsStride)];
+  __shared__ int wave_tiles[kWaves];
+  __shared__ int seg_r, seg_t;
   __bf16* const Ks = smem;                                // [kStages][kBN][kKsStride]
   __bf16* const Vs = smem + kStages * kBN * kKsStride;    // [kStages][kBN][kVsStride]
 
@@ -56,26 +79,69 @@ __global__ __launch_bounds__(kThreads, 2) void decode_attn_kernel(DecParams p) {
   // kv head fastest: the workgroups that read the same pages (each its own 256-byte slice of every token row)
   // are dispatched together, one per XCD, and walk the pages at the same time
   const int kvh = blockIdx.x % p.Hkv;
-  const int split = (blockIdx.x / p.Hkv) % p.n_splits;
-  const int r = blockIdx.x / (p.n_splits * p.Hkv);
+  const int share = blockIdx.x / p.Hkv;
   const int G = p.G;
+  const float c = p.scale * kLog2e;
+
+  // ---- which tiles: `left` of them from tile t of request r on
+  int r = share, t = 0, left = 0;
+  if (p.n_shares > 0) {
+    const int per = (p.n_req + kThreads - 1) / kThreads;   // requests per thread, consecutive ones
+    const int r0 = min(tid * per, p.n_req), r1 = min(r0 + per, p.n_req);
+    int own = 0;
+    for (int i = r0; i < r1; ++i) own += tiles_of(p, i);
+    int upto = own;
+    for (int o = 1; o < 64; o <<= 1) {
+      const int x = __shfl_up(upto, o);
+      if (lane >= o) upto += x;
+    }
+    if (lane == 63) wave_tiles[wave] = upto;
+    __syncthreads();
+    int total = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      const int x = wave_tiles[w];
+      if (w < wave) upto += x;
+      total += x;
+    }
+    int before = upto - own;
+    if (blockIdx.x == 0) {   // the merge kernel finds its pieces from these
+      int x = before;
+      for (int i = r0; i < r1; ++i) {
+        p.first_tile[i] = x;
+        x += tiles_of(p, i);
+      }
+      if (tid == 0) p.first_tile[p.n_req] = total;
+    }
+    const int n = min(p.n_shares, total);
+    if (share >= n) return;
+    const int begin = share_begin(share, total, n);
+    left = share_begin(share + 1, total, n) - begin;
+    if (before <= begin && begin < upto) {
+      int i = r0;
+      for (int nt = tiles_of(p, i); before + nt <= begin; nt = tiles_of(p, i)) {
+        before += nt;
+        ++i;
+      }
+      seg_r = i;
+      seg_t = begin - before;
+    }
+    __syncthreads();
+    r = seg_r;
+    t = seg_t;
+  }
+  for (;; ++r, t = 0) {
+  r = __builtin_amdgcn_readfirstlane(r);
   int ctx = __builtin_amdgcn_readfirstlane(p.ctx_len[r]);
   ctx = max(0, min(ctx, p.max_blocks * SKV_BLOCK_TOKENS));
-  const int t0 = split * p.tiles_per_split;
-  const int t1 = min(t0 + p.tiles_per_split, (ctx + kBN - 1) / kBN);
-  const float c = p.scale * kLog2e;
-  const size_t part = ((size_t)(r * p.Hkv + kvh) * p.n_splits + split) * G;
+  const int n_tiles = (ctx + kBN - 1) / kBN;
+  const int t0 = __builtin_amdgcn_readfirstlane(t);
+  const int t1 = p.n_shares > 0 ? min(n_tiles, t0 + left) : n_tiles;
 
-  if (t0 >= t1) {  // nothing cached in this key range (whole workgroup): an empty partial state
-    if (tid < G) {
-      if (p.n_splits > 1) {
-        p.part_m[part + tid] = -INFINITY;
-        p.part_l[part + tid] = 0.f;
-      } else {
-        __bf16* dst = (__bf16*)p.out + ((size_t)r * p.Hq + kvh * G + tid) * kD;
-        for (int d = 0; d < kD; ++d) dst[d] = (__bf16)0.f;
-      }
-    }
+  if (t0 >= t1) {  // nothing cached
+    if (p.n_shares > 0) continue;   // (the merge kernel writes the zeros; a tile is left, so a request follows)
+    for (int i = tid; i < G * kD; i += kThreads)
+      ((__bf16*)p.out)[((size_t)r * p.Hq + kvh * G) * kD + i] = (__bf16)0.f;
     return;
   }
 
@@ -96,7 +162,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_attn_kernel(DecParams p) {
   const unsigned row_bytes = (unsigned)p.Hkv * kD * 2u;
   auto fetch_window = [&](int w, uint64_t& ak, uint64_t& av) __attribute__((always_inline)) {
     const int gi = (t0 + 16 * w) * 4 + lane;
-    uint64_t k = (uint64_t)p.zero_page, v = k;
+    uint64_t k = 0, v = 0;   // 0: no data (past the context, or a page id outside the pool), reads as zeros
     if (gi * SKV_BLOCK_TOKENS < ctx && gi < p.max_blocks) {
       const int page = p.page_table[(size_t)r * p.max_blocks + gi];
       if (page >= 0 && page < p.n_pages) {
@@ -118,7 +184,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_attn_kernel(DecParams p) {
 
   // ---- global -> registers -> LDS: 16 threads x 16 B per key row, four 16-key groups per tile.  Buffer
   // loads check each lane's offset against the bytes that exist from the group's base on, so the rows of
-  // the last page past ctx come back as zeros, whatever the pool holds there.
+  // the last page past ctx come back as zeros, whatever the pool holds there, and so does an absent page (no bytes exist).
   u32x4 kregA[4], vregA[4], kregB[4], vregB[4];  // two tiles in flight: kt+1 (landed or landing) and kt+2
   const int t_row = tid >> 4;
   const unsigned t_off = (unsigned)t_row * row_bytes + (unsigned)(tid & 15) * 16u;
@@ -128,8 +194,9 @@ __global__ __launch_bounds__(kThreads, 2) void decode_attn_kernel(DecParams p) {
       const int idx = (((kt - t0) & 15) << 2) + cc;
       int n_valid = ctx - (kt * kBN + cc * 16);  // clamped to 0..16 on the scalar unit
       asm("s_max_i32 %0, %1, 0\n\ts_min_i32 %0, %0, 16" : "=s"(n_valid) : "s"(n_valid) : "scc");
-      const int nrec = n_valid * (int)row_bytes;
-      const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc(lane_bcast(ak_w, idx), 0, nrec, 0x00020000);
+      void* const ka = lane_bcast(ak_w, idx);
+      const int nrec = ka ? n_valid * (int)row_bytes : 0;
+      const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc(ka, 0, nrec, 0x00020000);
       const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(lane_bcast(av_w, idx), 0, nrec, 0x00020000);
       // cache policy 2 = non-temporal: every byte is used once, so the stream should not displace what L2 holds
       kreg[cc] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rk, (int)t_off, 0, 2));
@@ -265,7 +332,8 @@ __global__ __launch_bounds__(kThreads, 2) void decode_attn_kernel(DecParams p) {
 #pragma unroll
         for (int j = 0; j < 8; ++j) acc[j] += wgt * src[j];
       }
-      if (p.n_splits > 1) {
+      if (t0 > 0 || t1 < n_tiles) {   // a piece of a request
+        const size_t part = ((size_t)(2 * share + (t0 == 0 ? 1 : 0)) * p.Hkv + kvh) * G;
         if ((tid & 15) == 0) {
           p.part_m[part + head] = ms;
           p.part_l[part + head] = L;
@@ -281,31 +349,76 @@ __global__ __launch_bounds__(kThreads, 2) void decode_attn_kernel(DecParams p) {
       }
     }
   }
+  left -= t1 - t0;
+  if (left <= 0) return;
+  __syncthreads();   // the merge area is read; the next request's tiles go there
+  }
 }
 
-// Merge of the key splits: one workgroup per (request, query head), one thread per d.
-__global__ __launch_bounds__(kD) void decode_merge_kernel(DecParams p) {
+// Merge of the pieces of the requests that were cut: one workgroup per (request, query head).  Bound by latency, so no load
+// waits for another: the weights of up to kThreads pieces are taken at once, one piece per thread, and the eight
+// half-wavefronts then sum every eighth piece's output, 16 bytes a lane, four pieces in flight each.
+__global__ __launch_bounds__(kThreads) void decode_merge_kernel(DecParams p) {
+  constexpr int kTeams = kThreads / 32;
+  __shared__ float wgt[kThreads], red_m[kWaves], red_l[kWaves];
+  __shared__ f32x4 red_o[kTeams][32];
   const int r = blockIdx.x / p.Hq, h = blockIdx.x % p.Hq;
   const int kvh = h / p.G, head = h % p.G;
-  const int d = threadIdx.x;
+  const int tid = threadIdx.x, team = tid >> 5, d4 = tid & 31;
   const float c = p.scale * kLog2e;
-  const size_t base = (size_t)(r * p.Hkv + kvh) * p.n_splits;
-  float ms = -INFINITY;
-  for (int s = 0; s < p.n_splits; ++s) ms = fmaxf(ms, p.part_m[(base + s) * p.G + head]);
-  float L = 0.f, acc = 0.f;
-  for (int s = 0; s < p.n_splits; ++s) {
-    const size_t i = (base + s) * p.G + head;
-    const float m = p.part_m[i];
-    if (m == -INFINITY) continue;  // empty split: its O was never written
-    const float wgt = __builtin_amdgcn_exp2f((m - ms) * c);
-    L += wgt * p.part_l[i];
-    acc += wgt * p.part_o[i * kD + d];
+  const int tile0 = p.first_tile[r], tile1 = p.first_tile[r + 1], total = p.first_tile[p.n_req];
+  u32x2* const dst = (u32x2*)((__bf16*)p.out + ((size_t)r * p.Hq + h) * kD + 4 * d4);
+  if (tile0 == tile1) {   // an empty context
+    if (tid < 32) *dst = u32x2{0u, 0u};
+    return;
   }
-  ((__bf16*)p.out)[((size_t)r * p.Hq + h) * kD + d] = (__bf16)(L > 0.f ? acc / L : 0.f);
-}
-
-__global__ void zero_fill_kernel(uint4* p, int n) {
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) p[i] = make_uint4(0u, 0u, 0u, 0u);
+  const int n = min(p.n_shares, total);
+  const int i0 = share_of(tile0, total, n), i1 = share_of(tile1 - 1, total, n);
+  const int pieces = i1 - i0 + 1;
+  if (pieces == 1) return;   // finished by that share
+  auto piece = [&](int j) { return ((size_t)(2 * (i0 + j) + (j == 0 ? 1 : 0)) * p.Hkv + kvh) * p.G + head; };
+  float m0 = -INFINITY, ms = -INFINITY;   // this thread's first piece (all of them, as a rule); the largest of all
+  for (int s = tid; s < pieces; s += kThreads) {
+    const float m = p.part_m[piece(s)];
+    if (s == tid) m0 = m;
+    ms = fmaxf(ms, m);
+  }
+  for (int o = 32; o >= 1; o >>= 1) ms = fmaxf(ms, __shfl_xor(ms, o));
+  if ((tid & 63) == 0) red_m[tid >> 6] = ms;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) ms = fmaxf(ms, red_m[w]);
+  float L = 0.f;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  for (int s0 = 0; s0 < pieces; s0 += kThreads) {
+    const int s = s0 + tid, n_here = min(kThreads, pieces - s0);
+    float w = 0.f;
+    if (s < pieces) {
+      const float m = s0 == 0 ? m0 : p.part_m[piece(s)];
+      if (m != -INFINITY) {   // otherwise every weight of the piece is 0
+        w = __builtin_amdgcn_exp2f((m - ms) * c);
+        L += w * p.part_l[piece(s)];
+      }
+    }
+    if (s0 > 0) __syncthreads();   // the weights before are done with
+    wgt[tid] = w;
+    __syncthreads();
+#pragma unroll 4
+    for (int i = team; i < n_here; i += kTeams) acc += wgt[i] * *(const f32x4*)(p.part_o + piece(s0 + i) * kD + 4 * d4);
+  }
+  for (int o = 32; o >= 1; o >>= 1) L += __shfl_xor(L, o);
+  if ((tid & 63) == 0) red_l[tid >> 6] = L;
+  red_o[team][d4] = acc;
+  __syncthreads();
+  if (tid < 32) {
+    L = (red_l[0] + red_l[1]) + (red_l[2] + red_l[3]);
+#pragma unroll
+    for (int g = 1; g < kTeams; ++g) acc += red_o[g][d4];
+    const float inv = L > 0.f ? 1.f / L : 0.f;
+    const bf16x2 y0 = __builtin_convertvector(f32x2{acc[0] * inv, acc[1] * inv}, bf16x2);
+    const bf16x2 y1 = __builtin_convertvector(f32x2{acc[2] * inv, acc[3] * inv}, bf16x2);
+    *dst = u32x2{__builtin_bit_cast(uint32_t, y0), __builtin_bit_cast(uint32_t, y1)};
+  }
 }
 
 int check_decode(const skv_attn_desc* d) {
@@ -316,20 +429,29 @@ int check_decode(const skv_attn_desc* d) {
   return SKV_OK;
 }
 
-// Key splits: about 4096 workgroups, i.e. eight rounds over the 512 workgroup slots of the chip (finer splits
-// shorten the tail when contexts differ in length; coarser ones amortise the start-up of a workgroup).
-void split_plan(const skv_attn_desc* d, int32_t n_req, int32_t max_blocks, int* n_splits, int* tiles_per_split) {
+// Shares per kv head: one workgroup per slot of the chip (two or four rounds: slower throughout, up to 2 x for few requests).
+// 0, a workgroup per request and no merge, where contexts are so short that cutting them costs more than it gains: one
+// request of 2 / 4 / 6 / 8 tiles takes 5.8 / 8.0 / 10.5 / 13.3 us whole and 9.9 us cut; 200 requests of one kv head of up to
+// 12 / 24 tiles 18.8 / 32.9 us whole, 25.8 / 31.3 cut; 256 requests of 8 kv heads of up to 4 / 12 / 24 tiles 39 / 88 / 172
+// whole, 52 / 94 / 170 cut.
+int shares_for(const skv_attn_desc* d, int32_t n_req, int32_t max_blocks) {
   const int64_t max_tiles = ((int64_t)max_blocks * SKV_BLOCK_TOKENS + kBN - 1) / kBN;
   const int64_t units = (int64_t)n_req * d->n_kv_heads;
-  int64_t want = units > 0 ? (4096 + units - 1) / units : 1;
-  if (want > max_tiles) want = max_tiles;
-  if (want < 1) want = 1;
-  const int64_t tps = max_tiles > 0 ? (max_tiles + want - 1) / want : 1;
-  *tiles_per_split = (int)(tps < 1 ? 1 : tps);
-  *n_splits = (int)(max_tiles > 0 ? (max_tiles + *tiles_per_split - 1) / *tiles_per_split : 1);
+  if (max_tiles <= (units < kSlots / 4 ? 5 : 16) || n_req * max_tiles > 0x7fffffff) return 0;
+  return (int)std::min<int64_t>(std::max(kSlots / d->n_kv_heads, 1), n_req * max_tiles);
 }
-
-size_t zero_bytes(const skv_attn_desc* d) { return skv_align256((size_t)SKV_BLOCK_TOKENS * d->n_kv_heads * kD * 2); }
+struct Workspace {
+  size_t part_m, part_l, part_o, bytes;
+};
+Workspace workspace_for(const skv_attn_desc* d, int32_t n_req, int32_t max_blocks) {
+  const size_t pieces = (size_t)2 * shares_for(d, n_req, max_blocks) * d->n_q_heads;
+  Workspace w;
+  w.part_m = skv_align256(((size_t)n_req + 1) * sizeof(int32_t));
+  w.part_l = w.part_m + skv_align256(pieces * sizeof(float));
+  w.part_o = w.part_l + skv_align256(pieces * sizeof(float));
+  w.bytes = w.part_o + pieces * kD * sizeof(float);
+  return w;
+}
 
 }  // namespace
 
@@ -338,11 +460,7 @@ extern "C" int skv_decode_attn_workspace_size(const skv_attn_desc* desc, int32_t
   int rc = check_decode(desc);
   if (rc) return rc;
   if (n_req < 0 || max_blocks < 0 || !bytes) return SKV_EINVAL;
-  int ns, tps;
-  split_plan(desc, n_req, max_blocks, &ns, &tps);
-  const size_t G = (size_t)(desc->n_q_heads / desc->n_kv_heads);
-  const size_t states = (size_t)n_req * desc->n_kv_heads * ns * G;
-  *bytes = zero_bytes(desc) + 2 * skv_align256(states * sizeof(float)) + skv_align256(states * kD * sizeof(float));
+  *bytes = workspace_for(desc, n_req, max_blocks).bytes;
   return SKV_OK;
 }
 
@@ -361,29 +479,24 @@ extern "C" int skv_decode_attn(const skv_attn_desc* desc, int32_t n_req, const v
   size_t need = 0;
   skv_decode_attn_workspace_size(desc, n_req, max_blocks, &need);
   if (!d_workspace || workspace_bytes < need) return SKV_ENOMEM;
-  int ns, tps;
-  split_plan(desc, n_req, max_blocks, &ns, &tps);
-  const int64_t grid = (int64_t)n_req * desc->n_kv_heads * ns;
+  const int shares = shares_for(desc, n_req, max_blocks);
+  const int64_t grid = (int64_t)(shares ? shares : n_req) * desc->n_kv_heads;
   if (grid > 0x7fffffff || (int64_t)n_req * desc->n_q_heads > 0x7fffffff) return SKV_ERANGE;
   hipStream_t st = (hipStream_t)stream;
-  const size_t G = (size_t)(desc->n_q_heads / desc->n_kv_heads);
-  const size_t states = (size_t)n_req * desc->n_kv_heads * ns * G;
   char* ws = (char*)d_workspace;
+  const Workspace w = workspace_for(desc, n_req, max_blocks);
   DecParams p;
   p.q = d_q; p.kpool = d_kpool; p.vpool = d_vpool; p.out = d_out;
   p.ctx_len = d_ctx_len; p.page_table = d_page_table;
-  p.zero_page = ws;
-  p.part_m = (float*)(ws + zero_bytes(desc));
-  p.part_l = (float*)((char*)p.part_m + skv_align256(states * sizeof(float)));
-  p.part_o = (float*)((char*)p.part_l + skv_align256(states * sizeof(float)));
+  p.first_tile = (int32_t*)ws;
+  p.part_m = (float*)(ws + w.part_m); p.part_l = (float*)(ws + w.part_l); p.part_o = (float*)(ws + w.part_o);
   p.n_req = n_req; p.max_blocks = max_blocks; p.n_pages = n_pages;
-  p.Hq = desc->n_q_heads; p.Hkv = desc->n_kv_heads; p.G = (int)G;
-  p.n_splits = ns; p.tiles_per_split = tps; p.scale = skv_softmax_scale(desc);
-  zero_fill_kernel<<<8, 256, 0, st>>>((uint4*)ws, (int)(zero_bytes(desc) / 16));
+  p.Hq = desc->n_q_heads; p.Hkv = desc->n_kv_heads; p.G = desc->n_q_heads / desc->n_kv_heads;
+  p.n_shares = shares; p.scale = skv_softmax_scale(desc);
   decode_attn_kernel<<<(int)grid, kThreads, 0, st>>>(p);
   SKV_HIP(hipGetLastError());
-  if (ns > 1) {
-    decode_merge_kernel<<<n_req * desc->n_q_heads, kD, 0, st>>>(p);
+  if (shares) {
+    decode_merge_kernel<<<n_req * desc->n_q_heads, kThreads, 0, st>>>(p);
     SKV_HIP(hipGetLastError());
   }
   return SKV_OK;

@@ -1,0 +1,32 @@
+"""Decode attention where the batch's key tiles are dealt to workgroups in equal shares: requests cut by a share's edge, whole
+inside a share, over many shares, empty; more requests than threads; fewer tiles than shares.  Tolerance of the decode tests."""
+import numpy as np
+import pytest
+
+from paper_2508_08438_amd import inputs
+from test_gpu_decode import check
+
+pytestmark = pytest.mark.gpu
+
+G = np.random.default_rng(8)
+# contexts, query / kv heads (64 shares of 8 kv heads, 512 of one, 170 of three)
+CASES = [
+    ([64 * 64], 32, 8), ([64 * 128] * 2, 8, 8), ([64 * 32] * 16, 8, 8),            # edges of shares = edges of requests
+    ([0, 0, 64 * 65 + 1, 0, 1, 0], 32, 8), ([30, 0, 2000, 63, 64, 65], 16, 1),     # fewer tiles than shares
+    ([20000, 1, 1, 1, 15, 0, 9000], 24, 3), ([1100] + [16] * 300 + [0] * 40 + [1090], 8, 8),
+    (G.integers(0, 1300, 700), 4, 1), ([5000] * 3, 6, 6),
+]
+
+
+@pytest.mark.parametrize("case", range(len(CASES)))
+def test_shares(case):
+    ctx, hq, hkv = CASES[case]
+    dw = inputs.decode_workload(seed=40 + case, ctx=ctx, hard=True, attn=inputs.AttnShape(hq, hkv, 128, "bf16"))
+    n = dw.n_req
+    check(dw, f"shares {case}", reqs=list(range(n)) if n < 10 else sorted({0, 1, n // 2, n - 2, n - 1, *range(0, n, 61)}))
+
+
+@pytest.mark.parametrize("n_req,blocks,hkv", [(1, 20, 8), (1, 21, 8), (16, 64, 8), (16, 65, 8)])
+def test_both_sides_of_the_rule(n_req, blocks, hkv):
+    dw = inputs.decode_workload(seed=n_req + blocks, ctx=[16 * blocks - 3] * n_req, hard=True)
+    check(dw, f"{n_req} x {blocks} blocks")
