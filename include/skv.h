@@ -318,8 +318,9 @@ int skv_mfma_rate(const void* d_operands, size_t operand_bytes, int32_t iters, i
                   size_t sink_bytes, double* flops, void* stream);
 
 /* Bytes of device workspace skv_prefill_attn needs for n_req requests and at most
- * total_q_rows uncached tokens in the batch (the work list of the bf16 kernel and one page of zeros that
- * stands in for key groups without data); the call overwrites it. */
+ * total_q_rows uncached tokens in the batch (the work list of the bf16 kernel, one page of zeros that
+ * stands in for key groups without data and, for small batches, the partial states of work items split along
+ * the keys); the call overwrites it. */
 int skv_prefill_attn_workspace_size(const skv_attn_desc* desc, int32_t n_req, int64_t total_q_rows,
                                     size_t* bytes);
 
@@ -336,7 +337,7 @@ int skv_prefill_attn_workspace_size(const skv_attn_desc* desc, int32_t n_req, in
  * [0, n_pages) are read as zeros.  bf16 computes QK^T and PV on the matrix cores with fp32
  * accumulation and fp32 softmax; fp32 computes in fp32 throughout.
  * Errors: SKV_EINVAL for null pointers or unsupported shapes, SKV_ENOMEM if the workspace is
- * smaller than skv_prefill_attn_workspace_size. */
+ * too small for the work list; with less than skv_prefill_attn_workspace_size bytes nothing is split. */
 int skv_prefill_attn(const skv_attn_desc* desc, int32_t n_req, const void* d_q, const void* d_knew,
                      const void* d_vnew, const int32_t* d_q_off, int64_t total_q_rows,
                      const void* d_kpool, const void* d_vpool, int32_t n_pages,
@@ -345,10 +346,11 @@ int skv_prefill_attn(const skv_attn_desc* desc, int32_t n_req, const void* d_q, 
 
 /* skv_prefill_attn for callers that cannot allocate device memory or hand over a workspace: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, results and errors as
- * skv_prefill_attn without the workspace: the work list and the page of zeros live in a device array built
+ * skv_prefill_attn without the workspace (nothing is split along the keys: small batches differ from it in rounding):
+ * the work list and the page of zeros live in a device array built
  * into the library (SKV_STATIC_SCRATCH_BYTES per GPU, held until the process ends), whose address on the
  * current device is looked up on the first call there.  The call allocates and frees nothing.
- * SKV_ERANGE when skv_prefill_attn_workspace_size for (n_req, total_q_rows) exceeds SKV_STATIC_SCRATCH_BYTES
+ * SKV_ERANGE when the work list for (n_req, total_q_rows) exceeds SKV_STATIC_SCRATCH_BYTES
  * (bf16 with 4 query heads per kv head: about 8 million uncached tokens per batch).
  * All calls on one GPU share the array, whichever stream they use: calls that overlap on a GPU race; calls
  * on one stream, or ordered by events, are safe (each call rewrites everything it reads). */

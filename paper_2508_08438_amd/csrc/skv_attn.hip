@@ -74,9 +74,11 @@ struct AttnParams {
 // ---- work list ---------------------------------------------------------------------------------
 // One workgroup.  items[] lists one 32-byte record per (request, q tile) pair -- {request, first suffix row of
 // the tile, first row of the request in Q, its suffix length S, its reused length L, end row of the tile, first key tile,
-// part} -- so that a workgroup of the attention kernel learns everything about its piece of work from one load.  A request's
-// heaviest (last) tile first.  The q tiles of a request are cut so that L + (first row of a tile) is a multiple of the
-// 64-key tile: the first tile is short when L is not, and every later tile ends exactly where a key tile ends, so
+// part} -- so that a workgroup of the attention kernel learns everything about its piece of work from one load.  Requests
+// with the most keys first, and of a request its heaviest (last) tile: what runs last is short, so the chip empties evenly,
+// and the tiles of a request stay together, so they find its keys in L2.  The q tiles of a request are cut so that
+// L + (first row of a tile) is a multiple of the 64-key tile (or of the q tile where that is shorter): the first tile is
+// short when L is not, and every later tile ends where a key tile ends, so
 // no workgroup streams a key tile for the sake of a few keys of round-up -- unless the short first tile makes the
 // request one tile longer than cutting from row 0 would and the reused prefix is long (L > S / 2): a tile more costs
 // a pass over about L + S / 2 keys, the round-up one more 64-key iteration in each of the S / 64 tiles.
@@ -87,6 +89,12 @@ struct AttnParams {
 // and attn_merge_kernel combines them.  The part length c is the smallest for which all parts run in one round, or in
 // two, of one workgroup per compute unit; a workgroup costs about kStartTiles key tiles before and after its loop, the
 // merge about as much again, and unless the split wins by that the items stay whole.
+//
+// The kernel is a chain of dependent steps on one compute unit, so every step is short: requests are ordered by a histogram
+// of their lengths, scans go through registers, and the search for c tries sixteen lengths at a time, one per wavefront
+// (one request of 257 rows: 10 us, 18 with one length at a time; lists without a split 5 us).  Order by length and
+// 32-row tiles: 32 requests of 264 rows behind 16..32 k keys, 64/8 heads: 7.32 -> 6.83 ms; 16 requests of 97..994 rows
+// behind up to 8 k, 32/8 heads (order only): 525 -> 512 us.
 constexpr int kItemInts = 8;
 constexpr int kCus = 256;             // compute units = workgroups that run at once
 constexpr int kMaxSlots = 2 * kCus;   // parts of a split batch, over all kv heads and head groups
@@ -112,7 +120,8 @@ __device__ inline Cut cut_of(int r, const int32_t* q_off, const int32_t* matched
   c.qb = q_off[r];
   c.S = q_off[r + 1] - c.qb;
   c.L = matched_len[r] > 0 ? matched_len[r] & ~(SKV_BLOCK_TOKENS - 1) : 0;   // whole blocks only
-  c.head_rows = min(c.S, (kBN - c.L % kBN) % kBN);                           // rows of the short first tile (0: none)
+  const int align = min(kBN, pos_per_wg);
+  c.head_rows = min(c.S, (align - c.L % align) % align);                     // rows of the short first tile (0: none)
   c.nt = c.S > 0 ? (c.head_rows > 0 ? 1 : 0) + (c.S - c.head_rows + pos_per_wg - 1) / pos_per_wg : 0;
   const int nt_plain = (c.S + pos_per_wg - 1) / pos_per_wg;
   if (nt_plain < c.nt && 2 * c.L > c.S) {   // the short first tile would cost a whole extra tile: cut from row 0 instead
@@ -124,131 +133,218 @@ __device__ inline Cut cut_of(int r, const int32_t* q_off, const int32_t* matched
 // Parts an item of n key tiles is split into at part length c: every part but the first starts at a key that all of the
 // item's rows see (key tile `last` or before), so that each part has a finite row maximum from its first keys on.
 __device__ inline int parts_of(int n, int last, int c) {
-  int parts = (n + c - 1) / c;
-  while (parts > 1 && (parts - 1) * ((n + parts - 1) / parts) > last) --parts;
+  int parts = (int)((unsigned)(n + c - 1) / (unsigned)c);
+  while (parts > 1 && (parts - 1) * (int)((unsigned)(n + parts - 1) / (unsigned)parts) > last) --parts;
   return parts;
 }
 
-constexpr int kSchedThreads = 1024;
+constexpr int kSchedThreads = 1024, kSchedWaves = kSchedThreads / 64;
+constexpr int kBuckets = 128;
+
+// inclusive scan over the workgroup; `total` of all threads (red: one place per wavefront; two barriers)
+__device__ inline int block_scan(int v, int* red, int& total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int o = 1; o < 64; o <<= 1) {
+    const int x = __shfl_up(v, o);
+    if (lane >= o) v += x;
+  }
+  if (lane == 63) red[wave] = v;
+  __syncthreads();
+  int x = lane < kSchedWaves ? red[lane] : 0, all = x;
+  if (lane >= wave) x = 0;
+  for (int o = kSchedWaves / 2; o >= 1; o >>= 1) {
+    x += __shfl_xor(x, o);
+    all += __shfl_xor(all, o);
+  }
+  total = __shfl(all, 0);
+  v += __shfl(x, 0);
+  __syncthreads();
+  return v;
+}
+__device__ inline int wave_max(int v) {
+  for (int o = 32; o >= 1; o >>= 1) v = max(v, __shfl_xor(v, o));
+  return v;
+}
+__device__ inline int wave_sum(int v) {
+  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
+  return v;
+}
+// first place whose scan value exceeds x (scan[n - 1] does)
+__device__ inline int place_of(const int* scan, int n, int x) {
+  int lo = 0, hi = n - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi) >> 1;
+    if (scan[mid] > x) hi = mid; else lo = mid + 1;
+  }
+  return lo;
+}
+
 __global__ __launch_bounds__(kSchedThreads) void attn_schedule_kernel(
     int n_req, const int32_t* __restrict__ q_off, const int32_t* __restrict__ matched_len, int pos_per_wg, int max_items,
     int units /* workgroups per item */, int32_t* __restrict__ n_items /* [0] items, [1] split items */,
     int32_t* __restrict__ items, int32_t* __restrict__ splits /* null: never split */, uint4* __restrict__ zero_page,
     int zero_vec) {
-  __shared__ int32_t sh[kSchedThreads];
-  __shared__ int32_t carry;
-  for (int i = threadIdx.x; i < zero_vec; i += kSchedThreads) zero_page[i] = make_uint4(0u, 0u, 0u, 0u);
-  if (threadIdx.x == 0) carry = 0;
-  __syncthreads();
+  __shared__ int scan[kSchedThreads], req_at[kSchedThreads], red[kSchedWaves], bucket[kBuckets];
+  __shared__ int4 item_a[kCus], item_b[kCus];   // the first records, for the split
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  for (int i = tid; i < zero_vec; i += kSchedThreads) zero_page[i] = make_uint4(0u, 0u, 0u, 0u);
+  int listed = 0;
   for (int base = 0; base < n_req; base += kSchedThreads) {
-    const int r = base + threadIdx.x;
-    sh[threadIdx.x] = r < n_req ? cut_of(r, q_off, matched_len, pos_per_wg).nt : 0;
-    __syncthreads();
-    for (int o = 1; o < kSchedThreads; o <<= 1) {
-      int add = threadIdx.x >= o ? sh[threadIdx.x - o] : 0;
-      __syncthreads();
-      sh[threadIdx.x] += add;
-      __syncthreads();
+    const int r = base + tid, n_here = min(kSchedThreads, n_req - base);
+    int nt = 0, keys = 0;
+    if (r < n_req) {
+      const Cut c = cut_of(r, q_off, matched_len, pos_per_wg);
+      nt = c.nt;
+      keys = nt > 0 ? c.L + c.S : 0;
     }
-    // the chunk's items, one per thread and turn: the request is found in the scan
-    const int first = carry, total = sh[kSchedThreads - 1];
-    for (int it = threadIdx.x; it < total && first + it < max_items; it += kSchedThreads) {
-      int lo = 0, hi = kSchedThreads - 1;   // smallest lo with sh[lo] > it
-      while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (sh[mid] > it) hi = mid; else lo = mid + 1;
+    // place in the order of falling length, to 1 / kBuckets of the longest
+    int place = tid;
+    if (n_here > 1) {
+      const int m = wave_max(keys);
+      if (lane == 0) red[wave] = m;
+      if (tid < kBuckets) bucket[tid] = 0;
+      __syncthreads();
+      const int longest = wave_max(lane < kSchedWaves ? red[lane] : 0);
+      int b = 0, rank = 0;
+      if (r < n_req) {
+        b = kBuckets - 1 - (int)((float)keys * ((kBuckets - 0.5f) / (float)max(longest, 1)));
+        b = max(0, min(kBuckets - 1, b));
+        rank = atomicAdd(&bucket[b], 1);
       }
-      const Cut c = cut_of(base + lo, q_off, matched_len, pos_per_wg);
-      int row0, row1;
-      c.tile(sh[lo] - 1 - it, pos_per_wg, row0, row1);   // the request's last tile first
-      int4* rec = (int4*)(items + (size_t)kItemInts * (first + it));
-      rec[0] = make_int4(base + lo, row0, c.qb, c.S);
-      rec[1] = make_int4(c.L, row1, 0, 0);
+      __syncthreads();
+      if (wave == 0) {   // exclusive scan, two buckets per lane
+        const int c0 = bucket[2 * lane], c1 = bucket[2 * lane + 1];
+        int x = c0 + c1;
+        for (int o = 1; o < 64; o <<= 1) {
+          const int y = __shfl_up(x, o);
+          if (lane >= o) x += y;
+        }
+        bucket[2 * lane] = x - c0 - c1;
+        bucket[2 * lane + 1] = x - c1;
+      }
+      __syncthreads();
+      place = bucket[b] + rank;
+    }
+    if (r < n_req) {
+      scan[place] = nt;
+      req_at[place] = r;
     }
     __syncthreads();
-    if (threadIdx.x == 0) carry += total;
+    int total;
+    const int upto = block_scan(tid < n_here ? scan[tid] : 0, red, total);
+    scan[tid] = upto;
+    __syncthreads();
+    // the chunk's items, one per thread and turn: the request is found in the scan
+    for (int it = tid; it < total && listed + it < max_items; it += kSchedThreads) {
+      const int at = place_of(scan, n_here, it), rr = req_at[at];
+      const Cut c = cut_of(rr, q_off, matched_len, pos_per_wg);
+      int row0, row1;
+      c.tile(scan[at] - 1 - it, pos_per_wg, row0, row1);   // the request's last tile first
+      const int4 a = make_int4(rr, row0, c.qb, c.S), b = make_int4(c.L, row1, 0, 0);
+      int4* rec = (int4*)(items + (size_t)kItemInts * (listed + it));
+      rec[0] = a;
+      rec[1] = b;
+      if (listed + it < kCus) {
+        item_a[listed + it] = a;
+        item_b[listed + it] = b;
+      }
+    }
+    listed += total;
     __syncthreads();
   }
-  const int n = min(carry, max_items);
+  const int n = min(listed, max_items);
   int n_out = n, n_split = 0;
-  if (splits && n > 0 && n <= kCus && n * units <= kMaxSlots) {   // few items: split their keys?  One item per thread.
-    __syncthreads();   // the records of the last chunk are read back below
-    const int i = threadIdx.x;
-    int4 a = {0, 0, 0, 0}, b = {0, 0, 0, 0};
-    int n_kt = 0, last = 0;
-    if (i < n) {
-      a = ((const int4*)(items + (size_t)kItemInts * i))[0];
-      b = ((const int4*)(items + (size_t)kItemInts * i))[1];
-      n_kt = (b.x + b.y + kBN - 1) / kBN;
-      last = (b.x + a.y) / kBN;
+  if (splits && n > 0 && n <= kCus && n * units <= kMaxSlots) {   // few items: split their keys?
+    // every wavefront holds all items, four per lane
+    int n_kt[kCus / 64], last[kCus / 64], longest = 0, sum = 0;
+#pragma unroll
+    for (int k = 0; k < kCus / 64; ++k) {
+      const int i = lane + 64 * k;
+      n_kt[k] = last[k] = 0;
+      if (i < n) {
+        const int4 a = item_a[i], b = item_b[i];
+        n_kt[k] = (b.x + b.y + kBN - 1) / kBN;
+        last[k] = (b.x + a.y) / kBN;
+      }
+      longest = max(longest, n_kt[k]);
+      sum += n_kt[k];
     }
-    __shared__ int red[kCus / 64];
-    auto block_sum = [&](int v) {   // over the first kCus threads
-      for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
-      if (i < kCus && (i & 63) == 0) red[i >> 6] = v;
+    longest = wave_max(longest);
+    sum = wave_sum(sum);
+    // smallest part length for which all parts have room in one round (wavefronts 0 .. 7) or two (8 .. 15): eight lengths
+    // between the last that did not fit and the first that did, until they meet
+    const int room1 = kCus / units, room2 = 2 * kCus / units, half = wave >> 3;
+    const int room = half ? room2 : room1;
+    int lo1 = 1, hi1 = longest, lo2 = 1, hi2 = longest;
+    if (room1 >= n) lo1 = max(1, min(longest, (sum + room1 - 1) / room1)); else lo1 = longest;
+    if (room2 >= n) lo2 = max(1, min(longest, (sum + room2 - 1) / room2)); else lo2 = longest;
+    int turn = 0;
+    __shared__ int fits[2][kSchedWaves];
+    while (lo1 < hi1 || lo2 < hi2) {
+      const int lo = half ? lo2 : lo1, hi = half ? hi2 : hi1;
+      const int c = lo + (int)(((long long)(hi - lo) * (wave & 7)) >> 3);   // wavefront 0 of the eight tries lo itself
+      int p = 0;
+#pragma unroll
+      for (int k = 0; k < kCus / 64; ++k)
+        if (lane + 64 * k < n) p += parts_of(n_kt[k], last[k], c);
+      p = wave_sum(p);
+      if (lane == 0) fits[turn & 1][wave] = p <= room;
       __syncthreads();
-      int s = 0;
-      for (int w = 0; w < kCus / 64; ++w) s += red[w];
-      __syncthreads();
-      return s;
-    };
-    int longest = n_kt;
-    for (int o = 32; o >= 1; o >>= 1) longest = max(longest, __shfl_xor(longest, o));
-    if (i < kCus && (i & 63) == 0) red[i >> 6] = longest;
-    __syncthreads();
-    longest = 0;
-    for (int w = 0; w < kCus / 64; ++w) longest = max(longest, red[w]);
-    __syncthreads();
+      const uint64_t ok = __ballot(lane < kSchedWaves && fits[turn & 1][lane & (kSchedWaves - 1)]);
+      auto narrow = [&](unsigned f, int& l, int& h) {   // f: bit k set where the k-th length fits
+        if (l >= h) return;
+        const int l0 = l, d = h - l, k = f ? __builtin_ctz(f) : 8;
+        if (k < 8) h = l0 + (int)(((long long)d * k) >> 3);
+        if (k > 0) l = l0 + (int)(((long long)d * (k - 1)) >> 3) + 1;
+      };
+      narrow((unsigned)ok & 255u, lo1, hi1);
+      narrow((unsigned)(ok >> 8) & 255u, lo2, hi2);
+      ++turn;
+    }
     const int rounds_whole = (n * units + kCus - 1) / kCus;
-    const int share = (block_sum(n_kt) * units + kCus - 1) / kCus;   // key tiles per compute unit
+    const int share = (sum * units + kCus - 1) / kCus;   // key tiles per compute unit
     const int whole = rounds_whole == 1 ? longest : max(longest, share + longest / 2);
     int best_c = longest, best_cost = rounds_whole * kStartTiles + whole - kStartTiles;   // (the split also merges)
-    for (int rounds = 1; rounds <= 2; ++rounds) {
-      const int room = rounds * kCus / units;
-      if (room < n) continue;
-      int lo = 1, hi = longest;   // smallest part length for which all parts have room
-      while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (block_sum(i < n ? parts_of(n_kt, last, mid) : 0) <= room) hi = mid; else lo = mid + 1;
-      }
-      if (rounds * (kStartTiles + lo) < best_cost) {
-        best_cost = rounds * (kStartTiles + lo);
-        best_c = lo;
-      }
+    if (room1 >= n && kStartTiles + hi1 < best_cost) {
+      best_cost = kStartTiles + hi1;
+      best_c = hi1;
     }
-    const int parts = i < n ? parts_of(n_kt, last, best_c) : 0;
-    const int total = block_sum(parts);
-    if (total > n && total <= max_items) {
-      // exclusive scans of the parts (place in the list), of the parts of split items (slot) and of the split items
-      sh[i] = parts | (parts > 1 ? parts << 10 | 1 << 20 : 0);
+    if (room2 >= n && 2 * (kStartTiles + hi2) < best_cost) best_c = hi2;
+    // scans of the parts (place in the list) and, packed, of the parts of split items (slot) and of the split items
+    int4 a = {0, 0, 0, 0}, b = {0, 0, 0, 0};
+    int parts = 0;
+    if (tid < n) {
+      a = item_a[tid];
+      b = item_b[tid];
+      parts = parts_of((b.x + b.y + kBN - 1) / kBN, (b.x + a.y) / kBN, best_c);
+    }
+    int total;
+    const int mine = parts | (parts > 1 ? parts << 10 | 1 << 20 : 0);
+    const int upto = block_scan(mine, red, total);
+    const int n_parts = total & 1023;
+    if (n_parts > n && n_parts <= max_items) {
+      scan[tid] = upto & 1023;
+      const int before = upto - mine, slot = (before >> 10) & 1023;
+      if (parts > 1) {
+        int4* sp = (int4*)(splits + kSplitInts * (before >> 20));
+        sp[0] = make_int4(a.y, b.y, a.z, slot);
+        sp[1] = make_int4(parts, 0, 0, 0);
+      }
+      if (tid < n) item_b[tid] = make_int4(b.x, b.y, parts, slot);
       __syncthreads();
-      for (int o = 1; o < kCus; o <<= 1) {
-        const int add = i >= o && i < kCus ? sh[i - o] : 0;
-        __syncthreads();
-        if (i < kCus) sh[i] += add;
-        __syncthreads();
+      for (int it = tid; it < n_parts; it += kSchedThreads) {
+        const int at = place_of(scan, n, it);
+        const int4 ia = item_a[at], ib = item_b[at];
+        const int j = it - (at ? scan[at - 1] : 0), kt = (ib.x + ib.y + kBN - 1) / kBN, len = (kt + ib.z - 1) / ib.z;
+        int4* rec = (int4*)(items + (size_t)kItemInts * it);
+        rec[0] = ia;
+        rec[1] = make_int4(ib.x, ib.y, j * len, ib.z > 1 ? (ib.w + j + 1) << kPartBits | min(len, kt - j * len) : 0);
       }
-      if (i < n) {
-        const int before = i ? sh[i - 1] : 0;
-        const int at = before & 1023, slot = (before >> 10) & 1023, si = before >> 20;
-        const int len = (n_kt + parts - 1) / parts;
-        for (int j = 0; j < parts; ++j) {
-          const int kt0 = j * len, n_part = min(len, n_kt - kt0);
-          int4* rec = (int4*)(items + (size_t)kItemInts * (at + j));
-          rec[0] = a;
-          rec[1] = make_int4(b.x, b.y, kt0, parts > 1 ? (slot + j + 1) << kPartBits | n_part : 0);
-        }
-        if (parts > 1) {
-          int4* sp = (int4*)(splits + kSplitInts * si);
-          sp[0] = make_int4(a.y, b.y, a.z, slot);
-          sp[1] = make_int4(parts, 0, 0, 0);
-        }
-      }
-      n_out = total;
-      n_split = sh[n - 1] >> 20;
+      n_out = n_parts;
+      n_split = total >> 20;
     }
   }
-  if (threadIdx.x == 0) {
+  if (tid == 0) {
     n_items[0] = n_out;
     n_items[1] = n_split;
   }
@@ -297,6 +393,24 @@ __device__ __forceinline__ void lds_wait(int n, bf16x8& a, bf16x8& b, bf16x8& c,
   asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(a), "+v"(b), "+v"(c), "+v"(d) : "i"(n));
 }
 
+// Workgroup b runs on XCD b % 8: all work of one kv head stays on one XCD where the heads allow it, so its K/V tiles are
+// re-read from that XCD's L2, and the merge finds the parts there.
+__device__ __forceinline__ void unit_of_block(int Hkv, int n_hg, int& item, int& kvh, int& hg) {
+  const int b = blockIdx.x;
+  int rest;
+  if (Hkv % 8 == 0) {
+    const int per = Hkv / 8;
+    const int xcd = b & 7, slot = b >> 3;
+    kvh = xcd + 8 * (slot % per);
+    rest = slot / per;
+  } else {
+    kvh = b % Hkv;
+    rest = b / Hkv;
+  }
+  hg = rest % n_hg;
+  item = rest / n_hg;
+}
+
 __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
   __shared__ __attribute__((aligned(16))) __bf16 smem[kKStages * kTile + kVStages * kTile +
                                                       kWaves * kStageRows * kD];
@@ -317,23 +431,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
   const int G = p.Hq / p.Hkv;
   const int n_hg = G / p.heads_per_wg;               // head groups per kv head
   int item, kvh, hg;
-  {
-    const int b = blockIdx.x;
-    if (p.Hkv % 8 == 0) {
-      // all work of one kv head stays on one XCD, so its K/V tiles are re-read from that XCD's L2
-      const int per = p.Hkv / 8;
-      const int xcd = b & 7, slot = b >> 3;
-      kvh = xcd + 8 * (slot % per);
-      const int rest = slot / per;
-      hg = rest % n_hg;
-      item = rest / n_hg;
-    } else {
-      kvh = b % p.Hkv;
-      const int rest = b / p.Hkv;
-      hg = rest % n_hg;
-      item = rest / n_hg;
-    }
-  }
+  unit_of_block(p.Hkv, n_hg, item, kvh, hg);
   // the record is read together with the item count (the grid bound keeps the index inside the list)
   const int4 rec0 = ((const int4*)(p.items + (size_t)kItemInts * item))[0];
   const int4 rec1 = ((const int4*)(p.items + (size_t)kItemInts * item))[1];
@@ -741,7 +839,9 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
     // mask(), and the row maximum behind it would read score registers the matrix core has not written yet)
     asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 3" : "+v"(s[0]));
     mask(s[0], 0);
-    m_ref = row_max(s[0]) * c;   // finite: key 0 is visible to every query
+    // key 0 is visible to every query; finite also where its score and those of the other first keys are -infinity (the
+    // reference then moves with the first score above it, and a part without any leaves nothing)
+    m_ref = fmaxf(row_max(s[0]) * c, -3.0e38f);
   }
 
   // ---- main loop.  Iteration kt (two half-steps) reads K(kt), K(kt + 1), V(kt - 1), V(kt).  It starts behind the
@@ -798,6 +898,8 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
     const int slot = (part >> kPartBits) - 1;
     const int unit = kvh * n_hg + hg;
     f32x4* dst = (f32x4*)(p.partials + ((size_t)slot * p.Hkv * n_hg + unit) * kSlotFloats + (size_t)wave * (64 * 66)) + lane;
+    const float l_all = l_run + swap_halves(l_run);
+    if (pos0 + l32 >= row1) return;   // not a row of the tile: never read
 #pragma unroll
     for (int a = 0; a < 4; ++a)
 #pragma unroll
@@ -805,7 +907,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
         dst[(a * 4 + i4) * 64] = f32x4{o[a][i4 * 4], o[a][i4 * 4 + 1], o[a][i4 * 4 + 2], o[a][i4 * 4 + 3]};
     float* ml = (float*)(dst - lane + 16 * 64) + lane;
     ml[0] = m_ref;
-    ml[64] = l_run + swap_halves(l_run);
+    ml[64] = l_all;
     return;
   }
 
@@ -847,47 +949,70 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
 }
 
 // ---- merge of the parts of split items -----------------------------------------------------------
-// One workgroup per (split item, kv head and head group, wavefront of the attention kernel); its wavefront a combines
-// d = 32 a .. 32 a + 31 of that wavefront's 32 rows, each lane what the same lane of every part wrote: coalesced 1 KB reads.
-// Bound by those reads (16.9 KB per part).
-__global__ __launch_bounds__(256) void attn_merge_kernel(AttnParams p) {
+// One workgroup per (split item, kv head and head group, wavefront of the attention kernel); its wavefront q combines
+// d = 16 q .. 16 q + 15 of that wavefront's 32 rows, each lane what the same lane of every part wrote: coalesced 1 KB reads.
+// Bound by latency: eight parts' states travel together and are folded into a running maximum, so the usual item takes one or
+// two trips to memory (references first and outputs after them, four parts at a time: 10.7 us for 10 parts of 3 items,
+// now 6.5).
+constexpr int kMergeThreads = 512, kMergeParts = 8;
+__global__ __launch_bounds__(kMergeThreads) void attn_merge_kernel(AttnParams p) {
   const int n_hg = p.Hq / p.Hkv / p.heads_per_wg, units = p.Hkv * n_hg;
-  const int wave = blockIdx.x % kWaves, unit = blockIdx.x / kWaves % units, si = blockIdx.x / kWaves / units;
+  int rest, kvh, hg;
+  unit_of_block(p.Hkv, n_hg, rest, kvh, hg);
+  const int wave = rest % kWaves, unit = kvh * n_hg + hg, si = rest / kWaves;
   if (si >= p.n_items[1]) return;
   const int4 a = ((const int4*)(p.splits + kSplitInts * si))[0];
   const int parts = p.splits[kSplitInts * si + 4];
   const int row0 = a.x, row1 = a.y, qbase = a.z, slot = a.w;
   const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
-  const int pos0 = row0 + (wave / p.heads_per_wg) * kRowsPerWave;
-  if (pos0 >= row1) return;
+  const int row = row0 + (wave / p.heads_per_wg) * kRowsPerWave + (lane & 31);
+  if (row >= row1) return;
   const size_t stride = (size_t)units * kSlotFloats;   // from one part to the next
   const float* src = p.partials + ((size_t)slot * units + unit) * kSlotFloats + (size_t)wave * (64 * 66);
-  float m = -INFINITY;
-  for (int j = 0; j < parts; ++j) m = fmaxf(m, src[j * stride + 64 * 64 + lane]);
-  float l = 0.f;
-  f32x4 acc[4] = {};
-#pragma unroll 4
-  for (int j = 0; j < parts; ++j) {
-    const float* s = src + j * stride;
-    const float f = __builtin_amdgcn_exp2f(s[64 * 64 + lane] - m);
-    l += f * s[64 * 65 + lane];
+  float m = -INFINITY, l = 0.f;
+  f32x4 acc[2] = {};
+  for (int j0 = 0; j0 < parts; j0 += kMergeParts) {   // (behind the end the last part stands in)
+    float ms[kMergeParts], ls[kMergeParts], m_new = m;
+    f32x4 x[kMergeParts][2];
 #pragma unroll
-    for (int i4 = 0; i4 < 4; ++i4) acc[i4] += f * ((const f32x4*)s)[(q * 4 + i4) * 64 + lane];
+    for (int k = 0; k < kMergeParts; ++k) {
+      const float* s = src + min(j0 + k, parts - 1) * stride;
+      ms[k] = s[64 * 64 + lane];
+      ls[k] = s[64 * 65 + lane];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) x[k][i] = ((const f32x4*)s)[(2 * q + i) * 64 + lane];
+    }
+#pragma unroll
+    for (int k = 0; k < kMergeParts; ++k) m_new = fmaxf(m_new, ms[k]);
+    const float keep = __builtin_amdgcn_exp2f(m - m_new);
+    m = m_new;
+    l *= keep;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) acc[i] *= keep;
+#pragma unroll
+    for (int k = 0; k < kMergeParts; ++k) {
+      if (j0 + k < parts) {
+        const float w = __builtin_amdgcn_exp2f(ms[k] - m);
+        l += w * ls[k];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) acc[i] += w * x[k][i];
+      }
+    }
   }
-  const int row = pos0 + (lane & 31);
-  if (row >= row1) return;
   const float inv = 1.0f / l;
-  const int head = (unit / n_hg) * (p.Hq / p.Hkv) + (unit % n_hg) * p.heads_per_wg + wave % p.heads_per_wg;
-  __bf16* dst = (__bf16*)p.out + ((size_t)(qbase + row) * p.Hq + head) * kD + 32 * q + 4 * (lane >> 5);
+  const int head = kvh * (p.Hq / p.Hkv) + hg * p.heads_per_wg + wave % p.heads_per_wg;
+  __bf16* dst = (__bf16*)p.out + ((size_t)(qbase + row) * p.Hq + head) * kD + 16 * q + 4 * (lane >> 5);
 #pragma unroll
-  for (int i4 = 0; i4 < 4; ++i4) {
-    const bf16x2 y0 = __builtin_convertvector((f32x2{acc[i4][0] * inv, acc[i4][1] * inv}), bf16x2);
-    const bf16x2 y1 = __builtin_convertvector((f32x2{acc[i4][2] * inv, acc[i4][3] * inv}), bf16x2);
-    *(u32x2*)(dst + 8 * i4) = u32x2{__builtin_bit_cast(uint32_t, y0), __builtin_bit_cast(uint32_t, y1)};
+  for (int i = 0; i < 2; ++i) {
+    const bf16x2 y0 = __builtin_convertvector((f32x2{acc[i][0] * inv, acc[i][1] * inv}), bf16x2);
+    const bf16x2 y1 = __builtin_convertvector((f32x2{acc[i][2] * inv, acc[i][3] * inv}), bf16x2);
+    *(u32x2*)(dst + 8 * i) = u32x2{__builtin_bit_cast(uint32_t, y0), __builtin_bit_cast(uint32_t, y1)};
   }
 }
 
-int heads_per_wg_for(int G) { return G % 4 == 0 ? 4 : (G % 2 == 0 ? 2 : 1); }  // divides kWaves
+// Query heads per workgroup: divides kWaves.  Eight where the kv head serves a multiple of eight: tiles of 32 rows fit a
+// request's rows closer than the 64 of four heads.  `fine` false: at most four (a shorter work list).
+int heads_per_wg_for(int G, bool fine) { return fine && G % 8 == 0 ? 8 : (G % 4 == 0 ? 4 : (G % 2 == 0 ? 2 : 1)); }
 
 int check_attn(const skv_attn_desc* d) {
   if (!d) return SKV_EINVAL;
@@ -897,27 +1022,24 @@ int check_attn(const skv_attn_desc* d) {
   return SKV_EINVAL;
 }
 
-int64_t max_items_for(const skv_attn_desc* d, int32_t n_req, int64_t total_q_rows) {
-  if (d->dtype != SKV_BF16) return 0;
-  const int hpw = heads_per_wg_for(d->n_q_heads / d->n_kv_heads);
-  const int pos_per_wg = (kWaves / hpw) * kRowsPerWave;
-  return total_q_rows / pos_per_wg + 2 * (int64_t)n_req;   // per request: a short first tile and a ragged last one
+// How a call is laid out: from the description and the bounds the host knows.
+struct Layout {
+  int heads_per_wg, pos_per_wg, units;   // units: workgroups per item
+  int64_t max_items, max_parts;          // max_parts: room for parts of split items, 0 if nothing is split
+};
+Layout layout_for(const skv_attn_desc* d, int32_t n_req, int64_t total_q_rows, bool fine, bool split) {
+  Layout y;
+  y.heads_per_wg = heads_per_wg_for(d->n_q_heads / d->n_kv_heads, fine);
+  y.pos_per_wg = (kWaves / y.heads_per_wg) * kRowsPerWave;
+  y.units = d->n_q_heads / y.heads_per_wg;
+  // with more workgroups than two rounds of the chip there is nothing to fill
+  y.max_parts = split && total_q_rows / y.pos_per_wg * y.units <= kMaxSlots && y.units <= kCus ? kMaxSlots / y.units : 0;
+  y.max_items = total_q_rows / y.pos_per_wg + 2 * (int64_t)n_req + y.max_parts;   // per request: a short first tile and a ragged last one
+  if (d->dtype != SKV_BF16) y.max_items = y.max_parts = 0;
+  return y;
 }
-
-// Workgroups per item, and whether a batch of this bound is small enough that its items may be split along the keys
-// (with more workgroups than two rounds of the chip there is nothing to fill).
-int units_of(const skv_attn_desc* d) {
-  return d->n_kv_heads * (d->n_q_heads / d->n_kv_heads / heads_per_wg_for(d->n_q_heads / d->n_kv_heads));
-}
-int64_t max_parts_for(const skv_attn_desc* d, int64_t total_q_rows) {
-  if (d->dtype != SKV_BF16) return 0;
-  const int pos_per_wg = (kWaves / heads_per_wg_for(d->n_q_heads / d->n_kv_heads)) * kRowsPerWave;
-  const int units = units_of(d);
-  return total_q_rows / pos_per_wg * units <= kMaxSlots && units <= kCus ? kMaxSlots / units : 0;
-}
-size_t split_bytes(const skv_attn_desc* d, int64_t total_q_rows) {
-  const int64_t parts = max_parts_for(d, total_q_rows);
-  return parts ? kCus * kSplitInts * sizeof(int32_t) + (size_t)parts * units_of(d) * kSlotFloats * sizeof(float) : 0;
+size_t split_bytes(const Layout& y) {
+  return y.max_parts ? kCus * kSplitInts * sizeof(int32_t) + (size_t)y.max_parts * y.units * kSlotFloats * sizeof(float) : 0;
 }
 
 size_t zero_page_bytes(const skv_attn_desc* d) {
@@ -926,10 +1048,9 @@ size_t zero_page_bytes(const skv_attn_desc* d) {
 
 }  // namespace
 
-// Workspace without the area for split items: what a call needs at the least.
-static size_t base_workspace(const skv_attn_desc* desc, int32_t n_req, int64_t total_q_rows) {
-  const int64_t records = max_items_for(desc, n_req, total_q_rows) + max_parts_for(desc, total_q_rows);
-  return 256 + zero_page_bytes(desc) + skv_align256((size_t)records * kItemInts * sizeof(int32_t));
+// Work list and page of zeros: what a call needs at the least.
+static size_t list_bytes(const skv_attn_desc* desc, const Layout& y) {
+  return 256 + zero_page_bytes(desc) + skv_align256((size_t)y.max_items * kItemInts * sizeof(int32_t));
 }
 
 extern "C" int skv_prefill_attn_workspace_size(const skv_attn_desc* desc, int32_t n_req,
@@ -937,7 +1058,8 @@ extern "C" int skv_prefill_attn_workspace_size(const skv_attn_desc* desc, int32_
   int rc = check_attn(desc);
   if (rc) return rc;
   if (n_req < 0 || total_q_rows < 0 || !bytes) return SKV_EINVAL;
-  *bytes = base_workspace(desc, n_req, total_q_rows) + split_bytes(desc, total_q_rows);
+  const Layout y = layout_for(desc, n_req, total_q_rows, true, true);
+  *bytes = list_bytes(desc, y) + split_bytes(y);
   return SKV_OK;
 }
 
@@ -959,7 +1081,7 @@ static int prefill_attn_enqueue(const skv_attn_desc* desc, int32_t n_req, const 
                                 int64_t total_q_rows, const void* d_kpool, const void* d_vpool,
                                 int32_t n_pages, const int32_t* d_matched_len,
                                 const int32_t* d_page_table, int32_t max_blocks, void* d_out,
-                                void* d_workspace, bool may_split, void* stream) {
+                                void* d_workspace, const Layout& y, void* stream) {
   hipStream_t st = (hipStream_t)stream;
 
   AttnParams p;
@@ -970,7 +1092,7 @@ static int prefill_attn_enqueue(const skv_attn_desc* desc, int32_t n_req, const 
   p.items = (const int32_t*)((char*)d_workspace + 256 + zero_page_bytes(desc));
   p.n_req = n_req; p.max_blocks = max_blocks; p.n_pages = n_pages;
   p.Hq = desc->n_q_heads; p.Hkv = desc->n_kv_heads;
-  p.heads_per_wg = heads_per_wg_for(desc->n_q_heads / desc->n_kv_heads);
+  p.heads_per_wg = y.heads_per_wg;
   p.scale = skv_softmax_scale(desc);
 
   if (desc->dtype == SKV_F32) {
@@ -980,23 +1102,19 @@ static int prefill_attn_enqueue(const skv_attn_desc* desc, int32_t n_req, const 
     return skv_attn_f32_enqueue(f, desc->head_dim, stream);
   }
 
-  const int64_t max_parts = may_split ? max_parts_for(desc, total_q_rows) : 0;
-  const int64_t max_items = max_items_for(desc, n_req, total_q_rows) + max_parts;
-  const int pos_per_wg = (kWaves / p.heads_per_wg) * kRowsPerWave;
-  const int units = units_of(desc);
-  const int64_t grid = max_items * units;
-  if (grid > 0x7fffffff || max_items > 0x3fffffff) return SKV_ERANGE;
-  char* const split_area = (char*)d_workspace + base_workspace(desc, n_req, total_q_rows);
-  p.splits = max_parts ? (const int32_t*)split_area : nullptr;
-  p.partials = max_parts ? (float*)(split_area + kCus * kSplitInts * sizeof(int32_t)) : nullptr;
-  attn_schedule_kernel<<<1, kSchedThreads, 0, st>>>(n_req, d_q_off, d_matched_len, pos_per_wg, (int)max_items, units,
+  const int64_t grid = y.max_items * y.units;
+  if (grid > 0x7fffffff || y.max_items > 0x3fffffff) return SKV_ERANGE;
+  char* const split_area = (char*)d_workspace + list_bytes(desc, y);
+  p.splits = y.max_parts ? (const int32_t*)split_area : nullptr;
+  p.partials = y.max_parts ? (float*)(split_area + kCus * kSplitInts * sizeof(int32_t)) : nullptr;
+  attn_schedule_kernel<<<1, kSchedThreads, 0, st>>>(n_req, d_q_off, d_matched_len, y.pos_per_wg, (int)y.max_items, y.units,
                                                     (int32_t*)d_workspace, (int32_t*)p.items, (int32_t*)p.splits,
                                                     (uint4*)p.zero_page, (int)(zero_page_bytes(desc) / 16));
   SKV_HIP(hipGetLastError());
   attn_bf16_kernel<<<(int)grid, kThreads, 0, st>>>(p);
   SKV_HIP(hipGetLastError());
-  if (max_parts) {   // a split item has two parts at least
-    attn_merge_kernel<<<(int)(max_parts / 2 * units * kWaves), 256, 0, st>>>(p);
+  if (y.max_parts) {   // a split item has two parts at least
+    attn_merge_kernel<<<(int)(y.max_parts / 2 * y.units * kWaves), kMergeThreads, 0, st>>>(p);
     SKV_HIP(hipGetLastError());
   }
   return SKV_OK;
@@ -1015,12 +1133,13 @@ extern "C" int skv_prefill_attn(const skv_attn_desc* desc, int32_t n_req, const 
   rc = check_attn_buffers(d_q, d_knew, d_vnew, d_q_off, d_kpool, d_vpool, d_matched_len, d_page_table, max_blocks,
                           d_out);
   if (rc) return rc;
-  size_t need = 0;
-  skv_prefill_attn_workspace_size(desc, n_req, total_q_rows, &need);
-  if (!d_workspace || workspace_bytes < need) return SKV_ENOMEM;
+  // a workspace that holds the plain work list is enough: the call then splits nothing
+  Layout y = layout_for(desc, n_req, total_q_rows, true, true);
+  if (workspace_bytes < list_bytes(desc, y) + split_bytes(y)) y = layout_for(desc, n_req, total_q_rows, false, false);
+  if (!d_workspace || workspace_bytes < list_bytes(desc, y)) return SKV_ENOMEM;
   if ((uintptr_t)d_workspace & 15) return SKV_EINVAL;
   return prefill_attn_enqueue(desc, n_req, d_q, d_knew, d_vnew, d_q_off, total_q_rows, d_kpool, d_vpool, n_pages,
-                              d_matched_len, d_page_table, max_blocks, d_out, d_workspace, true, stream);
+                              d_matched_len, d_page_table, max_blocks, d_out, d_workspace, y, stream);
 }
 
 // ---- the same call for callers that cannot allocate ---------------------------------------------
@@ -1061,15 +1180,16 @@ extern "C" int skv_prefill_attn_static(const skv_attn_desc* desc, int32_t n_req,
   rc = check_attn_buffers(d_q, d_knew, d_vnew, d_q_off, d_kpool, d_vpool, d_matched_len, d_page_table, max_blocks,
                           d_out);
   if (rc) return rc;
-  if (base_workspace(desc, n_req, total_q_rows) > (size_t)SKV_STATIC_SCRATCH_BYTES)
-    return SKV_ERANGE;   // batch too large for the built-in scratch
+  Layout y = layout_for(desc, n_req, total_q_rows, true, false);
+  if (list_bytes(desc, y) > (size_t)SKV_STATIC_SCRATCH_BYTES) y = layout_for(desc, n_req, total_q_rows, false, false);
+  if (list_bytes(desc, y) > (size_t)SKV_STATIC_SCRATCH_BYTES) return SKV_ERANGE;   // batch too large for the built-in scratch
   void* ws = nullptr;
   rc = scratch_of_current_device(&ws);
   if (rc) return rc;
   // the schedule kernel rewrites the item count, the page of zeros and every record it hands out on each call,
   // so nothing of the previous call's contents is read
   return prefill_attn_enqueue(desc, n_req, d_q, d_knew, d_vnew, d_q_off, total_q_rows, d_kpool, d_vpool, n_pages,
-                              d_matched_len, d_page_table, max_blocks, d_out, ws, false, stream);
+                              d_matched_len, d_page_table, max_blocks, d_out, ws, y, stream);
 }
 
 // ---- measurement aid: what the matrix cores sustain on given operand values ----

@@ -6,6 +6,7 @@ import re
 
 import numpy as np
 import pytest
+import torch
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -162,6 +163,11 @@ def test_static_scratch_attention_rejects_oversized_batches_before_touching_the_
     args = [fake, fake, fake, fake, rows, fake, fake, 8, fake, fake, 4, fake, None]
     assert l.skv_prefill_attn_static(C.byref(good), 4, *args) == -3
     assert l.skv_prefill_attn_static(C.byref(good), 0, *args) == 0           # empty batch
+    if not torch.cuda.is_available():   # inside the scratch, on lists of either tile: refused by the missing device only
+        for hq, last in ((32, 64 * 130032 + 63), (64, 64 * 130032 + 63)):
+            for n_rows, code in ((last // 2, -4), (last, -4), (last + 1, -3)):
+                args[4] = n_rows
+                assert l.skv_prefill_attn_static(C.byref(skv.attn_desc(hq, 8, 128, "bf16")), 4, *args) == code
     args[0] = None
     assert l.skv_prefill_attn_static(C.byref(good), 4, *args) == -1          # null tensor
     assert l.skv_prefill_attn_static(None, 4, *args) == -1

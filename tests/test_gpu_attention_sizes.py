@@ -85,3 +85,59 @@ def test_bf16_split_parts_with_their_own_references():
         c["kpool"][c["page_table"][0, j]] *= (j % 40) * 2.0
     got, want = run_attn(c), oracle.attention(**c, n_threads=8)
     assert np.abs(got - want).max() <= 2e-2 * max(1.0, np.abs(want).max())   # output rounding at values above 1
+
+
+@pytest.mark.parametrize("hq,hkv", [(8, 1), (4, 1), (16, 2)])
+def test_bf16_work_list_of_many_requests(hq, hkv):
+    # more requests than the list is made of at a time, lengths in no order, some alike, some empty; tiles of 32 and 64 rows
+    g = np.random.default_rng(hq)
+    S = g.choice([0, 1, 2, 5, 17, 31, 32, 33, 64, 65], 1500, p=[.3, .3, .1, .1, .05, .03, .03, .03, .03, .03])
+    S[[3, 700, 1400]] = 150, 97, 130
+    k = g.integers(0, 3, 1500)
+    k[[3, 700, 1023, 1024]] = 20, 9, 30, 2
+    c = attn_case(91, 1500, hq, hkv, 128, torch.bfloat16, 31, S, k, n_pages=int(k.sum()) + 3)
+    got, want = run_attn(c), oracle.attention(**c, n_threads=8)
+    assert np.isfinite(got).all()
+    assert np.abs(got - want).max() <= 2e-2
+
+
+def _run_with(c, workspace_bytes):
+    from paper_2508_08438_amd import binding as skv
+    dev = "cuda:0"
+    x = {n: (v if torch.is_tensor(v) else torch.from_numpy(v)).to(dev) for n, v in c.items()}
+    desc = skv.attn_desc(x["q"].shape[1], x["kpool"].shape[2], 128, torch.bfloat16)
+    full = skv.skv_prefill_attn_workspace_size(desc, len(c["matched_len"]), x["q"].shape[0])
+    ws = torch.zeros(full if workspace_bytes is None else workspace_bytes, dtype=torch.uint8, device=dev)
+    out = torch.full_like(x["q"], 7.0)
+    skv.skv_prefill_attn(desc, x["q"], x["knew"], x["vnew"], x["q_off"], x["kpool"], x["vpool"], x["matched_len"],
+                         x["page_table"], x["page_table"].shape[1], out, ws)
+    torch.cuda.synchronize()
+    return out.double().cpu().numpy(), full
+
+
+@pytest.mark.parametrize("hq,hkv", [(8, 2), (8, 1)])
+def test_bf16_plain_work_list_is_enough(hq, hkv):
+    from paper_2508_08438_amd import binding as skv
+    c = attn_case(13, 2, hq, hkv, 128, torch.bfloat16, 150, [70, 9], [150, 40], n_pages=200)
+    want = oracle.attention(**c, n_threads=8)
+    # item count, page of zeros, a record of 32 bytes for each of 79 / 64 (rows per tile of four heads) + 2 per request
+    plain = 256 + 16 * hkv * 256 + 256
+    got, full = _run_with(c, plain)
+    assert full > plain and np.abs(got - want).max() <= 2e-2
+    with pytest.raises(skv.SkvError) as e:
+        _run_with(c, plain - 1)
+    assert e.value.code == skv.SKV_ENOMEM
+
+
+@pytest.mark.parametrize("split", [True, False])
+def test_bf16_runs_of_keys_without_weight(split):
+    # scores of -infinity over the first pages, over whole parts, and over the new keys of one request
+    c = attn_case(14, 2, 8, 2, 128, torch.bfloat16, 130, [70, 40], [128, 100], n_pages=230)
+    c["q"] = c["q"].abs() + 0.01
+    for r, pages in ((0, range(0, 4)), (0, range(20, 90)), (1, range(96, 100))):
+        for j in pages:
+            c["kpool"][c["page_table"][r, j]] = float("-inf")
+    c["knew"][70:] = float("-inf")
+    got, _ = _run_with(c, None if split else 256 + 16 * 2 * 256 + 256)
+    want = oracle.attention(**c, n_threads=8)
+    assert np.isfinite(want).all() and np.abs(got - want).max() <= 2e-2
