@@ -141,26 +141,6 @@ __device__ inline int parts_of(int n, int last, int c) {
 constexpr int kSchedThreads = 1024, kSchedWaves = kSchedThreads / 64;
 constexpr int kBuckets = 128;
 
-// inclusive scan over the workgroup; `total` of all threads (red: one place per wavefront; two barriers)
-__device__ inline int block_scan(int v, int* red, int& total) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int o = 1; o < 64; o <<= 1) {
-    const int x = __shfl_up(v, o);
-    if (lane >= o) v += x;
-  }
-  if (lane == 63) red[wave] = v;
-  __syncthreads();
-  int x = lane < kSchedWaves ? red[lane] : 0, all = x;
-  if (lane >= wave) x = 0;
-  for (int o = kSchedWaves / 2; o >= 1; o >>= 1) {
-    x += __shfl_xor(x, o);
-    all += __shfl_xor(all, o);
-  }
-  total = __shfl(all, 0);
-  v += __shfl(x, 0);
-  __syncthreads();
-  return v;
-}
 __device__ inline int wave_max(int v) {
   for (int o = 32; o >= 1; o >>= 1) v = max(v, __shfl_xor(v, o));
   return v;
@@ -231,7 +211,7 @@ __global__ __launch_bounds__(kSchedThreads) void attn_schedule_kernel(
     }
     __syncthreads();
     int total;
-    const int upto = block_scan(tid < n_here ? scan[tid] : 0, red, total);
+    const int upto = skv_block_scan<kSchedThreads>(tid < n_here ? scan[tid] : 0, red, total);
     scan[tid] = upto;
     __syncthreads();
     // the chunk's items, one per thread and turn: the request is found in the scan
@@ -320,7 +300,7 @@ __global__ __launch_bounds__(kSchedThreads) void attn_schedule_kernel(
     }
     int total;
     const int mine = parts | (parts > 1 ? parts << 10 | 1 << 20 : 0);
-    const int upto = block_scan(mine, red, total);
+    const int upto = skv_block_scan<kSchedThreads>(mine, red, total);
     const int n_parts = total & 1023;
     if (n_parts > n && n_parts <= max_items) {
       scan[tid] = upto & 1023;

@@ -26,7 +26,11 @@ struct SkvSlot {       // 16 bytes
   int32_t child;       // node index, -1 = empty, -2 = removed (probing goes on)
   int32_t pad;
 };
-#define SKV_CTR_STRIDE 8  // uint32 per block: [0] hit_cur, [1..4] tenant bitmap, [5] hit_pre, [6] u_pre, [7] predicate streak
+// Per-block counters, one plane of uint32 per field: 0 hit_cur, 1..4 tenant bitmap, 5 hit_pre, 6 u_pre, 7 predicate streak.
+// Planes and not records: the blocks of a path are contiguous, so the atomics of a wavefront on one field fall into two or
+// three cache lines, where 32-byte records took sixteen (4096 lookups, 0.77 M matched blocks: 69.6 us with records, 34.4
+// with planes, 29 without any atomics).
+#define SKV_CTR_FIELDS 8
 
 struct SkvTreeDev {
   const int32_t* tok;     // [n_blocks][16]
@@ -34,7 +38,8 @@ struct SkvTreeDev {
   int32_t* meta;          // [n_blocks]   bit31 = private_tag, bits 0..30 = creator_id (demotion sets bit31)
   const int32_t* canon;   // [n_blocks]   input block id that created the entry
   const int32_t* flat_of; // [n_in_blocks] flat index of the entry an input block created, -1 if none
-  uint32_t* ctr;          // [n_blocks][SKV_CTR_STRIDE]
+  uint32_t* ctr;          // [SKV_CTR_FIELDS][ctr_plane]
+  size_t ctr_plane;       // blocks the slab has room for
   uint32_t* epoch;        // [n_blocks]   epoch counter value at the block's last access
   uint32_t* limits;       // [1] SKV_LIMIT_* bits of the limits the branching lookup has run into since the last read
   const SkvNode* nodes;   // [n_nodes+1]
@@ -70,6 +75,31 @@ inline uint64_t skv_hash_block_host(const int32_t* tok) {
   for (uint32_t i = 0; i < 16; ++i) s += skv_mix_tok((uint32_t)tok[i], i);
   return skv_hash_fin(s);
 }
+
+#ifdef __HIPCC__
+// Inclusive scan over a workgroup of kThreads; `total` of all threads.  red: one place per wavefront.  Two barriers.
+template <int kThreads>
+__device__ inline int skv_block_scan(int v, int* red, int& total) {
+  constexpr int kWaves = kThreads / 64;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int o = 1; o < 64; o <<= 1) {
+    const int x = __shfl_up(v, o);
+    if (lane >= o) v += x;
+  }
+  if (lane == 63) red[wave] = v;
+  __syncthreads();
+  int x = lane < kWaves ? red[lane] : 0, all = x;
+  if (lane >= wave) x = 0;
+  for (int o = kWaves / 2; o >= 1; o >>= 1) {
+    x += __shfl_xor(x, o);
+    all += __shfl_xor(all, o);
+  }
+  total = __shfl(all, 0);
+  v += __shfl(x, 0);
+  __syncthreads();
+  return v;
+}
+#endif
 
 // ---- error plumbing ---------------------------------------------------------------------------
 void skv_set_hip_error(int e);
