@@ -1,6 +1,5 @@
 """Compiled assembly of further matrix-instruction kernels, scanned for readers that come too early behind a branch (see
-mfma_hazard_scan).  `need`: idle states a result needs before a vector instruction may read it -- 18 behind the 16-pass
-fp32 32x32x2 instruction, 12 behind the bf16 ones."""
+mfma_hazard_scan).  `need`: idle states a result needs before a vector instruction may read it -- 12 behind the bf16 ones."""
 import os
 import subprocess
 
@@ -10,7 +9,7 @@ from paper_2508_08438_amd import build
 
 
 @pytest.mark.parametrize("src,kernels,need", [
-    ("skv_attn_f32.hip", ["attn_f32_kernelILi64E", "attn_f32_kernelILi128E"], 18),
+    ("skv_attn_f32.hip", ["attn_f32_kernelILi64E", "attn_f32_kernelILi128E", "attn_f32_tile_kernel"], 12),
 ])
 def test_no_early_reader_behind_a_branch(src, kernels, need, tmp_path):
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -52,6 +52,67 @@ def test_fp32_maxima_that_keep_moving():
     assert np.abs(got - want).max() <= 5 * 5 * 400 * 2.0 ** -24
 
 
+# Long suffixes in number: 128-row tiles of d 64 (32 tiles of 16 heads and more).  Edges of wavefronts, tiles and key tiles.
+LARGE = dict(S=[257, 383, 384, 385, 511, 512, 513, 130, 1000, 640], k=[0, 1, 2, 3, 4, 5, 0, 70, 9, 33])
+
+
+@pytest.mark.parametrize("hq,hkv", [(16, 2), (16, 16)])
+def test_fp32_large_tiles(hq, hkv):
+    S, k = LARGE["S"], LARGE["k"]
+    c = attn_case(hkv, len(S), hq, hkv, 64, torch.float32, max(k) + 1, S, k, n_pages=sum(k) + 3)
+    for r, j in ((2, 1), (7, 0), (7, 69)):
+        for pool in ("kpool", "vpool"):
+            c[pool][c["page_table"][r, j]] = 0
+    want = oracle.attention(**c, n_threads=8)
+    for n, (r, j) in enumerate(((2, 1), (7, 0), (7, 69))):
+        c["page_table"][r, j] = -1 if n % 2 else sum(k) + 3 + n
+    got = run_attn(c)
+    assert np.isfinite(got).all()
+    assert np.abs(got - want).max() <= F32_TOL
+
+
+def test_fp32_pages_of_more_than_64_tiles():
+    # a wavefront of the large tiles holds the page ids of 64 key tiles (4096 keys) at a time
+    S, k = [260, 1030, 2900], [300, 0, 513]
+    c = attn_case(3, 3, 16, 1, 64, torch.float32, max(k) + 1, S, k, n_pages=sum(k) + 3)
+    rows = (np.repeat([0, 1, 2], 40).astype(np.int32), np.tile(np.arange(40) % 16, 3).astype(np.int32),
+            np.concatenate([np.linspace(0, s - 1, 40) for s in S]).astype(np.int32))
+    want = oracle.attention(**c, rows=rows, n_threads=8)
+    got = run_attn(c)
+    at = np.array([c["q_off"][r] + i for r, i in zip(rows[0], rows[2])])
+    assert np.abs(got[at, rows[1]] - want.reshape(len(at), -1)).max() <= F32_TOL
+
+
+@pytest.mark.parametrize("large,d", [(False, 64), (False, 128), (True, 64)])
+def test_fp32_values_without_pieces(large, d):
+    # what is not finite, or too large for bf16, reaches the rows that see it and no others
+    S, k = (LARGE["S"], LARGE["k"]) if large else ([70, 5, 40], [3, 1, 0])
+    n = len(S)
+    c = attn_case(31, n, 16, 2, d, torch.float32, max(k) + 1, S, k, n_pages=sum(k) + 3)
+    c["q"] = c["q"].abs() + 0.1
+    r = 0 if not large else 8
+    first = int(c["q_off"][r])
+    nan_row, inf_row, big_row = S[r] - 3, S[r] - 20, S[r] - 30
+    low = int(c["page_table"][r, 1 if not large else 4]) if k[r] > 1 else None
+    if low is not None:
+        c["kpool"][low] = float("-inf")               # no weight
+    c["vnew"][first + big_row, :, 3] = 3.4e38         # finite, rounds to infinity as bf16
+    want = oracle.attention(**c, n_threads=8)
+    c["vnew"][first + nan_row, 0] = float("nan")
+    c["vnew"][first + inf_row, 1, 5] = float("inf")
+    got = run_attn(c)
+    scale = np.maximum(1.0, np.abs(want))             # the large value: relative, as its weight is
+    err = np.abs(got - want) / scale
+    G = 8
+    rows, heads = np.arange(first, first + S[r]), np.arange(16)
+    clean = np.ones(got.shape, bool)
+    clean[first + nan_row: first + S[r], :G] = False
+    clean[first + inf_row: first + S[r], G:, 5] = False
+    assert np.isfinite(got[clean]).all() and err[clean].max() <= F32_TOL
+    assert np.isnan(got[first + nan_row: first + S[r], :G]).all()
+    assert np.isposinf(got[first + inf_row: first + S[r], G:, 5]).all()
+
+
 # bf16, items split along their keys (few work items behind many keys): 1, 2, 3 .. key tiles a part, parts that end before
 # and behind the reused prefix, short first row tiles, rows of several requests.  Tolerance of the unsplit kernel.
 SPLIT = [
