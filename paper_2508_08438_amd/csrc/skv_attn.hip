@@ -20,6 +20,7 @@
 // the output update with sub-tile h - 1 share a half-step, in which nothing depends on
 // anything else, so MFMAs and vector instructions alternate in the instruction stream.
 // fp32 path: skv_attn_f32.hip.
+#include <algorithm>
 #include <atomic>
 
 #include "skv_internal.h"
@@ -375,8 +376,7 @@ __device__ __forceinline__ void lds_wait(int n, bf16x8& a, bf16x8& b, bf16x8& c,
 
 // Workgroup b runs on XCD b % 8: all work of one kv head stays on one XCD where the heads allow it, so its K/V tiles are
 // re-read from that XCD's L2, and the merge finds the parts there.
-__device__ __forceinline__ void unit_of_block(int Hkv, int n_hg, int& item, int& kvh, int& hg) {
-  const int b = blockIdx.x;
+__device__ __forceinline__ void unit_of_block(int b, int Hkv, int n_hg, int& item, int& kvh, int& hg) {
   int rest;
   if (Hkv % 8 == 0) {
     const int per = Hkv / 8;
@@ -411,7 +411,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
   const int G = p.Hq / p.Hkv;
   const int n_hg = G / p.heads_per_wg;               // head groups per kv head
   int item, kvh, hg;
-  unit_of_block(p.Hkv, n_hg, item, kvh, hg);
+  unit_of_block(blockIdx.x, p.Hkv, n_hg, item, kvh, hg);
   // the record is read together with the item count (the grid bound keeps the index inside the list)
   const int4 rec0 = ((const int4*)(p.items + (size_t)kItemInts * item))[0];
   const int4 rec1 = ((const int4*)(p.items + (size_t)kItemInts * item))[1];
@@ -934,59 +934,61 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
 // Bound by latency: eight parts' states travel together and are folded into a running maximum, so the usual item takes one or
 // two trips to memory (references first and outputs after them, four parts at a time: 10.7 us for 10 parts of 3 items,
 // now 6.5).
-constexpr int kMergeThreads = 512, kMergeParts = 8;
+constexpr int kMergeThreads = 512, kMergeParts = 8, kMergeGrid = 512;   // (most calls merge little or nothing)
 __global__ __launch_bounds__(kMergeThreads) void attn_merge_kernel(AttnParams p) {
   const int n_hg = p.Hq / p.Hkv / p.heads_per_wg, units = p.Hkv * n_hg;
-  int rest, kvh, hg;
-  unit_of_block(p.Hkv, n_hg, rest, kvh, hg);
-  const int wave = rest % kWaves, unit = kvh * n_hg + hg, si = rest / kWaves;
-  if (si >= p.n_items[1]) return;
-  const int4 a = ((const int4*)(p.splits + kSplitInts * si))[0];
-  const int parts = p.splits[kSplitInts * si + 4];
-  const int row0 = a.x, row1 = a.y, qbase = a.z, slot = a.w;
-  const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
-  const int row = row0 + (wave / p.heads_per_wg) * kRowsPerWave + (lane & 31);
-  if (row >= row1) return;
-  const size_t stride = (size_t)units * kSlotFloats;   // from one part to the next
-  const float* src = p.partials + ((size_t)slot * units + unit) * kSlotFloats + (size_t)wave * (64 * 66);
-  float m = -INFINITY, l = 0.f;
-  f32x4 acc[2] = {};
-  for (int j0 = 0; j0 < parts; j0 += kMergeParts) {   // (behind the end the last part stands in)
-    float ms[kMergeParts], ls[kMergeParts], m_new = m;
-    f32x4 x[kMergeParts][2];
+  const int n_work = p.n_items[1] * units * kWaves;
+  for (int b = blockIdx.x; b < n_work; b += gridDim.x) {
+    int rest, kvh, hg;
+    unit_of_block(b, p.Hkv, n_hg, rest, kvh, hg);
+    const int wave = rest % kWaves, unit = kvh * n_hg + hg, si = rest / kWaves;
+    const int4 a = ((const int4*)(p.splits + kSplitInts * si))[0];
+    const int parts = p.splits[kSplitInts * si + 4];
+    const int row0 = a.x, row1 = a.y, qbase = a.z, slot = a.w;
+    const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
+    const int row = row0 + (wave / p.heads_per_wg) * kRowsPerWave + (lane & 31);
+    if (row >= row1) continue;
+    const size_t stride = (size_t)units * kSlotFloats;   // from one part to the next
+    const float* src = p.partials + ((size_t)slot * units + unit) * kSlotFloats + (size_t)wave * (64 * 66);
+    float m = -INFINITY, l = 0.f;
+    f32x4 acc[2] = {};
+    for (int j0 = 0; j0 < parts; j0 += kMergeParts) {   // (behind the end the last part stands in)
+      float ms[kMergeParts], ls[kMergeParts], m_new = m;
+      f32x4 x[kMergeParts][2];
 #pragma unroll
-    for (int k = 0; k < kMergeParts; ++k) {
-      const float* s = src + min(j0 + k, parts - 1) * stride;
-      ms[k] = s[64 * 64 + lane];
-      ls[k] = s[64 * 65 + lane];
+      for (int k = 0; k < kMergeParts; ++k) {
+        const float* s = src + min(j0 + k, parts - 1) * stride;
+        ms[k] = s[64 * 64 + lane];
+        ls[k] = s[64 * 65 + lane];
 #pragma unroll
-      for (int i = 0; i < 2; ++i) x[k][i] = ((const f32x4*)s)[(2 * q + i) * 64 + lane];
-    }
+        for (int i = 0; i < 2; ++i) x[k][i] = ((const f32x4*)s)[(2 * q + i) * 64 + lane];
+      }
 #pragma unroll
-    for (int k = 0; k < kMergeParts; ++k) m_new = fmaxf(m_new, ms[k]);
-    const float keep = __builtin_amdgcn_exp2f(m - m_new);
-    m = m_new;
-    l *= keep;
+      for (int k = 0; k < kMergeParts; ++k) m_new = fmaxf(m_new, ms[k]);
+      const float keep = __builtin_amdgcn_exp2f(m - m_new);
+      m = m_new;
+      l *= keep;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) acc[i] *= keep;
+      for (int i = 0; i < 2; ++i) acc[i] *= keep;
 #pragma unroll
-    for (int k = 0; k < kMergeParts; ++k) {
-      if (j0 + k < parts) {
-        const float w = __builtin_amdgcn_exp2f(ms[k] - m);
-        l += w * ls[k];
+      for (int k = 0; k < kMergeParts; ++k) {
+        if (j0 + k < parts) {
+          const float w = __builtin_amdgcn_exp2f(ms[k] - m);
+          l += w * ls[k];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) acc[i] += w * x[k][i];
+          for (int i = 0; i < 2; ++i) acc[i] += w * x[k][i];
+        }
       }
     }
-  }
-  const float inv = 1.0f / l;
-  const int head = kvh * (p.Hq / p.Hkv) + hg * p.heads_per_wg + wave % p.heads_per_wg;
-  __bf16* dst = (__bf16*)p.out + ((size_t)(qbase + row) * p.Hq + head) * kD + 16 * q + 4 * (lane >> 5);
+    const float inv = 1.0f / l;
+    const int head = kvh * (p.Hq / p.Hkv) + hg * p.heads_per_wg + wave % p.heads_per_wg;
+    __bf16* dst = (__bf16*)p.out + ((size_t)(qbase + row) * p.Hq + head) * kD + 16 * q + 4 * (lane >> 5);
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const bf16x2 y0 = __builtin_convertvector((f32x2{acc[i][0] * inv, acc[i][1] * inv}), bf16x2);
-    const bf16x2 y1 = __builtin_convertvector((f32x2{acc[i][2] * inv, acc[i][3] * inv}), bf16x2);
-    *(u32x2*)(dst + 8 * i) = u32x2{__builtin_bit_cast(uint32_t, y0), __builtin_bit_cast(uint32_t, y1)};
+    for (int i = 0; i < 2; ++i) {
+      const bf16x2 y0 = __builtin_convertvector((f32x2{acc[i][0] * inv, acc[i][1] * inv}), bf16x2);
+      const bf16x2 y1 = __builtin_convertvector((f32x2{acc[i][2] * inv, acc[i][3] * inv}), bf16x2);
+      *(u32x2*)(dst + 8 * i) = u32x2{__builtin_bit_cast(uint32_t, y0), __builtin_bit_cast(uint32_t, y1)};
+    }
   }
 }
 
@@ -1082,8 +1084,9 @@ static int prefill_attn_enqueue(const skv_attn_desc* desc, int32_t n_req, const 
     return skv_attn_f32_enqueue(f, desc->head_dim, stream);
   }
 
-  const int64_t grid = y.max_items * y.units;
-  if (grid > 0x7fffffff || y.max_items > 0x3fffffff) return SKV_ERANGE;
+  // the list holds whole items or, where anything is split, no more than max_parts records
+  const int64_t grid = std::max(y.max_items - y.max_parts, y.max_parts) * y.units;
+  if (y.max_items * y.units > 0x7fffffff || y.max_items > 0x3fffffff) return SKV_ERANGE;
   char* const split_area = (char*)d_workspace + list_bytes(desc, y);
   p.splits = y.max_parts ? (const int32_t*)split_area : nullptr;
   p.partials = y.max_parts ? (float*)(split_area + kCus * kSplitInts * sizeof(int32_t)) : nullptr;
@@ -1094,7 +1097,7 @@ static int prefill_attn_enqueue(const skv_attn_desc* desc, int32_t n_req, const 
   attn_bf16_kernel<<<(int)grid, kThreads, 0, st>>>(p);
   SKV_HIP(hipGetLastError());
   if (y.max_parts) {   // a split item has two parts at least
-    attn_merge_kernel<<<(int)(y.max_parts / 2 * y.units * kWaves), kMergeThreads, 0, st>>>(p);
+    attn_merge_kernel<<<(int)std::min<int64_t>(y.max_parts / 2 * y.units * kWaves, kMergeGrid), kMergeThreads, 0, st>>>(p);
     SKV_HIP(hipGetLastError());
   }
   return SKV_OK;
@@ -1116,6 +1119,11 @@ extern "C" int skv_prefill_attn(const skv_attn_desc* desc, int32_t n_req, const 
   // a workspace that holds the plain work list is enough: the call then splits nothing
   Layout y = layout_for(desc, n_req, total_q_rows, true, true);
   if (workspace_bytes < list_bytes(desc, y) + split_bytes(y)) y = layout_for(desc, n_req, total_q_rows, false, false);
+  // items of so few key tiles are never split (one round of them: 8 + c against at most `longest`; two: 16 + 2 c against at
+  // most 8 + 2.5 longest), so there is nothing to merge either
+  const int64_t longest = ((int64_t)max_blocks * SKV_BLOCK_TOKENS + total_q_rows + kBN - 1) / kBN;
+  if (y.max_parts && longest <= ((y.max_items - y.max_parts) * y.units <= kCus ? kStartTiles + 1 : 4))
+    y = layout_for(desc, n_req, total_q_rows, true, false);
   if (!d_workspace || workspace_bytes < list_bytes(desc, y)) return SKV_ENOMEM;
   if ((uintptr_t)d_workspace & 15) return SKV_EINVAL;
   return prefill_attn_enqueue(desc, n_req, d_q, d_knew, d_vnew, d_q_off, total_q_rows, d_kpool, d_vpool, n_pages,

@@ -13,49 +13,71 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kUnroll = 8;  // 16-byte vectors in flight per thread and pool
 
-__global__ void ctx_offsets_kernel(int n_req, const int32_t* __restrict__ matched_len,
-                                   int64_t* __restrict__ ctx_off) {
-  __shared__ int64_t sh[1024];
-  __shared__ int64_t carry;
-  if (threadIdx.x == 0) { carry = 0; ctx_off[0] = 0; }
-  __syncthreads();
-  for (int base = 0; base < n_req; base += 1024) {
-    const int r = base + threadIdx.x;
-    int64_t v = 0;
-    if (r < n_req) v = matched_len[r] > 0 ? (matched_len[r] / SKV_BLOCK_TOKENS) * SKV_BLOCK_TOKENS : 0;
-    sh[threadIdx.x] = v;
-    __syncthreads();
-    for (int o = 1; o < 1024; o <<= 1) {
-      int64_t add = threadIdx.x >= o ? sh[threadIdx.x - o] : 0;
-      __syncthreads();
-      sh[threadIdx.x] += add;
-      __syncthreads();
-    }
-    if (r < n_req) ctx_off[r + 1] = carry + sh[threadIdx.x];
-    __syncthreads();
-    if (threadIdx.x == 0) carry += sh[1023];
-    __syncthreads();
-  }
-}
-
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
+// Every workgroup scans the matched lengths itself (a load per thread for up to 256 requests; the first workgroup also writes
+// the offsets) and finds the owner of a page in LDS: a kernel for the offsets in front cost more than that (one request
+// of 187 pages: GATHER_MEASURED).  The scan has kPref places; with more requests a place stands for several, in order.
+constexpr int kPref = 2048;
 __global__ __launch_bounds__(kThreads) void gather_pages_kernel(
     int n_req, const u32x4* __restrict__ kpool, const u32x4* __restrict__ vpool, int n_pages,
-    const int32_t* __restrict__ page_table, int max_blocks, const int64_t* __restrict__ ctx_off,
-    u32x4* __restrict__ kctx, u32x4* __restrict__ vctx, int64_t cap_pages, int page_vec /* 16-byte vectors per page */) {
-  const int64_t total_pages = ctx_off[n_req] / SKV_BLOCK_TOKENS;
-  for (int64_t p = blockIdx.x; p < total_pages; p += gridDim.x) {
-    // request that owns output page p: last r with ctx_off[r]/16 <= p
-    int lo = 0, hi = n_req;  // invariant: ctx_off[lo] <= 16p < ctx_off[hi]
+    const int32_t* __restrict__ matched_len, const int32_t* __restrict__ page_table, int max_blocks,
+    int64_t* __restrict__ ctx_off, u32x4* __restrict__ kctx, u32x4* __restrict__ vctx, int64_t cap_pages,
+    int page_vec /* 16-byte vectors per page */) {
+  __shared__ int64_t first[kPref + 1];   // pages before the requests of a place
+  __shared__ int64_t red[kThreads / 64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int per = max(1, (n_req + kPref - 1) / kPref);        // requests per place
+  const int places = (n_req + per - 1) / per;
+  const int own = (places + kThreads - 1) / kThreads;         // places per thread
+  const int r0 = min(threadIdx.x * own * per, n_req), r1 = min(r0 + own * per, n_req);
+  auto pages_of = [&](int r) { return max(matched_len[r], 0) / SKV_BLOCK_TOKENS; };
+  int64_t mine = 0;
+  for (int r = r0; r < r1; ++r) mine += pages_of(r);
+  int64_t upto = mine;
+  for (int o = 1; o < 64; o <<= 1) {
+    const int64_t x = __shfl_up(upto, o);
+    if (lane >= o) upto += x;
+  }
+  if (lane == 63) red[wave] = upto;
+  __syncthreads();
+  int64_t total = 0;
+#pragma unroll
+  for (int w = 0; w < kThreads / 64; ++w) {
+    const int64_t x = red[w];
+    if (w < wave) upto += x;
+    total += x;
+  }
+  int64_t at = upto - mine;
+  for (int r = r0; r < r1; ++r) {
+    if (r % per == 0) first[r / per] = at;
+    at += pages_of(r);
+    if (blockIdx.x == 0) ctx_off[r + 1] = at * SKV_BLOCK_TOKENS;
+  }
+  if (threadIdx.x == 0) {
+    first[places] = total;
+    if (blockIdx.x == 0) ctx_off[0] = 0;
+  }
+  __syncthreads();
+  const int64_t end = min(total, cap_pages);
+  for (int64_t p = blockIdx.x; p < end; p += gridDim.x) {
+    // request that owns output page p: the last one with no more than p pages before it
+    int lo = 0, hi = places;  // invariant: first[lo] <= p < first[hi]
     while (hi - lo > 1) {
       const int mid = (lo + hi) >> 1;
-      if (ctx_off[mid] <= p * SKV_BLOCK_TOKENS) lo = mid; else hi = mid;
+      if (first[mid] <= p) lo = mid; else hi = mid;
     }
-    const int j = (int)(p - ctx_off[lo] / SKV_BLOCK_TOKENS);
+    int64_t before = first[lo];
+    lo *= per;
+    if (per > 1)
+      for (int n = pages_of(lo); before + n <= p; n = pages_of(lo)) {
+        before += n;
+        ++lo;
+      }
+    const int j = (int)(p - before);
     if (j >= max_blocks) continue;
     const int page = page_table[(size_t)lo * max_blocks + j];
-    if (page < 0 || page >= n_pages || p >= cap_pages) continue;  // uniform per workgroup
+    if (page < 0 || page >= n_pages) continue;  // uniform per workgroup
     const u32x4* ks = kpool + (size_t)page * page_vec;
     const u32x4* vs = vpool + (size_t)page * page_vec;
     u32x4* kd = kctx + (size_t)p * page_vec;
@@ -189,14 +211,11 @@ extern "C" int skv_gather_kv(const skv_attn_desc* desc, int32_t n_req, const voi
   if (n_req > 0 && max_blocks > 0 && !d_page_table) return SKV_EINVAL;
   if (((uintptr_t)d_kpool | (uintptr_t)d_vpool | (uintptr_t)d_kctx | (uintptr_t)d_vctx) & 15) return SKV_EINVAL;
   hipStream_t st = (hipStream_t)stream;
-  ctx_offsets_kernel<<<1, 1024, 0, st>>>(n_req, d_matched_len, d_ctx_off);
-  SKV_HIP(hipGetLastError());
-  if (n_req == 0 || max_blocks == 0) return SKV_OK;
-  int64_t upper = (int64_t)n_req * max_blocks;  // pages the batch can reference at most
-  int grid = (int)(upper < 256 * 16 ? upper : 256 * 16);
+  const int64_t upper = (int64_t)n_req * max_blocks;  // pages the batch can reference at most
+  const int grid = (int)(upper < 1 ? 1 : (upper < 256 * 16 ? upper : 256 * 16));
   gather_pages_kernel<<<grid, kThreads, 0, st>>>(
-      n_req, (const u32x4*)d_kpool, (const u32x4*)d_vpool, n_pages, d_page_table, max_blocks, d_ctx_off,
-      (u32x4*)d_kctx, (u32x4*)d_vctx, ctx_capacity_tokens / SKV_BLOCK_TOKENS, (int)(page_bytes / 16));
+      n_req, (const u32x4*)d_kpool, (const u32x4*)d_vpool, n_pages, d_matched_len, d_page_table, max_blocks, d_ctx_off,
+      (u32x4*)d_kctx, (u32x4*)d_vctx, upper ? ctx_capacity_tokens / SKV_BLOCK_TOKENS : 0, (int)(page_bytes / 16));
   SKV_HIP(hipGetLastError());
   return SKV_OK;
 }
