@@ -88,8 +88,10 @@ struct AttnParams {
 // behind 24 k cached tokens: 80 workgroups, 0.50 ms).  Their items are split along the keys: every part is a record of its
 // own (part = (slot + 1) << kPartBits | key tiles), leaves its unnormalised output, reference and row sum in the workspace,
 // and attn_merge_kernel combines them.  The part length c is the smallest for which all parts run in one round, or in
-// two, of one workgroup per compute unit; a workgroup costs about kStartTiles key tiles before and after its loop, the
-// merge about as much again, and unless the split wins by that the items stay whole.
+// two, of one workgroup per compute unit.  Whole items take 11.5 + 1.27 us per key tile of the longest, split ones 28 + 1.9 us
+// per key tile and compute unit (start-up, partial states and merge included; 144 shapes of 8 .. 160 workgroups, both forms
+// timed): the batch is split where that is less.  E.g. 137 rows behind 2048 cached ones 53 -> 30 us; 300 behind 512 stay whole
+// (28 us; split 30).
 //
 // The kernel is a chain of dependent steps on one compute unit, so every step is short: requests are ordered by a histogram
 // of their lengths, scans go through registers, and the search for c tries sixteen lengths at a time, one per wavefront
@@ -100,6 +102,8 @@ constexpr int kItemInts = 8;
 constexpr int kCus = 256;             // compute units = workgroups that run at once
 constexpr int kMaxSlots = 2 * kCus;   // parts of a split batch, over all kv heads and head groups
 constexpr int kStartTiles = 8;
+constexpr int kTileWhole = 127, kTileSplit = 190, kSplitCost = 1650;   // 10 ns
+constexpr int kSplitUnits = 160;      // equal items in more workgroups than this are never split
 constexpr int kPartBits = 20;         // key tiles of a part
 constexpr int kSplitInts = 8;         // {first row, end row, first row of the request in Q, first slot, parts, 0, 0, 0}
 constexpr int kSlotFloats = kWaves * 64 * (64 + 2);   // per wavefront and lane: 64 of O^T, reference, row sum
@@ -252,6 +256,9 @@ __global__ __launch_bounds__(kSchedThreads) void attn_schedule_kernel(
     }
     longest = wave_max(longest);
     sum = wave_sum(sum);
+    const int share = (sum * units + kCus - 1) / kCus;   // key tiles per compute unit
+    const int whole = n * units <= kCus ? longest : max(longest, share + longest / 2);
+    const bool worth = kTileWhole * (long long)whole > kSplitCost + kTileSplit * (long long)share;
     // smallest part length for which all parts have room in one round (wavefronts 0 .. 7) or two (8 .. 15): eight lengths
     // between the last that did not fit and the first that did, until they meet
     const int room1 = kCus / units, room2 = 2 * kCus / units, half = wave >> 3;
@@ -261,7 +268,7 @@ __global__ __launch_bounds__(kSchedThreads) void attn_schedule_kernel(
     if (room2 >= n) lo2 = max(1, min(longest, (sum + room2 - 1) / room2)); else lo2 = longest;
     int turn = 0;
     __shared__ int fits[2][kSchedWaves];
-    while (lo1 < hi1 || lo2 < hi2) {
+    while (worth && (lo1 < hi1 || lo2 < hi2)) {
       const int lo = half ? lo2 : lo1, hi = half ? hi2 : hi1;
       const int c = lo + (int)(((long long)(hi - lo) * (wave & 7)) >> 3);   // wavefront 0 of the eight tries lo itself
       int p = 0;
@@ -282,15 +289,12 @@ __global__ __launch_bounds__(kSchedThreads) void attn_schedule_kernel(
       narrow((unsigned)(ok >> 8) & 255u, lo2, hi2);
       ++turn;
     }
-    const int rounds_whole = (n * units + kCus - 1) / kCus;
-    const int share = (sum * units + kCus - 1) / kCus;   // key tiles per compute unit
-    const int whole = rounds_whole == 1 ? longest : max(longest, share + longest / 2);
-    int best_c = longest, best_cost = rounds_whole * kStartTiles + whole - kStartTiles;   // (the split also merges)
-    if (room1 >= n && kStartTiles + hi1 < best_cost) {
-      best_cost = kStartTiles + hi1;
-      best_c = hi1;
+    int best_c = longest;
+    if (worth) {
+      // one round of workgroups, which cost about kStartTiles tiles before and after their loop, or two
+      const bool one = room1 >= n && kStartTiles + hi1 <= 2 * (kStartTiles + hi2);
+      best_c = one ? hi1 : hi2;
     }
-    if (room2 >= n && 2 * (kStartTiles + hi2) < best_cost) best_c = hi2;
     // scans of the parts (place in the list) and, packed, of the parts of split items (slot) and of the split items
     int4 a = {0, 0, 0, 0}, b = {0, 0, 0, 0};
     int parts = 0;
@@ -934,7 +938,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
 // Bound by latency: eight parts' states travel together and are folded into a running maximum, so the usual item takes one or
 // two trips to memory (references first and outputs after them, four parts at a time: 10.7 us for 10 parts of 3 items,
 // now 6.5).
-constexpr int kMergeThreads = 512, kMergeParts = 8, kMergeGrid = 512;   // (most calls merge little or nothing)
+constexpr int kMergeThreads = 512, kMergeParts = 8, kMergeGrid = 256;   // (most calls merge little or nothing)
 __global__ __launch_bounds__(kMergeThreads) void attn_merge_kernel(AttnParams p) {
   const int n_hg = p.Hq / p.Hkv / p.heads_per_wg, units = p.Hkv * n_hg;
   const int n_work = p.n_items[1] * units * kWaves;
@@ -1014,8 +1018,9 @@ Layout layout_for(const skv_attn_desc* d, int32_t n_req, int64_t total_q_rows, b
   y.heads_per_wg = heads_per_wg_for(d->n_q_heads / d->n_kv_heads, fine);
   y.pos_per_wg = (kWaves / y.heads_per_wg) * kRowsPerWave;
   y.units = d->n_q_heads / y.heads_per_wg;
-  // with more workgroups than two rounds of the chip there is nothing to fill
-  y.max_parts = split && total_q_rows / y.pos_per_wg * y.units <= kMaxSlots && y.units <= kCus ? kMaxSlots / y.units : 0;
+  // where no split can come of it the merge is not launched either (it costs 4.7 us)
+  const bool few = total_q_rows / y.pos_per_wg * y.units <= kSplitUnits && (int64_t)n_req * y.units <= 2 * kMaxSlots && y.units <= kCus;
+  y.max_parts = split && few ? kMaxSlots / y.units : 0;
   y.max_items = total_q_rows / y.pos_per_wg + 2 * (int64_t)n_req + y.max_parts;   // per request: a short first tile and a ragged last one
   if (d->dtype != SKV_BF16) y.max_items = y.max_parts = 0;
   return y;
@@ -1119,11 +1124,9 @@ extern "C" int skv_prefill_attn(const skv_attn_desc* desc, int32_t n_req, const 
   // a workspace that holds the plain work list is enough: the call then splits nothing
   Layout y = layout_for(desc, n_req, total_q_rows, true, true);
   if (workspace_bytes < list_bytes(desc, y) + split_bytes(y)) y = layout_for(desc, n_req, total_q_rows, false, false);
-  // items of so few key tiles are never split (one round of them: 8 + c against at most `longest`; two: 16 + 2 c against at
-  // most 8 + 2.5 longest), so there is nothing to merge either
   const int64_t longest = ((int64_t)max_blocks * SKV_BLOCK_TOKENS + total_q_rows + kBN - 1) / kBN;
-  if (y.max_parts && longest <= ((y.max_items - y.max_parts) * y.units <= kCus ? kStartTiles + 1 : 4))
-    y = layout_for(desc, n_req, total_q_rows, true, false);
+  const bool one_round = (y.max_items - y.max_parts) * y.units <= kCus;   // otherwise `whole` is up to 2.5 times the longest item
+  if (y.max_parts && (one_round ? 2 : 5) * kTileWhole * longest <= 2 * kSplitCost) y = layout_for(desc, n_req, total_q_rows, true, false);
   if (!d_workspace || workspace_bytes < list_bytes(desc, y)) return SKV_ENOMEM;
   if ((uintptr_t)d_workspace & 15) return SKV_EINVAL;
   return prefill_attn_enqueue(desc, n_req, d_q, d_knew, d_vnew, d_q_off, total_q_rows, d_kpool, d_vpool, n_pages,
