@@ -1124,9 +1124,11 @@ extern "C" int skv_prefill_attn(const skv_attn_desc* desc, int32_t n_req, const 
   // a workspace that holds the plain work list is enough: the call then splits nothing
   Layout y = layout_for(desc, n_req, total_q_rows, true, true);
   if (workspace_bytes < list_bytes(desc, y) + split_bytes(y)) y = layout_for(desc, n_req, total_q_rows, false, false);
-  const int64_t longest = ((int64_t)max_blocks * SKV_BLOCK_TOKENS + total_q_rows + kBN - 1) / kBN;
-  const bool one_round = (y.max_items - y.max_parts) * y.units <= kCus;   // otherwise `whole` is up to 2.5 times the longest item
-  if (y.max_parts && (one_round ? 2 : 5) * kTileWhole * longest <= 2 * kSplitCost) y = layout_for(desc, n_req, total_q_rows, true, false);
+  // the device's rule on what the host knows (a table filled to its width, rows spread evenly, items of 0.7 of the longest on
+  // average): where it does not split, neither search nor merge are launched -- 3.2 us of a pass of 55
+  const int64_t longest = ((int64_t)max_blocks * SKV_BLOCK_TOKENS + total_q_rows / n_req) / kBN + 1;
+  const int64_t about = total_q_rows / y.pos_per_wg * y.units * longest * 7 / (10 * kCus);   // key tiles per compute unit
+  if (y.max_parts && kTileWhole * longest <= kSplitCost + kTileSplit * about) y = layout_for(desc, n_req, total_q_rows, true, false);
   if (!d_workspace || workspace_bytes < list_bytes(desc, y)) return SKV_ENOMEM;
   if ((uintptr_t)d_workspace & 15) return SKV_EINVAL;
   return prefill_attn_enqueue(desc, n_req, d_q, d_knew, d_vnew, d_q_off, total_q_rows, d_kpool, d_vpool, n_pages,
