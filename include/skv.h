@@ -52,7 +52,11 @@ const char* skv_strerror(int code);
 /* hipError_t of the last failing HIP call on this thread (0 if none). */
 int skv_last_hip_error(void);
 
-typedef struct skv_tree skv_tree; /* opaque host handle; owns host bookkeeping only */
+/* Opaque host handle; owns host memory only: a copy of the index's structure and, from the first skv_tree_insert,
+ * skv_evict or skv_tree_compact on, 1 MiB of pinned memory that small transfers go through (without it, or where they do not
+ * fit, they are copies from ordinary memory).  skv_tree_destroy leaves the pinned piece to the next tree that needs one; that
+ * tree frees all but four of those it finds. */
+typedef struct skv_tree skv_tree;
 
 /* Cached side: n_seq token sequences, each a whole number of 16-token blocks, with one
  * (private_tag, creator_id, KV address) triple per block (Section 4.3.1: every entry

@@ -9,6 +9,7 @@
 #include <algorithm>
 #include <cstdlib>
 #include <cstring>
+#include <mutex>
 #include <new>
 #include <vector>
 
@@ -84,34 +85,57 @@ struct SkvHostMirror {
   // every call that enqueues such a kernel marks the copy stale and the next reader fetches it again.
   std::vector<int32_t> vis;           // [n_blocks]
   bool vis_stale = false;
-  // Pinned memory the write side exchanges data with the device through (grown as needed, the tree's until it goes; every
-  // call that uses it waits for its own kernels before it returns), and arrays kept from call to call: fresh ones of these
-  // sizes come from the system page by page on every call.
+  // Pinned memory small transfers go through: kStageBytes of it from the first write on, null before, and as long as none is
+  // to be had.  Every call that uses it waits for its own kernels before it returns.
   char* stage = nullptr;
-  size_t stage_bytes = 0;
-  std::vector<uint8_t> prot;
-  std::vector<int32_t> spare_tok, spare_canon, spare_page, spare_vis, spare_flat_of;   // compaction builds here, then swaps
-  ~SkvHostMirror() {
-    if (stage) (void)hipHostFree(stage);
-  }
-  // room for every block the slab can hold: an append never moves the array
-  void reserve_blocks() {
-    const size_t n = (size_t)cap_blocks;
-    if (tok.capacity() < n * 16) tok.reserve(n * 16);
-    for (std::vector<int32_t>* v : {&canon, &page, &vis, &node_of, &flat_of})
-      if (v->capacity() < n) v->reserve(n);
-  }
-  int reserve_stage(size_t bytes) {
-    if (bytes <= stage_bytes) return SKV_OK;
-    if (stage) SKV_HIP(hipHostFree(stage));
-    stage = nullptr;
-    stage_bytes = 0;
-    const size_t n = std::max<size_t>(2 * bytes, 1 << 16);
-    SKV_HIP(hipHostMalloc((void**)&stage, n, hipHostMallocPortable));
-    stage_bytes = n;
-    return SKV_OK;
-  }
+  ~SkvHostMirror();
+  bool have_stage();
 };
+
+// Stages of trees that are gone.  skv_tree_destroy makes no runtime call (a collector may run it at any time, inside a stream
+// capture too, where freeing pinned memory is an error): it leaves the stage here, linked through its first bytes.  The next
+// tree to write takes one over, which also spares it the first touch of fresh pinned pages (0.4 ms per MB), and frees what is
+// here beyond kParkedStages.
+namespace {
+constexpr size_t kStageBytes = 1 << 20;   // larger transfers are copies from and to ordinary memory (0.05 to 0.07 ms per MB)
+constexpr int kParkedStages = 4;
+struct Parked {
+  Parked* next;
+};
+std::mutex parked_lock;
+Parked* parked = nullptr;
+}  // namespace
+
+SkvHostMirror::~SkvHostMirror() {
+  if (!stage) return;
+  const std::lock_guard<std::mutex> hold(parked_lock);
+  parked = new (stage) Parked{parked};
+}
+
+bool SkvHostMirror::have_stage() {
+  if (stage) return true;
+  Parked* rest = nullptr;
+  {
+    const std::lock_guard<std::mutex> hold(parked_lock);
+    Parked** at = &parked;
+    if (parked) {
+      stage = (char*)parked;
+      parked = parked->next;
+    }
+    for (int k = 0; *at && k < kParkedStages; ++k) at = &(*at)->next;
+    std::swap(rest, *at);
+  }
+  while (rest) {
+    Parked* const p = rest;
+    rest = p->next;
+    (void)hipHostFree(p);
+  }
+  if (!stage && hipHostMalloc((void**)&stage, kStageBytes, hipHostMallocPortable) != hipSuccess) {
+    stage = nullptr;
+    (void)hipGetLastError();   // no failure of the call: it copies instead
+  }
+  return stage != nullptr;
+}
 
 namespace {
 
@@ -242,10 +266,9 @@ __global__ void fill_planes_kernel(uint32_t* p, size_t from, size_t n, int plane
 
 // Words moved between the slab and the pinned memory, several spans in one launch (blockIdx.y).  One launch and one wait take
 // the place of a copy per array, each through a staging buffer of the runtime's (64 requests, 7.7 k new blocks in an index of
-// 67 k: insertion 192 -> 145 us, eviction 225 -> 150, a compaction 1.39 -> 0.9 ms, the arrays kept from call to call included).
+// 67 k: insertion 192 -> 145 us, eviction 225 -> 150).
 constexpr int kMaxSpans = 16;
 struct Spans {
-  int n = 0;
   uint32_t* dev[kMaxSpans];
   uint32_t* host[kMaxSpans];
   size_t words[kMaxSpans];
@@ -484,32 +507,71 @@ extern "C" int skv_tree_build(const skv_tree_desc* d, void* d_slab, size_t bytes
   return SKV_OK;
 }
 
-// Spans of the staging memory, laid out one behind the other.
+// What one call moves between the slab and host memory: through the stage, one span behind the other, where it fits, otherwise
+// a copy per span.
 namespace {
 struct Mover {
   SkvHostMirror* m;
-  Spans s;
-  size_t used = 0;
-  void* add(size_t dev_off, size_t bytes) {   // -> the span's place in the staging memory
-    char* at = m->stage + used;
-    if (bytes == 0) return at;
-    s.dev[s.n] = (uint32_t*)(m->base + dev_off);
-    s.host[s.n] = (uint32_t*)at;
-    s.words[s.n++] = bytes / 4;
-    used += (bytes + 15) & ~(size_t)15;
-    return at;
-  }
-  void put(size_t dev_off, const void* src, size_t bytes) {
-    if (bytes) memcpy(add(dev_off, bytes), src, bytes);
+  int n = 0;
+  size_t bytes = 0;   // in the stage
+  size_t dev_off[kMaxSpans], len[kMaxSpans];
+  void* host[kMaxSpans];
+  static size_t padded(size_t b) { return (b + 15) & ~(size_t)15; }
+  void add(size_t off, const void* p, size_t b) {   // p stays valid until the call's wait
+    if (!b) return;
+    if (n < kMaxSpans) {
+      dev_off[n] = off;
+      host[n] = const_cast<void*>(p);
+      len[n] = b;
+    }
+    bytes += padded(b);
+    ++n;
   }
   template <bool kUp>
-  int enqueue(hipStream_t st) {
-    if (s.n) {
-      size_t longest = 0;
-      for (int k = 0; k < s.n; ++k) longest = std::max(longest, s.words[k]);
-      const unsigned wide = (unsigned)std::min<size_t>((longest + 255) / 256, 512);
-      move_spans_kernel<kUp><<<dim3(wide, s.n), 256, 0, st>>>(s);
-      SKV_HIP(hipGetLastError());
+  int launch(hipStream_t st) const {
+    Spans s;
+    size_t at = 0, longest = 0;
+    for (int k = 0; k < n; ++k) {
+      s.dev[k] = (uint32_t*)(m->base + dev_off[k]);
+      s.host[k] = (uint32_t*)(m->stage + at);
+      s.words[k] = len[k] / 4;
+      longest = std::max(longest, s.words[k]);
+      if (kUp) memcpy(m->stage + at, host[k], len[k]);
+      at += padded(len[k]);
+    }
+    if (n == 0) return SKV_OK;
+    move_spans_kernel<kUp><<<dim3((unsigned)std::min<size_t>((longest + 255) / 256, 512), n), 256, 0, st>>>(s);
+    SKV_HIP(hipGetLastError());
+    return SKV_OK;
+  }
+  // Enqueues the upload; `behind`: bytes the caller wants in the stage behind the spans.  *staged: it went through the stage.
+  int up(hipStream_t st, size_t behind = 0, bool* staged = nullptr) {
+    if (n > kMaxSpans) return SKV_EINVAL;
+    const bool fits = bytes + behind <= kStageBytes && m->have_stage();
+    if (staged) *staged = fits;
+    if (fits) return launch<true>(st);
+    for (int k = 0; k < n; ++k) SKV_HIP(hipMemcpyAsync(m->base + dev_off[k], host[k], len[k], hipMemcpyHostToDevice, st));
+    return SKV_OK;
+  }
+  // Fetches the spans and waits.  `in_place`: they may stay in the stage (-> true there), behind one another.
+  int down(hipStream_t st, bool* in_place = nullptr) {
+    if (n > kMaxSpans) return SKV_EINVAL;
+    const bool fits = bytes <= kStageBytes && m->have_stage();
+    if (fits) {
+      const int rc = launch<false>(st);
+      if (rc) return rc;
+    } else {
+      for (int k = 0; k < n; ++k) SKV_HIP(hipMemcpyAsync(host[k], m->base + dev_off[k], len[k], hipMemcpyDeviceToHost, st));
+    }
+    SKV_HIP(hipStreamSynchronize(st));
+    if (in_place) {
+      *in_place = fits;
+    } else if (fits) {
+      size_t at = 0;
+      for (int k = 0; k < n; ++k) {
+        memcpy(host[k], m->stage + at, len[k]);
+        at += padded(len[k]);
+      }
     }
     return SKV_OK;
   }
@@ -835,7 +897,6 @@ extern "C" int skv_tree_insert(skv_tree* t, int32_t n_req, const int32_t* req_of
   const std::vector<uint8_t> used0 = m->page_used;
   const std::vector<int32_t> filled0 = m->filled, parent0 = m->parent, node_of0 = m->node_of;
   const size_t slots_used0 = m->slots_used, tok0 = m->tok.size(), blocks0 = m->canon.size(), in0 = m->flat_of.size();
-  m->reserve_blocks();
   Inserter ins{t, m, t->dev.n_blocks, t->n_in_blocks, {}, {}, SIZE_MAX, 0, SIZE_MAX, 0};
   hipStream_t st = (hipStream_t)stream;
   // The requester's own path depends on the visibility bits.  The host's copy of them is exact unless a
@@ -870,26 +931,23 @@ extern "C" int skv_tree_insert(skv_tree* t, int32_t n_req, const int32_t* req_of
   // upload: the appended block records, then the spans of node and slot records that changed
   const int64_t nb0 = t->dev.n_blocks, nin0 = t->n_in_blocks, add = ins.n_blocks - nb0;
   if (private_copies && add > 0) t->has_copies = 1;
-  const size_t n_node = ins.node_hi > ins.node_lo ? ins.node_hi - ins.node_lo : 0, n_slot = ins.slot_hi > ins.slot_lo ? ins.slot_hi - ins.slot_lo : 0;
-  int rc = m->reserve_stage((size_t)add * 84 + (n_node + n_slot) * 16 + 16 * kMaxSpans);
-  if (rc) return rc;
-  Mover up{m, {}};
-  if (add > 0) {
-    up.put(m->L.tok + (size_t)nb0 * 64, &m->tok[(size_t)nb0 * 16], (size_t)add * 64);
-    up.put(m->L.page + (size_t)nb0 * 4, ins.page.data(), (size_t)add * 4);
-    up.put(m->L.meta + (size_t)nb0 * 4, ins.meta.data(), (size_t)add * 4);
-    int32_t* canon = (int32_t*)up.add(m->L.canon + (size_t)nb0 * 4, (size_t)add * 4);
-    int32_t* flat_of = (int32_t*)up.add(m->L.flat_of + (size_t)nin0 * 4, (size_t)add * 4);
-    uint32_t* epoch = (uint32_t*)up.add(m->L.epoch + (size_t)nb0 * 4, (size_t)add * 4);
-    for (int64_t i = 0; i < add; ++i) {
-      canon[i] = (int32_t)(nin0 + i);
-      flat_of[i] = (int32_t)(nb0 + i);
-      epoch[i] = t->dev.cur_epoch;
-    }
+  std::vector<int32_t> ids(3 * (size_t)add);   // canon, flat_of, epoch of the new blocks
+  for (int64_t i = 0; i < add; ++i) {
+    ids[i] = (int32_t)(nin0 + i);
+    ids[add + i] = (int32_t)(nb0 + i);
+    ids[2 * add + i] = (int32_t)t->dev.cur_epoch;
   }
-  if (n_node) up.put(m->L.nodes + ins.node_lo * sizeof(SkvNode), &m->nodes[ins.node_lo], n_node * sizeof(SkvNode));
-  if (n_slot) up.put(m->L.slots + ins.slot_lo * sizeof(SkvSlot), &m->slots[ins.slot_lo], n_slot * sizeof(SkvSlot));
-  rc = up.enqueue<true>(st);
+  const size_t n_node = ins.node_hi > ins.node_lo ? ins.node_hi - ins.node_lo : 0, n_slot = ins.slot_hi > ins.slot_lo ? ins.slot_hi - ins.slot_lo : 0;
+  Mover up{m};
+  up.add(m->L.tok + (size_t)nb0 * 64, m->tok.data() + (size_t)nb0 * 16, (size_t)add * 64);
+  up.add(m->L.page + (size_t)nb0 * 4, ins.page.data(), (size_t)add * 4);
+  up.add(m->L.meta + (size_t)nb0 * 4, ins.meta.data(), (size_t)add * 4);
+  up.add(m->L.canon + (size_t)nb0 * 4, ids.data(), (size_t)add * 4);
+  up.add(m->L.flat_of + (size_t)nin0 * 4, ids.data() + add, (size_t)add * 4);
+  up.add(m->L.epoch + (size_t)nb0 * 4, ids.data() + 2 * add, (size_t)add * 4);
+  if (n_node) up.add(m->L.nodes + ins.node_lo * sizeof(SkvNode), &m->nodes[ins.node_lo], n_node * sizeof(SkvNode));
+  if (n_slot) up.add(m->L.slots + ins.slot_lo * sizeof(SkvSlot), &m->slots[ins.slot_lo], n_slot * sizeof(SkvSlot));
+  const int rc = up.up(st);
   if (rc) return rc;
   SKV_HIP(hipStreamSynchronize(st));
   t->dev.n_blocks = (int32_t)ins.n_blocks;
@@ -924,15 +982,15 @@ extern "C" int skv_evict(skv_tree* t, int64_t n_want, const int32_t* protect_ids
   const int64_t nb = t->dev.n_blocks;
   if (n_want == 0 || nb == 0) return SKV_OK;
   hipStream_t st = (hipStream_t)stream;
-  int rc = m->reserve_stage((size_t)nb * 4 + 16);
+  std::vector<uint32_t> own;
+  if ((size_t)nb * 4 > kStageBytes || !m->have_stage()) own.resize((size_t)nb);
+  Mover down{m};
+  down.add(m->L.epoch, own.data(), (size_t)nb * 4);
+  bool in_stage = false;
+  int rc = down.down(st, &in_stage);
   if (rc) return rc;
-  Mover down{m, {}};
-  const uint32_t* epoch = (const uint32_t*)down.add(m->L.epoch, (size_t)nb * 4);
-  rc = down.enqueue<false>(st);
-  if (rc) return rc;
-  SKV_HIP(hipStreamSynchronize(st));
-  std::vector<uint8_t>& prot = m->prot;
-  prot.assign((size_t)t->n_in_blocks, 0);
+  const uint32_t* const epoch = in_stage ? (const uint32_t*)m->stage : own.data();
+  std::vector<uint8_t> prot((size_t)t->n_in_blocks, 0);
   for (int64_t i = 0; i < n_protect; ++i)
     if (protect_ids[i] >= 0 && protect_ids[i] < t->n_in_blocks) prot[protect_ids[i]] = 1;
   // candidates: the last block of every childless node, oldest (epoch, block id) first
@@ -947,7 +1005,7 @@ extern "C" int skv_evict(skv_tree* t, int64_t n_want, const int32_t* protect_ids
   };
   for (int32_t n = 1; n < (int32_t)m->nodes.size(); ++n)
     if (m->kids[n] == 0 && m->nodes[n].n_blocks > 0) push_tail(n);
-  size_t node_lo = SIZE_MAX, node_hi = 0, slot_lo = SIZE_MAX, slot_hi = 0;
+  size_t node_lo = SIZE_MAX, node_hi = 0, slot_lo = SIZE_MAX, slot_hi = 0, blk_lo = SIZE_MAX, blk_hi = 0, id_lo = SIZE_MAX, id_hi = 0;
   std::vector<int32_t> gone;   // record and input id of every evicted block
   gone.reserve(2 * (size_t)std::min(n_want, nb));
   int64_t done = 0;
@@ -971,6 +1029,8 @@ extern "C" int skv_evict(skv_tree* t, int64_t n_want, const int32_t* protect_ids
     m->flat_of[c.id] = -1;
     gone.push_back(f);
     gone.push_back(c.id);
+    blk_lo = std::min(blk_lo, (size_t)f); blk_hi = std::max(blk_hi, (size_t)f + 1);
+    id_lo = std::min(id_lo, (size_t)c.id); id_hi = std::max(id_hi, (size_t)c.id + 1);
     nd.n_blocks--;
     node_lo = std::min(node_lo, (size_t)c.node); node_hi = std::max(node_hi, (size_t)c.node + 1);
     if (nd.n_blocks > 0) {
@@ -1001,17 +1061,21 @@ extern "C" int skv_evict(skv_tree* t, int64_t n_want, const int32_t* protect_ids
   m->live_blocks -= done;
   if (!done) return SKV_OK;
   const size_t n_node = node_hi - node_lo, n_slot = slot_hi > slot_lo ? slot_hi - slot_lo : 0;   // (a block is gone: so a node changed)
-  rc = m->reserve_stage((size_t)done * 8 + (n_node + n_slot) * 16 + 64);
+  Mover up{m};
+  up.add(m->L.nodes + node_lo * sizeof(SkvNode), &m->nodes[node_lo], n_node * sizeof(SkvNode));
+  if (n_slot) up.add(m->L.slots + slot_lo * sizeof(SkvSlot), &m->slots[slot_lo], n_slot * sizeof(SkvSlot));
+  bool staged;
+  rc = up.up(st, gone.size() * 4, &staged);
   if (rc) return rc;
-  Mover up{m, {}};
-  up.put(m->L.nodes + node_lo * sizeof(SkvNode), &m->nodes[node_lo], n_node * sizeof(SkvNode));
-  if (n_slot) up.put(m->L.slots + slot_lo * sizeof(SkvSlot), &m->slots[slot_lo], n_slot * sizeof(SkvSlot));
-  int32_t* rec_id = (int32_t*)(m->stage + up.used);
-  memcpy(rec_id, gone.data(), gone.size() * 4);
-  rc = up.enqueue<true>(st);
-  if (rc) return rc;
-  evict_kernel<<<grid_for((size_t)done, 256), 256, 0, st>>>((int32_t*)(m->base + m->L.canon), (int32_t*)(m->base + m->L.flat_of), rec_id, done);
-  SKV_HIP(hipGetLastError());
+  if (staged) {
+    int32_t* const rec_id = (int32_t*)(m->stage + up.bytes);
+    memcpy(rec_id, gone.data(), gone.size() * 4);
+    evict_kernel<<<grid_for((size_t)done, 256), 256, 0, st>>>((int32_t*)(m->base + m->L.canon), (int32_t*)(m->base + m->L.flat_of), rec_id, done);
+    SKV_HIP(hipGetLastError());
+  } else {
+    SKV_HIP(hipMemcpyAsync(m->base + m->L.canon + blk_lo * 4, &m->canon[blk_lo], (blk_hi - blk_lo) * 4, hipMemcpyHostToDevice, st));
+    SKV_HIP(hipMemcpyAsync(m->base + m->L.flat_of + id_lo * 4, &m->flat_of[id_lo], (id_hi - id_lo) * 4, hipMemcpyHostToDevice, st));
+  }
   SKV_HIP(hipStreamSynchronize(st));
   return SKV_OK;
 }
@@ -1032,17 +1096,17 @@ extern "C" int skv_tree_compact(skv_tree* t, int32_t* id_map, int64_t* n_in_bloc
   const size_t plane = t->dev.ctr_plane;
   // the state the kernels own, as the device has it: visibility, epochs, counter planes
   const size_t live = (size_t)m->live_blocks;
-  // room for what is read and, behind it, for what is written (a child takes four slots at the most, a table four at the least)
-  int rc = m->reserve_stage((size_t)nb_old * 4 * (2 + SKV_CTR_FIELDS) + live * (64 + 4 * (4 + 1 + SKV_CTR_FIELDS)) + m->nodes.size() * 16 * 9 + 32 * kMaxSpans);
+  std::vector<uint32_t> words((size_t)nb_old * (2 + SKV_CTR_FIELDS) + live * (1 + SKV_CTR_FIELDS));   // read, and behind it written
+  uint32_t* const state = words.data();
+  const int32_t* meta = (const int32_t*)state;
+  const uint32_t *epoch = state + nb_old, *ctr[SKV_CTR_FIELDS];
+  for (int q = 0; q < SKV_CTR_FIELDS; ++q) ctr[q] = state + (size_t)nb_old * (2 + q);
+  Mover down{m};
+  down.add(m->L.meta, state, (size_t)nb_old * 4);
+  down.add(m->L.epoch, state + nb_old, (size_t)nb_old * 4);
+  for (int q = 0; q < SKV_CTR_FIELDS; ++q) down.add(m->L.ctr + q * plane * 4, ctr[q], (size_t)nb_old * 4);
+  int rc = down.down(st);
   if (rc) return rc;
-  Mover down{m, {}};
-  const int32_t* meta = (const int32_t*)down.add(m->L.meta, (size_t)nb_old * 4);
-  const uint32_t* epoch = (const uint32_t*)down.add(m->L.epoch, (size_t)nb_old * 4);
-  const uint32_t* ctr[SKV_CTR_FIELDS];
-  for (int q = 0; q < SKV_CTR_FIELDS; ++q) ctr[q] = (const uint32_t*)down.add(m->L.ctr + q * plane * 4, (size_t)nb_old * 4);
-  rc = down.enqueue<false>(st);
-  if (rc) return rc;
-  SKV_HIP(hipStreamSynchronize(st));
   // dense input ids, old order kept
   std::vector<int32_t> new_id((size_t)nin_old, -1);
   int32_t n_ids = 0;
@@ -1052,16 +1116,11 @@ extern "C" int skv_tree_compact(skv_tree* t, int32_t* id_map, int64_t* n_in_bloc
   std::vector<SkvNode> nodes;
   std::vector<int32_t> kids, parent, old_of_new;
   std::vector<SkvSlot> slots;
-  std::vector<int32_t>&tok = m->spare_tok, &canon = m->spare_canon, &page = m->spare_page, &n_meta = m->spare_vis, &flat_of = m->spare_flat_of;
-  tok.reserve((size_t)m->cap_blocks * 16);
-  tok.resize(live * 16); canon.resize(live); page.resize(live); n_meta.resize(live);
-  flat_of.assign((size_t)n_ids, -1);
+  std::vector<int32_t> tok(live * 16), canon(live), page(live), n_meta(live), flat_of((size_t)n_ids, -1);
   const Layout& L = m->L;
-  Mover up{m, {}, down.used};
-  int32_t* const up_tok = (int32_t*)up.add(L.tok, live * 64);
-  uint32_t* const up_epoch = (uint32_t*)up.add(L.epoch, live * 4);
-  uint32_t* up_ctr[SKV_CTR_FIELDS];
-  for (int q = 0; q < SKV_CTR_FIELDS; ++q) up_ctr[q] = (uint32_t*)up.add(L.ctr + q * plane * 4, live * 4);
+  uint32_t* const n_epoch = state + (size_t)nb_old * (2 + SKV_CTR_FIELDS);
+  uint32_t* n_ctr[SKV_CTR_FIELDS];
+  for (int q = 0; q < SKV_CTR_FIELDS; ++q) n_ctr[q] = n_epoch + live * (1 + q);
   size_t filled_blocks = 0;
   std::vector<std::pair<int32_t, int32_t>> todo;   // (old node, new parent)
   todo.push_back({0, -1});
@@ -1086,9 +1145,8 @@ extern "C" int skv_tree_compact(skv_tree* t, int32_t* id_map, int64_t* n_in_bloc
       memcpy(&tok[g * 16], &m->tok[f * 16], n * 64);
       memcpy(&page[g], &m->page[f], n * 4);
       memcpy(&n_meta[g], meta + f, n * 4);
-      memcpy(up_tok + g * 16, &m->tok[f * 16], n * 64);
-      memcpy(up_epoch + g, epoch + f, n * 4);
-      for (int q = 0; q < SKV_CTR_FIELDS; ++q) memcpy(up_ctr[q] + g, ctr[q] + f, n * 4);
+      memcpy(n_epoch + g, epoch + f, n * 4);
+      for (int q = 0; q < SKV_CTR_FIELDS; ++q) memcpy(n_ctr[q] + g, ctr[q] + f, n * 4);
       filled_blocks += n;
     }
     if (np >= 0) {   // the hash of its first block keys the node in its parent's table
@@ -1118,13 +1176,17 @@ extern "C" int skv_tree_compact(skv_tree* t, int32_t* id_map, int64_t* n_in_bloc
   const int64_t nb = (int64_t)filled_blocks;
   if (nb != m->live_blocks) return SKV_EINVAL;   // the mirror lost track of a block: refuse rather than drop it
   // write everything back; counters and epochs of the free records start from zero again
-  up.put(L.page, page.data(), page.size() * 4);
-  up.put(L.meta, n_meta.data(), n_meta.size() * 4);
-  up.put(L.canon, canon.data(), canon.size() * 4);
-  up.put(L.flat_of, flat_of.data(), flat_of.size() * 4);
-  up.put(L.nodes, nodes.data(), nodes.size() * sizeof(SkvNode));
-  up.put(L.slots, slots.data(), slots.size() * sizeof(SkvSlot));
-  rc = up.enqueue<true>(st);
+  Mover up{m};
+  up.add(L.tok, tok.data(), live * 64);
+  up.add(L.page, page.data(), live * 4);
+  up.add(L.meta, n_meta.data(), live * 4);
+  up.add(L.canon, canon.data(), live * 4);
+  up.add(L.flat_of, flat_of.data(), flat_of.size() * 4);
+  up.add(L.nodes, nodes.data(), nodes.size() * sizeof(SkvNode));
+  up.add(L.slots, slots.data(), slots.size() * sizeof(SkvSlot));
+  up.add(L.epoch, n_epoch, live * 4);
+  for (int q = 0; q < SKV_CTR_FIELDS; ++q) up.add(L.ctr + q * plane * 4, n_ctr[q], live * 4);
+  rc = up.up(st);
   if (rc) return rc;
   if (m->cap_blocks > nb) {
     const size_t n = (size_t)(m->cap_blocks - nb);
@@ -1140,11 +1202,11 @@ extern "C" int skv_tree_compact(skv_tree* t, int32_t* id_map, int64_t* n_in_bloc
   m->parent = std::move(parent);
   m->slots = std::move(slots);
   m->slots_used = m->slots.size();
-  m->tok.swap(tok);
-  m->canon.swap(canon);
-  m->page.swap(page);
-  m->flat_of.swap(flat_of);
-  m->vis.swap(n_meta);   // just read back: exact
+  m->tok = std::move(tok);
+  m->canon = std::move(canon);
+  m->page = std::move(page);
+  m->flat_of = std::move(flat_of);
+  m->vis = std::move(n_meta);   // just read back: exact
   m->node_of.assign((size_t)nb, 0);
   for (size_t n = 1; n < m->nodes.size(); ++n)
     for (int32_t k = 0; k < m->nodes[n].n_blocks; ++k) m->node_of[(size_t)m->nodes[n].first + k] = (int32_t)n;
