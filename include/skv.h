@@ -375,7 +375,8 @@ int skv_prefill_attn_static(const skv_attn_desc* desc, int32_t n_req, const void
  * reads as zeros; rows of the last page beyond ctx_len are never used, whatever they hold.  Pools of several
  * layers are handled by passing the layer's base pointers.  The workspace (device, 16-byte aligned,
  * skv_decode_attn_workspace_size bytes) holds the partial softmax states of the key splits; it is overwritten
- * by every call.  Errors as skv_prefill_attn. */
+ * by every call.  The size never falls as n_req or max_blocks grow: the workspace of the largest batch serves every smaller
+ * one.  Errors as skv_prefill_attn, but SKV_ENOMEM for less than that size. */
 int skv_decode_attn_workspace_size(const skv_attn_desc* desc, int32_t n_req, int32_t max_blocks, size_t* bytes);
 int skv_decode_attn(const skv_attn_desc* desc, int32_t n_req, const void* d_q, const void* d_kpool,
                     const void* d_vpool, int32_t n_pages, const int32_t* d_ctx_len, const int32_t* d_page_table,

@@ -434,17 +434,23 @@ int check_decode(const skv_attn_desc* d) {
 // request of 2 / 4 / 6 / 8 tiles takes 5.8 / 8.0 / 10.5 / 13.3 us whole and 9.9 us cut; 200 requests of one kv head of up to
 // 12 / 24 tiles 18.8 / 32.9 us whole, 25.8 / 31.3 cut; 256 requests of 8 kv heads of up to 4 / 12 / 24 tiles 39 / 88 / 172
 // whole, 52 / 94 / 170 cut.
+int64_t max_tiles_of(int32_t max_blocks) { return ((int64_t)max_blocks * SKV_BLOCK_TOKENS + kBN - 1) / kBN; }
+int64_t most_shares(const skv_attn_desc* d, int32_t n_req, int32_t max_blocks) {
+  return std::min<int64_t>(std::max(kSlots / d->n_kv_heads, 1), n_req * max_tiles_of(max_blocks));
+}
 int shares_for(const skv_attn_desc* d, int32_t n_req, int32_t max_blocks) {
-  const int64_t max_tiles = ((int64_t)max_blocks * SKV_BLOCK_TOKENS + kBN - 1) / kBN;
+  const int64_t max_tiles = max_tiles_of(max_blocks);
   const int64_t units = (int64_t)n_req * d->n_kv_heads;
   if (max_tiles <= (units < kSlots / 4 ? 5 : 16) || n_req * max_tiles > 0x7fffffff) return 0;
-  return (int)std::min<int64_t>(std::max(kSlots / d->n_kv_heads, 1), n_req * max_tiles);
+  return (int)most_shares(d, n_req, max_blocks);
 }
+// Room for shares whether the call takes them or not: the size never falls as n_req or max_blocks grow, so a workspace of the
+// largest batch serves every smaller one.
 struct Workspace {
   size_t part_m, part_l, part_o, bytes;
 };
 Workspace workspace_for(const skv_attn_desc* d, int32_t n_req, int32_t max_blocks) {
-  const size_t pieces = (size_t)2 * shares_for(d, n_req, max_blocks) * d->n_q_heads;
+  const size_t shares = (size_t)most_shares(d, n_req, max_blocks), pieces = 2 * shares * d->n_q_heads;
   Workspace w;
   w.part_m = skv_align256(((size_t)n_req + 1) * sizeof(int32_t));
   w.part_l = w.part_m + skv_align256(pieces * sizeof(float));

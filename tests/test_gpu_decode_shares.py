@@ -2,9 +2,10 @@
 inside a share, over many shares, empty; more requests than threads; fewer tiles than shares.  Tolerance of the decode tests."""
 import numpy as np
 import pytest
+import torch
 
 from paper_2508_08438_amd import inputs
-from test_gpu_decode import check
+from test_gpu_decode import check, device_run
 
 pytestmark = pytest.mark.gpu
 
@@ -30,3 +31,18 @@ def test_shares(case):
 def test_both_sides_of_the_rule(n_req, blocks, hkv):
     dw = inputs.decode_workload(seed=n_req + blocks, ctx=[16 * blocks - 3] * n_req, hard=True)
     check(dw, f"{n_req} x {blocks} blocks")
+
+
+def test_workspace_of_a_larger_batch():
+    from paper_2508_08438_amd import binding as skv
+    desc = skv.attn_desc(32, 8, 128, "bf16")
+    ws = torch.empty(skv.skv_decode_attn_workspace_size(desc, 256, 64), dtype=torch.uint8, device="cuda:0")
+    for n_req in (1, 4, 15, 16, 17, 200):
+        dw = inputs.decode_workload(seed=n_req, ctx=G.integers(0, 1025, n_req), hard=True)
+        table = np.full((n_req, 64), -1, np.int32)
+        table[:, : dw.max_blocks] = dw.page_table
+        dw.page_table = table
+        q, kpool, vpool, want = device_run(dw)
+        out = torch.full_like(want, 7.0)
+        skv.skv_decode_attn(desc, q, kpool, vpool, torch.from_numpy(dw.ctx_len).to(q.device), torch.from_numpy(table).to(q.device), 64, out, ws)
+        assert torch.equal(out, want)
