@@ -40,10 +40,11 @@ struct DecParams {
   const void *q, *kpool, *vpool;
   void* out;
   const int32_t *ctx_len, *page_table;
-  int32_t* first_tile;              // [n_req + 1] tiles of the requests before this one
+  int4* cuts;                       // [n_cuts] a request that was cut (-1: none), its first and end tile, all tiles
   float *part_m, *part_l, *part_o;  // [2 * n_shares][Hkv][G] (x d for part_o)
   int n_req, max_blocks, n_pages, Hq, Hkv, G;
   int n_shares;                     // workgroups per kv head the tiles are dealt to; 0: one workgroup per request
+  int n_cuts;                       // n_req: by request; n_shares - 1 where that is less: by the share of the first piece
   float scale;
 };
 
@@ -89,7 +90,14 @@ __global__ __launch_bounds__(kThreads, 2) void decode_attn_kernel(DecParams p) {
     const int per = (p.n_req + kThreads - 1) / kThreads;   // requests per thread, consecutive ones
     const int r0 = min(tid * per, p.n_req), r1 = min(r0 + per, p.n_req);
     int own = 0;
-    for (int i = r0; i < r1; ++i) own += tiles_of(p, i);
+    for (int i = r0; i < r1; ++i) {
+      const int nt = tiles_of(p, i);
+      own += nt;
+      if (nt == 0 && i % p.n_shares == share) {   // an empty context: no share holds a tile of it
+        u32x4* const dst = (u32x4*)((__bf16*)p.out + ((size_t)i * p.Hq + kvh * G) * kD);
+        for (int k = 0; k < G * kD / 8; ++k) dst[k] = u32x4{0u, 0u, 0u, 0u};
+      }
+    }
     int upto = own;
     for (int o = 1; o < 64; o <<= 1) {
       const int x = __shfl_up(upto, o);
@@ -105,21 +113,27 @@ __global__ __launch_bounds__(kThreads, 2) void decode_attn_kernel(DecParams p) {
       total += x;
     }
     int before = upto - own;
+    const int n = min(p.n_shares, total);
     if (blockIdx.x == 0) {   // the merge kernel finds its pieces from these
+      const bool by_req = p.n_cuts == p.n_req;
+      if (!by_req) {
+        for (int i = tid; i < p.n_cuts; i += kThreads) p.cuts[i].x = -1;
+        __syncthreads();
+      }
       int x = before;
       for (int i = r0; i < r1; ++i) {
-        p.first_tile[i] = x;
-        x += tiles_of(p, i);
+        const int nt = tiles_of(p, i), i0 = nt > 0 ? share_of(x, total, n) : 0;
+        const bool cut = nt > 0 && x + nt > share_begin(i0 + 1, total, n);
+        if (by_req || cut) p.cuts[by_req ? i : i0] = make_int4(cut ? i : -1, x, x + nt, total);
+        x += nt;
       }
-      if (tid == 0) p.first_tile[p.n_req] = total;
     }
-    const int n = min(p.n_shares, total);
     if (share >= n) return;
     const int begin = share_begin(share, total, n);
     left = share_begin(share + 1, total, n) - begin;
     if (before <= begin && begin < upto) {
-      int i = r0;
-      for (int nt = tiles_of(p, i); before + nt <= begin; nt = tiles_of(p, i)) {
+      int i = r0, nt = tiles_of(p, i);
+      for (; before + nt <= begin; nt = tiles_of(p, i)) {
         before += nt;
         ++i;
       }
@@ -139,7 +153,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_attn_kernel(DecParams p) {
   const int t1 = p.n_shares > 0 ? min(n_tiles, t0 + left) : n_tiles;
 
   if (t0 >= t1) {  // nothing cached
-    if (p.n_shares > 0) continue;   // (the merge kernel writes the zeros; a tile is left, so a request follows)
+    if (p.n_shares > 0) continue;   // (a tile is left, so a request follows)
     for (int i = tid; i < G * kD; i += kThreads)
       ((__bf16*)p.out)[((size_t)r * p.Hq + kvh * G) * kD + i] = (__bf16)0.f;
     return;
@@ -355,27 +369,24 @@ __global__ __launch_bounds__(kThreads, 2) void decode_attn_kernel(DecParams p) {
   }
 }
 
-// Merge of the pieces of the requests that were cut: one workgroup per (request, query head).  Bound by latency, so no load
+// Merge of the pieces of the requests that were cut: one workgroup per (entry of the list, query head).  Bound by latency, so no load
 // waits for another: the weights of up to kThreads pieces are taken at once, one piece per thread, and the eight
 // half-wavefronts then sum every eighth piece's output, 16 bytes a lane, four pieces in flight each.
 __global__ __launch_bounds__(kThreads) void decode_merge_kernel(DecParams p) {
   constexpr int kTeams = kThreads / 32;
   __shared__ float wgt[kThreads], red_m[kWaves], red_l[kWaves];
   __shared__ f32x4 red_o[kTeams][32];
-  const int r = blockIdx.x / p.Hq, h = blockIdx.x % p.Hq;
-  const int kvh = h / p.G, head = h % p.G;
-  const int tid = threadIdx.x, team = tid >> 5, d4 = tid & 31;
-  const float c = p.scale * kLog2e;
-  const int tile0 = p.first_tile[r], tile1 = p.first_tile[r + 1], total = p.first_tile[p.n_req];
-  u32x2* const dst = (u32x2*)((__bf16*)p.out + ((size_t)r * p.Hq + h) * kD + 4 * d4);
-  if (tile0 == tile1) {   // an empty context
-    if (tid < 32) *dst = u32x2{0u, 0u};
-    return;
-  }
+  const int h = blockIdx.x % p.Hq;
+  const int4 cut = p.cuts[blockIdx.x / p.Hq];
+  if (cut.x < 0) return;
+  const int r = cut.x, tile0 = cut.y, tile1 = cut.z, total = cut.w;
   const int n = min(p.n_shares, total);
   const int i0 = share_of(tile0, total, n), i1 = share_of(tile1 - 1, total, n);
   const int pieces = i1 - i0 + 1;
-  if (pieces == 1) return;   // finished by that share
+  const int kvh = h / p.G, head = h % p.G;
+  const int tid = threadIdx.x, team = tid >> 5, d4 = tid & 31;
+  const float c = p.scale * kLog2e;
+  u32x2* const dst = (u32x2*)((__bf16*)p.out + ((size_t)r * p.Hq + h) * kD + 4 * d4);
   auto piece = [&](int j) { return ((size_t)(2 * (i0 + j) + (j == 0 ? 1 : 0)) * p.Hkv + kvh) * p.G + head; };
   float m0 = -INFINITY, ms = -INFINITY;   // this thread's first piece (all of them, as a rule); the largest of all
   for (int s = tid; s < pieces; s += kThreads) {
@@ -452,10 +463,10 @@ struct Workspace {
 Workspace workspace_for(const skv_attn_desc* d, int32_t n_req, int32_t max_blocks) {
   const size_t shares = (size_t)most_shares(d, n_req, max_blocks), pieces = 2 * shares * d->n_q_heads;
   Workspace w;
-  w.part_m = skv_align256(((size_t)n_req + 1) * sizeof(int32_t));
+  w.part_m = skv_align256(shares * sizeof(int4));
   w.part_l = w.part_m + skv_align256(pieces * sizeof(float));
   w.part_o = w.part_l + skv_align256(pieces * sizeof(float));
-  w.bytes = w.part_o + pieces * kD * sizeof(float);
+  w.bytes = std::max<size_t>(w.part_o + pieces * kD * sizeof(float), 256);
   return w;
 }
 
@@ -494,15 +505,16 @@ extern "C" int skv_decode_attn(const skv_attn_desc* desc, int32_t n_req, const v
   DecParams p;
   p.q = d_q; p.kpool = d_kpool; p.vpool = d_vpool; p.out = d_out;
   p.ctx_len = d_ctx_len; p.page_table = d_page_table;
-  p.first_tile = (int32_t*)ws;
+  p.cuts = (int4*)ws;
   p.part_m = (float*)(ws + w.part_m); p.part_l = (float*)(ws + w.part_l); p.part_o = (float*)(ws + w.part_o);
   p.n_req = n_req; p.max_blocks = max_blocks; p.n_pages = n_pages;
   p.Hq = desc->n_q_heads; p.Hkv = desc->n_kv_heads; p.G = desc->n_q_heads / desc->n_kv_heads;
   p.n_shares = shares; p.scale = skv_softmax_scale(desc);
+  p.n_cuts = std::min(n_req, shares - 1);
   decode_attn_kernel<<<(int)grid, kThreads, 0, st>>>(p);
   SKV_HIP(hipGetLastError());
-  if (shares) {
-    decode_merge_kernel<<<n_req * desc->n_q_heads, kThreads, 0, st>>>(p);
+  if (shares > 1) {
+    decode_merge_kernel<<<p.n_cuts * desc->n_q_heads, kThreads, 0, st>>>(p);
     SKV_HIP(hipGetLastError());
   }
   return SKV_OK;

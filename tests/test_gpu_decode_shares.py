@@ -33,6 +33,17 @@ def test_both_sides_of_the_rule(n_req, blocks, hkv):
     check(dw, f"{n_req} x {blocks} blocks")
 
 
+@pytest.mark.parametrize("n_req,hkv,width", [(600, 8, 512), (513, 1, 300), (512, 1, 300), (511, 1, 300), (64, 8, 700), (63, 8, 700)])
+def test_wide_tables(n_req, hkv, width):
+    # the table says little about the contexts: many requests of a tile or none, some cut, both forms of the list of cut requests
+    ctx = np.concatenate([G.choice([0, 0, 1, 16, 63, 64, 65, 130], n_req - 4), [3000, 0, 900, 0]])
+    dw = inputs.decode_workload(seed=n_req + hkv, ctx=ctx, hard=True, attn=inputs.AttnShape(2 * hkv, hkv, 128, "bf16"))
+    table = np.full((n_req, width), -1, np.int32)
+    table[:, : dw.max_blocks] = dw.page_table
+    dw.page_table = table
+    check(dw, f"wide {n_req}", reqs=sorted({*range(0, n_req, 23), n_req - 4, n_req - 3, n_req - 2, n_req - 1}))
+
+
 def test_workspace_of_a_larger_batch():
     from paper_2508_08438_amd import binding as skv
     desc = skv.attn_desc(32, 8, 128, "bf16")
