@@ -5,7 +5,7 @@ import pytest
 import torch
 
 from paper_2508_08438_amd import inputs
-from test_gpu_decode import check, device_run
+from test_gpu_decode import check, device_run, oracle_rows
 
 pytestmark = pytest.mark.gpu
 
@@ -57,3 +57,17 @@ def test_workspace_of_a_larger_batch():
         out = torch.full_like(want, 7.0)
         skv.skv_decode_attn(desc, q, kpool, vpool, torch.from_numpy(dw.ctx_len).to(q.device), torch.from_numpy(table).to(q.device), 64, out, ws)
         assert torch.equal(out, want)
+
+
+@pytest.mark.parametrize("ctx,hq,hkv", [([32000], 32, 8), ([3000] * 4, 24, 2), ([60, 300, 1000] * 50, 8, 8), ([5000, 77, 900, 12000], 16, 1)])
+def test_only_the_output_is_rounded_to_bf16(ctx, hq, hkv):
+    # half a unit in the last of the result's eight significant bits: 2^-8 of it.  Weights are right to 2^-16, exponents, whose
+    # arguments stay below 128, to 2^-17: together below 2^-15 of the largest value.  (Weights of eight bits: 2^-8 of it.)
+    dw = inputs.decode_workload(seed=len(ctx), ctx=ctx, hard=True, attn=inputs.AttnShape(hq, hkv, 128, "bf16"))
+    reqs = list(range(len(ctx)))[:6]
+    q, kpool, vpool, out = device_run(dw)
+    reqs, _, want = oracle_rows(dw, q, reqs)
+    got = out[reqs].double().cpu().numpy().reshape(want.shape)
+    v_max = float(vpool[~vpool.isnan()].abs().max())
+    over = (np.abs(got - want) - np.abs(want) * 2.0 ** -8 * 1.001).max() / v_max
+    assert over <= 2.0 ** -15
