@@ -65,6 +65,8 @@ __device__ inline int share_of(int tile, int T, int n) {
 // Bound by HBM: 64 requests of 4096..16384 tokens, 8 kv heads (2.68 GB): 436 us = 6.15 TB/s; dealt by request and key range
 // in eight rounds, with most ranges of the shorter contexts empty, 487 us.  256 of 100..4000: 378 us (461).  One of 32000:
 // 31 us (53).
+// kShares false: one workgroup per request and kv head.
+template <bool kShares>
 __global__ __launch_bounds__(kThreads, 2) void decode_attn_kernel(DecParams p) {
   __shared__ __attribute__((aligned(16))) __bf16 smem[kStages * kBN * (kKsStride + kVsStride)];
   __shared__ int wave_tiles[kWaves];
@@ -86,7 +88,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_attn_kernel(DecParams p) {
 
   // ---- which tiles: `left` of them from tile t of request r on
   int r = share, t = 0, left = 0;
-  if (p.n_shares > 0) {
+  if constexpr (kShares) {
     const int per = (p.n_req + kThreads - 1) / kThreads;   // requests per thread, consecutive ones
     const int r0 = min(tid * per, p.n_req), r1 = min(r0 + per, p.n_req);
     int own = 0;
@@ -150,10 +152,10 @@ __global__ __launch_bounds__(kThreads, 2) void decode_attn_kernel(DecParams p) {
   ctx = max(0, min(ctx, p.max_blocks * SKV_BLOCK_TOKENS));
   const int n_tiles = (ctx + kBN - 1) / kBN;
   const int t0 = __builtin_amdgcn_readfirstlane(t);
-  const int t1 = p.n_shares > 0 ? min(n_tiles, t0 + left) : n_tiles;
+  const int t1 = kShares ? min(n_tiles, t0 + left) : n_tiles;
 
   if (t0 >= t1) {  // nothing cached
-    if (p.n_shares > 0) continue;   // (a tile is left, so a request follows)
+    if (kShares) continue;   // (a tile is left, so a request follows)
     for (int i = tid; i < G * kD; i += kThreads)
       ((__bf16*)p.out)[((size_t)r * p.Hq + kvh * G) * kD + i] = (__bf16)0.f;
     return;
@@ -359,7 +361,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_attn_kernel(DecParams p) {
 #pragma unroll
         for (int j = 0; j < 8; ++j) acc[j] += wgt * src[j];
       }
-      if (t0 > 0 || t1 < n_tiles) {   // a piece of a request
+      if (kShares && (t0 > 0 || t1 < n_tiles)) {   // a piece of a request
         const size_t part = ((size_t)(2 * share + (t0 == 0 ? 1 : 0)) * p.Hkv + kvh) * G;
         if ((tid & 15) == 0) {
           p.part_m[part + head] = ms;
@@ -376,6 +378,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_attn_kernel(DecParams p) {
       }
     }
   }
+  if (!kShares) return;
   left -= t1 - t0;
   if (left <= 0) return;
   __syncthreads();   // the merge area is read; the next request's tiles go there
@@ -455,9 +458,9 @@ int check_decode(const skv_attn_desc* d) {
 
 // Shares per kv head: one workgroup per slot of the chip (two or four rounds: slower throughout, up to 2 x for few requests).
 // 0, a workgroup per request and no merge, where contexts are so short that cutting them costs more than it gains: one
-// request of 2 / 4 / 6 / 8 tiles takes 5.8 / 8.0 / 10.5 / 13.3 us whole and 9.9 us cut; 200 requests of one kv head of up to
-// 12 / 24 tiles 18.8 / 32.9 us whole, 25.8 / 31.3 cut; 256 requests of 8 kv heads of up to 4 / 12 / 24 tiles 39 / 88 / 172
-// whole, 52 / 94 / 170 cut.
+// request of 2 / 4 / 6 / 8 tiles takes 5.8 / 8.0 / 10.5 / 13.3 us whole and 9.9 us cut; 16 of 8 kv heads of 11 / 16 tiles 18.5 /
+// 24.9 whole, 20.0 / 22.1 cut, and where only one of them is that long 15.6 / 17.6 cut; 64 of 8 kv heads of 11 / 16 tiles
+// 34.8 / 48.0 whole, 36.9 / 50.4 cut; 128 of one kv head of 11 / 16 tiles 18.5 / 24.7 whole, 27.9 / 29.9 cut.
 int64_t max_tiles_of(int32_t max_blocks) { return ((int64_t)max_blocks * SKV_BLOCK_TOKENS + kBN - 1) / kBN; }
 int64_t most_shares(const skv_attn_desc* d, int32_t n_req, int32_t max_blocks) {
   return std::min<int64_t>(std::max(kSlots / d->n_kv_heads, 1), n_req * max_tiles_of(max_blocks));
@@ -465,7 +468,7 @@ int64_t most_shares(const skv_attn_desc* d, int32_t n_req, int32_t max_blocks) {
 int shares_for(const skv_attn_desc* d, int32_t n_req, int32_t max_blocks) {
   const int64_t max_tiles = max_tiles_of(max_blocks);
   const int64_t units = (int64_t)n_req * d->n_kv_heads;
-  if (max_tiles <= (units < kSlots / 4 ? 5 : 16) || n_req * max_tiles > 0x7fffffff) return 0;
+  if (max_tiles <= (units < kSlots / 4 ? 5 : n_req <= 16 ? 11 : 16) || n_req * max_tiles > 0x7fffffff) return 0;
   return (int)most_shares(d, n_req, max_blocks);
 }
 // Room for shares whether the call takes them or not: the size never falls as n_req or max_blocks grow, so a workspace of the
@@ -524,7 +527,10 @@ extern "C" int skv_decode_attn(const skv_attn_desc* desc, int32_t n_req, const v
   p.Hq = desc->n_q_heads; p.Hkv = desc->n_kv_heads; p.G = desc->n_q_heads / desc->n_kv_heads;
   p.n_shares = shares; p.scale = skv_softmax_scale(desc);
   p.n_cuts = std::min(n_req, shares - 1);
-  decode_attn_kernel<<<(int)grid, kThreads, 0, st>>>(p);
+  if (shares == 0)
+    decode_attn_kernel<false><<<(int)grid, kThreads, 0, st>>>(p);
+  else
+    decode_attn_kernel<true><<<(int)grid, kThreads, 0, st>>>(p);
   SKV_HIP(hipGetLastError());
   if (shares > 1) {
     decode_merge_kernel<<<p.n_cuts * desc->n_q_heads, kThreads, 0, st>>>(p);
