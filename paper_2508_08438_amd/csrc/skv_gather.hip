@@ -15,65 +15,74 @@ constexpr int kUnroll = 8;  // 16-byte vectors in flight per thread and pool
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-// Every workgroup scans the matched lengths itself (a load per thread for up to 256 requests; the first workgroup also writes
-// the offsets) and finds the owner of a page in LDS: a kernel for the offsets in front cost more than that (one request
-// of 187 pages: 4.5 us and a launch).  The scan has kPref places; with more requests a place stands for several, in order.
-constexpr int kPref = 2048;
+// Where the output of every request starts, one workgroup.
+constexpr int kOffThreads = 1024, kOffPer = 4;
+__global__ __launch_bounds__(kOffThreads) void ctx_offsets_kernel(int n_req, const int32_t* __restrict__ matched_len,
+                                                                  int64_t* __restrict__ ctx_off) {
+  __shared__ int64_t red[kOffThreads / 64];
+  int64_t carry = 0;
+  if (threadIdx.x == 0) ctx_off[0] = 0;
+  for (int64_t base = 0; base < n_req; base += kOffThreads * kOffPer) {
+    const int64_t r0 = base + threadIdx.x * kOffPer;
+    int64_t v[kOffPer], own = 0, total;
+#pragma unroll
+    for (int k = 0; k < kOffPer; ++k) v[k] = r0 + k < n_req ? max(matched_len[r0 + k], 0) / SKV_BLOCK_TOKENS : 0;
+#pragma unroll
+    for (int k = 0; k < kOffPer; ++k) own += v[k];
+    int64_t x = carry + skv_block_scan<kOffThreads>(own, red, total) - own;
+    carry += total;
+#pragma unroll
+    for (int k = 0; k < kOffPer; ++k) {
+      x += v[k];
+      if (r0 + k < n_req) ctx_off[r0 + k + 1] = x * SKV_BLOCK_TOKENS;
+    }
+  }
+}
+
+// kScan: every workgroup scans the matched lengths itself (the first one also writes the offsets) and finds the owner of a page
+// in LDS.  A kernel for the offsets in front costs a launch, 4.5 us for one request, but reads the lengths once: one page each of
+// 16 / 256 / 512 requests 14.0 / 19.4 / 23.5 us scanned, 16.6 / 22.0 / 24.4 with that kernel; of 1024 / 4096 / 16384 33.6 / 158 /
+// 685 scanned, 33.7 / 113 / 432 with it; 40 pages each of 1024 1053 and 1044.
+constexpr int kPref = 512;
+template <bool kScan>
 __global__ __launch_bounds__(kThreads) void gather_pages_kernel(
     int n_req, const u32x4* __restrict__ kpool, const u32x4* __restrict__ vpool, int n_pages,
     const int32_t* __restrict__ matched_len, const int32_t* __restrict__ page_table, int max_blocks,
     int64_t* __restrict__ ctx_off, u32x4* __restrict__ kctx, u32x4* __restrict__ vctx, int64_t cap_pages,
     int page_vec /* 16-byte vectors per page */) {
-  __shared__ int64_t first[kPref + 1];   // pages before the requests of a place
-  __shared__ int64_t red[kThreads / 64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int per = max(1, (n_req + kPref - 1) / kPref);        // requests per place
-  const int places = (n_req + per - 1) / per;
-  const int own = (places + kThreads - 1) / kThreads;         // places per thread
-  const int r0 = min(threadIdx.x * own * per, n_req), r1 = min(r0 + own * per, n_req);
-  auto pages_of = [&](int r) { return max(matched_len[r], 0) / SKV_BLOCK_TOKENS; };
-  int64_t mine = 0;
-  for (int r = r0; r < r1; ++r) mine += pages_of(r);
-  int64_t upto = mine;
-  for (int o = 1; o < 64; o <<= 1) {
-    const int64_t x = __shfl_up(upto, o);
-    if (lane >= o) upto += x;
+  __shared__ int64_t first[kScan ? kPref + 1 : 1];   // pages before a request
+  int64_t total;
+  if constexpr (kScan) {
+    __shared__ int64_t red[kThreads / 64];
+    const int own = (n_req + kThreads - 1) / kThreads;         // requests per thread
+    const int r0 = min((int)threadIdx.x * own, n_req), r1 = min(r0 + own, n_req);
+    auto pages_of = [&](int r) { return max(matched_len[r], 0) / SKV_BLOCK_TOKENS; };
+    int64_t mine = 0;
+    for (int r = r0; r < r1; ++r) mine += pages_of(r);
+    int64_t at = skv_block_scan<kThreads>(mine, red, total) - mine;
+    for (int r = r0; r < r1; ++r) {
+      first[r] = at;
+      at += pages_of(r);
+      if (blockIdx.x == 0) ctx_off[r + 1] = at * SKV_BLOCK_TOKENS;
+    }
+    if (threadIdx.x == 0) {
+      first[n_req] = total;
+      if (blockIdx.x == 0) ctx_off[0] = 0;
+    }
+    __syncthreads();
+  } else {
+    total = ctx_off[n_req] / SKV_BLOCK_TOKENS;
   }
-  if (lane == 63) red[wave] = upto;
-  __syncthreads();
-  int64_t total = 0;
-#pragma unroll
-  for (int w = 0; w < kThreads / 64; ++w) {
-    const int64_t x = red[w];
-    if (w < wave) upto += x;
-    total += x;
-  }
-  int64_t at = upto - mine;
-  for (int r = r0; r < r1; ++r) {
-    if (r % per == 0) first[r / per] = at;
-    at += pages_of(r);
-    if (blockIdx.x == 0) ctx_off[r + 1] = at * SKV_BLOCK_TOKENS;
-  }
-  if (threadIdx.x == 0) {
-    first[places] = total;
-    if (blockIdx.x == 0) ctx_off[0] = 0;
-  }
-  __syncthreads();
+  auto pages_before = [&](int r) { return kScan ? first[r] : ctx_off[r] / SKV_BLOCK_TOKENS; };
   const int64_t end = min(total, cap_pages);
   for (int64_t p = blockIdx.x; p < end; p += gridDim.x) {
     // request that owns output page p: the last one with no more than p pages before it
-    int lo = 0, hi = places;  // invariant: first[lo] <= p < first[hi]
+    int lo = 0, hi = n_req;  // invariant: pages_before(lo) <= p < pages_before(hi)
     while (hi - lo > 1) {
       const int mid = (lo + hi) >> 1;
-      if (first[mid] <= p) lo = mid; else hi = mid;
+      if (pages_before(mid) <= p) lo = mid; else hi = mid;
     }
-    int64_t before = first[lo];
-    lo *= per;
-    if (per > 1)
-      for (int n = pages_of(lo); before + n <= p; n = pages_of(lo)) {
-        before += n;
-        ++lo;
-      }
+    const int64_t before = pages_before(lo);
     const int j = (int)(p - before);
     if (j >= max_blocks) continue;
     const int page = page_table[(size_t)lo * max_blocks + j];
@@ -213,7 +222,13 @@ extern "C" int skv_gather_kv(const skv_attn_desc* desc, int32_t n_req, const voi
   hipStream_t st = (hipStream_t)stream;
   const int64_t upper = (int64_t)n_req * max_blocks;  // pages the batch can reference at most
   const int grid = (int)(upper < 1 ? 1 : (upper < 256 * 16 ? upper : 256 * 16));
-  gather_pages_kernel<<<grid, kThreads, 0, st>>>(
+  auto gather = n_req <= kPref ? gather_pages_kernel<true> : gather_pages_kernel<false>;
+  if (n_req > kPref) {
+    ctx_offsets_kernel<<<1, kOffThreads, 0, st>>>(n_req, d_matched_len, d_ctx_off);
+    SKV_HIP(hipGetLastError());
+    if (max_blocks == 0) return SKV_OK;
+  }
+  gather<<<grid, kThreads, 0, st>>>(
       n_req, (const u32x4*)d_kpool, (const u32x4*)d_vpool, n_pages, d_matched_len, d_page_table, max_blocks, d_ctx_off,
       (u32x4*)d_kctx, (u32x4*)d_vctx, upper ? ctx_capacity_tokens / SKV_BLOCK_TOKENS : 0, (int)(page_bytes / 16));
   SKV_HIP(hipGetLastError());

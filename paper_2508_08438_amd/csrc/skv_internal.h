@@ -78,17 +78,17 @@ inline uint64_t skv_hash_block_host(const int32_t* tok) {
 
 #ifdef __HIPCC__
 // Inclusive scan over a workgroup of kThreads; `total` of all threads.  red: one place per wavefront.  Two barriers.
-template <int kThreads>
-__device__ inline int skv_block_scan(int v, int* red, int& total) {
+template <int kThreads, typename T>
+__device__ inline T skv_block_scan(T v, T* red, T& total) {
   constexpr int kWaves = kThreads / 64;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   for (int o = 1; o < 64; o <<= 1) {
-    const int x = __shfl_up(v, o);
+    const T x = __shfl_up(v, o);
     if (lane >= o) v += x;
   }
   if (lane == 63) red[wave] = v;
   __syncthreads();
-  int x = lane < kWaves ? red[lane] : 0, all = x;
+  T x = lane < kWaves ? red[lane] : 0, all = x;
   if (lane >= wave) x = 0;
   for (int o = kWaves / 2; o >= 1; o >>= 1) {
     x += __shfl_xor(x, o);
