@@ -101,47 +101,103 @@ struct Item {
   }
 };
 
-// Infinities and NaN, and values that round to infinity as bf16, have no pieces, and a matrix product carries them into rows
-// that do not see their key.  A tile that met one is taken again row by row, a wavefront each, over the keys the row sees.
-template <int D>
-__device__ __forceinline__ void rows_one_by_one(const SkvAttnF32Params& p, const Item& it) {
-  constexpr int kPer = D / 64;
-  const int lane = threadIdx.x & 63;
+// ---- rows in plain fp32 arithmetic: a wavefront per row and head.  A lane takes every 64th key with a softmax state
+// and an output of its own; in the end the lanes' outputs are summed so that each is left with every 64th value.
+struct Row {
+  int r, L, qbase, tok, h;   // request, its reused length, its first row in Q, the row, the head
+};
+// kKept: values of the output kept at once; with fewer than D the keys are scored again for the next.
+template <int D, int kKept>
+__device__ __forceinline__ void one_row(const SkvAttnF32Params& p, const Row& row) {
+  const int lane = threadIdx.x & 63, hk = row.h / (p.Hq / p.Hkv);
+  const int n_keys = row.L + row.tok - row.qbase + 1;
+  constexpr int kLoad = 64;   // values of a K or V row in flight; of 128, K and V at once would not fit the registers
   const float c = p.scale * kLog2e;
-  for (int row = it.row0 + (threadIdx.x >> 6); row < it.row1; row += kWaves) {
-    const size_t at = ((size_t)(it.qbase + row) * p.Hq + it.h) * D + lane;
-    const float* q = (const float*)p.q + at;
-    float m = -INFINITY, l = 0.f, acc[kPer];
+  // (one row for the whole wavefront: through the scalar unit, no vector registers)
+  const auto q = (const __attribute__((address_space(4))) float*)((uint64_t)p.q + ((uint64_t)row.tok * p.Hq + row.h) * (D * 4));
+#pragma unroll 1
+  for (int first = 0; first < D; first += kKept) {
+  float m = -INFINITY, l = 0.f, acc[kKept];
 #pragma unroll
-    for (int v = 0; v < kPer; ++v) acc[v] = 0.f;
-    for (int key = 0; key <= it.L + row; ++key) {
-      const float *kp = nullptr, *vp = nullptr;   // an absent page reads as zeros
-      if (key < it.L) {
-        const int g = key / SKV_BLOCK_TOKENS, page = g < p.max_blocks ? p.page_table[(size_t)it.r * p.max_blocks + g] : -1;
-        if (page >= 0 && page < p.n_pages) {
-          const size_t off = (((size_t)page * SKV_BLOCK_TOKENS + key % SKV_BLOCK_TOKENS) * p.Hkv + it.hk) * D + lane;
-          kp = (const float*)p.kpool + off;
-          vp = (const float*)p.vpool + off;
-        }
-      } else {
-        const size_t off = ((size_t)(it.qbase + key - it.L) * p.Hkv + it.hk) * D + lane;
-        kp = (const float*)p.knew + off;
-        vp = (const float*)p.vnew + off;
+  for (int d = 0; d < kKept; ++d) acc[d] = 0.f;
+  for (int key = lane; key < n_keys; key += 64) {
+    const float *kr = nullptr, *vr = nullptr;   // an absent page reads as zeros
+    if (key < row.L) {
+      const int g = key / SKV_BLOCK_TOKENS, page = g < p.max_blocks ? p.page_table[(size_t)row.r * p.max_blocks + g] : -1;
+      if (page >= 0 && page < p.n_pages) {
+        const size_t off = (((size_t)page * SKV_BLOCK_TOKENS + key % SKV_BLOCK_TOKENS) * p.Hkv + hk) * D;
+        kr = (const float*)p.kpool + off;
+        vr = (const float*)p.vpool + off;
       }
-      float s = 0.f;
-#pragma unroll
-      for (int v = 0; v < kPer; ++v) s = __builtin_fmaf(q[64 * v], kp ? kp[64 * v] : 0.f, s);
-      for (int x = 32; x >= 1; x >>= 1) s += __shfl_xor(s, x);
-      s *= c;
-      const float m_new = fmaxf(m, s), ref = m_new == -INFINITY ? 0.f : m_new;
-      const float alpha = __builtin_amdgcn_exp2f(m - ref), w = __builtin_amdgcn_exp2f(s - ref);
-      l = l * alpha + w;
-#pragma unroll
-      for (int v = 0; v < kPer; ++v) acc[v] = acc[v] * alpha + w * (vp ? vp[64 * v] : 0.f);
-      m = m_new;
+    } else {
+      const size_t off = ((size_t)(row.qbase + key - row.L) * p.Hkv + hk) * D;
+      kr = (const float*)p.knew + off;
+      vr = (const float*)p.vnew + off;
     }
+    float s = 0.f;
+    if (kr) {
+      f32x4 sum = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int v = 0; v < kPer; ++v) ((float*)p.out)[at + 64 * v] = acc[v] / l;
+      for (int d0 = 0; d0 < D; d0 += kLoad) {
+        f32x4 x[kLoad / 4];
+#pragma unroll
+        for (int i = 0; i < kLoad / 4; ++i) x[i] = *(const f32x4*)(kr + d0 + 4 * i);
+#pragma unroll
+        for (int d = 0; d < kLoad; ++d) sum[d % 4] = __builtin_fmaf(q[d0 + d], x[d / 4][d % 4], sum[d % 4]);
+        if (D > 64) __builtin_amdgcn_sched_barrier(0);
+      }
+      s = ((sum[0] + sum[1]) + (sum[2] + sum[3])) * c;
+    }
+    const float m_new = fmaxf(m, s), ref = m_new == -INFINITY ? 0.f : m_new;
+    const float alpha = __builtin_amdgcn_exp2f(m - ref), w = __builtin_amdgcn_exp2f(s - ref);
+    m = m_new;
+    l = l * alpha + w;
+    if (vr) {
+#pragma unroll
+      for (int d0 = 0; d0 < kKept; d0 += kLoad) {
+        f32x4 x[kLoad / 4];
+#pragma unroll
+        for (int i = 0; i < kLoad / 4; ++i) x[i] = *(const f32x4*)(vr + first + d0 + 4 * i);
+#pragma unroll
+        for (int d = 0; d < kLoad; ++d) acc[d0 + d] = acc[d0 + d] * alpha + w * x[d / 4][d % 4];
+        if (D > 64) __builtin_amdgcn_sched_barrier(0);
+      }
+    } else {
+#pragma unroll
+      for (int d = 0; d < kKept; ++d) acc[d] *= alpha;
+    }
+  }
+  float all = m;
+  for (int x = 32; x >= 1; x >>= 1) all = fmaxf(all, __shfl_xor(all, x));
+  const float f = __builtin_amdgcn_exp2f(m - (all == -INFINITY ? 0.f : all));   // a lane without a key: 0
+  l *= f;
+  for (int x = 32; x >= 1; x >>= 1) l += __shfl_xor(l, x);
+  float* const out = (float*)p.out + ((size_t)row.tok * p.Hq + row.h) * D + first + lane;
+#pragma unroll
+  for (int v = 0; v < kKept / 64; ++v) {
+    float a[64];
+#pragma unroll
+    for (int d = 0; d < 64; ++d) a[d] = acc[64 * v + d] * f;
+#pragma unroll
+    for (int n = 32; n >= 1; n >>= 1)   // the halves of the wavefront swap halves of what is left: lane i ends with value i
+#pragma unroll
+      for (int d = 0; d < n; ++d) {
+        const bool up = lane & n;
+        const float keep = up ? a[d + n] : a[d], give = up ? a[d] : a[d + n];
+        a[d] = keep + __shfl_xor(give, n);
+      }
+    out[64 * v] = a[0] / l;
+  }
+  }
+}
+
+// Infinities and NaN, and values that round to infinity as bf16, have no pieces, and a matrix product carries them into rows
+// that do not see their key.  A tile that met one is taken again row by row, over the keys the row sees.
+template <int D, int W>
+__device__ __forceinline__ void rows_one_by_one(const SkvAttnF32Params& p, const Item& it) {
+  for (int i = it.row0 + (threadIdx.x >> 6); i < it.row1; i += W) {
+    const Row row = {it.r, it.L, it.qbase, __builtin_amdgcn_readfirstlane(it.qbase + i), it.h};
+    one_row<D, 64>(p, row);   // (all 128 at once would cost the tile's loop registers)
   }
 }
 template <int kA>
@@ -387,7 +443,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 2 : 1) void attn_f32_kernel(Skv
   }
   l_run += other_half(l_run);
   if (__builtin_expect(__syncthreads_or(!all_finite(o, l_run)), 0)) {   // (Q is no longer needed behind this either)
-    rows_one_by_one<D>(p, it);
+    rows_one_by_one<D, kWaves>(p, it);
     return;
   }
 
@@ -603,7 +659,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_f32_tile_kernel(SkvAttnF32Pa
   l_run += other_half(l_run);
 
   if (__builtin_expect(__syncthreads_or(!all_finite(o, l_run)), 0)) {
-    rows_one_by_one<D>(p, it);
+    rows_one_by_one<D, kWaves>(p, it);
     return;
   }
   // ---- output, through LDS: whole rows leave together

@@ -1,0 +1,47 @@
+"""fp32 prefill attention is as exact as fp32: against the fp64 oracle, for each of its kernels and over the magnitudes fp32 has.
+
+Bound: a weight 2^x carries |x| 2^-24 from the rounding of its exponent's argument (|x| about 8 for the keys that count), its
+score and the sums less; as a 2-norm over results these are independent, and 8 * 2^-24 = 4.8e-7 is not reached.  With two bf16
+pieces instead of three the products are off by 2^-17 and the results by 2e-6 to 7e-6."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from test_gpu_parity import attn_case, run_attn
+
+pytestmark = pytest.mark.gpu
+REL = 8 * 2.0 ** -24
+
+G = np.random.default_rng(5)
+MANY = dict(S=G.choice([1, 2, 3, 33, 40], 600, p=[.5, .3, .1, .05, .05]), k=G.choice([0, 1, 2, 3, 9], 600))
+# query / kv heads, head size, rows and reused blocks per request
+CASES = {
+    "four wavefronts": (4, 2, 64, [40, 130, 7], [10, 30, 64]),
+    "four wavefronts, 128": (8, 2, 128, [40, 130, 7], [10, 30, 64]),
+    "one wavefront": (8, 4, 64, MANY["S"], MANY["k"]),
+    "one wavefront, 128": (8, 2, 128, MANY["S"][:300], MANY["k"][:300]),
+    "rows": (8, 4, 64, [1] * 300, MANY["k"][:300]),
+    "rows, 128": (8, 2, 128, [1] * 300 + [2] * 20 + [0] * 5, [*MANY["k"][:324], 70]),
+    "128 rows": (16, 2, 64, [257, 383, 384, 385, 511, 512, 513, 130, 1000, 640], [0, 1, 2, 3, 4, 5, 0, 70, 9, 33]),
+}
+
+
+def case(name, seed=1):
+    hq, hkv, d, S, k = CASES[name]
+    return attn_case(seed, len(S), hq, hkv, d, torch.float32, max(k) + 1, S, k, n_pages=int(sum(k)) + 3)
+
+
+def compare(c, want):
+    got = run_attn(c)
+    assert np.isfinite(got).all()
+    assert np.linalg.norm(got - want) <= REL * np.linalg.norm(want)
+    return got
+
+
+@pytest.mark.parametrize("name", CASES)
+@pytest.mark.parametrize("spread", [1.0, 4.0])
+def test_as_exact_as_fp32(name, spread):
+    c = case(name)
+    c["q"] *= spread
+    compare(c, oracle.attention(**c, n_threads=16))
