@@ -339,7 +339,10 @@ int skv_prefill_attn_workspace_size(const skv_attn_desc* desc, int32_t n_req, in
  * total_q_rows is a host-side upper bound of d_q_off[n_req] (the rows allocated in d_q / d_out);
  * rows beyond d_q_off[n_req] are left untouched.  S_r == 0 is legal.  Pages with an id outside
  * [0, n_pages) are read as zeros.  bf16 computes QK^T and PV on the matrix cores with fp32
- * accumulation and fp32 softmax; fp32 computes in fp32 throughout.
+ * accumulation and fp32 softmax.  fp32 is as exact as fp32 arithmetic: its products run on the matrix cores as three bf16
+ * pieces per value (six products, fp32 accumulation); rows that meet values without exact pieces -- not finite, beyond
+ * what rounds to a bf16, a query outside [2^-100, 2^80], a column of V below 2^-95 throughout -- are computed in plain fp32,
+ * which is slower.  Softmax weights below 2^-110 of a row's largest carry fewer bits.
  * Errors: SKV_EINVAL for null pointers or unsupported shapes, SKV_ENOMEM if the workspace is
  * too small for the work list; with less than skv_prefill_attn_workspace_size bytes nothing is split. */
 int skv_prefill_attn(const skv_attn_desc* desc, int32_t n_req, const void* d_q, const void* d_knew,

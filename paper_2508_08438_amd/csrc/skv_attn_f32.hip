@@ -191,14 +191,64 @@ __device__ __forceinline__ void one_row(const SkvAttnF32Params& p, const Row& ro
   }
 }
 
-// Infinities and NaN, and values that round to infinity as bf16, have no pieces, and a matrix product carries them into rows
-// that do not see their key.  A tile that met one is taken again row by row, over the keys the row sees.
+// What has no exact pieces: infinities and NaN, which a matrix product would also carry into rows that do not see their key,
+// values that round to infinity as bf16, and magnitudes so small that a piece would not be a normal number.  A tile that met one
+// is taken again row by row, over the keys the row sees.
 template <int D, int W>
 __device__ __forceinline__ void rows_one_by_one(const SkvAttnF32Params& p, const Item& it) {
   for (int i = it.row0 + (threadIdx.x >> 6); i < it.row1; i += W) {
     const Row row = {it.r, it.L, it.qbase, __builtin_amdgcn_readfirstlane(it.qbase + i), it.h};
     one_row<D, 64>(p, row);   // (all 128 at once would cost the tile's loop registers)
   }
+}
+// Small magnitudes.  Pieces are exact down to 2^-110.  Q within [2^-100, 2^80] (or zero) splits exactly, and what K's pieces lose,
+// 2^-134 at the most, then changes a score by less than 2^-47; a column of V with a value of 2^-95 or more loses less than 2^-39
+// of it.  The weights need no such rule: what they lose is 2^-134 of a row's largest.
+struct RangeOfQ {
+  uint32_t least = 0xffffffffu, most = 0;   // of the magnitudes' bits, less one (so that zero does not count), and as they are
+  __device__ __forceinline__ void add(float x) {
+    const uint32_t u = __builtin_bit_cast(uint32_t, x) & 0x7fffffffu;
+    least = min(least, u - 1u);
+    most = max(most, u);
+  }
+  __device__ __forceinline__ bool odd() const { return least < ((127u - 100u) << 23) - 1u || most > (127u + 80u) << 23; }
+};
+// A sum over a column of V that small has values (or zeros) below 2^-95 only, were there 2^25 keys.
+template <int kA>
+__device__ __forceinline__ bool some_small(const f32x16 (&o)[kA], float l) {
+  bool small = false;
+#pragma unroll
+  for (int a = 0; a < kA; ++a)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) small |= fabsf(o[a][e]) < 0x1p-70f;
+  return small && l > 0.f;   // (no key, no sum)
+}
+// Which of the two it is: every wavefront looks at every W-th 16-key group, a lane at a column.
+template <int D, int W>
+__device__ __forceinline__ bool tiny_columns(const SkvAttnF32Params& p, const Item& it) {
+  constexpr int kPer = D / 64;
+  const int lane = threadIdx.x & 63, key_end = it.L + it.row1;
+  uint32_t bits[kPer] = {};
+  for (int g = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); g * SKV_BLOCK_TOKENS < key_end; g += W) {
+    const int key0 = g * SKV_BLOCK_TOKENS;
+    const float* v = nullptr;
+    if (key0 >= it.L) {
+      v = (const float*)p.vnew + ((size_t)(it.qbase + key0 - it.L) * p.Hkv + it.hk) * D;
+    } else if (g < p.max_blocks) {
+      const int page = p.page_table[(size_t)it.r * p.max_blocks + g];
+      if (page >= 0 && page < p.n_pages) v = (const float*)p.vpool + ((size_t)page * SKV_BLOCK_TOKENS * p.Hkv + it.hk) * D;
+    }
+    if (!v) continue;
+    const int last = min(SKV_BLOCK_TOKENS, key_end - key0) - 1;
+#pragma unroll
+    for (int i = 0; i < SKV_BLOCK_TOKENS; ++i)
+#pragma unroll
+      for (int k = 0; k < kPer; ++k) bits[k] |= __builtin_bit_cast(uint32_t, v[(size_t)min(i, last) * p.Hkv * D + 64 * k + lane]);
+  }
+  bool tiny = false;   // no value with one of the three highest exponent bits, and not all zero
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) tiny |= (bits[k] & 0x7fffffffu) != 0 && (bits[k] & 0x70000000u) == 0;
+  return tiny;
 }
 template <int kA>
 __device__ __forceinline__ bool all_finite(const f32x16 (&o)[kA], float l) {
@@ -377,12 +427,15 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 2 : 1) void attn_f32_kernel(Skv
 
   float m_run = -INFINITY, l_run = 0.f;   // running maximum (scaled, exp2 units) and this half's running sum, per query
   const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  RangeOfQ q_range;
   // Q: through LDS, read as B operands from there (its registers would cost the second wavefront of the SIMD)
   for (int i = threadIdx.x; i < kRows * (D / 8); i += kThreads) {
     const int row = i % kRows, th = i / kRows;   // th = 2 step + half
     const f32x4* src = (const f32x4*)((const float*)p.q + ((size_t)(qbase + min(row0 + row, S - 1)) * p.Hq + h) * D + 16 * (th >> 1) + 4 * (th & 1));
     const f32x4 x0 = src[0], x1 = src[2];
     const float x[8] = {x0[0], x0[1], x0[2], x0[3], x1[0], x1[1], x1[2], x1[3]};
+#pragma unroll
+    for (int k = 0; k < 8; ++k) q_range.add(x[k]);
     const Pieces q = split8(x);
 #pragma unroll
     for (int k = 0; k < 3; ++k) q_lds[(k * (D / 8) + th) * kRows + row] = __builtin_bit_cast(u32x4, q.p[k]);
@@ -442,9 +495,12 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 2 : 1) void attn_f32_kernel(Skv
     asm volatile("s_nop 7\n\ts_nop 3");
   }
   l_run += other_half(l_run);
-  if (__builtin_expect(__syncthreads_or(!all_finite(o, l_run)), 0)) {   // (Q is no longer needed behind this either)
-    rows_one_by_one<D, kWaves>(p, it);
-    return;
+  const bool no_pieces = q_range.odd() || !all_finite(o, l_run), small = some_small(o, l_run);
+  if (__builtin_expect(__syncthreads_or(no_pieces || small), 0)) {   // (Q is no longer needed behind this either)
+    if (__syncthreads_or(no_pieces || tiny_columns<D, kWaves>(p, it))) {
+      rows_one_by_one<D, kWaves>(p, it);
+      return;
+    }
   }
 
   // ---- output.  Lane (query l32, half), accumulator row e: d = kA m .. with m = 8 (e / 4) + 4 half + e % 4
@@ -535,6 +591,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_f32_tile_kernel(SkvAttnF32Pa
   int win_cur = window(0), win_nxt = window(1);
   f32x4 kraw[2 * kKc];
   float vraw[16];
+  RangeOfQ q_range;
   auto load_tile = [&](int tile) __attribute__((always_inline)) {
     if (tile > 0 && (tile & 63) == 0) {
       win_cur = win_nxt;
@@ -606,6 +663,8 @@ __global__ __launch_bounds__(kThreads, 2) void attn_f32_tile_kernel(SkvAttnF32Pa
     for (int t = 0; t < kT; ++t) {
       const f32x4 a = *(const f32x4*)(src + 16 * t), b = *(const f32x4*)(src + 16 * t + 4);
       const float x[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+#pragma unroll
+      for (int k = 0; k < 8; ++k) q_range.add(x[k]);
       qp[t] = split8(x);
     }
   }
@@ -658,9 +717,12 @@ __global__ __launch_bounds__(kThreads, 2) void attn_f32_tile_kernel(SkvAttnF32Pa
   }
   l_run += other_half(l_run);
 
-  if (__builtin_expect(__syncthreads_or(!all_finite(o, l_run)), 0)) {
-    rows_one_by_one<D, kWaves>(p, it);
-    return;
+  const bool no_pieces = q_range.odd() || !all_finite(o, l_run), small = some_small(o, l_run);
+  if (__builtin_expect(__syncthreads_or(no_pieces || small), 0)) {
+    if (__syncthreads_or(no_pieces || tiny_columns<D, kWaves>(p, it))) {
+      rows_one_by_one<D, kWaves>(p, it);
+      return;
+    }
   }
   // ---- output, through LDS: whole rows leave together
   {

@@ -45,3 +45,27 @@ def test_as_exact_as_fp32(name, spread):
     c = case(name)
     c["q"] *= spread
     compare(c, oracle.attention(**c, n_threads=16))
+
+
+@pytest.mark.parametrize("name", CASES)
+@pytest.mark.parametrize("q,k,v", [(0, 0, -118), (118, -118, 0), (-118, 118, 0), (60, -60, 60), (0, 0, 100)])
+def test_magnitudes(name, q, k, v):
+    # powers of two change nothing but exponents: the results are those of the same case without them, times 2^v
+    c = case(name)
+    want = oracle.attention(**c, n_threads=16)
+    c["q"] *= 2.0 ** q
+    for n, e in (("knew", k), ("kpool", k), ("vnew", v), ("vpool", v)):
+        c[n] *= 2.0 ** e
+    compare(c, want * 2.0 ** v)
+
+
+@pytest.mark.parametrize("name", CASES)
+def test_small_and_zero_columns(name):
+    c = case(name)
+    for n in ("vnew", "vpool"):
+        c[n][..., 5] *= 2.0 ** -118
+        c[n][..., 9] = 0.0
+    want = oracle.attention(**c, n_threads=16)
+    got = compare(c, want)
+    assert np.linalg.norm(got[..., 5] - want[..., 5]) <= REL * np.linalg.norm(want[..., 5])
+    assert not got[..., 9].any()
