@@ -325,10 +325,12 @@ __device__ __forceinline__ void add_block(f32x16& o, const Pieces& v0, const Pie
 //        d = (D / 32) m + a.
 // Bound by latency and the splitting (5.5 vector instructions per value, 80 values per lane and block at D = 64).
 // D = 128 has a SIMD's registers to one wavefront (two spill: 2.70 ms instead of 2.38 for 40 requests of up to 2500 rows).
-// Attention alone, us, on the fp32 matrix instruction -> so: 8 requests of 144..320 rows, 8/8 heads, d 64: 27 -> 21; 100 of up
+// W: wavefronts of a workgroup, one where the batch fills the chip by itself (the rule stands at the end).
+// Attention alone, us, on the fp32 matrix instruction -> so, four wavefronts: 8 requests of 144..320 rows, 8/8 heads, d 64: 27 -> 21; 100 of up
 // to 30 rows behind 512..2048 cached ones: 140 -> 95; the same at 8/2 heads, d 128: 225 -> 227.
-template <int D>
-__global__ __launch_bounds__(kThreads, D == 64 ? 2 : 1) void attn_f32_kernel(SkvAttnF32Params p) {
+template <int D, int W>
+__global__ __launch_bounds__(64 * W, D == 64 ? 2 : 1) void attn_f32_kernel(SkvAttnF32Params p) {
+  constexpr int kWaves = W, kThreads = 64 * W;
   constexpr int kJ = D / 8;        // 16-byte pieces of a K row per lane
   constexpr int kA = D / 32;       // output accumulators
   typedef typename vec_of<kA>::type vvec;
@@ -428,6 +430,14 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 2 : 1) void attn_f32_kernel(Skv
   float m_run = -INFINITY, l_run = 0.f;   // running maximum (scaled, exp2 units) and this half's running sum, per query
   const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   RangeOfQ q_range;
+  int b = wave, page_nxt = -1;
+  uint64_t ka = 0, va = 0;
+  bool ok = true;
+  if (b < n_blocks) {   // the first K rows travel while Q does
+    locate(b, page_of(b), ka, va, ok);
+    if (b + kWaves < n_blocks) page_nxt = page_of(b + kWaves);
+    load_k(ka, ok);
+  }
   // Q: through LDS, read as B operands from there (its registers would cost the second wavefront of the SIMD)
   for (int i = threadIdx.x; i < kRows * (D / 8); i += kThreads) {
     const int row = i % kRows, th = i / kRows;   // th = 2 step + half
@@ -441,14 +451,7 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 2 : 1) void attn_f32_kernel(Skv
     for (int k = 0; k < 3; ++k) q_lds[(k * (D / 8) + th) * kRows + row] = __builtin_bit_cast(u32x4, q.p[k]);
   }
   __syncthreads();
-  int b = wave;
   if (b < n_blocks) {
-    uint64_t ka, va;
-    bool ok;
-    int page_nxt = page_of(b);
-    locate(b, page_nxt, ka, va, ok);
-    load_k(ka, ok);
-    page_nxt = b + kWaves < n_blocks ? page_of(b + kWaves) : -1;
     // One block: its V rows travel during the scores, the next block's K rows during the softmax and the output update.
     for (; b < n_blocks; b += kWaves) {
       load_v(b, va, ok);
@@ -497,8 +500,8 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 2 : 1) void attn_f32_kernel(Skv
   l_run += other_half(l_run);
   const bool no_pieces = q_range.odd() || !all_finite(o, l_run), small = some_small(o, l_run);
   if (__builtin_expect(__syncthreads_or(no_pieces || small), 0)) {   // (Q is no longer needed behind this either)
-    if (__syncthreads_or(no_pieces || tiny_columns<D, kWaves>(p, it))) {
-      rows_one_by_one<D, kWaves>(p, it);
+    if (__syncthreads_or(no_pieces || tiny_columns<D, W>(p, it))) {
+      rows_one_by_one<D, W>(p, it);
       return;
     }
   }
@@ -739,22 +742,59 @@ __global__ __launch_bounds__(kThreads, 2) void attn_f32_tile_kernel(SkvAttnF32Pa
     *(f32x4*)(out + (size_t)(i / (D / 4)) * p.Hq * D + i % (D / 4) * 4) = *(const f32x4*)(red_o + (size_t)(i / (D / 4)) * kRedStride + i % (D / 4) * 4);
 }
 
+// ---- one row per request ---------------------------------------------------------------------------
+// A wavefront per row and head in plain arithmetic: the tiles above are 32 rows, whatever a request has.
+template <int D>
+__global__ __launch_bounds__(kThreads, D == 64 ? 3 : 1) void attn_f32_rows_kernel(SkvAttnF32Params p) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t at = (int64_t)blockIdx.x * kWaves + wave;
+  const int tok = (int)(at / p.Hq);
+  if (tok >= min(p.max_rows, (int64_t)p.q_off[p.n_req])) return;
+  int r = 0;   // the last request that starts at or before the row
+  for (int n = p.n_req; n > 1;) {
+    const int step = (n + 63) / 64, idx = r + lane * step;
+    const int k = __builtin_popcountll(__ballot(idx < r + n && p.q_off[idx] <= tok));
+    const int lo = r + (k > 0 ? k - 1 : 0) * step;
+    n = min(step, r + n - lo);
+    r = lo;
+  }
+  r = __builtin_amdgcn_readfirstlane(r);
+  const int L = __builtin_amdgcn_readfirstlane(p.matched_len[r]);
+  const Row row = {r, L > 0 ? L & ~(SKV_BLOCK_TOKENS - 1) : 0, __builtin_amdgcn_readfirstlane(p.q_off[r]), tok, (int)(at % p.Hq)};
+  one_row<D, D>(p, row);
+}
+
 }  // namespace
 
 // Large tiles where suffixes fill them (256 rows on average) and there are enough for every workgroup slot of the chip: 64
 // requests x 1070 rows x 8 heads 660 us against 775, 32 x 290 rows 41 against 45; below, 8 x 290 rows 28 us against 21.
+// Where the items fill the chip by themselves, one wavefront takes each: four times as many at once, nothing to merge.  256 / 1000
+// requests of one row, 8 heads, d 64, behind no keys 25.7 / 84.6 us with four, 12.4 / 31.6 with one; behind 96 33.4 / 132 and 28.5 /
+// 95; behind 480 99.9 / 390 and 106 / 385, so up to two rounds the width of the table decides.  Single rows in such numbers are
+// better off without tiles: 12.7 / 20.9, 24.5 / 85, 102 / 362 (two rows each behind 96 keys: 39.3 / 135 against 28.5 / 99).
 int skv_attn_f32_enqueue(const SkvAttnF32Params& p, int head_dim, void* stream) {
   const hipStream_t st = (hipStream_t)stream;
-  const int64_t tiles = p.max_rows / (kRows * kWaves);
+  const int64_t tiles = p.max_rows / (kRows * kWaves), slots = head_dim == 64 ? 2048 : 1024;   // slots: wavefronts at once
   const bool large = head_dim == 64 && tiles >= 2 * (int64_t)p.n_req && tiles * p.Hq >= 512;
   const int64_t items = ((large ? tiles : p.max_rows / kRows) + p.n_req) * p.Hq;
   if (items > 0x7fffffff) return SKV_ERANGE;
+  const bool rows = items >= slots && 2 * p.max_rows <= 3 * (int64_t)p.n_req;
+  const bool alone = items >= 2 * slots || (items >= slots && p.max_blocks <= 16) || (items >= slots / 2 && p.max_blocks <= 2);
+  const int row_groups = (int)((p.max_rows * p.Hq + kWaves - 1) / kWaves);   // (no more than items, where they are used)
   if (large)
     attn_f32_tile_kernel<<<(int)items, kThreads, 0, st>>>(p);
+  else if (head_dim == 64 && rows)
+    attn_f32_rows_kernel<64><<<row_groups, kThreads, 0, st>>>(p);
+  else if (head_dim == 64 && alone)
+    attn_f32_kernel<64, 1><<<(int)items, 64, 0, st>>>(p);
   else if (head_dim == 64)
-    attn_f32_kernel<64><<<(int)items, kThreads, 0, st>>>(p);
+    attn_f32_kernel<64, kWaves><<<(int)items, kThreads, 0, st>>>(p);
+  else if (rows)
+    attn_f32_rows_kernel<128><<<row_groups, kThreads, 0, st>>>(p);
+  else if (alone)
+    attn_f32_kernel<128, 1><<<(int)items, 64, 0, st>>>(p);
   else
-    attn_f32_kernel<128><<<(int)items, kThreads, 0, st>>>(p);
+    attn_f32_kernel<128, kWaves><<<(int)items, kThreads, 0, st>>>(p);
   SKV_HIP(hipGetLastError());
   return SKV_OK;
 }

@@ -69,3 +69,21 @@ def test_small_and_zero_columns(name):
     got = compare(c, want)
     assert np.linalg.norm(got[..., 5] - want[..., 5]) <= REL * np.linalg.norm(want[..., 5])
     assert not got[..., 9].any()
+
+
+@pytest.mark.parametrize("name", ["one wavefront", "one wavefront, 128"])
+def test_values_without_pieces(name):
+    # what is not finite reaches the rows that see it and no others
+    c = case(name)
+    want = oracle.attention(**c, n_threads=16)
+    r = int(np.flatnonzero((np.asarray(CASES[name][3]) == 33) & (np.asarray(CASES[name][4]) > 0))[0])
+    first = int(c["q_off"][r])
+    c["vnew"][first + 20, 0, 3] = float("inf")
+    c["knew"][first + 30] = float("nan")
+    got = run_attn(c)
+    G = c["q"].shape[1] // c["knew"].shape[1]
+    seen = np.zeros(got.shape, bool)
+    seen[first + 20: first + 33, :G, 3] = True
+    seen[first + 30: first + 33] = True
+    assert np.linalg.norm((got - want)[~seen]) <= REL * np.linalg.norm(want[~seen])
+    assert np.isposinf(got[first + 20: first + 30, :G, 3]).all() and np.isnan(got[first + 30: first + 33]).all()
