@@ -322,9 +322,9 @@ int skv_mfma_rate(const void* d_operands, size_t operand_bytes, int32_t iters, i
                   size_t sink_bytes, double* flops, void* stream);
 
 /* Bytes of device workspace skv_prefill_attn needs for n_req requests and at most
- * total_q_rows uncached tokens in the batch (the work list of the bf16 kernel, one page of zeros that
- * stands in for key groups without data and, for small batches, the partial states of work items split along
- * the keys); the call overwrites it. */
+ * total_q_rows uncached tokens in the batch (bf16: the work list, one page of zeros that stands in for key groups without
+ * data, and 69 MB for the partial states of work items that small batches split along the keys); the call overwrites it.
+ * The size never falls as n_req or total_q_rows grow: the workspace of the largest batch serves every smaller one. */
 int skv_prefill_attn_workspace_size(const skv_attn_desc* desc, int32_t n_req, int64_t total_q_rows,
                                     size_t* bytes);
 

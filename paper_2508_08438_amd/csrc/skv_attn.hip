@@ -61,14 +61,14 @@ constexpr float kLog2e = 1.4426950408889634f;
 struct AttnParams {
   const void *q, *knew, *vnew, *kpool, *vpool;
   void* out;
-  const int32_t *q_off, *matched_len, *page_table;
+  const int32_t* page_table;
   const int32_t* items;      // kItemInts ints per work item
   const int32_t* n_items;
   const char* zero_page;     // 16 rows of zeros: stands in for a group of keys that has no data
   const int32_t* splits;     // kSplitInts ints per work item whose keys are split over several workgroups
   float* partials;           // kSlotFloats floats per part and (kv head, head group); null: nothing is ever split
-  int n_req, max_blocks, n_pages, Hq, Hkv;
-  int heads_per_wg;          // query heads of one kv head handled by one workgroup (1, 2 or 4)
+  int max_blocks, n_pages, Hq, Hkv;
+  int heads_per_wg;          // query heads of one kv head handled by one workgroup (1, 2, 4 or 8)
   float scale;
 };
 
@@ -1018,12 +1018,19 @@ Layout layout_for(const skv_attn_desc* d, int32_t n_req, int64_t total_q_rows, b
   y.heads_per_wg = heads_per_wg_for(d->n_q_heads / d->n_kv_heads, fine);
   y.pos_per_wg = (kWaves / y.heads_per_wg) * kRowsPerWave;
   y.units = d->n_q_heads / y.heads_per_wg;
-  // where no split can come of it the merge is not launched either (it costs 4.7 us)
-  const bool few = total_q_rows / y.pos_per_wg * y.units <= kSplitUnits && (int64_t)n_req * y.units <= 2 * kMaxSlots && y.units <= kCus;
-  y.max_parts = split && few ? kMaxSlots / y.units : 0;
+  y.max_parts = split && y.units <= kCus ? kMaxSlots / y.units : 0;
   y.max_items = total_q_rows / y.pos_per_wg + 2 * (int64_t)n_req + y.max_parts;   // per request: a short first tile and a ragged last one
   if (d->dtype != SKV_BF16) y.max_items = y.max_parts = 0;
   return y;
+}
+// Whether any split can come of the call: where none can neither search nor merge are launched.
+bool may_split(const Layout& y, int32_t n_req, int64_t total_q_rows, int32_t max_blocks) {
+  if (total_q_rows / y.pos_per_wg * y.units > kSplitUnits || (int64_t)n_req * y.units > 2 * kMaxSlots) return false;
+  // the device's rule on what the host knows (a table filled to its width, rows spread evenly, items of 0.7 of the longest on
+  // average): where it does not split, neither search nor merge are launched -- 3.2 us of a pass of 55
+  const int64_t longest = ((int64_t)max_blocks * SKV_BLOCK_TOKENS + total_q_rows / n_req) / kBN + 1;
+  const int64_t about = total_q_rows / y.pos_per_wg * y.units * longest * 7 / (10 * kCus);   // key tiles per compute unit
+  return kTileWhole * longest > kSplitCost + kTileSplit * about;
 }
 size_t split_bytes(const Layout& y) {
   return y.max_parts ? kCus * kSplitInts * sizeof(int32_t) + (size_t)y.max_parts * y.units * kSlotFloats * sizeof(float) : 0;
@@ -1035,7 +1042,7 @@ size_t zero_page_bytes(const skv_attn_desc* d) {
 
 }  // namespace
 
-// Work list and page of zeros: what a call needs at the least.
+// Work list and page of zeros: what a call needs at the least.  No part of the size falls as n_req or total_q_rows grow.
 static size_t list_bytes(const skv_attn_desc* desc, const Layout& y) {
   return 256 + zero_page_bytes(desc) + skv_align256((size_t)y.max_items * kItemInts * sizeof(int32_t));
 }
@@ -1045,8 +1052,11 @@ extern "C" int skv_prefill_attn_workspace_size(const skv_attn_desc* desc, int32_
   int rc = check_attn(desc);
   if (rc) return rc;
   if (n_req < 0 || total_q_rows < 0 || !bytes) return SKV_EINVAL;
-  const Layout y = layout_for(desc, n_req, total_q_rows, true, true);
-  *bytes = list_bytes(desc, y) + split_bytes(y);
+  *bytes = 0;
+  for (const bool fine : {false, true}) {   // whichever tiles a call takes
+    const Layout y = layout_for(desc, n_req, total_q_rows, fine, true);
+    *bytes = std::max(*bytes, list_bytes(desc, y) + split_bytes(y));
+  }
   return SKV_OK;
 }
 
@@ -1073,11 +1083,11 @@ static int prefill_attn_enqueue(const skv_attn_desc* desc, int32_t n_req, const 
 
   AttnParams p;
   p.q = d_q; p.knew = d_knew; p.vnew = d_vnew; p.kpool = d_kpool; p.vpool = d_vpool; p.out = d_out;
-  p.q_off = d_q_off; p.matched_len = d_matched_len; p.page_table = d_page_table;
+  p.page_table = d_page_table;
   p.n_items = (const int32_t*)d_workspace;
   p.zero_page = (const char*)d_workspace + 256;
   p.items = (const int32_t*)((char*)d_workspace + 256 + zero_page_bytes(desc));
-  p.n_req = n_req; p.max_blocks = max_blocks; p.n_pages = n_pages;
+  p.max_blocks = max_blocks; p.n_pages = n_pages;
   p.Hq = desc->n_q_heads; p.Hkv = desc->n_kv_heads;
   p.heads_per_wg = y.heads_per_wg;
   p.scale = skv_softmax_scale(desc);
@@ -1121,14 +1131,11 @@ extern "C" int skv_prefill_attn(const skv_attn_desc* desc, int32_t n_req, const 
   rc = check_attn_buffers(d_q, d_knew, d_vnew, d_q_off, d_kpool, d_vpool, d_matched_len, d_page_table, max_blocks,
                           d_out);
   if (rc) return rc;
-  // a workspace that holds the plain work list is enough: the call then splits nothing
+  // a workspace that holds the plain work list is enough: the call then splits nothing, and takes 32-row tiles if their list fits
   Layout y = layout_for(desc, n_req, total_q_rows, true, true);
-  if (workspace_bytes < list_bytes(desc, y) + split_bytes(y)) y = layout_for(desc, n_req, total_q_rows, false, false);
-  // the device's rule on what the host knows (a table filled to its width, rows spread evenly, items of 0.7 of the longest on
-  // average): where it does not split, neither search nor merge are launched -- 3.2 us of a pass of 55
-  const int64_t longest = ((int64_t)max_blocks * SKV_BLOCK_TOKENS + total_q_rows / n_req) / kBN + 1;
-  const int64_t about = total_q_rows / y.pos_per_wg * y.units * longest * 7 / (10 * kCus);   // key tiles per compute unit
-  if (y.max_parts && kTileWhole * longest <= kSplitCost + kTileSplit * about) y = layout_for(desc, n_req, total_q_rows, true, false);
+  if (y.max_parts && (!may_split(y, n_req, total_q_rows, max_blocks) || workspace_bytes < list_bytes(desc, y) + split_bytes(y)))
+    y = layout_for(desc, n_req, total_q_rows, true, false);
+  if (workspace_bytes < list_bytes(desc, y)) y = layout_for(desc, n_req, total_q_rows, false, false);
   if (!d_workspace || workspace_bytes < list_bytes(desc, y)) return SKV_ENOMEM;
   if ((uintptr_t)d_workspace & 15) return SKV_EINVAL;
   return prefill_attn_enqueue(desc, n_req, d_q, d_knew, d_vnew, d_q_off, total_q_rows, d_kpool, d_vpool, n_pages,

@@ -190,6 +190,20 @@ def test_bf16_plain_work_list_is_enough(hq, hkv):
     assert e.value.code == skv.SKV_ENOMEM
 
 
+@pytest.mark.parametrize("hq,hkv", [(32, 8), (64, 8), (8, 1)])
+def test_bf16_workspace_of_a_larger_batch(hq, hkv):
+    # a server's one buffer, sized for its largest batch: small batches are split along their keys as with a buffer of their own
+    from paper_2508_08438_amd import binding as skv
+    largest = skv.skv_prefill_attn_workspace_size(skv.attn_desc(hq, hkv, 128, "bf16"), 256, 65536)
+    for S, k in (([137], [187]), ([64, 9, 300], [150, 40, 7])):
+        c = attn_case(13, len(S), hq, hkv, 128, torch.bfloat16, max(k), S, k, n_pages=sum(k) + 1)
+        own, _ = _run_with(c, None)
+        got, _ = _run_with(c, largest)
+        plain, _ = _run_with(c, 256 + 16 * hkv * 256 + 1024)
+        assert np.array_equal(got, own)
+        assert not np.array_equal(got, plain)     # (parts round their own way: so there were parts)
+
+
 @pytest.mark.parametrize("split", [True, False])
 def test_bf16_runs_of_keys_without_weight(split):
     # scores of -infinity over the first pages, over whole parts, and over the new keys of one request
