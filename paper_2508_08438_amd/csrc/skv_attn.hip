@@ -395,6 +395,8 @@ __device__ __forceinline__ void unit_of_block(int b, int Hkv, int n_hg, int& ite
   item = rest / n_hg;
 }
 
+// kParts: the list may hold parts of items.  Without, 0.3 us less of a workgroup's start goes into what a part needs.
+template <bool kParts>
 __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
   __shared__ __attribute__((aligned(16))) __bf16 smem[kKStages * kTile + kVStages * kTile +
                                                       kWaves * kStageRows * kD];
@@ -420,8 +422,8 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
   const int4 rec0 = ((const int4*)(p.items + (size_t)kItemInts * item))[0];
   const int4 rec1 = ((const int4*)(p.items + (size_t)kItemInts * item))[1];
   if (item >= *p.n_items) return;
-  const int kt0 = __builtin_amdgcn_readfirstlane(rec1.z);    // first key tile of this part
-  const int part = __builtin_amdgcn_readfirstlane(rec1.w);   // 0: the whole item
+  const int kt0 = kParts ? __builtin_amdgcn_readfirstlane(rec1.z) : 0;    // first key tile of this part
+  const int part = kParts ? __builtin_amdgcn_readfirstlane(rec1.w) : 0;   // 0: the whole item
   // Everything below counts keys from the part's first one: the reused length and with it every position shifts.
   const int L = __builtin_amdgcn_readfirstlane(rec1.x) - kt0 * kBN;                         // may be negative
   const int row1 = __builtin_amdgcn_readfirstlane(rec1.y);                                  // end row of the q tile
@@ -1109,7 +1111,10 @@ static int prefill_attn_enqueue(const skv_attn_desc* desc, int32_t n_req, const 
                                                     (int32_t*)d_workspace, (int32_t*)p.items, (int32_t*)p.splits,
                                                     (uint4*)p.zero_page, (int)(zero_page_bytes(desc) / 16));
   SKV_HIP(hipGetLastError());
-  attn_bf16_kernel<<<(int)grid, kThreads, 0, st>>>(p);
+  if (y.max_parts)
+    attn_bf16_kernel<true><<<(int)grid, kThreads, 0, st>>>(p);
+  else
+    attn_bf16_kernel<false><<<(int)grid, kThreads, 0, st>>>(p);
   SKV_HIP(hipGetLastError());
   if (y.max_parts) {   // a split item has two parts at least
     attn_merge_kernel<<<(int)std::min<int64_t>(y.max_parts / 2 * y.units * kWaves, kMergeGrid), kMergeThreads, 0, st>>>(p);

@@ -12,6 +12,7 @@ from paper_2508_08438_amd import build
     ("skv_attn_f32.hip", ["attn_f32_kernelILi64E", "attn_f32_kernelILi128E", "attn_f32_tile_kernel"], 12),
     ("skv_attn_f32.hip", ["attn_f32_kernelILi64ELi1E", "attn_f32_kernelILi64ELi4E", "attn_f32_kernelILi128ELi1E",
                           "attn_f32_kernelILi128ELi4E"], 12),
+    ("skv_attn.hip", ["attn_bf16_kernelILb0E", "attn_bf16_kernelILb1E"], 12),
     ("skv_decode.hip", ["decode_attn_kernelILb0E", "decode_attn_kernelILb1E"], 12),
 ])
 def test_no_early_reader_behind_a_branch(src, kernels, need, tmp_path):
