@@ -88,47 +88,51 @@ struct AttnParams {
 // behind 24 k cached tokens: 80 workgroups, 0.50 ms).  Their items are split along the keys: every part is a record of its
 // own (part = (slot + 1) << kPartBits | key tiles), leaves its unnormalised output, reference and row sum in the workspace,
 // and attn_merge_kernel combines them.  The part length c is the smallest for which all parts run in one round, or in
-// two, of one workgroup per compute unit.  Whole items take 11.5 + 1.27 us per key tile of the longest, split ones 28 + 1.9 us
-// per key tile and compute unit (start-up, partial states and merge included; 144 shapes of 8 .. 160 workgroups, both forms
-// timed): the batch is split where that is less.  E.g. 137 rows behind 2048 cached ones 53 -> 30 us; 300 behind 512 stay whole
-// (28 us; split 30).
+// two, of one workgroup per compute unit.  Whole items take 12 us + 1.27 per key tile of the longest, 0.87 where half the
+// wavefronts or more have no rows; split ones 22 us, 8 for the partial states of full workgroups, and 1.7 times the tiles' time per
+// compute unit (1105 shapes of 1 .. 1000 requests, whole and split timed): the batch is split where that is less.  E.g. 137 rows
+// behind 2992 cached ones, 32 query heads over 8: 72 -> 33 us; 137 of each of 8 requests behind 1488 stay whole (49 us).
 //
 // The kernel is a chain of dependent steps on one compute unit, so every step is short: requests are ordered by a histogram
 // of their lengths, scans go through registers, and the search for c tries sixteen lengths at a time, one per wavefront
-// (one request of 257 rows: 10 us, 18 with one length at a time; lists without a split 5 us).  Order by length and
+// (one request of 257 rows: 10 us, 18 with one length at a time; lists without a split 4.3 us).  Order by length and
 // 32-row tiles: 32 requests of 264 rows behind 16..32 k keys, 64/8 heads: 7.32 -> 6.83 ms; 16 requests of 97..994 rows
 // behind up to 8 k, 32/8 heads (order only): 525 -> 512 us.
 constexpr int kItemInts = 8;
 constexpr int kCus = 256;             // compute units = workgroups that run at once
 constexpr int kMaxSlots = 2 * kCus;   // parts of a split batch, over all kv heads and head groups
 constexpr int kStartTiles = 8;
-constexpr int kTileWhole = 127, kTileSplit = 190, kSplitCost = 1650;   // 10 ns
-constexpr int kSplitUnits = 160;      // equal items in more workgroups than this are never split
+constexpr int kLogFull = 8;           // query rows of a workgroup's wavefronts (logarithm)
+static_assert(1 << kLogFull == kWaves * kRowsPerWave);
+// 10 ns: a key tile of a workgroup with rows for more than half its wavefronts, or for less
+constexpr int kTileFull = 127, kTileHalf = 87;
+constexpr float kWholeCost = 1200.f, kSplitCost = 2200.f, kStateCost = 800.f, kSplitTime = 1.7f;   // 10 ns; the last a factor
 constexpr int kPartBits = 20;         // key tiles of a part
 constexpr int kSplitInts = 8;         // {first row, end row, first row of the request in Q, first slot, parts, 0, 0, 0}
 constexpr int kSlotFloats = kWaves * 64 * (64 + 2);   // per wavefront and lane: 64 of O^T, reference, row sum
 
+// (tile heights are powers of two and handed on as their logarithms: a division is a microsecond of this kernel's chain)
 struct Cut {   // how one request's suffix is cut into q tiles
   int S, L, qb, head_rows, nt;
-  __device__ void tile(int j, int pos_per_wg, int& row0, int& row1) const {   // j-th tile from the front
+  __device__ void tile(int j, int pos_log, int& row0, int& row1) const {   // j-th tile from the front
     if (head_rows > 0 && j == 0) {
       row0 = 0;
       row1 = head_rows;
     } else {
-      row0 = head_rows + (j - (head_rows > 0 ? 1 : 0)) * pos_per_wg;
-      row1 = min(S, row0 + pos_per_wg);
+      row0 = head_rows + ((j - (head_rows > 0 ? 1 : 0)) << pos_log);
+      row1 = min(S, row0 + (1 << pos_log));
     }
   }
 };
-__device__ inline Cut cut_of(int r, const int32_t* q_off, const int32_t* matched_len, int pos_per_wg) {
+__device__ inline Cut cut_of(int q_begin, int q_end, int matched, int pos_log) {
   Cut c;
-  c.qb = q_off[r];
-  c.S = q_off[r + 1] - c.qb;
-  c.L = matched_len[r] > 0 ? matched_len[r] & ~(SKV_BLOCK_TOKENS - 1) : 0;   // whole blocks only
-  const int align = min(kBN, pos_per_wg);
-  c.head_rows = min(c.S, (align - c.L % align) % align);                     // rows of the short first tile (0: none)
-  c.nt = c.S > 0 ? (c.head_rows > 0 ? 1 : 0) + (c.S - c.head_rows + pos_per_wg - 1) / pos_per_wg : 0;
-  const int nt_plain = (c.S + pos_per_wg - 1) / pos_per_wg;
+  c.qb = q_begin;
+  c.S = q_end - q_begin;
+  c.L = matched > 0 ? matched & ~(SKV_BLOCK_TOKENS - 1) : 0;   // whole blocks only
+  const int last = (1 << pos_log) - 1, align = min(kBN - 1, last);
+  c.head_rows = min(c.S, -c.L & align);                        // rows of the short first tile (0: none)
+  c.nt = c.S > 0 ? (c.head_rows > 0 ? 1 : 0) + ((c.S - c.head_rows + last) >> pos_log) : 0;
+  const int nt_plain = (c.S + last) >> pos_log;
   if (nt_plain < c.nt && 2 * c.L > c.S) {   // the short first tile would cost a whole extra tile: cut from row 0 instead
     c.head_rows = 0;
     c.nt = nt_plain;
@@ -143,14 +147,30 @@ __device__ inline int parts_of(int n, int last, int c) {
   return parts;
 }
 
+__host__ __device__ inline int tile_time(int rows, int pos_log) {   // of a workgroup with that many rows of its q tile
+  const int active = ((rows + kRowsPerWave - 1) / kRowsPerWave) << (kLogFull - pos_log);
+  return active * 2 <= kWaves ? kTileHalf : kTileFull;
+}
+// The two forecasts.  workgroups: of the whole items; longest: the longest one's time; share: the time of all per compute unit;
+// fill: query rows per row of the items' wavefronts.
+__host__ __device__ inline float whole_time(float workgroups, float longest, float share) {
+  const float two = share + longest / 2;
+  return kWholeCost + (workgroups <= kCus || two < longest ? longest : two);
+}
+__host__ __device__ inline float split_time(float share, float fill) {
+  return kSplitCost + kStateCost * (fill < 1.f ? fill : 1.f) + kSplitTime * share;
+}
+
 constexpr int kSchedThreads = 1024, kSchedWaves = kSchedThreads / 64;
 constexpr int kBuckets = 128;
 
-__device__ inline int wave_max(int v) {
+template <typename T>
+__device__ inline T wave_max(T v) {
   for (int o = 32; o >= 1; o >>= 1) v = max(v, __shfl_xor(v, o));
   return v;
 }
-__device__ inline int wave_sum(int v) {
+template <typename T>
+__device__ inline T wave_sum(T v) {
   for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
   return v;
 }
@@ -165,31 +185,32 @@ __device__ inline int place_of(const int* scan, int n, int x) {
 }
 
 __global__ __launch_bounds__(kSchedThreads) void attn_schedule_kernel(
-    int n_req, const int32_t* __restrict__ q_off, const int32_t* __restrict__ matched_len, int pos_per_wg, int max_items,
-    int units /* workgroups per item */, int32_t* __restrict__ n_items /* [0] items, [1] split items */,
-    int32_t* __restrict__ items, int32_t* __restrict__ splits /* null: never split */, uint4* __restrict__ zero_page,
+    int n_req, const int32_t* __restrict__ q_off, const int32_t* __restrict__ matched_len, int pos_log, int max_items,
+    int units /* workgroups per item */,
+    float rows_filled /* query rows, over the heads of a workgroup */,
+    int32_t* __restrict__ n_items /* [0] items, [1] split items */, int32_t* __restrict__ items, int32_t* __restrict__ splits /* null: never split */, uint4* __restrict__ zero_page,
     int zero_vec) {
-  __shared__ int scan[kSchedThreads], req_at[kSchedThreads], red[kSchedWaves], bucket[kBuckets];
+  __shared__ int scan[kSchedThreads], red[kSchedWaves], bucket[kBuckets];
+  __shared__ int4 req_at[kSchedThreads];   // request, first row, rows, reused length
   __shared__ int4 item_a[kCus], item_b[kCus];   // the first records, for the split
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   for (int i = tid; i < zero_vec; i += kSchedThreads) zero_page[i] = make_uint4(0u, 0u, 0u, 0u);
   int listed = 0;
   for (int base = 0; base < n_req; base += kSchedThreads) {
     const int r = base + tid, n_here = min(kSchedThreads, n_req - base);
-    int nt = 0, keys = 0;
-    if (r < n_req) {
-      const Cut c = cut_of(r, q_off, matched_len, pos_per_wg);
-      nt = c.nt;
-      keys = nt > 0 ? c.L + c.S : 0;
-    }
+    Cut mine = {};
+    if (r < n_req) mine = cut_of(q_off[r], q_off[r + 1], matched_len[r], pos_log);
+    const int keys = mine.nt > 0 ? mine.L + mine.S : 0;
     // place in the order of falling length, to 1 / kBuckets of the longest
-    int place = tid;
+    int place = tid, longest = 0;
     if (n_here > 1) {
       const int m = wave_max(keys);
       if (lane == 0) red[wave] = m;
       if (tid < kBuckets) bucket[tid] = 0;
       __syncthreads();
-      const int longest = wave_max(lane < kSchedWaves ? red[lane] : 0);
+      longest = wave_max(lane < kSchedWaves ? red[lane] : 0);
+    }
+    if (longest > 0) {
       int b = 0, rank = 0;
       if (r < n_req) {
         b = kBuckets - 1 - (int)((float)keys * ((kBuckets - 0.5f) / (float)max(longest, 1)));
@@ -211,8 +232,8 @@ __global__ __launch_bounds__(kSchedThreads) void attn_schedule_kernel(
       place = bucket[b] + rank;
     }
     if (r < n_req) {
-      scan[place] = nt;
-      req_at[place] = r;
+      scan[place] = mine.nt;
+      req_at[place] = make_int4(r, mine.qb, mine.S, mine.L);
     }
     __syncthreads();
     int total;
@@ -221,11 +242,12 @@ __global__ __launch_bounds__(kSchedThreads) void attn_schedule_kernel(
     __syncthreads();
     // the chunk's items, one per thread and turn: the request is found in the scan
     for (int it = tid; it < total && listed + it < max_items; it += kSchedThreads) {
-      const int at = place_of(scan, n_here, it), rr = req_at[at];
-      const Cut c = cut_of(rr, q_off, matched_len, pos_per_wg);
+      const int at = place_of(scan, n_here, it);
+      const int4 q = req_at[at];
+      const Cut c = cut_of(q.y, q.y + q.z, q.w, pos_log);
       int row0, row1;
-      c.tile(scan[at] - 1 - it, pos_per_wg, row0, row1);   // the request's last tile first
-      const int4 a = make_int4(rr, row0, c.qb, c.S), b = make_int4(c.L, row1, 0, 0);
+      c.tile(scan[at] - 1 - it, pos_log, row0, row1);   // the request's last tile first
+      const int4 a = make_int4(q.x, row0, c.qb, c.S), b = make_int4(c.L, row1, 0, 0);
       int4* rec = (int4*)(items + (size_t)kItemInts * (listed + it));
       rec[0] = a;
       rec[1] = b;
@@ -242,6 +264,7 @@ __global__ __launch_bounds__(kSchedThreads) void attn_schedule_kernel(
   if (splits && n > 0 && n <= kCus && n * units <= kMaxSlots) {   // few items: split their keys?
     // every wavefront holds all items, four per lane
     int n_kt[kCus / 64], last[kCus / 64], longest = 0, sum = 0;
+    float longest_time = 0.f, sum_time = 0.f;
 #pragma unroll
     for (int k = 0; k < kCus / 64; ++k) {
       const int i = lane + 64 * k;
@@ -250,83 +273,84 @@ __global__ __launch_bounds__(kSchedThreads) void attn_schedule_kernel(
         const int4 a = item_a[i], b = item_b[i];
         n_kt[k] = (b.x + b.y + kBN - 1) / kBN;
         last[k] = (b.x + a.y) / kBN;
+        const float time = (float)n_kt[k] * tile_time(b.y - a.y, pos_log);
+        longest_time = fmaxf(longest_time, time);
+        sum_time += time;
       }
       longest = max(longest, n_kt[k]);
       sum += n_kt[k];
     }
     longest = wave_max(longest);
     sum = wave_sum(sum);
-    const int share = (sum * units + kCus - 1) / kCus;   // key tiles per compute unit
-    const int whole = n * units <= kCus ? longest : max(longest, share + longest / 2);
-    const bool worth = kTileWhole * (long long)whole > kSplitCost + kTileSplit * (long long)share;
-    // smallest part length for which all parts have room in one round (wavefronts 0 .. 7) or two (8 .. 15): eight lengths
-    // between the last that did not fit and the first that did, until they meet
-    const int room1 = kCus / units, room2 = 2 * kCus / units, half = wave >> 3;
-    const int room = half ? room2 : room1;
-    int lo1 = 1, hi1 = longest, lo2 = 1, hi2 = longest;
-    if (room1 >= n) lo1 = max(1, min(longest, (sum + room1 - 1) / room1)); else lo1 = longest;
-    if (room2 >= n) lo2 = max(1, min(longest, (sum + room2 - 1) / room2)); else lo2 = longest;
-    int turn = 0;
-    __shared__ int fits[2][kSchedWaves];
-    while (worth && (lo1 < hi1 || lo2 < hi2)) {
-      const int lo = half ? lo2 : lo1, hi = half ? hi2 : hi1;
-      const int c = lo + (int)(((long long)(hi - lo) * (wave & 7)) >> 3);   // wavefront 0 of the eight tries lo itself
-      int p = 0;
-#pragma unroll
-      for (int k = 0; k < kCus / 64; ++k)
-        if (lane + 64 * k < n) p += parts_of(n_kt[k], last[k], c);
-      p = wave_sum(p);
-      if (lane == 0) fits[turn & 1][wave] = p <= room;
-      __syncthreads();
-      const uint64_t ok = __ballot(lane < kSchedWaves && fits[turn & 1][lane & (kSchedWaves - 1)]);
-      auto narrow = [&](unsigned f, int& l, int& h) {   // f: bit k set where the k-th length fits
-        if (l >= h) return;
-        const int l0 = l, d = h - l, k = f ? __builtin_ctz(f) : 8;
-        if (k < 8) h = l0 + (int)(((long long)d * k) >> 3);
-        if (k > 0) l = l0 + (int)(((long long)d * (k - 1)) >> 3) + 1;
-      };
-      narrow((unsigned)ok & 255u, lo1, hi1);
-      narrow((unsigned)(ok >> 8) & 255u, lo2, hi2);
-      ++turn;
-    }
-    int best_c = longest;
+    longest_time = wave_max(longest_time);
+    const float share = wave_sum(sum_time) * units / kCus;
+    const bool worth = split_time(share, rows_filled / (n << kLogFull)) < whole_time(n * units, longest_time, share);
     if (worth) {
+      // smallest part length for which all parts have room in one round (wavefronts 0 .. 7) or two (8 .. 15): eight lengths
+      // between the last that did not fit and the first that did, until they meet
+      const int room1 = kCus / units, room2 = 2 * kCus / units, half = wave >> 3;
+      const int room = half ? room2 : room1;
+      int lo1 = 1, hi1 = longest, lo2 = 1, hi2 = longest;
+      if (room1 >= n) lo1 = max(1, min(longest, (sum + room1 - 1) / room1)); else lo1 = longest;
+      if (room2 >= n) lo2 = max(1, min(longest, (sum + room2 - 1) / room2)); else lo2 = longest;
+      int turn = 0;
+      __shared__ int fits[2][kSchedWaves];
+      while (lo1 < hi1 || lo2 < hi2) {
+        const int lo = half ? lo2 : lo1, hi = half ? hi2 : hi1;
+        const int c = lo + (int)(((long long)(hi - lo) * (wave & 7)) >> 3);   // wavefront 0 of the eight tries lo itself
+        int p = 0;
+  #pragma unroll
+        for (int k = 0; k < kCus / 64; ++k)
+          if (lane + 64 * k < n) p += parts_of(n_kt[k], last[k], c);
+        p = wave_sum(p);
+        if (lane == 0) fits[turn & 1][wave] = p <= room;
+        __syncthreads();
+        const uint64_t ok = __ballot(lane < kSchedWaves && fits[turn & 1][lane & (kSchedWaves - 1)]);
+        auto narrow = [&](unsigned f, int& l, int& h) {   // f: bit k set where the k-th length fits
+          if (l >= h) return;
+          const int l0 = l, d = h - l, k = f ? __builtin_ctz(f) : 8;
+          if (k < 8) h = l0 + (int)(((long long)d * k) >> 3);
+          if (k > 0) l = l0 + (int)(((long long)d * (k - 1)) >> 3) + 1;
+        };
+        narrow((unsigned)ok & 255u, lo1, hi1);
+        narrow((unsigned)(ok >> 8) & 255u, lo2, hi2);
+        ++turn;
+      }
       // one round of workgroups, which cost about kStartTiles tiles before and after their loop, or two
-      const bool one = room1 >= n && kStartTiles + hi1 <= 2 * (kStartTiles + hi2);
-      best_c = one ? hi1 : hi2;
-    }
-    // scans of the parts (place in the list) and, packed, of the parts of split items (slot) and of the split items
-    int4 a = {0, 0, 0, 0}, b = {0, 0, 0, 0};
-    int parts = 0;
-    if (tid < n) {
-      a = item_a[tid];
-      b = item_b[tid];
-      parts = parts_of((b.x + b.y + kBN - 1) / kBN, (b.x + a.y) / kBN, best_c);
-    }
-    int total;
-    const int mine = parts | (parts > 1 ? parts << 10 | 1 << 20 : 0);
-    const int upto = skv_block_scan<kSchedThreads>(mine, red, total);
-    const int n_parts = total & 1023;
-    if (n_parts > n && n_parts <= max_items) {
-      scan[tid] = upto & 1023;
-      const int before = upto - mine, slot = (before >> 10) & 1023;
-      if (parts > 1) {
-        int4* sp = (int4*)(splits + kSplitInts * (before >> 20));
-        sp[0] = make_int4(a.y, b.y, a.z, slot);
-        sp[1] = make_int4(parts, 0, 0, 0);
+      const int best_c = room1 >= n && kStartTiles + hi1 <= 2 * (kStartTiles + hi2) ? hi1 : hi2;
+      // scans of the parts (place in the list) and, packed, of the parts of split items (slot) and of the split items
+      int4 a = {0, 0, 0, 0}, b = {0, 0, 0, 0};
+      int parts = 0;
+      if (tid < n) {
+        a = item_a[tid];
+        b = item_b[tid];
+        parts = parts_of((b.x + b.y + kBN - 1) / kBN, (b.x + a.y) / kBN, best_c);
       }
-      if (tid < n) item_b[tid] = make_int4(b.x, b.y, parts, slot);
-      __syncthreads();
-      for (int it = tid; it < n_parts; it += kSchedThreads) {
-        const int at = place_of(scan, n, it);
-        const int4 ia = item_a[at], ib = item_b[at];
-        const int j = it - (at ? scan[at - 1] : 0), kt = (ib.x + ib.y + kBN - 1) / kBN, len = (kt + ib.z - 1) / ib.z;
-        int4* rec = (int4*)(items + (size_t)kItemInts * it);
-        rec[0] = ia;
-        rec[1] = make_int4(ib.x, ib.y, j * len, ib.z > 1 ? (ib.w + j + 1) << kPartBits | min(len, kt - j * len) : 0);
+      int total;
+      const int mine = parts | (parts > 1 ? parts << 10 | 1 << 20 : 0);
+      const int upto = skv_block_scan<kSchedThreads>(mine, red, total);
+      const int n_parts = total & 1023;
+      if (n_parts > n && n_parts <= max_items) {
+        scan[tid] = upto & 1023;
+        const int before = upto - mine, slot = (before >> 10) & 1023;
+        if (parts > 1) {
+          int4* sp = (int4*)(splits + kSplitInts * (before >> 20));
+          sp[0] = make_int4(a.y, b.y, a.z, slot);
+          sp[1] = make_int4(parts, 0, 0, 0);
+        }
+        if (tid < n) item_b[tid] = make_int4(b.x, b.y, parts, slot);
+        __syncthreads();
+        for (int it = tid; it < n_parts; it += kSchedThreads) {
+          const int at = place_of(scan, n, it);
+          const int4 ia = item_a[at], ib = item_b[at];
+          const int j = it - (at ? scan[at - 1] : 0), kt = (ib.x + ib.y + kBN - 1) / kBN, len = (kt + ib.z - 1) / ib.z;
+          int4* rec = (int4*)(items + (size_t)kItemInts * it);
+          rec[0] = ia;
+          rec[1] = make_int4(ib.x, ib.y, j * len, ib.z > 1 ? (ib.w + j + 1) << kPartBits | min(len, kt - j * len) : 0);
+        }
+        n_out = n_parts;
+        n_split = total >> 20;
       }
-      n_out = n_parts;
-      n_split = total >> 20;
     }
   }
   if (tid == 0) {
@@ -998,8 +1022,7 @@ __global__ __launch_bounds__(kMergeThreads) void attn_merge_kernel(AttnParams p)
   }
 }
 
-// Query heads per workgroup: divides kWaves.  Eight where the kv head serves a multiple of eight: tiles of 32 rows fit a
-// request's rows closer than the 64 of four heads.  `fine` false: at most four (a shorter work list).
+// Query heads per workgroup: divides kWaves.  `fine`: eight where the kv head serves a multiple of eight.
 int heads_per_wg_for(int G, bool fine) { return fine && G % 8 == 0 ? 8 : (G % 4 == 0 ? 4 : (G % 2 == 0 ? 2 : 1)); }
 
 int check_attn(const skv_attn_desc* d) {
@@ -1012,27 +1035,56 @@ int check_attn(const skv_attn_desc* d) {
 
 // How a call is laid out: from the description and the bounds the host knows.
 struct Layout {
-  int heads_per_wg, pos_per_wg, units;   // units: workgroups per item
+  int heads_per_wg, pos_log, units;      // pos_log: logarithm of the rows of a q tile; units: workgroups per item
   int64_t max_items, max_parts;          // max_parts: room for parts of split items, 0 if nothing is split
 };
 Layout layout_for(const skv_attn_desc* d, int32_t n_req, int64_t total_q_rows, bool fine, bool split) {
   Layout y;
   y.heads_per_wg = heads_per_wg_for(d->n_q_heads / d->n_kv_heads, fine);
-  y.pos_per_wg = (kWaves / y.heads_per_wg) * kRowsPerWave;
+  y.pos_log = kLogFull - __builtin_ctz(y.heads_per_wg);
   y.units = d->n_q_heads / y.heads_per_wg;
   y.max_parts = split && y.units <= kCus ? kMaxSlots / y.units : 0;
-  y.max_items = total_q_rows / y.pos_per_wg + 2 * (int64_t)n_req + y.max_parts;   // per request: a short first tile and a ragged last one
+  y.max_items = (total_q_rows >> y.pos_log) + 2 * (int64_t)n_req + y.max_parts;   // per request: a short first tile and a ragged last one
   if (d->dtype != SKV_BF16) y.max_items = y.max_parts = 0;
   return y;
 }
-// Whether any split can come of the call: where none can neither search nor merge are launched.
+// What the host knows of a call: rows as if spread evenly, a table filled to its width.
+int64_t mean_rows(int32_t n_req, int64_t total_q_rows) { return (total_q_rows + n_req - 1) / n_req; }
+int64_t key_tiles(int64_t rows, int32_t max_blocks) { return ((int64_t)max_blocks * SKV_BLOCK_TOKENS + rows) / kBN + 1; }
+// Whether any split can come of it (the device's rule, with items of 0.7 of the longest on average): where none can neither
+// search nor merge are launched -- 3.2 us of a pass of 55.
 bool may_split(const Layout& y, int32_t n_req, int64_t total_q_rows, int32_t max_blocks) {
-  if (total_q_rows / y.pos_per_wg * y.units > kSplitUnits || (int64_t)n_req * y.units > 2 * kMaxSlots) return false;
-  // the device's rule on what the host knows (a table filled to its width, rows spread evenly, items of 0.7 of the longest on
-  // average): where it does not split, neither search nor merge are launched -- 3.2 us of a pass of 55
-  const int64_t longest = ((int64_t)max_blocks * SKV_BLOCK_TOKENS + total_q_rows / n_req) / kBN + 1;
-  const int64_t about = total_q_rows / y.pos_per_wg * y.units * longest * 7 / (10 * kCus);   // key tiles per compute unit
-  return kTileWhole * longest > kSplitCost + kTileSplit * about;
+  // more parts than there is room for
+  if ((total_q_rows >> y.pos_log) * y.units > kMaxSlots || (int64_t)n_req * y.units > 2 * kMaxSlots) return false;
+  const int64_t rows = mean_rows(n_req, total_q_rows), tiles = (rows + (1 << y.pos_log) - 1) >> y.pos_log, items = n_req * tiles;
+  const float kt = (float)key_tiles(rows, max_blocks);
+  const int last = tile_time((int)(rows - ((tiles - 1) << y.pos_log)), y.pos_log);
+  const float share = 0.7f * n_req * y.units * ((tiles - 1) * kTileFull + last) * kt / kCus;
+  return split_time(share, (float)total_q_rows / (items << y.pos_log)) <
+         whole_time(items * y.units, kt * (tiles > 1 ? kTileFull : last), share);
+}
+// Tiles of eight heads and 32 rows, or of four heads and 64: eight take half the workgroups for requests of up to 32 rows, and
+// fewer where the last tile fits closer, but each costs half a key tile more (it may end inside one) and four heads in the one
+// tile of a short request leave half the wavefronts idle, which makes a key tile shorter.  Where either fills the chip the sums decide,
+// of requests that end anywhere in a tile: 64 query heads over 8, 256 requests of 1 .. 16 rows behind 500 to 1400 523 -> 322 us,
+// 32 of 264 behind 16 .. 32 k 7.32 -> 6.83 ms.  Where four heads leave compute units without work eight would only leave more:
+// one request of a row behind 512 15.8 us with four heads, 18.0 with eight; unless the keys are split, where the sums decide again
+// (3 of a row behind 12000 64 -> 54 us).
+bool eight_heads(const skv_attn_desc* d, int32_t n_req, int64_t total_q_rows, int32_t max_blocks, bool split) {
+  if ((d->n_q_heads / d->n_kv_heads) % 8) return false;
+  const int64_t rows = mean_rows(n_req, total_q_rows);
+  const float kt = (float)key_tiles(rows, max_blocks), at_ends = 6.f * kTileFull;   // at_ends: of a workgroup outside its loop
+  const float tiles8 = std::max(1.f, rows / 32.f + 0.5f), tiles4 = std::max(1.f, rows / 64.f + 0.5f);
+  const float wgs8 = (float)n_req * (d->n_q_heads / 8) * tiles8, wgs4 = (float)n_req * (d->n_q_heads / 4) * tiles4;
+  const float full = kt * kTileFull + at_ends, last4 = kt * (rows <= 32 ? kTileHalf : 0.5f * (kTileHalf + kTileFull)) + at_ends;
+  const float time8 = wgs8 * (full + (rows > 32 ? 0.5f * kTileFull : 0.f));
+  const float time4 = (float)n_req * (d->n_q_heads / 4) * ((tiles4 - 1.f) * full + last4);
+  if (wgs4 <= kCus) {
+    if (!split) return false;
+    if (rows > 32) return kt >= 32 && time8 < 0.98f * time4;
+    return split_time(wgs8 * kt * kTileFull / kCus, (float)rows / kRowsPerWave) < 0.9f * whole_time(wgs4, kt * kTileHalf, 0.f);
+  }
+  return std::max(time8, kCus * full) < time4;
 }
 size_t split_bytes(const Layout& y) {
   return y.max_parts ? kCus * kSplitInts * sizeof(int32_t) + (size_t)y.max_parts * y.units * kSlotFloats * sizeof(float) : 0;
@@ -1107,7 +1159,8 @@ static int prefill_attn_enqueue(const skv_attn_desc* desc, int32_t n_req, const 
   char* const split_area = (char*)d_workspace + list_bytes(desc, y);
   p.splits = y.max_parts ? (const int32_t*)split_area : nullptr;
   p.partials = y.max_parts ? (float*)(split_area + kCus * kSplitInts * sizeof(int32_t)) : nullptr;
-  attn_schedule_kernel<<<1, kSchedThreads, 0, st>>>(n_req, d_q_off, d_matched_len, y.pos_per_wg, (int)y.max_items, y.units,
+  attn_schedule_kernel<<<1, kSchedThreads, 0, st>>>(n_req, d_q_off, d_matched_len, y.pos_log, (int)y.max_items, y.units,
+                                                    (float)total_q_rows * y.heads_per_wg,
                                                     (int32_t*)d_workspace, (int32_t*)p.items, (int32_t*)p.splits,
                                                     (uint4*)p.zero_page, (int)(zero_page_bytes(desc) / 16));
   SKV_HIP(hipGetLastError());
@@ -1137,9 +1190,9 @@ extern "C" int skv_prefill_attn(const skv_attn_desc* desc, int32_t n_req, const 
                           d_out);
   if (rc) return rc;
   // a workspace that holds the plain work list is enough: the call then splits nothing, and takes 32-row tiles if their list fits
-  Layout y = layout_for(desc, n_req, total_q_rows, true, true);
+  Layout y = layout_for(desc, n_req, total_q_rows, eight_heads(desc, n_req, total_q_rows, max_blocks, true), true);
   if (y.max_parts && (!may_split(y, n_req, total_q_rows, max_blocks) || workspace_bytes < list_bytes(desc, y) + split_bytes(y)))
-    y = layout_for(desc, n_req, total_q_rows, true, false);
+    y = layout_for(desc, n_req, total_q_rows, eight_heads(desc, n_req, total_q_rows, max_blocks, false), false);
   if (workspace_bytes < list_bytes(desc, y)) y = layout_for(desc, n_req, total_q_rows, false, false);
   if (!d_workspace || workspace_bytes < list_bytes(desc, y)) return SKV_ENOMEM;
   if ((uintptr_t)d_workspace & 15) return SKV_EINVAL;
@@ -1185,7 +1238,7 @@ extern "C" int skv_prefill_attn_static(const skv_attn_desc* desc, int32_t n_req,
   rc = check_attn_buffers(d_q, d_knew, d_vnew, d_q_off, d_kpool, d_vpool, d_matched_len, d_page_table, max_blocks,
                           d_out);
   if (rc) return rc;
-  Layout y = layout_for(desc, n_req, total_q_rows, true, false);
+  Layout y = layout_for(desc, n_req, total_q_rows, eight_heads(desc, n_req, total_q_rows, max_blocks, false), false);
   if (list_bytes(desc, y) > (size_t)SKV_STATIC_SCRATCH_BYTES) y = layout_for(desc, n_req, total_q_rows, false, false);
   if (list_bytes(desc, y) > (size_t)SKV_STATIC_SCRATCH_BYTES) return SKV_ERANGE;   // batch too large for the built-in scratch
   void* ws = nullptr;

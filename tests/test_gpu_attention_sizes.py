@@ -162,6 +162,35 @@ def test_bf16_work_list_of_many_requests(hq, hkv):
     assert np.abs(got - want).max() <= 2e-2
 
 
+# Eight query heads per kv head: tiles of 32 rows of eight heads or of 64 rows of four, whichever the lengths favour.  One request
+# or several that fill less than the chip; tables wider than what is reused; enough
+# to fill the chip with short and with ragged requests, with the last tile on either side of 32 rows.
+EIGHT = [
+    (64, 8, [1], [2], 600), (16, 2, [40, 64, 65, 33], [0, 1, 2, 9], 700), (8, 1, [64, 200], [7, 3], 10), (16, 1, [1] * 300, [1] * 300, 1),
+    (64, 8, [20] * 40, [3] * 40, 3), (16, 2, [97, 31, 160, 0, 1] * 40, [1, 0, 2, 3, 1] * 40, 3), (64, 8, [300] * 3, [20] * 3, 20),
+    (32, 2, [33] * 200, [2] * 200, 2),
+]
+
+
+@pytest.mark.parametrize("case", range(len(EIGHT)))
+@pytest.mark.parametrize("static", [False, True])
+def test_bf16_eight_heads(case, static):
+    from paper_2508_08438_amd import binding as skv
+    hq, hkv, S, k, width = EIGHT[case]
+    c = attn_case(80 + case, len(S), hq, hkv, 128, torch.bfloat16, width, S, k, n_pages=sum(k) + 3)
+    if static:
+        x = {n: (v if torch.is_tensor(v) else torch.from_numpy(v)).to("cuda:0") for n, v in c.items()}
+        out = torch.full_like(x["q"], 7.0)
+        skv.skv_prefill_attn_static(skv.attn_desc(hq, hkv, 128, "bf16"), x["q"], x["knew"], x["vnew"], x["q_off"], x["kpool"],
+                                    x["vpool"], x["matched_len"], x["page_table"], width, out)
+        got = out.double().cpu().numpy()
+    else:
+        got = run_attn(c)
+    want = oracle.attention(**c, n_threads=16)
+    assert np.isfinite(got).all()
+    assert np.abs(got - want).max() <= 2e-2
+
+
 def _run_with(c, workspace_bytes):
     from paper_2508_08438_amd import binding as skv
     dev = "cuda:0"
