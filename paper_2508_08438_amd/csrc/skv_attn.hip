@@ -22,6 +22,7 @@
 // fp32 path: skv_attn_f32.hip.
 #include <algorithm>
 #include <atomic>
+#include <climits>
 
 #include "skv_internal.h"
 
@@ -75,8 +76,8 @@ struct AttnParams {
 // ---- work list ---------------------------------------------------------------------------------
 // One workgroup.  items[] lists one 32-byte record per (request, q tile) pair -- {request, first suffix row of
 // the tile, first row of the request in Q, its suffix length S, its reused length L, end row of the tile, first key tile,
-// part} -- so that a workgroup of the attention kernel learns everything about its piece of work from one load.  Requests
-// with the most keys first, and of a request its heaviest (last) tile: what runs last is short, so the chip empties evenly,
+// part} -- so that a workgroup of the attention kernel learns everything about its piece of work from one load.  Where it
+// pays (order_above) requests with the most keys come first, and of a request always its heaviest (last) tile: what runs last is short, so the chip empties evenly,
 // and the tiles of a request stay together, so they find its keys in L2.  The q tiles of a request are cut so that
 // L + (first row of a tile) is a multiple of the 64-key tile (or of the q tile where that is shorter): the first tile is
 // short when L is not, and every later tile ends where a key tile ends, so
@@ -95,7 +96,7 @@ struct AttnParams {
 //
 // The kernel is a chain of dependent steps on one compute unit, so every step is short: requests are ordered by a histogram
 // of their lengths, scans go through registers, and the search for c tries sixteen lengths at a time, one per wavefront
-// (one request of 257 rows: 10 us, 18 with one length at a time; lists without a split 4.3 us).  Order by length and
+// (one request of 257 rows: 10 us, 18 with one length at a time; lists without a split 3.6 us).  Order by length and
 // 32-row tiles: 32 requests of 264 rows behind 16..32 k keys, 64/8 heads: 7.32 -> 6.83 ms; 16 requests of 97..994 rows
 // behind up to 8 k, 32/8 heads (order only): 525 -> 512 us.
 constexpr int kItemInts = 8;
@@ -186,7 +187,7 @@ __device__ inline int place_of(const int* scan, int n, int x) {
 
 __global__ __launch_bounds__(kSchedThreads) void attn_schedule_kernel(
     int n_req, const int32_t* __restrict__ q_off, const int32_t* __restrict__ matched_len, int pos_log, int max_items,
-    int units /* workgroups per item */,
+    int units /* workgroups per item */, int order_above /* requests are ordered by length if one is longer */,
     float rows_filled /* query rows, over the heads of a workgroup */,
     int32_t* __restrict__ n_items /* [0] items, [1] split items */, int32_t* __restrict__ items, int32_t* __restrict__ splits /* null: never split */, uint4* __restrict__ zero_page,
     int zero_vec) {
@@ -203,14 +204,14 @@ __global__ __launch_bounds__(kSchedThreads) void attn_schedule_kernel(
     const int keys = mine.nt > 0 ? mine.L + mine.S : 0;
     // place in the order of falling length, to 1 / kBuckets of the longest
     int place = tid, longest = 0;
-    if (n_here > 1) {
+    if (n_here > 1 && order_above < INT_MAX) {
       const int m = wave_max(keys);
       if (lane == 0) red[wave] = m;
       if (tid < kBuckets) bucket[tid] = 0;
       __syncthreads();
       longest = wave_max(lane < kSchedWaves ? red[lane] : 0);
     }
-    if (longest > 0) {
+    if (longest > order_above) {
       int b = 0, rank = 0;
       if (r < n_req) {
         b = kBuckets - 1 - (int)((float)keys * ((kBuckets - 0.5f) / (float)max(longest, 1)));
@@ -1086,6 +1087,14 @@ bool eight_heads(const skv_attn_desc* d, int32_t n_req, int64_t total_q_rows, in
   }
   return std::max(time8, kCus * full) < time4;
 }
+// Keys above which a longest request has the requests ordered by length.  Order is worth its 1.3 us where workgroups queue and
+// one that starts late ends late: in a few rounds (64 requests of up to 39 rows behind up to 496, 16 query heads over 1: 42 ->
+// 35 us), or behind long prefixes; many rounds of short requests run better as they come (200 of up to 63 rows, 32 over 8: 60.6 ->
+// 55).
+int order_above(const Layout& y, int32_t n_req, int64_t total_q_rows) {
+  const float tiles = std::max(1.f, (float)mean_rows(n_req, total_q_rows) / (1 << y.pos_log) + 0.5f), wgs = tiles * n_req * y.units;
+  return wgs <= kCus ? INT_MAX : wgs <= 4 * kCus ? 0 : 1024;
+}
 size_t split_bytes(const Layout& y) {
   return y.max_parts ? kCus * kSplitInts * sizeof(int32_t) + (size_t)y.max_parts * y.units * kSlotFloats * sizeof(float) : 0;
 }
@@ -1160,7 +1169,7 @@ static int prefill_attn_enqueue(const skv_attn_desc* desc, int32_t n_req, const 
   p.splits = y.max_parts ? (const int32_t*)split_area : nullptr;
   p.partials = y.max_parts ? (float*)(split_area + kCus * kSplitInts * sizeof(int32_t)) : nullptr;
   attn_schedule_kernel<<<1, kSchedThreads, 0, st>>>(n_req, d_q_off, d_matched_len, y.pos_log, (int)y.max_items, y.units,
-                                                    (float)total_q_rows * y.heads_per_wg,
+                                                    order_above(y, n_req, total_q_rows), (float)total_q_rows * y.heads_per_wg,
                                                     (int32_t*)d_workspace, (int32_t*)p.items, (int32_t*)p.splits,
                                                     (uint4*)p.zero_page, (int)(zero_page_bytes(desc) / 16));
   SKV_HIP(hipGetLastError());
