@@ -1083,7 +1083,7 @@ bool eight_heads(const skv_attn_desc* d, int32_t n_req, int64_t total_q_rows, in
   if (wgs4 <= kCus) {
     if (!split) return false;
     if (rows > 32) return kt >= 32 && time8 < 0.98f * time4;
-    return split_time(wgs8 * kt * kTileFull / kCus, (float)rows / kRowsPerWave) < 0.9f * whole_time(wgs4, kt * kTileHalf, 0.f);
+    return split_time(wgs8 * kt * kTileFull / kCus, (float)rows / kRowsPerWave) < whole_time(wgs4, kt * kTileHalf, 0.f);
   }
   return std::max(time8, kCus * full) < time4;
 }
