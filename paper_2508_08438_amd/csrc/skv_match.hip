@@ -101,9 +101,11 @@ __global__ __launch_bounds__(kWave* kWavesPerWg) void skv_match_kernel(
   int32_t* row = page_table + (size_t)r * max_blocks;
   const uint32_t tbit = 1u << (tenant & 31);
   uint32_t* const tenants = t.ctr + (size_t)(1 + (tenant >> 5)) * t.ctr_plane;   // the bitmap word this tenant is in
-  // Steps of a node whose loads are in flight together.  Few requests wait for their own loads; many cover each other's, and
-  // one step takes 60 registers less, so that all wavefronts of 4096 requests are resident (34.3 us with four steps, 30.6 with
-  // two, 28.4 with one; 16384 requests 60.2 -> 54.3).
+  // Steps of a node whose loads are in flight together.  A workgroup per request waits for its own loads: four.  A wavefront per
+  // request has others beside it that cover them, and the shorter round compares less past the end of a match: one.  Requests of
+  // 500 matched blocks, one against four steps: 513 22 / 24 us, 1000 23 / 25, 2048 27 / 31; above 2048 four steps also
+  // take too many registers (184 against 80) for all wavefronts to be resident: 2500 31 / 43, 8192 72 / 96.  5 or 60 blocks: no
+  // difference up to 2048, 8192 17 / 22 and 22 / 31.
   constexpr int kAhead = kCoop > 1 ? 4 : 1;
   constexpr int kGroup = kAhead * kStepBlocks;        // blocks one wavefront compares per round
   constexpr int kRound = kCoop * kGroup;
