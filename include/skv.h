@@ -54,7 +54,8 @@ int skv_last_hip_error(void);
 
 /* Opaque host handle; owns host memory only: a copy of the index's structure and, from the first skv_tree_insert,
  * skv_evict or skv_tree_compact on, 1 MiB of pinned memory that small transfers go through (without it, or where they do not
- * fit, they are copies from ordinary memory).  skv_tree_destroy leaves the pinned piece to the next tree that needs one; that
+ * fit, they are copies from ordinary memory).  The arrays an insertion and a compaction work on stay with the handle as well:
+ * up to a second copy of the structure, and 76 bytes per block record.  skv_tree_destroy leaves the pinned piece to the next tree that needs one; that
  * tree frees all but four of those it finds. */
 typedef struct skv_tree skv_tree;
 
