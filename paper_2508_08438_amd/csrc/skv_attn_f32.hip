@@ -2,12 +2,13 @@
 // the request's own new rows), with fp32 accuracy in products, sums and softmax.
 //
 // The contractions run on the bf16 matrix instruction, whose rate is sixteen times that of the fp32 one, on operands split
-// into three bf16 pieces each (exactly; what has no exact pieces is taken row by row in plain fp32): a = a0 + a1 + a2, a . b = the six products a_i b_j with i + j <= 2, all accumulated in
-// fp32; what is left out is below 2^-24 of the product.  Against 64-bit sums the results are 1.1e-7 to 2.2e-7 off (2-norm;
-// N(0,1) inputs, 200 to 3000 keys) where fp32 multiply-adds, one key after another per lane, are 1.7e-7 to 2.9e-7 off and the
-// fp32 matrix instruction 2.3e-7 to 5.8e-7; with scores 6 and 30 times as wide the three keep that order.  The products are formed transposed, S^T = K Q^T and O^T = V^T P^T,
-// so a query is a lane column: the softmax is a register reduction plus one exchange between the halves of the wavefront,
-// and the accumulator registers of S^T are the B operand of the second product as they stand.
+// into three bf16 pieces each (exactly; what has no exact pieces is taken row by row in plain fp32): a = a0 + a1 + a2, a . b =
+// the six products a_i b_j with i + j <= 2, all accumulated in fp32; what is left out is below 2^-24 of the product.  Against
+// 64-bit sums the results are 1.1e-7 to 2.2e-7 off (2-norm; N(0,1) inputs, 200 to 3000 keys) where fp32 multiply-adds, one key
+// after another per lane, are 1.7e-7 to 2.9e-7 off and the fp32 matrix instruction 2.3e-7 to 5.8e-7; with scores 6 and 30
+// times as wide the three keep that order.  The products are formed transposed, S^T = K Q^T and O^T = V^T P^T, so a query is a
+// lane column: the softmax is a register reduction plus one exchange between the halves of the wavefront, and the accumulator
+// registers of S^T are the B operand of the second product as they stand.
 #include "skv_internal.h"
 
 namespace {
