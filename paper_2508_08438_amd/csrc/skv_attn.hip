@@ -789,7 +789,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
     if (active(h + 1)) {
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        lds_wait(0, kfr[i & 3]);
+        lds_wait(3, kfr[i & 3]);
         dst = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfr[i & 3], qf[i], i == 0 ? zero16 : dst, 0, 0, 0);
         kfr[i & 3] = i < 4 ? k_frag(kb, i + 4) : k_frag(kb_next, i - 4);
         __builtin_amdgcn_sched_barrier(0);
@@ -798,7 +798,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
     if (h > 0 && active(h - 1)) {
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        lds_wait(0, vfr[i & 3]);
+        lds_wait(6, vfr[i & 3]);
         o[i & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vfr[i & 3], p_use[i >> 2], o[i & 3], 0, 0, 0);
         vfr[i & 3] = i < 4 ? v_frag(vb, i + 4) : v_frag(vb_next, i - 4);
         __builtin_amdgcn_sched_barrier(0);
@@ -841,7 +841,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
   if (active(0)) {
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) {
-      lds_wait(0, kfr[ks & 3]);
+      lds_wait(3, kfr[ks & 3]);
       s[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfr[ks & 3], qf[ks], ks == 0 ? zero16 : s[0], 0, 0, 0);
       kfr[ks & 3] = ks < 4 ? k_frag(k_base, ks + 4) : k_frag(k_base + kHalfBytes, ks - 4);
       __builtin_amdgcn_sched_barrier(0);
