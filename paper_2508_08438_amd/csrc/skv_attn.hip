@@ -361,16 +361,15 @@ __global__ __launch_bounds__(kSchedThreads) void attn_schedule_kernel(
 }
 
 // ---- bf16 MFMA kernel --------------------------------------------------------------------------
-// Value of the lane 32 positions away (the other half of the wavefront): v_permlane32_swap exchanges the
-// upper half of its first operand with the lower half of its second.
-__device__ inline float swap_halves(float x) {
+// max / sum of a value and the one 32 lanes away (the other half of the wavefront): v_permlane32_swap exchanges the upper
+// half of its first operand with the lower half of its second, after which `a` holds the lower half's value in both halves
+// and `b` the upper half's, so no lane select is needed
+__device__ inline float sum_halves(float x) {
   float a = x, b = x;
   // the wait states the compiler places between a VALU write and this instruction are added by hand
   asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(a), "+v"(b));
-  return (threadIdx.x & 32) ? a : b;
+  return a + b;
 }
-// max / sum of a value and the one 32 lanes away: after the swap `a` holds the lower half's value in both halves
-// and `b` the upper half's, so no lane select is needed
 __device__ inline float max_halves(float x) {
   float a = x, b = x;
   asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(a), "+v"(b));
@@ -403,6 +402,20 @@ __device__ __forceinline__ void lds_wait(int n, bf16x8& a, bf16x8& b, bf16x8& c,
   asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(a), "+v"(b), "+v"(c), "+v"(d) : "i"(n));
 }
 
+// A wavefront's 32 query rows: up to four heads of as few positions (lane l: head l % heads of position l / heads), so that the
+// last tile of a request occupies no more wavefronts than its rows fill, and the rows of a position come and go as one
+// piece of memory.
+struct Packing {
+  int heads_log, groups_log;   // logarithms: heads of a wavefront; wavefronts per position
+  __device__ __forceinline__ void wave(int w, int row0, int& head, int& row) const {   // first head (within the workgroup's) and row
+    head = (w & ((1 << groups_log) - 1)) << heads_log;
+    row = row0 + ((w >> groups_log) << (5 - heads_log));
+  }
+};
+__host__ __device__ __forceinline__ Packing packing(int heads_per_wg) {
+  return heads_per_wg == 8 ? Packing{2, 1} : heads_per_wg == 4 ? Packing{2, 0} : heads_per_wg == 2 ? Packing{1, 0} : Packing{0, 0};
+}
+
 // Workgroup b runs on XCD b % 8: all work of one kv head stays on one XCD where the heads allow it, so its K/V tiles are
 // re-read from that XCD's L2, and the merge finds the parts there.
 __device__ __forceinline__ void unit_of_block(int b, int Hkv, int n_hg, int& item, int& kvh, int& hg) {
@@ -429,14 +442,14 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
   __bf16* const Vs = smem + kKStages * kTile;
   // [kWaves][16 rows][16 chunks of 8 bf16]: each wave's own staging tile for its Q rows on the way in and its O rows
   // on the way out (16 rows at a time), 16-byte chunks XOR-swizzled by row so that row-wise and fragment-wise
-  // accesses are conflict free
-  __bf16* const stage = Vs + kVStages * kTile + (threadIdx.x >> 6) * (kStageRows * kD);
+  // accesses are conflict free: `stage` below
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform by construction
   const int l32 = lane & 31;
   const int half = lane >> 5;
+  __bf16* const stage = Vs + kVStages * kTile + wave * (kStageRows * kD);
 
   // ---- which piece of work: XCD-aware decode (workgroup b runs on XCD b % 8) ----
   const int G = p.Hq / p.Hkv;
@@ -458,10 +471,13 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
   const int S = __builtin_amdgcn_readfirstlane(rec0.w);
   const int Ltot = L + S;
 
-  const int head = kvh * G + hg * p.heads_per_wg + (wave % p.heads_per_wg);
-  const int pos0 = row0 + (wave / p.heads_per_wg) * kRowsPerWave;             // first row of this wave
+  const Packing pk_of = packing(p.heads_per_wg);
+  const int hl_log = pk_of.heads_log;
+  int head0, pos0;                                                            // first head and row of this wave
+  pk_of.wave(wave, row0, head0, pos0);
+  head0 += kvh * G + hg * p.heads_per_wg;
   const int n_tiles = part ? part & ((1 << kPartBits) - 1) : (L + row1 + kBN - 1) / kBN;   // 64-key tiles the workgroup streams
-  const int wave_key_end = pos0 < row1 ? min(L + min(row1, pos0 + kRowsPerWave), n_tiles * kBN) : 0;  // this wave needs keys [0, wave_key_end)
+  const int wave_key_end = pos0 < row1 ? min(L + min(row1, pos0 + (kRowsPerWave >> hl_log)), n_tiles * kBN) : 0;  // this wave needs keys [0, wave_key_end)
   const int32_t* const table = p.page_table + (size_t)r * p.max_blocks + kt0 * (kBN / SKV_BLOCK_TOKENS);
   const int table_len = p.max_blocks - kt0 * (kBN / SKV_BLOCK_TOKENS);
 
@@ -512,7 +528,8 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const int rr = (lane >> 4) + 4 * i;
-      const int row = min(pos0 + rr, S - 1);   // rows past the tile or the request are computed and dropped
+      const int row = min(pos0 + (rr >> hl_log), S - 1);   // rows past the tile or the request are computed and dropped
+      const int head = head0 + (rr & ((1 << hl_log) - 1));
       qv[i] = *(const u32x4*)((const __bf16*)p.q + ((size_t)(qbase + row) * p.Hq + head) * kD + c16 * 8);
     }
   }
@@ -541,10 +558,11 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
 
   // ---- global -> LDS, without a stop in registers ----
   // A tile is four 16-key groups; a group is one page of the pool or 16 consecutive new rows.  Each wavefront
-  // moves two segments of a tile (segments w and w + 8: keys 4w.. and 32 + 4w..) with direct-to-LDS loads: lane i
-  // fetches chunk 4 (i / 16) + i % 4 of key (i / 4) % 4 of the segment and the hardware puts it at slot i.
+  // moves two segments of a tile, half a group (2w and 2w + 1: keys 8w ..), with direct-to-LDS loads: lane i
+  // fetches chunk 4 (i / 16) + i % 4 of key (i / 4) % 4 of the segment and the hardware puts it at slot i.  Both take the
+  // group's base as the buffer's and differ in the scalar offset: no vector address is formed.
   const unsigned row_bytes = (unsigned)p.Hkv * kD * 2u;
-  const int t_row = (wave & 3) * 4 + ((lane >> 2) & 3);      // row of the 16-key group this lane fetches
+  const int t_row = (wave & 1) * 8 + ((lane >> 2) & 3);      // row of the 16-key group this lane fetches, and 4 further on
   const unsigned t_col = (unsigned)((lane >> 4) * 4 + (lane & 3)) * 16u;
   const unsigned t_off = (unsigned)t_row * row_bytes + t_col;
   // Group base addresses, one 16-key group per lane for 64 groups (16 tiles, a "window"): a pool page, 16 new rows,
@@ -554,43 +572,42 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
   auto lane_bcast = [&](uint64_t x, int idx) __attribute__((always_inline)) {
     const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)x, idx);
     const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), idx);
-    return (const __attribute__((address_space(1))) char*)(((uint64_t)hi << 32) | lo);   // global, not flat
+    return ((uint64_t)hi << 32) | lo;
   };
   uint64_t ak_cur, av_cur, ak_nxt, av_nxt;
   int win = 0;                       // window held in *_cur; *_nxt holds window win + 1
   window_bases(0, page_w0, ak_cur, av_cur);
   window_bases(1, page_w1, ak_nxt, av_nxt);
   typedef __attribute__((address_space(3))) void lds_void;
-  // one pool (K or V) of tile t into an LDS stage; `bases` holds the window of tile t
-  auto load_half_tile = [&](uint64_t bases, int t, __bf16* dst_stage) __attribute__((always_inline)) {
-    const int key_base = t * kBN;
-    __bf16* const dst = dst_stage + wave * kSeg;
+  const int group = wave >> 1;                               // 16-key group of this wave's segments
+  const unsigned quarter = 4u * row_bytes;
+  // one pool (K or V) of tile t into an LDS stage; `base`: of the wave's group
+  auto issue_half_tile = [&]<bool kWhole>(uint64_t base, int t, __bf16* dst_stage) __attribute__((always_inline)) {
+    __bf16* const dst = dst_stage + 2 * wave * kSeg;
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (int)(4 * quarter), 0x00020000);
+    if (!kWhole && t * kBN + kBN > Ltot) {   // the sequence ends inside this tile: rows past its end re-read its last row,
+      const int n_valid = Ltot - (t * kBN + group * 16);   // finite values that the causal mask keeps out
+      const int last = n_valid > 0 ? min(n_valid, 16) - 1 : 15;
 #pragma unroll
-    for (int cc = 0; cc < 2; ++cc) {
-      const int g = (wave >> 2) + 2 * cc;                    // 16-key group of segment wave + 8 cc
-      const int idx = ((t & 15) << 2) + g;
-      const auto gb = lane_bcast(bases, idx);
-      unsigned off = t_off;
-      if (key_base + kBN > Ltot) {  // the sequence ends inside this tile: rows past its end re-read its last row,
-        const int n_valid = Ltot - (key_base + g * 16);  // finite values that the causal mask keeps out
-        if (n_valid > 0 && n_valid < 16) off = (unsigned)min(t_row, n_valid - 1) * row_bytes + t_col;
-      }
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(gb + off),
-                                       (lds_void*)(dst + cc * 8 * kSeg), 16, 0, 0);
+      for (int cc = 0; cc < 2; ++cc)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void*)(dst + cc * kSeg), 16,
+                                                 (unsigned)min(t_row + 4 * cc, last) * row_bytes + t_col, 0, 0, 0);
+    } else {
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void*)dst, 16, t_off, 0, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void*)(dst + kSeg), 16, t_off, quarter, 0, 0);
     }
   };
   auto load_k_tile = [&](int t, int stage_idx) __attribute__((always_inline)) {
-    load_half_tile((t >> 4) == win ? ak_cur : ak_nxt, t, Ks + stage_idx * kTile);
+    issue_half_tile.template operator()<false>(lane_bcast((t >> 4) == win ? ak_cur : ak_nxt, ((t & 15) << 2) + group), t, Ks + stage_idx * kTile);
   };
   auto load_v_tile = [&](int t, int stage_idx) __attribute__((always_inline)) {
-    load_half_tile((t >> 4) == win ? av_cur : av_nxt, t, Vs + stage_idx * kTile);
+    issue_half_tile.template operator()<false>(lane_bcast((t >> 4) == win ? av_cur : av_nxt, ((t & 15) << 2) + group), t, Vs + stage_idx * kTile);
   };
-  // Inside the main loop the same loads are split in two: the segment bases of the tiles an iteration will request
+  // Inside the main loop the same loads are split in two: the bases of the tiles an iteration will request
   // (K two tiles ahead, V one) are broadcast out of the windows during the iteration before, between its half-steps,
   // so that the iteration itself starts with nothing but the four load instructions.  Right after a barrier every
   // wave of the workgroup is at this point at once, and what stands here keeps all matrix cores waiting.
-  typedef const __attribute__((address_space(1))) char* gptr;
-  gptr nk[2], nv[2];
+  uint64_t nk = 0, nv = 0;
   int pend_page = -1;
   bool pend = false;
   auto prep_bases = [&](int kt_next) __attribute__((always_inline)) {
@@ -601,27 +618,10 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
       pend_page = window_page(win + 1);
       pend = true;
     }
-    const int tk = kt_next + 2, tv = kt_next + 1;
-#pragma unroll
-    for (int cc = 0; cc < 2; ++cc) {
-      const int g = (wave >> 2) + 2 * cc;
-      nk[cc] = lane_bcast((tk >> 4) == win ? ak_cur : ak_nxt, ((tk & 15) << 2) + g);
-      nv[cc] = lane_bcast((tv >> 4) == win ? av_cur : av_nxt, ((tv & 15) << 2) + g);
-    }
-  };
-  auto issue_half_tile = [&]<bool kWhole>(const gptr (&b)[2], int t, __bf16* dst_stage) __attribute__((always_inline)) {
-    const int key_base = t * kBN;
-    __bf16* const dst = dst_stage + wave * kSeg;
-#pragma unroll
-    for (int cc = 0; cc < 2; ++cc) {
-      unsigned off = t_off;
-      if (!kWhole && key_base + kBN > Ltot) {   // as in load_half_tile
-        const int n_valid = Ltot - (key_base + ((wave >> 2) + 2 * cc) * 16);
-        if (n_valid > 0 && n_valid < 16) off = (unsigned)min(t_row, n_valid - 1) * row_bytes + t_col;
-      }
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(b[cc] + off),
-                                       (lds_void*)(dst + cc * 8 * kSeg), 16, 0, 0);
-    }
+    const int tk = kt_next + 2, tv = kt_next + 1;   // (V's window is the current one)
+    const int ik = ((tk & 15) << 2) + group;
+    nk = (tk >> 4) == win ? lane_bcast(ak_cur, ik) : lane_bcast(ak_nxt, ik);
+    nv = lane_bcast(av_cur, ((tv & 15) << 2) + group);
   };
   // a wave's direct loads are in LDS once its vector-memory counter has drained; the barrier then publishes them
   auto tile_barrier = [&]() __attribute__((always_inline)) {
@@ -657,11 +657,11 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
   // lane % 2 of chunk 4 a + 2 ((lane / 16) % 2) + (lane % 4) / 2.
   const int v_lane = half * kSeg + ((lane & 15) >> 2) * 32 + (2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) * 8 + 4 * (lane & 1);
   // fragment addresses are LDS byte addresses: a per-lane base plus constants that fit the offset field
-  auto k_frag = [&](uint32_t kb, int ks) __attribute__((always_inline)) {   // kb: stage + k_lane + mt * 8 kSeg
-    return lds_read_b128(kb, ((ks >> 1) * 128 + (ks & 1) * 16) * 2);
+  auto k_frag = [&](uint32_t kb, int ks, int more = 0) __attribute__((always_inline)) {   // kb + more: stage + k_lane + mt * 8 kSeg
+    return lds_read_b128(kb, ((ks >> 1) * 128 + (ks & 1) * 16) * 2 + more);
   };
-  auto v_frag = [&](uint32_t vb, int j) __attribute__((always_inline)) {   // vb: stage + v_lane + h * 8 kSeg; j = (g, a)
-    const int off = ((j >> 2) * 4 * kSeg + (j & 3) * 128) * 2;
+  auto v_frag = [&](uint32_t vb, int j, int more = 0) __attribute__((always_inline)) {   // vb + more: stage + v_lane + h * 8 kSeg; j = (g, a)
+    const int off = ((j >> 2) * 4 * kSeg + (j & 3) * 128) * 2 + more;
     const s16x4 lo = lds_read_tr16_b64(vb, off);
     const s16x4 hi = lds_read_tr16_b64(vb, off + 2 * kSeg * 2);
     return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
@@ -670,7 +670,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
   auto mask = [&](f32x16& x, int u) __attribute__((always_inline)) {
     const int key0 = u * 32;
     if (key0 + 31 > L + pos0) {
-      const int limit = L + pos0 + l32;  // last visible key of this lane's query
+      const int limit = L + pos0 + (l32 >> hl_log);  // last visible key of this lane's query
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
         const int key = key0 + (e >> 2) * 8 + half * 4 + (e & 3);
@@ -735,7 +735,8 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
   // each MFMA with fragments 4..7 and then with fragments 0..3 of the following sub-tile.
   // Fast form (every stage at work, no masked key in sub-tile h): the 16 MFMAs alternate and carry the softmax between
   // them; a fragment is waited for four pair-steps after its request, with eleven (K) or ten (V^T) younger reads.
-  auto half_step_fast = [&]<bool kMask>(int h, uint32_t kb, uint32_t kb_next, uint32_t vb, uint32_t vb_next, f32x16& dst,
+  auto half_step_fast = [&]<bool kMask, int kOff = 0, int kOffNext = 0, int vOff = 0, int vOffNext = 0>(
+                                        int h, uint32_t kb, uint32_t kb_next, uint32_t vb, uint32_t vb_next, f32x16& dst,
                                         f32x16& cur, bf16x8 (&p_use)[2], bf16x8 (&p_make)[2]) __attribute__((always_inline)) {
     if (kMask) mask(cur, h);
     ssum[0] = ssum[1] = 0.f;
@@ -748,7 +749,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
     for (int i = 0; i < 8; ++i) {
       lds_wait(11, kfr[i & 3]);
       dst = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfr[i & 3], qf[i], i == 0 ? zero16 : dst, 0, 0, 0);
-      kfr[i & 3] = i < 4 ? k_frag(kb, i + 4) : k_frag(kb_next, i - 4);
+      kfr[i & 3] = i < 4 ? k_frag(kb, i + 4, kOff) : k_frag(kb_next, i - 4, kOffNext);
       const float f0 = __builtin_amdgcn_exp2f(__builtin_fmaf(cur[2 * i], c, -m_ref));
       if (i > 0) {
         f32x2 pr = {e0, e1};
@@ -760,7 +761,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
       __builtin_amdgcn_sched_barrier(0);
       lds_wait(10, vfr[i & 3]);
       o[i & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vfr[i & 3], p_use[i >> 2], o[i & 3], 0, 0, 0);
-      vfr[i & 3] = i < 4 ? v_frag(vb, i + 4) : v_frag(vb_next, i - 4);
+      vfr[i & 3] = i < 4 ? v_frag(vb, i + 4, vOff) : v_frag(vb_next, i - 4, vOffNext);
       const float f1 = __builtin_amdgcn_exp2f(__builtin_fmaf(cur[2 * i + 1], c, -m_ref));
       if (i > 0) {
         ssum[1] += e1;
@@ -832,7 +833,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
   stage_q();
   tile_barrier();
   const uint32_t k_base = lds_addr(Ks + k_lane), v_base = lds_addr(Vs + v_lane);
-  constexpr uint32_t kStageBytes = kTile * 2, kHalfBytes = 8 * kSeg * 2;
+  constexpr int kStageBytes = kTile * 2, kHalfBytes = 8 * kSeg * 2;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     kfr[j] = k_frag(k_base, j);
@@ -866,25 +867,23 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
   // fast form with the mask applied and the general loads.
   const int kt_mid = (wave_key_end - 1) / 64;
   int st0 = 0;   // stage of K(kt) and V(kt); tile t sits in stage t % 3
-  auto iteration = [&]<int kForm>(int kt) __attribute__((always_inline)) {   // 0 general, 1 fast, 2 fast with masks
-    constexpr bool kFast = kForm == 1;
-    const int st1 = st0 == 2 ? 0 : st0 + 1;    // stage of tile kt + 1
-    const int st2 = st1 == 2 ? 0 : st1 + 1;    // stage of tiles kt + 2 and kt - 1
+  auto requests = [&]<bool kFast>(int kt, int st1, int st2) __attribute__((always_inline)) {
     if (__builtin_expect(pend, 0)) {
       window_bases(win + 1, pend_page, ak_nxt, av_nxt);
       pend = false;
     }
     if (kFast || kt + 2 < n_tiles) issue_half_tile.template operator()<kFast>(nk, kt + 2, Ks + st2 * kTile);
     if (kFast || kt + 1 < n_tiles) issue_half_tile.template operator()<kFast>(nv, kt + 1, Vs + st1 * kTile);
+  };
+  auto iteration = [&]<bool kMasked>(int kt) __attribute__((always_inline)) {   // general form, or the fast one with masks
+    const int st1 = st0 == 2 ? 0 : st0 + 1;    // stage of tile kt + 1
+    const int st2 = st1 == 2 ? 0 : st1 + 1;    // stage of tiles kt + 2 and kt - 1
+    requests.template operator()<false>(kt, st1, st2);
     const uint32_t kb0 = k_base + st0 * kStageBytes;   // K(kt)
     const uint32_t kb1 = k_base + st1 * kStageBytes;   // K(kt + 1)
     const uint32_t vbp = v_base + st2 * kStageBytes;   // V(kt - 1)
     const uint32_t vb0 = v_base + st0 * kStageBytes;   // V(kt)
-    if (kForm == 1) {
-      half_step_fast.template operator()<false>(2 * kt, kb0 + kHalfBytes, kb1, vbp + kHalfBytes, vb0, s[1], s[0], pb[1], pb[0]);
-      prep_bases(kt + 1);
-      half_step_fast.template operator()<false>(2 * kt + 1, kb1, kb1 + kHalfBytes, vb0, vb0 + kHalfBytes, s[0], s[1], pb[0], pb[1]);
-    } else if (kForm == 2) {
+    if (kMasked) {
       half_step_fast.template operator()<true>(2 * kt, kb0 + kHalfBytes, kb1, vbp + kHalfBytes, vb0, s[1], s[0], pb[1], pb[0]);
       prep_bases(kt + 1);
       half_step_fast.template operator()<true>(2 * kt + 1, kb1, kb1 + kHalfBytes, vb0, vb0 + kHalfBytes, s[0], s[1], pb[0], pb[1]);
@@ -896,27 +895,46 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
     tile_barrier();
     st0 = st1;
   };
+  // The fast form, three tiles to a turn: the stages are constants and go into the reads' offset fields.
+  auto fast = [&]<int kSt>(int kt) __attribute__((always_inline)) {
+    constexpr int st1 = (kSt + 1) % 3, st2 = (kSt + 2) % 3;
+    constexpr int k0 = kSt * kStageBytes, k1 = st1 * kStageBytes, vp = st2 * kStageBytes, half = kHalfBytes;
+    requests.template operator()<true>(kt, st1, st2);
+    half_step_fast.template operator()<false, k0 + half, k1, vp + half, k0>(2 * kt, k_base, k_base, v_base, v_base, s[1], s[0], pb[1], pb[0]);
+    prep_bases(kt + 1);
+    half_step_fast.template operator()<false, k1, k1 + half, k0, k0 + half>(2 * kt + 1, k_base, k_base, v_base, v_base, s[0], s[1], pb[0], pb[1]);
+    tile_barrier();
+  };
   int kt = 0;
   prep_bases(0);
-  iteration.template operator()<0>(kt++);
-  for (; kt < kt_fast; ++kt) iteration.template operator()<1>(kt);
-  for (; kt < kt_mid; ++kt) iteration.template operator()<2>(kt);
-  for (; kt <= n_tiles; ++kt) iteration.template operator()<0>(kt);
+  iteration.template operator()<false>(kt++);
+  for (; kt + 2 < kt_fast; kt += 3) {   // (st0 is 1)
+    fast.template operator()<1>(kt);
+    fast.template operator()<2>(kt + 1);
+    fast.template operator()<0>(kt + 2);
+  }
+  for (; kt < kt_mid; ++kt) iteration.template operator()<true>(kt);
+  for (; kt <= n_tiles; ++kt) iteration.template operator()<false>(kt);
 
   // ---- a part of a split item: O^T as it lies in the registers, the reference and the row sum
   if (pos0 >= row1) return;
+  // (the lane number anew: what is addressed by it from here on would otherwise be worked out in front of the main loop and
+  // hold registers through it)
+  int lane_e;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane_e));
+  const int row_e = lane_e & 31, half_e = lane_e >> 5;
   if (part) {
     const int slot = (part >> kPartBits) - 1;
     const int unit = kvh * n_hg + hg;
-    f32x4* dst = (f32x4*)(p.partials + ((size_t)slot * p.Hkv * n_hg + unit) * kSlotFloats + (size_t)wave * (64 * 66)) + lane;
-    const float l_all = l_run + swap_halves(l_run);
-    if (pos0 + l32 >= row1) return;   // not a row of the tile: never read
+    f32x4* dst = (f32x4*)(p.partials + ((size_t)slot * p.Hkv * n_hg + unit) * kSlotFloats + (size_t)wave * (64 * 66)) + lane_e;
+    const float l_all = sum_halves(l_run);
+    if (pos0 + (row_e >> hl_log) >= row1) return;   // not a row of the tile: never read
 #pragma unroll
     for (int a = 0; a < 4; ++a)
 #pragma unroll
       for (int i4 = 0; i4 < 4; ++i4)
         dst[(a * 4 + i4) * 64] = f32x4{o[a][i4 * 4], o[a][i4 * 4 + 1], o[a][i4 * 4 + 2], o[a][i4 * 4 + 3]};
-    float* ml = (float*)(dst - lane + 16 * 64) + lane;
+    float* ml = (float*)(dst - lane_e + 16 * 64) + lane_e;
     ml[0] = m_ref;
     ml[64] = l_all;
     return;
@@ -926,13 +944,13 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
   // pieces of one output row.  They go through the wave's staging tile, 16 rows at a time, and leave as whole
   // 256-byte rows.
   {
-    const float lsum = l_run + swap_halves(l_run);
+    const float lsum = sum_halves(l_run);
     const float inv = 1.0f / lsum;
-    const int c16 = lane & 15;
+    const int c16 = lane_e & 15;
 #pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
-      if ((l32 >> 4) == pass) {
-        const int rr = l32 & 15;
+      if ((row_e >> 4) == pass) {
+        const int rr = row_e & 15;
         __bf16* row = stage + rr * kD;
 #pragma unroll
         for (int a = 0; a < 4; ++a)
@@ -944,14 +962,14 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
             bf16x2 y1 = __builtin_convertvector(x1, bf16x2);
             u32x2 wv = {__builtin_bit_cast(uint32_t, y0), __builtin_bit_cast(uint32_t, y1)};
             const int chunk = a * 4 + i4;   // d = 8 chunk + 4 half .. + 3
-            *(u32x2*)(row + (((chunk ^ rr) << 3) + 4 * half)) = wv;
+            *(u32x2*)(row + (((chunk ^ rr) << 3) + 4 * half_e)) = wv;
           }
       }
       // same wave wrote and reads: the LDS operations of one wave complete in order
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int rr = (lane >> 4) + 4 * i;   // row within the pass
-        const int pos = pos0 + 16 * pass + rr;
+        const int rr = (lane_e >> 4) + 4 * i;   // row within the pass
+        const int pos = pos0 + ((16 * pass + rr) >> hl_log), head = head0 + (rr & ((1 << hl_log) - 1));
         const u32x4 v = *(const u32x4*)(stage + rr * kD + ((c16 ^ rr) << 3));
         if (pos < row1) *(u32x4*)((__bf16*)p.out + ((size_t)(qbase + pos) * p.Hq + head) * kD + c16 * 8) = v;
       }
@@ -977,7 +995,10 @@ __global__ __launch_bounds__(kMergeThreads) void attn_merge_kernel(AttnParams p)
     const int parts = p.splits[kSplitInts * si + 4];
     const int row0 = a.x, row1 = a.y, qbase = a.z, slot = a.w;
     const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
-    const int row = row0 + (wave / p.heads_per_wg) * kRowsPerWave + (lane & 31);
+    const Packing pk = packing(p.heads_per_wg);
+    int row, head;
+    pk.wave(wave, row0, head, row);
+    row += (lane & 31) >> pk.heads_log;
     if (row >= row1) continue;
     const size_t stride = (size_t)units * kSlotFloats;   // from one part to the next
     const float* src = p.partials + ((size_t)slot * units + unit) * kSlotFloats + (size_t)wave * (64 * 66);
@@ -1012,7 +1033,7 @@ __global__ __launch_bounds__(kMergeThreads) void attn_merge_kernel(AttnParams p)
       }
     }
     const float inv = 1.0f / l;
-    const int head = kvh * (p.Hq / p.Hkv) + hg * p.heads_per_wg + wave % p.heads_per_wg;
+    head += kvh * (p.Hq / p.Hkv) + hg * p.heads_per_wg + (lane & ((1 << pk.heads_log) - 1));
     __bf16* dst = (__bf16*)p.out + ((size_t)(qbase + row) * p.Hq + head) * kD + 16 * q + 4 * (lane >> 5);
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
