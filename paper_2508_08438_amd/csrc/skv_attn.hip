@@ -398,6 +398,9 @@ __device__ __forceinline__ s16x4 lds_read_tr16_b64(uint32_t addr, int byte_off) 
 __device__ __forceinline__ void lds_wait(int n, bf16x8& a) {
   asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(a) : "i"(n));
 }
+__device__ __forceinline__ void lds_wait(int n, bf16x8& a, bf16x8& b) {
+  asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(a), "+v"(b) : "i"(n));
+}
 __device__ __forceinline__ void lds_wait(int n, bf16x8& a, bf16x8& b, bf16x8& c, bf16x8& d) {
   asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(a), "+v"(b), "+v"(c), "+v"(d) : "i"(n));
 }
@@ -530,7 +533,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
       const int rr = (lane >> 4) + 4 * i;
       const int row = min(pos0 + (rr >> hl_log), S - 1);   // rows past the tile or the request are computed and dropped
       const int head = head0 + (rr & ((1 << hl_log) - 1));
-      qv[i] = *(const u32x4*)((const __bf16*)p.q + ((size_t)(qbase + row) * p.Hq + head) * kD + c16 * 8);
+      qv[i] = __builtin_nontemporal_load((const u32x4*)((const __bf16*)p.q + ((size_t)(qbase + row) * p.Hq + head) * kD + c16 * 8));
     }
   }
   auto stage_q = [&]() __attribute__((always_inline)) {
@@ -734,57 +737,54 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
   // The rings hold fragments 0..3 of sub-tile h + 1 (K) and of sub-tile h - 1 (V^T) on entry and are refilled behind
   // each MFMA with fragments 4..7 and then with fragments 0..3 of the following sub-tile.
   // Fast form (every stage at work, no masked key in sub-tile h): the 16 MFMAs alternate and carry the softmax between
-  // them; a fragment is waited for four pair-steps after its request, with eleven (K) or ten (V^T) younger reads.
+  // them; the two fragments of a pair-step are waited for together, four pair-steps after their request, with nine younger
+  // reads.  kOff ..: constant parts of the four addresses.
   auto half_step_fast = [&]<bool kMask, int kOff = 0, int kOffNext = 0, int vOff = 0, int vOffNext = 0>(
                                         int h, uint32_t kb, uint32_t kb_next, uint32_t vb, uint32_t vb_next, f32x16& dst,
                                         f32x16& cur, bf16x8 (&p_use)[2], bf16x8 (&p_make)[2]) __attribute__((always_inline)) {
     if (kMask) mask(cur, h);
     ssum[0] = ssum[1] = 0.f;
-    // One exponential behind every MFMA, never two in a row: the transcendental unit takes about four issue slots
-    // per instruction but works beside the issue port, so a second one right behind the first would hold the
-    // wavefront until the unit is free again.  The pair is packed and summed one step later, behind the next
-    // exponential.
-    float e0 = 0.f, e1 = 0.f;
+    // One exponential behind every MFMA (and one in front of the first's reads), never two in a row: the transcendental
+    // unit takes about four issue slots per instruction but works beside the issue port, so a second one right behind the
+    // first would hold the wavefront until the unit is free again.  A pair is packed and summed one step later; the last one
+    // comes a step early, so that the sums are there when the last MFMA has been issued.
+    float e[16];
+    auto ex = [&](int k) __attribute__((always_inline)) { e[k] = __builtin_amdgcn_exp2f(__builtin_fmaf(cur[k], c, -m_ref)); };
+    auto pack = [&](int k) __attribute__((always_inline)) {   // pair k
+      f32x2 pr = {e[2 * k], e[2 * k + 1]};
+      const bf16x2 cv = __builtin_convertvector(pr, bf16x2);
+      pk[2 * (k & 3)] = cv[0];
+      pk[2 * (k & 3) + 1] = cv[1];
+      if ((k & 3) == 3) p_make[k >> 2] = pk;
+    };
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      lds_wait(11, kfr[i & 3]);
+      lds_wait(9, kfr[i & 3], vfr[i & 3]);
       dst = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfr[i & 3], qf[i], i == 0 ? zero16 : dst, 0, 0, 0);
+      if (i == 0) ex(0);
       kfr[i & 3] = i < 4 ? k_frag(kb, i + 4, kOff) : k_frag(kb_next, i - 4, kOffNext);
-      const float f0 = __builtin_amdgcn_exp2f(__builtin_fmaf(cur[2 * i], c, -m_ref));
+      ex(2 * i + 1);
       if (i > 0) {
-        f32x2 pr = {e0, e1};
-        const bf16x2 cv = __builtin_convertvector(pr, bf16x2);
-        pk[2 * ((i - 1) & 3)] = cv[0];
-        pk[2 * ((i - 1) & 3) + 1] = cv[1];
-        ssum[0] += e0;
+        pack(i - 1);
+        ssum[0] += e[2 * i - 2];
       }
       __builtin_amdgcn_sched_barrier(0);
-      lds_wait(10, vfr[i & 3]);
       o[i & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vfr[i & 3], p_use[i >> 2], o[i & 3], 0, 0, 0);
       vfr[i & 3] = i < 4 ? v_frag(vb, i + 4, vOff) : v_frag(vb_next, i - 4, vOffNext);
-      const float f1 = __builtin_amdgcn_exp2f(__builtin_fmaf(cur[2 * i + 1], c, -m_ref));
-      if (i > 0) {
-        ssum[1] += e1;
-        if (((i - 1) & 3) == 3) p_make[(i - 1) >> 2] = pk;
+      if (i < 7) ex(2 * i + 2);
+      if (i > 0) ssum[1] += e[2 * i - 1];
+      if (i == 7) {
+        pack(7);
+        ssum[0] += e[14];
+        ssum[1] += e[15];
       }
-      e0 = f0;
-      e1 = f1;
       __builtin_amdgcn_sched_barrier(0);
-    }
-    {
-      f32x2 pr = {e0, e1};
-      const bf16x2 cv = __builtin_convertvector(pr, bf16x2);
-      pk[6] = cv[0];
-      pk[7] = cv[1];
-      ssum[0] += e0;
-      ssum[1] += e1;
-      p_make[1] = pk;
     }
     if (__builtin_expect(__any(!(ssum[0] + ssum[1] <= kSumLimit)), 0)) move_reference(cur, p_make);
     l_run += ssum[0] + ssum[1];
   };
-  // General form (first and last iterations of a wave): each stage is tested, runs as a block of its own, and waits
-  // for every outstanding read.
+  // General form (first and last iterations of a wave): each stage is tested and runs as a block of its own; an MFMA waits
+  // for its fragment with the three requested since behind it.
   auto half_step_slow = [&](int h, uint32_t kb, uint32_t kb_next, uint32_t vb, uint32_t vb_next, f32x16& dst,
                             f32x16& cur, bf16x8 (&p_use)[2], bf16x8 (&p_make)[2]) __attribute__((always_inline)) {
     if (active(h + 1)) {
@@ -971,7 +971,8 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
         const int rr = (lane_e >> 4) + 4 * i;   // row within the pass
         const int pos = pos0 + ((16 * pass + rr) >> hl_log), head = head0 + (rr & ((1 << hl_log) - 1));
         const u32x4 v = *(const u32x4*)(stage + rr * kD + ((c16 ^ rr) << 3));
-        if (pos < row1) *(u32x4*)((__bf16*)p.out + ((size_t)(qbase + pos) * p.Hq + head) * kD + c16 * 8) = v;
+        if (pos < row1)   // (Q and the output pass once: they leave L2 to K and V)
+          __builtin_nontemporal_store(v, (u32x4*)((__bf16*)p.out + ((size_t)(qbase + pos) * p.Hq + head) * kD + c16 * 8));
       }
     }
   }
