@@ -21,6 +21,7 @@ SKV_LIMIT_BRANCH_POINTS, SKV_LIMIT_COPIES, SKV_LIMIT_WALKS = 1, 2, 4
 EXPORTS = ["skv_strerror", "skv_last_hip_error", "skv_tree_build_size", "skv_tree_size_for_capacity", "skv_tree_build", "skv_tree_insert", "skv_set_epoch", "skv_block_epochs_read", "skv_evict", "skv_tree_compact", "skv_mfma_rate",
            "skv_tree_info", "skv_tree_destroy", "skv_match", "skv_match_limits_read", "skv_counters_read",
            "skv_counters_reset", "skv_window_roll", "skv_promote", "skv_block_state_read", "skv_suffix_offsets", "skv_gather_kv",
+           "skv_gather_kv_beside",
            "skv_scatter_kv", "skv_stream_copy", "skv_decode_attn_workspace_size", "skv_decode_attn",
            "skv_prefill_attn_workspace_size", "skv_prefill_attn", "skv_prefill_attn_static"]
 
@@ -83,7 +84,7 @@ def lib():
         l.skv_tree_insert.argtypes = [vp, i32, vp, vp, vp, vp, vp, i32, i32, vp, vp, vp, vp]
         l.skv_scatter_kv.argtypes = [C.POINTER(AttnDesc), i32, vp, vp, vp, vp, i32, vp, vp, i32, vp]
         l.skv_suffix_offsets.argtypes = [i32, vp, vp, vp, vp]
-        l.skv_gather_kv.argtypes = [C.POINTER(AttnDesc), i32, vp, vp, i32, vp, vp, i32, vp, vp, vp, i64, vp]
+        l.skv_gather_kv.argtypes = l.skv_gather_kv_beside.argtypes = [C.POINTER(AttnDesc), i32, vp, vp, i32, vp, vp, i32, vp, vp, vp, i64, vp]
         l.skv_prefill_attn_workspace_size.argtypes = [C.POINTER(AttnDesc), i32, i64, C.POINTER(C.c_size_t)]
         l.skv_prefill_attn.argtypes = [C.POINTER(AttnDesc), i32, vp, vp, vp, vp, i64, vp, vp, i32, vp, vp,
                                        i32, vp, vp, C.c_size_t, vp]
@@ -318,15 +319,16 @@ def skv_suffix_offsets(req_off, matched_len, q_off, stream=None):
 
 
 def skv_gather_kv(desc: AttnDesc, kpool, vpool, matched_len, page_table, max_blocks, ctx_off, kctx, vctx,
-                  stream=None):
+                  stream=None, beside=False):
+    """beside: the form for a stream of its own next to skv_prefill_attn (skv_gather_kv_beside)."""
     n_req = matched_len.numel()
     assert ctx_off.dtype == torch.int64 and ctx_off.numel() == n_req + 1
     row = desc.n_kv_heads * desc.head_dim
     cap = kctx.numel() // row
     assert vctx.numel() // row >= cap
-    _check(lib().skv_gather_kv(C.byref(desc), n_req, _dptr(kpool), _dptr(vpool), kpool.shape[0],
-                               _dptr(matched_len), _dptr(page_table), max_blocks, _dptr(ctx_off),
-                               _dptr(kctx), _dptr(vctx), cap, _stream(stream)), "skv_gather_kv")
+    call = lib().skv_gather_kv_beside if beside else lib().skv_gather_kv
+    _check(call(C.byref(desc), n_req, _dptr(kpool), _dptr(vpool), kpool.shape[0], _dptr(matched_len), _dptr(page_table),
+                max_blocks, _dptr(ctx_off), _dptr(kctx), _dptr(vctx), cap, _stream(stream)), "skv_gather_kv")
 
 
 def skv_prefill_attn_workspace_size(desc: AttnDesc, n_req, total_q_rows) -> int:

@@ -113,6 +113,72 @@ __global__ __launch_bounds__(kThreads) void gather_pages_kernel(
   }
 }
 
+// The same copy for a call that runs beside a kernel which holds most of the chip's registers (prefill attention: 240 of a
+// SIMD's 512 for each of two wavefronts): one workgroup per compute unit with one wavefront per SIMD in the 32 registers that
+// are left, so it needs no compute unit of its own and takes what the other kernel leaves of the memory's time.  Addresses are
+// buffer descriptors and scalar offsets for the registers' sake; what lies behind a page's end is neither read nor written.
+constexpr int kBesideGrid = 256, kBesideUnroll = 3;
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(32))) void gather_beside_kernel(
+    int n_req, const char* __restrict__ kpool, const char* __restrict__ vpool, int n_pages,
+    const int32_t* __restrict__ matched_len, const int32_t* __restrict__ page_table, int max_blocks,
+    int64_t* __restrict__ ctx_off, char* __restrict__ kctx, char* __restrict__ vctx, int64_t cap_pages, int page_bytes) {
+  __shared__ int64_t first[kPref + 1];   // pages before a request
+  // (a scan through LDS: the one through lanes holds too many registers)
+  for (int r = threadIdx.x; r <= n_req; r += kThreads) first[r] = r ? max(matched_len[r - 1], 0) / SKV_BLOCK_TOKENS : 0;
+  __syncthreads();
+  for (int o = 1; o <= n_req; o <<= 1) {
+    int64_t below[(kPref + kThreads) / kThreads];
+#pragma unroll
+    for (int k = 0; k < (kPref + kThreads) / kThreads; ++k) {
+      const int r = threadIdx.x + k * kThreads;
+      below[k] = r >= o && r <= n_req ? first[r - o] : 0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < (kPref + kThreads) / kThreads; ++k) {
+      const int r = threadIdx.x + k * kThreads;
+      if (r <= n_req) first[r] += below[k];
+    }
+    __syncthreads();
+  }
+  if (blockIdx.x == 0)
+    for (int r = threadIdx.x; r <= n_req; r += kThreads) ctx_off[r] = first[r] * SKV_BLOCK_TOKENS;
+  auto uniform = [](int64_t x) __attribute__((always_inline)) {
+    return (int64_t)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x) |
+                     (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)((uint64_t)x >> 32)) << 32);
+  };
+  const int64_t end = uniform(min(first[n_req], cap_pages));
+  const unsigned at = threadIdx.x * 16;
+  int r = 0;   // request that owns output page p
+  for (int64_t p = blockIdx.x; p < end; p += kBesideGrid) {
+    while (uniform(first[r + 1]) <= p) ++r;
+    const int64_t j = p - uniform(first[r]);
+    if (j >= max_blocks) continue;
+    const int page = __builtin_amdgcn_readfirstlane(page_table[(size_t)r * max_blocks + j]);
+    if (page < 0 || page >= n_pages) continue;
+    const __amdgpu_buffer_rsrc_t ks = __builtin_amdgcn_make_buffer_rsrc((void*)(kpool + (size_t)page * page_bytes), 0, page_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t vs = __builtin_amdgcn_make_buffer_rsrc((void*)(vpool + (size_t)page * page_bytes), 0, page_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t kd = __builtin_amdgcn_make_buffer_rsrc((void*)(kctx + (size_t)p * page_bytes), 0, page_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t vd = __builtin_amdgcn_make_buffer_rsrc((void*)(vctx + (size_t)p * page_bytes), 0, page_bytes, 0x00020000);
+    constexpr int kStep = kThreads * 16;
+    for (int base = 0; base < page_bytes; base += kBesideUnroll * kStep) {
+      u32x4 a[kBesideUnroll], b[kBesideUnroll];
+#pragma unroll
+      for (int u = 0; u < kBesideUnroll; ++u) {   // (2: non-temporal; a step begins inside the page, so the range check holds)
+        if (base + u * kStep >= page_bytes) break;
+        a[u] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(ks, at, base + u * kStep, 2));
+        b[u] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(vs, at, base + u * kStep, 2));
+      }
+#pragma unroll
+      for (int u = 0; u < kBesideUnroll; ++u) {
+        if (base + u * kStep >= page_bytes) break;
+        __builtin_amdgcn_raw_buffer_store_b128(a[u], kd, at, base + u * kStep, 2);
+        __builtin_amdgcn_raw_buffer_store_b128(b[u], vd, at, base + u * kStep, 2);
+      }
+    }
+  }
+}
+
 // Inverse of the gather: one workgroup per (request, new block) slot of the table, persistent grid.
 __global__ __launch_bounds__(kThreads) void scatter_pages_kernel(
     int n_req, const u32x4* __restrict__ knew, const u32x4* __restrict__ vnew, const int32_t* __restrict__ q_off,
@@ -205,10 +271,9 @@ extern "C" int skv_scatter_kv(const skv_attn_desc* desc, int32_t n_req, const vo
   return SKV_OK;
 }
 
-extern "C" int skv_gather_kv(const skv_attn_desc* desc, int32_t n_req, const void* d_kpool,
-                             const void* d_vpool, int32_t n_pages, const int32_t* d_matched_len,
-                             const int32_t* d_page_table, int32_t max_blocks, int64_t* d_ctx_off,
-                             void* d_kctx, void* d_vctx, int64_t ctx_capacity_tokens, void* stream) {
+static int gather_enqueue(const skv_attn_desc* desc, int32_t n_req, const void* d_kpool, const void* d_vpool, int32_t n_pages,
+                          const int32_t* d_matched_len, const int32_t* d_page_table, int32_t max_blocks, int64_t* d_ctx_off,
+                          void* d_kctx, void* d_vctx, int64_t ctx_capacity_tokens, bool beside, void* stream) {
   if (!desc || n_req < 0 || n_pages < 0 || max_blocks < 0 || ctx_capacity_tokens < 0) return SKV_EINVAL;
   if (desc->dtype != SKV_F32 && desc->dtype != SKV_BF16) return SKV_EINVAL;
   if (desc->n_kv_heads < 1 || desc->head_dim < 1) return SKV_EINVAL;
@@ -222,6 +287,13 @@ extern "C" int skv_gather_kv(const skv_attn_desc* desc, int32_t n_req, const voi
   hipStream_t st = (hipStream_t)stream;
   const int64_t upper = (int64_t)n_req * max_blocks;  // pages the batch can reference at most
   const int grid = (int)(upper < 1 ? 1 : (upper < 256 * 16 ? upper : 256 * 16));
+  if (beside && n_req <= kPref && page_bytes <= 0x7fffffff) {
+    gather_beside_kernel<<<kBesideGrid, kThreads, 0, st>>>(
+        n_req, (const char*)d_kpool, (const char*)d_vpool, n_pages, d_matched_len, d_page_table, max_blocks, d_ctx_off,
+        (char*)d_kctx, (char*)d_vctx, upper ? ctx_capacity_tokens / SKV_BLOCK_TOKENS : 0, (int)page_bytes);
+    SKV_HIP(hipGetLastError());
+    return SKV_OK;
+  }
   auto gather = n_req <= kPref ? gather_pages_kernel<true> : gather_pages_kernel<false>;
   if (n_req > kPref) {
     ctx_offsets_kernel<<<1, kOffThreads, 0, st>>>(n_req, d_matched_len, d_ctx_off);
@@ -233,4 +305,19 @@ extern "C" int skv_gather_kv(const skv_attn_desc* desc, int32_t n_req, const voi
       (u32x4*)d_kctx, (u32x4*)d_vctx, upper ? ctx_capacity_tokens / SKV_BLOCK_TOKENS : 0, (int)(page_bytes / 16));
   SKV_HIP(hipGetLastError());
   return SKV_OK;
+}
+
+extern "C" int skv_gather_kv(const skv_attn_desc* desc, int32_t n_req, const void* d_kpool, const void* d_vpool,
+                             int32_t n_pages, const int32_t* d_matched_len, const int32_t* d_page_table, int32_t max_blocks,
+                             int64_t* d_ctx_off, void* d_kctx, void* d_vctx, int64_t ctx_capacity_tokens, void* stream) {
+  return gather_enqueue(desc, n_req, d_kpool, d_vpool, n_pages, d_matched_len, d_page_table, max_blocks, d_ctx_off, d_kctx, d_vctx,
+                        ctx_capacity_tokens, false, stream);
+}
+
+extern "C" int skv_gather_kv_beside(const skv_attn_desc* desc, int32_t n_req, const void* d_kpool, const void* d_vpool,
+                                    int32_t n_pages, const int32_t* d_matched_len, const int32_t* d_page_table,
+                                    int32_t max_blocks, int64_t* d_ctx_off, void* d_kctx, void* d_vctx,
+                                    int64_t ctx_capacity_tokens, void* stream) {
+  return gather_enqueue(desc, n_req, d_kpool, d_vpool, n_pages, d_matched_len, d_page_table, max_blocks, d_ctx_off, d_kctx, d_vctx,
+                        ctx_capacity_tokens, true, stream);
 }
