@@ -26,6 +26,10 @@ EXPORTS = ["skv_strerror", "skv_last_hip_error", "skv_tree_build_size", "skv_tre
            "skv_prefill_attn_workspace_size", "skv_prefill_attn", "skv_prefill_attn_static"]
 
 
+_current_raw_stream = torch._C._cuda_getCurrentRawStream
+_current_device = torch._C._cuda_getDevice
+
+
 class SkvError(RuntimeError):
     def __init__(self, code, where):
         self.code = code
@@ -107,12 +111,13 @@ def _dptr(t):
     if t is None:
         return None
     assert isinstance(t, torch.Tensor) and t.is_cuda and t.is_contiguous(), "device tensor expected"
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream(stream):
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return C.c_void_p(s.cuda_stream)
+    """The current one by its handle: a stream object is 1.5 us of a call.  (A tensor or tree on the device is at hand, so
+    torch has initialised it.)"""
+    return _current_raw_stream(_current_device()) if stream is None else stream.cuda_stream
 
 
 def attn_desc(n_q_heads, n_kv_heads, head_dim, dtype, scale=None) -> AttnDesc:
