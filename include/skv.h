@@ -331,8 +331,8 @@ int skv_mfma_rate(const void* d_operands, size_t operand_bytes, int32_t iters, i
                   size_t sink_bytes, double* flops, void* stream);
 
 /* Bytes of device workspace skv_prefill_attn needs for n_req requests and at most
- * total_q_rows uncached tokens in the batch (bf16: the work list, one page of zeros that stands in for key groups without
- * data, and 69 MB for the partial states of work items that small batches split along the keys); the call overwrites it.
+ * total_q_rows uncached tokens in the batch (bf16: the work list, one page of 16 rows, and
+ * 69 MB for the partial states of work items that small batches split along the keys); the call overwrites it.
  * The size never falls as n_req or total_q_rows grow: the workspace of the largest batch serves every smaller one. */
 int skv_prefill_attn_workspace_size(const skv_attn_desc* desc, int32_t n_req, int64_t total_q_rows,
                                     size_t* bytes);
@@ -363,7 +363,7 @@ int skv_prefill_attn(const skv_attn_desc* desc, int32_t n_req, const void* d_q, 
 /* skv_prefill_attn for callers that cannot allocate device memory or hand over a workspace: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, results and errors as
  * skv_prefill_attn without the workspace (nothing is split along the keys: small batches differ from it in rounding):
- * the work list and the page of zeros live in a device array built
+ * the work list lives in a device array built
  * into the library (SKV_STATIC_SCRATCH_BYTES per GPU, held until the process ends), whose address on the
  * current device is looked up on the first call there.  The call allocates and frees nothing.
  * SKV_ERANGE when the work list for (n_req, total_q_rows) exceeds SKV_STATIC_SCRATCH_BYTES

@@ -65,12 +65,17 @@ struct AttnParams {
   const int32_t* page_table;
   const int32_t* items;      // kItemInts ints per work item
   const int32_t* n_items;
-  const char* zero_page;     // 16 rows of zeros: stands in for a group of keys that has no data
   const int32_t* splits;     // kSplitInts ints per work item whose keys are split over several workgroups
   float* partials;           // kSlotFloats floats per part and (kv head, head group); null: nothing is ever split
   int max_blocks, n_pages, Hq, Hkv;
   int heads_per_wg;          // query heads of one kv head handled by one workgroup (1, 2, 4 or 8)
   float scale;
+  // what the work list is made of, for workgroups that find their item themselves
+  const int32_t *q_off, *matched_len;
+  int32_t* splits_out;       // = splits and n_items, written by them for the merge
+  int32_t* n_items_out;
+  int n_req, pos_log, max_items, order_above;
+  float rows_filled;
 };
 
 // ---- work list ---------------------------------------------------------------------------------
@@ -189,13 +194,11 @@ __global__ __launch_bounds__(kSchedThreads) void attn_schedule_kernel(
     int n_req, const int32_t* __restrict__ q_off, const int32_t* __restrict__ matched_len, int pos_log, int max_items,
     int units /* workgroups per item */, int order_above /* requests are ordered by length if one is longer */,
     float rows_filled /* query rows, over the heads of a workgroup */,
-    int32_t* __restrict__ n_items /* [0] items, [1] split items */, int32_t* __restrict__ items, int32_t* __restrict__ splits /* null: never split */, uint4* __restrict__ zero_page,
-    int zero_vec) {
+    int32_t* __restrict__ n_items /* [0] items, [1] split items */, int32_t* __restrict__ items, int32_t* __restrict__ splits /* null: never split */) {
   __shared__ int scan[kSchedThreads], red[kSchedWaves], bucket[kBuckets];
   __shared__ int4 req_at[kSchedThreads];   // request, first row, rows, reused length
   __shared__ int4 item_a[kCus], item_b[kCus];   // the first records, for the split
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  for (int i = tid; i < zero_vec; i += kSchedThreads) zero_page[i] = make_uint4(0u, 0u, 0u, 0u);
   int listed = 0;
   for (int base = 0; base < n_req; base += kSchedThreads) {
     const int r = base + tid, n_here = min(kSchedThreads, n_req - base);
@@ -360,6 +363,137 @@ __global__ __launch_bounds__(kSchedThreads) void attn_schedule_kernel(
   }
 }
 
+// ---- the same list without a kernel in front of the attention -------------------------------------
+// Of up to 64 requests every wavefront works its item out for itself, a request per lane and nothing through LDS: the same cuts,
+// order (exactly by length here), forecasts and part lengths as above.  A list costs a launch and a chain of barriers, 5 to 9 us
+// of every call; this 0.5 to 1.5 us of a workgroup's start, 2 to 4 where a split is searched for (for one round of workgroups:
+// a second one has never paid where the first has room for every item).
+constexpr int kPlanRequests = 64, kPlanItems = 64;   // kPlanItems: a lane each, where they may be split
+struct Work {
+  int r, row0, row1, qbase, S, L, kt0, part;   // kt0: first key tile of the part, part: as in a record
+};
+// unit: kv head and head group of the caller; one of them writes what the merge reads.  False: no such item.
+template <bool kParts>
+__device__ __forceinline__ bool plan_item(const AttnParams& p, int item, int unit, int units, Work& w) {
+  const int lane = threadIdx.x & 63;
+  const bool writes = kParts && unit == 0 && threadIdx.x == 0;
+  auto at_lane = [](int x, int from) __attribute__((always_inline)) { return __builtin_amdgcn_readlane(x, from); };
+  auto scan = [&](int x) __attribute__((always_inline)) {   // inclusive
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int y = __shfl_up(x, o);
+      if (lane >= o) x += y;
+    }
+    return x;
+  };
+  int r = lane, qb = 0, qe = 0, L = 0;
+  if (lane < p.n_req) {
+    qb = p.q_off[lane];
+    qe = p.q_off[lane + 1];
+    L = p.matched_len[lane];
+  }
+  Cut c = cut_of(qb, qe, L, p.pos_log);
+  if (p.order_above < INT_MAX) {
+    const int keys = c.nt > 0 ? c.L + c.S : 0;
+    if (wave_max(keys) > p.order_above) {
+      int place = lane < p.n_req ? 0 : lane;
+      for (int j = 0; j < p.n_req; ++j) {
+        const int k = at_lane(keys, j);
+        if (lane < p.n_req) place += k > keys || (k == keys && j < lane);
+      }
+      auto move = [&](int x) __attribute__((always_inline)) { return __builtin_amdgcn_ds_permute(place * 4, x); };
+      r = move(r);
+      c = cut_of(move(qb), move(qe), move(L), p.pos_log);
+    }
+  }
+  const int upto = scan(c.nt), total = at_lane(upto, 63);
+  auto tile_of = [&](int own, const Cut& cut, int up) __attribute__((always_inline)) {   // the request's last tile first
+    int row0, row1;
+    cut.tile(up - 1 - own, p.pos_log, row0, row1);
+    return int2{row0, row1};
+  };
+  w.kt0 = w.part = 0;
+  if (!kParts || total > kPlanItems || total * units > kCus || total == 0) {   // whole items
+    if (writes && item == 0) p.n_items_out[1] = 0;
+    if (item >= total) return false;
+    const int at = __builtin_popcountll(__ballot(upto <= item));
+    const Cut mine = {at_lane(c.S, at), at_lane(c.L, at), at_lane(c.qb, at), at_lane(c.head_rows, at), at_lane(c.nt, at)};
+    const int2 rows = tile_of(item, mine, at_lane(upto, at));
+    w.r = at_lane(r, at);
+    w.row0 = rows.x;
+    w.row1 = rows.y;
+    w.qbase = mine.qb;
+    w.S = mine.S;
+    w.L = mine.L;
+    return true;
+  }
+  // lane i: item i
+  const int n = total;
+  int at = 0;
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1)
+    if (__shfl(upto, at + o - 1) <= lane) at += o;
+  at = min(at, 63);
+  const Cut mine = {__shfl(c.S, at), __shfl(c.L, at), __shfl(c.qb, at), __shfl(c.head_rows, at), __shfl(c.nt, at)};
+  const int2 rows = tile_of(min(lane, n - 1), mine, __shfl(upto, at));
+  r = __shfl(r, at);
+  const bool have = lane < n;
+  const int n_kt = have ? (mine.L + rows.y + kBN - 1) / kBN : 0, last = have ? (mine.L + rows.x) / kBN : 0;
+  const float time = (float)n_kt * tile_time(rows.y - rows.x, p.pos_log);
+  const int longest = wave_max(n_kt), sum = wave_sum(n_kt);
+  const float longest_time = wave_max(have ? time : 0.f), share = wave_sum(have ? time : 0.f) * units / kCus;
+  int parts = have ? 1 : 0;
+  if (split_time(share, p.rows_filled / (n << kLogFull)) < whole_time(n * units, longest_time, share)) {
+    // smallest part length for which all parts run in one round: sixteen lengths at a time between the last that did not fit and
+    // the first that did, the items of a length dealt to four lanes
+    const int room = kCus / units;
+    int lo = max(1, min(longest, (sum + room - 1) / room)), hi = longest;
+    while (lo < hi) {
+      const int d = hi - lo, len = lo + (int)(((long long)d * (lane >> 2)) >> 4);   // the first tries lo itself
+      int total_parts = 0;
+      for (int i0 = 0; i0 < n; i0 += 4) {
+        const int i = i0 + (lane & 3), kt = __shfl(n_kt, i & 63), la = __shfl(last, i & 63);
+        if (i < n) total_parts += parts_of(kt, la, len);
+      }
+      total_parts += __shfl_xor(total_parts, 1);
+      total_parts += __shfl_xor(total_parts, 2);
+      const uint64_t fits = __ballot(total_parts <= room);
+      const int k = fits ? __builtin_ctzll(fits) >> 2 : 16, l0 = lo;
+      if (k < 16) hi = l0 + (int)(((long long)d * k) >> 4);
+      if (k > 0) lo = l0 + (int)(((long long)d * (k - 1)) >> 4) + 1;
+    }
+    if (have) parts = parts_of(n_kt, last, hi);
+  }
+  const int part_upto = scan(parts), n_parts = at_lane(part_upto, 63);
+  const bool split = n_parts > n && n_parts <= p.max_items;
+  if (!split) parts = have ? 1 : 0;
+  const uint64_t cut_items = __ballot(parts > 1);
+  if (writes && item == 0) p.n_items_out[1] = __builtin_popcountll(cut_items);
+  if (item >= (split ? n_parts : n)) return false;
+  const int own = split ? __builtin_popcountll(__ballot(part_upto <= item)) : item;
+  w.r = at_lane(r, own);
+  w.row0 = at_lane(rows.x, own);
+  w.row1 = at_lane(rows.y, own);
+  w.qbase = at_lane(mine.qb, own);
+  w.S = at_lane(mine.S, own);
+  w.L = at_lane(mine.L, own);
+  if (split) {
+    const int slot_upto = scan(parts > 1 ? parts : 0);
+    const int of = at_lane(parts, own), j = item - (at_lane(part_upto, own) - of), kt = at_lane(n_kt, own);
+    const int len = (int)((unsigned)(kt + of - 1) / (unsigned)of), slot = at_lane(slot_upto, own) - of;
+    w.kt0 = j * len;
+    if (of > 1) {
+      w.part = (slot + j + 1) << kPartBits | min(len, kt - j * len);
+      if (writes && j == 0) {
+        int4* sp = (int4*)(p.splits_out + kSplitInts * __builtin_popcountll(cut_items & ((1ull << own) - 1)));
+        sp[0] = make_int4(w.row0, w.row1, w.qbase, slot);
+        sp[1] = make_int4(of, 0, 0, 0);
+      }
+    }
+  }
+  return true;
+}
+
 // ---- bf16 MFMA kernel --------------------------------------------------------------------------
 // max / sum of a value and the one 32 lanes away (the other half of the wavefront): v_permlane32_swap exchanges the upper
 // half of its first operand with the lower half of its second, after which `a` holds the lower half's value in both halves
@@ -437,7 +571,8 @@ __device__ __forceinline__ void unit_of_block(int b, int Hkv, int n_hg, int& ite
 }
 
 // kParts: the list may hold parts of items.  Without, 0.3 us less of a workgroup's start goes into what a part needs.
-template <bool kParts>
+// kPlan: no list, the workgroup finds its item itself.
+template <bool kParts, bool kPlan>
 __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
   __shared__ __attribute__((aligned(16))) __bf16 smem[kKStages * kTile + kVStages * kTile +
                                                       kWaves * kStageRows * kD];
@@ -459,19 +594,25 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
   const int n_hg = G / p.heads_per_wg;               // head groups per kv head
   int item, kvh, hg;
   unit_of_block(blockIdx.x, p.Hkv, n_hg, item, kvh, hg);
-  // the record is read together with the item count (the grid bound keeps the index inside the list)
-  const int4 rec0 = ((const int4*)(p.items + (size_t)kItemInts * item))[0];
-  const int4 rec1 = ((const int4*)(p.items + (size_t)kItemInts * item))[1];
-  if (item >= *p.n_items) return;
-  const int kt0 = kParts ? __builtin_amdgcn_readfirstlane(rec1.z) : 0;    // first key tile of this part
-  const int part = kParts ? __builtin_amdgcn_readfirstlane(rec1.w) : 0;   // 0: the whole item
+  Work w;
+  if constexpr (kPlan) {
+    if (!plan_item<kParts>(p, item, kvh * n_hg + hg, p.Hkv * n_hg, w)) return;
+  } else {
+    // the record is read together with the item count (the grid bound keeps the index inside the list)
+    const int4 rec0 = ((const int4*)(p.items + (size_t)kItemInts * item))[0];
+    const int4 rec1 = ((const int4*)(p.items + (size_t)kItemInts * item))[1];
+    if (item >= *p.n_items) return;
+    w = {rec0.x, rec0.y, rec1.y, rec0.z, rec0.w, rec1.x, rec1.z, rec1.w};
+  }
+  const int kt0 = kParts ? __builtin_amdgcn_readfirstlane(w.kt0) : 0;    // first key tile of this part
+  const int part = kParts ? __builtin_amdgcn_readfirstlane(w.part) : 0;  // 0: the whole item
   // Everything below counts keys from the part's first one: the reused length and with it every position shifts.
-  const int L = __builtin_amdgcn_readfirstlane(rec1.x) - kt0 * kBN;                         // may be negative
-  const int row1 = __builtin_amdgcn_readfirstlane(rec1.y);                                  // end row of the q tile
-  const int r = __builtin_amdgcn_readfirstlane(rec0.x);
-  const int row0 = __builtin_amdgcn_readfirstlane(rec0.y);                                  // first row of the q tile
-  const int qbase = __builtin_amdgcn_readfirstlane(rec0.z);
-  const int S = __builtin_amdgcn_readfirstlane(rec0.w);
+  const int L = __builtin_amdgcn_readfirstlane(w.L) - kt0 * kBN;                            // may be negative
+  const int row1 = __builtin_amdgcn_readfirstlane(w.row1);                                  // end row of the q tile
+  const int r = __builtin_amdgcn_readfirstlane(w.r);
+  const int row0 = __builtin_amdgcn_readfirstlane(w.row0);                                  // first row of the q tile
+  const int qbase = __builtin_amdgcn_readfirstlane(w.qbase);
+  const int S = __builtin_amdgcn_readfirstlane(w.S);
   const int Ltot = L + S;
 
   const Packing pk_of = packing(p.heads_per_wg);
@@ -495,14 +636,14 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
     if (gi * SKV_BLOCK_TOKENS < L && gi < table_len) page = __builtin_nontemporal_load(&table[gi]);
     return page;
   };
-  // (the five base addresses as values: selecting between the fields of the argument block itself makes the
+  // (the four base addresses as values: selecting between the fields of the argument block itself makes the
   // compiler select their addresses and load through them, a vector-memory read that everything behind it waits for)
   const uint64_t kpool_a = (uint64_t)p.kpool, vpool_a = (uint64_t)p.vpool, knew_a = (uint64_t)p.knew,
-                 vnew_a = (uint64_t)p.vnew, zero_a = (uint64_t)p.zero_page;
+                 vnew_a = (uint64_t)p.vnew;
   auto window_bases = [&](int w, int page, uint64_t& ak, uint64_t& av) __attribute__((always_inline)) {
     const int gi = w * 64 + lane;
     const int key0 = gi * SKV_BLOCK_TOKENS;
-    uint64_t k = zero_a, v = zero_a;
+    uint64_t k = 0, v = 0;
     if (key0 < L) {
       if (page >= 0 && page < p.n_pages) {
         const uint64_t off = ((uint64_t)page * SKV_BLOCK_TOKENS * p.Hkv + kvh) * (kD * 2);
@@ -563,13 +704,14 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
   // A tile is four 16-key groups; a group is one page of the pool or 16 consecutive new rows.  Each wavefront
   // moves two segments of a tile, half a group (2w and 2w + 1: keys 8w ..), with direct-to-LDS loads: lane i
   // fetches chunk 4 (i / 16) + i % 4 of key (i / 4) % 4 of the segment and the hardware puts it at slot i.  Both take the
-  // group's base as the buffer's and differ in the scalar offset: no vector address is formed.
+  // group's base as the buffer's and constant offsets: no vector address is formed.
   const unsigned row_bytes = (unsigned)p.Hkv * kD * 2u;
   const int t_row = (wave & 1) * 8 + ((lane >> 2) & 3);      // row of the 16-key group this lane fetches, and 4 further on
   const unsigned t_col = (unsigned)((lane >> 4) * 4 + (lane & 3)) * 16u;
   const unsigned t_off = (unsigned)t_row * row_bytes + t_col;
   // Group base addresses, one 16-key group per lane for 64 groups (16 tiles, a "window"): a pool page, 16 new rows,
-  // or the page of zeros when the group has no data (past the end of the sequence, or a page id outside the pool).
+  // or 0 when the group has no data (past the end of the sequence, or a page id outside the pool): an empty buffer, whose rows
+  // arrive as zeros.
   // A tile's bases are read with lane broadcasts.  Two consecutive windows are held; K tiles run one tile ahead of
   // V tiles, so for one iteration in sixteen K reads the later window while V still reads the earlier one.
   auto lane_bcast = [&](uint64_t x, int idx) __attribute__((always_inline)) {
@@ -583,22 +725,16 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
   window_bases(1, page_w1, ak_nxt, av_nxt);
   typedef __attribute__((address_space(3))) void lds_void;
   const int group = wave >> 1;                               // 16-key group of this wave's segments
-  const unsigned quarter = 4u * row_bytes;
-  // one pool (K or V) of tile t into an LDS stage; `base`: of the wave's group
+  const unsigned t_off4 = t_off + 4u * row_bytes;            // (a scalar offset would have to lie inside the buffer)
+  // one pool (K or V) of tile t into an LDS stage; `base`: of the wave's group.  Where the sequence ends inside the tile so does
+  // the buffer: what lies behind arrives as zeros, and the causal mask keeps it out.
   auto issue_half_tile = [&]<bool kWhole>(uint64_t base, int t, __bf16* dst_stage) __attribute__((always_inline)) {
     __bf16* const dst = dst_stage + 2 * wave * kSeg;
-    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (int)(4 * quarter), 0x00020000);
-    if (!kWhole && t * kBN + kBN > Ltot) {   // the sequence ends inside this tile: rows past its end re-read its last row,
-      const int n_valid = Ltot - (t * kBN + group * 16);   // finite values that the causal mask keeps out
-      const int last = n_valid > 0 ? min(n_valid, 16) - 1 : 15;
-#pragma unroll
-      for (int cc = 0; cc < 2; ++cc)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void*)(dst + cc * kSeg), 16,
-                                                 (unsigned)min(t_row + 4 * cc, last) * row_bytes + t_col, 0, 0, 0);
-    } else {
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void*)dst, 16, t_off, 0, 0, 0);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void*)(dst + kSeg), 16, t_off, quarter, 0, 0);
-    }
+    const int rows = kWhole ? 16 : max(0, min(16, Ltot - (t * kBN + group * 16)));
+    const __amdgpu_buffer_rsrc_t rsrc =
+        __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, base ? rows * (int)row_bytes : 0, 0x00020000);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void*)dst, 16, t_off, 0, 0, 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void*)(dst + kSeg), 16, t_off4, 0, 0, 0);
   };
   auto load_k_tile = [&](int t, int stage_idx) __attribute__((always_inline)) {
     issue_half_tile.template operator()<false>(lane_bcast((t >> 4) == win ? ak_cur : ak_nxt, ((t & 15) << 2) + group), t, Ks + stage_idx * kTile);
@@ -1117,19 +1253,27 @@ int order_above(const Layout& y, int32_t n_req, int64_t total_q_rows) {
   const float tiles = std::max(1.f, (float)mean_rows(n_req, total_q_rows) / (1 << y.pos_log) + 0.5f), wgs = tiles * n_req * y.units;
   return wgs <= kCus ? INT_MAX : wgs <= 4 * kCus ? 0 : 1024;
 }
+// Whether workgroups find their items themselves (plan_item): a request per lane and, where items may be split, an item per
+// lane, in one round of workgroups.  Behind the first round every workgroup, surplus ones too, would pay for it where a list is
+// read in 1 us: 16 requests of 510 rows, 4.5 rounds, 497 us either way.
+bool plan_in_place(const Layout& y, int32_t n_req) {
+  const int64_t items = y.max_items - y.max_parts;
+  return n_req <= kPlanRequests && items * y.units <= kCus && (!y.max_parts || items <= kPlanItems);
+}
 size_t split_bytes(const Layout& y) {
   return y.max_parts ? kCus * kSplitInts * sizeof(int32_t) + (size_t)y.max_parts * y.units * kSlotFloats * sizeof(float) : 0;
 }
 
-size_t zero_page_bytes(const skv_attn_desc* d) {
-  return d->dtype == SKV_BF16 ? skv_align256((size_t)SKV_BLOCK_TOKENS * d->n_kv_heads * kD * 2) : 0;
+size_t list_offset(const skv_attn_desc* d) {
+  return 256 + (d->dtype == SKV_BF16 ? skv_align256((size_t)SKV_BLOCK_TOKENS * d->n_kv_heads * kD * 2) : 0);
 }
 
 }  // namespace
 
-// Work list and page of zeros: what a call needs at the least.  No part of the size falls as n_req or total_q_rows grow.
-static size_t list_bytes(const skv_attn_desc* desc, const Layout& y) {
-  return 256 + zero_page_bytes(desc) + skv_align256((size_t)y.max_items * kItemInts * sizeof(int32_t));
+// What a call needs at the least: the work list, behind a page that no kernel uses any longer and that the interface's sizes (what
+// is accepted, what is refused) go on to count.  The size does not fall as n_req or total_q_rows grow.
+static size_t list_bytes(const skv_attn_desc* d, const Layout& y) {
+  return list_offset(d) + skv_align256((size_t)y.max_items * kItemInts * sizeof(int32_t));
 }
 
 extern "C" int skv_prefill_attn_workspace_size(const skv_attn_desc* desc, int32_t n_req,
@@ -1170,8 +1314,7 @@ static int prefill_attn_enqueue(const skv_attn_desc* desc, int32_t n_req, const 
   p.q = d_q; p.knew = d_knew; p.vnew = d_vnew; p.kpool = d_kpool; p.vpool = d_vpool; p.out = d_out;
   p.page_table = d_page_table;
   p.n_items = (const int32_t*)d_workspace;
-  p.zero_page = (const char*)d_workspace + 256;
-  p.items = (const int32_t*)((char*)d_workspace + 256 + zero_page_bytes(desc));
+  p.items = (const int32_t*)((char*)d_workspace + list_offset(desc));
   p.max_blocks = max_blocks; p.n_pages = n_pages;
   p.Hq = desc->n_q_heads; p.Hkv = desc->n_kv_heads;
   p.heads_per_wg = y.heads_per_wg;
@@ -1185,20 +1328,29 @@ static int prefill_attn_enqueue(const skv_attn_desc* desc, int32_t n_req, const 
   }
 
   // the list holds whole items or, where anything is split, no more than max_parts records
-  const int64_t grid = std::max(y.max_items - y.max_parts, y.max_parts) * y.units;
+  const bool plan = plan_in_place(y, n_req);
+  const int64_t grid = (plan && y.max_parts ? kCus / y.units : std::max(y.max_items - y.max_parts, y.max_parts)) * y.units;
   if (y.max_items * y.units > 0x7fffffff || y.max_items > 0x3fffffff) return SKV_ERANGE;
   char* const split_area = (char*)d_workspace + list_bytes(desc, y);
   p.splits = y.max_parts ? (const int32_t*)split_area : nullptr;
   p.partials = y.max_parts ? (float*)(split_area + kCus * kSplitInts * sizeof(int32_t)) : nullptr;
-  attn_schedule_kernel<<<1, kSchedThreads, 0, st>>>(n_req, d_q_off, d_matched_len, y.pos_log, (int)y.max_items, y.units,
-                                                    order_above(y, n_req, total_q_rows), (float)total_q_rows * y.heads_per_wg,
-                                                    (int32_t*)d_workspace, (int32_t*)p.items, (int32_t*)p.splits,
-                                                    (uint4*)p.zero_page, (int)(zero_page_bytes(desc) / 16));
-  SKV_HIP(hipGetLastError());
-  if (y.max_parts)
-    attn_bf16_kernel<true><<<(int)grid, kThreads, 0, st>>>(p);
-  else
-    attn_bf16_kernel<false><<<(int)grid, kThreads, 0, st>>>(p);
+  p.q_off = d_q_off;
+  p.matched_len = d_matched_len;
+  p.n_items_out = (int32_t*)d_workspace;
+  p.splits_out = (int32_t*)p.splits;
+  p.n_req = n_req;
+  p.pos_log = y.pos_log;
+  p.max_items = (int)y.max_items;
+  p.order_above = order_above(y, n_req, total_q_rows);
+  p.rows_filled = (float)total_q_rows * y.heads_per_wg;
+  if (!plan) {
+    attn_schedule_kernel<<<1, kSchedThreads, 0, st>>>(n_req, d_q_off, d_matched_len, y.pos_log, p.max_items, y.units, p.order_above,
+                                                      p.rows_filled, p.n_items_out, (int32_t*)p.items, p.splits_out);
+    SKV_HIP(hipGetLastError());
+  }
+  const auto kernel = y.max_parts ? (plan ? attn_bf16_kernel<true, true> : attn_bf16_kernel<true, false>)
+                                  : (plan ? attn_bf16_kernel<false, true> : attn_bf16_kernel<false, false>);
+  kernel<<<(int)grid, kThreads, 0, st>>>(p);
   SKV_HIP(hipGetLastError());
   if (y.max_parts) {   // a split item has two parts at least
     attn_merge_kernel<<<(int)std::min<int64_t>(y.max_parts / 2 * y.units * kWaves, kMergeGrid), kMergeThreads, 0, st>>>(p);
@@ -1232,7 +1384,7 @@ extern "C" int skv_prefill_attn(const skv_attn_desc* desc, int32_t n_req, const 
 }
 
 // ---- the same call for callers that cannot allocate ---------------------------------------------
-// The work list and the page of zeros live in a file-scope device array instead of a caller workspace.  Every GPU
+// The work list lives in a file-scope device array instead of a caller workspace.  Every GPU
 // the library runs on holds its own copy of the array at its own address, looked up once per device.
 static __device__ __align__(256) unsigned char scratch[SKV_STATIC_SCRATCH_BYTES];
 
@@ -1275,7 +1427,7 @@ extern "C" int skv_prefill_attn_static(const skv_attn_desc* desc, int32_t n_req,
   void* ws = nullptr;
   rc = scratch_of_current_device(&ws);
   if (rc) return rc;
-  // the schedule kernel rewrites the item count, the page of zeros and every record it hands out on each call,
+  // the schedule kernel rewrites the item count and every record it hands out on each call,
   // so nothing of the previous call's contents is read
   return prefill_attn_enqueue(desc, n_req, d_q, d_knew, d_vnew, d_q_off, total_q_rows, d_kpool, d_vpool, n_pages,
                               d_matched_len, d_page_table, max_blocks, d_out, ws, y, stream);
