@@ -1123,13 +1123,19 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
 constexpr int kMergeThreads = 512, kMergeParts = 8, kMergeGrid = 256;   // (most calls merge little or nothing)
 __global__ __launch_bounds__(kMergeThreads) void attn_merge_kernel(AttnParams p) {
   const int n_hg = p.Hq / p.Hkv / p.heads_per_wg, units = p.Hkv * n_hg;
+  int rest, kvh, hg;
+  unit_of_block(blockIdx.x, p.Hkv, n_hg, rest, kvh, hg);
+  // (the record travels with the count: there is room for kCus of them, whatever the count)
+  int4 a = ((const int4*)(p.splits + kSplitInts * min(rest / kWaves, kCus - 1)))[0];
+  int parts = p.splits[kSplitInts * min(rest / kWaves, kCus - 1) + 4];
   const int n_work = p.n_items[1] * units * kWaves;
   for (int b = blockIdx.x; b < n_work; b += gridDim.x) {
-    int rest, kvh, hg;
-    unit_of_block(b, p.Hkv, n_hg, rest, kvh, hg);
-    const int wave = rest % kWaves, unit = kvh * n_hg + hg, si = rest / kWaves;
-    const int4 a = ((const int4*)(p.splits + kSplitInts * si))[0];
-    const int parts = p.splits[kSplitInts * si + 4];
+    if (b != (int)blockIdx.x) {
+      unit_of_block(b, p.Hkv, n_hg, rest, kvh, hg);
+      a = ((const int4*)(p.splits + kSplitInts * (rest / kWaves)))[0];
+      parts = p.splits[kSplitInts * (rest / kWaves) + 4];
+    }
+    const int wave = rest % kWaves, unit = kvh * n_hg + hg;
     const int row0 = a.x, row1 = a.y, qbase = a.z, slot = a.w;
     const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
     const Packing pk = packing(p.heads_per_wg);
