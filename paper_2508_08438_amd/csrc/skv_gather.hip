@@ -118,6 +118,7 @@ __global__ __launch_bounds__(kThreads) void gather_pages_kernel(
 // SIMD's 512 for each of two wavefronts): one workgroup per compute unit with one wavefront per SIMD in the 32 registers that
 // are left, so it needs no compute unit of its own and takes what the other kernel leaves of the memory's time.  Addresses are
 // buffer descriptors and scalar offsets for the registers' sake; what lies behind a page's end is neither read nor written.
+// Alone it is the faster form of a large copy too (large_copy).
 constexpr int kBesideGrid = 256, kBesideUnroll = 3;
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(32))) void gather_beside_kernel(
     int n_req, const char* __restrict__ kpool, const char* __restrict__ vpool, int n_pages,
@@ -238,6 +239,10 @@ __global__ __launch_bounds__(kThreads) void stream_copy_kernel(const u32x4* __re
   }
 }
 
+// One workgroup per compute unit keeps enough in flight and goes through neighbouring pages together: us of the plain form / of that one,
+// 32 KB pages 1024 24.8 / 25.8, 2048 51.5 / 47.6, 4096 101 / 93, 16384 401 / 379 (5.67 TB/s); 64 KB 512 28.2 / 26.5; 16 KB 2048
+// 26.9 / 26.1, 16384 197 / 184; 8 KB 65536 409 / 379; but 4 KB, one load per thread and pool, 16384 52.6 / 68.0.
+bool large_copy(int64_t pages, int64_t page_bytes) { return page_bytes >= 8192 && pages * page_bytes >= (48 << 20); }
 // Workgroups per page: where a batch has no page for every compute unit a page of 32 KB is several workgroups' worth of loads in
 // flight.  us with 1 / 2 / 4 slices: 16 pages 4.95 / 4.1 / 3.8, 128 (of the fp32 pool's 32 KB) 6.4 / 5.6 / 5.3, 187 6.3 / 5.9 / 6.2,
 // 512 11.9 / 12.3 / 14.1.
@@ -293,7 +298,7 @@ static int gather_enqueue(const skv_attn_desc* desc, int32_t n_req, const void* 
   hipStream_t st = (hipStream_t)stream;
   const int64_t upper = (int64_t)n_req * max_blocks;  // pages the batch can reference at most
   const int grid = (int)(upper < 1 ? 1 : (upper < 256 * 16 ? upper : 256 * 16));
-  if (beside && n_req <= kPref && page_bytes <= 0x7fffffff) {
+  if ((beside || large_copy(upper, page_bytes)) && n_req <= kPref && page_bytes <= 0x7fffffff) {
     gather_beside_kernel<<<kBesideGrid, kThreads, 0, st>>>(
         n_req, (const char*)d_kpool, (const char*)d_vpool, n_pages, d_matched_len, d_page_table, max_blocks, d_ctx_off,
         (char*)d_kctx, (char*)d_vctx, upper ? ctx_capacity_tokens / SKV_BLOCK_TOKENS : 0, (int)page_bytes);

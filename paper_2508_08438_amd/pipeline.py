@@ -2,6 +2,8 @@
 of the path.  Only buffer management and calls into `binding`; no arithmetic of the method."""
 from __future__ import annotations
 
+import threading
+
 import numpy as np
 import torch
 
@@ -23,6 +25,20 @@ def _tiled_from_host(chunk: torch.Tensor, n_rows: int, device) -> torch.Tensor:
 # 15 us and attention slows by a third of the copy's time: us a pass, beside / one after the other: 98 MB behind one request
 # of 257 rows 271 / 279; 205 MB, 16 requests, 488 / 541; 3.3 GB, 32 requests, 6960 / 7690; 12 MB, one request, 102 / 52.
 GATHER_BESIDE_BYTES = 64 << 20
+
+# One stream per device for these copies, whatever the number of sessions: streams are dealt to four hardware queues, and a copy on
+# the queue of the attention's own stream runs behind it (24 requests behind 1700 keys, on nine streams one after the other: 260
+# to 264 us, on the sixth 296).  A capture takes a stream of the session's own, which no other thread can be using.
+_copy_streams = {}
+_copy_lock = threading.Lock()
+
+
+def _copy_stream(device):
+    with _copy_lock:
+        if device not in _copy_streams:
+            _copy_streams[device] = torch.cuda.Stream(device)
+            _copy_streams[device].record_event()      # its queue is there before the first pass
+        return _copy_streams[device]
 
 
 class Session:
@@ -61,7 +77,7 @@ class Session:
                 w.fill_pool("k", self.kpool)
                 w.fill_pool("v", self.vpool)
         self.q = None
-        self.side = None     # stream of a copy beside the attention
+        self.side = self.side_capture = None     # streams of a copy beside the attention
 
     # -- one-off: lay out Q / K_new / V_new for the suffixes this workload's match leaves uncached
     def prepare(self):
@@ -93,8 +109,7 @@ class Session:
         self.workspace = torch.empty(nbytes, dtype=torch.uint8, device=dev)
         copied = 2 * self.kctx.numel() * self.kctx.element_size()
         if self.do_gather and a.dtype == "bf16" and copied >= GATHER_BESIDE_BYTES:   # (fp32 attention leaves no registers)
-            self.side = torch.cuda.Stream(dev)
-            self.side.record_event()      # its queue is there before the first pass
+            self.side, self.side_capture = _copy_stream(self.q.device), torch.cuda.Stream(dev)
         skv.skv_counters_reset(self.tree)
 
     # -- the individual stages (each only enqueues on the current stream)
@@ -113,7 +128,7 @@ class Session:
                              self.matched_len, self.page_table, self.max_blocks, self.out, self.workspace)
 
     def gather_and_attention(self):
-        """Both read the match's results and neither the other's: a large copy runs on the session's second stream beside
+        """Both read the match's results and neither the other's: a large copy runs on a stream of its own beside
         the attention.  The current stream waits for it before this returns, also where attention() raises."""
         main = torch.cuda.current_stream() if self.side and self.do_gather else None
         if main is None or main.device != self.side.device:
@@ -121,13 +136,14 @@ class Session:
                 self.gather()
             self.attention()
             return
+        side = self.side_capture if torch.cuda.is_current_stream_capturing() else self.side
         matched = main.record_event()
         try:
             self.attention()      # first: it is what the copy has to fit beside
         finally:
-            self.side.wait_event(matched)
-            self.gather(stream=self.side, beside=True)
-            main.wait_stream(self.side)
+            side.wait_event(matched)
+            self.gather(stream=side, beside=True)
+            main.wait_stream(side)
 
     def step(self):
         if self.q is None:
