@@ -360,6 +360,17 @@ int skv_prefill_attn(const skv_attn_desc* desc, int32_t n_req, const void* d_q, 
                      const int32_t* d_matched_len, const int32_t* d_page_table, int32_t max_blocks,
                      void* d_out, void* d_workspace, size_t workspace_bytes, void* stream);
 
+/* Everything of a step behind its lookup in one call: skv_suffix_offsets (d_q_off is written), skv_gather_kv and
+ * skv_prefill_attn, with the results and errors of the three.  An error of the attention's arguments leaves the other two done,
+ * as when they are called in front of it.  Fewer launches than the three: small batches make the offsets in another kernel's first steps and
+ * copy their pages beside the merge of split items. */
+int skv_prefill_step(const skv_attn_desc* desc, int32_t n_req, const int32_t* d_req_off, const void* d_q,
+                     const void* d_knew, const void* d_vnew, int32_t* d_q_off, int64_t total_q_rows,
+                     const void* d_kpool, const void* d_vpool, int32_t n_pages, const int32_t* d_matched_len,
+                     const int32_t* d_page_table, int32_t max_blocks, void* d_out, int64_t* d_ctx_off, void* d_kctx,
+                     void* d_vctx, int64_t ctx_capacity_tokens, void* d_workspace, size_t workspace_bytes,
+                     void* stream);
+
 /* skv_prefill_attn for callers that cannot allocate device memory or hand over a workspace: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, results and errors as
  * skv_prefill_attn without the workspace (nothing is split along the keys: small batches differ from it in rounding):

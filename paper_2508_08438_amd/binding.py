@@ -23,7 +23,7 @@ EXPORTS = ["skv_strerror", "skv_last_hip_error", "skv_tree_build_size", "skv_tre
            "skv_counters_reset", "skv_window_roll", "skv_promote", "skv_block_state_read", "skv_suffix_offsets", "skv_gather_kv",
            "skv_gather_kv_beside",
            "skv_scatter_kv", "skv_stream_copy", "skv_decode_attn_workspace_size", "skv_decode_attn",
-           "skv_prefill_attn_workspace_size", "skv_prefill_attn", "skv_prefill_attn_static"]
+           "skv_prefill_attn_workspace_size", "skv_prefill_attn", "skv_prefill_step", "skv_prefill_attn_static"]
 
 
 _current_raw_stream = torch._C._cuda_getCurrentRawStream
@@ -92,6 +92,8 @@ def lib():
         l.skv_prefill_attn_workspace_size.argtypes = [C.POINTER(AttnDesc), i32, i64, C.POINTER(C.c_size_t)]
         l.skv_prefill_attn.argtypes = [C.POINTER(AttnDesc), i32, vp, vp, vp, vp, i64, vp, vp, i32, vp, vp,
                                        i32, vp, vp, C.c_size_t, vp]
+        l.skv_prefill_step.argtypes = [C.POINTER(AttnDesc), i32, vp, vp, vp, vp, vp, i64, vp, vp, i32, vp, vp, i32, vp, vp, vp, vp,
+                                       i64, vp, C.c_size_t, vp]
         l.skv_prefill_attn_static.argtypes = [C.POINTER(AttnDesc), i32, vp, vp, vp, vp, i64, vp, vp, i32, vp, vp,
                                               i32, vp, vp]
         l.skv_stream_copy.argtypes = [vp, vp, C.c_size_t, vp]
@@ -353,6 +355,20 @@ def skv_prefill_attn(desc: AttnDesc, q, knew, vnew, q_off, kpool, vpool, matched
                                   _dptr(page_table), max_blocks, _dptr(out), _dptr(workspace),
                                   workspace.numel() * workspace.element_size(), _stream(stream)),
            "skv_prefill_attn")
+
+
+def skv_prefill_step(desc: AttnDesc, req_off, q, knew, vnew, q_off, kpool, vpool, matched_len, page_table, max_blocks, out,
+                     ctx_off, kctx, vctx, workspace, stream=None):
+    """skv_suffix_offsets, skv_gather_kv and skv_prefill_attn in one call."""
+    n_req, total, row = matched_len.numel(), q.shape[0], desc.n_kv_heads * desc.head_dim
+    assert out.shape == q.shape and knew.shape[0] >= total and vnew.shape[0] >= total
+    assert ctx_off.dtype == torch.int64 and ctx_off.numel() == n_req + 1 and req_off.numel() == q_off.numel() == n_req + 1
+    cap = kctx.numel() // row
+    assert vctx.numel() // row >= cap
+    _check(lib().skv_prefill_step(C.byref(desc), n_req, _dptr(req_off), _dptr(q), _dptr(knew), _dptr(vnew), _dptr(q_off), total,
+                                  _dptr(kpool), _dptr(vpool), kpool.shape[0], _dptr(matched_len), _dptr(page_table), max_blocks,
+                                  _dptr(out), _dptr(ctx_off), _dptr(kctx), _dptr(vctx), cap, _dptr(workspace),
+                                  workspace.numel() * workspace.element_size(), _stream(stream)), "skv_prefill_step")
 
 
 def skv_prefill_attn_static(desc: AttnDesc, q, knew, vnew, q_off, kpool, vpool, matched_len, page_table, max_blocks,

@@ -24,7 +24,7 @@
 #include <atomic>
 #include <climits>
 
-#include "skv_internal.h"
+#include "skv_gather.h"
 
 namespace {
 
@@ -33,7 +33,6 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
@@ -72,6 +71,8 @@ struct AttnParams {
   float scale;
   // what the work list is made of, for workgroups that find their item themselves
   const int32_t *q_off, *matched_len;
+  const int32_t* req_off;    // not null: q_off is still to come, they make it from this and write it
+  int32_t* q_off_out;
   int32_t* splits_out;       // = splits and n_items, written by them for the merge
   int32_t* n_items_out;
   int n_req, pos_log, max_items, order_above;
@@ -387,7 +388,19 @@ __device__ __forceinline__ bool plan_item(const AttnParams& p, int item, int uni
     return x;
   };
   int r = lane, qb = 0, qe = 0, L = 0;
-  if (lane < p.n_req) {
+  if (p.req_off) {
+    if (lane < p.n_req) {
+      L = p.matched_len[lane];
+      qe = max(0, p.req_off[lane + 1] - p.req_off[lane] - L);
+    }
+    const int own = qe;
+    qe = scan(own);
+    qb = qe - own;
+    if (item == 0 && unit == 0 && threadIdx.x < 64) {
+      if (lane == 0) p.q_off_out[0] = 0;
+      if (lane < p.n_req) p.q_off_out[lane + 1] = qe;
+    }
+  } else if (lane < p.n_req) {
     qb = p.q_off[lane];
     qe = p.q_off[lane + 1];
     L = p.matched_len[lane];
@@ -1121,7 +1134,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
 // two trips to memory (references first and outputs after them, four parts at a time: 10.7 us for 10 parts of 3 items,
 // now 6.5).
 constexpr int kMergeThreads = 512, kMergeParts = 8, kMergeGrid = 256;   // (most calls merge little or nothing)
-__global__ __launch_bounds__(kMergeThreads) void attn_merge_kernel(AttnParams p) {
+__device__ __forceinline__ void merge_parts(const AttnParams& p, int n_blocks) {
   const int n_hg = p.Hq / p.Hkv / p.heads_per_wg, units = p.Hkv * n_hg;
   int rest, kvh, hg;
   unit_of_block(blockIdx.x, p.Hkv, n_hg, rest, kvh, hg);
@@ -1129,7 +1142,7 @@ __global__ __launch_bounds__(kMergeThreads) void attn_merge_kernel(AttnParams p)
   int4 a = ((const int4*)(p.splits + kSplitInts * min(rest / kWaves, kCus - 1)))[0];
   int parts = p.splits[kSplitInts * min(rest / kWaves, kCus - 1) + 4];
   const int n_work = p.n_items[1] * units * kWaves;
-  for (int b = blockIdx.x; b < n_work; b += gridDim.x) {
+  for (int b = blockIdx.x; b < n_work; b += n_blocks) {
     if (b != (int)blockIdx.x) {
       unit_of_block(b, p.Hkv, n_hg, rest, kvh, hg);
       a = ((const int4*)(p.splits + kSplitInts * (rest / kWaves)))[0];
@@ -1185,6 +1198,18 @@ __global__ __launch_bounds__(kMergeThreads) void attn_merge_kernel(AttnParams p)
       *(u32x2*)(dst + 8 * i) = u32x2{__builtin_bit_cast(uint32_t, y0), __builtin_bit_cast(uint32_t, y1)};
     }
   }
+}
+
+__global__ __launch_bounds__(kMergeThreads) void attn_merge_kernel(AttnParams p) { merge_parts(p, gridDim.x); }
+// The merge waits for one read behind the other and the copy of a step's pages for the memory: where a step needs both they share
+// a launch (merge_blocks workgroups and the rest), two workgroups to a compute unit.  One request of 137 rows behind 2992 keys
+// (187 pages): 8.0 + 7.0 us apart, 10.8 together.
+__global__ __launch_bounds__(kMergeThreads, 4) void attn_merge_gather_kernel(AttnParams p, SkvGather g, int merge_blocks) {
+  __shared__ int64_t first[kSkvGatherScan + 1];
+  if ((int)blockIdx.x < merge_blocks)
+    merge_parts(p, merge_blocks);
+  else
+    skv_gather_pages<true, kMergeThreads, 4>(g, (int)blockIdx.x - merge_blocks, (int)gridDim.x - merge_blocks, first);
 }
 
 // Query heads per workgroup: divides kWaves.  `fine`: eight where the kv head serves a multiple of eight.
@@ -1295,6 +1320,11 @@ extern "C" int skv_prefill_attn_workspace_size(const skv_attn_desc* desc, int32_
   return SKV_OK;
 }
 
+// (fp32 has no list, and a limit of its own)
+static bool too_many_items(const skv_attn_desc* d, const Layout& y) {
+  return d->dtype == SKV_BF16 && (y.max_items * y.units > 0x7fffffff || y.max_items > 0x3fffffff);
+}
+
 // Host-checkable argument errors common to both entry points.
 static int check_attn_buffers(const void* d_q, const void* d_knew, const void* d_vnew, const int32_t* d_q_off,
                               const void* d_kpool, const void* d_vpool, const int32_t* d_matched_len,
@@ -1307,14 +1337,28 @@ static int check_attn_buffers(const void* d_q, const void* d_knew, const void* d
   return SKV_OK;
 }
 
-// Shared by both entry points: enqueues the schedule kernel and the attention kernel on checked arguments.
+// What a whole step behind its lookup adds: the suffix offsets, made from req_off, and the gather.
+struct StepExtras {
+  const int32_t* req_off;
+  int32_t* q_off;
+  SkvGather gather;
+};
+
+// Shared by the entry points: enqueues the schedule kernel and the attention kernel on checked arguments.
 static int prefill_attn_enqueue(const skv_attn_desc* desc, int32_t n_req, const void* d_q,
                                 const void* d_knew, const void* d_vnew, const int32_t* d_q_off,
                                 int64_t total_q_rows, const void* d_kpool, const void* d_vpool,
                                 int32_t n_pages, const int32_t* d_matched_len,
                                 const int32_t* d_page_table, int32_t max_blocks, void* d_out,
-                                void* d_workspace, const Layout& y, void* stream) {
+                                void* d_workspace, const Layout& y, const StepExtras* x, void* stream) {
   hipStream_t st = (hipStream_t)stream;
+  // of up to kSkvGatherScan requests a plan with parts makes the suffix offsets itself, and its pages travel beside the merge
+  const bool plan = desc->dtype == SKV_BF16 && plan_in_place(y, n_req);
+  const bool late = x && plan && y.max_parts && !x->gather.large;
+  if (x && !late) {
+    const int rc = skv_gather_enqueue(x->gather, false, x->req_off, x->q_off, stream);
+    if (rc) return rc;
+  }
 
   AttnParams p;
   p.q = d_q; p.knew = d_knew; p.vnew = d_vnew; p.kpool = d_kpool; p.vpool = d_vpool; p.out = d_out;
@@ -1334,14 +1378,14 @@ static int prefill_attn_enqueue(const skv_attn_desc* desc, int32_t n_req, const 
   }
 
   // the list holds whole items or, where anything is split, no more than max_parts records
-  const bool plan = plan_in_place(y, n_req);
   const int64_t grid = (plan && y.max_parts ? kCus / y.units : std::max(y.max_items - y.max_parts, y.max_parts)) * y.units;
-  if (y.max_items * y.units > 0x7fffffff || y.max_items > 0x3fffffff) return SKV_ERANGE;
   char* const split_area = (char*)d_workspace + list_bytes(desc, y);
   p.splits = y.max_parts ? (const int32_t*)split_area : nullptr;
   p.partials = y.max_parts ? (float*)(split_area + kCus * kSplitInts * sizeof(int32_t)) : nullptr;
   p.q_off = d_q_off;
   p.matched_len = d_matched_len;
+  p.req_off = late ? x->req_off : nullptr;
+  p.q_off_out = late ? x->q_off : nullptr;
   p.n_items_out = (int32_t*)d_workspace;
   p.splits_out = (int32_t*)p.splits;
   p.n_req = n_req;
@@ -1359,10 +1403,37 @@ static int prefill_attn_enqueue(const skv_attn_desc* desc, int32_t n_req, const 
   kernel<<<(int)grid, kThreads, 0, st>>>(p);
   SKV_HIP(hipGetLastError());
   if (y.max_parts) {   // a split item has two parts at least
-    attn_merge_kernel<<<(int)std::min<int64_t>(y.max_parts / 2 * y.units * kWaves, kMergeGrid), kMergeThreads, 0, st>>>(p);
+    const int merge_blocks = (int)std::min<int64_t>(y.max_parts / 2 * y.units * kWaves, kMergeGrid);
+    if (late)
+      attn_merge_gather_kernel<<<merge_blocks + skv_gather_blocks(x->gather), kMergeThreads, 0, st>>>(p, x->gather, merge_blocks);
+    else
+      attn_merge_kernel<<<merge_blocks, kMergeThreads, 0, st>>>(p);
     SKV_HIP(hipGetLastError());
   }
   return SKV_OK;
+}
+
+// Arguments checked and the layout chosen; y's list fits the workspace.  *empty: nothing to compute.
+static int prefill_attn_check(const skv_attn_desc* desc, int32_t n_req, const void* d_q, const void* d_knew, const void* d_vnew,
+                              const int32_t* d_q_off, int64_t total_q_rows, const void* d_kpool, const void* d_vpool, int32_t n_pages,
+                              const int32_t* d_matched_len, const int32_t* d_page_table, int32_t max_blocks, const void* d_out,
+                              const void* d_workspace, size_t workspace_bytes, Layout& y, bool& empty) {
+  int rc = check_attn(desc);
+  if (rc) return rc;
+  if (n_req < 0 || total_q_rows < 0 || n_pages < 0 || max_blocks < 0) return SKV_EINVAL;
+  empty = n_req == 0 || total_q_rows == 0;
+  if (empty) return SKV_OK;
+  rc = check_attn_buffers(d_q, d_knew, d_vnew, d_q_off, d_kpool, d_vpool, d_matched_len, d_page_table, max_blocks,
+                          d_out);
+  if (rc) return rc;
+  // a workspace that holds the plain work list is enough: the call then splits nothing, and takes 32-row tiles if their list fits
+  y = layout_for(desc, n_req, total_q_rows, eight_heads(desc, n_req, total_q_rows, max_blocks, true), true);
+  if (y.max_parts && (!may_split(y, n_req, total_q_rows, max_blocks) || workspace_bytes < list_bytes(desc, y) + split_bytes(y)))
+    y = layout_for(desc, n_req, total_q_rows, eight_heads(desc, n_req, total_q_rows, max_blocks, false), false);
+  if (workspace_bytes < list_bytes(desc, y)) y = layout_for(desc, n_req, total_q_rows, false, false);
+  if (!d_workspace || workspace_bytes < list_bytes(desc, y)) return SKV_ENOMEM;
+  if ((uintptr_t)d_workspace & 15) return SKV_EINVAL;
+  return too_many_items(desc, y) ? SKV_ERANGE : SKV_OK;
 }
 
 extern "C" int skv_prefill_attn(const skv_attn_desc* desc, int32_t n_req, const void* d_q,
@@ -1371,22 +1442,36 @@ extern "C" int skv_prefill_attn(const skv_attn_desc* desc, int32_t n_req, const 
                                 int32_t n_pages, const int32_t* d_matched_len,
                                 const int32_t* d_page_table, int32_t max_blocks, void* d_out,
                                 void* d_workspace, size_t workspace_bytes, void* stream) {
-  int rc = check_attn(desc);
-  if (rc) return rc;
-  if (n_req < 0 || total_q_rows < 0 || n_pages < 0 || max_blocks < 0) return SKV_EINVAL;
-  if (n_req == 0 || total_q_rows == 0) return SKV_OK;
-  rc = check_attn_buffers(d_q, d_knew, d_vnew, d_q_off, d_kpool, d_vpool, d_matched_len, d_page_table, max_blocks,
-                          d_out);
-  if (rc) return rc;
-  // a workspace that holds the plain work list is enough: the call then splits nothing, and takes 32-row tiles if their list fits
-  Layout y = layout_for(desc, n_req, total_q_rows, eight_heads(desc, n_req, total_q_rows, max_blocks, true), true);
-  if (y.max_parts && (!may_split(y, n_req, total_q_rows, max_blocks) || workspace_bytes < list_bytes(desc, y) + split_bytes(y)))
-    y = layout_for(desc, n_req, total_q_rows, eight_heads(desc, n_req, total_q_rows, max_blocks, false), false);
-  if (workspace_bytes < list_bytes(desc, y)) y = layout_for(desc, n_req, total_q_rows, false, false);
-  if (!d_workspace || workspace_bytes < list_bytes(desc, y)) return SKV_ENOMEM;
-  if ((uintptr_t)d_workspace & 15) return SKV_EINVAL;
+  Layout y;
+  bool empty;
+  const int rc = prefill_attn_check(desc, n_req, d_q, d_knew, d_vnew, d_q_off, total_q_rows, d_kpool, d_vpool, n_pages, d_matched_len,
+                                    d_page_table, max_blocks, d_out, d_workspace, workspace_bytes, y, empty);
+  if (rc || empty) return rc;
   return prefill_attn_enqueue(desc, n_req, d_q, d_knew, d_vnew, d_q_off, total_q_rows, d_kpool, d_vpool, n_pages,
-                              d_matched_len, d_page_table, max_blocks, d_out, d_workspace, y, stream);
+                              d_matched_len, d_page_table, max_blocks, d_out, d_workspace, y, nullptr, stream);
+}
+
+extern "C" int skv_prefill_step(const skv_attn_desc* desc, int32_t n_req, const int32_t* d_req_off, const void* d_q,
+                                const void* d_knew, const void* d_vnew, int32_t* d_q_off, int64_t total_q_rows,
+                                const void* d_kpool, const void* d_vpool, int32_t n_pages, const int32_t* d_matched_len,
+                                const int32_t* d_page_table, int32_t max_blocks, void* d_out, int64_t* d_ctx_off, void* d_kctx,
+                                void* d_vctx, int64_t ctx_capacity_tokens, void* d_workspace, size_t workspace_bytes,
+                                void* stream) {
+  StepExtras x = {d_req_off, d_q_off, {}};
+  if (n_req < 0 || !d_q_off || (n_req > 0 && (!d_req_off || !d_matched_len))) return SKV_EINVAL;
+  int rc = skv_gather_check(desc, n_req, d_kpool, d_vpool, n_pages, d_matched_len, d_page_table, max_blocks, d_ctx_off, d_kctx, d_vctx,
+                            ctx_capacity_tokens, &x.gather);
+  if (rc) return rc;
+  Layout y;
+  bool empty = false;
+  rc = prefill_attn_check(desc, n_req, d_q, d_knew, d_vnew, d_q_off, total_q_rows, d_kpool, d_vpool, n_pages, d_matched_len,
+                          d_page_table, max_blocks, d_out, d_workspace, workspace_bytes, y, empty);
+  if (rc || empty) {   // what does not depend on the attention happens all the same
+    const int rg = skv_gather_enqueue(x.gather, false, d_req_off, d_q_off, stream);
+    return rg ? rg : rc;
+  }
+  return prefill_attn_enqueue(desc, n_req, d_q, d_knew, d_vnew, d_q_off, total_q_rows, d_kpool, d_vpool, n_pages,
+                              d_matched_len, d_page_table, max_blocks, d_out, d_workspace, y, &x, stream);
 }
 
 // ---- the same call for callers that cannot allocate ---------------------------------------------
@@ -1429,14 +1514,14 @@ extern "C" int skv_prefill_attn_static(const skv_attn_desc* desc, int32_t n_req,
   if (rc) return rc;
   Layout y = layout_for(desc, n_req, total_q_rows, eight_heads(desc, n_req, total_q_rows, max_blocks, false), false);
   if (list_bytes(desc, y) > (size_t)SKV_STATIC_SCRATCH_BYTES) y = layout_for(desc, n_req, total_q_rows, false, false);
-  if (list_bytes(desc, y) > (size_t)SKV_STATIC_SCRATCH_BYTES) return SKV_ERANGE;   // batch too large for the built-in scratch
+  if (list_bytes(desc, y) > (size_t)SKV_STATIC_SCRATCH_BYTES || too_many_items(desc, y)) return SKV_ERANGE;   // batch too large for the built-in scratch
   void* ws = nullptr;
   rc = scratch_of_current_device(&ws);
   if (rc) return rc;
   // the schedule kernel rewrites the item count and every record it hands out on each call,
   // so nothing of the previous call's contents is read
   return prefill_attn_enqueue(desc, n_req, d_q, d_knew, d_vnew, d_q_off, total_q_rows, d_kpool, d_vpool, n_pages,
-                              d_matched_len, d_page_table, max_blocks, d_out, ws, y, stream);
+                              d_matched_len, d_page_table, max_blocks, d_out, ws, y, nullptr, stream);
 }
 
 // ---- measurement aid: what the matrix cores sustain on given operand values ----

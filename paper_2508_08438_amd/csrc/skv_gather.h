@@ -1,0 +1,100 @@
+// The page copy of the gather, for the kernels that carry it: alone, or beside other work of the same step.
+#ifndef SKV_GATHER_H
+#define SKV_GATHER_H
+#include "skv_internal.h"
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+struct SkvGather {
+  int n_req;
+  const u32x4 *kpool, *vpool;
+  int n_pages;
+  const int32_t *matched_len, *page_table;
+  int max_blocks;
+  int64_t* ctx_off;
+  u32x4 *kctx, *vctx;
+  int64_t cap_pages;
+  int page_vec;   // 16-byte vectors per page
+  int slices;     // workgroups per page
+  bool large;     // enough bytes for the form of one workgroup per compute unit
+};
+constexpr int kSkvGatherScan = 512;   // requests up to which every workgroup scans the matched lengths itself
+
+// Arguments checked and laid out; workgroups of a call; the call.  d_q_off: the suffix offsets are written too.
+int skv_gather_check(const skv_attn_desc* desc, int32_t n_req, const void* d_kpool, const void* d_vpool, int32_t n_pages,
+                     const int32_t* d_matched_len, const int32_t* d_page_table, int32_t max_blocks, int64_t* d_ctx_off, void* d_kctx,
+                     void* d_vctx, int64_t ctx_capacity_tokens, SkvGather* g);
+int skv_gather_blocks(const SkvGather& g);
+int skv_gather_enqueue(const SkvGather& g, bool beside, const int32_t* d_req_off, int32_t* d_q_off, void* stream);
+
+#ifdef __HIPCC__
+// What workgroup `block` of n_blocks copies (n_blocks is a multiple of the slices): it loops over the global list of matched pages, each
+// moving as 16-byte vectors with all loads of a step issued before its stores.  kScan: the workgroup scans the matched lengths
+// itself (the first one also writes the offsets) and finds the owner of a page in `first`, kSkvGatherScan + 1 places in LDS.
+template <bool kScan, int kThreads, int kUnroll>
+__device__ __forceinline__ void skv_gather_pages(const SkvGather& g, int block, int n_blocks, int64_t* first) {
+  const int n_req = g.n_req;
+  int64_t total;
+  if constexpr (kScan) {
+    __shared__ int64_t red[kThreads / 64];
+    const int own = (n_req + kThreads - 1) / kThreads;         // requests per thread
+    const int r0 = min((int)threadIdx.x * own, n_req), r1 = min(r0 + own, n_req);
+    auto pages_of = [&](int r) { return max(g.matched_len[r], 0) / SKV_BLOCK_TOKENS; };
+    int64_t mine = 0;
+    for (int r = r0; r < r1; ++r) mine += pages_of(r);
+    int64_t at = skv_block_scan<kThreads>(mine, red, total) - mine;
+    for (int r = r0; r < r1; ++r) {
+      first[r] = at;
+      at += pages_of(r);
+      if (block == 0) g.ctx_off[r + 1] = at * SKV_BLOCK_TOKENS;
+    }
+    if (threadIdx.x == 0) {
+      first[n_req] = total;
+      if (block == 0) g.ctx_off[0] = 0;
+    }
+    __syncthreads();
+  } else {
+    total = g.ctx_off[n_req] / SKV_BLOCK_TOKENS;
+  }
+  auto pages_before = [&](int r) { return kScan ? first[r] : g.ctx_off[r] / SKV_BLOCK_TOKENS; };
+  const int64_t end = min(total, g.cap_pages);
+  const int slice = block % g.slices, v0 = g.page_vec / g.slices * slice, v1 = slice + 1 < g.slices ? v0 + g.page_vec / g.slices : g.page_vec;
+  for (int64_t p = block / g.slices; p < end; p += n_blocks / g.slices) {
+    // request that owns output page p: the last one with no more than p pages before it
+    int lo = 0, hi = n_req;  // invariant: pages_before(lo) <= p < pages_before(hi)
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) >> 1;
+      if (pages_before(mid) <= p) lo = mid; else hi = mid;
+    }
+    const int64_t before = pages_before(lo);
+    const int j = (int)(p - before);
+    if (j >= g.max_blocks) continue;
+    const int page = g.page_table[(size_t)lo * g.max_blocks + j];
+    if (page < 0 || page >= g.n_pages) continue;  // uniform per workgroup
+    const u32x4* ks = g.kpool + (size_t)page * g.page_vec;
+    const u32x4* vs = g.vpool + (size_t)page * g.page_vec;
+    u32x4* kd = g.kctx + (size_t)p * g.page_vec;
+    u32x4* vd = g.vctx + (size_t)p * g.page_vec;
+    for (int base = v0; base < v1; base += kThreads * kUnroll) {
+      u32x4 a[kUnroll], b[kUnroll];
+#pragma unroll
+      for (int u = 0; u < kUnroll; ++u) {
+        const int i = base + u * kThreads + threadIdx.x;
+        if (i < v1) {
+          a[u] = __builtin_nontemporal_load(ks + i);
+          b[u] = __builtin_nontemporal_load(vs + i);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < kUnroll; ++u) {
+        const int i = base + u * kThreads + threadIdx.x;
+        if (i < v1) {
+          __builtin_nontemporal_store(a[u], kd + i);
+          __builtin_nontemporal_store(b[u], vd + i);
+        }
+      }
+    }
+  }
+}
+#endif
+#endif

@@ -3,17 +3,13 @@
 // SafeKV Section 4.3.2: after the lookup stops at a compressed node the required KV blocks are
 // read directly from its address vector.  Here the address vector is the page table written by
 // the match; a page is one contiguous chunk of 16 * n_kv_heads * head_dim elements, so the
-// gather is a batch of page-sized copies chosen by the table.  Workgroups loop over the global
-// list of matched pages (persistent grid), each page moving as 16-byte vectors with all loads
-// of a step issued before its stores.
-#include "skv_internal.h"
+// gather is a batch of page-sized copies chosen by the table (the copy itself: skv_gather_pages).
+#include "skv_gather.h"
 
 namespace {
 
 constexpr int kThreads = 256;
 constexpr int kUnroll = 8;  // 16-byte vectors in flight per thread and pool
-
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // Where the output of every request starts, one workgroup.
 constexpr int kOffThreads = 1024, kOffPer = 4;
@@ -39,79 +35,33 @@ __global__ __launch_bounds__(kOffThreads) void ctx_offsets_kernel(int n_req, con
   }
 }
 
-// kScan: every workgroup scans the matched lengths itself (the first one also writes the offsets) and finds the owner of a page
-// in LDS.  A kernel for the offsets in front costs a launch, 4.5 us for one request, but reads the lengths once: one page each of
-// 16 / 256 / 512 requests 14.0 / 19.4 / 23.5 us scanned, 16.6 / 22.0 / 24.4 with that kernel; of 1024 / 4096 / 16384 33.6 / 158 /
-// 685 scanned, 33.7 / 113 / 432 with it; 40 pages each of 1024 1053 and 1044.
-constexpr int kPref = 512;
-template <bool kScan>
-__global__ __launch_bounds__(kThreads) void gather_pages_kernel(
-    int n_req, const u32x4* __restrict__ kpool, const u32x4* __restrict__ vpool, int n_pages,
-    const int32_t* __restrict__ matched_len, const int32_t* __restrict__ page_table, int max_blocks,
-    int64_t* __restrict__ ctx_off, u32x4* __restrict__ kctx, u32x4* __restrict__ vctx, int64_t cap_pages,
-    int page_vec /* 16-byte vectors per page */, int slices) {
-  __shared__ int64_t first[kScan ? kPref + 1 : 1];   // pages before a request
-  int64_t total;
-  if constexpr (kScan) {
-    __shared__ int64_t red[kThreads / 64];
-    const int own = (n_req + kThreads - 1) / kThreads;         // requests per thread
-    const int r0 = min((int)threadIdx.x * own, n_req), r1 = min(r0 + own, n_req);
-    auto pages_of = [&](int r) { return max(matched_len[r], 0) / SKV_BLOCK_TOKENS; };
-    int64_t mine = 0;
-    for (int r = r0; r < r1; ++r) mine += pages_of(r);
-    int64_t at = skv_block_scan<kThreads>(mine, red, total) - mine;
-    for (int r = r0; r < r1; ++r) {
-      first[r] = at;
-      at += pages_of(r);
-      if (blockIdx.x == 0) ctx_off[r + 1] = at * SKV_BLOCK_TOKENS;
-    }
-    if (threadIdx.x == 0) {
-      first[n_req] = total;
-      if (blockIdx.x == 0) ctx_off[0] = 0;
-    }
-    __syncthreads();
-  } else {
-    total = ctx_off[n_req] / SKV_BLOCK_TOKENS;
-  }
-  auto pages_before = [&](int r) { return kScan ? first[r] : ctx_off[r] / SKV_BLOCK_TOKENS; };
-  const int64_t end = min(total, cap_pages);
-  const int slice = (int)blockIdx.x % slices, v0 = page_vec / slices * slice, v1 = slice + 1 < slices ? v0 + page_vec / slices : page_vec;
-  for (int64_t p = blockIdx.x / slices; p < end; p += gridDim.x / slices) {
-    // request that owns output page p: the last one with no more than p pages before it
-    int lo = 0, hi = n_req;  // invariant: pages_before(lo) <= p < pages_before(hi)
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if (pages_before(mid) <= p) lo = mid; else hi = mid;
-    }
-    const int64_t before = pages_before(lo);
-    const int j = (int)(p - before);
-    if (j >= max_blocks) continue;
-    const int page = page_table[(size_t)lo * max_blocks + j];
-    if (page < 0 || page >= n_pages) continue;  // uniform per workgroup
-    const u32x4* ks = kpool + (size_t)page * page_vec;
-    const u32x4* vs = vpool + (size_t)page * page_vec;
-    u32x4* kd = kctx + (size_t)p * page_vec;
-    u32x4* vd = vctx + (size_t)p * page_vec;
-    for (int base = v0; base < v1; base += kThreads * kUnroll) {
-      u32x4 a[kUnroll], b[kUnroll];
+// A kernel for the offsets in front of it (kScan false) costs a launch, 4.5 us for one request, but reads the lengths once: one page
+// each of 16 / 256 / 512 requests 14.0 / 19.4 / 23.5 us scanned, 16.6 / 22.0 / 24.4 with that kernel; of 1024 / 4096 / 16384 33.6 /
+// 158 / 685 scanned, 33.7 / 113 / 432 with it; 40 pages each of 1024 1053 and 1044.
+// kOffsets: the first workgroup writes the suffix offsets instead (skv_suffix_offsets of up to kSkvGatherScan requests), which
+// neither reads nor delays a page: one launch less in a step.
+template <bool kScan, bool kOffsets>
+__global__ __launch_bounds__(kThreads) void gather_pages_kernel(SkvGather g, const int32_t* __restrict__ req_off, int32_t* __restrict__ q_off) {
+  if constexpr (kOffsets) {
+    if (blockIdx.x == 0) {
+      __shared__ int red[kThreads / 64];
+      constexpr int kPer = kSkvGatherScan / kThreads;
+      int v[kPer], own = 0, total;
+      const int r0 = threadIdx.x * kPer;
 #pragma unroll
-      for (int u = 0; u < kUnroll; ++u) {
-        const int i = base + u * kThreads + threadIdx.x;
-        if (i < v1) {
-          a[u] = __builtin_nontemporal_load(ks + i);
-          b[u] = __builtin_nontemporal_load(vs + i);
-        }
-      }
+      for (int k = 0; k < kPer; ++k) own += v[k] = r0 + k < g.n_req ? max(0, req_off[r0 + k + 1] - req_off[r0 + k] - g.matched_len[r0 + k]) : 0;
+      int x = skv_block_scan<kThreads>(own, red, total) - own;
+      if (threadIdx.x == 0) q_off[0] = 0;
 #pragma unroll
-      for (int u = 0; u < kUnroll; ++u) {
-        const int i = base + u * kThreads + threadIdx.x;
-        if (i < v1) {
-          __builtin_nontemporal_store(a[u], kd + i);
-          __builtin_nontemporal_store(b[u], vd + i);
-        }
+      for (int k = 0; k < kPer; ++k) {
+        x += v[k];
+        if (r0 + k < g.n_req) q_off[r0 + k + 1] = x;
       }
+      return;
     }
   }
+  __shared__ int64_t first[kScan ? kSkvGatherScan + 1 : 1];
+  skv_gather_pages<kScan, kThreads, kUnroll>(g, (int)blockIdx.x - kOffsets, (int)gridDim.x - kOffsets, first);
 }
 
 // The same copy for a call that runs beside a kernel which holds most of the chip's registers (prefill attention: 240 of a
@@ -119,6 +69,7 @@ __global__ __launch_bounds__(kThreads) void gather_pages_kernel(
 // are left, so it needs no compute unit of its own and takes what the other kernel leaves of the memory's time.  Addresses are
 // buffer descriptors and scalar offsets for the registers' sake; what lies behind a page's end is neither read nor written.
 // Alone it is the faster form of a large copy too (large_copy).
+constexpr int kPref = kSkvGatherScan;
 constexpr int kBesideGrid = 256, kBesideUnroll = 3;
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(32))) void gather_beside_kernel(
     int n_req, const char* __restrict__ kpool, const char* __restrict__ vpool, int n_pages,
@@ -282,9 +233,9 @@ extern "C" int skv_scatter_kv(const skv_attn_desc* desc, int32_t n_req, const vo
   return SKV_OK;
 }
 
-static int gather_enqueue(const skv_attn_desc* desc, int32_t n_req, const void* d_kpool, const void* d_vpool, int32_t n_pages,
-                          const int32_t* d_matched_len, const int32_t* d_page_table, int32_t max_blocks, int64_t* d_ctx_off,
-                          void* d_kctx, void* d_vctx, int64_t ctx_capacity_tokens, bool beside, void* stream) {
+int skv_gather_check(const skv_attn_desc* desc, int32_t n_req, const void* d_kpool, const void* d_vpool, int32_t n_pages,
+                     const int32_t* d_matched_len, const int32_t* d_page_table, int32_t max_blocks, int64_t* d_ctx_off, void* d_kctx,
+                     void* d_vctx, int64_t ctx_capacity_tokens, SkvGather* g) {
   if (!desc || n_req < 0 || n_pages < 0 || max_blocks < 0 || ctx_capacity_tokens < 0) return SKV_EINVAL;
   if (desc->dtype != SKV_F32 && desc->dtype != SKV_BF16) return SKV_EINVAL;
   if (desc->n_kv_heads < 1 || desc->head_dim < 1) return SKV_EINVAL;
@@ -295,34 +246,65 @@ static int gather_enqueue(const skv_attn_desc* desc, int32_t n_req, const void* 
   if (n_req > 0 && (!d_matched_len || !d_kpool || !d_vpool || !d_kctx || !d_vctx)) return SKV_EINVAL;
   if (n_req > 0 && max_blocks > 0 && !d_page_table) return SKV_EINVAL;
   if (((uintptr_t)d_kpool | (uintptr_t)d_vpool | (uintptr_t)d_kctx | (uintptr_t)d_vctx) & 15) return SKV_EINVAL;
-  hipStream_t st = (hipStream_t)stream;
   const int64_t upper = (int64_t)n_req * max_blocks;  // pages the batch can reference at most
-  const int grid = (int)(upper < 1 ? 1 : (upper < 256 * 16 ? upper : 256 * 16));
-  if ((beside || large_copy(upper, page_bytes)) && n_req <= kPref && page_bytes <= 0x7fffffff) {
+  *g = {n_req, (const u32x4*)d_kpool, (const u32x4*)d_vpool, n_pages, d_matched_len, d_page_table, max_blocks, d_ctx_off,
+        (u32x4*)d_kctx, (u32x4*)d_vctx, upper ? ctx_capacity_tokens / SKV_BLOCK_TOKENS : 0, (int)(page_bytes / 16), slices_for(upper),
+        n_req <= kPref && page_bytes <= 0x7fffffff && large_copy(upper, page_bytes)};
+  return SKV_OK;
+}
+
+int skv_gather_blocks(const SkvGather& g) {
+  const int64_t upper = (int64_t)g.n_req * g.max_blocks;
+  return (int)(upper < 1 ? 1 : (upper < 256 * 16 ? upper : 256 * 16)) * g.slices;
+}
+
+int skv_gather_enqueue(const SkvGather& g, bool beside, const int32_t* d_req_off, int32_t* d_q_off, void* stream) {
+  hipStream_t st = (hipStream_t)stream;
+  const bool scan = g.n_req <= kPref;
+  if (scan && (beside || g.large) && (int64_t)g.page_vec * 16 <= 0x7fffffff) {
+    if (d_q_off) {
+      const int rc = skv_suffix_offsets(g.n_req, d_req_off, g.matched_len, d_q_off, stream);
+      if (rc) return rc;
+    }
     gather_beside_kernel<<<kBesideGrid, kThreads, 0, st>>>(
-        n_req, (const char*)d_kpool, (const char*)d_vpool, n_pages, d_matched_len, d_page_table, max_blocks, d_ctx_off,
-        (char*)d_kctx, (char*)d_vctx, upper ? ctx_capacity_tokens / SKV_BLOCK_TOKENS : 0, (int)page_bytes);
+        g.n_req, (const char*)g.kpool, (const char*)g.vpool, g.n_pages, g.matched_len, g.page_table, g.max_blocks, g.ctx_off,
+        (char*)g.kctx, (char*)g.vctx, g.cap_pages, g.page_vec * 16);
     SKV_HIP(hipGetLastError());
     return SKV_OK;
   }
-  auto gather = n_req <= kPref ? gather_pages_kernel<true> : gather_pages_kernel<false>;
-  if (n_req > kPref) {
-    ctx_offsets_kernel<<<1, kOffThreads, 0, st>>>(n_req, d_matched_len, d_ctx_off);
+  if (scan) {
+    if (d_q_off)
+      gather_pages_kernel<true, true><<<skv_gather_blocks(g) + 1, kThreads, 0, st>>>(g, d_req_off, d_q_off);
+    else
+      gather_pages_kernel<true, false><<<skv_gather_blocks(g), kThreads, 0, st>>>(g, nullptr, nullptr);
     SKV_HIP(hipGetLastError());
-    if (max_blocks == 0) return SKV_OK;
+    return SKV_OK;
   }
-  const int slices = slices_for(upper);
-  gather<<<grid * slices, kThreads, 0, st>>>(
-      n_req, (const u32x4*)d_kpool, (const u32x4*)d_vpool, n_pages, d_matched_len, d_page_table, max_blocks, d_ctx_off,
-      (u32x4*)d_kctx, (u32x4*)d_vctx, upper ? ctx_capacity_tokens / SKV_BLOCK_TOKENS : 0, (int)(page_bytes / 16), slices);
+  if (d_q_off) {
+    const int rc = skv_suffix_offsets(g.n_req, d_req_off, g.matched_len, d_q_off, stream);
+    if (rc) return rc;
+  }
+  ctx_offsets_kernel<<<1, kOffThreads, 0, st>>>(g.n_req, g.matched_len, g.ctx_off);
+  SKV_HIP(hipGetLastError());
+  if (g.max_blocks == 0) return SKV_OK;
+  gather_pages_kernel<false, false><<<skv_gather_blocks(g), kThreads, 0, st>>>(g, nullptr, nullptr);
   SKV_HIP(hipGetLastError());
   return SKV_OK;
+}
+
+static int gather_call(const skv_attn_desc* desc, int32_t n_req, const void* d_kpool, const void* d_vpool, int32_t n_pages,
+                       const int32_t* d_matched_len, const int32_t* d_page_table, int32_t max_blocks, int64_t* d_ctx_off, void* d_kctx,
+                       void* d_vctx, int64_t ctx_capacity_tokens, bool beside, void* stream) {
+  SkvGather g;
+  const int rc = skv_gather_check(desc, n_req, d_kpool, d_vpool, n_pages, d_matched_len, d_page_table, max_blocks, d_ctx_off, d_kctx,
+                                  d_vctx, ctx_capacity_tokens, &g);
+  return rc ? rc : skv_gather_enqueue(g, beside, nullptr, nullptr, stream);
 }
 
 extern "C" int skv_gather_kv(const skv_attn_desc* desc, int32_t n_req, const void* d_kpool, const void* d_vpool,
                              int32_t n_pages, const int32_t* d_matched_len, const int32_t* d_page_table, int32_t max_blocks,
                              int64_t* d_ctx_off, void* d_kctx, void* d_vctx, int64_t ctx_capacity_tokens, void* stream) {
-  return gather_enqueue(desc, n_req, d_kpool, d_vpool, n_pages, d_matched_len, d_page_table, max_blocks, d_ctx_off, d_kctx, d_vctx,
+  return gather_call(desc, n_req, d_kpool, d_vpool, n_pages, d_matched_len, d_page_table, max_blocks, d_ctx_off, d_kctx, d_vctx,
                         ctx_capacity_tokens, false, stream);
 }
 
@@ -330,6 +312,6 @@ extern "C" int skv_gather_kv_beside(const skv_attn_desc* desc, int32_t n_req, co
                                     int32_t n_pages, const int32_t* d_matched_len, const int32_t* d_page_table,
                                     int32_t max_blocks, int64_t* d_ctx_off, void* d_kctx, void* d_vctx,
                                     int64_t ctx_capacity_tokens, void* stream) {
-  return gather_enqueue(desc, n_req, d_kpool, d_vpool, n_pages, d_matched_len, d_page_table, max_blocks, d_ctx_off, d_kctx, d_vctx,
+  return gather_call(desc, n_req, d_kpool, d_vpool, n_pages, d_matched_len, d_page_table, max_blocks, d_ctx_off, d_kctx, d_vctx,
                         ctx_capacity_tokens, true, stream);
 }

@@ -113,10 +113,13 @@ class Session:
         skv.skv_counters_reset(self.tree)
 
     # -- the individual stages (each only enqueues on the current stream)
-    def match(self):
+    def lookup(self):
         skv.skv_counters_reset(self.tree)
         skv.skv_match(self.tree, self.req_off, self.req_tokens, self.req_tenant, self.max_blocks,
                       self.matched_len, self.page_table)
+
+    def match(self):
+        self.lookup()
         skv.skv_suffix_offsets(self.req_off, self.matched_len, self.q_off)
 
     def gather(self, stream=None, beside=False):
@@ -127,15 +130,20 @@ class Session:
         skv.skv_prefill_attn(self.desc, self.q, self.knew, self.vnew, self.q_off, self.kpool, self.vpool,
                              self.matched_len, self.page_table, self.max_blocks, self.out, self.workspace)
 
-    def gather_and_attention(self):
-        """Both read the match's results and neither the other's: a large copy runs on a stream of its own beside
-        the attention.  The current stream waits for it before this returns, also where attention() raises."""
-        main = torch.cuda.current_stream() if self.side and self.do_gather else None
+    def _pass(self):
+        """Gather and attention both read the match's results and neither the other's: a large copy runs on a stream of its own
+        beside the attention (the current stream waits for it before this returns, also where attention() raises); what is
+        smaller, and the suffix offsets, share the attention's call."""
+        self.lookup()
+        if not self.do_gather:
+            skv.skv_suffix_offsets(self.req_off, self.matched_len, self.q_off)
+            return self.attention()
+        main = torch.cuda.current_stream() if self.side else None
         if main is None or main.device != self.side.device:
-            if self.do_gather:
-                self.gather()
-            self.attention()
-            return
+            return skv.skv_prefill_step(self.desc, self.req_off, self.q, self.knew, self.vnew, self.q_off, self.kpool, self.vpool,
+                                        self.matched_len, self.page_table, self.max_blocks, self.out, self.ctx_off, self.kctx,
+                                        self.vctx, self.workspace)
+        skv.skv_suffix_offsets(self.req_off, self.matched_len, self.q_off)
         side = self.side_capture if torch.cuda.is_current_stream_capturing() else self.side
         matched = main.record_event()
         try:
@@ -148,8 +156,7 @@ class Session:
     def step(self):
         if self.q is None:
             self.prepare()
-        self.match()
-        self.gather_and_attention()
+        self._pass()
         return {"matched_len": self.matched_len, "page_table": self.page_table, "q_off": self.q_off,
                 "ctx_off": self.ctx_off, "out": self.out, "kctx": self.kctx, "vctx": self.vctx}
 
@@ -162,8 +169,7 @@ class Session:
         torch.cuda.synchronize(self.device)
         self.graph = torch.cuda.CUDAGraph()
         with torch.cuda.graph(self.graph):
-            self.match()
-            self.gather_and_attention()
+            self._pass()
         return self.graph
 
     def replay(self):
