@@ -102,12 +102,18 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(32))) void
   };
   const int64_t end = uniform(min(first[n_req], cap_pages));
   const unsigned at = threadIdx.x * 16;
-  int r = 0;   // request that owns output page p
-  for (int64_t p = blockIdx.x; p < end; p += kBesideGrid) {
+  // Page ids are asked for a page ahead: one workgroup per compute unit has nobody to cover the read.
+  int r = 0;   // request that owns the page
+  auto page_of = [&](int64_t p) __attribute__((always_inline)) {
+    if (p >= end) return -1;
     while (uniform(first[r + 1]) <= p) ++r;
     const int64_t j = p - uniform(first[r]);
-    if (j >= max_blocks) continue;
-    const int page = __builtin_amdgcn_readfirstlane(page_table[(size_t)r * max_blocks + j]);
+    return j < max_blocks ? page_table[(size_t)r * max_blocks + j] : -1;
+  };
+  int next = page_of(blockIdx.x);
+  for (int64_t p = blockIdx.x; p < end; p += kBesideGrid) {
+    const int page = __builtin_amdgcn_readfirstlane(next);
+    next = page_of(p + kBesideGrid);
     if (page < 0 || page >= n_pages) continue;
     const __amdgpu_buffer_rsrc_t ks = __builtin_amdgcn_make_buffer_rsrc((void*)(kpool + (size_t)page * page_bytes), 0, page_bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t vs = __builtin_amdgcn_make_buffer_rsrc((void*)(vpool + (size_t)page * page_bytes), 0, page_bytes, 0x00020000);
@@ -192,8 +198,9 @@ __global__ __launch_bounds__(kThreads) void stream_copy_kernel(const u32x4* __re
 
 // One workgroup per compute unit keeps enough in flight and goes through neighbouring pages together: us of the plain form / of that one,
 // 32 KB pages 1024 24.8 / 25.8, 2048 51.5 / 47.6, 4096 101 / 93, 16384 401 / 379 (5.67 TB/s); 64 KB 512 28.2 / 26.5; 16 KB 2048
-// 26.9 / 26.1, 16384 197 / 184; 8 KB 65536 409 / 379; but 4 KB, one load per thread and pool, 16384 52.6 / 68.0.
-bool large_copy(int64_t pages, int64_t page_bytes) { return page_bytes >= 8192 && pages * page_bytes >= (48 << 20); }
+// 26.9 / 26.1, 16384 197 / 184.  Below, a page is too few loads per thread and the scan in front too long: 8 KB of 253 requests, 22500
+// pages, 74.2 / 78.3; 4 KB 16384 52.6 / 68.0.
+bool large_copy(int64_t pages, int64_t page_bytes) { return page_bytes >= 16384 && pages * page_bytes >= (48 << 20); }
 // Workgroups per page: where a batch has no page for every compute unit a page of 32 KB is several workgroups' worth of loads in
 // flight.  us with 1 / 2 / 4 slices: 16 pages 4.95 / 4.1 / 3.8, 128 (of the fp32 pool's 32 KB) 6.4 / 5.6 / 5.3, 187 6.3 / 5.9 / 6.2,
 // 512 11.9 / 12.3 / 14.1.
