@@ -206,6 +206,14 @@ int skv_match(skv_tree* tree, int32_t n_req, const int32_t* d_req_off, const int
               const int32_t* d_req_tenant, int32_t max_blocks, int32_t* d_matched_len,
               int32_t* d_page_table, int32_t* d_path_end, void* stream);
 
+/* skv_counters_reset and skv_match in one call, for a step that opens a monitoring window.  Of up to 512 requests, on a tree without
+ * copies, it is one launch; the counters are then cleared but not yet updated: *left (HOST) is 1, and the matched blocks' records, in
+ * d_records (n_req * max_blocks), are for skv_prefill_step to count.  Otherwise, and where d_records is NULL, *left is 0 and
+ * the counters are complete.  Results and errors of the two calls. */
+int skv_match_window(skv_tree* tree, int32_t n_req, const int32_t* d_req_off, const int32_t* d_req_tokens,
+                     const int32_t* d_req_tenant, int32_t max_blocks, int32_t* d_matched_len, int32_t* d_page_table,
+                     int32_t* d_records, int32_t* left, void* stream);
+
 /* Limits of the branching lookup (trees with per-tenant copies, Section 4.1): which of them any request has run
  * into since the tree was built or the word was last cleared -- SKV_LIMIT_BRANCH_POINTS (more than 10 positions
  * with several visible copies on one walk), SKV_LIMIT_COPIES (more than 64 visible copies at one position),
@@ -362,14 +370,15 @@ int skv_prefill_attn(const skv_attn_desc* desc, int32_t n_req, const void* d_q, 
 
 /* Everything of a step behind its lookup in one call: skv_suffix_offsets (d_q_off is written), skv_gather_kv and
  * skv_prefill_attn, with the results and errors of the three.  An error of the attention's arguments leaves the other two done,
- * as when they are called in front of it.  Fewer launches than the three: small batches make the offsets in another kernel's first steps and
+ * as when they are called in front of it.  d_records, where not NULL: what skv_match_window left to count, with its tree, tenants and
+ * matched lengths (the tree unchanged since); it is counted in any case.  Fewer launches than the three: small batches make the offsets in another kernel's first steps and
  * copy their pages beside the merge of split items. */
 int skv_prefill_step(const skv_attn_desc* desc, int32_t n_req, const int32_t* d_req_off, const void* d_q,
                      const void* d_knew, const void* d_vnew, int32_t* d_q_off, int64_t total_q_rows,
                      const void* d_kpool, const void* d_vpool, int32_t n_pages, const int32_t* d_matched_len,
                      const int32_t* d_page_table, int32_t max_blocks, void* d_out, int64_t* d_ctx_off, void* d_kctx,
-                     void* d_vctx, int64_t ctx_capacity_tokens, void* d_workspace, size_t workspace_bytes,
-                     void* stream);
+                     void* d_vctx, int64_t ctx_capacity_tokens, const skv_tree* tree, const int32_t* d_req_tenant,
+                     const int32_t* d_records, void* d_workspace, size_t workspace_bytes, void* stream);
 
 /* skv_prefill_attn for callers that cannot allocate device memory or hand over a workspace: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, results and errors as

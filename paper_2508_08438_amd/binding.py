@@ -19,7 +19,7 @@ SKV_OK, SKV_EINVAL, SKV_ENOMEM, SKV_ERANGE, SKV_EHIP = 0, -1, -2, -3, -4
 SKV_LIMIT_BRANCH_POINTS, SKV_LIMIT_COPIES, SKV_LIMIT_WALKS = 1, 2, 4
 
 EXPORTS = ["skv_strerror", "skv_last_hip_error", "skv_tree_build_size", "skv_tree_size_for_capacity", "skv_tree_build", "skv_tree_insert", "skv_set_epoch", "skv_block_epochs_read", "skv_evict", "skv_tree_compact", "skv_mfma_rate",
-           "skv_tree_info", "skv_tree_destroy", "skv_match", "skv_match_limits_read", "skv_counters_read",
+           "skv_tree_info", "skv_tree_destroy", "skv_match", "skv_match_window", "skv_match_limits_read", "skv_counters_read",
            "skv_counters_reset", "skv_window_roll", "skv_promote", "skv_block_state_read", "skv_suffix_offsets", "skv_gather_kv",
            "skv_gather_kv_beside",
            "skv_scatter_kv", "skv_stream_copy", "skv_decode_attn_workspace_size", "skv_decode_attn",
@@ -74,6 +74,7 @@ def lib():
         l.skv_tree_destroy.argtypes = [vp]
         l.skv_tree_destroy.restype = None
         l.skv_match.argtypes = [vp, i32, vp, vp, vp, i32, vp, vp, vp, vp]
+        l.skv_match_window.argtypes = [vp, i32, vp, vp, vp, i32, vp, vp, vp, C.POINTER(i32), vp]
         l.skv_counters_read.argtypes = [vp, vp, vp, vp]
         l.skv_counters_reset.argtypes = [vp, vp]
         l.skv_window_roll.argtypes = [vp, C.POINTER(RdrPolicy), vp, vp]
@@ -93,7 +94,7 @@ def lib():
         l.skv_prefill_attn.argtypes = [C.POINTER(AttnDesc), i32, vp, vp, vp, vp, i64, vp, vp, i32, vp, vp,
                                        i32, vp, vp, C.c_size_t, vp]
         l.skv_prefill_step.argtypes = [C.POINTER(AttnDesc), i32, vp, vp, vp, vp, vp, i64, vp, vp, i32, vp, vp, i32, vp, vp, vp, vp,
-                                       i64, vp, C.c_size_t, vp]
+                                       i64, vp, vp, vp, vp, C.c_size_t, vp]
         l.skv_prefill_attn_static.argtypes = [C.POINTER(AttnDesc), i32, vp, vp, vp, vp, i64, vp, vp, i32, vp, vp,
                                               i32, vp, vp]
         l.skv_stream_copy.argtypes = [vp, vp, C.c_size_t, vp]
@@ -265,6 +266,17 @@ def skv_match(tree: Tree, req_off, req_tokens, req_tenant, max_blocks, matched_l
                            _dptr(path_end) if path_end is not None else None, _stream(stream)), "skv_match")
 
 
+def skv_match_window(tree: Tree, req_off, req_tokens, req_tenant, max_blocks, matched_len, page_table, records, stream=None) -> bool:
+    """skv_counters_reset and skv_match; True: the counters of the matched records are left to skv_prefill_step."""
+    n_req, left = req_tenant.numel(), C.c_int32()
+    assert req_off.dtype == req_tokens.dtype == req_tenant.dtype == matched_len.dtype == page_table.dtype == records.dtype == torch.int32
+    assert req_off.numel() == n_req + 1 and matched_len.numel() >= n_req
+    assert page_table.numel() >= n_req * max_blocks and records.numel() >= n_req * max_blocks
+    _check(lib().skv_match_window(tree.handle, n_req, _dptr(req_off), _dptr(req_tokens), _dptr(req_tenant), max_blocks,
+                                  _dptr(matched_len), _dptr(page_table), _dptr(records), C.byref(left), _stream(stream)), "skv_match_window")
+    return left.value != 0
+
+
 def skv_match_limits_read(tree: Tree, clear=True, stream=None) -> int:
     v = C.c_uint32()
     with torch.cuda.device(tree.slab.device):
@@ -358,8 +370,8 @@ def skv_prefill_attn(desc: AttnDesc, q, knew, vnew, q_off, kpool, vpool, matched
 
 
 def skv_prefill_step(desc: AttnDesc, req_off, q, knew, vnew, q_off, kpool, vpool, matched_len, page_table, max_blocks, out,
-                     ctx_off, kctx, vctx, workspace, stream=None):
-    """skv_suffix_offsets, skv_gather_kv and skv_prefill_attn in one call."""
+                     ctx_off, kctx, vctx, workspace, stream=None, tree=None, req_tenant=None, records=None):
+    """skv_suffix_offsets, skv_gather_kv and skv_prefill_attn in one call; records: what skv_match_window left to count."""
     n_req, total, row = matched_len.numel(), q.shape[0], desc.n_kv_heads * desc.head_dim
     assert out.shape == q.shape and knew.shape[0] >= total and vnew.shape[0] >= total
     assert ctx_off.dtype == torch.int64 and ctx_off.numel() == n_req + 1 and req_off.numel() == q_off.numel() == n_req + 1
@@ -367,7 +379,8 @@ def skv_prefill_step(desc: AttnDesc, req_off, q, knew, vnew, q_off, kpool, vpool
     assert vctx.numel() // row >= cap
     _check(lib().skv_prefill_step(C.byref(desc), n_req, _dptr(req_off), _dptr(q), _dptr(knew), _dptr(vnew), _dptr(q_off), total,
                                   _dptr(kpool), _dptr(vpool), kpool.shape[0], _dptr(matched_len), _dptr(page_table), max_blocks,
-                                  _dptr(out), _dptr(ctx_off), _dptr(kctx), _dptr(vctx), cap, _dptr(workspace),
+                                  _dptr(out), _dptr(ctx_off), _dptr(kctx), _dptr(vctx), cap, tree.handle if tree else None,
+                                  _dptr(req_tenant), _dptr(records), _dptr(workspace),
                                   workspace.numel() * workspace.element_size(), _stream(stream)), "skv_prefill_step")
 
 

@@ -1202,14 +1202,17 @@ __device__ __forceinline__ void merge_parts(const AttnParams& p, int n_blocks) {
 
 __global__ __launch_bounds__(kMergeThreads) void attn_merge_kernel(AttnParams p) { merge_parts(p, gridDim.x); }
 // The merge waits for one read behind the other and the copy of a step's pages for the memory: where a step needs both they share
-// a launch (merge_blocks workgroups and the rest), two workgroups to a compute unit.  One request of 137 rows behind 2992 keys
+// a launch (merge_blocks workgroups, n_count for the counters of a request each, and the rest), two workgroups to a compute unit.  One request of 137 rows behind 2992 keys
 // (187 pages): 8.0 + 7.0 us apart, 10.8 together.
-__global__ __launch_bounds__(kMergeThreads, 4) void attn_merge_gather_kernel(AttnParams p, SkvGather g, int merge_blocks) {
+__global__ __launch_bounds__(kMergeThreads, 4) void attn_merge_gather_kernel(AttnParams p, SkvGather g, SkvCount count, int merge_blocks, int n_count) {
   __shared__ int64_t first[kSkvGatherScan + 1];
+  const int others = merge_blocks + n_count;
   if ((int)blockIdx.x < merge_blocks)
     merge_parts(p, merge_blocks);
+  else if ((int)blockIdx.x < others)
+    skv_count_request(count, (int)blockIdx.x - merge_blocks);
   else
-    skv_gather_pages<true, kMergeThreads, 4>(g, (int)blockIdx.x - merge_blocks, (int)gridDim.x - merge_blocks, first);
+    skv_gather_pages<true, kMergeThreads, 4>(g, (int)blockIdx.x - others, (int)gridDim.x - others, first);
 }
 
 // Query heads per workgroup: divides kWaves.  `fine`: eight where the kv head serves a multiple of eight.
@@ -1337,11 +1340,12 @@ static int check_attn_buffers(const void* d_q, const void* d_knew, const void* d
   return SKV_OK;
 }
 
-// What a whole step behind its lookup adds: the suffix offsets, made from req_off, and the gather.
+// What a whole step behind its lookup adds: the suffix offsets, made from req_off, the gather, and counters the lookup left.
 struct StepExtras {
   const int32_t* req_off;
   int32_t* q_off;
   SkvGather gather;
+  SkvCount count;
 };
 
 // Shared by the entry points: enqueues the schedule kernel and the attention kernel on checked arguments.
@@ -1356,7 +1360,7 @@ static int prefill_attn_enqueue(const skv_attn_desc* desc, int32_t n_req, const 
   const bool plan = desc->dtype == SKV_BF16 && plan_in_place(y, n_req);
   const bool late = x && plan && y.max_parts && !x->gather.large;
   if (x && !late) {
-    const int rc = skv_gather_enqueue(x->gather, false, x->req_off, x->q_off, stream);
+    const int rc = skv_gather_enqueue(x->gather, false, x->req_off, x->q_off, x->count, stream);
     if (rc) return rc;
   }
 
@@ -1404,8 +1408,10 @@ static int prefill_attn_enqueue(const skv_attn_desc* desc, int32_t n_req, const 
   SKV_HIP(hipGetLastError());
   if (y.max_parts) {   // a split item has two parts at least
     const int merge_blocks = (int)std::min<int64_t>(y.max_parts / 2 * y.units * kWaves, kMergeGrid);
+    const int n_count = late && x->count.records ? n_req : 0;
     if (late)
-      attn_merge_gather_kernel<<<merge_blocks + skv_gather_blocks(x->gather), kMergeThreads, 0, st>>>(p, x->gather, merge_blocks);
+      attn_merge_gather_kernel<<<merge_blocks + n_count + skv_gather_blocks(x->gather), kMergeThreads, 0, st>>>(p, x->gather, x->count,
+                                                                                                               merge_blocks, n_count);
     else
       attn_merge_kernel<<<merge_blocks, kMergeThreads, 0, st>>>(p);
     SKV_HIP(hipGetLastError());
@@ -1455,19 +1461,24 @@ extern "C" int skv_prefill_step(const skv_attn_desc* desc, int32_t n_req, const 
                                 const void* d_knew, const void* d_vnew, int32_t* d_q_off, int64_t total_q_rows,
                                 const void* d_kpool, const void* d_vpool, int32_t n_pages, const int32_t* d_matched_len,
                                 const int32_t* d_page_table, int32_t max_blocks, void* d_out, int64_t* d_ctx_off, void* d_kctx,
-                                void* d_vctx, int64_t ctx_capacity_tokens, void* d_workspace, size_t workspace_bytes,
-                                void* stream) {
-  StepExtras x = {d_req_off, d_q_off, {}};
+                                void* d_vctx, int64_t ctx_capacity_tokens, const skv_tree* tree, const int32_t* d_req_tenant,
+                                const int32_t* d_records, void* d_workspace, size_t workspace_bytes, void* stream) {
   if (n_req < 0 || !d_q_off || (n_req > 0 && (!d_req_off || !d_matched_len))) return SKV_EINVAL;
+  if (d_records && (!tree || !d_req_tenant || max_blocks < 0)) return SKV_EINVAL;
+  StepExtras x = {d_req_off, d_q_off, {}, {}};
+  if (d_records) x.count = {tree->dev.ctr, tree->dev.ctr_plane, d_records, d_req_tenant, d_matched_len, max_blocks, n_req};
   int rc = skv_gather_check(desc, n_req, d_kpool, d_vpool, n_pages, d_matched_len, d_page_table, max_blocks, d_ctx_off, d_kctx, d_vctx,
                             ctx_capacity_tokens, &x.gather);
-  if (rc) return rc;
+  if (rc) {   // (the lookup has happened: its counters are not lost)
+    const int rn = skv_count_enqueue(x.count, stream);
+    return rn ? rn : rc;
+  }
   Layout y;
   bool empty = false;
   rc = prefill_attn_check(desc, n_req, d_q, d_knew, d_vnew, d_q_off, total_q_rows, d_kpool, d_vpool, n_pages, d_matched_len,
                           d_page_table, max_blocks, d_out, d_workspace, workspace_bytes, y, empty);
   if (rc || empty) {   // what does not depend on the attention happens all the same
-    const int rg = skv_gather_enqueue(x.gather, false, d_req_off, d_q_off, stream);
+    const int rg = skv_gather_enqueue(x.gather, false, d_req_off, d_q_off, x.count, stream);
     return rg ? rg : rc;
   }
   return prefill_attn_enqueue(desc, n_req, d_q, d_knew, d_vnew, d_q_off, total_q_rows, d_kpool, d_vpool, n_pages,

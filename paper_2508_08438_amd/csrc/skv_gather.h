@@ -20,14 +20,35 @@ struct SkvGather {
 };
 constexpr int kSkvGatherScan = 512;   // requests up to which every workgroup scans the matched lengths itself
 
-// Arguments checked and laid out; workgroups of a call; the call.  d_q_off: the suffix offsets are written too.
+// Counter updates that a lookup left for a later kernel (skv_match_window): those of the matched blocks' records.
+struct SkvCount {
+  uint32_t* ctr;
+  size_t ctr_plane;
+  const int32_t *records, *req_tenant, *matched_len;   // records null: nothing is left
+  int max_blocks, n_req;
+};
+
+// Arguments checked and laid out; workgroups of a call; the call.  d_q_off: the suffix offsets are written too; count: and those counters.
 int skv_gather_check(const skv_attn_desc* desc, int32_t n_req, const void* d_kpool, const void* d_vpool, int32_t n_pages,
                      const int32_t* d_matched_len, const int32_t* d_page_table, int32_t max_blocks, int64_t* d_ctx_off, void* d_kctx,
                      void* d_vctx, int64_t ctx_capacity_tokens, SkvGather* g);
 int skv_gather_blocks(const SkvGather& g);
-int skv_gather_enqueue(const SkvGather& g, bool beside, const int32_t* d_req_off, int32_t* d_q_off, void* stream);
+int skv_gather_enqueue(const SkvGather& g, bool beside, const int32_t* d_req_off, int32_t* d_q_off, const SkvCount& count, void* stream);
+int skv_count_enqueue(const SkvCount& count, void* stream);
 
 #ifdef __HIPCC__
+// Request r's: a workgroup.
+__device__ __forceinline__ void skv_count_request(const SkvCount& c, int r) {
+  const int n = min(max(c.matched_len[r], 0) / SKV_BLOCK_TOKENS, c.max_blocks), tenant = c.req_tenant[r];
+  if (n <= 0) return;   // (only a tenant of the tree has matched anything)
+  uint32_t* const tenants = c.ctr + (size_t)(1 + (tenant >> 5)) * c.ctr_plane;
+  for (int i = threadIdx.x; i < n; i += blockDim.x) {
+    const int blk = c.records[(size_t)r * c.max_blocks + i];
+    atomicAdd(c.ctr + blk, 1u);
+    atomicOr(tenants + blk, 1u << (tenant & 31));
+  }
+}
+
 // What workgroup `block` of n_blocks copies (n_blocks is a multiple of the slices): it loops over the global list of matched pages, each
 // moving as 16-byte vectors with all loads of a step issued before its stores.  kScan: the workgroup scans the matched lengths
 // itself (the first one also writes the offsets) and finds the owner of a page in `first`, kSkvGatherScan + 1 places in LDS.

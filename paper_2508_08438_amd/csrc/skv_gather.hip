@@ -39,9 +39,10 @@ __global__ __launch_bounds__(kOffThreads) void ctx_offsets_kernel(int n_req, con
 // each of 16 / 256 / 512 requests 14.0 / 19.4 / 23.5 us scanned, 16.6 / 22.0 / 24.4 with that kernel; of 1024 / 4096 / 16384 33.6 /
 // 158 / 685 scanned, 33.7 / 113 / 432 with it; 40 pages each of 1024 1053 and 1044.
 // kOffsets: the first workgroup writes the suffix offsets instead (skv_suffix_offsets of up to kSkvGatherScan requests), which
-// neither reads nor delays a page: one launch less in a step.
+// neither reads nor delays a page: one launch less in a step.  n_count workgroups behind it update the counters of a request each.
 template <bool kScan, bool kOffsets>
-__global__ __launch_bounds__(kThreads) void gather_pages_kernel(SkvGather g, const int32_t* __restrict__ req_off, int32_t* __restrict__ q_off) {
+__global__ __launch_bounds__(kThreads) void gather_pages_kernel(SkvGather g, const int32_t* __restrict__ req_off, int32_t* __restrict__ q_off,
+                                                                SkvCount count, int n_count) {
   if constexpr (kOffsets) {
     if (blockIdx.x == 0) {
       __shared__ int red[kThreads / 64];
@@ -59,10 +60,14 @@ __global__ __launch_bounds__(kThreads) void gather_pages_kernel(SkvGather g, con
       }
       return;
     }
+    if ((int)blockIdx.x <= n_count) return skv_count_request(count, (int)blockIdx.x - 1);
   }
   __shared__ int64_t first[kScan ? kSkvGatherScan + 1 : 1];
-  skv_gather_pages<kScan, kThreads, kUnroll>(g, (int)blockIdx.x - kOffsets, (int)gridDim.x - kOffsets, first);
+  const int others = kOffsets ? 1 + n_count : 0;
+  skv_gather_pages<kScan, kThreads, kUnroll>(g, (int)blockIdx.x - others, (int)gridDim.x - others, first);
 }
+
+__global__ __launch_bounds__(kThreads) void count_matched_kernel(SkvCount count) { skv_count_request(count, blockIdx.x); }
 
 // The same copy for a call that runs beside a kernel which holds most of the chip's registers (prefill attention: 240 of a
 // SIMD's 512 for each of two wavefronts): one workgroup per compute unit with one wavefront per SIMD in the 32 registers that
@@ -265,36 +270,37 @@ int skv_gather_blocks(const SkvGather& g) {
   return (int)(upper < 1 ? 1 : (upper < 256 * 16 ? upper : 256 * 16)) * g.slices;
 }
 
-int skv_gather_enqueue(const SkvGather& g, bool beside, const int32_t* d_req_off, int32_t* d_q_off, void* stream) {
+int skv_count_enqueue(const SkvCount& count, void* stream) {
+  if (!count.records || count.n_req == 0) return SKV_OK;
+  count_matched_kernel<<<count.n_req, kThreads, 0, (hipStream_t)stream>>>(count);
+  SKV_HIP(hipGetLastError());
+  return SKV_OK;
+}
+
+int skv_gather_enqueue(const SkvGather& g, bool beside, const int32_t* d_req_off, int32_t* d_q_off, const SkvCount& count, void* stream) {
   hipStream_t st = (hipStream_t)stream;
-  const bool scan = g.n_req <= kPref;
-  if (scan && (beside || g.large) && (int64_t)g.page_vec * 16 <= 0x7fffffff) {
-    if (d_q_off) {
-      const int rc = skv_suffix_offsets(g.n_req, d_req_off, g.matched_len, d_q_off, stream);
-      if (rc) return rc;
-    }
+  const bool scan = g.n_req <= kPref, large = scan && (beside || g.large) && (int64_t)g.page_vec * 16 <= 0x7fffffff;
+  if (scan && !large && d_q_off) {
+    const int n_count = count.records ? g.n_req : 0;
+    gather_pages_kernel<true, true><<<1 + n_count + skv_gather_blocks(g), kThreads, 0, st>>>(g, d_req_off, d_q_off, count, n_count);
+    SKV_HIP(hipGetLastError());
+    return SKV_OK;
+  }
+  int rc = d_q_off ? skv_suffix_offsets(g.n_req, d_req_off, g.matched_len, d_q_off, stream) : SKV_OK;
+  if (rc == SKV_OK) rc = skv_count_enqueue(count, stream);
+  if (rc) return rc;
+  if (large) {
     gather_beside_kernel<<<kBesideGrid, kThreads, 0, st>>>(
         g.n_req, (const char*)g.kpool, (const char*)g.vpool, g.n_pages, g.matched_len, g.page_table, g.max_blocks, g.ctx_off,
         (char*)g.kctx, (char*)g.vctx, g.cap_pages, g.page_vec * 16);
+  } else if (scan) {
+    gather_pages_kernel<true, false><<<skv_gather_blocks(g), kThreads, 0, st>>>(g, nullptr, nullptr, count, 0);
+  } else {
+    ctx_offsets_kernel<<<1, kOffThreads, 0, st>>>(g.n_req, g.matched_len, g.ctx_off);
     SKV_HIP(hipGetLastError());
-    return SKV_OK;
+    if (g.max_blocks == 0) return SKV_OK;
+    gather_pages_kernel<false, false><<<skv_gather_blocks(g), kThreads, 0, st>>>(g, nullptr, nullptr, count, 0);
   }
-  if (scan) {
-    if (d_q_off)
-      gather_pages_kernel<true, true><<<skv_gather_blocks(g) + 1, kThreads, 0, st>>>(g, d_req_off, d_q_off);
-    else
-      gather_pages_kernel<true, false><<<skv_gather_blocks(g), kThreads, 0, st>>>(g, nullptr, nullptr);
-    SKV_HIP(hipGetLastError());
-    return SKV_OK;
-  }
-  if (d_q_off) {
-    const int rc = skv_suffix_offsets(g.n_req, d_req_off, g.matched_len, d_q_off, stream);
-    if (rc) return rc;
-  }
-  ctx_offsets_kernel<<<1, kOffThreads, 0, st>>>(g.n_req, g.matched_len, g.ctx_off);
-  SKV_HIP(hipGetLastError());
-  if (g.max_blocks == 0) return SKV_OK;
-  gather_pages_kernel<false, false><<<skv_gather_blocks(g), kThreads, 0, st>>>(g, nullptr, nullptr);
   SKV_HIP(hipGetLastError());
   return SKV_OK;
 }
@@ -305,7 +311,7 @@ static int gather_call(const skv_attn_desc* desc, int32_t n_req, const void* d_k
   SkvGather g;
   const int rc = skv_gather_check(desc, n_req, d_kpool, d_vpool, n_pages, d_matched_len, d_page_table, max_blocks, d_ctx_off, d_kctx,
                                   d_vctx, ctx_capacity_tokens, &g);
-  return rc ? rc : skv_gather_enqueue(g, beside, nullptr, nullptr, stream);
+  return rc ? rc : skv_gather_enqueue(g, beside, nullptr, nullptr, SkvCount{}, stream);
 }
 
 extern "C" int skv_gather_kv(const skv_attn_desc* desc, int32_t n_req, const void* d_kpool, const void* d_vpool,

@@ -12,6 +12,8 @@
 // not see; the smaller of the two ends the walk.  The lanes of the matched blocks then copy
 // the page ids and issue the counter atomics.  The four wavefronts of a workgroup take
 // disjoint parts of a long node's span and combine their stop positions through LDS.
+#include <algorithm>
+
 #include "skv_internal.h"
 
 namespace {
@@ -82,11 +84,22 @@ __device__ inline int find_child(const SkvTreeDev& t, const SkvNode nd, const in
 // wavefront, whose first mismatch or invisible block is combined through LDS into the round's stop position.  Each
 // wavefront then records (page ids, counters, epochs) the blocks of its own group that lie before that position.
 // Every branch around a barrier depends only on values that are equal in all four wavefronts.
-template <int kCoop>
+// kWindow: the lookup opens a monitoring window.  Clearing the counters was a launch in front; here the workgroups behind the
+// requests' clear them, and since those may be later than a walk the matched blocks' records are kept, for a kernel that follows
+// anyway to count (skv_prefill_step).  us a pass of a step: one request behind 2992 keys 39.1 -> 36.8, eight fp32 requests 31.2 -> 29.8.
+template <int kCoop, bool kWindow = false>
 __global__ __launch_bounds__(kWave* kWavesPerWg) void skv_match_kernel(
     SkvTreeDev t, int n_req, const int32_t* __restrict__ req_off, const int32_t* __restrict__ req_tok,
     const int32_t* __restrict__ req_tenant, int max_blocks, int32_t* __restrict__ matched_len,
-    int32_t* __restrict__ page_table, int32_t* __restrict__ path_end) {
+    int32_t* __restrict__ page_table, int32_t* __restrict__ path_end, int32_t* __restrict__ records) {
+  if (kWindow && (int)blockIdx.x >= n_req) {
+    const int stride = ((int)gridDim.x - n_req) * (int)blockDim.x;
+    for (int b = ((int)blockIdx.x - n_req) * (int)blockDim.x + (int)threadIdx.x; b < t.n_blocks; b += stride) {
+#pragma unroll
+      for (int k = 0; k <= 4; ++k) t.ctr[k * t.ctr_plane + b] = 0;
+    }
+    return;
+  }
   __shared__ int stop_at[2][kWavesPerWg];   // per round parity and wavefront: blocks of the node matched before its stop
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = kCoop > 1 ? uniform(threadIdx.x >> 6) : 0;   // wavefront within the request's team
@@ -207,8 +220,12 @@ __global__ __launch_bounds__(kWave* kWavesPerWg) void skv_match_kernel(
         if (c + lane < g0 + mine) {
           const int blk = first + c + lane;
           row[jn + c + lane] = pg[s];
-          atomicAdd(t.ctr + blk, 1u);
-          atomicOr(tenants + blk, tbit);
+          if constexpr (kWindow) {
+            records[(size_t)r * max_blocks + jn + c + lane] = blk;
+          } else {
+            atomicAdd(t.ctr + blk, 1u);
+            atomicOr(tenants + blk, tbit);
+          }
           t.epoch[blk] = t.cur_epoch;  // every lookup of one batch writes the same value
         }
       }
@@ -450,11 +467,31 @@ extern "C" int skv_match(skv_tree* t, int32_t n_req, const int32_t* d_req_off,
         t->dev, n_req, d_req_off, d_req_tokens, d_req_tenant, max_blocks, d_matched_len, d_page_table, d_path_end);
   else if (n_req <= kCoopMaxRequests)   // few requests: a workgroup each
     skv_match_kernel<kWavesPerWg><<<n_req, kWave * kWavesPerWg, 0, (hipStream_t)stream>>>(
-        t->dev, n_req, d_req_off, d_req_tokens, d_req_tenant, max_blocks, d_matched_len, d_page_table, d_path_end);
+        t->dev, n_req, d_req_off, d_req_tokens, d_req_tenant, max_blocks, d_matched_len, d_page_table, d_path_end,
+        nullptr);
   else
     skv_match_kernel<1><<<grid, kWave * kWavesPerWg, 0, (hipStream_t)stream>>>(
-        t->dev, n_req, d_req_off, d_req_tokens, d_req_tenant, max_blocks, d_matched_len, d_page_table, d_path_end);
+        t->dev, n_req, d_req_off, d_req_tokens, d_req_tenant, max_blocks, d_matched_len, d_page_table, d_path_end,
+        nullptr);
   SKV_HIP(hipGetLastError());
+  return SKV_OK;
+}
+
+extern "C" int skv_match_window(skv_tree* t, int32_t n_req, const int32_t* d_req_off, const int32_t* d_req_tokens,
+                                const int32_t* d_req_tenant, int32_t max_blocks, int32_t* d_matched_len, int32_t* d_page_table,
+                                int32_t* d_records, int32_t* left, void* stream) {
+  if (!t || !left || n_req < 0 || max_blocks < 0) return SKV_EINVAL;
+  *left = 0;
+  if (n_req == 0 || n_req > kCoopMaxRequests || max_blocks == 0 || t->has_copies || t->dev.n_blocks == 0 || !d_records) {
+    const int rc = skv_counters_reset(t, stream);
+    return rc ? rc : skv_match(t, n_req, d_req_off, d_req_tokens, d_req_tenant, max_blocks, d_matched_len, d_page_table, nullptr, stream);
+  }
+  if (!d_req_off || !d_req_tokens || !d_req_tenant || !d_matched_len || !d_page_table) return SKV_EINVAL;
+  const int clear = std::min((t->dev.n_blocks + kWave * kWavesPerWg - 1) / (kWave * kWavesPerWg), 4096);
+  skv_match_kernel<kWavesPerWg, true><<<n_req + clear, kWave * kWavesPerWg, 0, (hipStream_t)stream>>>(
+      t->dev, n_req, d_req_off, d_req_tokens, d_req_tenant, max_blocks, d_matched_len, d_page_table, nullptr, d_records);
+  SKV_HIP(hipGetLastError());
+  *left = 1;
   return SKV_OK;
 }
 

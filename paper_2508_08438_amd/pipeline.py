@@ -105,6 +105,7 @@ class Session:
             self.out = torch.zeros_like(self.q)
             self.kctx = torch.zeros((n_ctx, a.n_kv_heads, a.head_dim), dtype=a.torch_dtype, device=dev)
             self.vctx = torch.zeros_like(self.kctx)
+        self.records = torch.empty_like(self.page_table)     # of the matched blocks, between the kernels of a step
         nbytes = skv.skv_prefill_attn_workspace_size(self.desc, w.n_req, self.q.shape[0])
         self.workspace = torch.empty(nbytes, dtype=torch.uint8, device=dev)
         copied = 2 * self.kctx.numel() * self.kctx.element_size()
@@ -113,13 +114,10 @@ class Session:
         skv.skv_counters_reset(self.tree)
 
     # -- the individual stages (each only enqueues on the current stream)
-    def lookup(self):
+    def match(self):
         skv.skv_counters_reset(self.tree)
         skv.skv_match(self.tree, self.req_off, self.req_tokens, self.req_tenant, self.max_blocks,
                       self.matched_len, self.page_table)
-
-    def match(self):
-        self.lookup()
         skv.skv_suffix_offsets(self.req_off, self.matched_len, self.q_off)
 
     def gather(self, stream=None, beside=False):
@@ -133,17 +131,18 @@ class Session:
     def _pass(self):
         """Gather and attention both read the match's results and neither the other's: a large copy runs on a stream of its own
         beside the attention (the current stream waits for it before this returns, also where attention() raises); what is
-        smaller, and the suffix offsets, share the attention's call."""
-        self.lookup()
-        if not self.do_gather:
-            skv.skv_suffix_offsets(self.req_off, self.matched_len, self.q_off)
-            return self.attention()
+        smaller, the suffix offsets and the counters of the lookup share the attention's call."""
         main = torch.cuda.current_stream() if self.side else None
-        if main is None or main.device != self.side.device:
+        if self.do_gather and (main is None or main.device != self.side.device):
+            left = skv.skv_match_window(self.tree, self.req_off, self.req_tokens, self.req_tenant, self.max_blocks, self.matched_len,
+                                        self.page_table, self.records)
             return skv.skv_prefill_step(self.desc, self.req_off, self.q, self.knew, self.vnew, self.q_off, self.kpool, self.vpool,
                                         self.matched_len, self.page_table, self.max_blocks, self.out, self.ctx_off, self.kctx,
-                                        self.vctx, self.workspace)
-        skv.skv_suffix_offsets(self.req_off, self.matched_len, self.q_off)
+                                        self.vctx, self.workspace, tree=self.tree, req_tenant=self.req_tenant,
+                                        records=self.records if left else None)
+        self.match()
+        if not self.do_gather:
+            return self.attention()
         side = self.side_capture if torch.cuda.is_current_stream_capturing() else self.side
         matched = main.record_event()
         try:

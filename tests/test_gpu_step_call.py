@@ -97,3 +97,33 @@ def test_matched_beyond_the_request_and_short_staging():
     _stages(desc, c, ws, want)
     _step(desc, c, ws, got)
     _same(want, got)
+
+
+# counters cleared beside the lookup and updated behind it: 512 requests and 513, which have a launch for each; a split call and fp32
+@pytest.mark.parametrize("n_req,dtype,hq,hkv,d", [(1, "bf16", 8, 2, 128), (12, "bf16", 8, 1, 128), (40, "f32", 4, 2, 64), (512, "bf16", 4, 1, 128),
+                                                   (513, "bf16", 4, 1, 128)])
+def test_counters_of_a_step(n_req, dtype, hq, hkv, d):
+    from paper_2508_08438_amd import inputs, pipeline
+    w = inputs.small_random(seed=n_req + 5, n_seq=8, max_blocks=24, n_req=n_req, vocab=50, n_tenants=100, attn=inputs.AttnShape(hq, hkv, d, dtype))
+    s = pipeline.Session(w)
+    s.match()
+    want = s.counters()
+    assert want[0].sum() > 0
+    state = [x.cpu().clone() for x in (s.matched_len, s.page_table, s.q_off)]
+
+    def check():
+        assert all(np.array_equal(a, b) for a, b in zip(want, s.counters()))
+        assert all(torch.equal(a, b.cpu()) for a, b in zip(state, (s.matched_len, s.page_table, s.q_off)))
+    for _ in range(2):
+        s.step()
+        check()
+    s.capture_step()
+    for _ in range(3):
+        s.replay()
+        check()
+        s.step()
+        check()
+    s.workspace = s.workspace[:64]      # an attention that is refused has counted all the same
+    with pytest.raises(skv.SkvError):
+        s.step()
+    check()
