@@ -4,6 +4,8 @@
 // read directly from its address vector.  Here the address vector is the page table written by
 // the match; a page is one contiguous chunk of 16 * n_kv_heads * head_dim elements, so the
 // gather is a batch of page-sized copies chosen by the table (the copy itself: skv_gather_pages).
+#include <algorithm>
+
 #include "skv_gather.h"
 
 namespace {
@@ -258,15 +260,16 @@ int skv_gather_check(const skv_attn_desc* desc, int32_t n_req, const void* d_kpo
   if (n_req > 0 && (!d_matched_len || !d_kpool || !d_vpool || !d_kctx || !d_vctx)) return SKV_EINVAL;
   if (n_req > 0 && max_blocks > 0 && !d_page_table) return SKV_EINVAL;
   if (((uintptr_t)d_kpool | (uintptr_t)d_vpool | (uintptr_t)d_kctx | (uintptr_t)d_vctx) & 15) return SKV_EINVAL;
-  const int64_t upper = (int64_t)n_req * max_blocks;  // pages the batch can reference at most
+  // pages the batch can move at most: what the table holds and, often far less (private blocks end a match early), what the staging does
+  const int64_t upper = std::min((int64_t)n_req * max_blocks, ctx_capacity_tokens / SKV_BLOCK_TOKENS);
   *g = {n_req, (const u32x4*)d_kpool, (const u32x4*)d_vpool, n_pages, d_matched_len, d_page_table, max_blocks, d_ctx_off,
-        (u32x4*)d_kctx, (u32x4*)d_vctx, upper ? ctx_capacity_tokens / SKV_BLOCK_TOKENS : 0, (int)(page_bytes / 16), slices_for(upper),
+        (u32x4*)d_kctx, (u32x4*)d_vctx, n_req && max_blocks ? ctx_capacity_tokens / SKV_BLOCK_TOKENS : 0, (int)(page_bytes / 16), slices_for(upper),
         n_req <= kPref && page_bytes <= 0x7fffffff && large_copy(upper, page_bytes)};
   return SKV_OK;
 }
 
 int skv_gather_blocks(const SkvGather& g) {
-  const int64_t upper = (int64_t)g.n_req * g.max_blocks;
+  const int64_t upper = std::min((int64_t)g.n_req * g.max_blocks, g.cap_pages);
   return (int)(upper < 1 ? 1 : (upper < 256 * 16 ? upper : 256 * 16)) * g.slices;
 }
 
