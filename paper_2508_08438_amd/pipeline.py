@@ -22,9 +22,10 @@ def _tiled_from_host(chunk: torch.Tensor, n_rows: int, device) -> torch.Tensor:
 
 
 # K and V bytes from which a step copies them on a stream of its own beside the attention.  The two queues' waits cost about
-# 15 us and attention slows by a third of the copy's time: us a pass, beside / one after the other: 98 MB behind one request
-# of 257 rows 271 / 279; 205 MB, 16 requests, 488 / 541; 3.3 GB, 32 requests, 6960 / 7690; 12 MB, one request, 102 / 52.
-GATHER_BESIDE_BYTES = 64 << 20
+# 15 us, attention slows by a third of the copy's time, and offsets and counters take launches of their own again: us a pass, beside /
+# in one call: 12 MB behind one request 59 / 37.5; 79 MB, 24 requests, 321 / 320; 98 MB, one of 257 rows, 252 / 241; 205 MB, 16
+# requests, 487 / 523; 3.3 GB, 32 requests, 6865 / 7524.
+GATHER_BESIDE_BYTES = 128 << 20
 
 # One stream per device for these copies, whatever the number of sessions: streams are dealt to four hardware queues, and a copy on
 # the queue of the attention's own stream runs behind it (24 requests behind 1700 keys, on nine streams one after the other: 260
