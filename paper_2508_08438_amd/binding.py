@@ -7,6 +7,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import sys
 
 import numpy as np
 import torch
@@ -101,6 +102,8 @@ def lib():
         l.skv_tree_compact.argtypes = [vp, vp, C.POINTER(i64), vp]
         l.skv_mfma_rate.argtypes = [vp, C.c_size_t, i32, i32, vp, C.c_size_t, C.POINTER(C.c_double), vp]
         l.skv_match_limits_read.argtypes = [vp, C.POINTER(C.c_uint32), i32, vp]
+        l.hipStreamCreateWithFlags.argtypes = [C.POINTER(vp), C.c_uint]   # (of the HIP runtime the library is linked with)
+        l.hipStreamDestroy.argtypes = [vp]
         _lib = l
     return _lib
 
@@ -121,6 +124,28 @@ def _stream(stream):
     """The current one by its handle: a stream object is 1.5 us of a call.  (A tensor or tree on the device is at hand, so
     torch has initialised it.)"""
     return _current_raw_stream(_current_device()) if stream is None else stream.cuda_stream
+
+
+def _stream_destroy(handle):
+    lib().hipStreamDestroy(handle)
+
+
+class OwnStream(torch.cuda.ExternalStream):
+    """A stream that nobody else is given, destroyed with this object.  torch.cuda.Stream deals out the same 32 of a device over and over, so
+    two of its holders may share one -- and what one launches on it becomes part of a capture the other has begun.  (__del__ and
+    no weakref.finalize: torch's stream objects die without clearing their weak references.)"""
+
+    def __new__(cls, device):
+        h = C.c_void_p()
+        with torch.cuda.device(device):
+            e = lib().hipStreamCreateWithFlags(C.byref(h), 1)      # non-blocking, default priority: as torch's
+        if e:
+            raise RuntimeError(f"hipStreamCreateWithFlags: hipError {e}")
+        return super().__new__(cls, h.value, device=device)
+
+    def __del__(self):
+        if not sys.is_finalizing():
+            _stream_destroy(self.cuda_stream)
 
 
 def attn_desc(n_q_heads, n_kv_heads, head_dim, dtype, scale=None) -> AttnDesc:

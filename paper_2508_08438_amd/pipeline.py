@@ -29,7 +29,7 @@ GATHER_BESIDE_BYTES = 128 << 20
 
 # One stream per device for these copies, whatever the number of sessions: streams are dealt to four hardware queues, and a copy on
 # the queue of the attention's own stream runs behind it (24 requests behind 1700 keys, on nine streams one after the other: 260
-# to 264 us, on the sixth 296).  A capture takes a stream of the session's own, which no other thread can be using.
+# to 264 us, on the sixth 296).  A capture takes a stream of the session's own.  Neither is of torch's pool (binding.OwnStream).
 _copy_streams = {}
 _copy_lock = threading.Lock()
 
@@ -37,7 +37,7 @@ _copy_lock = threading.Lock()
 def _copy_stream(device):
     with _copy_lock:
         if device not in _copy_streams:
-            _copy_streams[device] = torch.cuda.Stream(device)
+            _copy_streams[device] = skv.OwnStream(device)
             _copy_streams[device].record_event()      # its queue is there before the first pass
         return _copy_streams[device]
 
@@ -111,7 +111,7 @@ class Session:
         self.workspace = torch.empty(nbytes, dtype=torch.uint8, device=dev)
         copied = 2 * self.kctx.numel() * self.kctx.element_size()
         if self.do_gather and a.dtype == "bf16" and copied >= GATHER_BESIDE_BYTES:   # (fp32 attention leaves no registers)
-            self.side, self.side_capture = _copy_stream(self.q.device), torch.cuda.Stream(dev)
+            self.side, self.side_capture = _copy_stream(self.q.device), skv.OwnStream(dev)
         skv.skv_counters_reset(self.tree)
 
     # -- the individual stages (each only enqueues on the current stream)
