@@ -370,9 +370,10 @@ int skv_prefill_attn(const skv_attn_desc* desc, int32_t n_req, const void* d_q, 
 
 /* Everything of a step behind its lookup in one call: skv_suffix_offsets (d_q_off is written), skv_gather_kv and
  * skv_prefill_attn, with the results and errors of the three.  An error of the attention's arguments leaves the other two done,
- * as when they are called in front of it.  d_records, where not NULL: what skv_match_window left to count, with its tree, tenants and
- * matched lengths (the tree unchanged since); it is counted in any case.  Fewer launches than the three: small batches make the offsets in another kernel's first steps and
- * copy their pages beside the merge of split items. */
+ * as when they are called in front of it.  d_records, where not NULL: what skv_match_window left to count, with its tree, tenants,
+ * matched lengths, n_req and max_blocks (the tree unchanged since); it is counted also where an error of the other arguments is returned
+ * (not on SKV_EHIP).  Fewer launches than the three: small batches make the offsets in another kernel's first steps and copy their
+ * pages beside the merge of split items. */
 int skv_prefill_step(const skv_attn_desc* desc, int32_t n_req, const int32_t* d_req_off, const void* d_q,
                      const void* d_knew, const void* d_vnew, int32_t* d_q_off, int64_t total_q_rows,
                      const void* d_kpool, const void* d_vpool, int32_t n_pages, const int32_t* d_matched_len,

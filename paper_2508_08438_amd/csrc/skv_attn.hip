@@ -1463,12 +1463,15 @@ extern "C" int skv_prefill_step(const skv_attn_desc* desc, int32_t n_req, const 
                                 const int32_t* d_page_table, int32_t max_blocks, void* d_out, int64_t* d_ctx_off, void* d_kctx,
                                 void* d_vctx, int64_t ctx_capacity_tokens, const skv_tree* tree, const int32_t* d_req_tenant,
                                 const int32_t* d_records, void* d_workspace, size_t workspace_bytes, void* stream) {
-  if (n_req < 0 || !d_q_off || (n_req > 0 && (!d_req_off || !d_matched_len))) return SKV_EINVAL;
-  if (d_records && (!tree || !d_req_tenant || max_blocks < 0)) return SKV_EINVAL;
   StepExtras x = {d_req_off, d_q_off, {}, {}};
-  if (d_records) x.count = {tree->dev.ctr, tree->dev.ctr_plane, d_records, d_req_tenant, d_matched_len, max_blocks, n_req};
-  int rc = skv_gather_check(desc, n_req, d_kpool, d_vpool, n_pages, d_matched_len, d_page_table, max_blocks, d_ctx_off, d_kctx, d_vctx,
-                            ctx_capacity_tokens, &x.gather);
+  if (d_records) {
+    if (!tree || !d_req_tenant || n_req < 0 || max_blocks < 0 || (n_req > 0 && !d_matched_len)) return SKV_EINVAL;   // nothing to count by
+    x.count = {tree->dev.ctr, tree->dev.ctr_plane, d_records, d_req_tenant, d_matched_len, max_blocks, n_req};
+  }
+  int rc = SKV_EINVAL;
+  if (n_req >= 0 && d_q_off && (n_req == 0 || (d_req_off && d_matched_len)))
+    rc = skv_gather_check(desc, n_req, d_kpool, d_vpool, n_pages, d_matched_len, d_page_table, max_blocks, d_ctx_off, d_kctx, d_vctx,
+                          ctx_capacity_tokens, &x.gather);
   if (rc) {   // (the lookup has happened: its counters are not lost)
     const int rn = skv_count_enqueue(x.count, stream);
     return rn ? rn : rc;
