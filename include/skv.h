@@ -370,7 +370,7 @@ int skv_prefill_attn(const skv_attn_desc* desc, int32_t n_req, const void* d_q, 
 
 /* Everything of a step behind its lookup in one call: skv_suffix_offsets (d_q_off is written), skv_gather_kv and
  * skv_prefill_attn, with the results and errors of the three.  An error of the attention's arguments leaves the other two done,
- * as when they are called in front of it.  d_records, where not NULL: what skv_match_window left to count, with its tree, tenants,
+ * as when they are called in front of it; one of theirs leaves all three undone.  d_records, where not NULL: what skv_match_window left to count, with its tree, tenants,
  * matched lengths, n_req and max_blocks (the tree unchanged since); it is counted also where an error of the other arguments is returned
  * (not on SKV_EHIP).  Fewer launches than the three: small batches make the offsets in another kernel's first steps and copy their
  * pages beside the merge of split items. */
