@@ -400,6 +400,10 @@ def skv_prefill_step(desc: AttnDesc, req_off, q, knew, vnew, q_off, kpool, vpool
     n_req, total, row = matched_len.numel(), q.shape[0], desc.n_kv_heads * desc.head_dim
     assert out.shape == q.shape and knew.shape[0] >= total and vnew.shape[0] >= total
     assert ctx_off.dtype == torch.int64 and ctx_off.numel() == n_req + 1 and req_off.numel() == q_off.numel() == n_req + 1
+    assert req_off.dtype == q_off.dtype == matched_len.dtype == page_table.dtype == torch.int32 and page_table.numel() >= n_req * max_blocks
+    if records is not None:      # record numbers and tenants become addresses
+        assert tree is not None and records.dtype == req_tenant.dtype == torch.int32
+        assert records.numel() >= n_req * max_blocks and req_tenant.numel() >= n_req
     cap = kctx.numel() // row
     assert vctx.numel() // row >= cap
     _check(lib().skv_prefill_step(C.byref(desc), n_req, _dptr(req_off), _dptr(q), _dptr(knew), _dptr(vnew), _dptr(q_off), total,
