@@ -27,8 +27,9 @@ EXPORTS = ["skv_strerror", "skv_last_hip_error", "skv_tree_build_size", "skv_tre
            "skv_prefill_attn_workspace_size", "skv_prefill_attn", "skv_prefill_step", "skv_prefill_attn_static"]
 
 
-_current_raw_stream = torch._C._cuda_getCurrentRawStream
-_current_device = torch._C._cuda_getDevice
+# (not part of torch's interface, and absent from a torch without GPU support)
+_current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
 
 
 class SkvError(RuntimeError):
@@ -123,7 +124,11 @@ def _dptr(t):
 def _stream(stream):
     """The current one by its handle: a stream object is 1.5 us of a call.  (A tensor or tree on the device is at hand, so
     torch has initialised it.)"""
-    return _current_raw_stream(_current_device()) if stream is None else stream.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if _current_raw_stream is None or _current_device is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _current_raw_stream(_current_device())
 
 
 def _stream_destroy(handle):
