@@ -743,7 +743,8 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
   // the buffer: what lies behind arrives as zeros, and the causal mask keeps it out.
   auto issue_half_tile = [&]<bool kWhole>(uint64_t base, int t, __bf16* dst_stage) __attribute__((always_inline)) {
     __bf16* const dst = dst_stage + 2 * wave * kSeg;
-    const int rows = kWhole ? 16 : max(0, min(16, Ltot - (t * kBN + group * 16)));
+    // (the compiler clamps in vector registers, and a descriptor that is not scalar costs a loop around each load)
+    const int rows = kWhole ? 16 : __builtin_amdgcn_readfirstlane(max(0, min(16, Ltot - (t * kBN + group * 16))));
     const __amdgpu_buffer_rsrc_t rsrc =
         __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, base ? rows * (int)row_bytes : 0, 0x00020000);
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void*)dst, 16, t_off, 0, 0, 0);

@@ -1,0 +1,33 @@
+"""Compiled assembly of the bf16 prefill kernel: a load to LDS takes its buffer descriptor from scalar registers.  Where the compiler holds a
+part of it in vector registers it wraps the load in a loop over the lanes' values, at the very point where all wavefronts of a workgroup
+stand behind a barrier."""
+import os
+import re
+import subprocess
+
+import pytest
+from paper_2508_08438_amd import build
+
+LOAD = re.compile(r"buffer_load_dwordx4 .*\blds\b")
+
+
+@pytest.fixture(scope="module")
+def asm(tmp_path_factory):
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    flags = [f for f in build.FLAGS if f not in ("-shared", "-fPIC")]
+    out = str(tmp_path_factory.mktemp("asm") / "k.s")
+    r = subprocess.run([hipcc, *flags, "--cuda-device-only", "-S", "-I", build.INCLUDE, "-I", build.CSRC, "-o", out,
+                        os.path.join(build.CSRC, "skv_attn.hip")], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert r.returncode == 0, r.stdout
+    return open(out).read()
+
+
+@pytest.mark.parametrize("form", ["Lb0ELb0E", "Lb0ELb1E", "Lb1ELb0E", "Lb1ELb1E"])
+def test_descriptors_are_scalar(asm, form):
+    m = re.search(r"^_ZN\S*attn_bf16_kernelI" + form + r"\S*:", asm, re.M)
+    body = asm[m.end():asm.index(".Lfunc_end", m.end())]
+    parts = re.split(r"^(\.LBB\w+):", body, flags=re.M)
+    blocks = dict(zip(parts[1::2], parts[2::2]))
+    assert len(LOAD.findall(body)) >= 12
+    looped = [name for name, b in blocks.items() if LOAD.search(b) and re.search(r"s_cbranch_execnz " + re.escape(name) + r"\b", b)]
+    assert not looped
