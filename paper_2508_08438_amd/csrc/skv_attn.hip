@@ -1257,28 +1257,41 @@ bool may_split(const Layout& y, int32_t n_req, int64_t total_q_rows, int32_t max
   return split_time(share, (float)total_q_rows / (items << y.pos_log)) <
          whole_time(items * y.units, kt * (tiles > 1 ? kTileFull : last), share);
 }
+// Whether workgroups find their items themselves (plan_item): a request per lane and, where items may be split, an item per
+// lane, in one round of workgroups.  Behind the first round every workgroup, surplus ones too, would pay for it where a list is
+// read in 1 us: 16 requests of 510 rows, 4.5 rounds, 497 us either way.
+bool plan_in_place(const Layout& y, int32_t n_req) {
+  const int64_t items = y.max_items - y.max_parts;
+  return n_req <= kPlanRequests && items * y.units <= kCus && (!y.max_parts || items <= kPlanItems);
+}
 // Tiles of eight heads and 32 rows, or of four heads and 64: eight take half the workgroups for requests of up to 32 rows, and
 // fewer where the last tile fits closer, but each costs half a key tile more (it may end inside one) and four heads in the one
 // tile of a short request leave half the wavefronts idle, which makes a key tile shorter.  Where either fills the chip the sums decide,
 // of requests that end anywhere in a tile: 64 query heads over 8, 256 requests of 1 .. 16 rows behind 500 to 1400 523 -> 322 us,
 // 32 of 264 behind 16 .. 32 k 7.32 -> 6.83 ms.  Where four heads leave compute units without work eight would only leave more:
 // one request of a row behind 512 15.8 us with four heads, 18.0 with eight; unless the keys are split, where the sums decide again
-// (3 of a row behind 12000 64 -> 54 us).
+// (3 of a row behind 12000 64 -> 54 us).  A tile of up to 16 rows fills half the wavefronts of eight heads as well, one of up to 32 those
+// of four: 15 requests of up to 6 rows behind up to 26 k, 64 over 8, 359 -> 216 us, 20 of a row behind 6 k 168 -> 89 (2573 shapes: other
+// tiles for 121, their time 0.68 on average; 2 slower, by 5 and 8 %).  Splits from a list start later than the forecast's error allows
+// for: they have to be a tenth shorter.
 bool eight_heads(const skv_attn_desc* d, int32_t n_req, int64_t total_q_rows, int32_t max_blocks, bool split) {
   if ((d->n_q_heads / d->n_kv_heads) % 8) return false;
   const int64_t rows = mean_rows(n_req, total_q_rows);
   const float kt = (float)key_tiles(rows, max_blocks), at_ends = 6.f * kTileFull;   // at_ends: of a workgroup outside its loop
   const float tiles8 = std::max(1.f, rows / 32.f + 0.5f), tiles4 = std::max(1.f, rows / 64.f + 0.5f);
   const float wgs8 = (float)n_req * (d->n_q_heads / 8) * tiles8, wgs4 = (float)n_req * (d->n_q_heads / 4) * tiles4;
+  const bool half8 = rows <= 16;
+  const int tile8 = half8 ? kTileHalf : kTileFull;
   const float full = kt * kTileFull + at_ends, last4 = kt * (rows <= 32 ? kTileHalf : 0.5f * (kTileHalf + kTileFull)) + at_ends;
-  const float time8 = wgs8 * (full + (rows > 32 ? 0.5f * kTileFull : 0.f));
+  const float whole8 = kt * tile8 + at_ends, time8 = wgs8 * (whole8 + (rows > 32 ? 0.5f * kTileFull : 0.f));
   const float time4 = (float)n_req * (d->n_q_heads / 4) * ((tiles4 - 1.f) * full + last4);
   if (wgs4 <= kCus) {
     if (!split) return false;
     if (rows > 32) return kt >= 32 && time8 < 0.98f * time4;
-    return split_time(wgs8 * kt * kTileFull / kCus, (float)rows / kRowsPerWave) < whole_time(wgs4, kt * kTileHalf, 0.f);
+    const float most = half8 && !plan_in_place(layout_for(d, n_req, total_q_rows, true, true), n_req) ? 0.9f : 1.f;
+    return split_time(wgs8 * kt * tile8 / kCus, (float)rows / kRowsPerWave) < most * whole_time(wgs4, kt * kTileHalf, 0.f);
   }
-  return std::max(time8, kCus * full) < time4;
+  return std::max(time8, kCus * whole8) < time4;
 }
 // Keys above which a longest request has the requests ordered by length.  Order is worth its 1.3 us where workgroups queue and
 // one that starts late ends late: in a few rounds (64 requests of up to 39 rows behind up to 496, 16 query heads over 1: 42 ->
@@ -1287,13 +1300,6 @@ bool eight_heads(const skv_attn_desc* d, int32_t n_req, int64_t total_q_rows, in
 int order_above(const Layout& y, int32_t n_req, int64_t total_q_rows) {
   const float tiles = std::max(1.f, (float)mean_rows(n_req, total_q_rows) / (1 << y.pos_log) + 0.5f), wgs = tiles * n_req * y.units;
   return wgs <= kCus ? INT_MAX : wgs <= 4 * kCus ? 0 : 1024;
-}
-// Whether workgroups find their items themselves (plan_item): a request per lane and, where items may be split, an item per
-// lane, in one round of workgroups.  Behind the first round every workgroup, surplus ones too, would pay for it where a list is
-// read in 1 us: 16 requests of 510 rows, 4.5 rounds, 497 us either way.
-bool plan_in_place(const Layout& y, int32_t n_req) {
-  const int64_t items = y.max_items - y.max_parts;
-  return n_req <= kPlanRequests && items * y.units <= kCus && (!y.max_parts || items <= kPlanItems);
 }
 size_t split_bytes(const Layout& y) {
   return y.max_parts ? kCus * kSplitInts * sizeof(int32_t) + (size_t)y.max_parts * y.units * kSlotFloats * sizeof(float) : 0;
