@@ -367,8 +367,8 @@ __global__ __launch_bounds__(kSchedThreads) void attn_schedule_kernel(
 // ---- the same list without a kernel in front of the attention -------------------------------------
 // Of up to 64 requests every wavefront works its item out for itself, a request per lane and nothing through LDS: the same cuts,
 // order (exactly by length here), forecasts and part lengths as above.  A list costs a launch and a chain of barriers, 5 to 9 us
-// of every call; this 0.5 to 1.5 us of a workgroup's start, 2 to 4 where a split is searched for (for one round of workgroups:
-// a second one has never paid where the first has room for every item).
+// of every call; this 0.5 to 1.5 us of a workgroup's start, 2 to 4 where a split is searched for.  Parts fill one round of workgroups
+// here: the workgroups that a second one needs room for cost every call 3 to 8 us where the parts leave it empty.
 constexpr int kPlanRequests = 64, kPlanItems = 64;   // kPlanItems: a lane each, where they may be split
 struct Work {
   int r, row0, row1, qbase, S, L, kt0, part;   // kt0: first key tile of the part, part: as in a record
@@ -1264,6 +1264,18 @@ bool plan_in_place(const Layout& y, int32_t n_req) {
   const int64_t items = y.max_items - y.max_parts;
   return n_req <= kPlanRequests && items * y.units <= kCus && (!y.max_parts || items <= kPlanItems);
 }
+// Whether the parts of a split call are likely to be shorter in two rounds of workgroups, from what the host knows: such a call takes the list,
+// whose kernel tries both.  Few items whose number does not divide a round: 3 requests of 770 rows behind 7.7 k cached tokens, 16 heads
+// over 8, 21 items in 32 places stay whole in one round, 178 us, and are split in two, 134.  The list costs 5 us and the estimate
+// errs where lengths differ, hence kTwoTiles (1986 calls of up to 14 requests behind up to 48 k: 0 / 10 / 16 / 30 tiles take the list for
+// 253 / 159 / 115 / 72 of them; 83 / 80 / 67 / 46 are faster by 3 to 30 %, 108 / 37 / 20 / 8 slower by 3 to 9 %).
+constexpr int kTwoTiles = 16;
+bool two_rounds(const Layout& y, int32_t n_req, int64_t total_q_rows, int32_t max_blocks) {
+  const int64_t rows = mean_rows(n_req, total_q_rows), kt = key_tiles(rows, max_blocks);
+  const int64_t items = n_req * ((rows + (1 << y.pos_log) - 1) >> y.pos_log);
+  auto longest = [&](int64_t room) { return (kt + std::max<int64_t>(1, room / items) - 1) / std::max<int64_t>(1, room / items); };
+  return kStartTiles + longest(kCus / y.units) > 2 * (kStartTiles + longest(2 * kCus / y.units)) + kTwoTiles;
+}
 // Tiles of eight heads and 32 rows, or of four heads and 64: eight take half the workgroups for requests of up to 32 rows, and
 // fewer where the last tile fits closer, but each costs half a key tile more (it may end inside one) and four heads in the one
 // tile of a short request leave half the wavefronts idle, which makes a key tile shorter.  Where either fills the chip the sums decide,
@@ -1364,7 +1376,7 @@ static int prefill_attn_enqueue(const skv_attn_desc* desc, int32_t n_req, const 
                                 void* d_workspace, const Layout& y, const StepExtras* x, void* stream) {
   hipStream_t st = (hipStream_t)stream;
   // of up to kSkvGatherScan requests a plan with parts makes the suffix offsets itself, and its pages travel beside the merge
-  const bool plan = desc->dtype == SKV_BF16 && plan_in_place(y, n_req);
+  const bool plan = desc->dtype == SKV_BF16 && plan_in_place(y, n_req) && !(y.max_parts && two_rounds(y, n_req, total_q_rows, max_blocks));
   const bool late = x && plan && y.max_parts && !x->gather.large;
   if (x && !late) {
     const int rc = skv_gather_enqueue(x->gather, false, x->req_off, x->q_off, x->count, stream);
