@@ -66,7 +66,8 @@ __global__ __launch_bounds__(kThreads) void gather_pages_kernel(SkvGather g, con
   }
   __shared__ int64_t first[kScan ? kSkvGatherScan + 1 : 1];
   const int others = kOffsets ? 1 + n_count : 0;
-  skv_gather_pages<kScan, kThreads, kUnroll>(g, (int)blockIdx.x - others, (int)gridDim.x - others, first);
+  skv_gather_pages<kScan, kThreads, kUnroll>(g, (int)blockIdx.x - others, (int)gridDim.x - others, first, g.kpool, g.vpool, g.matched_len,
+                                             g.page_table, g.ctx_off, g.kctx, g.vctx);
 }
 
 __global__ __launch_bounds__(kThreads) void count_matched_kernel(SkvCount count) { skv_count_request(count, blockIdx.x); }

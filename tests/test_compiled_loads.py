@@ -1,6 +1,6 @@
-"""Compiled assembly of the bf16 prefill kernel: a load to LDS takes its buffer descriptor from scalar registers.  Where the compiler holds a
+"""Compiled assembly.  The bf16 prefill kernel: a load to LDS takes its buffer descriptor from scalar registers.  Where the compiler holds a
 part of it in vector registers it wraps the load in a loop over the lanes' values, at the very point where all wavefronts of a workgroup
-stand behind a barrier."""
+stand behind a barrier.  The gather of more than 512 requests: offsets and table are read with scalar loads."""
 import os
 import re
 import subprocess
@@ -11,15 +11,19 @@ from paper_2508_08438_amd import build
 LOAD = re.compile(r"buffer_load_dwordx4 .*\blds\b")
 
 
-@pytest.fixture(scope="module")
-def asm(tmp_path_factory):
+def _compile(src, tmp_path_factory):
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     flags = [f for f in build.FLAGS if f not in ("-shared", "-fPIC")]
     out = str(tmp_path_factory.mktemp("asm") / "k.s")
     r = subprocess.run([hipcc, *flags, "--cuda-device-only", "-S", "-I", build.INCLUDE, "-I", build.CSRC, "-o", out,
-                        os.path.join(build.CSRC, "skv_attn.hip")], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+                        os.path.join(build.CSRC, src)], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     assert r.returncode == 0, r.stdout
     return open(out).read()
+
+
+@pytest.fixture(scope="module")
+def asm(tmp_path_factory):
+    return _compile("skv_attn.hip", tmp_path_factory)
 
 
 @pytest.mark.parametrize("form", ["Lb0ELb0E", "Lb0ELb1E", "Lb1ELb0E", "Lb1ELb1E"])
@@ -31,3 +35,10 @@ def test_descriptors_are_scalar(asm, form):
     assert len(LOAD.findall(body)) >= 12
     looped = [name for name, b in blocks.items() if LOAD.search(b) and re.search(r"s_cbranch_execnz " + re.escape(name) + r"\b", b)]
     assert not looped
+
+
+def test_gather_reads_offsets_with_scalar_loads(tmp_path_factory):
+    asm = _compile("skv_gather.hip", tmp_path_factory)
+    m = re.search(r"^_ZN\S*gather_pages_kernelILb0ELb0E\S*:", asm, re.M)
+    body = asm[m.end():asm.index(".Lfunc_end", m.end())]
+    assert "global_load_dwordx4" in body and not re.search(r"global_load_dword(x2)? ", body)
