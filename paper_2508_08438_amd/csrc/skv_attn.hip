@@ -1213,8 +1213,8 @@ __global__ __launch_bounds__(kMergeThreads, 4) void attn_merge_gather_kernel(Att
   else if ((int)blockIdx.x < others)
     skv_count_request(count, (int)blockIdx.x - merge_blocks);
   else
-    skv_gather_pages<true, kMergeThreads, 4>(g, (int)blockIdx.x - others, (int)gridDim.x - others, first, g.kpool, g.vpool, g.matched_len,
-                                             g.page_table, g.ctx_off, g.kctx, g.vctx);
+    skv_gather_pages<true, true, kMergeThreads, 4>(g, (int)blockIdx.x - others, (int)gridDim.x - others, first, g.kpool, g.vpool,
+                                                   g.matched_len, g.page_table, g.ctx_off, g.kctx, g.vctx);
 }
 
 // Query heads per workgroup: divides kWaves.  `fine`: eight where the kv head serves a multiple of eight.

@@ -15,7 +15,7 @@ struct SkvGather {
   u32x4 *kctx, *vctx;
   int64_t cap_pages;
   int page_vec;   // 16-byte vectors per page
-  int slices;     // workgroups per page
+  int slices_log; // logarithm of the workgroups per page
   bool large;     // enough bytes for the form of one workgroup per compute unit
 };
 constexpr int kSkvGatherScan = 512;   // requests up to which every workgroup scans the matched lengths itself
@@ -49,12 +49,13 @@ __device__ __forceinline__ void skv_count_request(const SkvCount& c, int r) {
   }
 }
 
-// What workgroup `block` of n_blocks copies (n_blocks is a multiple of the slices): it loops over the global list of matched pages, each
-// moving as 16-byte vectors with all loads of a step issued before its stores.  kScan: the workgroup scans the matched lengths
+// What workgroup `block` of n_blocks copies (n_blocks is a multiple of the slices; kSliced: a page may have several): it loops over the
+// global list of matched pages, each moving as 16-byte vectors with all loads of a step issued before its stores.  kScan: the workgroup scans the matched lengths
 // itself (the first one also writes the offsets) and finds the owner of a page in `first`, kSkvGatherScan + 1 places in LDS.
 // (The pointers as arguments: only there does __restrict__ tell the compiler that the copies leave offsets and table alone, so that it
-// reads these with scalar loads.  Of 599 requests, 23490 pages of 4 KB: 75 us, 115 with vector loads.)
-template <bool kScan, int kThreads, int kUnroll>
+// reads these with scalar loads.  Of 599 requests, 23490 pages of 4 KB: 75 us, 115 with vector loads.  Slices known at run time only
+// cost calls without any up to a tenth: 860 pages of 32 KB 19.0 us, 21.9 with two divisions for them, 21.0 with shifts.)
+template <bool kScan, bool kSliced, int kThreads, int kUnroll>
 __device__ __forceinline__ void skv_gather_pages(const SkvGather& g, int block, int n_blocks, int64_t* first, const u32x4* __restrict__ kpool,
                                                  const u32x4* __restrict__ vpool, const int32_t* __restrict__ matched_len,
                                                  const int32_t* __restrict__ page_table, int64_t* __restrict__ ctx_off,
@@ -84,8 +85,9 @@ __device__ __forceinline__ void skv_gather_pages(const SkvGather& g, int block, 
   }
   auto pages_before = [&](int r) { return kScan ? first[r] : ctx_off[r] / SKV_BLOCK_TOKENS; };
   const int64_t end = min(total, g.cap_pages);
-  const int slice = block % g.slices, v0 = g.page_vec / g.slices * slice, v1 = slice + 1 < g.slices ? v0 + g.page_vec / g.slices : g.page_vec;
-  for (int64_t p = block / g.slices; p < end; p += n_blocks / g.slices) {
+  const int log = kSliced ? g.slices_log : 0, slice = block & ((1 << log) - 1), per_slice = g.page_vec >> log;
+  const int v0 = per_slice * slice, v1 = (slice + 1) >> log ? g.page_vec : v0 + per_slice;   // (the last takes the rest)
+  for (int64_t p = block >> log; p < end; p += n_blocks >> log) {
     // request that owns output page p: the last one with no more than p pages before it
     int lo = 0, hi = n_req;  // invariant: pages_before(lo) <= p < pages_before(hi)
     while (hi - lo > 1) {

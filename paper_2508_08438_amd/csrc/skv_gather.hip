@@ -42,7 +42,7 @@ __global__ __launch_bounds__(kOffThreads) void ctx_offsets_kernel(int n_req, con
 // 158 / 685 scanned, 33.7 / 113 / 432 with it; 40 pages each of 1024 1053 and 1044.
 // kOffsets: the first workgroup writes the suffix offsets instead (skv_suffix_offsets of up to kSkvGatherScan requests), which
 // neither reads nor delays a page: one launch less in a step.  n_count workgroups behind it update the counters of a request each.
-template <bool kScan, bool kOffsets>
+template <bool kScan, bool kOffsets, bool kSliced>
 __global__ __launch_bounds__(kThreads) void gather_pages_kernel(SkvGather g, const int32_t* __restrict__ req_off, int32_t* __restrict__ q_off,
                                                                 SkvCount count, int n_count) {
   if constexpr (kOffsets) {
@@ -66,8 +66,8 @@ __global__ __launch_bounds__(kThreads) void gather_pages_kernel(SkvGather g, con
   }
   __shared__ int64_t first[kScan ? kSkvGatherScan + 1 : 1];
   const int others = kOffsets ? 1 + n_count : 0;
-  skv_gather_pages<kScan, kThreads, kUnroll>(g, (int)blockIdx.x - others, (int)gridDim.x - others, first, g.kpool, g.vpool, g.matched_len,
-                                             g.page_table, g.ctx_off, g.kctx, g.vctx);
+  skv_gather_pages<kScan, kSliced, kThreads, kUnroll>(g, (int)blockIdx.x - others, (int)gridDim.x - others, first, g.kpool, g.vpool,
+                                                      g.matched_len, g.page_table, g.ctx_off, g.kctx, g.vctx);
 }
 
 __global__ __launch_bounds__(kThreads) void count_matched_kernel(SkvCount count) { skv_count_request(count, blockIdx.x); }
@@ -212,7 +212,7 @@ bool large_copy(int64_t pages, int64_t page_bytes) { return page_bytes >= 16384 
 // Workgroups per page: where a batch has no page for every compute unit a page of 32 KB is several workgroups' worth of loads in
 // flight.  us with 1 / 2 / 4 slices: 16 pages 4.95 / 4.1 / 3.8, 128 (of the fp32 pool's 32 KB) 6.4 / 5.6 / 5.3, 187 6.3 / 5.9 / 6.2,
 // 512 11.9 / 12.3 / 14.1.
-int slices_for(int64_t pages) { return pages <= 128 ? 4 : pages <= 256 ? 2 : 1; }
+int slices_log_for(int64_t pages) { return pages <= 128 ? 2 : pages <= 256 ? 1 : 0; }
 
 }  // namespace
 
@@ -264,14 +264,14 @@ int skv_gather_check(const skv_attn_desc* desc, int32_t n_req, const void* d_kpo
   // pages the batch can move at most: what the table holds and, often far less (private blocks end a match early), what the staging does
   const int64_t upper = std::min((int64_t)n_req * max_blocks, ctx_capacity_tokens / SKV_BLOCK_TOKENS);
   *g = {n_req, (const u32x4*)d_kpool, (const u32x4*)d_vpool, n_pages, d_matched_len, d_page_table, max_blocks, d_ctx_off,
-        (u32x4*)d_kctx, (u32x4*)d_vctx, n_req && max_blocks ? ctx_capacity_tokens / SKV_BLOCK_TOKENS : 0, (int)(page_bytes / 16), slices_for(upper),
-        n_req <= kPref && page_bytes <= 0x7fffffff && large_copy(upper, page_bytes)};
+        (u32x4*)d_kctx, (u32x4*)d_vctx, n_req && max_blocks ? ctx_capacity_tokens / SKV_BLOCK_TOKENS : 0, (int)(page_bytes / 16),
+        n_req <= kPref ? slices_log_for(upper) : 0, n_req <= kPref && page_bytes <= 0x7fffffff && large_copy(upper, page_bytes)};
   return SKV_OK;
 }
 
 int skv_gather_blocks(const SkvGather& g) {
   const int64_t upper = std::min((int64_t)g.n_req * g.max_blocks, g.cap_pages);
-  return (int)(upper < 1 ? 1 : (upper < 256 * 16 ? upper : 256 * 16)) * g.slices;
+  return (int)(upper < 1 ? 1 : (upper < 256 * 16 ? upper : 256 * 16)) << g.slices_log;
 }
 
 int skv_count_enqueue(const SkvCount& count, void* stream) {
@@ -286,7 +286,8 @@ int skv_gather_enqueue(const SkvGather& g, bool beside, const int32_t* d_req_off
   const bool scan = g.n_req <= kPref, large = scan && (beside || g.large) && (int64_t)g.page_vec * 16 <= 0x7fffffff;
   if (scan && !large && d_q_off) {
     const int n_count = count.records ? g.n_req : 0;
-    gather_pages_kernel<true, true><<<1 + n_count + skv_gather_blocks(g), kThreads, 0, st>>>(g, d_req_off, d_q_off, count, n_count);
+    const auto kernel = g.slices_log ? gather_pages_kernel<true, true, true> : gather_pages_kernel<true, true, false>;
+    kernel<<<1 + n_count + skv_gather_blocks(g), kThreads, 0, st>>>(g, d_req_off, d_q_off, count, n_count);
     SKV_HIP(hipGetLastError());
     return SKV_OK;
   }
@@ -298,12 +299,13 @@ int skv_gather_enqueue(const SkvGather& g, bool beside, const int32_t* d_req_off
         g.n_req, (const char*)g.kpool, (const char*)g.vpool, g.n_pages, g.matched_len, g.page_table, g.max_blocks, g.ctx_off,
         (char*)g.kctx, (char*)g.vctx, g.cap_pages, g.page_vec * 16);
   } else if (scan) {
-    gather_pages_kernel<true, false><<<skv_gather_blocks(g), kThreads, 0, st>>>(g, nullptr, nullptr, count, 0);
+    const auto kernel = g.slices_log ? gather_pages_kernel<true, false, true> : gather_pages_kernel<true, false, false>;
+    kernel<<<skv_gather_blocks(g), kThreads, 0, st>>>(g, nullptr, nullptr, count, 0);
   } else {
     ctx_offsets_kernel<<<1, kOffThreads, 0, st>>>(g.n_req, g.matched_len, g.ctx_off);
     SKV_HIP(hipGetLastError());
     if (g.max_blocks == 0) return SKV_OK;
-    gather_pages_kernel<false, false><<<skv_gather_blocks(g), kThreads, 0, st>>>(g, nullptr, nullptr, count, 0);
+    gather_pages_kernel<false, false, false><<<skv_gather_blocks(g), kThreads, 0, st>>>(g, nullptr, nullptr, count, 0);
   }
   SKV_HIP(hipGetLastError());
   return SKV_OK;
