@@ -114,7 +114,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(32))) void
   int r = 0;   // request that owns the page
   auto page_of = [&](int64_t p) __attribute__((always_inline)) {
     if (p >= end) return -1;
-    while (uniform(first[r + 1]) <= p) ++r;
+    if (uniform(first[r + 1]) <= p) {   // (it does end: p < first[n_req])
+      int lo = r + 1, hi = n_req;       // first[lo] <= p < first[hi]
+      while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (uniform(first[mid]) <= p) lo = mid; else hi = mid;
+      }
+      r = lo;
+    }
     const int64_t j = p - uniform(first[r]);
     return j < max_blocks ? page_table[(size_t)r * max_blocks + j] : -1;
   };
