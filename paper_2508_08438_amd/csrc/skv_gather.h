@@ -16,7 +16,7 @@ struct SkvGather {
   int64_t cap_pages;
   int page_vec;   // 16-byte vectors per page
   int slices_log; // logarithm of the workgroups per page
-  bool large;     // enough bytes for the form of one workgroup per compute unit
+  bool large;     // a copy with a launch of its own
 };
 constexpr int kSkvGatherScan = 512;   // requests up to which every workgroup scans the matched lengths itself
 

@@ -76,7 +76,11 @@ __global__ __launch_bounds__(kThreads) void count_matched_kernel(SkvCount count)
 // SIMD's 512 for each of two wavefronts): one workgroup per compute unit with one wavefront per SIMD in the 32 registers that
 // are left, so it needs no compute unit of its own and takes what the other kernel leaves of the memory's time.  Addresses are
 // buffer descriptors and scalar offsets for the registers' sake; what lies behind a page's end is neither read nor written.
-// Alone it is the faster form of a large copy too (large_copy).
+// Alone it is the faster form of a large copy too: one workgroup per compute unit keeps enough in flight and goes through neighbouring
+// pages together.  us of the plain form / of this one, 32 KB pages 1024 24.8 / 25.8, 2048 51.5 / 47.6, 4096 101 / 93, 16384 401 / 379 (5.67
+// TB/s); 16 KB 2048 26.9 / 26.1, 16384 197 / 184; but 8 KB of 253 requests, 22500 pages, 74.2 / 78.3; 4 KB 16384 52.6 / 68.0.  Only for
+// callers that know how full their staging is: skv_gather_kv knows its size alone, and 822 pages of 382 requests in one for 24660 take
+// 19.8 / 24.2, 520 of 104 14.5 / 16.5.
 constexpr int kPref = kSkvGatherScan;
 constexpr int kBesideGrid = 256, kBesideUnroll = 3;
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(32))) void gather_beside_kernel(
@@ -211,10 +215,7 @@ __global__ __launch_bounds__(kThreads) void stream_copy_kernel(const u32x4* __re
   }
 }
 
-// One workgroup per compute unit keeps enough in flight and goes through neighbouring pages together: us of the plain form / of that one,
-// 32 KB pages 1024 24.8 / 25.8, 2048 51.5 / 47.6, 4096 101 / 93, 16384 401 / 379 (5.67 TB/s); 64 KB 512 28.2 / 26.5; 16 KB 2048
-// 26.9 / 26.1, 16384 197 / 184.  Below, a page is too few loads per thread and the scan in front too long: 8 KB of 253 requests, 22500
-// pages, 74.2 / 78.3; 4 KB 16384 52.6 / 68.0.
+// What a step does not let the merge of split items carry.
 bool large_copy(int64_t pages, int64_t page_bytes) { return page_bytes >= 16384 && pages * page_bytes >= (48 << 20); }
 // Workgroups per page: where a batch has no page for every compute unit a page of 32 KB is several workgroups' worth of loads in
 // flight.  us with 1 / 2 / 4 slices: 16 pages 4.95 / 4.1 / 3.8, 128 (of the fp32 pool's 32 KB) 6.4 / 5.6 / 5.3, 187 6.3 / 5.9 / 6.2,
@@ -272,7 +273,7 @@ int skv_gather_check(const skv_attn_desc* desc, int32_t n_req, const void* d_kpo
   const int64_t upper = std::min((int64_t)n_req * max_blocks, ctx_capacity_tokens / SKV_BLOCK_TOKENS);
   *g = {n_req, (const u32x4*)d_kpool, (const u32x4*)d_vpool, n_pages, d_matched_len, d_page_table, max_blocks, d_ctx_off,
         (u32x4*)d_kctx, (u32x4*)d_vctx, n_req && max_blocks ? ctx_capacity_tokens / SKV_BLOCK_TOKENS : 0, (int)(page_bytes / 16),
-        n_req <= kPref ? slices_log_for(upper) : 0, n_req <= kPref && page_bytes <= 0x7fffffff && large_copy(upper, page_bytes)};
+        n_req <= kPref ? slices_log_for(upper) : 0, large_copy(upper, page_bytes)};
   return SKV_OK;
 }
 
@@ -290,8 +291,9 @@ int skv_count_enqueue(const SkvCount& count, void* stream) {
 
 int skv_gather_enqueue(const SkvGather& g, bool beside, const int32_t* d_req_off, int32_t* d_q_off, const SkvCount& count, void* stream) {
   hipStream_t st = (hipStream_t)stream;
-  const bool scan = g.n_req <= kPref, large = scan && (beside || g.large) && (int64_t)g.page_vec * 16 <= 0x7fffffff;
-  if (scan && !large && d_q_off) {
+  const bool scan = g.n_req <= kPref;
+  beside = beside && scan && (int64_t)g.page_vec * 16 <= 0x7fffffff;
+  if (scan && !beside && d_q_off) {
     const int n_count = count.records ? g.n_req : 0;
     const auto kernel = g.slices_log ? gather_pages_kernel<true, true, true> : gather_pages_kernel<true, true, false>;
     kernel<<<1 + n_count + skv_gather_blocks(g), kThreads, 0, st>>>(g, d_req_off, d_q_off, count, n_count);
@@ -301,7 +303,7 @@ int skv_gather_enqueue(const SkvGather& g, bool beside, const int32_t* d_req_off
   int rc = d_q_off ? skv_suffix_offsets(g.n_req, d_req_off, g.matched_len, d_q_off, stream) : SKV_OK;
   if (rc == SKV_OK) rc = skv_count_enqueue(count, stream);
   if (rc) return rc;
-  if (large) {
+  if (beside) {
     gather_beside_kernel<<<kBesideGrid, kThreads, 0, st>>>(
         g.n_req, (const char*)g.kpool, (const char*)g.vpool, g.n_pages, g.matched_len, g.page_table, g.max_blocks, g.ctx_off,
         (char*)g.kctx, (char*)g.vctx, g.cap_pages, g.page_vec * 16);

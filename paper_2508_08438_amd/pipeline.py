@@ -27,6 +27,10 @@ def _tiled_from_host(chunk: torch.Tensor, n_rows: int, device) -> torch.Tensor:
 # requests, 487 / 523; 3.3 GB, 32 requests, 6865 / 7524.
 GATHER_BESIDE_BYTES = 128 << 20
 
+# Bytes a pool and a page from which that form of the copy is the faster one alone (4096 pages of 32 KB 101 -> 93 us): a session's staging
+# is as large as what it holds.
+GATHER_ALONE_BYTES, GATHER_ALONE_PAGE = 48 << 20, 16384
+
 # One stream per device for these copies, whatever the number of sessions: streams are dealt to four hardware queues, and a copy on
 # the queue of the attention's own stream runs behind it (24 requests behind 1700 keys, on nine streams one after the other: 260
 # to 264 us, on the sixth 296).  A capture takes a stream of the session's own.  Neither is of torch's pool (binding.OwnStream).
@@ -106,6 +110,8 @@ class Session:
             self.out = torch.zeros_like(self.q)
             self.kctx = torch.zeros((n_ctx, a.n_kv_heads, a.head_dim), dtype=a.torch_dtype, device=dev)
             self.vctx = torch.zeros_like(self.kctx)
+        page = BLOCK * a.n_kv_heads * a.head_dim * self.kctx.element_size()
+        self.large_copy = page >= GATHER_ALONE_PAGE and self.kctx.numel() * self.kctx.element_size() >= GATHER_ALONE_BYTES
         self.records = torch.empty_like(self.page_table)     # of the matched blocks, between the kernels of a step
         nbytes = skv.skv_prefill_attn_workspace_size(self.desc, w.n_req, self.q.shape[0])
         self.workspace = torch.empty(nbytes, dtype=torch.uint8, device=dev)
@@ -123,7 +129,8 @@ class Session:
 
     def gather(self, stream=None, beside=False):
         skv.skv_gather_kv(self.desc, self.kpool, self.vpool, self.matched_len, self.page_table,
-                          self.max_blocks, self.ctx_off, self.kctx, self.vctx, stream=stream, beside=beside)
+                          self.max_blocks, self.ctx_off, self.kctx, self.vctx, stream=stream,
+                          beside=beside or self.large_copy)
 
     def attention(self):
         skv.skv_prefill_attn(self.desc, self.q, self.knew, self.vnew, self.q_off, self.kpool, self.vpool,
