@@ -23,8 +23,9 @@ def _tiled_from_host(chunk: torch.Tensor, n_rows: int, device) -> torch.Tensor:
 
 # K and V bytes from which a step copies them on a stream of its own beside the attention.  The two queues' waits cost about
 # 15 us, attention slows by a third of the copy's time, and offsets and counters take launches of their own again: us a pass, beside /
-# in one call: 12 MB behind one request 59 / 37.5; 79 MB, 24 requests, 321 / 320; 98 MB, one of 257 rows, 252 / 241; 205 MB, 16
-# requests, 487 / 523; 3.3 GB, 32 requests, 6865 / 7524.
+# in one call: 12 MB behind one request 59 / 37.5; 98 MB, 3 of 8 rows, 85 / 81; 154 MB, 7 of up to 137, 110 / 114; 250 MB, 93 of 46, 145 /
+# 175; 3.3 GB, 32 requests, 6865 / 7524.  Of 70 steps of 65 MB to 1.4 GB, attention from 26 us to 1.2 ms, one call is the faster for 18 of
+# the 20 below the line (the others by 1 and 4 %), two streams for 45 of the 50 above it (the others by up to 6 %).
 GATHER_BESIDE_BYTES = 128 << 20
 
 # Bytes a pool and a page from which that form of the copy is the faster one alone (4096 pages of 32 KB 101 -> 93 us): a session's staging
