@@ -75,7 +75,7 @@ struct AttnParams {
   int32_t* q_off_out;
   int32_t* splits_out;       // = splits and n_items, written by them for the merge
   int32_t* n_items_out;
-  int n_req, pos_log, max_items, order_above;
+  int n_req, pos_log, max_items;
   float rows_filled;
 };
 
@@ -366,7 +366,7 @@ __global__ __launch_bounds__(kSchedThreads) void attn_schedule_kernel(
 
 // ---- the same list without a kernel in front of the attention -------------------------------------
 // Of up to 64 requests every wavefront works its item out for itself, a request per lane and nothing through LDS: the same cuts,
-// order (exactly by length here), forecasts and part lengths as above.  A list costs a launch and a chain of barriers, 5 to 9 us
+// forecasts and part lengths as above (an order by length has nothing to give in one round of workgroups).  A list costs a launch and a chain of barriers, 5 to 9 us
 // of every call; this 0.5 to 1.5 us of a workgroup's start, 2 to 4 where a split is searched for.  Parts fill one round of workgroups
 // here: the workgroups that a second one needs room for cost every call 3 to 8 us where the parts leave it empty.
 constexpr int kPlanRequests = 64, kPlanItems = 64;   // kPlanItems: a lane each, where they may be split
@@ -387,7 +387,7 @@ __device__ __forceinline__ bool plan_item(const AttnParams& p, int item, int uni
     }
     return x;
   };
-  int r = lane, qb = 0, qe = 0, L = 0;
+  int qb = 0, qe = 0, L = 0;
   if (p.req_off) {
     if (lane < p.n_req) {
       L = p.matched_len[lane];
@@ -405,20 +405,7 @@ __device__ __forceinline__ bool plan_item(const AttnParams& p, int item, int uni
     qe = p.q_off[lane + 1];
     L = p.matched_len[lane];
   }
-  Cut c = cut_of(qb, qe, L, p.pos_log);
-  if (p.order_above < INT_MAX) {
-    const int keys = c.nt > 0 ? c.L + c.S : 0;
-    if (wave_max(keys) > p.order_above) {
-      int place = lane < p.n_req ? 0 : lane;
-      for (int j = 0; j < p.n_req; ++j) {
-        const int k = at_lane(keys, j);
-        if (lane < p.n_req) place += k > keys || (k == keys && j < lane);
-      }
-      auto move = [&](int x) __attribute__((always_inline)) { return __builtin_amdgcn_ds_permute(place * 4, x); };
-      r = move(r);
-      c = cut_of(move(qb), move(qe), move(L), p.pos_log);
-    }
-  }
+  const Cut c = cut_of(qb, qe, L, p.pos_log);
   const int upto = scan(c.nt), total = at_lane(upto, 63);
   auto tile_of = [&](int own, const Cut& cut, int up) __attribute__((always_inline)) {   // the request's last tile first
     int row0, row1;
@@ -432,7 +419,7 @@ __device__ __forceinline__ bool plan_item(const AttnParams& p, int item, int uni
     const int at = __builtin_popcountll(__ballot(upto <= item));
     const Cut mine = {at_lane(c.S, at), at_lane(c.L, at), at_lane(c.qb, at), at_lane(c.head_rows, at), at_lane(c.nt, at)};
     const int2 rows = tile_of(item, mine, at_lane(upto, at));
-    w.r = at_lane(r, at);
+    w.r = at;
     w.row0 = rows.x;
     w.row1 = rows.y;
     w.qbase = mine.qb;
@@ -449,7 +436,6 @@ __device__ __forceinline__ bool plan_item(const AttnParams& p, int item, int uni
   at = min(at, 63);
   const Cut mine = {__shfl(c.S, at), __shfl(c.L, at), __shfl(c.qb, at), __shfl(c.head_rows, at), __shfl(c.nt, at)};
   const int2 rows = tile_of(min(lane, n - 1), mine, __shfl(upto, at));
-  r = __shfl(r, at);
   const bool have = lane < n;
   const int n_kt = have ? (mine.L + rows.y + kBN - 1) / kBN : 0, last = have ? (mine.L + rows.x) / kBN : 0;
   const float time = (float)n_kt * tile_time(rows.y - rows.x, p.pos_log);
@@ -484,7 +470,7 @@ __device__ __forceinline__ bool plan_item(const AttnParams& p, int item, int uni
   if (writes && item == 0) p.n_items_out[1] = __builtin_popcountll(cut_items);
   if (item >= (split ? n_parts : n)) return false;
   const int own = split ? __builtin_popcountll(__ballot(part_upto <= item)) : item;
-  w.r = at_lane(r, own);
+  w.r = at_lane(at, own);
   w.row0 = at_lane(rows.x, own);
   w.row1 = at_lane(rows.y, own);
   w.qbase = at_lane(mine.qb, own);
@@ -1415,11 +1401,10 @@ static int prefill_attn_enqueue(const skv_attn_desc* desc, int32_t n_req, const 
   p.n_req = n_req;
   p.pos_log = y.pos_log;
   p.max_items = (int)y.max_items;
-  p.order_above = order_above(y, n_req, total_q_rows);
   p.rows_filled = (float)total_q_rows * y.heads_per_wg;
   if (!plan) {
-    attn_schedule_kernel<<<1, kSchedThreads, 0, st>>>(n_req, d_q_off, d_matched_len, y.pos_log, p.max_items, y.units, p.order_above,
-                                                      p.rows_filled, p.n_items_out, (int32_t*)p.items, p.splits_out);
+    attn_schedule_kernel<<<1, kSchedThreads, 0, st>>>(n_req, d_q_off, d_matched_len, y.pos_log, p.max_items, y.units,
+                                                      order_above(y, n_req, total_q_rows), p.rows_filled, p.n_items_out, (int32_t*)p.items, p.splits_out);
     SKV_HIP(hipGetLastError());
   }
   const auto kernel = y.max_parts ? (plan ? attn_bf16_kernel<true, true> : attn_bf16_kernel<true, false>)

@@ -1,5 +1,5 @@
 """bf16 prefill attention where workgroups find their items themselves (up to 64 requests) and where a list is made in front: on both
-sides of every limit between them, with and without items split along the keys, in and out of order.  Against the fp64 oracle."""
+sides of every limit between them, with and without items split along the keys.  Against the fp64 oracle."""
 import numpy as np
 import pytest
 import torch
@@ -16,7 +16,7 @@ PLAN = [
     # short first tiles and tiles cut from row 0; heads alone, in pairs, four and eight; lengths far apart
     (4, 4, [300, 5], [90, 300]), (4, 2, [200, 1, 0, 129], [33, 250, 4, 100]), (32, 8, [137], [187]), (64, 8, [257, 3], [500, 7]),
     (16, 2, [64, 65, 63, 1], [4, 9, 130, 260]),
-    # unsplit: 63, 64, 65 requests, ordered by length or as they come; eight rounds of workgroups and more
+    # unsplit: 63, 64, 65 requests; eight rounds of workgroups and more, from a list
     (8, 2, [33, 70] * 31 + [1], [1, 9] * 31 + [80]), (8, 2, [33, 70] * 32, [1, 9] * 32), (8, 2, [33, 70] * 32 + [1], [1, 9] * 32 + [80]),
     (32, 8, [65] * 60 + [900], [2] * 61), (32, 8, [200] * 64, [2] * 64), (32, 8, [260] * 64, [0, 1] * 32),
 ]
