@@ -59,7 +59,7 @@ CASES = [
     # unsplit and with a list: 33, 64, 65 requests; 512 and 513, where the copy no longer scans
     (8, 1, 128, "bf16", [1] * 33, [60] * 33), (8, 2, 128, "bf16", [33, 70] * 32, [1, 9] * 32), (8, 2, 128, "bf16", [33] * 65, [2] * 65),
     (4, 1, 128, "bf16", [3, 0] * 256, [1, 2] * 256), (4, 1, 128, "bf16", [3] * 513, [1] * 513),
-    # fp32: the offsets with the copy; a copy large enough for its own form (48 MB a pool), in front of either type
+    # fp32: the offsets with the copy; a copy with a launch of its own (48 MB a pool), in front of either type
     (8, 8, 64, "f32", [64, 1, 80], [16, 0, 3]), (4, 2, 64, "f32", [2] * 257, [1] * 257), (8, 8, 128, "f32", [9, 30], [300, 420]),
     (8, 8, 128, "bf16", [40], [1600]),
     # nothing cached, nothing new, nobody
@@ -77,6 +77,21 @@ def test_step_is_its_stages(case):
     ws.fill_(0xa5)
     _step(desc, c, ws, got)
     _same(want, got)
+
+
+@pytest.mark.parametrize("case", [12, 13, 14])
+def test_copy_is_the_pages(case):
+    """What the stages above are compared with: the copy by torch's indexing, absent pages left as they were."""
+    hq, hkv, d, dtype, S, k = CASES[case]
+    desc, c, ws, outputs = _buffers(case, S, k, hq, hkv, d, dtype, max(k) + 1)
+    want, got = outputs(), outputs()
+    _step(desc, c, ws, got)
+    pages = torch.cat([c["table"][r, :n] for r, n in enumerate(k)]).long()
+    here = (pages >= 0) & (pages < c["kpool"].shape[0])
+    for ctx, pool in (("kctx", "kpool"), ("vctx", "vpool")):
+        want[ctx][:-B].view(-1, B, hkv, d)[here] = c[pool][pages[here]]
+        assert torch.equal(want[ctx], got[ctx])
+    assert got["ctx_off"].tolist() == [B * sum(k[:r]) for r in range(len(k) + 1)]
 
 
 def test_refused_attention_leaves_offsets_and_copy():
