@@ -9,8 +9,8 @@
 // bf16 path: flash-style streaming over 64-key tiles with online softmax in fp32; the two
 // contractions (K.Q^T and V^T.P^T) run on the matrix cores (v_mfma_f32_32x32x16_bf16), the
 // softmax on the vector ALU.  A workgroup of eight wavefronts shares every K/V tile through
-// LDS; each wavefront owns 32 query rows of one head (the query heads of one kv head share a
-// workgroup, so a K/V tile is fetched once for the group).  K/V rows travel global -> LDS with
+// LDS; each wavefront owns 32 query rows, those of up to four heads at as few positions (the query heads of one
+// kv head share a workgroup, so a K/V tile is fetched once for the group).  K/V rows travel global -> LDS with
 // direct-to-LDS loads (no stop in registers, no LDS store instructions), three stages each.
 // The products are formed transposed (S^T = K Q^T, O^T = V^T P^T) so that a query is a
 // lane-column of the MFMA accumulator: row sums are register reductions, and the P^T
@@ -95,10 +95,15 @@ struct AttnParams {
 // behind 24 k cached tokens: 80 workgroups, 0.50 ms).  Their items are split along the keys: every part is a record of its
 // own (part = (slot + 1) << kPartBits | key tiles), leaves its unnormalised output, reference and row sum in the workspace,
 // and attn_merge_kernel combines them.  The part length c is the smallest for which all parts run in one round, or in
-// two, of one workgroup per compute unit.  Whole items take 12 us + 1.27 per key tile of the longest, 0.87 where half the
+// two, of one workgroup per compute unit.  Forecast: whole items take 12 us + 1.27 per key tile of the longest, 0.87 where half the
 // wavefronts or more have no rows; split ones 22 us, 8 for the partial states of full workgroups, and 1.7 times the tiles' time per
-// compute unit (1105 shapes of 1 .. 1000 requests, whole and split timed): the batch is split where that is less.  E.g. 137 rows
-// behind 2992 cached ones, 32 query heads over 8: 72 -> 33 us; 137 of each of 8 requests behind 1488 stay whole (49 us).
+// compute unit; the batch is split where that is less.  E.g. 137 rows behind 2992 cached ones, 32 query heads over 8: 72 -> 33 us; 137 of
+// each of 8 requests behind 1488 stay whole (49 us).
+// These are figures of an earlier kernel (1105 shapes, whole and split timed).  Now (3650 shapes, each form timed) a call from a list takes
+// 10.5 us + 1.31 / 0.81 whole and 17 + 9 + 1.45 split, one whose workgroups find their items 6.7 + 1.20 / 0.76 and 12 + 7 to 11 + 1.4 to 1.6:
+// nearly all too high, which nearly cancels where they are compared: the choice is 0.5 % behind the best on average, 3.7 % where a kv head
+// serves eight query heads or more.  Figures of its own for each of the two changed 302 choices there, 174 for the better and 88 for
+// the worse.
 //
 // The kernel is a chain of dependent steps on one compute unit, so every step is short: requests are ordered by a histogram
 // of their lengths, scans go through registers, and the search for c tries sixteen lengths at a time, one per wavefront
@@ -111,7 +116,9 @@ constexpr int kMaxSlots = 2 * kCus;   // parts of a split batch, over all kv hea
 constexpr int kStartTiles = 8;
 constexpr int kLogFull = 8;           // query rows of a workgroup's wavefronts (logarithm)
 static_assert(1 << kLogFull == kWaves * kRowsPerWave);
-// 10 ns: a key tile of a workgroup with rows for more than half its wavefronts, or for less
+// 10 ns: a key tile of a workgroup with rows for more than half its wavefronts, or for less.  (tile_time counts a tile of eight heads and up
+// to 16 rows as full, which it is not; counted by Packing 4 of 2573 calls change from split to whole, all for the worse, by up to 29 %:
+// the figures' error again.  eight_heads counts it as half.)
 constexpr int kTileFull = 127, kTileHalf = 87;
 constexpr float kWholeCost = 1200.f, kSplitCost = 2200.f, kStateCost = 800.f, kSplitTime = 1.7f;   // 10 ns; the last a factor
 constexpr int kPartBits = 20;         // key tiles of a part
