@@ -9,6 +9,8 @@
 // times as wide the three keep that order.  The products are formed transposed, S^T = K Q^T and O^T = V^T P^T, so a query is a
 // lane column: the softmax is a register reduction plus one exchange between the halves of the wavefront, and the accumulator
 // registers of S^T are the B operand of the second product as they stand.
+#include <type_traits>
+
 #include "skv_internal.h"
 
 namespace {
@@ -530,15 +532,22 @@ __global__ __launch_bounds__(64 * W, D == 64 ? 2 : 1) void attn_f32_kernel(SkvAt
     float m = -INFINITY;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) m = fmaxf(m, red_m[w][row]);
-    float l = 0.f;
-    vvec acc = {};
+    // More states are more roundings: those of eight wavefronts are summed in 64 bits, without which their results were 1 to 5 % further
+    // off than those of four.
+    using Sum = std::conditional_t<(W > 4), double, float>;
+    Sum l = 0, acc[kA] = {};
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) {
       const float f = __builtin_amdgcn_exp2f(red_m[w][row] - m);   // a wavefront without a visible key: 0
-      l += f * red_l[w][row];
-      acc += f * *(const vvec*)(red_o + (size_t)(w * kRows + row) * kRedStride + d);
+      const vvec x = *(const vvec*)(red_o + (size_t)(w * kRows + row) * kRedStride + d);
+      l += (Sum)f * red_l[w][row];
+#pragma unroll
+      for (int a = 0; a < kA; ++a) acc[a] += (Sum)f * x[a];
     }
-    *(vvec*)((float*)p.out + (out_row + (size_t)row * p.Hq) * D + d) = acc / l;
+    vvec y;
+#pragma unroll
+    for (int a = 0; a < kA; ++a) y[a] = (float)(acc[a] / l);
+    *(vvec*)((float*)p.out + (out_row + (size_t)row * p.Hq) * D + d) = y;
   }
 }
 
