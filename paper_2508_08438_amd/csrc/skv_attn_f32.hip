@@ -783,8 +783,9 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 1) void attn_f32_rows_kerne
 // 95; behind 480 99.9 / 390 and 106 / 385, so up to two rounds the width of the table decides.  Single rows in such numbers are
 // better off without tiles: 12.7 / 20.9, 24.5 / 85, 102 / 362 (two rows each behind 96 keys: 39.3 / 135 against 28.5 / 99).
 // Where every item has a compute unit to itself eight wavefronts share its keys (d 64; at 128 a SIMD holds one): 8 requests of 72 rows
-// behind 256, 8 heads, 12.5 us with four, 11.9 with eight; one of 64 behind 2048 39.0 / 32.8, 2 of 300 behind 1000 28.4 / 25.1; 16 of 64
-// behind 256, 384 items, 16.1 / 20.7.
+// behind 256, 8 heads, 12.5 us with four, 11.9 with eight; one of 64 behind 2048 37.0 / 31.9, 2 of 300 behind 1000 28.4 / 25.1; 16 of 64
+// behind 256, 384 items, 16.1 / 20.7.  Up to 256 keys, a block of 32 for each of the eight, the four have two at most and fewer states to
+// merge: one of 40 behind 80 7.0 / 7.7, 16 of 33 behind 208 9.7 / 10.3 (behind 272 11.7 either way).
 int skv_attn_f32_enqueue(const SkvAttnF32Params& p, int head_dim, void* stream) {
   const hipStream_t st = (hipStream_t)stream;
   const int64_t tiles = p.max_rows / (kRows * kWaves), slots = head_dim == 64 ? 2048 : 1024;   // slots: wavefronts at once
@@ -800,7 +801,7 @@ int skv_attn_f32_enqueue(const SkvAttnF32Params& p, int head_dim, void* stream) 
     attn_f32_rows_kernel<64><<<row_groups, kThreads, 0, st>>>(p);
   else if (head_dim == 64 && alone)
     attn_f32_kernel<64, 1><<<(int)items, 64, 0, st>>>(p);
-  else if (head_dim == 64 && items <= 256)
+  else if (head_dim == 64 && items <= 256 && (p.max_blocks > 16 || p.max_rows > 256 * (int64_t)p.n_req))
     attn_f32_kernel<64, 2 * kWaves><<<(int)items, 2 * kThreads, 0, st>>>(p);
   else if (head_dim == 64)
     attn_f32_kernel<64, kWaves><<<(int)items, kThreads, 0, st>>>(p);

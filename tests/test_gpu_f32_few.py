@@ -1,4 +1,4 @@
-"""fp32 prefill attention of few items, whose keys eight wavefronts share, is as exact as that of many, where four do: the same requests alone
+"""fp32 prefill attention of few items, whose keys eight wavefronts share (more than 256 of them), is as exact as that of many, where four do: the same requests alone
 and in enough copies, both against the fp64 oracle."""
 import numpy as np
 import pytest
@@ -23,7 +23,7 @@ def _copies(c, n):
 def test_few_items_are_as_exact():
     ratio = []
     for hq, hkv, S, k, n in [(8, 8, [64], [16], 16), (8, 2, [100, 37], [40, 21], 6), (4, 2, [300], [12], 8), (8, 8, [132], [56], 7), (4, 4, [33] * 3, [90] * 3, 14),
-                             (8, 4, [97], [10], 9), (16, 4, [60, 20], [30, 75], 5)]:
+                             (8, 4, [97], [20], 9), (16, 4, [60, 20], [30, 75], 5)]:
         c = attn_case(hq + sum(S), len(S), hq, hkv, 64, torch.float32, max(k) + 1, S, k, n_pages=sum(k) + 3)
         items = lambda m: (m * sum(S) // 32 + m * len(S)) * hq
         assert items(1) <= 256 < items(n) < 1024
@@ -32,3 +32,15 @@ def test_few_items_are_as_exact():
         assert not np.array_equal(few, many)
         ratio.append(np.linalg.norm(few - want) / np.linalg.norm(many - want))
     assert np.mean(ratio) <= 1.0, ratio
+
+
+# a table of up to 256 keys: four wavefronts here too, hence the same bits; one block or row more: eight
+@pytest.mark.parametrize("S,k,eight", [([1], [15], False), ([40, 3], [0, 5], False), ([256], [3], False), ([33] * 9, [15] * 9, False),
+                                       ([33] * 9, [16] * 9, True), ([257], [15], True)])
+def test_few_keys_take_four_wavefronts(S, k, eight):
+    c = attn_case(sum(S), len(S), 8, 8, 64, torch.float32, max(k) + 1, S, k, n_pages=sum(k) + 3)
+    n, items = next((m, i) for m in range(2, 99) if (i := (m * sum(S) // 32 + m * len(S)) * 8) > 256)
+    assert (sum(S) // 32 + len(S)) * 8 <= 256 and items < 1024
+    few, many = run_attn(c), run_attn(_copies(c, n))[: sum(S)]
+    assert np.array_equal(few, many) != eight
+    assert np.abs(few - oracle.attention(**c, n_threads=16)).max() <= 1e-5
