@@ -1263,12 +1263,17 @@ bool plan_in_place(const Layout& y, int32_t n_req) {
 // over 8, 21 items in 32 places stay whole in one round, 178 us, and are split in two, 134.  The list costs 5 us and the estimate
 // errs where lengths differ, hence kTwoTiles (1986 calls of up to 14 requests behind up to 48 k: 0 / 10 / 16 / 30 tiles take the list for
 // 253 / 159 / 115 / 72 of them; 83 / 80 / 67 / 46 are faster by 3 to 30 %, 108 / 37 / 20 / 8 slower by 3 to 9 %).
-constexpr int kTwoTiles = 16;
+// The host does not see how uneven the lengths are, and two rounds take them better than one: the only request's are even, but of several
+// whose longest part is kLongPart key tiles and more the list decides, at 4 % of such a call at most (372 of 14273 calls of 2 to 16
+// requests take it for that, 112 faster by 3 to 37 %, 9 slower by 5 to 11: 2 of 351 and 377 rows behind 9.8 and 19 k, 64 heads over 8,
+// 456 us in one round, 350; from 100 key tiles on twice the calls, and the rest of them no faster).
+constexpr int kTwoTiles = 16, kLongPart = 150;
 bool two_rounds(const Layout& y, int32_t n_req, int64_t total_q_rows, int32_t max_blocks) {
   const int64_t rows = mean_rows(n_req, total_q_rows), kt = key_tiles(rows, max_blocks);
   const int64_t items = n_req * ((rows + (1 << y.pos_log) - 1) >> y.pos_log);
   auto longest = [&](int64_t room) { return (kt + std::max<int64_t>(1, room / items) - 1) / std::max<int64_t>(1, room / items); };
-  return kStartTiles + longest(kCus / y.units) > 2 * (kStartTiles + longest(2 * kCus / y.units)) + kTwoTiles;
+  const int64_t one = longest(kCus / y.units);
+  return (n_req > 1 && one >= kLongPart) || kStartTiles + one > 2 * (kStartTiles + longest(2 * kCus / y.units)) + kTwoTiles;
 }
 // Tiles of eight heads and 32 rows, or of four heads and 64: eight take half the workgroups for requests of up to 32 rows, and
 // fewer where the last tile fits closer, but each costs half a key tile more (it may end inside one) and four heads in the one

@@ -16,6 +16,8 @@ pytestmark = pytest.mark.gpu
     (28, 65, [427, 213, 213, 213, 427, 341, 213, 427, 128, 213], 72),
     (20, 130, [110, 367, 110, 183, 183, 367, 183, 110, 110, 183], 96),
     (12, 200, [117, 117, 393, 393, 196, 393, 393, 117, 196, 117, 393], 166),
+    # as many items as leave nothing to split in one round, of lengths that do not say so: 150 key tiles and 148
+    (28, 129, [600, 150, 600, 150, 600, 150, 600, 150, 600], 72), (28, 129, [580, 150, 580, 150, 580, 150, 580, 150, 580], 0),
     # a quarter of the keys; one request of them
     (28, 65, [106, 53, 53, 53, 106, 85, 53, 106, 32, 53], 0), (28, 65, [427], 0), (12, 200, [393, 117], 0),
 ])
