@@ -7,7 +7,7 @@
 // page table the match produced) and to its own positions 0..i.
 //
 // bf16 path: flash-style streaming over 64-key tiles with online softmax in fp32; the two
-// contractions (K.Q^T and V^T.P^T) run on the matrix cores (v_mfma_f32_32x32x16_bf16), the
+// contractions (K.Q^T and V^T.P^T) run on the matrix cores (v_mfma_f32_16x16x32_bf16), the
 // softmax on the vector ALU.  A workgroup of eight wavefronts shares every K/V tile through
 // LDS; each wavefront owns 32 query rows, those of up to four heads at as few positions (the query heads of one
 // kv head share a workgroup, so a K/V tile is fetched once for the group).  K/V rows travel global -> LDS with
@@ -35,8 +35,6 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef short s16x8 __attribute__((ext_vector_type(8)));
-typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
 constexpr int kD = 128;          // head dim of the bf16 kernel
 constexpr int kBN = 64;          // keys per LDS tile
@@ -47,15 +45,16 @@ constexpr float kSumLimit = 4096.f;   // move the softmax reference when a lane'
 constexpr int kRowsPerWave = 32; // query rows per wavefront
 constexpr int kWaves = 8;        // two per SIMD: one wave's softmax overlaps the other's MFMAs
 constexpr int kThreads = kWaves * 64;
-// LDS tile layout (K and V alike): a 64-key tile is 16 segments of 4 keys, 1040 bytes apart.  Inside a segment the
-// 16-byte piece (key q of the segment, chunk c of the 256-byte row) sits at (c / 4) * 256 + q * 64 + (c % 4) * 16.
+// LDS tile layout (K and V alike): a 64-key tile is 16 segments of 4 keys, 1 KB each.  Inside segment s the
+// 16-byte piece (key q of the segment, chunk c of the 256-byte row) sits at (c / 4) * 256 + q * 64 + (c % 4 ^ turn(s)) * 16.
 // One direct-to-LDS load of a wavefront fills one segment: the hardware puts what lane i fetched at byte 16 i, so
-// lane i fetches chunk 4 (i / 16) + i % 4 of key (i / 4) % 4 -- four lanes read 64 consecutive bytes of a row.
-// The K fragment reads (ds_read_b128: 16 lanes = 16 keys, one chunk) and the V^T fragment reads
-// (ds_read_b64_tr_b16: 32 lanes = 4 keys x 64 bytes) are free of bank conflicts, and the addresses of different
-// fragments differ by constants only.
-constexpr int kSeg = 520;            // bf16 elements per segment (1040 B)
+// lane i fetches chunk 4 (i / 16) + (i % 4 ^ turn(s)) of key (i / 4) % 4 -- four lanes read 64 consecutive bytes of a row.
+// turn() makes the fragment reads free of bank conflicts: K (ds_read_b128, 16 lanes = one chunk of 16 keys) asks for four different
+// values in four segments, V^T (ds_read_b64_tr_b16, 32 lanes = 32 bytes of 4 keys in two segments) for values that differ in bit 1 in
+// neighbouring ones.  The addresses of different fragments differ by constants only (V^T's by two sets of them).
+constexpr int kSeg = 512;            // bf16 elements per segment
 constexpr int kTile = 16 * kSeg;     // bf16 elements per 64-key tile
+__device__ __forceinline__ int turn(int s) { return ((s >> 1) & 1) | ((s ^ (s >> 1)) & 1) << 1; }   // 0, 2, 3, 1
 constexpr float kLog2e = 1.4426950408889634f;
 
 struct AttnParams {
@@ -501,18 +500,26 @@ __device__ __forceinline__ bool plan_item(const AttnParams& p, int item, int uni
 }
 
 // ---- bf16 MFMA kernel --------------------------------------------------------------------------
-// max / sum of a value and the one 32 lanes away (the other half of the wavefront): v_permlane32_swap exchanges the upper
-// half of its first operand with the lower half of its second, after which `a` holds the lower half's value in both halves
-// and `b` the upper half's, so no lane select is needed
-__device__ inline float sum_halves(float x) {
-  float a = x, b = x;
+// max / sum of a value over the four lanes 16 apart: v_permlane16_swap exchanges the odd rows of 16 lanes of its first operand with
+// the even rows of its second, v_permlane32_swap the upper half of the first with the lower half of the second; on two copies of a
+// value either leaves the one row's or half's value in `a` and the other's in `b`, so no lane select is needed
+__device__ inline void swap_rows(float& a, float& b) {
   // the wait states the compiler places between a VALU write and this instruction are added by hand
-  asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(a), "+v"(b));
+  asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1\n\ts_nop 1" : "+v"(a), "+v"(b));
+}
+__device__ inline void swap_halves(float& a, float& b) { asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(a), "+v"(b)); }
+__device__ inline float sum_quads(float x) {
+  float a = x, b = x;
+  swap_rows(a, b);
+  a = b = a + b;
+  swap_halves(a, b);
   return a + b;
 }
-__device__ inline float max_halves(float x) {
+__device__ inline float max_quads(float x) {
   float a = x, b = x;
-  asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(a), "+v"(b));
+  swap_rows(a, b);
+  a = b = fmaxf(a, b);
+  swap_halves(a, b);
   return fmaxf(a, b);
 }
 
@@ -591,8 +598,8 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform by construction
-  const int l32 = lane & 31;
-  const int half = lane >> 5;
+  const int l16 = lane & 15;
+  const int quad = lane >> 4;
   __bf16* const stage = Vs + kVStages * kTile + wave * (kStageRows * kD);
 
   // ---- which piece of work: XCD-aware decode (workgroup b runs on XCD b % 8) ----
@@ -666,12 +673,12 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
   };
   const int page_w0 = window_page(0), page_w1 = window_page(1);
 
-  // ---- Q fragments (B operand of S^T = K Q^T): lane holds query l32, d = 16 ks + 8 half .. +7
+  // ---- Q fragments (B operand of S^T = K Q^T): lane holds query 16 g + l16, d = 32 ks + 8 quad .. +7
   // Rows are fetched whole (16 lanes x 16 B per row) and picked up from the wave's staging tile.  The scores leave the
   // matrix core unscaled; scale * log2(e) is applied in fp32 by the multiply-add that also subtracts the reference
   // (scaling Q itself would round it to bf16 a second time: visible when scores spread over hundreds of units).
   const float c = p.scale * kLog2e;
-  bf16x8 qf[8];
+  bf16x8 qf[2][4];   // [g][ks]
   u32x4 qv[8];
   {
     const int c16 = lane & 15;
@@ -692,29 +699,25 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
         const int rr = (lane >> 4) + 4 * i;    // row within the pass
         *(u32x4*)(stage + rr * kD + ((c16 ^ rr) << 3)) = qv[4 * pass + i];
       }
-      if ((l32 >> 4) == pass) {
-        const int rr = l32 & 15;
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks) qf[ks] = *(const bf16x8*)(stage + rr * kD + (((2 * ks + half) ^ rr) << 3));
-      }
+      for (int ks = 0; ks < 4; ++ks) qf[pass][ks] = *(const bf16x8*)(stage + l16 * kD + (((4 * ks + quad) ^ l16) << 3));
     }
   };
 
-  f32x16 o[4];   // O^T accumulators: d = 32 a + 8(e/4) + 4 half + e%4, query = l32
+  const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
+  f32x4 o[8][2];   // O^T accumulators: o[a][g][i]: d = 16 a + 4 quad + i, query 16 g + l16
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) o[a][e] = 0.f;
+  for (int a = 0; a < 8; ++a) o[a][0] = o[a][1] = zero4;
 
   // ---- global -> LDS, without a stop in registers ----
   // A tile is four 16-key groups; a group is one page of the pool or 16 consecutive new rows.  Each wavefront
   // moves two segments of a tile, half a group (2w and 2w + 1: keys 8w ..), with direct-to-LDS loads: lane i
-  // fetches chunk 4 (i / 16) + i % 4 of key (i / 4) % 4 of the segment and the hardware puts it at slot i.  Both take the
+  // fetches its piece of the segment (turn()) and the hardware puts it at slot i.  Both take the
   // group's base as the buffer's and constant offsets: no vector address is formed.
   const unsigned row_bytes = (unsigned)p.Hkv * kD * 2u;
   const int t_row = (wave & 1) * 8 + ((lane >> 2) & 3);      // row of the 16-key group this lane fetches, and 4 further on
-  const unsigned t_col = (unsigned)((lane >> 4) * 4 + (lane & 3)) * 16u;
-  const unsigned t_off = (unsigned)t_row * row_bytes + t_col;
+  auto t_col = [&](int seg) { return (unsigned)(quad * 4 + ((lane & 3) ^ turn(seg))) * 16u; };
+  const unsigned t_off = (unsigned)t_row * row_bytes + t_col(2 * wave);
   // Group base addresses, one 16-key group per lane for 64 groups (16 tiles, a "window"): a pool page, 16 new rows,
   // or 0 when the group has no data (past the end of the sequence, or a page id outside the pool): an empty buffer, whose rows
   // arrive as zeros.
@@ -731,7 +734,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
   window_bases(1, page_w1, ak_nxt, av_nxt);
   typedef __attribute__((address_space(3))) void lds_void;
   const int group = wave >> 1;                               // 16-key group of this wave's segments
-  const unsigned t_off4 = t_off + 4u * row_bytes;            // (a scalar offset would have to lie inside the buffer)
+  const unsigned t_off4 = (unsigned)(t_row + 4) * row_bytes + t_col(2 * wave + 1);   // (a scalar offset would have to lie inside the buffer)
   // one pool (K or V) of tile t into an LDS stage; `base`: of the wave's group.  Where the sequence ends inside the tile so does
   // the buffer: what lies behind arrives as zeros, and the causal mask keeps it out.
   auto issue_half_tile = [&]<bool kWhole>(uint64_t base, int t, __bf16* dst_stage) __attribute__((always_inline)) {
@@ -778,77 +781,84 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
   // ---- the steps of the pipeline ----
   // Work advances in 32-key sub-tiles (half an LDS tile), three of them in flight: half-step h puts the scores of
   // sub-tile h + 1 and the output update with sub-tile h - 1 on the matrix core and computes the softmax of sub-tile
-  // h on the vector ALU.  Nothing inside a half-step depends on anything else inside it, so its 16 MFMAs alternate
-  // (score, output, score, ...) with two or three vector instructions behind each: the vector work runs beside the
+  // h on the vector ALU.  Nothing inside a half-step depends on anything else inside it, so its 32 MFMAs alternate
+  // (two score, two output, two score, ...) with two or three vector instructions behind each pair: the vector work runs beside the
   // MFMAs instead of between them.  Two score accumulators and two P^T buffers alternate.
-  f32x16 s[2];      // S^T of two consecutive sub-tiles: [32 keys][32 queries], raw dot products
-  bf16x8 pb[2][2];  // P^T as B operands: [sub-tile parity][16-key group]
+  // A fragment serves the two query groups: 16x16x32 takes the fragment reads and the cycles of 32x32x16 and moves half as much through
+  // the accumulators, and the chip's clock under matrix load depends on what moves (MFMAs alone on N(0,1) operands 1765 -> 2044 TFLOP/s;
+  // with the fragment reads and this softmax's instructions beside them 1440 -> 1500).  Clock in this loop 1.70 -> 1.89 GHz, 64 requests of
+  // 100 .. 9000 rows 14.0 -> 13.3 ms (1150 -> 1211 TFLOP/s), of 1070 791 -> 756 us.
+  typedef f32x4 Scores[2][2];   // S^T of a sub-tile: [k][g][i]: key 16 k + 4 quad + i, query 16 g + l16; raw dot products
+  Scores s[2];
+  bf16x8 pb[2][2];  // P^T as B operands: [sub-tile parity][g], keys 4 quad .. + 3 and 16 + 4 quad .. + 3
   bf16x8 kfr[4];    // K fragment ring: runs four fragments ahead, across sub-tiles
   bf16x8 vfr[4];    // V^T fragment ring, likewise
-  float m_ref = 0.f;   // reference the exponentials are taken against (score * scale * log2(e): exp2 units), per query
-  float l_run = 0.f;   // running row sum over this lane-half's keys
+  float m_ref[2] = {0.f, 0.f};   // reference the exponentials are taken against (score * scale * log2(e): exp2 units), per query
+  float l_run[2] = {0.f, 0.f};   // running row sum over this lane's keys
 #pragma unroll
-  for (int e = 0; e < 16; ++e) s[0][e] = s[1][e] = 0.f;
-  const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  for (int k = 0; k < 8; ++k) s[k >> 2][(k >> 1) & 1][k & 1] = zero4;
 #pragma unroll
   for (int e = 0; e < 8; ++e) pb[0][0][e] = pb[0][1][e] = pb[1][0][e] = pb[1][1][e] = (__bf16)0.f;
-  // K fragment (ks, mt): lane (l32, half) wants key l32 + 32 mt, chunk 2 ks + half.  In bf16 elements:
-  //   segment (l32 / 4 + 8 mt) * kSeg + key-in-segment (l32 % 4) * 32 + (ks / 2) * 128 + (2 (ks % 2) + half) * 8
-  const int k_lane = (l32 >> 2) * kSeg + (l32 & 3) * 32 + half * 8;
-  // The PV A operand wants, per lane (d = 32 a + l32), the eight keys {4 half + 0..3, 8 + 4 half + 0..3}
-  // of a 16-key group -- the keys this lane-half's P^T registers hold.  Each quad comes from one LDS
+  // K fragment i = (k, ks): lane (l16, quad) wants key 16 k + l16 of the sub-tile, chunk 4 ks + quad.
+  const int k_lane = (l16 >> 2) * kSeg + (l16 & 3) * 32 + (quad ^ turn(l16 >> 2)) * 8;
+  // The PV A operand wants, per lane (d = 16 a + l16), the eight keys {4 quad + 0..3, 16 + 4 quad + 0..3}
+  // of the sub-tile -- the keys this lane's P^T registers hold.  Each four come from one LDS
   // transpose load: within 16 lanes, lane i supplies the address of 4 consecutive d of key (i / 4) at d
-  // offset 4 (i % 4) and receives d offset i of the four keys.  For fragment (g16, a) the lane's key is
-  // 16 g16 + 4 half + (lane % 16) / 4 (segment 4 g16 + half, second load two segments on) and its 8 bytes are piece
-  // lane % 2 of chunk 4 a + 2 ((lane / 16) % 2) + (lane % 4) / 2.
-  const int v_lane = half * kSeg + ((lane & 15) >> 2) * 32 + (2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) * 8 + 4 * (lane & 1);
-  // fragment addresses are LDS byte addresses: a per-lane base plus constants that fit the offset field
-  auto k_frag = [&](uint32_t kb, int ks, int more = 0) __attribute__((always_inline)) {   // kb + more: stage + k_lane + mt * 8 kSeg
-    return lds_read_b128(kb, ((ks >> 1) * 128 + (ks & 1) * 16) * 2 + more);
+  // offset 4 (i % 4) and receives d offset i of the four keys.  They lie in segment quad (second load: four
+  // segments on); the lane's 8 bytes are piece lane % 2 of chunk 2 a + (lane % 4) / 2.
+  const int v_lane = quad * kSeg + (l16 >> 2) * 32 + (((lane & 3) >> 1) ^ turn(quad)) * 8 + 4 * (lane & 1);
+  const uint32_t k_base = lds_addr(Ks + k_lane), v_base[2] = {lds_addr(Vs + v_lane), lds_addr(Vs + (v_lane ^ 16))};   // of even and odd a
+  auto k_frag = [&](uint32_t at, int i, int more = 0) __attribute__((always_inline)) {   // at + more: byte offset of the sub-tile
+    return lds_read_b128(k_base + at, ((i >> 2) * 4 * kSeg + (i & 3) * 128) * 2 + more);
   };
-  auto v_frag = [&](uint32_t vb, int j, int more = 0) __attribute__((always_inline)) {   // vb + more: stage + v_lane + h * 8 kSeg; j = (g, a)
-    const int off = ((j >> 2) * 4 * kSeg + (j & 3) * 128) * 2 + more;
-    const s16x4 lo = lds_read_tr16_b64(vb, off);
-    const s16x4 hi = lds_read_tr16_b64(vb, off + 2 * kSeg * 2);
+  auto v_frag = [&](uint32_t at, int a, int more = 0) __attribute__((always_inline)) {
+    const int off = (a >> 1) * 256 + more;
+    const s16x4 lo = lds_read_tr16_b64(v_base[a & 1] + at, off);
+    const s16x4 hi = lds_read_tr16_b64(v_base[a & 1] + at, off + 4 * kSeg * 2);
     return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
   };
   // causal mask of sub-tile u (keys 32 u ..), applied where the sub-tile reaches past the wave's first row
-  auto mask = [&](f32x16& x, int u) __attribute__((always_inline)) {
+  auto mask = [&](Scores& x, int u) __attribute__((always_inline)) {
     const int key0 = u * 32;
     if (key0 + 31 > L + pos0) {
-      const int limit = L + pos0 + (l32 >> hl_log);  // last visible key of this lane's query
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int key = key0 + (e >> 2) * 8 + half * 4 + (e & 3);
-        if (key > limit) x[e] = -INFINITY;
+      for (int g = 0; g < 2; ++g) {
+        const int limit = L + pos0 + ((16 * g + l16) >> hl_log);  // last visible key of this lane's query
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (key0 + (e >> 2) * 16 + quad * 4 + (e & 3) > limit) x[e >> 2][g][e & 3] = -INFINITY;
       }
     }
   };
-  auto row_max = [&](const f32x16& x) __attribute__((always_inline)) {
-    float m4[4];   // four independent reduction chains
+  auto row_max = [&](const Scores& x, int g) __attribute__((always_inline)) {
+    float m4[4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) m4[k] = fmaxf(x[k], x[k + 4]);
-#pragma unroll
-    for (int e = 8; e < 16; ++e) m4[e & 3] = fmaxf(m4[e & 3], x[e]);
-    float mx = fmaxf(fmaxf(m4[0], m4[1]), fmaxf(m4[2], m4[3]));
-    return max_halves(mx);
+    for (int k = 0; k < 4; ++k) m4[k] = fmaxf(x[0][g][k], x[1][g][k]);
+    return max_quads(fmaxf(fmaxf(m4[0], m4[1]), fmaxf(m4[2], m4[3])));
   };
-  // exponentials of one pair of scores -> packed bf16, plain fp32 adds for the row sum (the packed dot-product
-  // instruction that would add the pair in one step does not run beside the MFMAs, the adds do)
+  // Exponential k of a lane's sixteen: key group k / 8, query group (k / 4) % 2; plain fp32 adds for the row sum (the packed
+  // dot-product instruction that would add a pair in one step does not run beside the MFMAs, the adds do).
   float ssum[2];
-  bf16x8 pk;
-  auto exp_pair = [&](const f32x16& cur, int i, bf16x8 (&p_make)[2], float& e0, float& e1, int part) __attribute__((always_inline)) {
-    if (part == 0) {
-      e0 = __builtin_amdgcn_exp2f(__builtin_fmaf(cur[2 * i], c, -m_ref));
-      e1 = __builtin_amdgcn_exp2f(__builtin_fmaf(cur[2 * i + 1], c, -m_ref));
-    } else {
-      f32x2 pr = {e0, e1};
-      const bf16x2 cv = __builtin_convertvector(pr, bf16x2);
-      ssum[0] += e0;
-      ssum[1] += e1;
-      pk[2 * (i & 3)] = cv[0];
-      pk[2 * (i & 3) + 1] = cv[1];
-      if ((i & 3) == 3) p_make[i >> 2] = pk;
+  auto arg = [&](const Scores& cur, int k) __attribute__((always_inline)) {
+    const int g = (k >> 2) & 1;
+    return __builtin_fmaf(cur[k >> 3][g][k & 3], c, -m_ref[g]);
+  };
+  auto pack = [&](int k, float e0, float e1, bf16x8 (&p_make)[2]) __attribute__((always_inline)) {   // pair k
+    const f32x2 pr = {e0, e1};
+    const bf16x2 cv = __builtin_convertvector(pr, bf16x2);
+    const int at = (k >> 2) * 4 + 2 * (k & 1);
+    p_make[(k >> 1) & 1][at] = cv[0];
+    p_make[(k >> 1) & 1][at + 1] = cv[1];
+  };
+  auto tripped = [&]() __attribute__((always_inline)) { return __any(!(ssum[0] <= kSumLimit) || !(ssum[1] <= kSumLimit)); };
+  auto exps = [&](const Scores& cur, bf16x8 (&p_make)[2]) __attribute__((always_inline)) {   // all of them
+    ssum[0] = ssum[1] = 0.f;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const float e0 = __builtin_amdgcn_exp2f(arg(cur, 2 * k)), e1 = __builtin_amdgcn_exp2f(arg(cur, 2 * k + 1));
+      pack(k, e0, e1, p_make);
+      ssum[(k >> 1) & 1] += e0;
+      ssum[(k >> 1) & 1] += e1;
     }
   };
   // The softmax keeps a reference per query; exponentials are taken against it as it stands, which leaves the
@@ -856,85 +866,82 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
   // at least kSumLimit / 16 above the reference; infinities and NaNs trip it too) is the reference moved to that
   // sub-tile's row maximum: O and the row sum are rescaled and this sub-tile's exponentials are taken again.  This
   // happens between half-steps, after the output update that still belongs to the old reference has been issued.
-  auto move_reference = [&](const f32x16& cur, bf16x8 (&p_make)[2]) __attribute__((always_inline)) {
-    const float mx = row_max(cur) * c;
-    const bool trip = !(max_halves(ssum[0] + ssum[1]) <= kSumLimit);
-    const float m_new = trip ? mx : m_ref;
-    const float alpha = __builtin_amdgcn_exp2f(m_ref - m_new);
-    m_ref = m_new;
-    l_run *= alpha;
+  auto move_reference = [&](const Scores& cur, bf16x8 (&p_make)[2]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+    for (int g = 0; g < 2; ++g) {
+      const float mx = row_max(cur, g) * c;
+      const bool trip = !(max_quads(ssum[g]) <= kSumLimit);
+      const float m_new = trip ? mx : m_ref[g];
+      const float alpha = __builtin_amdgcn_exp2f(m_ref[g] - m_new);
+      m_ref[g] = m_new;
+      l_run[g] *= alpha;
 #pragma unroll
-      for (int e = 0; e < 16; ++e) o[a][e] *= alpha;
-    ssum[0] = ssum[1] = 0.f;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      float e0, e1;
-      exp_pair(cur, i, p_make, e0, e1, 0);
-      exp_pair(cur, i, p_make, e0, e1, 1);
+      for (int a = 0; a < 8; ++a) o[a][g] *= alpha;
     }
+    exps(cur, p_make);
   };
   auto active = [&](int u) __attribute__((always_inline)) { return u * 32 < wave_key_end; };
-  // One half-step.  kb / kb_next: K of sub-tiles h + 1 and h + 2; vb / vb_next: V of sub-tiles h - 1 and h.
+  // One half-step.  kb / kb_next: K of sub-tiles h + 1 and h + 2 (byte offsets in LDS); vb / vb_next: V of sub-tiles h - 1 and h.
   // The rings hold fragments 0..3 of sub-tile h + 1 (K) and of sub-tile h - 1 (V^T) on entry and are refilled behind
   // each MFMA with fragments 4..7 and then with fragments 0..3 of the following sub-tile.
-  // Fast form (every stage at work, no masked key in sub-tile h): the 16 MFMAs alternate and carry the softmax between
-  // them; the two fragments of a pair-step are waited for together, four pair-steps after their request, with nine younger
-  // reads.  kOff ..: constant parts of the four addresses.
+  // Fast form (every stage at work, no masked key in sub-tile h): the 32 MFMAs alternate and carry the softmax between
+  // them; a fragment is waited for four steps after its request, with the ten or eleven reads behind it outstanding.  kOff ..: constant parts of the four addresses.
   auto half_step_fast = [&]<bool kMask, int kOff = 0, int kOffNext = 0, int vOff = 0, int vOffNext = 0>(
-                                        int h, uint32_t kb, uint32_t kb_next, uint32_t vb, uint32_t vb_next, f32x16& dst,
-                                        f32x16& cur, bf16x8 (&p_use)[2], bf16x8 (&p_make)[2]) __attribute__((always_inline)) {
+                                        int h, uint32_t kb, uint32_t kb_next, uint32_t vb, uint32_t vb_next, Scores& dst,
+                                        Scores& cur, bf16x8 (&p_use)[2], bf16x8 (&p_make)[2]) __attribute__((always_inline)) {
     if (kMask) mask(cur, h);
     ssum[0] = ssum[1] = 0.f;
-    // One exponential behind every MFMA (and one in front of the first's reads), never two in a row: the transcendental
+    // One exponential behind the first MFMA of every pair (and one in front of them all), never two in a row: the transcendental
     // unit takes about four issue slots per instruction but works beside the issue port, so a second one right behind the
-    // first would hold the wavefront until the unit is free again.  A pair is packed and summed one step later; the last one
-    // comes a step early, so that the sums are there when the last MFMA has been issued.
-    float e[16];
-    auto ex = [&](int k) __attribute__((always_inline)) { e[k] = __builtin_amdgcn_exp2f(__builtin_fmaf(cur[k], c, -m_ref)); };
-    auto pack = [&](int k) __attribute__((always_inline)) {   // pair k
-      f32x2 pr = {e[2 * k], e[2 * k + 1]};
-      const bf16x2 cv = __builtin_convertvector(pr, bf16x2);
-      pk[2 * (k & 3)] = cv[0];
-      pk[2 * (k & 3) + 1] = cv[1];
-      if ((k & 3) == 3) p_make[k >> 2] = pk;
-    };
+    // first would hold the wavefront until the unit is free again.  Its argument is worked out a pair ahead, for the same reason; a pair of
+    // weights is packed and summed one step later; the last one comes a step early, so that the sums are there when the last MFMA has been
+    // issued.  (Argument and exponential together behind the pair, one wait for both fragments: 1 to 3 % slower.)
+    float e[16], arg_next = arg(cur, 1);
+    auto sum = [&](int k) __attribute__((always_inline)) { ssum[(k >> 2) & 1] += e[k]; };
+    e[0] = __builtin_amdgcn_exp2f(arg(cur, 0));
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      lds_wait(9, kfr[i & 3], vfr[i & 3]);
-      dst = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfr[i & 3], qf[i], i == 0 ? zero16 : dst, 0, 0, 0);
-      if (i == 0) ex(0);
+      const int k = i >> 2, ks = i & 3;
+      lds_wait(11, kfr[i & 3]);   // behind it: its V^T fragment, three steps
+      dst[k][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kfr[i & 3], qf[0][ks], ks == 0 ? zero4 : dst[k][0], 0, 0, 0);
+      e[2 * i + 1] = __builtin_amdgcn_exp2f(arg_next);
+      dst[k][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kfr[i & 3], qf[1][ks], ks == 0 ? zero4 : dst[k][1], 0, 0, 0);
       kfr[i & 3] = i < 4 ? k_frag(kb, i + 4, kOff) : k_frag(kb_next, i - 4, kOffNext);
-      ex(2 * i + 1);
-      if (i > 0) {
-        pack(i - 1);
-        ssum[0] += e[2 * i - 2];
-      }
+      if (i < 7) arg_next = arg(cur, 2 * i + 2);
+      if (i > 0) sum(2 * i - 2);
       __builtin_amdgcn_sched_barrier(0);
-      o[i & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vfr[i & 3], p_use[i >> 2], o[i & 3], 0, 0, 0);
+      lds_wait(10, vfr[i & 3]);   // behind it: three steps, a K fragment
+      o[i][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vfr[i & 3], p_use[0], o[i][0], 0, 0, 0);
+      if (i < 7) e[2 * i + 2] = __builtin_amdgcn_exp2f(arg_next);
+      o[i][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vfr[i & 3], p_use[1], o[i][1], 0, 0, 0);
       vfr[i & 3] = i < 4 ? v_frag(vb, i + 4, vOff) : v_frag(vb_next, i - 4, vOffNext);
-      if (i < 7) ex(2 * i + 2);
-      if (i > 0) ssum[1] += e[2 * i - 1];
+      if (i < 7) arg_next = arg(cur, 2 * i + 3);
+      if (i > 0) {
+        pack(i - 1, e[2 * i - 2], e[2 * i - 1], p_make);
+        sum(2 * i - 1);
+      }
       if (i == 7) {
-        pack(7);
-        ssum[0] += e[14];
-        ssum[1] += e[15];
+        pack(7, e[14], e[15], p_make);
+        sum(14);
+        sum(15);
       }
       __builtin_amdgcn_sched_barrier(0);
     }
-    if (__builtin_expect(__any(!(ssum[0] + ssum[1] <= kSumLimit)), 0)) move_reference(cur, p_make);
-    l_run += ssum[0] + ssum[1];
+    if (__builtin_expect(tripped(), 0)) move_reference(cur, p_make);
+    l_run[0] += ssum[0];
+    l_run[1] += ssum[1];
   };
   // General form (first and last iterations of a wave): each stage is tested and runs as a block of its own; an MFMA waits
   // for its fragment with the three requested since behind it.
-  auto half_step_slow = [&](int h, uint32_t kb, uint32_t kb_next, uint32_t vb, uint32_t vb_next, f32x16& dst,
-                            f32x16& cur, bf16x8 (&p_use)[2], bf16x8 (&p_make)[2]) __attribute__((always_inline)) {
+  auto half_step_slow = [&](int h, uint32_t kb, uint32_t kb_next, uint32_t vb, uint32_t vb_next, Scores& dst,
+                            Scores& cur, bf16x8 (&p_use)[2], bf16x8 (&p_make)[2]) __attribute__((always_inline)) {
     if (active(h + 1)) {
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         lds_wait(3, kfr[i & 3]);
-        dst = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfr[i & 3], qf[i], i == 0 ? zero16 : dst, 0, 0, 0);
+#pragma unroll
+        for (int g = 0; g < 2; ++g)
+          dst[i >> 2][g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kfr[i & 3], qf[g][i & 3], (i & 3) == 0 ? zero4 : dst[i >> 2][g], 0, 0, 0);
         kfr[i & 3] = i < 4 ? k_frag(kb, i + 4) : k_frag(kb_next, i - 4);
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -943,7 +950,8 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         lds_wait(6, vfr[i & 3]);
-        o[i & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vfr[i & 3], p_use[i >> 2], o[i & 3], 0, 0, 0);
+#pragma unroll
+        for (int g = 0; g < 2; ++g) o[i][g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vfr[i & 3], p_use[g], o[i][g], 0, 0, 0);
         vfr[i & 3] = i < 4 ? v_frag(vb, i + 4) : v_frag(vb_next, i - 4);
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -954,15 +962,10 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
     }
     if (active(h)) {
       mask(cur, h);
-      ssum[0] = ssum[1] = 0.f;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        float e0, e1;
-        exp_pair(cur, i, p_make, e0, e1, 0);
-        exp_pair(cur, i, p_make, e0, e1, 1);
-      }
-      if (__builtin_expect(__any(!(ssum[0] + ssum[1] <= kSumLimit)), 0)) move_reference(cur, p_make);
-      l_run += ssum[0] + ssum[1];
+      exps(cur, p_make);
+      if (__builtin_expect(tripped(), 0)) move_reference(cur, p_make);
+      l_run[0] += ssum[0];
+      l_run[1] += ssum[1];
     }
     // whatever follows finds every fragment of the rings in place
     lds_wait(0, kfr[0], kfr[1], kfr[2], kfr[3]);
@@ -975,28 +978,30 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
   load_v_tile(0, 0);
   stage_q();
   tile_barrier();
-  const uint32_t k_base = lds_addr(Ks + k_lane), v_base = lds_addr(Vs + v_lane);
   constexpr int kStageBytes = kTile * 2, kHalfBytes = 8 * kSeg * 2;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    kfr[j] = k_frag(k_base, j);
+    kfr[j] = k_frag(0, j);
     vfr[j] = kfr[j];   // defined; the V^T ring fills itself during half-step 0
   }
   if (active(0)) {
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {
-      lds_wait(3, kfr[ks & 3]);
-      s[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfr[ks & 3], qf[ks], ks == 0 ? zero16 : s[0], 0, 0, 0);
-      kfr[ks & 3] = ks < 4 ? k_frag(k_base, ks + 4) : k_frag(k_base + kHalfBytes, ks - 4);
+    for (int i = 0; i < 8; ++i) {
+      lds_wait(3, kfr[i & 3]);
+#pragma unroll
+      for (int g = 0; g < 2; ++g)
+        s[0][i >> 2][g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kfr[i & 3], qf[g][i & 3], (i & 3) == 0 ? zero4 : s[0][i >> 2][g], 0, 0, 0);
+      kfr[i & 3] = i < 4 ? k_frag(0, i + 4) : k_frag(0, i - 4, kHalfBytes);
       __builtin_amdgcn_sched_barrier(0);
     }
     // (idle states for the last MFMA: the compiler's wait-state insertion does not look through the branch inside
     // mask(), and the row maximum behind it would read score registers the matrix core has not written yet)
-    asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 3" : "+v"(s[0]));
+    asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 3" : "+v"(s[0][0][0]), "+v"(s[0][0][1]), "+v"(s[0][1][0]), "+v"(s[0][1][1]));
     mask(s[0], 0);
     // key 0 is visible to every query; finite also where its score and those of the other first keys are -infinity (the
     // reference then moves with the first score above it, and a part without any leaves nothing)
-    m_ref = fmaxf(row_max(s[0]) * c, -3.0e38f);
+#pragma unroll
+    for (int g = 0; g < 2; ++g) m_ref[g] = fmaxf(row_max(s[0], g) * c, -3.0e38f);
   }
 
   // ---- main loop.  Iteration kt (two half-steps) reads K(kt), K(kt + 1), V(kt - 1), V(kt).  It starts behind the
@@ -1022,10 +1027,10 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
     const int st1 = st0 == 2 ? 0 : st0 + 1;    // stage of tile kt + 1
     const int st2 = st1 == 2 ? 0 : st1 + 1;    // stage of tiles kt + 2 and kt - 1
     requests.template operator()<false>(kt, st1, st2);
-    const uint32_t kb0 = k_base + st0 * kStageBytes;   // K(kt)
-    const uint32_t kb1 = k_base + st1 * kStageBytes;   // K(kt + 1)
-    const uint32_t vbp = v_base + st2 * kStageBytes;   // V(kt - 1)
-    const uint32_t vb0 = v_base + st0 * kStageBytes;   // V(kt)
+    const uint32_t kb0 = st0 * kStageBytes;   // K(kt)
+    const uint32_t kb1 = st1 * kStageBytes;   // K(kt + 1)
+    const uint32_t vbp = st2 * kStageBytes;   // V(kt - 1)
+    const uint32_t vb0 = st0 * kStageBytes;   // V(kt)
     if (kMasked) {
       half_step_fast.template operator()<true>(2 * kt, kb0 + kHalfBytes, kb1, vbp + kHalfBytes, vb0, s[1], s[0], pb[1], pb[0]);
       prep_bases(kt + 1);
@@ -1043,9 +1048,9 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
     constexpr int st1 = (kSt + 1) % 3, st2 = (kSt + 2) % 3;
     constexpr int k0 = kSt * kStageBytes, k1 = st1 * kStageBytes, vp = st2 * kStageBytes, half = kHalfBytes;
     requests.template operator()<true>(kt, st1, st2);
-    half_step_fast.template operator()<false, k0 + half, k1, vp + half, k0>(2 * kt, k_base, k_base, v_base, v_base, s[1], s[0], pb[1], pb[0]);
+    half_step_fast.template operator()<false, k0 + half, k1, vp + half, k0>(2 * kt, 0, 0, 0, 0, s[1], s[0], pb[1], pb[0]);
     prep_bases(kt + 1);
-    half_step_fast.template operator()<false, k1, k1 + half, k0, k0 + half>(2 * kt + 1, k_base, k_base, v_base, v_base, s[0], s[1], pb[0], pb[1]);
+    half_step_fast.template operator()<false, k1, k1 + half, k0, k0 + half>(2 * kt + 1, 0, 0, 0, 0, s[0], s[1], pb[0], pb[1]);
     tile_barrier();
   };
   int kt = 0;
@@ -1065,48 +1070,42 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
   // hold registers through it)
   int lane_e;
   asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane_e));
-  const int row_e = lane_e & 31, half_e = lane_e >> 5;
+  const int row_e = lane_e & 15, quad_e = lane_e >> 4;
   if (part) {
     const int slot = (part >> kPartBits) - 1;
     const int unit = kvh * n_hg + hg;
     f32x4* dst = (f32x4*)(p.partials + ((size_t)slot * p.Hkv * n_hg + unit) * kSlotFloats + (size_t)wave * (64 * 66)) + lane_e;
-    const float l_all = sum_halves(l_run);
-    if (pos0 + (row_e >> hl_log) >= row1) return;   // not a row of the tile: never read
+    float* const ml = (float*)(dst - lane_e + 16 * 64) + row_e;
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+    for (int g = 0; g < 2; ++g) {
+      const float l_all = sum_quads(l_run[g]);
+      if (pos0 + ((16 * g + row_e) >> hl_log) >= row1) continue;   // not a row of the tile: never read
 #pragma unroll
-      for (int i4 = 0; i4 < 4; ++i4)
-        dst[(a * 4 + i4) * 64] = f32x4{o[a][i4 * 4], o[a][i4 * 4 + 1], o[a][i4 * 4 + 2], o[a][i4 * 4 + 3]};
-    float* ml = (float*)(dst - lane_e + 16 * 64) + lane_e;
-    ml[0] = m_ref;
-    ml[64] = l_all;
+      for (int a = 0; a < 8; ++a) dst[(a * 2 + g) * 64] = o[a][g];
+      if (quad_e == 0) {
+        ml[16 * g] = m_ref[g];
+        ml[64 + 16 * g] = l_all;
+      }
+    }
     return;
   }
 
-  // ---- normalise and store.  A lane holds query l32 with d = 32 a + 8 (e/4) + 4 half + e%4, i.e. sixteen 8-byte
-  // pieces of one output row.  They go through the wave's staging tile, 16 rows at a time, and leave as whole
+  // ---- normalise and store.  A lane holds queries l16 and 16 + l16 with d = 16 a + 4 quad + i, i.e. eight 8-byte
+  // pieces of each one's output row.  They go through the wave's staging tile, 16 rows at a time, and leave as whole
   // 256-byte rows.
   {
-    const float lsum = sum_halves(l_run);
-    const float inv = 1.0f / lsum;
     const int c16 = lane_e & 15;
 #pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
-      if ((row_e >> 4) == pass) {
-        const int rr = row_e & 15;
-        __bf16* row = stage + rr * kD;
+      const float inv = 1.0f / sum_quads(l_run[pass]);
+      __bf16* const row = stage + row_e * kD;
 #pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-          for (int i4 = 0; i4 < 4; ++i4) {
-            f32x2 x0 = {o[a][i4 * 4 + 0] * inv, o[a][i4 * 4 + 1] * inv};
-            f32x2 x1 = {o[a][i4 * 4 + 2] * inv, o[a][i4 * 4 + 3] * inv};
-            bf16x2 y0 = __builtin_convertvector(x0, bf16x2);
-            bf16x2 y1 = __builtin_convertvector(x1, bf16x2);
-            u32x2 wv = {__builtin_bit_cast(uint32_t, y0), __builtin_bit_cast(uint32_t, y1)};
-            const int chunk = a * 4 + i4;   // d = 8 chunk + 4 half .. + 3
-            *(u32x2*)(row + (((chunk ^ rr) << 3) + 4 * half_e)) = wv;
-          }
+      for (int a = 0; a < 8; ++a) {
+        const f32x4 x = o[a][pass] * inv;
+        const bf16x2 y0 = __builtin_convertvector(f32x2{x[0], x[1]}, bf16x2);
+        const bf16x2 y1 = __builtin_convertvector(f32x2{x[2], x[3]}, bf16x2);
+        const int chunk = 2 * a + (quad_e >> 1);   // its half quad % 2
+        *(u32x2*)(row + (((chunk ^ row_e) << 3) + 4 * (quad_e & 1))) = u32x2{__builtin_bit_cast(uint32_t, y0), __builtin_bit_cast(uint32_t, y1)};
       }
       // same wave wrote and reads: the LDS operations of one wave complete in order
 #pragma unroll
@@ -1123,7 +1122,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
 
 // ---- merge of the parts of split items -----------------------------------------------------------
 // One workgroup per (split item, kv head and head group, wavefront of the attention kernel); its wavefront q combines
-// d = 16 q .. 16 q + 15 of that wavefront's 32 rows, each lane what the same lane of every part wrote: coalesced 1 KB reads.
+// d = 32 (q % 4) .. + 31 of 16 of that wavefront's 32 rows, each lane what the same lane of every part wrote: coalesced 1 KB reads.
 // Bound by latency: eight parts' states travel together and are folded into a running maximum, so the usual item takes one or
 // two trips to memory (references first and outputs after them, four parts at a time: 10.7 us for 10 parts of 3 items,
 // now 6.5).
@@ -1148,7 +1147,8 @@ __device__ __forceinline__ void merge_parts(const AttnParams& p, int n_blocks) {
     const Packing pk = packing(p.heads_per_wg);
     int row, head;
     pk.wave(wave, row0, head, row);
-    row += (lane & 31) >> pk.heads_log;
+    const int at = 16 * (q >> 2) + (lane & 15);   // of the 32 rows
+    row += at >> pk.heads_log;
     if (row >= row1) continue;
     const size_t stride = (size_t)units * kSlotFloats;   // from one part to the next
     const float* src = p.partials + ((size_t)slot * units + unit) * kSlotFloats + (size_t)wave * (64 * 66);
@@ -1160,10 +1160,10 @@ __device__ __forceinline__ void merge_parts(const AttnParams& p, int n_blocks) {
 #pragma unroll
       for (int k = 0; k < kMergeParts; ++k) {
         const float* s = src + min(j0 + k, parts - 1) * stride;
-        ms[k] = s[64 * 64 + lane];
-        ls[k] = s[64 * 65 + lane];
+        ms[k] = s[64 * 64 + at];
+        ls[k] = s[64 * 65 + at];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) x[k][i] = ((const f32x4*)s)[(2 * q + i) * 64 + lane];
+        for (int i = 0; i < 2; ++i) x[k][i] = ((const f32x4*)s)[((2 * (q & 3) + i) * 2 + (q >> 2)) * 64 + lane];
       }
 #pragma unroll
       for (int k = 0; k < kMergeParts; ++k) m_new = fmaxf(m_new, ms[k]);
@@ -1183,13 +1183,13 @@ __device__ __forceinline__ void merge_parts(const AttnParams& p, int n_blocks) {
       }
     }
     const float inv = 1.0f / l;
-    head += kvh * (p.Hq / p.Hkv) + hg * p.heads_per_wg + (lane & ((1 << pk.heads_log) - 1));
-    __bf16* dst = (__bf16*)p.out + ((size_t)(qbase + row) * p.Hq + head) * kD + 16 * q + 4 * (lane >> 5);
+    head += kvh * (p.Hq / p.Hkv) + hg * p.heads_per_wg + (at & ((1 << pk.heads_log) - 1));
+    __bf16* dst = (__bf16*)p.out + ((size_t)(qbase + row) * p.Hq + head) * kD + 32 * (q & 3) + 4 * (lane >> 4);
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       const bf16x2 y0 = __builtin_convertvector((f32x2{acc[i][0] * inv, acc[i][1] * inv}), bf16x2);
       const bf16x2 y1 = __builtin_convertvector((f32x2{acc[i][2] * inv, acc[i][3] * inv}), bf16x2);
-      *(u32x2*)(dst + 8 * i) = u32x2{__builtin_bit_cast(uint32_t, y0), __builtin_bit_cast(uint32_t, y1)};
+      *(u32x2*)(dst + 16 * i) = u32x2{__builtin_bit_cast(uint32_t, y0), __builtin_bit_cast(uint32_t, y1)};
     }
   }
 }
