@@ -74,7 +74,9 @@ __global__ __launch_bounds__(kThreads) void count_matched_kernel(SkvCount count)
 
 // The same copy for a call that runs beside a kernel which holds most of the chip's registers (prefill attention: 240 of a
 // SIMD's 512 for each of two wavefronts): one workgroup per compute unit with one wavefront per SIMD in the 32 registers that
-// are left, so it needs no compute unit of its own and takes what the other kernel leaves of the memory's time.  Addresses are
+// are left, and none of the LDS, which two of its workgroups may fill (with 4 KB for a scan of the offsets instead of the lanes it had
+// to wait for one of them to end, and they for it: 335 MB beside 50 us of attention 268 us, now 110), so it needs no compute unit of its
+// own and takes what the other kernel leaves of the memory's time.  Addresses are
 // buffer descriptors and scalar offsets for the registers' sake; what lies behind a page's end is neither read nor written.
 // Alone it is the faster form of a large copy too: one workgroup per compute unit keeps enough in flight and goes through neighbouring
 // pages together.  us of the plain form / of this one, 32 KB pages 1024 24.8 / 25.8, 2048 51.5 / 47.6, 4096 101 / 93, 16384 401 / 379 (5.67
@@ -87,46 +89,50 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(32))) void
     int n_req, const char* __restrict__ kpool, const char* __restrict__ vpool, int n_pages,
     const int32_t* __restrict__ matched_len, const int32_t* __restrict__ page_table, int max_blocks,
     int64_t* __restrict__ ctx_off, char* __restrict__ kctx, char* __restrict__ vctx, int64_t cap_pages, int page_bytes) {
-  __shared__ int64_t first[kPref + 1];   // pages before a request
-  // (a scan through LDS: the one through lanes holds too many registers)
-  for (int r = threadIdx.x; r <= n_req; r += kThreads) first[r] = r ? max(matched_len[r - 1], 0) / SKV_BLOCK_TOKENS : 0;
-  __syncthreads();
-  for (int o = 1; o <= n_req; o <<= 1) {
-    int64_t below[(kPref + kThreads) / kThreads];
-#pragma unroll
-    for (int k = 0; k < (kPref + kThreads) / kThreads; ++k) {
-      const int r = threadIdx.x + k * kThreads;
-      below[k] = r >= o && r <= n_req ? first[r - o] : 0;
+  // A lane holds the pages before its `per` requests.  Nothing in LDS: two attention workgroups of four wavefronts leave none of it.
+  const int lane = threadIdx.x & 63, per = (n_req + 63) / 64;
+  auto pages_of = [&](int r) __attribute__((always_inline)) { return max(matched_len[r], 0) / SKV_BLOCK_TOKENS; };
+  const int r0 = min(lane * per, n_req), r1 = min(r0 + per, n_req);
+  int64_t before = 0, end;
+  {
+    for (int r = r0; r < r1; ++r) before += pages_of(r);
+    const int64_t own = before;
+    for (int o = 1; o < 64; o <<= 1) {
+      const int64_t x = __shfl_up(before, o);
+      if (lane >= o) before += x;
     }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < (kPref + kThreads) / kThreads; ++k) {
-      const int r = threadIdx.x + k * kThreads;
-      if (r <= n_req) first[r] += below[k];
+    end = min(__shfl(before, 63), cap_pages);
+    before -= own;
+    if (blockIdx.x == 0 && threadIdx.x < 64) {
+      int64_t at = before;
+      if (lane == 0) ctx_off[0] = 0;
+      for (int r = r0; r < r1; ++r) {
+        at += pages_of(r);
+        ctx_off[r + 1] = at * SKV_BLOCK_TOKENS;
+      }
     }
-    __syncthreads();
   }
-  if (blockIdx.x == 0)
-    for (int r = threadIdx.x; r <= n_req; r += kThreads) ctx_off[r] = first[r] * SKV_BLOCK_TOKENS;
-  auto uniform = [](int64_t x) __attribute__((always_inline)) {
-    return (int64_t)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x) |
-                     (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)((uint64_t)x >> 32)) << 32);
+  auto uniform = [](int64_t x, int from) __attribute__((always_inline)) {
+    return (int64_t)((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, from) |
+                     (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)x >> 32), from) << 32);
   };
-  const int64_t end = uniform(min(first[n_req], cap_pages));
+  end = uniform(end, 0);
   const unsigned at = threadIdx.x * 16;
   // Page ids are asked for a page ahead: one workgroup per compute unit has nobody to cover the read.
-  int r = 0;   // request that owns the page
+  int r = 0, n = 0;      // request that owns the page, its pages
+  int64_t first = 0;     // and the pages before it
   auto page_of = [&](int64_t p) __attribute__((always_inline)) {
     if (p >= end) return -1;
-    if (uniform(first[r + 1]) <= p) {   // (it does end: p < first[n_req])
-      int lo = r + 1, hi = n_req;       // first[lo] <= p < first[hi]
-      while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (uniform(first[mid]) <= p) lo = mid; else hi = mid;
+    if (p >= first + n) {   // (it does end: p < end)
+      const int l = __builtin_popcountll(__ballot(before <= p)) - 1;   // the last lane with no more than p pages before it
+      r = l * per;
+      first = uniform(before, l);
+      for (n = pages_of(r); p >= first + n; n = pages_of(r)) {
+        first += n;
+        ++r;
       }
-      r = lo;
     }
-    const int64_t j = p - uniform(first[r]);
+    const int64_t j = p - first;
     return j < max_blocks ? page_table[(size_t)r * max_blocks + j] : -1;
   };
   int next = page_of(blockIdx.x);
