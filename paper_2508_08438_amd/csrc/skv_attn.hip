@@ -38,8 +38,6 @@ typedef short s16x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kD = 128;          // head dim of the bf16 kernel
 constexpr int kBN = 64;          // keys per LDS tile
-constexpr int kKStages = 3;      // LDS stages of K: tiles kt, kt + 1 in use, kt + 2 arriving
-constexpr int kVStages = 3;      // LDS stages of V: tiles kt - 1, kt in use, kt + 1 arriving
 constexpr int kStageRows = 16;   // rows of a wave's Q / O staging tile
 constexpr float kSumLimit = 4096.f;   // move the softmax reference when a lane's sum of 16 exponentials exceeds this
 constexpr int kRowsPerWave = 32; // query rows per wavefront
@@ -53,7 +51,8 @@ constexpr int kThreads = kWaves * 64;
 // values in four segments, V^T (ds_read_b64_tr_b16, 32 lanes = 32 bytes of 4 keys in two segments) for values that differ in bit 1 in
 // neighbouring ones.  The addresses of different fragments differ by constants only (V^T's by two sets of them).
 constexpr int kSeg = 512;            // bf16 elements per segment
-constexpr int kTile = 16 * kSeg;     // bf16 elements per 64-key tile
+constexpr int kHalf = 8 * kSeg;      // bf16 elements per 32 keys: a stage
+constexpr int kHalfBytes = kHalf * 2;
 __device__ __forceinline__ int turn(int s) { return ((s >> 1) & 1) | ((s ^ (s >> 1)) & 1) << 1; }   // 0, 2, 3, 1
 constexpr float kLog2e = 1.4426950408889634f;
 
@@ -593,15 +592,33 @@ __device__ __forceinline__ void unit_of_block(int b, int Hkv, int n_hg, int& ite
   item = rest / n_hg;
 }
 
+// A workgroup has the compute unit to itself or (kTwo) is one of two.
+template <bool kTwo>
+struct Form {
+  static constexpr int waves = kTwo ? 4 : kWaves, threads = waves * 64;
+  // Stages of K, and of V.  In iteration kt K's 32-key halves 2 kt + 1 .. 2 kt + 3 are in use and 2 kt + 4, 2 kt + 5 arriving, V's
+  // 2 kt - 1 .. 2 kt + 1 and 2 kt + 2, 2 kt + 3: five, or six where there is room, which repeat after three tiles.
+  static constexpr int halves = kTwo ? 5 : 6;
+  static constexpr int loads = 16 / waves;                  // segments of a tile that a wavefront moves
+  static constexpr int stage_at = kTwo ? (halves + 2) * kHalf : 2 * halves * kHalf;   // Q and O: in V's idle stages, or behind
+  static constexpr int lds = kTwo ? 2 * halves * kHalf : stage_at + waves * kStageRows * kD;
+};
+// (not in the kernel's own text: in a template, where its arguments depend on the parameters, the host pass drops the kernel for it)
+__device__ __forceinline__ void lds_load_b128(__amdgpu_buffer_rsrc_t rsrc, __bf16* dst, unsigned off) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void*)dst, 16, off, 0, 0, 0);
+}
+
 // kParts: the list may hold parts of items.  Without, 0.3 us less of a workgroup's start goes into what a part needs.
 // kPlan: no list, the workgroup finds its item itself.
-template <bool kParts, bool kPlan>
-__global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
-  __shared__ __attribute__((aligned(16))) __bf16 smem[kKStages * kTile + kVStages * kTile +
-                                                      kWaves * kStageRows * kD];
+template <bool kParts, bool kPlan, bool kTwo>
+__global__ __launch_bounds__(Form<kTwo>::threads, 2) void attn_bf16_kernel(AttnParams p) {
+  using F = Form<kTwo>;
+  constexpr int kHalves = F::halves;
+  static_assert(!kTwo || !kParts);
+  __shared__ __attribute__((aligned(16))) __bf16 smem[F::lds];
   __bf16* const Ks = smem;
-  __bf16* const Vs = smem + kKStages * kTile;
-  // [kWaves][16 rows][16 chunks of 8 bf16]: each wave's own staging tile for its Q rows on the way in and its O rows
+  __bf16* const Vs = smem + kHalves * kHalf;
+  // [wavefronts][16 rows][16 chunks of 8 bf16]: each wave's own staging tile for its Q rows on the way in and its O rows
   // on the way out (16 rows at a time), 16-byte chunks XOR-swizzled by row so that row-wise and fragment-wise
   // accesses are conflict free: `stage` below
 
@@ -610,7 +627,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform by construction
   const int l16 = lane & 15;
   const int quad = lane >> 4;
-  __bf16* const stage = Vs + kVStages * kTile + wave * (kStageRows * kD);
+  __bf16* stage = smem + F::stage_at + wave * (kStageRows * kD);
 
   // ---- which piece of work: XCD-aware decode (workgroup b runs on XCD b % 8) ----
   const int G = p.G, n_hg = p.n_hg;
@@ -719,14 +736,19 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
   for (int a = 0; a < 8; ++a) o[a][0] = o[a][1] = zero4;
 
   // ---- global -> LDS, without a stop in registers ----
-  // A tile is four 16-key groups; a group is one page of the pool or 16 consecutive new rows.  Each wavefront
-  // moves two segments of a tile, half a group (2w and 2w + 1: keys 8w ..), with direct-to-LDS loads: lane i
-  // fetches its piece of the segment (turn()) and the hardware puts it at slot i.  Both take the
+  // A tile is four 16-key groups; a group is one page of the pool or 16 consecutive new rows.  Each of eight wavefronts
+  // moves two segments of a tile, half a group (2w and 2w + 1: keys 8w ..), each of four a group, with direct-to-LDS loads: lane i
+  // fetches its piece of the segment (turn()) and the hardware puts it at slot i.  All take the
   // group's base as the buffer's and constant offsets: no vector address is formed.
   const unsigned row_bytes = (unsigned)p.Hkv * kD * 2u;
-  const int t_row = (wave & 1) * 8 + ((lane >> 2) & 3);      // row of the 16-key group this lane fetches, and 4 further on
-  auto t_col = [&](int seg) { return (unsigned)(quad * 4 + ((lane & 3) ^ turn(seg))) * 16u; };
-  const unsigned t_off = (unsigned)t_row * row_bytes + t_col(2 * wave);
+  const int seg0 = F::loads * wave;                          // this wave's first segment
+  unsigned t_off[F::loads];                                  // (a scalar offset would have to lie inside the buffer)
+#pragma unroll
+  for (int k = 0; k < F::loads; ++k) {
+    const int t_row = ((seg0 + k) & 3) * 4 + ((lane >> 2) & 3);   // row of the 16-key group this lane fetches
+    t_off[k] = (unsigned)t_row * row_bytes + (unsigned)(quad * 4 + ((lane & 3) ^ turn(seg0 + k))) * 16u;
+    asm volatile("" : "+v"(t_off[k]));   // (not worked out anew from its parts, which take more registers)
+  }
   // Group base addresses, one 16-key group per lane for 64 groups (16 tiles, a "window"): a pool page, 16 new rows,
   // or 0 when the group has no data (past the end of the sequence, or a page id outside the pool): an empty buffer, whose rows
   // arrive as zeros.
@@ -741,25 +763,27 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
   int win = 0;                       // window held in *_cur; *_nxt holds window win + 1
   window_bases(0, page_w0, ak_cur, av_cur);
   window_bases(1, page_w1, ak_nxt, av_nxt);
-  typedef __attribute__((address_space(3))) void lds_void;
-  const int group = wave >> 1;                               // 16-key group of this wave's segments
-  const unsigned t_off4 = (unsigned)(t_row + 4) * row_bytes + t_col(2 * wave + 1);   // (a scalar offset would have to lie inside the buffer)
-  // one pool (K or V) of tile t into an LDS stage; `base`: of the wave's group.  Where the sequence ends inside the tile so does
+  const int group = seg0 >> 2;                               // 16-key group of this wave's segments
+  // where they go; h: stage of the tile's first half, h_next: of its second one
+  auto dst_in = [&](__bf16* stages, int h, int h_next) __attribute__((always_inline)) {
+    if (!kTwo) return stages + h * kHalf + seg0 * kSeg;   // (behind one another)
+    return stages + (seg0 >= 8 ? h_next : h) * kHalf + (seg0 & 7) * kSeg;
+  };
+  // one pool (K or V) of tile t; `base`: of the wave's group.  Where the sequence ends inside the tile so does
   // the buffer: what lies behind arrives as zeros, and the causal mask keeps it out.
-  auto issue_half_tile = [&]<bool kWhole>(uint64_t base, int t, __bf16* dst_stage) __attribute__((always_inline)) {
-    __bf16* const dst = dst_stage + 2 * wave * kSeg;
+  auto issue_tile = [&]<bool kWhole>(uint64_t base, int t, __bf16* dst) __attribute__((always_inline)) {
     // (the compiler clamps in vector registers, and a descriptor that is not scalar costs a loop around each load)
     const int rows = kWhole ? 16 : __builtin_amdgcn_readfirstlane(max(0, min(16, Ltot - (t * kBN + group * 16))));
     const __amdgpu_buffer_rsrc_t rsrc =
         __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, base ? rows * (int)row_bytes : 0, 0x00020000);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void*)dst, 16, t_off, 0, 0, 0);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void*)(dst + kSeg), 16, t_off4, 0, 0, 0);
+#pragma unroll
+    for (int k = 0; k < F::loads; ++k) lds_load_b128(rsrc, dst + k * kSeg, t_off[k]);
   };
-  auto load_k_tile = [&](int t, int stage_idx) __attribute__((always_inline)) {
-    issue_half_tile.template operator()<false>(lane_bcast((t >> 4) == win ? ak_cur : ak_nxt, ((t & 15) << 2) + group), t, Ks + stage_idx * kTile);
+  auto load_k_tile = [&](int t, int h) __attribute__((always_inline)) {
+    issue_tile.template operator()<false>(lane_bcast((t >> 4) == win ? ak_cur : ak_nxt, ((t & 15) << 2) + group), t, dst_in(Ks, h, h + 1));
   };
-  auto load_v_tile = [&](int t, int stage_idx) __attribute__((always_inline)) {
-    issue_half_tile.template operator()<false>(lane_bcast((t >> 4) == win ? av_cur : av_nxt, ((t & 15) << 2) + group), t, Vs + stage_idx * kTile);
+  auto load_v_tile = [&](int t, int h) __attribute__((always_inline)) {
+    issue_tile.template operator()<false>(lane_bcast((t >> 4) == win ? av_cur : av_nxt, ((t & 15) << 2) + group), t, dst_in(Vs, h, h + 1));
   };
   // Inside the main loop the same loads are split in two: the bases of the tiles an iteration will request
   // (K two tiles ahead, V one) are broadcast out of the windows during the iteration before, between its half-steps,
@@ -983,11 +1007,10 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
 
   // ---- prologue: tiles K(0), K(1), V(0); scores of sub-tile 0; the reference starts at its row maxima
   load_k_tile(0, 0);
-  if (n_tiles > 1) load_k_tile(1, 1);
+  if (n_tiles > 1) load_k_tile(1, 2);
   load_v_tile(0, 0);
   stage_q();
   tile_barrier();
-  constexpr int kStageBytes = kTile * 2, kHalfBytes = 8 * kSeg * 2;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     kfr[j] = k_frag(0, j);
@@ -1012,6 +1035,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
 #pragma unroll
     for (int g = 0; g < 2; ++g) m_ref[g] = fmaxf(row_max(s[0], g) * c, -3.0e38f);
   }
+  if (kTwo) __syncthreads();   // K's half 5, requested in iteration 0, takes the stage of half 0
 
   // ---- main loop.  Iteration kt (two half-steps) reads K(kt), K(kt + 1), V(kt - 1), V(kt).  It starts behind the
   // barrier that published K(kt + 1) and V(kt) and behind which no wave still reads K(kt - 1) or V(kt - 2): their
@@ -1026,57 +1050,58 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
   // the tiles they request may be ragged or absent (the last two or three before the diagonal tile): they run the
   // fast form with the mask applied and the general loads.
   const int kt_mid = (wave_key_end - 1) / 64;
-  int st0 = 0;   // stage of K(kt) and V(kt); tile t sits in stage t % 3
-  auto requests = [&]<bool kFast>(int kt, int st1, int st2) __attribute__((always_inline)) {
+  int h0 = 0;   // stage of K's half 2 kt and V's; half u sits in stage u % kHalves
+  auto requests = [&]<bool kFast>(int kt, int h2, int h3, int h4, int h5) __attribute__((always_inline)) {   // stages of halves 2 kt + 2 ..
     if (__builtin_expect(pend, 0)) {
       window_bases(win + 1, pend_page, ak_nxt, av_nxt);
       pend = false;
     }
-    if (kFast || kt + 2 < n_tiles) issue_half_tile.template operator()<kFast>(nk, kt + 2, Ks + st2 * kTile);
-    if (kFast || kt + 1 < n_tiles) issue_half_tile.template operator()<kFast>(nv, kt + 1, Vs + st1 * kTile);
+    if (kFast || kt + 2 < n_tiles) issue_tile.template operator()<kFast>(nk, kt + 2, dst_in(Ks, h4, h5));
+    if (kFast || kt + 1 < n_tiles) issue_tile.template operator()<kFast>(nv, kt + 1, dst_in(Vs, h2, h3));
   };
   auto iteration = [&]<bool kMasked>(int kt) __attribute__((always_inline)) {   // general form, or the fast one with masks
-    const int st1 = st0 == 2 ? 0 : st0 + 1;    // stage of tile kt + 1
-    const int st2 = st1 == 2 ? 0 : st1 + 1;    // stage of tiles kt + 2 and kt - 1
-    requests.template operator()<false>(kt, st1, st2);
-    const uint32_t kb0 = st0 * kStageBytes;   // K(kt)
-    const uint32_t kb1 = st1 * kStageBytes;   // K(kt + 1)
-    const uint32_t vbp = st2 * kStageBytes;   // V(kt - 1)
-    const uint32_t vb0 = st0 * kStageBytes;   // V(kt)
+    auto in = [&](int u) __attribute__((always_inline)) { return h0 + u >= kHalves ? h0 + u - kHalves : h0 + u; };   // of half 2 kt + u
+    const int h1 = in(1), h2 = in(2), h3 = in(3), h_1 = in(kHalves - 1);
+    requests.template operator()<false>(kt, h2, h3, in(4), in(5));
+    const uint32_t k1 = h1 * kHalfBytes, k2 = h2 * kHalfBytes, k3 = h3 * kHalfBytes;                     // K
+    const uint32_t v_1 = h_1 * kHalfBytes, v0 = h0 * kHalfBytes, v1 = h1 * kHalfBytes;                  // V
     if (kMasked) {
-      half_step_fast.template operator()<true>(2 * kt, kb0 + kHalfBytes, kb1, vbp + kHalfBytes, vb0, s[1], s[0], pb[1], pb[0]);
+      half_step_fast.template operator()<true>(2 * kt, k1, k2, v_1, v0, s[1], s[0], pb[1], pb[0]);
       prep_bases(kt + 1);
-      half_step_fast.template operator()<true>(2 * kt + 1, kb1, kb1 + kHalfBytes, vb0, vb0 + kHalfBytes, s[0], s[1], pb[0], pb[1]);
+      half_step_fast.template operator()<true>(2 * kt + 1, k2, k3, v0, v1, s[0], s[1], pb[0], pb[1]);
     } else {
-      half_step_slow(2 * kt, kb0 + kHalfBytes, kb1, vbp + kHalfBytes, vb0, s[1], s[0], pb[1], pb[0]);
+      half_step_slow(2 * kt, k1, k2, v_1, v0, s[1], s[0], pb[1], pb[0]);
       prep_bases(kt + 1);
-      half_step_slow(2 * kt + 1, kb1, kb1 + kHalfBytes, vb0, vb0 + kHalfBytes, s[0], s[1], pb[0], pb[1]);
+      half_step_slow(2 * kt + 1, k2, k3, v0, v1, s[0], s[1], pb[0], pb[1]);
     }
     if (kMasked || kt + 1 < n_tiles) tile_barrier();   // (nothing is published in the last one)
-    st0 = st1;
+    h0 = h2;
   };
-  // The fast form, three tiles to a turn: the stages are constants and go into the reads' offset fields.
-  auto fast = [&]<int kSt>(int kt) __attribute__((always_inline)) {
-    constexpr int st1 = (kSt + 1) % 3, st2 = (kSt + 2) % 3;
-    constexpr int k0 = kSt * kStageBytes, k1 = st1 * kStageBytes, vp = st2 * kStageBytes, half = kHalfBytes;
-    requests.template operator()<true>(kt, st1, st2);
-    half_step_fast.template operator()<false, k0 + half, k1, vp + half, k0>(2 * kt, 0, 0, 0, 0, s[1], s[0], pb[1], pb[0]);
+  // The fast form, unrolled until the stages repeat: they are constants and go into the reads' offset fields.
+  auto fast = [&]<int kH>(int kt) __attribute__((always_inline)) {   // kH: h0
+    constexpr int h1 = (kH + 1) % kHalves, h2 = (kH + 2) % kHalves, h3 = (kH + 3) % kHalves, h_1 = (kH + kHalves - 1) % kHalves;
+    requests.template operator()<true>(kt, h2, h3, (kH + 4) % kHalves, (kH + 5) % kHalves);
+    half_step_fast.template operator()<false, h1 * kHalfBytes, h2 * kHalfBytes, h_1 * kHalfBytes, kH * kHalfBytes>(2 * kt, 0, 0, 0, 0, s[1], s[0], pb[1], pb[0]);
     prep_bases(kt + 1);
-    half_step_fast.template operator()<false, k1, k1 + half, k0, k0 + half>(2 * kt + 1, 0, 0, 0, 0, s[0], s[1], pb[0], pb[1]);
+    half_step_fast.template operator()<false, h2 * kHalfBytes, h3 * kHalfBytes, kH * kHalfBytes, h1 * kHalfBytes>(2 * kt + 1, 0, 0, 0, 0, s[0], s[1], pb[0], pb[1]);
     tile_barrier();
   };
   int kt = 0;
   prep_bases(0);
   iteration.template operator()<false>(kt++);
-  for (; kt + 2 < kt_fast; kt += 3) {   // (st0 is 1)
-    fast.template operator()<1>(kt);
-    fast.template operator()<2>(kt + 1);
-    fast.template operator()<0>(kt + 2);
+  // (of two workgroups the one whose items are short does without: it would take more than the 240 registers that leave the copy beside
+  // them its 32)
+  if constexpr (!kTwo) {
+    for (; kt + 2 < kt_fast; kt += 3) {
+      fast.template operator()<2>(kt);
+      fast.template operator()<4>(kt + 1);
+      fast.template operator()<0>(kt + 2);
+    }
   }
   for (; kt < kt_mid; ++kt) iteration.template operator()<true>(kt);
   for (; kt < n_tiles; ++kt) iteration.template operator()<false>(kt);
   if (active(2 * n_tiles - 1)) {   // the output update with the last sub-tile
-    const uint32_t vb = (st0 == 0 ? 2 : st0 - 1) * kStageBytes + kHalfBytes;
+    const uint32_t vb = (h0 == 0 ? kHalves - 1 : h0 - 1) * kHalfBytes;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       if (i >= 4) lds_wait(14 - 2 * i, vfr[i & 3]);   // (0 .. 3 are there)
@@ -1113,6 +1138,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_bf16_kernel(AttnParams p) {
     return;
   }
 
+  if constexpr (kTwo) stage = Ks + ((h0 == 1 || h0 == 2) ? 2 * kHalf : 0) + wave * (kStageRows * kD);   // K's stages but half 2 n_tiles - 1, which others may still read
   // ---- normalise and store.  A lane holds queries l16 and 16 + l16 with d = 16 a + 4 quad + i, i.e. eight 8-byte
   // pieces of each one's output row.  They go through the wave's staging tile, 16 rows at a time, and leave as whole
   // 256-byte rows.
@@ -1246,13 +1272,15 @@ int check_attn(const skv_attn_desc* d) {
 
 // How a call is laid out: from the description and the bounds the host knows.
 struct Layout {
+  bool two;                              // workgroups of four wavefronts, two to a compute unit
   int heads_per_wg, pos_log, units;      // pos_log: logarithm of the rows of a q tile; units: workgroups per item
   int64_t max_items, max_parts;          // max_parts: room for parts of split items, 0 if nothing is split
 };
-Layout layout_for(const skv_attn_desc* d, int32_t n_req, int64_t total_q_rows, bool fine, bool split) {
+Layout layout_for(const skv_attn_desc* d, int32_t n_req, int64_t total_q_rows, bool fine, bool split, bool two = false) {
   Layout y;
+  y.two = two;
   y.heads_per_wg = heads_per_wg_for(d->n_q_heads / d->n_kv_heads, fine);
-  y.pos_log = kLogFull - __builtin_ctz(y.heads_per_wg);
+  y.pos_log = kLogFull - two - __builtin_ctz(y.heads_per_wg);
   y.units = d->n_q_heads / y.heads_per_wg;
   y.max_parts = split && y.units <= kCus ? kMaxSlots / y.units : 0;
   y.max_items = (total_q_rows >> y.pos_log) + 2 * (int64_t)n_req + y.max_parts;   // per request: a short first tile and a ragged last one
@@ -1327,6 +1355,24 @@ bool eight_heads(const skv_attn_desc* d, int32_t n_req, int64_t total_q_rows, in
   }
   return std::max(time8, kCus * whole8) < time4;
 }
+// Whether a call of whole items in several rounds takes workgroups of four wavefronts, two to a compute unit (tiles of half the rows,
+// eight heads where the kv head serves a multiple of eight): one's start and end run under the other's loop, and in a tile of up to half
+// the rows no wavefront is without any.  But K and V tiles travel twice as often: where items are long that counts for more, and where
+// they fill one round nothing is gained.  us with one / two: 512 requests of 64 rows behind nothing 142 / 123, behind 512 keys 412 / 411;
+// 1000 of 17 behind 32 177 / 98; 100 of 8 .. 32 behind 1600 .. 6400 339 / 309; 64 of 256 behind 8192 1956 / 2013; 8 query heads over 8, 64
+// of 500 .. 1100 193 / 177; 24 over 8, 100 of 50 .. 100 104 / 72.  (1523 calls of 4 .. 400 requests of up to 800 rows behind up to 300
+// pages: 0.87 of the time on average, 0.855 were every choice right; 48 are slower by 2 % and more, one by 16.)  Few rows behind
+// kTwoPool and more of K and V: the copy of those pages, where a step makes one beside, is what takes the time, and the second set of loads
+// costs it 2 to 3 % (128 of 8 .. 47 rows behind 2000 .. 3000, 1.5 GB: 550 / 566; 335 MB 130 / 130; 0.8 GB and 60 .. 105 rows 477 / 479).
+constexpr int kTwoKeys = 25, kTwoKeysEight = 16;   // key tiles of an item in the middle of its request
+constexpr float kTwoPool = 1 << 30;
+bool two_workgroups(const skv_attn_desc* d, const Layout& z, int32_t n_req, int64_t total_q_rows, int32_t max_blocks) {
+  const int64_t rows = mean_rows(n_req, total_q_rows), tile = 1 << z.pos_log;
+  const float wgs = (float)n_req * z.units * std::max(1.f, (float)rows / (2 * tile) + 0.5f);
+  const float keys = max_blocks * (float)SKV_BLOCK_TOKENS / kBN + rows / (2.f * kBN);
+  if (wgs <= kCus || (rows > tile && keys > (z.heads_per_wg == 8 ? kTwoKeysEight : kTwoKeys))) return false;
+  return rows > 2 * tile || (float)n_req * max_blocks * d->n_kv_heads * (SKV_BLOCK_TOKENS * kD * 4) < kTwoPool;
+}
 // Keys above which a longest request has the requests ordered by length.  Order is worth its 1.3 us where workgroups queue and
 // one that starts late ends late: in a few rounds (64 requests of up to 39 rows behind up to 496, 16 query heads over 1: 42 ->
 // 35 us), or behind long prefixes; many rounds of short requests run better as they come (200 of up to 63 rows, 32 over 8: 60.6 ->
@@ -1364,6 +1410,18 @@ extern "C" int skv_prefill_attn_workspace_size(const skv_attn_desc* desc, int32_
   return SKV_OK;
 }
 
+// The layout of a call that splits nothing, with list_room bytes for the list.  Where none fits it is the smallest, for the caller to refuse.
+static bool too_many_items(const skv_attn_desc* d, const Layout& y);
+static Layout whole_layout(const skv_attn_desc* d, int32_t n_req, int64_t total_q_rows, int32_t max_blocks, size_t list_room) {
+  Layout y = layout_for(d, n_req, total_q_rows, eight_heads(d, n_req, total_q_rows, max_blocks, false), false);
+  if (list_bytes(d, y) > list_room) y = layout_for(d, n_req, total_q_rows, false, false);
+  const Layout z = layout_for(d, n_req, total_q_rows, true, false, true);
+  if (d->dtype == SKV_BF16 && !plan_in_place(y, n_req) && two_workgroups(d, z, n_req, total_q_rows, max_blocks) && list_bytes(d, z) <= list_room &&
+      !too_many_items(d, z))
+    y = z;
+  return y;
+}
+
 // (fp32 has no list, and a limit of its own)
 static bool too_many_items(const skv_attn_desc* d, const Layout& y) {
   return d->dtype == SKV_BF16 && (y.max_items * y.units > 0x7fffffff || y.max_items > 0x3fffffff);
@@ -1398,7 +1456,7 @@ static int prefill_attn_enqueue(const skv_attn_desc* desc, int32_t n_req, const 
                                 void* d_workspace, const Layout& y, const StepExtras* x, void* stream) {
   hipStream_t st = (hipStream_t)stream;
   // of up to kSkvGatherScan requests a plan with parts makes the suffix offsets itself, and its pages travel beside the merge
-  const bool plan = desc->dtype == SKV_BF16 && plan_in_place(y, n_req) && !(y.max_parts && two_rounds(y, n_req, total_q_rows, max_blocks));
+  const bool plan = desc->dtype == SKV_BF16 && !y.two && plan_in_place(y, n_req) && !(y.max_parts && two_rounds(y, n_req, total_q_rows, max_blocks));
   const bool late = x && plan && y.max_parts && !x->gather.large;
   if (x && !late) {
     const int rc = skv_gather_enqueue(x->gather, false, x->req_off, x->q_off, x->count, stream);
@@ -1444,9 +1502,10 @@ static int prefill_attn_enqueue(const skv_attn_desc* desc, int32_t n_req, const 
                                                       order_above(y, n_req, total_q_rows), p.rows_filled, p.n_items_out, (int32_t*)p.items, p.splits_out);
     SKV_HIP(hipGetLastError());
   }
-  const auto kernel = y.max_parts ? (plan ? attn_bf16_kernel<true, true> : attn_bf16_kernel<true, false>)
-                                  : (plan ? attn_bf16_kernel<false, true> : attn_bf16_kernel<false, false>);
-  kernel<<<(int)grid, kThreads, 0, st>>>(p);
+  const auto kernel = y.two ? attn_bf16_kernel<false, false, true>
+                      : y.max_parts ? (plan ? attn_bf16_kernel<true, true, false> : attn_bf16_kernel<true, false, false>)
+                                    : (plan ? attn_bf16_kernel<false, true, false> : attn_bf16_kernel<false, false, false>);
+  kernel<<<(int)grid, y.two ? Form<true>::threads : kThreads, 0, st>>>(p);
   SKV_HIP(hipGetLastError());
   if (y.max_parts) {   // a split item has two parts at least
     const int merge_blocks = (int)std::min<int64_t>(y.max_parts / 2 * y.units * kWaves, kMergeGrid);
@@ -1476,9 +1535,8 @@ static int prefill_attn_check(const skv_attn_desc* desc, int32_t n_req, const vo
   if (rc) return rc;
   // a workspace that holds the plain work list is enough: the call then splits nothing, and takes 32-row tiles if their list fits
   y = layout_for(desc, n_req, total_q_rows, eight_heads(desc, n_req, total_q_rows, max_blocks, true), true);
-  if (y.max_parts && (!may_split(y, n_req, total_q_rows, max_blocks) || workspace_bytes < list_bytes(desc, y) + split_bytes(y)))
-    y = layout_for(desc, n_req, total_q_rows, eight_heads(desc, n_req, total_q_rows, max_blocks, false), false);
-  if (workspace_bytes < list_bytes(desc, y)) y = layout_for(desc, n_req, total_q_rows, false, false);
+  if (!y.max_parts || !may_split(y, n_req, total_q_rows, max_blocks) || workspace_bytes < list_bytes(desc, y) + split_bytes(y))
+    y = whole_layout(desc, n_req, total_q_rows, max_blocks, workspace_bytes);
   if (!d_workspace || workspace_bytes < list_bytes(desc, y)) return SKV_ENOMEM;
   if ((uintptr_t)d_workspace & 15) return SKV_EINVAL;
   return too_many_items(desc, y) ? SKV_ERANGE : SKV_OK;
@@ -1568,8 +1626,7 @@ extern "C" int skv_prefill_attn_static(const skv_attn_desc* desc, int32_t n_req,
   rc = check_attn_buffers(d_q, d_knew, d_vnew, d_q_off, d_kpool, d_vpool, d_matched_len, d_page_table, max_blocks,
                           d_out);
   if (rc) return rc;
-  Layout y = layout_for(desc, n_req, total_q_rows, eight_heads(desc, n_req, total_q_rows, max_blocks, false), false);
-  if (list_bytes(desc, y) > (size_t)SKV_STATIC_SCRATCH_BYTES) y = layout_for(desc, n_req, total_q_rows, false, false);
+  const Layout y = whole_layout(desc, n_req, total_q_rows, max_blocks, SKV_STATIC_SCRATCH_BYTES);
   if (list_bytes(desc, y) > (size_t)SKV_STATIC_SCRATCH_BYTES || too_many_items(desc, y)) return SKV_ERANGE;   // batch too large for the built-in scratch
   void* ws = nullptr;
   rc = scratch_of_current_device(&ws);
