@@ -178,15 +178,9 @@ constexpr int kSchedThreads = 1024, kSchedWaves = kSchedThreads / 64;
 constexpr int kBuckets = 128;
 
 template <typename T>
-__device__ inline T wave_max(T v) {
-  for (int o = 32; o >= 1; o >>= 1) v = max(v, __shfl_xor(v, o));
-  return v;
-}
+__device__ inline T wave_max(T v) { return skv_over_wave(v, SkvMax()); }
 template <typename T>
-__device__ inline T wave_sum(T v) {
-  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
-  return v;
-}
+__device__ inline T wave_sum(T v) { return skv_over_wave(v, SkvAdd()); }
 // first place whose scan value exceeds x (scan[n - 1] does)
 __device__ inline int place_of(const int* scan, int n, int x) {
   int lo = 0, hi = n - 1;
@@ -231,11 +225,7 @@ __global__ __launch_bounds__(kSchedThreads) void attn_schedule_kernel(
       __syncthreads();
       if (wave == 0) {   // exclusive scan, two buckets per lane
         const int c0 = bucket[2 * lane], c1 = bucket[2 * lane + 1];
-        int x = c0 + c1;
-        for (int o = 1; o < 64; o <<= 1) {
-          const int y = __shfl_up(x, o);
-          if (lane >= o) x += y;
-        }
+        const int x = skv_wave_scan(c0 + c1);
         bucket[2 * lane] = x - c0 - c1;
         bucket[2 * lane + 1] = x - c1;
       }
@@ -373,7 +363,7 @@ __global__ __launch_bounds__(kSchedThreads) void attn_schedule_kernel(
 // ---- the same list without a kernel in front of the attention -------------------------------------
 // Of up to 64 requests every wavefront works its item out for itself, a request per lane and nothing through LDS: the same cuts,
 // forecasts and part lengths as above (an order by length has nothing to give in one round of workgroups).  A list costs a launch and a chain of barriers, 5 to 9 us
-// of every call; this 0.5 to 1.5 us of a workgroup's start, 2 to 4 where a split is searched for.  Parts fill one round of workgroups
+// of every call; this 0.5 to 1.5 us of a workgroup's start, 2 to 3 where a split is searched for.  Parts fill one round of workgroups
 // here: the workgroups that a second one needs room for cost every call 3 to 8 us where the parts leave it empty.
 constexpr int kPlanRequests = 64, kPlanItems = 64;   // kPlanItems: a lane each, where they may be split
 struct Work {
@@ -385,14 +375,7 @@ __device__ __forceinline__ bool plan_item(const AttnParams& p, int item, int uni
   const int lane = threadIdx.x & 63;
   const bool writes = kParts && unit == 0 && threadIdx.x == 0;
   auto at_lane = [](int x, int from) __attribute__((always_inline)) { return __builtin_amdgcn_readlane(x, from); };
-  auto scan = [&](int x) __attribute__((always_inline)) {   // inclusive
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int y = __shfl_up(x, o);
-      if (lane >= o) x += y;
-    }
-    return x;
-  };
+  auto scan = [&](int x) __attribute__((always_inline)) { return skv_wave_scan(x); };   // inclusive
   int qb = 0, qe = 0, L = 0;
   if (p.req_off) {
     if (lane < p.n_req) {
@@ -435,13 +418,17 @@ __device__ __forceinline__ bool plan_item(const AttnParams& p, int item, int uni
   }
   // lane i: item i
   const int n = total;
-  int at = 0;
+  int at = 0, up = at_lane(upto, 0);
+  Cut mine = {at_lane(c.S, 0), at_lane(c.L, 0), at_lane(c.qb, 0), at_lane(c.head_rows, 0), at_lane(c.nt, 0)};
+  if (p.n_req > 1) {
 #pragma unroll
-  for (int o = 32; o >= 1; o >>= 1)
-    if (__shfl(upto, at + o - 1) <= lane) at += o;
-  at = min(at, 63);
-  const Cut mine = {__shfl(c.S, at), __shfl(c.L, at), __shfl(c.qb, at), __shfl(c.head_rows, at), __shfl(c.nt, at)};
-  const int2 rows = tile_of(min(lane, n - 1), mine, __shfl(upto, at));
+    for (int o = 32; o >= 1; o >>= 1)
+      if (__shfl(upto, at + o - 1) <= lane) at += o;
+    at = min(at, 63);
+    mine = {__shfl(c.S, at), __shfl(c.L, at), __shfl(c.qb, at), __shfl(c.head_rows, at), __shfl(c.nt, at)};
+    up = __shfl(upto, at);
+  }
+  const int2 rows = tile_of(min(lane, n - 1), mine, up);
   const bool have = lane < n;
   const int n_kt = have ? (mine.L + rows.y + kBN - 1) / kBN : 0, last = have ? (mine.L + rows.x) / kBN : 0;
   const float time = (float)n_kt * tile_time(rows.y - rows.x, p.pos_log);
@@ -460,8 +447,8 @@ __device__ __forceinline__ bool plan_item(const AttnParams& p, int item, int uni
         const int i = i0 + (lane & 3), kt = __shfl(n_kt, i & 63), la = __shfl(last, i & 63);
         if (i < n) total_parts += parts_of(kt, la, len);
       }
-      total_parts += __shfl_xor(total_parts, 1);
-      total_parts += __shfl_xor(total_parts, 2);
+      total_parts += skv_dpp<kSkvQuadXor1>(0, total_parts);
+      total_parts += skv_dpp<kSkvQuadXor2>(0, total_parts);
       const uint64_t fits = __ballot(total_parts <= room);
       const int k = fits ? __builtin_ctzll(fits) >> 2 : 16, l0 = lo;
       if (k < 16) hi = l0 + (int)(((long long)d * k) >> 4);
@@ -500,28 +487,9 @@ __device__ __forceinline__ bool plan_item(const AttnParams& p, int item, int uni
 }
 
 // ---- bf16 MFMA kernel --------------------------------------------------------------------------
-// max / sum of a value over the four lanes 16 apart: v_permlane16_swap exchanges the odd rows of 16 lanes of its first operand with
-// the even rows of its second, v_permlane32_swap the upper half of the first with the lower half of the second; on two copies of a
-// value either leaves the one row's or half's value in `a` and the other's in `b`, so no lane select is needed
-__device__ inline void swap_rows(float& a, float& b) {
-  // the wait states the compiler places between a VALU write and this instruction are added by hand
-  asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1\n\ts_nop 1" : "+v"(a), "+v"(b));
-}
-__device__ inline void swap_halves(float& a, float& b) { asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(a), "+v"(b)); }
-__device__ inline float sum_quads(float x) {
-  float a = x, b = x;
-  swap_rows(a, b);
-  a = b = a + b;
-  swap_halves(a, b);
-  return a + b;
-}
-__device__ inline float max_quads(float x) {
-  float a = x, b = x;
-  swap_rows(a, b);
-  a = b = fmaxf(a, b);
-  swap_halves(a, b);
-  return fmaxf(a, b);
-}
+// max / sum of a value over the four lanes 16 apart
+__device__ inline float sum_quads(float x) { return skv_over_rows(x, SkvAdd()); }
+__device__ inline float max_quads(float x) { return skv_over_rows(x, SkvMax()); }
 
 // LDS fragment reads as inline assembly, with their waits placed by hand.  The compiler puts a full
 // s_waitcnt vmcnt(0) in front of LDS reads it cannot tell apart from the targets of the direct-to-LDS loads in

@@ -100,11 +100,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_attn_kernel(DecParams p) {
         for (int k = 0; k < G * kD / 8; ++k) dst[k] = u32x4{0u, 0u, 0u, 0u};
       }
     }
-    int upto = own;
-    for (int o = 1; o < 64; o <<= 1) {
-      const int x = __shfl_up(upto, o);
-      if (lane >= o) upto += x;
-    }
+    int upto = skv_wave_scan(own);
     if (lane == 63) wave_tiles[wave] = upto;
     __syncthreads();
     int total = 0;
@@ -259,8 +255,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_attn_kernel(DecParams p) {
         if (key0 + i >= ctx) s[i] = -INFINITY;
     }
     float mx = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
-    mx = fmaxf(mx, __shfl_xor(mx, 16));
-    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    mx = skv_over_rows(mx, SkvMax());
     const float m_new = fmaxf(m_run, mx);
     float alpha = 1.f;
     f32x4 pr = {0.f, 0.f, 0.f, 0.f};
@@ -333,8 +328,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_attn_kernel(DecParams p) {
   float* red_m = red_o + kWaves * kMaxG * kD;        // [kWaves][16]
   float* red_l = red_m + kWaves * kMaxG;
   {
-    float lt = l_run + __shfl_xor(l_run, 16);
-    lt += __shfl_xor(lt, 32);
+    const float lt = skv_over_rows(l_run, SkvAdd());
     float* dst = red_o + (size_t)(wave * kMaxG + l16) * kD + 4 * g4;
 #pragma unroll
     for (int a = 0; a < 8; ++a) *(f32x4*)(dst + 16 * a) = o[a];
@@ -410,7 +404,7 @@ __global__ __launch_bounds__(kThreads) void decode_merge_kernel(DecParams p) {
     if (s == tid) m0 = m;
     ms = fmaxf(ms, m);
   }
-  for (int o = 32; o >= 1; o >>= 1) ms = fmaxf(ms, __shfl_xor(ms, o));
+  ms = skv_over_wave(ms, SkvMax());
   if ((tid & 63) == 0) red_m[tid >> 6] = ms;
   __syncthreads();
 #pragma unroll
@@ -433,7 +427,7 @@ __global__ __launch_bounds__(kThreads) void decode_merge_kernel(DecParams p) {
 #pragma unroll 4
     for (int i = team; i < n_here; i += kTeams) acc += wgt[i] * *(const f32x4*)(p.part_o + piece(s0 + i) * kD + 4 * d4);
   }
-  for (int o = 32; o >= 1; o >>= 1) L += __shfl_xor(L, o);
+  L = skv_over_wave(L, SkvAdd());
   if ((tid & 63) == 0) red_l[tid >> 6] = L;
   red_o[team][d4] = acc;
   __syncthreads();

@@ -97,11 +97,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(32))) void
   {
     for (int r = r0; r < r1; ++r) before += pages_of(r);
     const int64_t own = before;
-    for (int o = 1; o < 64; o <<= 1) {
-      const int64_t x = __shfl_up(before, o);
-      if (lane >= o) before += x;
-    }
-    end = min(__shfl(before, 63), cap_pages);
+    before = skv_wave_scan(before);
+    end = min(skv_lane(before, 63), cap_pages);
     before -= own;
     if (blockIdx.x == 0 && threadIdx.x < 64) {
       int64_t at = before;
@@ -112,11 +109,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(32))) void
       }
     }
   }
-  auto uniform = [](int64_t x, int from) __attribute__((always_inline)) {
-    return (int64_t)((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, from) |
-                     (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)x >> 32), from) << 32);
-  };
-  end = uniform(end, 0);
   const unsigned at = threadIdx.x * 16;
   // Page ids are asked for a page ahead: one workgroup per compute unit has nobody to cover the read.
   int r = 0, n = 0;      // request that owns the page, its pages
@@ -126,7 +118,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_num_vgpr(32))) void
     if (p >= first + n) {   // (it does end: p < end)
       const int l = __builtin_popcountll(__ballot(before <= p)) - 1;   // the last lane with no more than p pages before it
       r = l * per;
-      first = uniform(before, l);
+      first = skv_lane(before, l);
       for (n = pages_of(r); p >= first + n; n = pages_of(r)) {
         first += n;
         ++r;

@@ -77,25 +77,90 @@ inline uint64_t skv_hash_block_host(const int32_t* tok) {
 }
 
 #ifdef __HIPCC__
+// Moves between lanes on the vector unit: data-parallel primitives within a row of 16 lanes and swaps of rows and halves.  What __shfl
+// compiles to goes through the LDS unit, and a scan or a reduction is a chain of six of them: the chip's small kernels, and the start
+// of every large one that looks for its work, are such chains.  All lanes of the wavefront take part.  us before / after: an attention
+// workgroup of a split call finds its part 4.7 / 3.0 and 5.1 / 3.6; passes with one request behind 2992 keys 35.9 / 34.4, three decode
+// requests 12.5 / 11.9, 4096 lookups and their window 46.0 / 45.0.
+template <int kCtrl, int kRows = 0xf, typename T>
+__device__ __forceinline__ T skv_dpp(T old, T v) {   // lanes without a source, or in rows outside kRows, keep `old`
+  static_assert(sizeof(T) == 4 || sizeof(T) == 8);
+  if constexpr (sizeof(T) == 4) {
+    return __builtin_bit_cast(T, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, old), __builtin_bit_cast(int, v), kCtrl, kRows, 0xf, false));
+  } else {
+    const uint64_t o = __builtin_bit_cast(uint64_t, old), x = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = __builtin_amdgcn_update_dpp((int)(uint32_t)o, (int)(uint32_t)x, kCtrl, kRows, 0xf, false);
+    const uint32_t hi = __builtin_amdgcn_update_dpp((int)(uint32_t)(o >> 32), (int)(uint32_t)(x >> 32), kCtrl, kRows, 0xf, false);
+    return __builtin_bit_cast(T, (uint64_t)hi << 32 | lo);
+  }
+}
+constexpr int kSkvRowShr = 0x110, kSkvRowRor = 0x120, kSkvRowMirror = 0x140, kSkvHalfMirror = 0x141, kSkvBcast15 = 0x142, kSkvBcast31 = 0x143,
+              kSkvQuadXor1 = 0xB1, kSkvQuadXor2 = 0x4E;   // (shifts and rotations: + distance)
+// v_permlane16_swap exchanges the odd rows of its first operand with the even rows of its second, v_permlane32_swap the upper half of
+// the first with the lower half of the second; on two copies of a value either leaves the one row's or half's value in `a` and the
+// other's in `b`, so no lane select is needed.  (The wait states the compiler places between a VALU write and these are added by hand.)
+__device__ __forceinline__ void skv_swap_rows(float& a, float& b) { asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1\n\ts_nop 1" : "+v"(a), "+v"(b)); }
+__device__ __forceinline__ void skv_swap_halves(float& a, float& b) { asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(a), "+v"(b)); }
+// op over the four lanes 16 apart, over all lanes; every lane has the result (32-bit types)
+template <typename T, typename Op>
+__device__ __forceinline__ T skv_over_rows(T v, Op op) {
+  float a = __builtin_bit_cast(float, v), b = a;
+  skv_swap_rows(a, b);
+  a = b = __builtin_bit_cast(float, op(__builtin_bit_cast(T, a), __builtin_bit_cast(T, b)));
+  skv_swap_halves(a, b);
+  return op(__builtin_bit_cast(T, a), __builtin_bit_cast(T, b));
+}
+template <typename T, typename Op>
+__device__ __forceinline__ T skv_over_wave(T v, Op op) {
+  v = op(v, skv_dpp<kSkvQuadXor1>(v, v));
+  v = op(v, skv_dpp<kSkvQuadXor2>(v, v));
+  v = op(v, skv_dpp<kSkvHalfMirror>(v, v));
+  v = op(v, skv_dpp<kSkvRowMirror>(v, v));
+  return skv_over_rows(v, op);
+}
+struct SkvAdd { template <typename T> __device__ T operator()(T a, T b) const { return a + b; } };
+struct SkvMax {
+  __device__ float operator()(float a, float b) const { return fmaxf(a, b); }
+  __device__ int operator()(int a, int b) const { return max(a, b); }
+};
+template <typename T>
+__device__ __forceinline__ T skv_wave_scan(T v) {   // inclusive
+  const T zero = 0;
+  v += skv_dpp<kSkvRowShr + 1>(zero, v);
+  v += skv_dpp<kSkvRowShr + 2>(zero, v);
+  v += skv_dpp<kSkvRowShr + 4>(zero, v);
+  v += skv_dpp<kSkvRowShr + 8>(zero, v);
+  v += skv_dpp<kSkvBcast15, 0xa>(zero, v);
+  v += skv_dpp<kSkvBcast31, 0xc>(zero, v);
+  return v;
+}
+template <typename T>
+__device__ __forceinline__ T skv_lane(T v, int from) {   // `from` the same in all lanes
+  if constexpr (sizeof(T) == 4) {
+    return __builtin_bit_cast(T, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), from));
+  } else {
+    const uint64_t x = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)x, from), hi = __builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), from);
+    return __builtin_bit_cast(T, (uint64_t)hi << 32 | lo);
+  }
+}
 // Inclusive scan over a workgroup of kThreads; `total` of all threads.  red: one place per wavefront.  Two barriers.
 template <int kThreads, typename T>
 __device__ inline T skv_block_scan(T v, T* red, T& total) {
   constexpr int kWaves = kThreads / 64;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int o = 1; o < 64; o <<= 1) {
-    const T x = __shfl_up(v, o);
-    if (lane >= o) v += x;
-  }
+  static_assert(kWaves <= 16);   // a row of lanes
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  v = skv_wave_scan(v);
   if (lane == 63) red[wave] = v;
   __syncthreads();
-  T x = lane < kWaves ? red[lane] : 0, all = x;
-  if (lane >= wave) x = 0;
-  for (int o = kWaves / 2; o >= 1; o >>= 1) {
-    x += __shfl_xor(x, o);
-    all += __shfl_xor(all, o);
-  }
-  total = __shfl(all, 0);
-  v += __shfl(x, 0);
+  const T zero = 0;
+  T x = lane < kWaves ? red[lane] : zero;
+  x += skv_dpp<kSkvRowShr + 1>(zero, x);
+  x += skv_dpp<kSkvRowShr + 2>(zero, x);
+  x += skv_dpp<kSkvRowShr + 4>(zero, x);
+  x += skv_dpp<kSkvRowShr + 8>(zero, x);
+  total = skv_lane(x, kWaves - 1);
+  if (wave > 0) v += skv_lane(x, wave - 1);
   __syncthreads();
   return v;
 }

@@ -36,11 +36,10 @@ __device__ inline bool differ(tok4 p, tok4 q) { return ((p.x ^ q.x) | (p.y ^ q.y
 __device__ inline uint64_t hash_block(const int32_t* x, int lane) {
   uint64_t v = 0;
   if (lane < 16) v = skv_mix_tok((uint32_t)x[lane], (uint32_t)lane);
-  for (int o = 8; o >= 1; o >>= 1) {
-    uint32_t lo = __shfl_xor((uint32_t)v, o, 16);
-    uint32_t hi = __shfl_xor((uint32_t)(v >> 32), o, 16);
-    v += ((uint64_t)hi << 32) | lo;
-  }
+  v += skv_dpp<kSkvRowRor + 8>(v, v);   // (the sum over the row, in every lane of it)
+  v += skv_dpp<kSkvRowRor + 4>(v, v);
+  v += skv_dpp<kSkvRowRor + 2>(v, v);
+  v += skv_dpp<kSkvRowRor + 1>(v, v);
   v = skv_hash_fin(v);
   uint32_t lo = (uint32_t)uniform((int)(uint32_t)v);
   uint32_t hi = (uint32_t)uniform((int)(uint32_t)(v >> 32));
@@ -67,7 +66,7 @@ __device__ inline int find_child(const SkvTreeDev& t, const SkvNode nd, const in
     if (empty) cand &= (empty & (~empty + 1)) - 1;  // only slots probed before the first empty one
     while (cand) {
       const int l = __builtin_ctzll(cand);
-      const int child = __shfl(e.child, l);
+      const int child = skv_lane(e.child, l);
       const int cfirst = uniform(t.nodes[child].first);
       if (block_equal(x, t.tok + (size_t)cfirst * 16, lane)) return child;
       cand &= cand - 1;  // same hash, different tokens: keep probing
@@ -276,7 +275,7 @@ __device__ inline int find_child_ranked(const SkvTreeDev& t, const SkvNode nd, c
     if (empty) cand &= (empty & (~empty + 1)) - 1;
     while (cand) {
       const int l = __builtin_ctzll(cand);
-      const int child = __shfl(e.child, l);
+      const int child = skv_lane(e.child, l);
       const int cfirst = uniform(t.nodes[child].first);
       if (block_equal(x, t.tok + (size_t)cfirst * 16, lane)) {
         const int m = uniform(t.meta[cfirst]);
@@ -289,7 +288,7 @@ __device__ inline int find_child_ranked(const SkvTreeDev& t, const SkvNode nd, c
           } else {   // more copies than lanes: keep the kMaxCopies oldest, and say so
             *limits |= SKV_LIMIT_COPIES;
             int worst = my_canon;
-            for (int o = 32; o >= 1; o >>= 1) worst = max(worst, __shfl_xor(worst, o));
+            worst = skv_over_wave(worst, SkvMax());
             if (id < worst) {
               const uint64_t holder = ballot64(my_canon == worst);
               if (lane == __builtin_ctzll(holder)) { my_canon = id; my_child = child; }
@@ -304,10 +303,10 @@ __device__ inline int find_child_ranked(const SkvTreeDev& t, const SkvNode nd, c
   *n_out = n;
   if (n == 0) return -1;
   int rank = 0;                    // how many candidates are older than this lane's
-  for (int i = 0; i < n; ++i) rank += __shfl(my_canon, i) < my_canon ? 1 : 0;
+  for (int i = 0; i < n; ++i) rank += skv_lane(my_canon, i) < my_canon ? 1 : 0;
   if (want >= n) want = 0;
   const uint64_t sel = ballot64(lane < n && rank == want);
-  return __shfl(my_child, __builtin_ctzll(sel));
+  return skv_lane(my_child, __builtin_ctzll(sel));
 }
 
 __global__ __launch_bounds__(kWave* kWavesPerWg) void skv_match_copies_kernel(
