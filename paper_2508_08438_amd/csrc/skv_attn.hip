@@ -513,9 +513,6 @@ __device__ __forceinline__ s16x4 lds_read_tr16_b64(uint32_t addr, int byte_off) 
 __device__ __forceinline__ void lds_wait(int n, bf16x8& a) {
   asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(a) : "i"(n));
 }
-__device__ __forceinline__ void lds_wait(int n, bf16x8& a, bf16x8& b) {
-  asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(a), "+v"(b) : "i"(n));
-}
 __device__ __forceinline__ void lds_wait(int n, bf16x8& a, bf16x8& b, bf16x8& c, bf16x8& d) {
   asm volatile("s_waitcnt lgkmcnt(%4)" : "+v"(a), "+v"(b), "+v"(c), "+v"(d) : "i"(n));
 }
