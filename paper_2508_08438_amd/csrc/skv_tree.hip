@@ -88,21 +88,16 @@ struct SkvHostMirror {
   // Pinned memory small transfers go through: kStageBytes of it from the first write on, null before, and as long as none is
   // to be had.  Every call that uses it waits for its own kernels before it returns.
   char* stage = nullptr;
-  // Kept for their memory only, nothing in them outlives a call: what an insertion goes back to when the slab is full, the
-  // arrays a compaction writes and changes places with, and marks per page or input block.  Fresh from the allocator on every
-  // call they are faulted in again, 0.3 us per 4 KB, and the records' arrays, whose room for the whole slab a compaction
-  // would lose, grow by copying: rounds of 64 requests in an index of 67 k, a compaction every eleven,
-  // 780 to 940 us against 745 to 760; a tree's first round 960 -> 640.
+  // Kept for their memory only, nothing in them outlives a call: what an insertion that may fill the slab goes back to, what a
+  // compaction lays out and changes places with, and marks per page or input block.  Fresh from the allocator on every
+  // call they are faulted in again, 0.3 us per 4 KB.
   struct {
     std::vector<SkvNode> nodes;
     std::vector<SkvSlot> slots;
     std::vector<uint8_t> page_used;
     std::vector<int32_t> kids, filled, parent, node_of;
   } saved;
-  struct {
-    std::vector<int32_t> tok, canon, page, vis, flat_of;
-    std::vector<uint32_t> words;
-  } spare;
+  std::vector<uint32_t> words;
   std::vector<uint8_t> marks;
   void reserve_records(std::vector<int32_t>& tok, std::initializer_list<std::vector<int32_t>*> others) const {   // for a full slab
     tok.reserve((size_t)cap_blocks * 16);
@@ -277,11 +272,10 @@ __global__ void promote_kernel(SkvTreeDev t, int64_t n_in_blocks, const int32_t*
   }
 }
 
-// words [from, n) of every plane
-__global__ void fill_planes_kernel(uint32_t* p, size_t from, size_t n, int planes) {
-  const size_t len = n - from;
+// words [from, from + len) of every plane
+__global__ void fill_planes_kernel(uint32_t* p, size_t plane, size_t from, size_t len, int planes) {
   for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < len * planes; i += (size_t)gridDim.x * blockDim.x)
-    p[i / len * n + from + i % len] = 0u;
+    p[i / len * plane + from + i % len] = 0u;
 }
 
 // Words moved between the slab and the pinned memory, several spans in one launch (blockIdx.y).  One launch and one wait take
@@ -912,9 +906,22 @@ extern "C" int skv_tree_insert(skv_tree* t, int32_t n_req, const int32_t* req_of
       }
     }
   }
-  // work on the mirror; a full slab restores the snapshot and changes nothing
-  m->saved.nodes = m->nodes; m->saved.kids = m->kids; m->saved.slots = m->slots; m->saved.page_used = m->page_used;
-  m->saved.filled = m->filled; m->saved.parent = m->parent; m->saved.node_of = m->node_of;
+  // Work on the mirror; a full slab restores the snapshot and changes nothing.  Where no block, node or table the requests can ask for
+  // passes what is free there is none to make, a copy of the index's size (116 -> 97 us for 64 requests, 7.7 k new blocks): a request adds the blocks it has pages for and two
+  // nodes at most, one with a table of four and one to a node whose table may move to one of twice its children.
+  bool fits;
+  {
+    int64_t blocks = 0, kids = n_req;
+    for (int32_t r = 0; r < n_req; ++r) blocks += have[r];
+    for (const int32_t k : m->kids) kids = std::max<int64_t>(kids, k + (int64_t)n_req);
+    fits = std::max<int64_t>(t->dev.n_blocks, t->n_in_blocks) + blocks <= m->cap_blocks &&
+           (int64_t)m->nodes.size() + 2 * (int64_t)n_req <= m->cap_blocks + 1 &&
+           (double)m->slots_used + (double)n_req * (4.0 * (double)kids + 8.0) <= (double)slots_for((size_t)m->cap_blocks);
+  }
+  if (!fits) {
+    m->saved.nodes = m->nodes; m->saved.kids = m->kids; m->saved.slots = m->slots; m->saved.page_used = m->page_used;
+    m->saved.filled = m->filled; m->saved.parent = m->parent; m->saved.node_of = m->node_of;
+  }
   const size_t slots_used0 = m->slots_used, tok0 = m->tok.size(), blocks0 = m->canon.size(), in0 = m->flat_of.size();
   Inserter ins{t, m, t->dev.n_blocks, t->n_in_blocks, {}, {}, SIZE_MAX, 0, SIZE_MAX, 0};
   hipStream_t st = (hipStream_t)stream;
@@ -940,6 +947,7 @@ extern "C" int skv_tree_insert(skv_tree* t, int32_t n_req, const int32_t* req_of
     first_inserted[r] = (int32_t)first;
     n_inserted[r] = (int32_t)n_new;
   }
+  if (full && fits) return SKV_EINVAL;   // (it cannot be: the bounds above)
   if (full) {
     m->nodes = m->saved.nodes; m->kids = m->saved.kids; m->slots = m->saved.slots; m->page_used = m->saved.page_used;
     m->filled = m->saved.filled; m->parent = m->saved.parent; m->node_of = m->saved.node_of;
@@ -1011,23 +1019,41 @@ extern "C" int skv_evict(skv_tree* t, int64_t n_want, const int32_t* protect_ids
   const uint32_t* const epoch = in_stage ? (const uint32_t*)m->stage : own.data();
   std::vector<uint8_t>& prot = m->marks;
   prot.assign((size_t)t->n_in_blocks, 0);
-  for (int64_t i = 0; i < n_protect; ++i)
-    if (protect_ids[i] >= 0 && protect_ids[i] < t->n_in_blocks) prot[protect_ids[i]] = 1;
+  constexpr int64_t kRun = 64;   // ids mostly come in runs
+  for (int64_t i = 0; i < n_protect;) {
+    const int64_t n = std::min(kRun, n_protect - i);
+    const int32_t first = protect_ids[i];
+    int32_t off = 0;
+    for (int64_t k = 0; k < n; ++k) off |= (int32_t)((uint32_t)protect_ids[i + k] - (uint32_t)first) ^ (int32_t)k;
+    if (off == 0 && first >= 0 && first + n <= t->n_in_blocks) {
+      memset(&prot[first], 1, (size_t)n);
+    } else {
+      for (int64_t k = 0; k < n; ++k)
+        if (protect_ids[i + k] >= 0 && protect_ids[i + k] < t->n_in_blocks) prot[protect_ids[i + k]] = 1;
+    }
+    i += n;
+  }
   // candidates: the last block of every childless node, oldest (epoch, block id) first
   struct Cand { uint32_t epoch; int32_t id, node; };
   auto later = [](const Cand& a, const Cand& b) { return a.epoch != b.epoch ? a.epoch > b.epoch : a.id > b.id; };
   std::vector<Cand> heap;
-  auto push_tail = [&](int32_t n) {
+  auto tail_of = [&](int32_t n) {
     const SkvNode& nd = m->nodes[n];
     const int32_t f = nd.first + nd.n_blocks - 1;
-    heap.push_back(Cand{epoch[f], m->canon[f], n});
+    return Cand{epoch[f], m->canon[f], n};
+  };
+  auto push_tail = [&](int32_t n) {
+    heap.push_back(tail_of(n));
     std::push_heap(heap.begin(), heap.end(), later);
   };
-  for (int32_t n = 1; n < (int32_t)m->nodes.size(); ++n)
-    if (m->kids[n] == 0 && m->nodes[n].n_blocks > 0) push_tail(n);
-  size_t node_lo = SIZE_MAX, node_hi = 0, slot_lo = SIZE_MAX, slot_hi = 0, blk_lo = SIZE_MAX, blk_hi = 0, id_lo = SIZE_MAX, id_hi = 0;
-  std::vector<int32_t> gone;   // record and input id of every evicted block
-  gone.reserve(2 * (size_t)std::min(n_want, nb));
+  for (int32_t n = 1; n < (int32_t)m->nodes.size(); ++n) {
+    if (m->kids[n] || m->nodes[n].n_blocks <= 0) continue;
+    const Cand tail = tail_of(n);
+    if (!prot[tail.id]) heap.push_back(tail);   // (in use: the node keeps its tail, and with it everything above)
+  }
+  std::make_heap(heap.begin(), heap.end(), later);
+  size_t node_lo = SIZE_MAX, node_hi = 0, slot_lo = SIZE_MAX, slot_hi = 0;
+  std::vector<int32_t> gone(2 * (size_t)std::min(n_want, nb));   // record and input id of every evicted block
   int64_t done = 0;
   bool held = false;           // `c` is the next candidate already: the block before the last one of the same node, not younger
   Cand c{};                    // than the oldest in the heap (a node's blocks mostly go one after another)
@@ -1038,21 +1064,22 @@ extern "C" int skv_evict(skv_tree* t, int64_t n_want, const int32_t* protect_ids
       heap.pop_back();
     }
     held = false;
-    if (prot[c.id]) continue;  // in use: this node keeps its tail, and with it everything above
     SkvNode& nd = m->nodes[c.node];
+    if (prot[c.id]) {   // in use, as above
+      node_lo = std::min(node_lo, (size_t)c.node); node_hi = std::max(node_hi, (size_t)c.node + 1);
+      continue;
+    }
     const int32_t f = nd.first + nd.n_blocks - 1;
+    const int32_t page = m->page[f];
     evicted_ids[done] = c.id;
-    evicted_pages[done] = m->page[f];
+    evicted_pages[done] = page;
+    gone[2 * done] = f;
+    gone[2 * done + 1] = c.id;
     ++done;
-    m->page_used[m->page[f]] = 0;
+    m->page_used[page] = 0;
     m->canon[f] = -1;
     m->flat_of[c.id] = -1;
-    gone.push_back(f);
-    gone.push_back(c.id);
-    blk_lo = std::min(blk_lo, (size_t)f); blk_hi = std::max(blk_hi, (size_t)f + 1);
-    id_lo = std::min(id_lo, (size_t)c.id); id_hi = std::max(id_hi, (size_t)c.id + 1);
     nd.n_blocks--;
-    node_lo = std::min(node_lo, (size_t)c.node); node_hi = std::max(node_hi, (size_t)c.node + 1);
     if (nd.n_blocks > 0) {
       const Cand next{epoch[f - 1], m->canon[f - 1], c.node};
       if (heap.empty() || !later(next, heap.front())) {
@@ -1061,8 +1088,10 @@ extern "C" int skv_evict(skv_tree* t, int64_t n_want, const int32_t* protect_ids
       } else {
         push_tail(c.node);
       }
-      continue;
+      if (held && done < n_want) continue;   // (the node is noted when it is left)
     }
+    node_lo = std::min(node_lo, (size_t)c.node); node_hi = std::max(node_hi, (size_t)c.node + 1);
+    if (nd.n_blocks > 0) continue;
     // the node is gone: its entry in the parent's table becomes a removed slot
     const int32_t p = m->parent[c.node];
     const SkvNode& pn = m->nodes[p];
@@ -1085,6 +1114,7 @@ extern "C" int skv_evict(skv_tree* t, int64_t n_want, const int32_t* protect_ids
   up.add(m->L.nodes + node_lo * sizeof(SkvNode), &m->nodes[node_lo], n_node * sizeof(SkvNode));
   if (n_slot) up.add(m->L.slots + slot_lo * sizeof(SkvSlot), &m->slots[slot_lo], n_slot * sizeof(SkvSlot));
   bool staged;
+  gone.resize(2 * (size_t)done);
   rc = up.up(st, gone.size() * 4, &staged);
   if (rc) return rc;
   if (staged) {
@@ -1093,6 +1123,12 @@ extern "C" int skv_evict(skv_tree* t, int64_t n_want, const int32_t* protect_ids
     evict_kernel<<<grid_for((size_t)done, 256), 256, 0, st>>>((int32_t*)(m->base + m->L.canon), (int32_t*)(m->base + m->L.flat_of), rec_id, done);
     SKV_HIP(hipGetLastError());
   } else {
+    size_t blk_lo = SIZE_MAX, blk_hi = 0, id_lo = SIZE_MAX, id_hi = 0;
+    for (int64_t i = 0; i < done; ++i) {
+      const size_t f = (size_t)gone[2 * i], id = (size_t)gone[2 * i + 1];
+      blk_lo = std::min(blk_lo, f); blk_hi = std::max(blk_hi, f + 1);
+      id_lo = std::min(id_lo, id); id_hi = std::max(id_hi, id + 1);
+    }
     SKV_HIP(hipMemcpyAsync(m->base + m->L.canon + blk_lo * 4, &m->canon[blk_lo], (blk_hi - blk_lo) * 4, hipMemcpyHostToDevice, st));
     SKV_HIP(hipMemcpyAsync(m->base + m->L.flat_of + id_lo * 4, &m->flat_of[id_lo], (id_hi - id_lo) * 4, hipMemcpyHostToDevice, st));
   }
@@ -1103,142 +1139,146 @@ extern "C" int skv_evict(skv_tree* t, int64_t n_want, const int32_t* protect_ids
 // ---- reclaiming record space (Section 4.3.2 Progressive Eviction: a chain's address vector shrinks as its entries
 // are released and the chain itself goes once the vector is empty) ----
 // Evictions shorten node runs and unlink emptied nodes, insertions abandon outgrown child tables and split runs; the
-// records they leave behind stay in the slab.  Compaction lays the live structure out afresh: nodes in depth-first
-// order with their blocks contiguous, child tables sized for the children they have, input block ids renumbered
-// densely in their old order (so "older copy" and eviction ties still compare the same way).  The per-block state
-// the kernels own (visibility bits, counters, epochs) is read back, permuted with the records and written again.
+// records they leave behind stay in the slab.  Compaction closes the gaps: block records, nodes and input block ids keep their order
+// (so "older copy" and eviction ties still compare the same way) and move up, child tables are laid out afresh for the children they
+// have.  What lies before the first gap stays where it is, on the device too, so the cost is that of the nodes and of what moves; of that,
+// the per-block state the kernels own (visibility bits, counters, epochs) is read back, moved with the records and written again.
+// (67 k blocks in 1.5 k nodes, ten rounds of 7.7 k inserted and evicted behind them: 115 us, laid out afresh throughout 1090.)
 extern "C" int skv_tree_compact(skv_tree* t, int32_t* id_map, int64_t* n_in_blocks_after, void* stream) {
   if (!t || !t->host) return SKV_EINVAL;
   SkvHostMirror* m = t->host;
   hipStream_t st = (hipStream_t)stream;
-  const int64_t nb_old = t->dev.n_blocks, nin_old = t->n_in_blocks;
+  const size_t nb_old = (size_t)t->dev.n_blocks, nin_old = (size_t)t->n_in_blocks, live = (size_t)m->live_blocks;
   if (nin_old > 0 && !id_map) return SKV_EINVAL;
   const size_t plane = t->dev.ctr_plane;
-  // the state the kernels own, as the device has it: visibility, epochs, counter planes
-  const size_t live = (size_t)m->live_blocks;
-  std::vector<uint32_t>& words = m->spare.words;   // read, and behind it written
-  words.resize((size_t)nb_old * (2 + SKV_CTR_FIELDS) + live * (1 + SKV_CTR_FIELDS));
-  uint32_t* const state = words.data();
-  const int32_t* meta = (const int32_t*)state;
-  const uint32_t *epoch = state + nb_old, *ctr[SKV_CTR_FIELDS];
-  for (int q = 0; q < SKV_CTR_FIELDS; ++q) ctr[q] = state + (size_t)nb_old * (2 + q);
-  Mover down{m};
-  down.add(m->L.meta, state, (size_t)nb_old * 4);
-  down.add(m->L.epoch, state + nb_old, (size_t)nb_old * 4);
-  for (int q = 0; q < SKV_CTR_FIELDS; ++q) down.add(m->L.ctr + q * plane * 4, ctr[q], (size_t)nb_old * 4);
-  int rc = down.down(st);
-  if (rc) return rc;
-  // dense input ids, old order kept
-  std::vector<int32_t> new_id((size_t)nin_old, -1);
-  int32_t n_ids = 0;
-  for (int64_t i = 0; i < nin_old; ++i)
-    if (m->flat_of[i] >= 0) new_id[i] = n_ids++;
-  // depth-first relabelling of the nodes that can still be reached; blocks follow their nodes
-  std::vector<SkvNode> nodes;
-  std::vector<int32_t> kids, parent, old_of_new;
-  std::vector<SkvSlot> slots;
-  std::vector<int32_t>&tok = m->spare.tok, &canon = m->spare.canon, &page = m->spare.page, &n_meta = m->spare.vis, &flat_of = m->spare.flat_of;
-  m->reserve_records(tok, {&canon, &page, &n_meta, &flat_of});
-  tok.resize(live * 16); canon.resize(live); page.resize(live); n_meta.resize(live);
-  flat_of.assign((size_t)n_ids, -1);
   const Layout& L = m->L;
-  uint32_t* const n_epoch = state + (size_t)nb_old * (2 + SKV_CTR_FIELDS);
-  uint32_t* n_ctr[SKV_CTR_FIELDS];
-  for (int q = 0; q < SKV_CTR_FIELDS; ++q) n_ctr[q] = n_epoch + live * (1 + q);
-  size_t filled_blocks = 0;
-  std::vector<std::pair<int32_t, int32_t>> todo;   // (old node, new parent)
-  todo.push_back({0, -1});
-  std::vector<std::vector<std::pair<uint64_t, int32_t>>> children;   // per new node: (hash, new child) in old table order
-  while (!todo.empty()) {
-    const auto [on, np] = todo.back();
-    todo.pop_back();
-    const SkvNode o = m->nodes[on];
-    const int32_t nn = (int32_t)nodes.size();
-    nodes.push_back(SkvNode{(int32_t)filled_blocks, o.n_blocks, 0, 0});
-    if (filled_blocks + (size_t)o.n_blocks > live) return SKV_EINVAL;   // the mirror lost track of a block: refuse rather than drop it
-    kids.push_back(0);
-    parent.push_back(np);
-    children.emplace_back();
-    if (const size_t n = (size_t)o.n_blocks) {   // a node's blocks lie together before and after
-      const size_t f = (size_t)o.first, g = filled_blocks;
-      for (size_t k = 0; k < n; ++k) {
-        const int32_t id = new_id[m->canon[f + k]];
-        canon[g + k] = id;
-        flat_of[id] = (int32_t)(g + k);
+  size_t f0 = 0, d0 = 0;   // the first record, and input id, that is gone
+  while (f0 < nb_old && m->canon[f0] >= 0) ++f0;
+  while (d0 < nin_old && m->flat_of[d0] >= 0) ++d0;
+  std::vector<int32_t> moved;   // nodes behind the gap, in the order of their records
+  size_t n_live = f0;
+  for (size_t f = f0; f < nb_old;) {
+    if (m->canon[f] < 0) {
+      ++f;
+      continue;
+    }
+    const int32_t n = m->node_of[f];
+    const SkvNode& nd = m->nodes[n];
+    if ((size_t)nd.first != f || nd.n_blocks <= 0 || f + (size_t)nd.n_blocks > nb_old) return SKV_EINVAL;   // the mirror lost track of a block: refuse rather than drop it
+    moved.push_back(n);
+    f += (size_t)nd.n_blocks;
+    n_live += (size_t)nd.n_blocks;
+  }
+  if (n_live != live) return SKV_EINVAL;
+  // what the kernels own of the records that move, as the device has it: visibility, epochs, counter planes
+  constexpr int kOwned = 2 + SKV_CTR_FIELDS;
+  const size_t n_read = live > f0 ? nb_old - f0 : 0, n_write = live - f0;
+  m->words.resize((n_read + n_write) * kOwned);
+  uint32_t *state[kOwned], *n_state[kOwned];
+  size_t off[kOwned];
+  for (int q = 0; q < kOwned; ++q) {
+    state[q] = m->words.data() + n_read * q;
+    n_state[q] = m->words.data() + n_read * kOwned + n_write * q;
+    off[q] = (q == 0 ? L.meta : q == 1 ? L.epoch : L.ctr + (q - 2) * plane * 4) + f0 * 4;
+  }
+  Mover down{m};
+  for (int q = 0; q < kOwned; ++q) down.add(off[q], state[q], n_read * 4);
+  int rc = n_read ? down.down(st) : SKV_OK;
+  if (rc) return rc;
+  // records
+  size_t g = f0, id_lo = d0, canon_lo = f0;
+  for (const int32_t n : moved) {
+    SkvNode& nd = m->nodes[n];
+    const size_t f = (size_t)nd.first, k = (size_t)nd.n_blocks;
+    memmove(&m->tok[g * 16], &m->tok[f * 16], k * 64);
+    memmove(&m->page[g], &m->page[f], k * 4);
+    memmove(&m->canon[g], &m->canon[f], k * 4);
+    for (int q = 0; q < kOwned; ++q) memcpy(n_state[q] + (g - f0), state[q] + (f - f0), k * 4);
+    memcpy(&m->vis[g], n_state[0] + (g - f0), k * 4);
+    for (size_t i = g; i < g + k; ++i) {
+      m->flat_of[m->canon[i]] = (int32_t)i;
+      id_lo = std::min(id_lo, (size_t)m->canon[i]);
+    }
+    nd.first = (int32_t)g;
+    g += k;
+  }
+  // dense input ids, old order kept
+  size_t n_ids = d0;
+  for (size_t i = 0; i < d0; ++i) id_map[i] = (int32_t)i;
+  for (size_t i = d0; i < nin_old; ++i) {
+    const int32_t f = m->flat_of[i];
+    id_map[i] = f < 0 ? -1 : (int32_t)n_ids;
+    if (f < 0) continue;
+    canon_lo = std::min(canon_lo, (size_t)f);
+    m->canon[f] = (int32_t)n_ids;
+    m->flat_of[n_ids++] = f;
+  }
+  m->tok.resize(live * 16); m->page.resize(live); m->canon.resize(live); m->vis.resize(live); m->node_of.resize(live);
+  m->flat_of.resize(n_ids);
+  // nodes, and their tables
+  std::vector<SkvNode>& nodes = m->saved.nodes;
+  std::vector<SkvSlot>& slots = m->saved.slots;
+  std::vector<int32_t>&kids = m->saved.kids, &filled = m->saved.filled, &parent = m->saved.parent;
+  nodes.clear(); slots.clear(); kids.clear(); filled.clear(); parent.clear();
+  std::vector<int32_t> new_node(m->nodes.size(), -1);
+  int32_t n_nodes = 0;
+  for (size_t n = 0; n < m->nodes.size(); ++n)
+    if (n == 0 || m->nodes[n].n_blocks > 0) new_node[n] = n_nodes++;
+  for (size_t n = 0; n < m->nodes.size(); ++n) {
+    if (new_node[n] < 0) continue;
+    SkvNode nd = m->nodes[n];
+    const SkvSlot* const old = m->slots.data() + nd.tab_off;
+    int32_t n_kids = 0;
+    for (int32_t q = 0; q < nd.tab_cap; ++q) n_kids += old[q].child >= 0;
+    const int32_t old_cap = nd.tab_cap;
+    nd.tab_off = nd.tab_cap = 0;
+    if (n_kids) {
+      const uint32_t cap = next_pow2((uint32_t)std::max(4, 2 * n_kids));
+      nd.tab_off = (int32_t)slots.size();
+      nd.tab_cap = (int32_t)cap;
+      slots.resize(slots.size() + cap, SkvSlot{0, 0, -1, 0});
+      for (int32_t q = 0; q < old_cap; ++q) {
+        if (old[q].child < 0) continue;
+        uint32_t at = old[q].hash_lo & (cap - 1);
+        while (slots[(size_t)nd.tab_off + at].child >= 0) at = (at + 1) & (cap - 1);
+        slots[(size_t)nd.tab_off + at] = SkvSlot{old[q].hash_lo, old[q].hash_hi, new_node[old[q].child], 0};
       }
-      memcpy(&tok[g * 16], &m->tok[f * 16], n * 64);
-      memcpy(&page[g], &m->page[f], n * 4);
-      memcpy(&n_meta[g], meta + f, n * 4);
-      memcpy(n_epoch + g, epoch + f, n * 4);
-      for (int q = 0; q < SKV_CTR_FIELDS; ++q) memcpy(n_ctr[q] + g, ctr[q] + f, n * 4);
-      filled_blocks += n;
     }
-    if (np >= 0) {   // the hash of its first block keys the node in its parent's table
-      const uint64_t h = skv_hash_block_host(&tok[(size_t)nodes[nn].first * 16]);
-      children[np].push_back({h, nn});
-      kids[np]++;
-    }
-    for (int32_t q = o.tab_cap - 1; q >= 0; --q) {
-      const int32_t c = m->slots[(size_t)o.tab_off + q].child;
-      if (c >= 0) todo.push_back({c, nn});
-    }
+    nodes.push_back(nd);
+    kids.push_back(n_kids);
+    filled.push_back(n_kids);
+    parent.push_back(m->parent[n] < 0 ? -1 : new_node[m->parent[n]]);
+    if (new_node[n] != (int32_t)n || (size_t)nd.first >= f0)
+      std::fill_n(m->node_of.begin() + nd.first, n ? nd.n_blocks : 0, new_node[n]);
   }
-  std::vector<int32_t> filled(nodes.size(), 0);
-  for (size_t n = 0; n < nodes.size(); ++n) {
-    if (children[n].empty()) continue;
-    const uint32_t cap = next_pow2((uint32_t)std::max<size_t>(4, 2 * children[n].size()));
-    nodes[n].tab_off = (int32_t)slots.size();
-    nodes[n].tab_cap = (int32_t)cap;
-    slots.resize(slots.size() + cap, SkvSlot{0, 0, -1, 0});
-    for (const auto& [h, c] : children[n]) {
-      uint32_t q = (uint32_t)h & (cap - 1);
-      while (slots[(size_t)nodes[n].tab_off + q].child >= 0) q = (q + 1) & (cap - 1);
-      slots[(size_t)nodes[n].tab_off + q] = SkvSlot{(uint32_t)h, (uint32_t)(h >> 32), c, 0};
-    }
-    filled[n] = (int32_t)children[n].size();
-  }
-  const int64_t nb = (int64_t)filled_blocks;
-  if (nb != m->live_blocks) return SKV_EINVAL;   // the mirror lost track of a block: refuse rather than drop it
-  // write everything back; counters and epochs of the free records start from zero again
+  m->nodes.swap(nodes);
+  m->slots.swap(slots);
+  m->kids.swap(kids);
+  m->filled.swap(filled);
+  m->parent.swap(parent);
+  m->slots_used = m->slots.size();
+  // write back what changed; counters and epochs of the free records start from zero again
   Mover up{m};
-  up.add(L.tok, tok.data(), live * 64);
-  up.add(L.page, page.data(), live * 4);
-  up.add(L.meta, n_meta.data(), live * 4);
-  up.add(L.canon, canon.data(), live * 4);
-  up.add(L.flat_of, flat_of.data(), flat_of.size() * 4);
-  up.add(L.nodes, nodes.data(), nodes.size() * sizeof(SkvNode));
-  up.add(L.slots, slots.data(), slots.size() * sizeof(SkvSlot));
-  up.add(L.epoch, n_epoch, live * 4);
-  for (int q = 0; q < SKV_CTR_FIELDS; ++q) up.add(L.ctr + q * plane * 4, n_ctr[q], live * 4);
+  up.add(L.tok + f0 * 64, m->tok.data() + f0 * 16, n_write * 64);
+  up.add(L.page + f0 * 4, m->page.data() + f0, n_write * 4);
+  up.add(L.canon + canon_lo * 4, m->canon.data() + canon_lo, (live - canon_lo) * 4);
+  up.add(L.flat_of + id_lo * 4, m->flat_of.data() + id_lo, (n_ids - id_lo) * 4);
+  up.add(L.nodes, m->nodes.data(), m->nodes.size() * sizeof(SkvNode));
+  up.add(L.slots, m->slots.data(), m->slots.size() * sizeof(SkvSlot));
+  for (int q = 0; q < kOwned; ++q) up.add(off[q], n_state[q], n_write * 4);
   rc = up.up(st);
   if (rc) return rc;
-  if (m->cap_blocks > nb) {
-    const size_t n = (size_t)(m->cap_blocks - nb);
-    fill_planes_kernel<<<grid_for(n * SKV_CTR_FIELDS, 256), 256, 0, st>>>(t->dev.ctr, (size_t)nb, t->dev.ctr_plane, SKV_CTR_FIELDS);
-    fill_u32_kernel<<<grid_for(n, 256), 256, 0, st>>>(t->dev.epoch + nb, n, 0u);
+  if (nb_old > live) {
+    const size_t n = nb_old - live;
+    fill_planes_kernel<<<grid_for(n * SKV_CTR_FIELDS, 256), 256, 0, st>>>(t->dev.ctr, plane, live, n, SKV_CTR_FIELDS);
+    fill_u32_kernel<<<grid_for(n, 256), 256, 0, st>>>(t->dev.epoch + live, n, 0u);
     SKV_HIP(hipGetLastError());
   }
   SKV_HIP(hipStreamSynchronize(st));
-  for (int64_t i = 0; i < nin_old; ++i) id_map[i] = new_id[i];
-  m->nodes = std::move(nodes);
-  m->kids = std::move(kids);
-  m->filled = std::move(filled);
-  m->parent = std::move(parent);
-  m->slots = std::move(slots);
-  m->slots_used = m->slots.size();
-  m->tok.swap(tok);
-  m->canon.swap(canon);
-  m->page.swap(page);
-  m->flat_of.swap(flat_of);
-  m->vis.swap(n_meta);   // just read back: exact
-  m->node_of.assign((size_t)nb, 0);
-  for (size_t n = 1; n < m->nodes.size(); ++n)
-    for (int32_t k = 0; k < m->nodes[n].n_blocks; ++k) m->node_of[(size_t)m->nodes[n].first + k] = (int32_t)n;
-  m->vis_stale = false;
-  t->dev.n_blocks = (int32_t)nb;
+  t->dev.n_blocks = (int32_t)live;
   t->dev.n_nodes = (int32_t)m->nodes.size() - 1;
-  t->n_in_blocks = n_ids;
-  if (n_in_blocks_after) *n_in_blocks_after = n_ids;
+  t->n_in_blocks = (int64_t)n_ids;
+  if (n_in_blocks_after) *n_in_blocks_after = (int64_t)n_ids;
   return SKV_OK;
 }
 
