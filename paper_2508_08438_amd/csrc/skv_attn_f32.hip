@@ -63,7 +63,13 @@ __device__ __forceinline__ f32x16 mfma_pieces(const Pieces& a, const Pieces& b, 
   return acc;
 }
 
-__device__ inline float other_half(float x) { return __shfl_xor(x, 32); }
+// op over a value and the one 32 lanes away
+template <typename Op>
+__device__ __forceinline__ float over_halves(float x, Op op) {
+  float a = x, b = x;
+  skv_swap_halves(a, b);
+  return op(a, b);
+}
 
 template <int N> struct vec_of;
 template <> struct vec_of<2> { typedef f32x2 type; };
@@ -170,11 +176,10 @@ __device__ __forceinline__ void one_row(const SkvAttnF32Params& p, const Row& ro
       for (int d = 0; d < kKept; ++d) acc[d] *= alpha;
     }
   }
-  float all = m;
-  for (int x = 32; x >= 1; x >>= 1) all = fmaxf(all, __shfl_xor(all, x));
+  const float all = skv_over_wave(m, SkvMax());
   const float f = __builtin_amdgcn_exp2f(m - (all == -INFINITY ? 0.f : all));   // a lane without a key: 0
   l *= f;
-  for (int x = 32; x >= 1; x >>= 1) l += __shfl_xor(l, x);
+  l = skv_over_wave(l, SkvAdd());
   float* const out = (float*)p.out + ((size_t)row.tok * p.Hq + row.h) * D + first + lane;
 #pragma unroll
   for (int v = 0; v < kKept / 64; ++v) {
@@ -277,7 +282,7 @@ __device__ __forceinline__ void softmax_step(f32x16& s, const f32x16& s_low, int
   float mx = s[0];
 #pragma unroll
   for (int e = 1; e < 16; ++e) mx = fmaxf(mx, s[e]);
-  mx = fmaxf(mx, other_half(mx)) * c;
+  mx = over_halves(mx, SkvMax()) * c;
   const float m_new = fmaxf(m_run, mx);
   const float ref = m_new == -INFINITY ? 0.f : m_new;   // no visible key so far: every term is 0
   float sum[2] = {0.f, 0.f};
@@ -500,7 +505,7 @@ __global__ __launch_bounds__(64 * W, D == 64 ? 2 : 1) void attn_f32_kernel(SkvAt
     }
     asm volatile("s_nop 7\n\ts_nop 3");
   }
-  l_run += other_half(l_run);
+  l_run = over_halves(l_run, SkvAdd());
   const bool no_pieces = q_range.odd() || !all_finite(o, l_run), small = some_small(o, l_run);
   if (__builtin_expect(__syncthreads_or(no_pieces || small), 0)) {   // (Q is no longer needed behind this either)
     if (__syncthreads_or(no_pieces || tiny_columns<D, W>(p, it))) {
@@ -728,7 +733,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_f32_tile_kernel(SkvAttnF32Pa
       if (key0 < key_end_w) block(key0, kb);
     }
   }
-  l_run += other_half(l_run);
+  l_run = over_halves(l_run, SkvAdd());
 
   const bool no_pieces = q_range.odd() || !all_finite(o, l_run), small = some_small(o, l_run);
   if (__builtin_expect(__syncthreads_or(no_pieces || small), 0)) {
