@@ -52,8 +52,14 @@ __device__ inline bool block_equal(const int32_t* a, const int32_t* b, int lane)
   return ballot64(ne) == 0;
 }
 
-// child of `nd` whose first block equals the request block at x, or -1
-__device__ inline int find_child(const SkvTreeDev& t, const SkvNode nd, const int32_t* x, int lane) {
+// The record of a node, the same in all lanes.
+__device__ inline SkvNode node_at(const SkvTreeDev& t, int node) {
+  const SkvNode n = t.nodes[node];
+  return {uniform(n.first), uniform(n.n_blocks), uniform(n.tab_off), uniform(n.tab_cap)};
+}
+
+// child of `nd` whose first block equals the request block at x, and its record; or -1
+__device__ inline int find_child(const SkvTreeDev& t, const SkvNode nd, const int32_t* x, int lane, SkvNode& found) {
   if (nd.tab_cap == 0) return -1;
   const uint64_t h = hash_block(x, lane);
   const uint32_t mask = (uint32_t)nd.tab_cap - 1u;
@@ -67,8 +73,8 @@ __device__ inline int find_child(const SkvTreeDev& t, const SkvNode nd, const in
     while (cand) {
       const int l = __builtin_ctzll(cand);
       const int child = skv_lane(e.child, l);
-      const int cfirst = uniform(t.nodes[child].first);
-      if (block_equal(x, t.tok + (size_t)cfirst * 16, lane)) return child;
+      found = node_at(t, child);
+      if (block_equal(x, t.tok + (size_t)found.first * 16, lane)) return child;
       cand &= cand - 1;  // same hash, different tokens: keep probing
     }
     if (empty) return -1;
@@ -105,6 +111,9 @@ __global__ __launch_bounds__(kWave* kWavesPerWg) void skv_match_kernel(
   const int r = kCoop > 1 ? blockIdx.x : blockIdx.x * kWavesPerWg + (threadIdx.x >> 6);
   if (kCoop == 1 && r >= n_req) return;  // whole wave leaves; this form has no barriers
   const int lo = uniform(req_off[r]), hi = uniform(req_off[r + 1]);
+  // Current node, the root.  A walk is a chain of reads, so none of them is made twice: the root's record travels with the offsets, a
+  // child's is the one its first block was found by (one request behind 2992 keys 5.2 -> 4.8 us, 16 of up to 8192 6.5 -> 6.1).
+  SkvNode cur = node_at(t, 0);
   const int tenant = uniform(req_tenant[r]);
   int nb = hi > lo ? (hi - lo) / SKV_BLOCK_TOKENS : 0;
   if (nb > max_blocks) nb = max_blocks;
@@ -123,19 +132,13 @@ __global__ __launch_bounds__(kWave* kWavesPerWg) void skv_match_kernel(
   constexpr int kRound = kCoop * kGroup;
 
   int j = 0;      // blocks matched so far
-  int node = 0;   // current node (root)
   int last = -1;  // record of the last matched block: where the path ends
   int parity = 0;
   bool stop = false;
   while (j < nb && !stop) {
-    SkvNode cur = t.nodes[node];
-    cur.tab_off = uniform(cur.tab_off);
-    cur.tab_cap = uniform(cur.tab_cap);
-    const int child = find_child(t, cur, x + (size_t)j * 16, lane);
-    if (child < 0) break;
-    SkvNode nd = t.nodes[child];
-    const int first = uniform(nd.first);
-    const int nblk = uniform(nd.n_blocks);
+    SkvNode nd;
+    if (find_child(t, cur, x + (size_t)j * 16, lane, nd) < 0) break;
+    const int first = nd.first, nblk = nd.n_blocks;
     const int span = min(nblk, nb - j);  // blocks of this node the request can still cover
     const int jn = j;                    // request block that faces the node's first block
     // With one wavefront per request (large batches) the very first round of a walk looks at kFirstBlocks blocks only:
@@ -232,7 +235,7 @@ __global__ __launch_bounds__(kWave* kWavesPerWg) void skv_match_kernel(
       if (upto > 0) last = first + upto - 1;
       if (ended) stop = true;
     }
-    node = child;
+    cur = nd;
   }
   if (wave == 0 && lane == 0) {
     matched_len[r] = j * SKV_BLOCK_TOKENS;
@@ -328,13 +331,11 @@ __global__ __launch_bounds__(kWave* kWavesPerWg) void skv_match_copies_kernel(
   // number; *n_choice / *counts describe the branch points met (how many visible copies each had).
   uint32_t limits = 0;   // SKV_LIMIT_* bits this request ran into (uniform)
   auto walk = [&](uint64_t ranks, int* n_choice, uint64_t* counts) {
-    int j = 0, node = 0, dp = 0;
+    int j = 0, dp = 0;
+    SkvNode cur = node_at(t, 0);
     uint64_t cnt = 0;
     bool stop = false;
     while (j < nb && !stop) {
-      SkvNode cur = t.nodes[node];
-      cur.tab_off = uniform(cur.tab_off);
-      cur.tab_cap = uniform(cur.tab_cap);
       int n = 0;
       const int want = dp < kMaxChoice ? (int)((ranks >> (6 * dp)) & 63) : 0;
       const int child = find_child_ranked(t, cur, x + (size_t)j * 16, tenant, lane, want, &n, &limits);
@@ -347,9 +348,8 @@ __global__ __launch_bounds__(kWave* kWavesPerWg) void skv_match_copies_kernel(
           limits |= SKV_LIMIT_BRANCH_POINTS;
         }
       }
-      SkvNode nd = t.nodes[child];
-      const int first = uniform(nd.first);
-      const int nblk = uniform(nd.n_blocks);
+      const SkvNode nd = node_at(t, child);
+      const int first = nd.first, nblk = nd.n_blocks;
       const int span = min(nblk, nb - j);
       for (int c = 0; c < span && !stop; c += kStepBlocks) {
         const int cb = min(kStepBlocks, span - c);
@@ -378,7 +378,7 @@ __global__ __launch_bounds__(kWave* kWavesPerWg) void skv_match_copies_kernel(
         j += take;
         if (take < cb) stop = true;
       }
-      node = child;
+      cur = nd;
     }
     *n_choice = dp;
     *counts = cnt;
