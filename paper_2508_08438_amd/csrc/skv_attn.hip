@@ -894,6 +894,9 @@ __global__ __launch_bounds__(Form<kTwo>::threads, 2) void attn_bf16_kernel(AttnP
     // first would hold the wavefront until the unit is free again.  Its argument is worked out a pair ahead, for the same reason; a pair of
     // weights is packed and summed one step later; the last one comes a step early, so that the sums are there when the last MFMA has been
     // issued.  (Argument and exponential together behind the pair, one wait for both fragments: 1 to 3 % slower.)
+    // The rest of a score pair's vector work stands between its MFMAs as well, and an output pair's second group goes first: 32 requests of
+    // 256 .. 270 rows behind 25600 .. 25920 keys 3362 / 3335 us, 64 of 100 .. 9000 rows 13.06 / 13.01 ms, 1070 rows the same.  (The output
+    // pair's work between its MFMAs too: 3387, 13.10.)
     float e[16], arg_next = arg(cur, 1);
     auto sum = [&](int k) __attribute__((always_inline)) { ssum[(k >> 2) & 1] += e[k]; };
     e[0] = __builtin_amdgcn_exp2f(arg(cur, 0));
@@ -903,15 +906,15 @@ __global__ __launch_bounds__(Form<kTwo>::threads, 2) void attn_bf16_kernel(AttnP
       lds_wait(11, kfr[i & 3]);   // behind it: its V^T fragment, three steps
       dst[k][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kfr[i & 3], qf[0][ks], ks == 0 ? zero4 : dst[k][0], 0, 0, 0);
       e[2 * i + 1] = __builtin_amdgcn_exp2f(arg_next);
-      dst[k][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kfr[i & 3], qf[1][ks], ks == 0 ? zero4 : dst[k][1], 0, 0, 0);
-      kfr[i & 3] = i < 4 ? k_frag(kb, i + 4, kOff) : k_frag(kb_next, i - 4, kOffNext);
       if (i < 7) arg_next = arg(cur, 2 * i + 2);
       if (i > 0) sum(2 * i - 2);
+      dst[k][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kfr[i & 3], qf[1][ks], ks == 0 ? zero4 : dst[k][1], 0, 0, 0);
+      kfr[i & 3] = i < 4 ? k_frag(kb, i + 4, kOff) : k_frag(kb_next, i - 4, kOffNext);
       __builtin_amdgcn_sched_barrier(0);
       lds_wait(10, vfr[i & 3]);   // behind it: three steps, a K fragment
-      o[i][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vfr[i & 3], p_use[0], o[i][0], 0, 0, 0);
-      if (i < 7) e[2 * i + 2] = __builtin_amdgcn_exp2f(arg_next);
       o[i][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vfr[i & 3], p_use[1], o[i][1], 0, 0, 0);
+      if (i < 7) e[2 * i + 2] = __builtin_amdgcn_exp2f(arg_next);
+      o[i][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vfr[i & 3], p_use[0], o[i][0], 0, 0, 0);
       vfr[i & 3] = i < 4 ? v_frag(vb, i + 4, vOff) : v_frag(vb_next, i - 4, vOffNext);
       if (i < 7) arg_next = arg(cur, 2 * i + 3);
       if (i > 0) {
@@ -1605,8 +1608,8 @@ extern "C" int skv_prefill_attn_static(const skv_attn_desc* desc, int32_t n_req,
 // ---- measurement aid: what the matrix cores sustain on given operand values ----
 // The clock the chip holds under matrix load depends on the values flowing through the multipliers, so the rate a
 // kernel can reach is a property of its data as well as of its code.  Every wavefront keeps six (A, B) operand
-// pairs of the caller's data in registers and issues the attention kernel's MFMA back to back into four
-// accumulators: no memory traffic, no other instructions.  One workgroup of eight wavefronts per compute unit; its
+// pairs of the caller's data in registers and issues 32x32x16 MFMAs (the products and cycles of the attention kernel's 16x16x32, at
+// a lower clock) back to back into four accumulators: no memory traffic, no other instructions.  One workgroup of eight wavefronts per compute unit; its
 // LDS claim keeps a second workgroup off the unit, so every SIMD runs exactly two wavefronts from start to end.
 // With side work, every MFMA is accompanied by what the attention kernel's softmax issues per MFMA at the least --
 // its A operand read from LDS (16 bytes per lane), one multiply-add, one exponential, one add and half a packed
