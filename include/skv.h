@@ -321,7 +321,8 @@ int skv_scatter_kv(const skv_attn_desc* desc, int32_t n_req, const void* d_knew,
 int skv_stream_copy(void* d_dst, const void* d_src, size_t bytes, void* stream);
 
 /* Measurement aid for the attention roofline (Section 2.1 attention; Section 6 reports prefill time): the rate at
- * which the chip sustains the bf16 matrix instruction of skv_prefill_attn (32x32x16, fp32 accumulate) on operand
+ * which the chip sustains the 32x32x16 bf16 matrix instruction (fp32 accumulate; skv_prefill_attn's 16x16x32 does as much
+ * in as many cycles and holds a higher clock, 2044 instead of 1765 TFLOP/s on N(0,1) values) on operand
  * values of the caller's choosing, with nothing else running -- operands stay in registers, one workgroup of eight
  * wavefronts per compute unit, `iters` rounds of 16 instructions each.  The clock under matrix load depends on the operand values,
  * so the rate for values distributed like a workload's K/V/Q is the ceiling that workload's attention can be held
