@@ -167,13 +167,14 @@ int skv_evict(skv_tree* tree, int64_t n_want, const int32_t* protect_ids, int64_
 
 /* Reclaim the record space that evictions and insertions leave behind (Section 4.3.2 Progressive Eviction: a
  * compressed chain's address vector shrinks as its entries are released, and the chain is removed once it is
- * empty): evicted block records, emptied nodes, abandoned child tables.  The live structure is laid out afresh in
- * the same slab, and the input block ids are renumbered densely in their old order: id_map (HOST, one entry per
- * input block id before the call) receives each id's new value, -1 for blocks that no longer exist;
- * *n_in_blocks_after (may be NULL) the new id count.  Lookups, counters, visibility bits and epochs are unchanged
+ * empty): evicted block records, emptied nodes, abandoned child tables.  Live records and nodes keep their order and close
+ * up in the same slab, child tables are laid out for the children they have, and the input block ids are renumbered densely in
+ * their old order: id_map (HOST, one entry per input block id before the call) receives each id's new value, -1 for blocks
+ * that no longer exist; *n_in_blocks_after (may be NULL) the new id count.  Lookups, counters, visibility bits and epochs are unchanged
  * apart from the renumbering; the capacity left for skv_tree_insert is the slab's capacity minus the live blocks.
- * Reads the kernels' per-block state back, uploads the whole structure on `stream` and synchronises it; must not
- * overlap with other calls on the tree.  Errors: SKV_EINVAL for a null tree or map. */
+ * Reads back the kernels' state of the blocks that move, uploads what changed on `stream` and synchronises it; must not
+ * overlap with other calls on the tree.  Errors: SKV_EINVAL for a null tree or map.  Where a transfer fails (SKV_EHIP) the
+ * host's side of the tree is what it was and id_map is not written; the slab may hold part of the new layout. */
 int skv_tree_compact(skv_tree* tree, int32_t* id_map, int64_t* n_in_blocks_after, void* stream);
 
 /* n_nodes: compressed nodes (root excluded); n_blocks: distinct cached blocks (evicted ones not counted);
