@@ -88,14 +88,12 @@ struct SkvHostMirror {
   // Pinned memory small transfers go through: kStageBytes of it from the first write on, null before, and as long as none is
   // to be had.  Every call that uses it waits for its own kernels before it returns.
   char* stage = nullptr;
-  // Kept for their memory only, nothing in them outlives a call: what an insertion that may fill the slab goes back to, what a
-  // compaction lays out and changes places with, and marks per page or input block.  Fresh from the allocator on every
-  // call they are faulted in again, 0.3 us per 4 KB.
+  // Kept for their memory only, nothing in them outlives a call: what a compaction lays out and changes places with, and marks per
+  // page or input block.  Fresh from the allocator on every call they are faulted in again, 0.3 us per 4 KB.
   struct {
     std::vector<SkvNode> nodes;
     std::vector<SkvSlot> slots;
-    std::vector<uint8_t> page_used;
-    std::vector<int32_t> kids, filled, parent, node_of;
+    std::vector<int32_t> kids, filled, parent;
   } saved;
   std::vector<uint32_t> words;
   std::vector<uint8_t> marks;
@@ -602,7 +600,40 @@ struct Inserter {
   int64_t n_blocks, n_in;            // running totals
   std::vector<int32_t> page, meta;   // per appended block
   size_t node_lo, node_hi, slot_lo, slot_hi;  // dirty spans of records that existed before [lo, hi)
-  bool full = false;
+  // What undo() needs: sizes before the call, and the records of then as they were before each change, oldest first.
+  struct Node { int32_t at; SkvNode rec; int32_t kids, filled; };
+  struct Slot { size_t at; SkvSlot rec; };
+  struct Run { int32_t node, first, n; };   // a node's records that went to a new one, and its children with them
+  std::vector<Node> old_nodes;
+  std::vector<Slot> old_slots;
+  std::vector<Run> cut;
+  const size_t nodes0 = m->nodes.size(), slots0 = m->slots_used, blocks0 = m->canon.size(), in0 = m->flat_of.size();
+
+  void keep_node(int32_t i) {
+    if ((size_t)i < nodes0) old_nodes.push_back(Node{i, m->nodes[i], m->kids[i], m->filled[i]});
+  }
+  // Takes back everything the insertions so far did to the mirror.
+  void undo() {
+    for (const int32_t p : page) m->page_used[p] = 0;
+    for (size_t i = old_slots.size(); i-- > 0;) m->slots[old_slots[i].at] = old_slots[i].rec;
+    for (size_t i = old_nodes.size(); i-- > 0;) {
+      const Node& o = old_nodes[i];
+      m->nodes[o.at] = o.rec; m->kids[o.at] = o.kids; m->filled[o.at] = o.filled;
+    }
+    m->nodes.resize(nodes0); m->kids.resize(nodes0); m->filled.resize(nodes0); m->parent.resize(nodes0);
+    m->slots.resize(slots0); m->slots_used = slots0;
+    m->tok.resize(blocks0 * 16); m->canon.resize(blocks0); m->page.resize(blocks0); m->vis.resize(blocks0); m->node_of.resize(blocks0);
+    m->flat_of.resize(in0);
+    for (const Run& c : cut) {
+      if ((size_t)c.node >= nodes0) continue;   // of this call's own
+      std::fill_n(m->node_of.begin() + c.first, c.n, c.node);
+      const SkvNode& n = m->nodes[c.node];
+      for (int32_t q = 0; q < n.tab_cap; ++q) {
+        const int32_t child = m->slots[(size_t)n.tab_off + q].child;
+        if (child >= 0) m->parent[child] = c.node;
+      }
+    }
+  }
 
   void touch_node(size_t i) { node_lo = std::min(node_lo, i); node_hi = std::max(node_hi, i + 1); }
   void touch_slot(size_t i) { slot_lo = std::min(slot_lo, i); slot_hi = std::max(slot_hi, i + 1); }
@@ -623,12 +654,14 @@ struct Inserter {
     uint32_t s = (uint32_t)h & (uint32_t)(n.tab_cap - 1);
     while (m->slots[(size_t)n.tab_off + s].child >= 0) s = (s + 1) & (uint32_t)(n.tab_cap - 1);
     if (m->slots[(size_t)n.tab_off + s].child == -1) m->filled[node]++;
+    if ((size_t)n.tab_off + s < slots0) old_slots.push_back(Slot{(size_t)n.tab_off + s, m->slots[(size_t)n.tab_off + s]});
     m->slots[(size_t)n.tab_off + s] = SkvSlot{(uint32_t)h, (uint32_t)(h >> 32), child, 0};
     touch_slot((size_t)n.tab_off + s);
   }
   // Adds a child; a table that would become more than half full moves to a fresh one of twice the size.
   bool add_child(int32_t node, uint64_t h, int32_t child) {
     SkvNode& n = m->nodes[node];
+    keep_node(node);
     const int32_t kids = m->kids[node] + 1;
     if (2 * (m->filled[node] + 1) > n.tab_cap) {  // removed entries count: a probe must always reach an empty slot
       const int32_t cap = (int32_t)next_pow2((uint32_t)(2 * kids) < 4u ? 4u : (uint32_t)(2 * kids));
@@ -787,6 +820,8 @@ struct Inserter {
   // Cuts node c after its first j blocks: a new node takes the rest together with the child table.
   bool split(int32_t c, int64_t j) {
     const SkvNode run = m->nodes[c];
+    keep_node(c);
+    cut.push_back(Run{c, run.first + (int32_t)j, run.n_blocks - (int32_t)j});
     const int32_t tail = (int32_t)m->nodes.size();
     m->nodes.push_back(SkvNode{run.first + (int32_t)j, run.n_blocks - (int32_t)j, run.tab_off, run.tab_cap});
     m->kids.push_back(m->kids[c]);
@@ -906,23 +941,8 @@ extern "C" int skv_tree_insert(skv_tree* t, int32_t n_req, const int32_t* req_of
       }
     }
   }
-  // Work on the mirror; a full slab restores the snapshot and changes nothing.  Where no block, node or table the requests can ask for
-  // passes what is free there is none to make, a copy of the index's size (116 -> 97 us for 64 requests, 7.7 k new blocks): a request adds the blocks it has pages for and two
-  // nodes at most, one with a table of four and one to a node whose table may move to one of twice its children.
-  bool fits;
-  {
-    int64_t blocks = 0, kids = n_req;
-    for (int32_t r = 0; r < n_req; ++r) blocks += have[r];
-    for (const int32_t k : m->kids) kids = std::max<int64_t>(kids, k + (int64_t)n_req);
-    fits = std::max<int64_t>(t->dev.n_blocks, t->n_in_blocks) + blocks <= m->cap_blocks &&
-           (int64_t)m->nodes.size() + 2 * (int64_t)n_req <= m->cap_blocks + 1 &&
-           (double)m->slots_used + (double)n_req * (4.0 * (double)kids + 8.0) <= (double)slots_for((size_t)m->cap_blocks);
-  }
-  if (!fits) {
-    m->saved.nodes = m->nodes; m->saved.kids = m->kids; m->saved.slots = m->slots; m->saved.page_used = m->page_used;
-    m->saved.filled = m->filled; m->saved.parent = m->parent; m->saved.node_of = m->node_of;
-  }
-  const size_t slots_used0 = m->slots_used, tok0 = m->tok.size(), blocks0 = m->canon.size(), in0 = m->flat_of.size();
+  // Work on the mirror; where the slab is full every change is taken back.  (From records kept of what changed: a snapshot is a copy of
+  // the index's size, 116 instead of 97 us for 64 requests, 7.7 k new blocks in 67 k.)
   Inserter ins{t, m, t->dev.n_blocks, t->n_in_blocks, {}, {}, SIZE_MAX, 0, SIZE_MAX, 0};
   hipStream_t st = (hipStream_t)stream;
   // The requester's own path depends on the visibility bits.  The host's copy of them is exact unless a
@@ -947,12 +967,8 @@ extern "C" int skv_tree_insert(skv_tree* t, int32_t n_req, const int32_t* req_of
     first_inserted[r] = (int32_t)first;
     n_inserted[r] = (int32_t)n_new;
   }
-  if (full && fits) return SKV_EINVAL;   // (it cannot be: the bounds above)
   if (full) {
-    m->nodes = m->saved.nodes; m->kids = m->saved.kids; m->slots = m->saved.slots; m->page_used = m->saved.page_used;
-    m->filled = m->saved.filled; m->parent = m->saved.parent; m->node_of = m->saved.node_of;
-    m->slots_used = slots_used0; m->tok.resize(tok0);
-    m->canon.resize(blocks0); m->page.resize(blocks0); m->vis.resize(blocks0); m->flat_of.resize(in0);
+    ins.undo();
     return SKV_ENOMEM;
   }
   // upload: the appended block records, then the spans of node and slot records that changed
