@@ -322,18 +322,18 @@ int skv_scatter_kv(const skv_attn_desc* desc, int32_t n_req, const void* d_knew,
 int skv_stream_copy(void* d_dst, const void* d_src, size_t bytes, void* stream);
 
 /* Measurement aid for the attention roofline (Section 2.1 attention; Section 6 reports prefill time): the rate at
- * which the chip sustains the 32x32x16 bf16 matrix instruction (fp32 accumulate; skv_prefill_attn's 16x16x32 does as much
- * in as many cycles and holds a higher clock, 2044 instead of 1765 TFLOP/s on N(0,1) values) on operand
- * values of the caller's choosing, with nothing else running -- operands stay in registers, one workgroup of eight
- * wavefronts per compute unit, `iters` rounds of 16 instructions each.  The clock under matrix load depends on the operand values,
- * so the rate for values distributed like a workload's K/V/Q is the ceiling that workload's attention can be held
- * against; constants give the nominal peak.  d_operands: DEVICE, at least SKV_MFMA_RATE_OPERAND_BYTES bytes of
+ * which the chip sustains the bf16 matrix instruction of skv_prefill_attn (16x16x32, fp32 accumulate, an A operand with two
+ * B operands) on operand values of the caller's choosing, with nothing else running -- operands stay in registers, one
+ * workgroup of eight wavefronts per compute unit, `iters` rounds of 16 pairs of instructions each.  The clock under matrix
+ * load depends on the operand values, so the rate for values distributed like a workload's K/V/Q is what that workload's
+ * attention can be held against; constants come close to the nominal peak.  The clock also takes several milliseconds of
+ * load to settle: calls before that read up to a third less.  d_operands: DEVICE, at least SKV_MFMA_RATE_OPERAND_BYTES bytes of
  * bf16 values, 16-byte aligned (read once); d_sink: DEVICE, at least SKV_MFMA_RATE_SINK_BYTES bytes (overwritten,
  * keeps the results alive).  *flops (HOST, may be NULL) receives the floating-point operations one call issues;
- * the caller times the call on `stream`.  side_work: 0 = the matrix instruction alone; 1 = every matrix
- * instruction accompanied by what the softmax of skv_prefill_attn issues per matrix instruction at the least (its A
+ * the caller times the call on `stream`.  side_work: 0 = the matrix instruction alone; 1 = every pair of them
+ * accompanied by what the softmax of skv_prefill_attn issues per pair at the least (its A
  * operand read from LDS, one multiply-add, one exponential, one add, half a packed conversion) on values that
- * depend on no matrix result, with no global load and no barrier: the rate that instruction mix can reach at all.
+ * depend on no matrix result, with no global load and no barrier: what that instruction mix sustains.
  * Errors: SKV_EINVAL for null or misaligned pointers, iters < 1 or side_work other than 0 or 1; SKV_ENOMEM for
  * buffers that are too small. */
 #define SKV_MFMA_RATE_OPERAND_BYTES ((size_t)512 * 512 * 6 * 32)

@@ -30,7 +30,6 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
@@ -1608,13 +1607,13 @@ extern "C" int skv_prefill_attn_static(const skv_attn_desc* desc, int32_t n_req,
 // ---- measurement aid: what the matrix cores sustain on given operand values ----
 // The clock the chip holds under matrix load depends on the values flowing through the multipliers, so the rate a
 // kernel can reach is a property of its data as well as of its code.  Every wavefront keeps six (A, B) operand
-// pairs of the caller's data in registers and issues 32x32x16 MFMAs (the products and cycles of the attention kernel's 16x16x32, at
-// a lower clock) back to back into four accumulators: no memory traffic, no other instructions.  One workgroup of eight wavefronts per compute unit; its
+// pairs of the caller's data in registers and issues the attention kernel's 16x16x32 MFMAs, an A operand with two B operands as there,
+// back to back into eight pairs of accumulators: no memory traffic, no other instructions.  One workgroup of eight wavefronts per compute unit; its
 // LDS claim keeps a second workgroup off the unit, so every SIMD runs exactly two wavefronts from start to end.
-// With side work, every MFMA is accompanied by what the attention kernel's softmax issues per MFMA at the least --
+// With side work, every pair of MFMAs is accompanied by what the attention kernel's softmax issues per pair at the least --
 // its A operand read from LDS (16 bytes per lane), one multiply-add, one exponential, one add and half a packed
 // conversion -- on values that depend on nothing the matrix core produces: no dependency on a result, no global
-// load, no barrier.  What this form sustains bounds any schedule of that instruction mix.
+// load, no barrier.  What this form sustains is a measure of that instruction mix, in the attention kernel's order.
 namespace {
 constexpr int kRateMaxBlocks = 512, kRateThreads = 512, kRatePairs = 6, kRateLdsBytes = 96 * 1024;
 template <bool kSide>
@@ -1629,11 +1628,9 @@ __global__ __launch_bounds__(kRateThreads) void mfma_rate_kernel(const u32x4* __
     a[i] = __builtin_bit_cast(bf16x8, x);
     b[i] = __builtin_bit_cast(bf16x8, y);
   }
-  f32x16 c[4];
+  f32x4 c[8][2];
 #pragma unroll
-  for (int j = 0; j < 4; ++j)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) c[j][e] = 0.f;
+  for (int j = 0; j < 8; ++j) c[j][0] = c[j][1] = f32x4{0.f, 0.f, 0.f, 0.f};
   float t = 0.f;
   if (kSide) {
     // the workgroup's own 96 KB of operand data fill the LDS; a wavefront reads A operands from its own 8 KB of it
@@ -1641,7 +1638,7 @@ __global__ __launch_bounds__(kRateThreads) void mfma_rate_kernel(const u32x4* __
     for (int i = threadIdx.x; i < kVecs; i += kRateThreads) claim[i] = ops[(size_t)blockIdx.x * kVecs + i];
     __syncthreads();
     const uint32_t abase = lds_addr(&claim[(threadIdx.x & 63) + (threadIdx.x >> 6) * 512]);
-    bf16x8 ar[4] = {a[0], a[1], a[2], a[3]};   // ring: the read behind MFMA j serves MFMA j + 4
+    bf16x8 ar[4] = {a[0], a[1], a[2], a[3]};   // ring: the read behind pair j serves pair j + 4
     float x[4], e_prev = 0.f, e_pp = 0.f;
 #pragma unroll
     for (int j = 0; j < 4; ++j) x[j] = (float)((threadIdx.x * 37 + j * 101) % 1000) * 0.001f;
@@ -1649,10 +1646,11 @@ __global__ __launch_bounds__(kRateThreads) void mfma_rate_kernel(const u32x4* __
 #pragma unroll
       for (int j = 0; j < 16; ++j) {
         lds_wait(3, ar[j & 3]);
-        c[j & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ar[j & 3], b[(j / 4 + j) % kRatePairs], c[j & 3], 0, 0, 0);
-        ar[j & 3] = lds_read_b128(abase, (j & 7) * 1024);
+        c[j & 7][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ar[j & 3], b[(j / 4 + j) % kRatePairs], c[j & 7][0], 0, 0, 0);
         x[j & 3] = __builtin_fmaf(-1.9371f, __builtin_fabsf(x[j & 3]), 1.0f);   // bounded, never settles
         const float e = __builtin_amdgcn_exp2f(x[j & 3]);
+        c[j & 7][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ar[j & 3], b[(j / 4 + j + 3) % kRatePairs], c[j & 7][1], 0, 0, 0);
+        ar[j & 3] = lds_read_b128(abase, (j & 7) * 1024);
         t += e_prev;                       // results are consumed one step late, as in the attention kernel: nothing
         if (j & 1) {                       // waits for the transcendental unit
           f32x2 pr = {e_pp, e_prev};
@@ -1669,13 +1667,15 @@ __global__ __launch_bounds__(kRateThreads) void mfma_rate_kernel(const u32x4* __
     for (int it = 0; it < iters; ++it) {
 #pragma unroll
       for (int j = 0; j < 16; ++j)
-        c[j & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[j % kRatePairs], b[(j / 4 + j) % kRatePairs], c[j & 3], 0, 0, 0);
+#pragma unroll
+        for (int g = 0; g < 2; ++g)
+          c[j & 7][g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[j % kRatePairs], b[(j / 4 + j + 3 * g) % kRatePairs], c[j & 7][g], 0, 0, 0);
     }
   }
 #pragma unroll
-  for (int j = 0; j < 4; ++j)
+  for (int j = 0; j < 16; ++j)
 #pragma unroll
-    for (int e = 0; e < 16; ++e) t += c[j][e];
+    for (int e = 0; e < 4; ++e) t += c[j >> 1][j & 1][e];
   volatile uint32_t* used = (volatile uint32_t*)claim;   // the array has to be used to be allocated
   used[threadIdx.x] = __float_as_uint(t);
   sink[lane_id] = __uint_as_float(used[threadIdx.x]);
@@ -1696,6 +1696,6 @@ extern "C" int skv_mfma_rate(const void* d_operands, size_t operand_bytes, int32
   else
     mfma_rate_kernel<false><<<blocks, kRateThreads, 0, (hipStream_t)stream>>>((const u32x4*)d_operands, d_sink, iters);
   SKV_HIP(hipGetLastError());
-  if (flops) *flops = (double)blocks * (kRateThreads / 64) * (double)iters * 16.0 * (2.0 * 32 * 32 * 16);
+  if (flops) *flops = (double)blocks * (kRateThreads / 64) * (double)iters * 32.0 * (2.0 * 16 * 16 * 32);
   return SKV_OK;
 }
