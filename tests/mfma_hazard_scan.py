@@ -17,9 +17,15 @@ def _regs(tok):
 
 
 def scan(asm_text: str, kernel: str, need: int = 12, horizon: int = 24):
-    """Readers of MFMA results reached through at least one branch with fewer than `need` issue states in between."""
+    """Readers of MFMA results reached through at least one branch with fewer than `need` issue states in between, in every kernel whose
+    symbol holds `kernel`: all instantiations of a template, which the compiler treats each in its own way."""
     lines = [l.rstrip() for l in asm_text.split("\n")]
-    start = [i for i, l in enumerate(lines) if re.match(r"^_Z.*" + kernel + ".*:", l)][0]
+    starts = [i for i, l in enumerate(lines) if re.match(r"^_Z.*" + kernel + ".*:", l)]
+    assert starts, kernel
+    return [hit for start in starts for hit in _scan_one(lines, start, need, horizon)]
+
+
+def _scan_one(lines, start, need, horizon):
     end = [i for i, l in enumerate(lines) if i > start and ".end_amdhsa_kernel" in l][0]
     body = [l for l in lines[start:end] if l.strip() and not l.strip().startswith(";")]
     labels = {}

@@ -26,9 +26,16 @@ def asm(tmp_path_factory):
     return _compile("skv_attn.hip", tmp_path_factory)
 
 
-@pytest.mark.parametrize("form", ["Lb0ELb0E", "Lb0ELb1E", "Lb1ELb0E", "Lb1ELb1E"])
+FORMS = ["Lb0ELb0ELb0E", "Lb0ELb1ELb0E", "Lb1ELb0ELb0E", "Lb1ELb1ELb0E", "Lb0ELb0ELb1E"]   # parts, plan, two workgroups
+
+
+def test_forms_are_all_of_them(asm):
+    assert sorted(re.findall(r"^_ZN\S*attn_bf16_kernelI(\w+E)EEv\S*:", asm, re.M)) == sorted(FORMS)
+
+
+@pytest.mark.parametrize("form", FORMS)
 def test_descriptors_are_scalar(asm, form):
-    m = re.search(r"^_ZN\S*attn_bf16_kernelI" + form + r"\S*:", asm, re.M)
+    m = re.search(r"^_ZN\S*attn_bf16_kernelI" + form + r"E\S*:", asm, re.M)
     body = asm[m.end():asm.index(".Lfunc_end", m.end())]
     parts = re.split(r"^(\.LBB\w+):", body, flags=re.M)
     blocks = dict(zip(parts[1::2], parts[2::2]))

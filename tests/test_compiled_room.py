@@ -2,10 +2,10 @@
 import re
 
 import pytest
-from test_compiled_loads import asm  # noqa: F401
+from test_compiled_loads import FORMS, asm  # noqa: F401
 
 
-@pytest.mark.parametrize("form", ["Lb0ELb0ELb0E", "Lb0ELb1ELb0E", "Lb1ELb0ELb0E", "Lb1ELb1ELb0E", "Lb0ELb0ELb1E"])
+@pytest.mark.parametrize("form", FORMS)
 def test_registers(asm, form):  # noqa: F811
     m = re.search(r"\.name:\s+_ZN\S*attn_bf16_kernelI" + form + r".*?\.vgpr_count:\s+(\d+)\s+\.vgpr_spill_count:\s+(\d+)", asm, re.S)
     assert (int(m.group(1)) + 7) // 8 * 8 <= 240 and int(m.group(2)) == 0
