@@ -8,10 +8,10 @@
 //
 // bf16 path: flash-style streaming over 64-key tiles with online softmax in fp32; the two
 // contractions (K.Q^T and V^T.P^T) run on the matrix cores (v_mfma_f32_16x16x32_bf16), the
-// softmax on the vector ALU.  A workgroup of eight wavefronts shares every K/V tile through
-// LDS; each wavefront owns 32 query rows, those of up to four heads at as few positions (the query heads of one
+// softmax on the vector ALU.  A workgroup of eight wavefronts (four, two workgroups to a compute unit, where items are
+// short) shares every K/V tile through LDS; each wavefront owns 32 query rows, those of up to four heads at as few positions (the query heads of one
 // kv head share a workgroup, so a K/V tile is fetched once for the group).  K/V rows travel global -> LDS with
-// direct-to-LDS loads (no stop in registers, no LDS store instructions), three stages each.
+// direct-to-LDS loads (no stop in registers, no LDS store instructions), six stages of 32 keys each, or five.
 // The products are formed transposed (S^T = K Q^T, O^T = V^T P^T) so that a query is a
 // lane-column of the MFMA accumulator: row sums are register reductions, and the P^T
 // accumulator registers are already in the B-operand layout of the second product; V^T
@@ -38,7 +38,7 @@ typedef short s16x4 __attribute__((ext_vector_type(4)));
 constexpr int kD = 128;          // head dim of the bf16 kernel
 constexpr int kBN = 64;          // keys per LDS tile
 constexpr int kStageRows = 16;   // rows of a wave's Q / O staging tile
-constexpr float kSumLimit = 4096.f;   // move the softmax reference when a lane's sum of 16 exponentials exceeds this
+constexpr float kSumLimit = 4096.f;   // move the softmax reference when a lane's sum over a query's 8 keys of a sub-tile exceeds this
 constexpr int kRowsPerWave = 32; // query rows per wavefront
 constexpr int kWaves = 8;        // two per SIMD: one wave's softmax overlaps the other's MFMAs
 constexpr int kThreads = kWaves * 64;
@@ -751,7 +751,7 @@ __global__ __launch_bounds__(Form<kTwo>::threads, 2) void attn_bf16_kernel(AttnP
   };
   // Inside the main loop the same loads are split in two: the bases of the tiles an iteration will request
   // (K two tiles ahead, V one) are broadcast out of the windows during the iteration before, between its half-steps,
-  // so that the iteration itself starts with nothing but the four load instructions.  Right after a barrier every
+  // so that the iteration itself starts with nothing but its load instructions (four, eight with four wavefronts).  Right after a barrier every
   // wave of the workgroup is at this point at once, and what stands here keeps all matrix cores waiting.
   uint64_t nk = 0, nv = 0;
   int pend_page = -1;
@@ -779,11 +779,11 @@ __global__ __launch_bounds__(Form<kTwo>::threads, 2) void attn_bf16_kernel(AttnP
   // Work advances in 32-key sub-tiles (half an LDS tile), three of them in flight: half-step h puts the scores of
   // sub-tile h + 1 and the output update with sub-tile h - 1 on the matrix core and computes the softmax of sub-tile
   // h on the vector ALU.  Nothing inside a half-step depends on anything else inside it, so its 32 MFMAs alternate
-  // (two score, two output, two score, ...) with two or three vector instructions behind each pair: the vector work runs beside the
-  // MFMAs instead of between them.  Two score accumulators and two P^T buffers alternate.
+  // (two score, two output, two score, ...) with the vector instructions of a score pair between its two and those of an output pair
+  // behind it: the vector work runs beside the MFMAs.  Two score accumulators and two P^T buffers alternate.
   // A fragment serves the two query groups: 16x16x32 takes the fragment reads and the cycles of 32x32x16 and moves half as much through
-  // the accumulators, and the chip's clock under matrix load depends on what moves (MFMAs alone on N(0,1) operands 1765 -> 2044 TFLOP/s;
-  // with the fragment reads and this softmax's instructions beside them 1440 -> 1500).  Clock in this loop 1.70 -> 1.89 GHz, 64 requests of
+  // the accumulators, and the chip's clock under matrix load depends on what moves (skv_mfma_rate on N(0,1) operands 1865 -> 2125 TFLOP/s,
+  // with an operand read and the least of this softmax beside each pair 1485 -> 1582).  Clock in this loop 1.70 -> 1.89 GHz, 64 requests of
   // 100 .. 9000 rows 14.0 -> 13.3 ms (1150 -> 1211 TFLOP/s), of 1070 791 -> 756 us.
   typedef f32x4 Scores[2][2];   // S^T of a sub-tile: [k][g][i]: key 16 k + 4 quad + i, query 16 g + l16; raw dot products
   Scores s[2];
@@ -860,7 +860,7 @@ __global__ __launch_bounds__(Form<kTwo>::threads, 2) void attn_bf16_kernel(AttnP
   };
   // The softmax keeps a reference per query; exponentials are taken against it as it stands, which leaves the
   // normalised result unchanged.  Only when a lane's sum of exponentials over a sub-tile passes kSumLimit (an element
-  // at least kSumLimit / 16 above the reference; infinities and NaNs trip it too) is the reference moved to that
+  // at least kSumLimit / 8 above the reference; infinities and NaNs trip it too) is the reference moved to that
   // sub-tile's row maximum: O and the row sum are rescaled and this sub-tile's exponentials are taken again.  This
   // happens between half-steps, after the output update that still belongs to the old reference has been issued.
   auto move_reference = [&](const Scores& cur, bf16x8 (&p_make)[2]) __attribute__((always_inline)) {
@@ -1328,7 +1328,9 @@ bool eight_heads(const skv_attn_desc* d, int32_t n_req, int64_t total_q_rows, in
 // they fill one round nothing is gained.  us with one / two: 512 requests of 64 rows behind nothing 142 / 123, behind 512 keys 412 / 411;
 // 1000 of 17 behind 32 177 / 98; 100 of 8 .. 32 behind 1600 .. 6400 339 / 309; 64 of 256 behind 8192 1956 / 2013; 8 query heads over 8, 64
 // of 500 .. 1100 193 / 177; 24 over 8, 100 of 50 .. 100 104 / 72.  (1523 calls of 4 .. 400 requests of up to 800 rows behind up to 300
-// pages: 0.87 of the time on average, 0.855 were every choice right; 48 are slower by 2 % and more, one by 16.)  Few rows behind
+// pages: 0.87 of the time on average, 0.855 were every choice right; 48 are slower by 2 % and more, one by 16.  The width of the table and the
+// mean rows are all that is known here, so lengths that differ and tables that are mostly empty are misjudged; the slower ones lie among the
+// others: by heads, rows or workgroups every part of the calls is faster on average, eight heads in 400 to 450 workgroups, the worst, 0.96.)  Few rows behind
 // kTwoPool and more of K and V: the copy of those pages, where a step makes one beside, is what takes the time, and the second set of loads
 // costs it 2 to 3 % (128 of 8 .. 47 rows behind 2000 .. 3000, 1.5 GB: 550 / 566; 335 MB 130 / 130; 0.8 GB and 60 .. 105 rows 477 / 479).
 constexpr int kTwoKeys = 25, kTwoKeysEight = 16;   // key tiles of an item in the middle of its request
