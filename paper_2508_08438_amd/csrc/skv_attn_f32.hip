@@ -54,6 +54,23 @@ __device__ __forceinline__ Pieces split8(const float (&x)[8]) {
   for (int k = 0; k < kPieces; ++k) r.p[k] = __builtin_bit_cast(bf16x8, w[k]);
   return r;
 }
+// The same in 16 steps of 16 values (8 of 8): a pair's first piece and what it leaves, then the other two.
+typedef u32x4 Words[kPieces];
+__device__ __forceinline__ void split_step(float& a, float& b, bool second, int at, Words& w) {
+  auto piece = [&](int k) __attribute__((always_inline)) {
+    const uint32_t h = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{a, b}), bf16x2));
+    w[k][at] = h;
+    if (k == 2) return;
+    a -= __builtin_bit_cast(float, h << 16);
+    b -= __builtin_bit_cast(float, h & 0xffff0000u);
+  };
+  if (!second) {
+    piece(0);
+  } else {
+    piece(1);
+    piece(2);
+  }
+}
 // Products of pieces i + j = kSum, added to acc.  A sum that takes the small ones first, or apart, is rounded at its full size
 // by the products of the first pieces only: that is what makes it as exact as a chain of fp32 multiply-adds.
 template <int kSum>
@@ -102,10 +119,57 @@ struct Item {
     const int n_tiles = (S + kTileRows - 1) / kTileRows;
     const int k_tile = t - (qbase / kTileRows + r);
     if (k_tile < 0 || k_tile >= n_tiles) return false;
-    row0 = (n_tiles - 1 - k_tile) * kTileRows;                 // the request's heaviest tile first
-    row1 = min(S, row0 + kTileRows);
     L = __builtin_amdgcn_readfirstlane(p.matched_len[r]);
     L = L > 0 ? L & ~(SKV_BLOCK_TOKENS - 1) : 0;               // whole blocks only
+    row0 = (n_tiles - 1 - k_tile) * kTileRows;                 // the request's heaviest tile first
+    row1 = min(S, row0 + kTileRows);
+    return true;
+  }
+  // The same places, dealt out anew among each 64 requests: of all of them the last tiles come first, by their number in the request (64
+  // requests of 1070 rows over 512 places: the chip empties 1 % after the mean and not 11 %).  What a request's rows leave over is its
+  // first tile, which sees the fewest keys, and so many rows more that a wavefront's start where a block of keys does.
+  template <int kTileRows>
+  __device__ __forceinline__ bool find_by_number(const SkvAttnF32Params& p) {
+    const int lane = threadIdx.x & 63;
+    h = blockIdx.x % p.Hq;
+    hk = h / (p.Hq / p.Hkv);
+    const int t = blockIdx.x / p.Hq;
+    int r0 = 0;   // first of the 64
+    for (int n = (p.n_req + 63) / 64; n > 1;) {
+      const int step = (n + 63) / 64, idx = lane * step;
+      const bool before = idx < n && p.q_off[r0 + 64 * idx] / kTileRows + r0 + 64 * idx <= t;
+      const int k = __builtin_popcountll(__ballot(before));
+      const int lo = (k > 0 ? k - 1 : 0) * step;
+      n = min(step, n - lo);
+      r0 += 64 * lo;
+    }
+    r0 = __builtin_amdgcn_readfirstlane(r0);
+    const bool have = r0 + lane < p.n_req;
+    const int begin = have ? p.q_off[r0 + lane] : 0;
+    const int rows = have ? (int)min((int64_t)(p.q_off[r0 + lane + 1] - begin), p.max_rows - begin) : 0;
+    const int own = have ? max(0, (rows + kTileRows - 1) / kTileRows) : 0;
+    int place = t - (__builtin_amdgcn_readfirstlane(begin) / kTileRows + r0);
+    auto from = [&](int number) __attribute__((always_inline)) { return skv_over_wave(max(0, own - number), SkvAdd()); };   // tiles of that number and higher ones
+    int lo = 0, hi = skv_over_wave(own, SkvMax());
+    if (place < 0 || place >= from(0)) return false;
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) >> 1;
+      if (from(mid) > place) lo = mid; else hi = mid;
+    }
+    const int tile = __builtin_amdgcn_readfirstlane(lo);
+    place -= __builtin_amdgcn_readfirstlane(from(tile + 1));
+    const uint64_t with = __ballot(own > tile);
+    const int at = __builtin_ctzll(__ballot(own > tile && __builtin_popcountll(with & ((1ull << lane) - 1)) == place));
+    r = r0 + at;
+    qbase = __builtin_amdgcn_readlane(begin, at);
+    S = __builtin_amdgcn_readlane(rows, at);
+    L = __builtin_amdgcn_readfirstlane(p.matched_len[r]);
+    L = L > 0 ? L & ~(SKV_BLOCK_TOKENS - 1) : 0;               // whole blocks only
+    int first = S - (__builtin_amdgcn_readlane(own, at) - 1) * kTileRows;
+    const int more = -(L + first) & (kKeys - 1);
+    if (first + more <= kTileRows) first += more;
+    row0 = tile > 0 ? first + (tile - 1) * kTileRows : 0;
+    row1 = min(S, first + tile * kTileRows);
     return true;
   }
 };
@@ -267,40 +331,75 @@ __device__ __forceinline__ bool all_finite(const f32x16 (&o)[kA], float l) {
   return l < INFINITY;
 }
 
-// Scores -> exponentials in place; the output moves to the new maximum where that has grown.  `seen`: the last key the
-// tile's first row sees; m_run: running maximum (scaled, exp2 units), l_run: this half's running sum, per query.
-template <int kA>
-__device__ __forceinline__ void softmax_step(f32x16& s, const f32x16& s_low, int key0, int seen, float c, f32x16 (&o)[kA], float& m_run, float& l_run) {
-  const int lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
+// A weight is taken against the reference as it stands: that moves to the largest score so far only where a lane's weights of one block
+// sum to more than kSumLimit (some score two or more above it; infinities and NaN too), or where there is none yet.  A maximum that moved with every block took 50
+// of its 400 vector instructions.  The score's small products are added last, to a sum no larger than the exponent itself: the results are
+// closer to 64 bits than with the maximum (2-norm, 64 requests of 1070 rows, N(0,1): 1.62e-7 -> 1.53e-7, scores 4 times as wide
+// 3.24e-7 -> 2.89e-7, 30 times 7.7e-7 -> 6.6e-7; one of 250 rows 1.31e-7 -> 1.23e-7).
+constexpr float kSumLimit = 64.f;
+__device__ __forceinline__ float weight(float s, float s_low, float c, float ref) {
+  return __builtin_amdgcn_exp2f(__builtin_fmaf(s_low, c, __builtin_fmaf(s, c, -ref)));
+}
+__device__ __forceinline__ float largest(const f32x16& s, const f32x16& s_low) {
+  float mx = s[0] + s_low[0];
 #pragma unroll
-  for (int e = 0; e < 16; ++e) s[e] += s_low[e];
-  if (key0 + kKeys - 1 > seen) {
-#pragma unroll
-    for (int e = 0; e < 16; ++e)
-      if (key0 + (e >> 2) * 8 + 4 * half + (e & 3) > seen + l32) s[e] = -INFINITY;
-  }
-  float mx = s[0];
-#pragma unroll
-  for (int e = 1; e < 16; ++e) mx = fmaxf(mx, s[e]);
-  mx = over_halves(mx, SkvMax()) * c;
-  const float m_new = fmaxf(m_run, mx);
-  const float ref = m_new == -INFINITY ? 0.f : m_new;   // no visible key so far: every term is 0
-  float sum[2] = {0.f, 0.f};
+  for (int e = 1; e < 16; ++e) mx = fmaxf(mx, s[e] + s_low[e]);
+  return mx;
+}
+// The reference of the queries whose weights summed to too much (trip; in either half), and the new weights.  Returns what everything that was
+// summed against the old one is to be multiplied by.  m_ref: reference (scaled, exp2 units), l_run: this half's running sum, per query.
+__device__ __forceinline__ float move_reference(const f32x16& s, const f32x16& s_low, bool trip, float c, float (&w)[16], float (&sum)[2], float& m_ref,
+                                                float& l_run) {
+  const float m_new = fmaxf(m_ref, over_halves(trip ? largest(s, s_low) : -INFINITY, SkvMax()) * c);
+  const float ref = m_new == -INFINITY ? 0.f : m_new;
+  const float alpha = __builtin_amdgcn_exp2f(m_ref - ref);
+  l_run *= alpha;
+  m_ref = m_new;
+  sum[0] = sum[1] = 0.f;
 #pragma unroll
   for (int e = 0; e < 16; ++e) {
-    s[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e], c, -ref));
-    sum[e & 1] += s[e];
+    w[e] = weight(s[e], s_low[e], c, ref);
+    sum[e & 1] += w[e];
   }
-  if (__any(m_new != m_run)) {
-    const float alpha = __builtin_amdgcn_exp2f(m_run - ref);
-    l_run *= alpha;
+  return alpha;
+}
+// `seen`: the last key the tile's first row sees
+__device__ __forceinline__ void mask(f32x16& s, f32x16& s_low, int key0, int seen) {
+  const int lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
+  if (key0 + kKeys - 1 > seen) {
+    const int limit = seen + l32 - key0 - 4 * half;
+#pragma unroll
+    for (int e = 0; e < 16; ++e)
+      if ((e >> 2) * 8 + (e & 3) > limit) {
+        s[e] = -INFINITY;
+        s_low[e] = 0.f;
+      }
+  }
+}
+// Scores -> weights, in place of s
+template <int kA>
+__device__ __forceinline__ void softmax_step(f32x16& s, f32x16& s_low, int key0, int seen, float c, f32x16 (&o)[kA], float& m_ref, float& l_run) {
+  mask(s, s_low, key0, seen);
+  float w[16], sum[2] = {0.f, 0.f};
+  const bool none = m_ref == -INFINITY;   // no key so far, nothing summed
+  if (__any(none)) m_ref = fmaxf(m_ref, over_halves(none ? largest(s, s_low) : -INFINITY, SkvMax()) * c);
+  const float ref = m_ref == -INFINITY ? 0.f : m_ref;   // still none: every term is 0
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    w[e] = weight(s[e], s_low[e], c, ref);
+    sum[e & 1] += w[e];
+  }
+  const bool trip = !(sum[0] + sum[1] <= kSumLimit);
+  if (__builtin_expect(__any(trip), 0)) {
+    const float alpha = move_reference(s, s_low, trip, c, w, sum, m_ref, l_run);
 #pragma unroll
     for (int a = 0; a < kA; ++a)
 #pragma unroll
       for (int e = 0; e < 16; ++e) o[a][e] *= alpha;
   }
-  m_run = m_new;
   l_run += sum[0] + sum[1];
+#pragma unroll
+  for (int e = 0; e < 16; ++e) s[e] = w[e];
 }
 // the weights of a block as B operands: 16-key group g of it
 __device__ __forceinline__ Pieces weights(const f32x16& s, int g) {
@@ -557,30 +656,32 @@ __global__ __launch_bounds__(64 * W, D == 64 ? 2 : 1) void attn_f32_kernel(SkvAt
 }
 
 // ---- long suffixes ----------------------------------------------------------------------------------
-// One workgroup per 128 rows, 32 to a wavefront, D = 64.  Splitting takes 5.5 vector instructions per value, so the workgroup
-// splits a 64-key tile once and shares the pieces through LDS, in the order the matrix instruction reads them:
+// One workgroup per 128 rows, 32 to a wavefront, D = 64.  Splitting takes 5.5 vector
+// instructions per value, so the workgroup splits a block of 32 keys once and shares the pieces through LDS, in the order the matrix
+// instruction reads them:
 //   K: [piece][chunk of 8 d][key], 16 bytes each: lane (key l32, half) of step t reads chunk 2 t + half.
 //   V: [piece][chunk of 8 keys][d], 16 bytes each; chunk 2 g + h holds keys 4 h .. + 3 and 8 + 4 h .. + 3 of 16-key group g,
 //      the keys whose weights half h of a wavefront holds in its score registers 8 g .. 8 g + 7.
-// The next tile's raw values travel in registers (32 per lane) while a tile is worked on; the second workgroup of the
-// compute unit covers the two barriers per tile.
-// What bounds it: the six products take 302 us of 64 requests x 1070 rows x 8 heads at the rate the instruction holds on
-// random operands (1.8 PFLOP/s), and little of the rest hides behind them -- without loads 568 us, without splitting K and V
-// 591, without the softmax 626, matrix products and LDS reads alone 463, all of it 660.  On the fp32 matrix instruction 859,
-// with the kernel above 775.
+// Two blocks of 32 keys are under way at once: the scores of block i + 1 run on the matrix cores beside the softmax of block i and the
+// splitting of its weights, the output products of block i beside the splitting of K(i + 2) and V(i + 1) and the sums of the output.  Two
+// buffers of K and two of V, one barrier a block; two workgroups to a compute unit.
+// What bounds it: issue, with two wavefronts on a SIMD and their waits (48 matrix instructions, 36 reads of LDS, 310 vector and 80 scalar
+// instructions a block), and the clock under that load: 64 requests x 1070 rows x 8 heads 568 us, 470 on constant values; the six products
+// alone are 302 at the rate the instruction holds on random operands.  One block at a time, splitting between two barriers and a
+// maximum per block: 641; the same with requests one after the other (Item::find): 584.  8 x 2000 rows 335 -> 253, 32 x 290 rows 64 -> 50.
+// 256 rows and eight wavefronts to a workgroup, one to a unit: 658 (a quarter of the wavefronts wait at the diagonal).
+constexpr int kBigRows = kRows * kWaves;
 __global__ __launch_bounds__(kThreads, 2) void attn_f32_tile_kernel(SkvAttnF32Params p) {
   constexpr int D = 64;
   constexpr int kT = D / 16;             // steps of the score product
   constexpr int kA = D / 32;             // output accumulators
-  constexpr int kTileRows = kRows * kWaves;
-  constexpr int kKc = D / 32;            // K chunks (8 values) per lane and tile
-  constexpr int kTile = 64;              // keys per LDS tile: a 16-key group (one page, or 16 new rows) per wavefront
-  constexpr int kHalfTile = kPieces * kTile * D / 8;         // 16-byte chunks of K, or of V
+  constexpr int kBuf = kPieces * kKeys * D / 8;              // 16-byte chunks of a block of K, or of V
   constexpr int kRedStride = D + 4;                          // floats per query row of a result in LDS
-  constexpr int kRed = kTileRows * kRedStride / 4;  // 16-byte chunks
-  __shared__ u32x4 smem[2 * kHalfTile > kRed ? 2 * kHalfTile : kRed];
+  static_assert(kBigRows * kRedStride / 4 <= 4 * kBuf);
+  __shared__ u32x4 smem[4 * kBuf + kBigRows * D / 8];
   u32x4* const k_lds = smem;
-  u32x4* const v_lds = smem + kHalfTile;
+  u32x4* const v_lds = smem + 2 * kBuf;
+  u32x4* const q_lds = smem + 4 * kBuf;  // Q's last pieces, [wavefront][step][lane]: in registers they would be 16 too many
   float* const red_o = (float*)smem;     // the results, after the loop
 
   const int lane = threadIdx.x & 63;
@@ -588,93 +689,86 @@ __global__ __launch_bounds__(kThreads, 2) void attn_f32_tile_kernel(SkvAttnF32Pa
   const int l32 = lane & 31, half = lane >> 5;
 
   Item it;
-  if (!it.find<kTileRows>(p)) return;
+  if (!it.find_by_number<kBigRows>(p)) return;
   const int h = it.h, hk = it.hk, r = it.r, qbase = it.qbase, S = it.S, L = it.L, row0 = it.row0, row1 = it.row1;
   const int key_end = L + row1;                               // keys [0, key_end) are seen by some row of the tile
-  const int n_tiles = (key_end + kTile - 1) / kTile;
+  const int n_blocks = (key_end + kKeys - 1) / kKeys;
   const float c = p.scale * kLog2e;
   // this wavefront's rows and keys
   const int row_w = row0 + kRows * wave;
   const int key_end_w = row_w < row1 ? L + min(row1, row_w + kRows) : 0;
+  const int seen = L + row_w;
 
-  // ---- a tile's raw values: wavefront w takes 16-key group w, whose rows lie in one page or behind one another in the new rows
-  const size_t row_len = (size_t)p.Hkv * D;
-  const int kg = lane & 15, kc = lane >> 4;   // K: key of the group, first chunk
-  // Page ids of this wavefront's groups for 64 tiles, one per lane, and for the 64 after them (a load of the id on its own,
-  // behind a tile's loads, would be waited for together with them).
+  // ---- a block's raw values: wavefronts 2 g and 2 g + 1 take 16-key group g, whose rows lie in one page or behind one another in the
+  // new rows: half the chunks of each of its K rows, half its V rows
+  const int group = wave >> 1, hh = wave & 1;
+  const int kg = lane & 15, kc = (lane >> 4) + 4 * hh;        // K: key of the group, chunk
+  // Page ids of this wavefront's group for 64 blocks, one per lane, and for the 64 after them (a load of the id on its own,
+  // behind a block's loads, would be waited for together with them).
   auto window = [&](int w) __attribute__((always_inline)) {
-    const int g = 4 * (64 * w + lane) + wave;
+    const int g = 2 * (64 * w + lane) + group;
     return (int64_t)g * SKV_BLOCK_TOKENS < L && g < p.max_blocks ? p.page_table[(size_t)r * p.max_blocks + g] : -1;
   };
-  int win_cur = window(0), win_nxt = window(1);
-  f32x4 kraw[2 * kKc];
-  float vraw[16];
-  RangeOfQ q_range;
-  auto load_tile = [&](int tile) __attribute__((always_inline)) {
-    if (tile > 0 && (tile & 63) == 0) {
-      win_cur = win_nxt;
-      win_nxt = window(tile / 64 + 1);
-    }
-    const int page = __builtin_amdgcn_readlane(win_cur, tile & 63);
-    const int key0 = tile * kTile + 16 * wave;
-    const float *kb, *vb;
-    int last = 15;   // rows behind it re-read it
-    if (key0 < L) {
-      if (page < 0 || page >= p.n_pages) {   // an absent page reads as zeros
+  int win = 0, win_cur = window(0), win_nxt = window(1);      // windows win and win + 1
+  // The group's rows of a block as a buffer that ends where they do: those behind, and an absent page, read as zeros.  K asks a block ahead
+  // of V, which finds the place worked out.
+  const unsigned row_bytes = (unsigned)p.Hkv * D * 4u;
+  const uint64_t kpool_a = (uint64_t)p.kpool, vpool_a = (uint64_t)p.vpool, knew_a = (uint64_t)p.knew, vnew_a = (uint64_t)p.vnew;
+  struct Rows {
+    uint64_t k, v;
+    int bytes;
+  } k_rows;
+  auto uniform = [](uint64_t x) __attribute__((always_inline)) {
+    return (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32)) << 32 | (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x);
+  };
+  auto rows_of = [&](int b) __attribute__((always_inline)) {
+    const int page = __builtin_amdgcn_readlane((b >> 6) == win ? win_cur : win_nxt, b & 63);
+    const int key0 = b * kKeys + 16 * group;
+    const bool old = key0 < L;
+    const int n = old ? (page >= 0 && page < p.n_pages ? 16 : 0) : max(0, min(16, key_end - key0));
+    const int64_t row = old ? (int64_t)page * SKV_BLOCK_TOKENS : qbase + key0 - L;
+    const uint64_t at = n ? (uint64_t)(row * p.Hkv + hk) * (D * 4) : 0;
+    return Rows{(old ? kpool_a : knew_a) + at, (old ? vpool_a : vnew_a) + at, n ? (int)((n - 1) * row_bytes) + D * 4 : 0};
+  };
+  auto buffer = [&](uint64_t at, int bytes) __attribute__((always_inline)) {   // (a descriptor that is not scalar costs a loop around each load)
+    return __builtin_amdgcn_make_buffer_rsrc((void*)uniform(at), 0, __builtin_amdgcn_readfirstlane(bytes), 0x00020000);
+  };
+  const unsigned k_off = (unsigned)kg * row_bytes + kc * 32u, v_off = (unsigned)(4 * hh) * row_bytes + lane * 4u;
+  float kraw[8], vraw[8];
+  auto load_k = [&](int b) __attribute__((always_inline)) {
+    k_rows = rows_of(b);
+    const auto rsrc = buffer(k_rows.k, k_rows.bytes);
+    const f32x4 x = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, k_off, 0, 0));
+    const f32x4 y = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, k_off + 16, 0, 0));
 #pragma unroll
-        for (int i = 0; i < 2 * kKc; ++i) kraw[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int i = 0; i < 16; ++i) vraw[i] = 0.f;
-        return;
-      }
-      const size_t off = ((size_t)page * SKV_BLOCK_TOKENS * p.Hkv + hk) * D;
-      kb = (const float*)p.kpool + off;
-      vb = (const float*)p.vpool + off;
-    } else {
-      const int first = min(key0, key_end - 1);
-      const size_t off = ((size_t)(qbase + first - L) * p.Hkv + hk) * D;
-      kb = (const float*)p.knew + off;
-      vb = (const float*)p.vnew + off;
-      last = min(15, key_end - 1 - first);
-    }
-    const float* src = kb + min(kg, last) * row_len + 8 * kc;
-#pragma unroll
-    for (int i = 0; i < kKc; ++i) {
-      kraw[2 * i] = *(const f32x4*)(src + 32 * i);
-      kraw[2 * i + 1] = *(const f32x4*)(src + 32 * i + 4);
-    }
-    if (__builtin_expect(last == 15, 1)) {
-#pragma unroll
-      for (int i = 0; i < 16; ++i) vraw[i] = vb[i * row_len + lane];
-    } else {
-#pragma unroll
-      for (int i = 0; i < 16; ++i) vraw[i] = vb[min(i, last) * row_len + lane];
+    for (int i = 0; i < 4; ++i) {
+      kraw[i] = x[i];
+      kraw[4 + i] = y[i];
     }
   };
-  auto store_tile = [&]() __attribute__((always_inline)) {
+  auto load_v = [&](const Rows& x) __attribute__((always_inline)) {
+    const auto rsrc = buffer(x.v, x.bytes);
 #pragma unroll
-    for (int i = 0; i < kKc; ++i) {
-      const f32x4 a = kraw[2 * i], b = kraw[2 * i + 1];
-      const float x[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
-      const Pieces k = split8(x);
-#pragma unroll
-      for (int q = 0; q < kPieces; ++q) k_lds[(q * (D / 8) + kc + 4 * i) * kTile + 16 * wave + kg] = __builtin_bit_cast(u32x4, k.p[q]);
-    }
-#pragma unroll
-    for (int hh = 0; hh < 2; ++hh) {
-      float x[8];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) x[i] = vraw[(i >> 2) * 8 + 4 * hh + (i & 3)];
-      const Pieces w = split8(x);
-#pragma unroll
-      for (int q = 0; q < kPieces; ++q) v_lds[(q * (kTile / 8) + 2 * wave + hh) * D + lane] = __builtin_bit_cast(u32x4, w.p[q]);
-    }
+    for (int i = 0; i < 8; ++i)
+      vraw[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc, v_off, (unsigned)((i >> 2) * 8 + (i & 3)) * row_bytes, 0));
   };
+  // (not in front of the branches around what is done with them: everybody would wait there for what has just been requested)
+  auto here = [](float (&x)[8]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) asm volatile("" : "+v"(x[i]));
+  };
+  u32x4* const k_dst = k_lds + kc * kKeys + 16 * group + kg;
+  u32x4* const v_dst = v_lds + wave * D + lane;
+  const u32x4* const k_src = k_lds + half * kKeys + l32;
+  const u32x4* const v_src = v_lds + half * D + l32;
 
-  load_tile(0);
+  load_k(0);
+  load_v(k_rows);
 
   // ---- Q pieces (B operand): lane (query l32, half), step t: d = 16 t + 8 half .. + 7
-  Pieces qp[kT];
+  bf16x8 qp[kT][2];
+  u32x4* const q_last = q_lds + wave * (kT * 64) + lane;
+  RangeOfQ q_range;
   {
     const float* src = (const float*)p.q + ((size_t)(qbase + min(row_w + l32, S - 1)) * p.Hq + h) * D + 8 * half;
 #pragma unroll
@@ -683,58 +777,194 @@ __global__ __launch_bounds__(kThreads, 2) void attn_f32_tile_kernel(SkvAttnF32Pa
       const float x[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
 #pragma unroll
       for (int k = 0; k < 8; ++k) q_range.add(x[k]);
-      qp[t] = split8(x);
+      const Pieces q = split8(x);
+      qp[t][0] = q.p[0];
+      qp[t][1] = q.p[1];
+      q_last[t * 64] = __builtin_bit_cast(u32x4, q.p[2]);   // (read by this lane only)
     }
   }
+  auto store_k = [&](int buf) __attribute__((always_inline)) {
+    const Pieces k = split8(kraw);
+#pragma unroll
+    for (int q = 0; q < kPieces; ++q) k_dst[buf * kBuf + q * (D / 8) * kKeys] = __builtin_bit_cast(u32x4, k.p[q]);
+  };
+  auto store_v = [&](int buf) __attribute__((always_inline)) {
+    const Pieces v = split8(vraw);
+#pragma unroll
+    for (int q = 0; q < kPieces; ++q) v_dst[buf * kBuf + q * (kKeys / 8) * D] = __builtin_bit_cast(u32x4, v.p[q]);
+  };
+  auto publish = [&]() __attribute__((always_inline)) {   // (loads from memory stay in flight)
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
 
   f32x16 o[kA];   // O^T: d = 32 a + 8 (e / 4) + 4 half + e % 4, query l32
 #pragma unroll
   for (int a = 0; a < kA; ++a)
 #pragma unroll
     for (int e = 0; e < 16; ++e) o[a][e] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;   // running maximum (scaled, exp2 units) and this half's running sum, per query
+  float m_ref = -INFINITY, l_run = 0.f;   // reference (scaled, exp2 units) and this half's running sum, per query
   const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  auto block = [&](int key0, int kb) __attribute__((always_inline)) {   // kb: block of 32 keys of the tile
-    f32x16 s = zero16, s_low = zero16;
-    __builtin_amdgcn_s_setprio(1);   // (before the vector work of the SIMD's other wavefront: 181 -> 177 us for 64 requests of 200 .. 600 rows)
+  struct Scores {
+    f32x16 s, low;
+  } sc[2];
+  sc[0].s = sc[0].low = sc[1].s = sc[1].low = zero16;
+  // Fragments of K, then of V: a piece's registers take the next step's as soon as it has been used (two sets spilled Q's pieces, and a
+  // reload waits for every load in flight).
+  bf16x8 frag[kPieces];
+  auto k_piece = [&](int buf, int t, int q) __attribute__((always_inline)) { frag[q] = __builtin_bit_cast(bf16x8, k_src[buf * kBuf + (q * (D / 8) + 2 * t) * kKeys]); };
+  auto v_piece = [&](int buf, int a, int g, int q) __attribute__((always_inline)) {
+    frag[q] = __builtin_bit_cast(bf16x8, v_src[buf * kBuf + (q * (kKeys / 8) + 2 * g) * D + 32 * a]);
+  };
+  auto active = [&](int i) __attribute__((always_inline)) { return i * kKeys < key_end_w; };   // block i of 32 keys
+
+  // Scores of a block, beside `side(j)`, j = 0 .. 23: what the vector unit does behind the j-th matrix instruction.  vbuf: whose first
+  // fragments are read behind them.
+  auto scores = [&](int buf, int vbuf, Scores& x, auto&& side) __attribute__((always_inline)) {
+#pragma unroll
+    for (int q = 2; q >= 0; --q) k_piece(buf, 0, q);
+    bf16x8 q2 = __builtin_bit_cast(bf16x8, q_last[0]);
 #pragma unroll
     for (int t = 0; t < kT; ++t) {
-      Pieces k;
 #pragma unroll
-      for (int q = 0; q < kPieces; ++q) k.p[q] = __builtin_bit_cast(bf16x8, k_lds[(q * (D / 8) + 2 * t + half) * kTile + kKeys * kb + l32]);
-      s_low = mfma_pieces<2>(k, qp[t], s_low);
-      s_low = mfma_pieces<1>(k, qp[t], s_low);
-      s = mfma_pieces<0>(k, qp[t], s);
-    }
-    __builtin_amdgcn_s_setprio(0);
-    // idle states for the last score instructions: their readers may sit behind a branch, through which the compiler does
-    // not count them
-    asm volatile("s_nop 7\n\ts_nop 3" : "+v"(s), "+v"(s_low));
-    softmax_step(s, s_low, key0, L + row_w, c, o, m_run, l_run);
-    const Pieces w[2] = {weights(s, 0), weights(s, 1)};
-#pragma unroll
-    for (int a = 0; a < kA; ++a) {
-      Pieces v[2];
-#pragma unroll
-      for (int g = 0; g < 2; ++g)
-#pragma unroll
-        for (int q = 0; q < kPieces; ++q)
-          v[g].p[q] = __builtin_bit_cast(bf16x8, v_lds[(q * (kTile / 8) + 2 * (2 * kb + g) + half) * D + 32 * a + l32]);
-      add_block(o[a], v[0], v[1], w);
+      for (int n = 0; n < 6; ++n) {
+        constexpr int kk[6] = {2, 1, 1, 0, 0, 0}, qq[6] = {0, 1, 0, 2, 1, 0};   // the largest apart
+        f32x16& acc = n < 5 ? x.low : x.s;
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag[kk[n]], qq[n] == 2 ? q2 : qp[t][qq[n] & 1], t == 0 && (n == 0 || n == 5) ? zero16 : acc, 0, 0, 0);
+        if (n == 0 || n == 2 || n == 5) {
+          if (t + 1 < kT) k_piece(buf, t + 1, kk[n]);
+          else v_piece(vbuf, 0, 0, kk[n]);
+        }
+        if (n == 3 && t + 1 < kT) q2 = __builtin_bit_cast(bf16x8, q_last[(t + 1) * 64]);
+        side(6 * t + n);
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
   };
-
-  for (int tile = 0; tile < n_tiles; ++tile) {
-    if (tile > 0) __syncthreads();   // every wavefront is done with the tile before
-    store_tile();
-    __syncthreads();
-    if (tile + 1 < n_tiles) load_tile(tile + 1);
-#pragma unroll 1
-    for (int kb = 0; kb < kTile / kKeys; ++kb) {
-      const int key0 = tile * kTile + kKeys * kb;
-      if (key0 < key_end_w) block(key0, kb);
+  // Weights of a block in 24 pieces of vector work: exponentials against the reference as it stands (0 .. 7), the reference moved where
+  // they sum to too much, the weights split (8 .. 23; a pair in two steps).
+  Words w[2];   // 16-key group g of the block
+  float x[16], sum[2], alpha = 1.f;   // alpha: what the output so far is to be multiplied by (here, in a branch of its own, it would be copied every time)
+  auto soften = [&](int j, Scores& cur) __attribute__((always_inline)) {
+    if (j == 0) {
+      sum[0] = sum[1] = 0.f;
+      asm volatile("" : "+v"(m_ref));   // (or what the two forms below have in common is worked out in front of them, into 16 registers more)
     }
+    if (j < 8) {
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        x[2 * j + k] = weight(cur.s[2 * j + k], cur.low[2 * j + k], c, m_ref);
+        sum[k] += x[2 * j + k];
+      }
+      return;
+    }
+    if (j == 8) {
+      const bool trip = !(sum[0] + sum[1] <= kSumLimit);
+      alpha = 1.f;
+      if (__builtin_expect(__any(trip), 0)) alpha = move_reference(cur.s, cur.low, trip, c, x, sum, m_ref, l_run);
+      l_run += sum[0] + sum[1];
+    }
+    const int pair = (j - 8) >> 1;
+    split_step(x[2 * pair], x[2 * pair + 1], j & 1, pair & 3, w[pair >> 2]);
+  };
+  // O^T += V^T P^T of a block: summed from zero, small products first, and added once; beside late(j), j = 0 .. 23, and the sums.
+  // (in place: the compiler sums into the block's registers and copies them back; nor does it see what the matrix core has not written yet)
+  auto add_to = [&](f32x16& y, int e, const f32x16& add) __attribute__((always_inline)) {
+    float x = y[e];
+    asm volatile("v_fma_f32 %0, %0, %1, %2" : "+v"(x) : "v"(alpha), "v"(add[e]));
+    y[e] = x;
+  };
+  auto output = [&](int buf, auto&& late) __attribute__((always_inline)) {
+    f32x16 add[kA];
+#pragma unroll
+    for (int a = 0; a < kA; ++a) {
+      bf16x8 first;   // the first group's largest piece waits for the second's small products
+#pragma unroll
+      for (int n = 0; n < 12; ++n) {
+        constexpr int vv[12] = {2, 1, 1, 0, 0, 2, 1, 1, 0, 0, 0, 0}, ww[12] = {0, 1, 0, 2, 1, 0, 1, 0, 2, 1, 0, 0};
+        const int g = n < 5 || n == 10 ? 0 : 1;
+        add[a] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(n == 10 ? first : frag[vv[n]], __builtin_bit_cast(bf16x8, w[g][ww[n]]), n == 0 ? zero16 : add[a], 0, 0, 0);
+        if (n == 4) first = frag[0];
+        if (n == 0 || n == 2 || n == 4) v_piece(buf, a, 1, vv[n]);
+        if (a + 1 < kA && (n == 5 || n == 7 || n == 11)) v_piece(buf, a + 1, 0, vv[n]);
+        late(12 * a + n);
+        if (a == 1 && n >= 4) {
+#pragma unroll
+          for (int e = 2 * (n - 4); e < 2 * (n - 4) + 2; ++e) add_to(o[0], e, add[0]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 1" : "+v"(add[1]));
+#pragma unroll
+    for (int e = 0; e < 16; ++e) add_to(o[1], e, add[1]);
+  };
+  auto nothing = [](int) __attribute__((always_inline)) {};
+  auto idle = [&](Scores& z) __attribute__((always_inline)) {   // for the last score instructions, whose readers may sit behind a branch
+    asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 1" : "+v"(z.s), "+v"(z.low));
+  };
+  // Block i, kB = i % 2.  (Behind the last one stale values are split and rows read again, for nobody.)
+  auto block = [&]<int kB>(int i) __attribute__((always_inline)) {
+    Scores &cur = sc[kB], &nxt = sc[kB ^ 1];
+    Words kw, vw;
+    const Rows v_rows = k_rows;   // of block i + 2
+    auto late = [&](int j) __attribute__((always_inline)) {
+      if (j == 0) here(kraw);
+      if (j == 12) here(vraw);
+      if (j < 8) split_step(kraw[j & ~1], kraw[j | 1], j & 1, j >> 1, kw);
+      else if (j < 11) k_dst[kB * kBuf + (j - 8) * (D / 8) * kKeys] = kw[j - 8];
+      else if (j >= 12 && j < 20) split_step(vraw[(j - 12) & ~1], vraw[(j - 12) | 1], j & 1, (j - 12) >> 1, vw);
+      else if (j >= 20 && j < 23) v_dst[(kB ^ 1) * kBuf + (j - 20) * (kKeys / 8) * D] = vw[j - 20];
+    };
+    if (active(i)) {
+      mask(cur.s, cur.low, i * kKeys, seen);
+      if (active(i + 1)) {
+        scores(kB ^ 1, kB, nxt, [&](int j) __attribute__((always_inline)) { soften(j, cur); });
+      } else {
+#pragma unroll
+        for (int q = 2; q >= 0; --q) v_piece(kB, 0, 0, q);
+#pragma unroll
+        for (int j = 0; j < 24; ++j) soften(j, cur);
+      }
+      output(kB, late);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 24; ++j) late(j);
+    }
+    // (requested in either branch the values would be copied behind it, and the copies wait for them)
+    load_k(i + 3);
+    load_v(v_rows);
+    if (((i + 3) >> 6) != win) {
+      ++win;
+      win_cur = win_nxt;
+      win_nxt = window(win + 1);
+      asm volatile("" : "+v"(win_nxt));   // (waited for here and not wherever it may be copied)
+    }
+    if (i + 1 < n_blocks) publish();
+  };
+
+  // ---- prologue: K(0), K(1), V(0) in LDS; scores of block 0, whose row maxima are the first reference
+  store_k(0);
+  load_k(1);
+  store_v(0);
+  load_v(k_rows);
+  store_k(1);
+  load_k(2);
+  publish();
+  if (active(0)) {
+    scores(0, 0, sc[0], nothing);
+    idle(sc[0]);
+    mask(sc[0].s, sc[0].low, 0, seen);
+    m_ref = fmaxf(over_halves(largest(sc[0].s, sc[0].low), SkvMax()) * c, -3.0e38f);   // (a row sees key 0)
   }
+  publish();   // (K(2) takes the place of K(0))
+  for (int i = 0; i < n_blocks; i += 2) {
+    block.template operator()<0>(i);
+    if (i + 1 >= n_blocks) break;
+    block.template operator()<1>(i + 1);
+  }
+  asm volatile("s_nop 7\n\ts_nop 3");
   l_run = over_halves(l_run, SkvAdd());
 
   const bool no_pieces = q_range.odd() || !all_finite(o, l_run), small = some_small(o, l_run);
@@ -746,12 +976,19 @@ __global__ __launch_bounds__(kThreads, 2) void attn_f32_tile_kernel(SkvAttnF32Pa
   }
   // ---- output, through LDS: whole rows leave together
   {
+    // o / l_run: a product and what it leaves, rounded as a division is but at a few places in a million (the sums are a row's weights, 1 to
+    // 2^31), in a third of its instructions
+    const float inv = 1.f / l_run;
+    auto over = [&](float x) __attribute__((always_inline)) {
+      const float y = x * inv;
+      return __builtin_fmaf(__builtin_fmaf(-y, l_run, x), inv, y);
+    };
     float* dst = red_o + (size_t)(kRows * wave + l32) * kRedStride + 4 * half;
 #pragma unroll
     for (int a = 0; a < kA; ++a)
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        *(f32x4*)(dst + 32 * a + 8 * i) = f32x4{o[a][4 * i], o[a][4 * i + 1], o[a][4 * i + 2], o[a][4 * i + 3]} / l_run;
+        *(f32x4*)(dst + 32 * a + 8 * i) = f32x4{over(o[a][4 * i]), over(o[a][4 * i + 1]), over(o[a][4 * i + 2]), over(o[a][4 * i + 3])};
   }
   __syncthreads();
   float* out = (float*)p.out + (((size_t)qbase + row0) * p.Hq + h) * D;
@@ -781,10 +1018,18 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 1) void attn_f32_rows_kerne
   one_row<D, D>(p, row);
 }
 
-}  // namespace
-
-// Large tiles where suffixes fill them (256 rows on average) and there are enough for every workgroup slot of the chip: 64
-// requests x 1070 rows x 8 heads 660 us against 775, 32 x 290 rows 41 against 45; below, 8 x 290 rows 28 us against 21.
+// Tiles of 128 rows where their workgroups outnumber the compute units and rows fill them.  us with 32 rows to a workgroup / so, 8 heads
+// over 8: 16 requests of 200 rows behind nothing 23.2 / 18.9, behind 1024 keys 75 / 68; 32 of 100 behind 256 32.2 / 28.3; 64 of 100 behind
+// 1024 161 / 110; but 16 of 100 (128 workgroups) behind nothing 10.5 / 14.0, behind 1024 41 / 63.  Of up to 96 rows some wavefronts have none, which in one
+// round is made up for (64 of 64 behind 256 37.4 / 32.2) and in several is not (150 of 64 behind nothing 27.5 / 41.2); many rounds of
+// few keys go faster with one wavefront to an item (150 of 128 behind nothing 52 / 59).  402 calls of 2 to 300 requests of up to 1500
+// rows: time 0.979 of that of the rule before (two tiles a request, 512 in all), 0.971 were every choice right; 14 are slower by 2 % and more.
+bool large_tiles(const SkvAttnF32Params& p) {
+  const int64_t rows = (p.max_rows + p.n_req - 1) / p.n_req, workgroups = p.n_req * ((rows + kBigRows - 1) / kBigRows) * p.Hq;
+  if (workgroups < 320 || rows <= 48) return false;
+  if (rows <= 96) return workgroups <= 512;
+  return workgroups < 1024 || (int64_t)p.max_blocks * SKV_BLOCK_TOKENS + rows > 224;
+}
 // Where the items fill the chip by themselves, one wavefront takes each: four times as many at once, nothing to merge.  256 / 1000
 // requests of one row, 8 heads, d 64, behind no keys 25.7 / 84.6 us with four, 12.4 / 31.6 with one; behind 96 33.4 / 132 and 28.5 /
 // 95; behind 480 99.9 / 390 and 106 / 385, so up to two rounds the width of the table decides.  Single rows in such numbers are
@@ -793,10 +1038,12 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 1) void attn_f32_rows_kerne
 // behind 256, 8 heads, 12.5 us with four, 11.9 with eight; one of 64 behind 2048 37.0 / 31.9, 2 of 300 behind 1000 28.4 / 25.1; 16 of 64
 // behind 256, 384 items, 16.1 / 20.7.  Up to 256 keys, a block of 32 for each of the eight, the four have two at most and fewer states to
 // merge: one of 40 behind 80 7.0 / 7.7, 16 of 33 behind 208 9.7 / 10.3 (behind 272 11.7 either way).
+}  // namespace
+
 int skv_attn_f32_enqueue(const SkvAttnF32Params& p, int head_dim, void* stream) {
   const hipStream_t st = (hipStream_t)stream;
-  const int64_t tiles = p.max_rows / (kRows * kWaves), slots = head_dim == 64 ? 2048 : 1024;   // slots: wavefronts at once
-  const bool large = head_dim == 64 && tiles >= 2 * (int64_t)p.n_req && tiles * p.Hq >= 512;
+  const int64_t tiles = p.max_rows / kBigRows, slots = head_dim == 64 ? 2048 : 1024;   // slots: wavefronts at once
+  const bool large = head_dim == 64 && large_tiles(p);
   const int64_t items = ((large ? tiles : p.max_rows / kRows) + p.n_req) * p.Hq;
   if (items > 0x7fffffff) return SKV_ERANGE;
   const bool rows = items >= slots && 2 * p.max_rows <= 3 * (int64_t)p.n_req;

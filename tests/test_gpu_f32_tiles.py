@@ -1,0 +1,76 @@
+"""fp32 prefill attention in tiles of 128 rows (more than 320 workgroups, 49 rows a request and more): tiles dealt out by their number among
+64 requests at a time, a first tile of what a request's rows leave over, blocks of 32 keys two at a time, a reference that moves when weights
+grow.  Against the fp64 oracle; bound as in test_gpu_f32_precision.py."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from test_gpu_parity import attn_case, run_attn
+
+pytestmark = pytest.mark.gpu
+REL = 8 * 2.0 ** -24
+
+G = np.random.default_rng(9)
+EDGES = [49, 127, 128, 129, 160, 161, 255, 256, 257, 31, 1, 0, 33, 384, 97, 512]
+# query / kv heads, rows and reused blocks per request
+CASES = {
+    "edges of tiles": (32, 2, EDGES, [0, 1, 2, 3, 4, 5, 6, 7, 0, 9, 1, 3, 2, 1, 13, 0]),
+    "more than 64 requests": (4, 4, G.integers(49, 140, 130), G.integers(0, 4, 130)),
+    "one of them alone in its 64": (8, 8, [60] * 64 + [130], [1] * 65),
+    "no rows among them": (16, 4, [0] * 70 + [300] * 11 + [0] * 3, [2] * 84),
+    "pages of more than 64 blocks of keys": (64, 4, [200, 330, 70, 64], [260, 129, 128, 0]),
+    "one long request": (32, 4, [1500], [5]),
+}
+
+
+def case(name, seed=3):
+    hq, hkv, S, k = CASES[name]
+    return attn_case(seed, len(S), hq, hkv, 64, torch.float32, max(max(k), 1), S, k, n_pages=int(sum(k)) + 3)
+
+
+def check(c, rel=REL):
+    want = oracle.attention(**c, n_threads=16)
+    got = run_attn(c)
+    err = np.linalg.norm(got - want) / np.linalg.norm(want)
+    print("error against 64 bits: %.3e" % err)
+    assert err <= rel
+
+
+@pytest.mark.parametrize("name", CASES)
+def test_tiles(name):
+    check(case(name))
+
+
+# Scores that grow along the keys: the reference moves in every block, and in some rows only.  Bound: the scores themselves are not small
+# here, and one of s (in exp2 units) carries s 2^-24 of its own rounding beside the 8 * 2^-24 of the exponent's argument; the rows' largest
+# scores, whose weights count, are `size` on average over rows and heads.
+@pytest.mark.parametrize("name", ["edges of tiles", "pages of more than 64 blocks of keys"])
+def test_growing_scores(name):
+    c = case(name)
+    c["kpool"] = c["kpool"].abs()
+    c["knew"] = c["knew"].abs()
+    c["q"][: len(c["q"]) // 2] = c["q"][: len(c["q"]) // 2].abs() * 2     # (towards larger scores; the others take both signs)
+    for r in range(len(c["matched_len"])):
+        n = c["q_off"][r + 1] - c["q_off"][r]
+        c["knew"][c["q_off"][r]: c["q_off"][r + 1]] *= torch.linspace(0.1, 2.0, int(n) + 1)[1:, None, None]
+    G = c["q"].shape[1] // c["knew"].shape[1]
+    size = [(c["q"][a:b, h] @ c["knew"][a:b, h // G].T).tril().amax(1).mean() for a, b in zip(c["q_off"][:-1], c["q_off"][1:]) if b > a
+            for h in range(c["q"].shape[1])]
+    size = float(np.mean(size)) / 8 * 1.4427
+    check(c, REL + size * 2.0 ** -24)
+
+
+def test_absent_pages_read_as_zeros():
+    c = case("pages of more than 64 blocks of keys")
+    c["page_table"][0, 3] = -1
+    c["page_table"][0, 200] = c["kpool"].shape[0]
+    c["page_table"][1, 128] = -1
+    want_c = dict(c)
+    zero = torch.zeros_like(c["kpool"][:1])                               # the oracle reads a page of zeros in their place
+    want_c["kpool"], want_c["vpool"] = torch.cat([c["kpool"], zero]), torch.cat([c["vpool"], zero])
+    pt = c["page_table"].copy()
+    pt[0, 3] = pt[0, 200] = pt[1, 128] = c["kpool"].shape[0]
+    want = oracle.attention(**dict(want_c, page_table=pt), n_threads=16)
+    got = run_attn(c)
+    assert np.linalg.norm(got - want) <= REL * np.linalg.norm(want)
