@@ -1427,7 +1427,7 @@ static int prefill_attn_enqueue(const skv_attn_desc* desc, int32_t n_req, const 
   // of up to kSkvGatherScan requests a plan with parts makes the suffix offsets itself, and its pages travel beside the merge
   const bool plan = desc->dtype == SKV_BF16 && !y.two && plan_in_place(y, n_req) && !(y.max_parts && two_rounds(y, n_req, total_q_rows, max_blocks));
   const bool late = x && plan && y.max_parts && !x->gather.large;
-  if (x && !late) {
+  if (x && !late && desc->dtype == SKV_BF16) {
     const int rc = skv_gather_enqueue(x->gather, false, x->req_off, x->q_off, x->count, stream);
     if (rc) return rc;
   }
@@ -1447,8 +1447,9 @@ static int prefill_attn_enqueue(const skv_attn_desc* desc, int32_t n_req, const 
   if (desc->dtype == SKV_F32) {
     const SkvAttnF32Params f = {d_q, d_knew, d_vnew, d_kpool, d_vpool, d_out, d_q_off, d_matched_len, d_page_table,
                                 n_req, max_blocks, n_pages, desc->n_q_heads, desc->n_kv_heads, skv_softmax_scale(desc),
-                                total_q_rows};
-    return skv_attn_f32_enqueue(f, desc->head_dim, stream);
+                                total_q_rows, nullptr};
+    const SkvStepRest rest = x ? SkvStepRest{&x->gather, x->req_off, x->q_off, &x->count} : SkvStepRest{};
+    return skv_attn_f32_enqueue(f, desc->head_dim, x ? &rest : nullptr, stream);
   }
 
   // the list holds whole items or, where anything is split, no more than max_parts records

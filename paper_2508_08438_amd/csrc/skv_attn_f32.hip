@@ -11,7 +11,7 @@
 // registers of S^T are the B operand of the second product as they stand.
 #include <type_traits>
 
-#include "skv_internal.h"
+#include "skv_gather.h"
 
 namespace {
 
@@ -97,13 +97,26 @@ template <> struct vec_of<4> { typedef f32x4 type; };
 // no tile maps to leave at once.
 struct Item {
   int h, hk, r, qbase, S, L, row0, row1;
-  template <int kTileRows>
-  __device__ __forceinline__ bool find(const SkvAttnF32Params& p) {
+  // Request lane's rows from what q_off is made of, for up to 64 requests: their end (the launch that writes q_off need not come first).
+  static __device__ __forceinline__ int rows_end(const SkvAttnF32Params& p, int& own) {
     const int lane = threadIdx.x & 63;
-    h = blockIdx.x % p.Hq;
+    own = lane < p.n_req ? max(0, p.req_off[lane + 1] - p.req_off[lane] - p.matched_len[lane]) : 0;
+    return skv_wave_scan(own);
+  }
+  template <int kTileRows>
+  __device__ __forceinline__ bool find(const SkvAttnF32Params& p, int block) {
+    const int lane = threadIdx.x & 63;
+    h = block % p.Hq;
     hk = h / (p.Hq / p.Hkv);
-    const int t = blockIdx.x / p.Hq;
+    const int t = block / p.Hq;
     r = 0;
+    if (p.req_off) {
+      int own;
+      const int end = rows_end(p, own);
+      r = __builtin_popcountll(__ballot(lane < p.n_req && (end - own) / kTileRows + lane <= t)) - 1;   // (lane 0 always counts)
+      qbase = __builtin_amdgcn_readlane(end - own, r);
+      S = __builtin_amdgcn_readlane(own, r);
+    } else {
     for (int n = p.n_req; n > 1;) {
       const int step = (n + 63) / 64;
       const int idx = r + lane * step;
@@ -115,7 +128,9 @@ struct Item {
     }
     r = __builtin_amdgcn_readfirstlane(r);
     qbase = __builtin_amdgcn_readfirstlane(p.q_off[r]);
-    S = (int)min((int64_t)(__builtin_amdgcn_readfirstlane(p.q_off[r + 1]) - qbase), p.max_rows - qbase);
+    S = __builtin_amdgcn_readfirstlane(p.q_off[r + 1]) - qbase;
+    }
+    S = (int)min((int64_t)S, p.max_rows - qbase);
     const int n_tiles = (S + kTileRows - 1) / kTileRows;
     const int k_tile = t - (qbase / kTileRows + r);
     if (k_tile < 0 || k_tile >= n_tiles) return false;
@@ -129,11 +144,11 @@ struct Item {
   // requests of 1070 rows over 512 places: the chip empties 1 % after the mean and not 11 %).  What a request's rows leave over is its
   // first tile, which sees the fewest keys, and so many rows more that a wavefront's start where a block of keys does.
   template <int kTileRows>
-  __device__ __forceinline__ bool find_by_number(const SkvAttnF32Params& p) {
+  __device__ __forceinline__ bool find_by_number(const SkvAttnF32Params& p, int block) {
     const int lane = threadIdx.x & 63;
-    h = blockIdx.x % p.Hq;
+    h = block % p.Hq;
     hk = h / (p.Hq / p.Hkv);
-    const int t = blockIdx.x / p.Hq;
+    const int t = block / p.Hq;
     int r0 = 0;   // first of the 64
     for (int n = (p.n_req + 63) / 64; n > 1;) {
       const int step = (n + 63) / 64, idx = lane * step;
@@ -145,8 +160,15 @@ struct Item {
     }
     r0 = __builtin_amdgcn_readfirstlane(r0);
     const bool have = r0 + lane < p.n_req;
-    const int begin = have ? p.q_off[r0 + lane] : 0;
-    const int rows = have ? (int)min((int64_t)(p.q_off[r0 + lane + 1] - begin), p.max_rows - begin) : 0;
+    int begin = 0, rows = 0;
+    if (p.req_off) {
+      const int end = rows_end(p, rows);
+      begin = end - rows;
+    } else if (have) {
+      begin = p.q_off[r0 + lane];
+      rows = p.q_off[r0 + lane + 1] - begin;
+    }
+    rows = (int)min((int64_t)rows, p.max_rows - begin);
     const int own = have ? max(0, (rows + kTileRows - 1) / kTileRows) : 0;
     int place = t - (__builtin_amdgcn_readfirstlane(begin) / kTileRows + r0);
     auto from = [&](int number) __attribute__((always_inline)) { return skv_over_wave(max(0, own - number), SkvAdd()); };   // tiles of that number and higher ones
@@ -436,7 +458,7 @@ __device__ __forceinline__ void add_block(f32x16& o, const Pieces& v0, const Pie
 // Attention alone, us, on the fp32 matrix instruction -> so, four wavefronts: 8 requests of 144..320 rows, 8/8 heads, d 64: 27 -> 21; 100 of up
 // to 30 rows behind 512..2048 cached ones: 140 -> 95; the same at 8/2 heads, d 128: 225 -> 227.
 template <int D, int W>
-__global__ __launch_bounds__(64 * W, D == 64 ? 2 : 1) void attn_f32_kernel(SkvAttnF32Params p) {
+__device__ __forceinline__ void attn_f32_item(const SkvAttnF32Params& p, int block) {
   constexpr int kWaves = W, kThreads = 64 * W;
   constexpr int kJ = D / 8;        // 16-byte pieces of a K row per lane
   constexpr int kA = D / 32;       // output accumulators
@@ -454,7 +476,7 @@ __global__ __launch_bounds__(64 * W, D == 64 ? 2 : 1) void attn_f32_kernel(SkvAt
   const int l32 = lane & 31, half = lane >> 5;
 
   Item it;
-  if (!it.find<kRows>(p)) return;
+  if (!it.find<kRows>(p, block)) return;
   const int h = it.h, hk = it.hk, r = it.r, qbase = it.qbase, S = it.S, L = it.L, row0 = it.row0, row1 = it.row1;
   const int key_end = L + row1;                               // keys [0, key_end) are seen by some row of the tile
   const int n_blocks = (key_end + kKeys - 1) / kKeys;
@@ -671,7 +693,7 @@ __global__ __launch_bounds__(64 * W, D == 64 ? 2 : 1) void attn_f32_kernel(SkvAt
 // maximum per block: 641; the same with requests one after the other (Item::find): 584.  8 x 2000 rows 335 -> 253, 32 x 290 rows 64 -> 50.
 // 256 rows and eight wavefronts to a workgroup, one to a unit: 658 (a quarter of the wavefronts wait at the diagonal).
 constexpr int kBigRows = kRows * kWaves;
-__global__ __launch_bounds__(kThreads, 2) void attn_f32_tile_kernel(SkvAttnF32Params p) {
+__device__ __forceinline__ void attn_f32_tile(const SkvAttnF32Params& p, int block_id) {
   constexpr int D = 64;
   constexpr int kT = D / 16;             // steps of the score product
   constexpr int kA = D / 32;             // output accumulators
@@ -689,7 +711,7 @@ __global__ __launch_bounds__(kThreads, 2) void attn_f32_tile_kernel(SkvAttnF32Pa
   const int l32 = lane & 31, half = lane >> 5;
 
   Item it;
-  if (!it.find_by_number<kBigRows>(p)) return;
+  if (!it.find_by_number<kBigRows>(p, block_id)) return;
   const int h = it.h, hk = it.hk, r = it.r, qbase = it.qbase, S = it.S, L = it.L, row0 = it.row0, row1 = it.row1;
   const int key_end = L + row1;                               // keys [0, key_end) are seen by some row of the tile
   const int n_blocks = (key_end + kKeys - 1) / kKeys;
@@ -1038,33 +1060,97 @@ bool large_tiles(const SkvAttnF32Params& p) {
 // behind 256, 8 heads, 12.5 us with four, 11.9 with eight; one of 64 behind 2048 37.0 / 31.9, 2 of 300 behind 1000 28.4 / 25.1; 16 of 64
 // behind 256, 384 items, 16.1 / 20.7.  Up to 256 keys, a block of 32 for each of the eight, the four have two at most and fewer states to
 // merge: one of 40 behind 80 7.0 / 7.7, 16 of 33 behind 208 9.7 / 10.3 (behind 272 11.7 either way).
+// What a launch carries behind its attention's workgroups: the rest of a step of up to 64 requests (a lane each).  It needs nothing of the
+// attention, nor that anything of it but q_off, which the workgroups work out (Item::rows_end).  So a step has one launch less, and short
+// workgroups to fill the places that the last long ones leave: eight requests of 270 rows behind 50 keys 28.0 -> 24.7 us a pass, 64 of 1080
+// 583 -> 567.  Not where items are so many that a wavefront takes one: those workgroups are too small to copy pages.
+struct Rest {
+  SkvGather gather;
+  int32_t* q_off;
+  SkvCount count;
+  int n_attn, n_count;
+};
+template <int W>
+__device__ __forceinline__ void rest_of_step(const SkvAttnF32Params& p, const Rest& x, int block) {
+  __shared__ int64_t first[kSkvGatherScan + 1];
+  if (block == 0) {
+    int own;
+    const int lane = threadIdx.x, end = Item::rows_end(p, own);
+    if (lane == 0) x.q_off[0] = 0;
+    if (lane < p.n_req) x.q_off[lane + 1] = end;
+  } else if (block <= x.n_count) {
+    skv_count_request(x.count, block - 1);
+  } else {
+    const int others = x.n_attn + 1 + x.n_count;
+    skv_gather_pages<true, true, 64 * W, 32 / W>(x.gather, (int)blockIdx.x - others, (int)gridDim.x - others, first, x.gather.kpool, x.gather.vpool,
+                                                 x.gather.matched_len, x.gather.page_table, x.gather.ctx_off, x.gather.kctx, x.gather.vctx);
+  }
+}
+template <int D, int W, bool kStep>
+__global__ __launch_bounds__(64 * W, D == 64 ? 2 : 1) void attn_f32_kernel(SkvAttnF32Params p, std::conditional_t<kStep, Rest, int> x) {
+  if constexpr (kStep)
+    if ((int)blockIdx.x >= x.n_attn) return rest_of_step<W>(p, x, (int)blockIdx.x - x.n_attn);
+  attn_f32_item<D, W>(p, blockIdx.x);
+}
+template <bool kStep>
+__global__ __launch_bounds__(kThreads, 2) void attn_f32_tile_kernel(SkvAttnF32Params p, std::conditional_t<kStep, Rest, int> x) {
+  if constexpr (kStep)
+    if ((int)blockIdx.x >= x.n_attn) return rest_of_step<kWaves>(p, x, (int)blockIdx.x - x.n_attn);
+  attn_f32_tile(p, blockIdx.x);
+}
+
 }  // namespace
 
-int skv_attn_f32_enqueue(const SkvAttnF32Params& p, int head_dim, void* stream) {
+int skv_attn_f32_enqueue(const SkvAttnF32Params& params, int head_dim, const SkvStepRest* rest, void* stream) {
   const hipStream_t st = (hipStream_t)stream;
+  SkvAttnF32Params p = params;
   const int64_t tiles = p.max_rows / kBigRows, slots = head_dim == 64 ? 2048 : 1024;   // slots: wavefronts at once
   const bool large = head_dim == 64 && large_tiles(p);
   const int64_t items = ((large ? tiles : p.max_rows / kRows) + p.n_req) * p.Hq;
-  if (items > 0x7fffffff) return SKV_ERANGE;
+  if (items > 0x7fffffff) {
+    const int rc = rest ? skv_gather_enqueue(*rest->gather, false, rest->req_off, rest->q_off, *rest->count, stream) : SKV_OK;
+    return rc ? rc : SKV_ERANGE;
+  }
   const bool rows = items >= slots && 2 * p.max_rows <= 3 * (int64_t)p.n_req;
   const bool alone = items >= 2 * slots || (items >= slots && p.max_blocks <= 16) || (items >= slots / 2 && p.max_blocks <= 2);
   const int row_groups = (int)((p.max_rows * p.Hq + kWaves - 1) / kWaves);   // (no more than items, where they are used)
+  const bool eight = head_dim == 64 && items <= 256 && (p.max_blocks > 16 || p.max_rows > 256 * (int64_t)p.n_req);
+  p.req_off = nullptr;
+  if (rest && p.n_req <= 64 && (large || !(rows || alone)) && items + 1 + p.n_req + skv_gather_blocks(*rest->gather) <= 0x7fffffff) {
+    p.req_off = rest->req_off;
+    const Rest x = {*rest->gather, rest->q_off, *rest->count, (int)items, rest->count->records ? p.n_req : 0};
+    const int grid = (int)items + 1 + x.n_count + skv_gather_blocks(x.gather);
+    if (large)
+      attn_f32_tile_kernel<true><<<grid, kThreads, 0, st>>>(p, x);
+    else if (eight)
+      attn_f32_kernel<64, 2 * kWaves, true><<<grid, 2 * kThreads, 0, st>>>(p, x);
+    else if (head_dim == 64)
+      attn_f32_kernel<64, kWaves, true><<<grid, kThreads, 0, st>>>(p, x);
+    else
+      attn_f32_kernel<128, kWaves, true><<<grid, kThreads, 0, st>>>(p, x);
+    SKV_HIP(hipGetLastError());
+    return SKV_OK;
+  }
+  if (rest) {
+    const int rc = skv_gather_enqueue(*rest->gather, false, rest->req_off, rest->q_off, *rest->count, stream);
+    if (rc) return rc;
+  }
   if (large)
-    attn_f32_tile_kernel<<<(int)items, kThreads, 0, st>>>(p);
+    attn_f32_tile_kernel<false><<<(int)items, kThreads, 0, st>>>(p, 0);
   else if (head_dim == 64 && rows)
     attn_f32_rows_kernel<64><<<row_groups, kThreads, 0, st>>>(p);
   else if (head_dim == 64 && alone)
-    attn_f32_kernel<64, 1><<<(int)items, 64, 0, st>>>(p);
-  else if (head_dim == 64 && items <= 256 && (p.max_blocks > 16 || p.max_rows > 256 * (int64_t)p.n_req))
-    attn_f32_kernel<64, 2 * kWaves><<<(int)items, 2 * kThreads, 0, st>>>(p);
+    attn_f32_kernel<64, 1, false><<<(int)items, 64, 0, st>>>(p, 0);
+  else if (eight)
+    attn_f32_kernel<64, 2 * kWaves, false><<<(int)items, 2 * kThreads, 0, st>>>(p, 0);
   else if (head_dim == 64)
-    attn_f32_kernel<64, kWaves><<<(int)items, kThreads, 0, st>>>(p);
+    attn_f32_kernel<64, kWaves, false><<<(int)items, kThreads, 0, st>>>(p, 0);
   else if (rows)
     attn_f32_rows_kernel<128><<<row_groups, kThreads, 0, st>>>(p);
   else if (alone)
-    attn_f32_kernel<128, 1><<<(int)items, 64, 0, st>>>(p);
+    attn_f32_kernel<128, 1, false><<<(int)items, 64, 0, st>>>(p, 0);
   else
-    attn_f32_kernel<128, kWaves><<<(int)items, kThreads, 0, st>>>(p);
+    attn_f32_kernel<128, kWaves, false><<<(int)items, kThreads, 0, st>>>(p, 0);
   SKV_HIP(hipGetLastError());
   return SKV_OK;
 }

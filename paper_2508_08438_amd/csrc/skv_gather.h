@@ -36,6 +36,25 @@ int skv_gather_blocks(const SkvGather& g);
 int skv_gather_enqueue(const SkvGather& g, bool beside, const int32_t* d_req_off, int32_t* d_q_off, const SkvCount& count, void* stream);
 int skv_count_enqueue(const SkvCount& count, void* stream);
 
+// ---- fp32 prefill attention (skv_attn_f32.hip), enqueued by skv_prefill_attn and skv_prefill_step on checked arguments ----
+struct SkvAttnF32Params {
+  const void *q, *knew, *vnew, *kpool, *vpool;
+  void* out;
+  const int32_t *q_off, *matched_len, *page_table;
+  int n_req, max_blocks, n_pages, Hq, Hkv;
+  float scale;
+  int64_t max_rows;          // rows of q and out
+  const int32_t* req_off;    // not null (the enqueuing function's choice): q_off is being written, it is made from this
+};
+// The rest of a step, with the attention or in front of it: suffix offsets, pages, counters.
+struct SkvStepRest {
+  const SkvGather* gather;
+  const int32_t* req_off;
+  int32_t* q_off;
+  const SkvCount* count;
+};
+int skv_attn_f32_enqueue(const SkvAttnF32Params& p, int head_dim, const SkvStepRest* rest, void* stream);
+
 #ifdef __HIPCC__
 // Request r's: a workgroup.
 __device__ __forceinline__ void skv_count_request(const SkvCount& c, int r) {

@@ -187,15 +187,4 @@ static inline float skv_softmax_scale(const skv_attn_desc* d) {
   return 1.0f / sqrtf((float)d->head_dim);
 }
 
-// ---- fp32 prefill attention (skv_attn_f32.hip), enqueued by skv_prefill_attn on checked arguments ----
-struct SkvAttnF32Params {
-  const void *q, *knew, *vnew, *kpool, *vpool;
-  void* out;
-  const int32_t *q_off, *matched_len, *page_table;
-  int n_req, max_blocks, n_pages, Hq, Hkv;
-  float scale;
-  int64_t max_rows;   // rows of q and out
-};
-int skv_attn_f32_enqueue(const SkvAttnF32Params& p, int head_dim, void* stream);
-
 #endif
