@@ -143,5 +143,78 @@ __device__ __forceinline__ void skv_gather_pages(const SkvGather& g, int block, 
     }
   }
 }
+
+// The same copy without LDS and in few registers: beside, or in the launch of, a kernel that holds most of both.  Up to kSkvGatherScan
+// requests; workgroup `block` of n_blocks takes whole pages; the first one writes the offsets.
+template <int kThreads, int kUnroll>
+__device__ __forceinline__ void skv_copy_pages(int n_req, const char* __restrict__ kpool, const char* __restrict__ vpool, int n_pages,
+                                               const int32_t* __restrict__ matched_len, const int32_t* __restrict__ page_table, int max_blocks,
+                                               int64_t* __restrict__ ctx_off, char* __restrict__ kctx, char* __restrict__ vctx,
+                                               int64_t cap_pages, int page_bytes, int block, int n_blocks) {
+  // A lane holds the pages before its `per` requests.  Nothing in LDS: two attention workgroups of four wavefronts leave none of it.
+  const int lane = threadIdx.x & 63, per = (n_req + 63) / 64;
+  auto pages_of = [&](int r) __attribute__((always_inline)) { return max(matched_len[r], 0) / SKV_BLOCK_TOKENS; };
+  const int r0 = min(lane * per, n_req), r1 = min(r0 + per, n_req);
+  int64_t before = 0, end;
+  {
+    for (int r = r0; r < r1; ++r) before += pages_of(r);
+    const int64_t own = before;
+    before = skv_wave_scan(before);
+    end = min(skv_lane(before, 63), cap_pages);
+    before -= own;
+    if (block == 0 && threadIdx.x < 64) {
+      int64_t at = before;
+      if (lane == 0) ctx_off[0] = 0;
+      for (int r = r0; r < r1; ++r) {
+        at += pages_of(r);
+        ctx_off[r + 1] = at * SKV_BLOCK_TOKENS;
+      }
+    }
+  }
+  const unsigned at = threadIdx.x * 16;
+  // Page ids are asked for a page ahead: one workgroup per compute unit has nobody to cover the read.
+  int r = 0, n = 0;      // request that owns the page, its pages
+  int64_t first = 0;     // and the pages before it
+  auto page_of = [&](int64_t p) __attribute__((always_inline)) {
+    if (p >= end) return -1;
+    if (p >= first + n) {   // (it does end: p < end)
+      const int l = __builtin_popcountll(__ballot(before <= p)) - 1;   // the last lane with no more than p pages before it
+      r = l * per;
+      first = skv_lane(before, l);
+      for (n = pages_of(r); p >= first + n; n = pages_of(r)) {
+        first += n;
+        ++r;
+      }
+    }
+    const int64_t j = p - first;
+    return j < max_blocks ? page_table[(size_t)r * max_blocks + j] : -1;
+  };
+  int next = page_of(block);
+  for (int64_t p = block; p < end; p += n_blocks) {
+    const int page = __builtin_amdgcn_readfirstlane(next);
+    next = page_of(p + n_blocks);
+    if (page < 0 || page >= n_pages) continue;
+    const __amdgpu_buffer_rsrc_t ks = __builtin_amdgcn_make_buffer_rsrc((void*)(kpool + (size_t)page * page_bytes), 0, page_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t vs = __builtin_amdgcn_make_buffer_rsrc((void*)(vpool + (size_t)page * page_bytes), 0, page_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t kd = __builtin_amdgcn_make_buffer_rsrc((void*)(kctx + (size_t)p * page_bytes), 0, page_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t vd = __builtin_amdgcn_make_buffer_rsrc((void*)(vctx + (size_t)p * page_bytes), 0, page_bytes, 0x00020000);
+    constexpr int kStep = kThreads * 16;
+    for (int base = 0; base < page_bytes; base += kUnroll * kStep) {
+      u32x4 a[kUnroll], b[kUnroll];
+#pragma unroll
+      for (int u = 0; u < kUnroll; ++u) {   // (2: non-temporal; a step begins inside the page, so the range check holds)
+        if (base + u * kStep >= page_bytes) break;
+        a[u] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(ks, at, base + u * kStep, 2));
+        b[u] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(vs, at, base + u * kStep, 2));
+      }
+#pragma unroll
+      for (int u = 0; u < kUnroll; ++u) {
+        if (base + u * kStep >= page_bytes) break;
+        __builtin_amdgcn_raw_buffer_store_b128(a[u], kd, at, base + u * kStep, 2);
+        __builtin_amdgcn_raw_buffer_store_b128(b[u], vd, at, base + u * kStep, 2);
+      }
+    }
+  }
+}
 #endif
 #endif
