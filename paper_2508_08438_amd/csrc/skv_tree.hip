@@ -10,6 +10,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
+#include <numeric>
 #include <new>
 #include <vector>
 
@@ -598,7 +599,6 @@ struct Inserter {
   skv_tree* t;
   SkvHostMirror* m;
   int64_t n_blocks, n_in;            // running totals
-  std::vector<int32_t> page, meta;   // per appended block
   size_t node_lo, node_hi, slot_lo, slot_hi;  // dirty spans of records that existed before [lo, hi)
   // What undo() needs: sizes before the call, and the records of then as they were before each change, oldest first.
   struct Node { int32_t at; SkvNode rec; int32_t kids, filled; };
@@ -614,7 +614,7 @@ struct Inserter {
   }
   // Takes back everything the insertions so far did to the mirror.
   void undo() {
-    for (const int32_t p : page) m->page_used[p] = 0;
+    for (size_t i = blocks0; i < m->page.size(); ++i) m->page_used[m->page[i]] = 0;
     for (size_t i = old_slots.size(); i-- > 0;) m->slots[old_slots[i].at] = old_slots[i].rec;
     for (size_t i = old_nodes.size(); i-- > 0;) {
       const Node& o = old_nodes[i];
@@ -852,17 +852,19 @@ struct Inserter {
     m->parent.push_back(node);
     touch_node((size_t)fresh);
     if (!add_child(node, skv_hash_block_host(x + i * 16), fresh)) return false;
+    // (an array at a time, which the upload then reads where it lies: 64 requests with 7.7 k new blocks 116 -> 90 us a call, 40 of it
+    // upload and wait; a block at a time went through eleven vectors)
+    const int32_t* const own = pages + (i - k_vis);
     m->tok.insert(m->tok.end(), x + i * 16, x + nb * 16);
-    for (int64_t j = i; j < nb; ++j) {
-      page.push_back(pages[j - k_vis]);
-      meta.push_back((int32_t)0x80000000 | tenant);
-      m->vis.push_back((int32_t)0x80000000 | tenant);
-      m->node_of.push_back(fresh);
-      m->page.push_back(pages[j - k_vis]);
-      m->canon.push_back((int32_t)(n_in + (j - i)));
-      m->flat_of.push_back((int32_t)(n_blocks + (j - i)));
-      m->page_used[pages[j - k_vis]] = 1;
-    }
+    m->vis.insert(m->vis.end(), (size_t)add, (int32_t)0x80000000 | tenant);
+    m->node_of.insert(m->node_of.end(), (size_t)add, fresh);
+    m->page.insert(m->page.end(), own, own + add);
+    const size_t c0 = m->canon.size(), f0 = m->flat_of.size();
+    m->canon.resize(c0 + (size_t)add);
+    m->flat_of.resize(f0 + (size_t)add);
+    std::iota(m->canon.begin() + c0, m->canon.end(), (int32_t)n_in);
+    std::iota(m->flat_of.begin() + f0, m->flat_of.end(), (int32_t)n_blocks);
+    for (int64_t j = 0; j < add; ++j) m->page_used[own[j]] = 1;
     n_blocks += add;
     n_in += add;
     *n_new = add;
@@ -943,7 +945,7 @@ extern "C" int skv_tree_insert(skv_tree* t, int32_t n_req, const int32_t* req_of
   }
   // Work on the mirror; where the slab is full every change is taken back.  (From records kept of what changed: a snapshot is a copy of
   // the index's size, 116 instead of 97 us for 64 requests, 7.7 k new blocks in 67 k.)
-  Inserter ins{t, m, t->dev.n_blocks, t->n_in_blocks, {}, {}, SIZE_MAX, 0, SIZE_MAX, 0};
+  Inserter ins{t, m, t->dev.n_blocks, t->n_in_blocks, SIZE_MAX, 0, SIZE_MAX, 0};
   hipStream_t st = (hipStream_t)stream;
   // The requester's own path depends on the visibility bits.  The host's copy of them is exact unless a
   // promotion or a safeguard window has been enqueued since it was taken; only then is it fetched again.
@@ -974,20 +976,15 @@ extern "C" int skv_tree_insert(skv_tree* t, int32_t n_req, const int32_t* req_of
   // upload: the appended block records, then the spans of node and slot records that changed
   const int64_t nb0 = t->dev.n_blocks, nin0 = t->n_in_blocks, add = ins.n_blocks - nb0;
   if (private_copies && add > 0) t->has_copies = 1;
-  std::vector<int32_t> ids(3 * (size_t)add);   // canon, flat_of, epoch of the new blocks
-  for (int64_t i = 0; i < add; ++i) {
-    ids[i] = (int32_t)(nin0 + i);
-    ids[add + i] = (int32_t)(nb0 + i);
-    ids[2 * add + i] = (int32_t)t->dev.cur_epoch;
-  }
+  const std::vector<uint32_t> epochs((size_t)add, t->dev.cur_epoch);
   const size_t n_node = ins.node_hi > ins.node_lo ? ins.node_hi - ins.node_lo : 0, n_slot = ins.slot_hi > ins.slot_lo ? ins.slot_hi - ins.slot_lo : 0;
   Mover up{m};
   up.add(m->L.tok + (size_t)nb0 * 64, m->tok.data() + (size_t)nb0 * 16, (size_t)add * 64);
-  up.add(m->L.page + (size_t)nb0 * 4, ins.page.data(), (size_t)add * 4);
-  up.add(m->L.meta + (size_t)nb0 * 4, ins.meta.data(), (size_t)add * 4);
-  up.add(m->L.canon + (size_t)nb0 * 4, ids.data(), (size_t)add * 4);
-  up.add(m->L.flat_of + (size_t)nin0 * 4, ids.data() + add, (size_t)add * 4);
-  up.add(m->L.epoch + (size_t)nb0 * 4, ids.data() + 2 * add, (size_t)add * 4);
+  up.add(m->L.page + (size_t)nb0 * 4, m->page.data() + nb0, (size_t)add * 4);
+  up.add(m->L.meta + (size_t)nb0 * 4, m->vis.data() + nb0, (size_t)add * 4);
+  up.add(m->L.canon + (size_t)nb0 * 4, m->canon.data() + nb0, (size_t)add * 4);
+  up.add(m->L.flat_of + (size_t)nin0 * 4, m->flat_of.data() + nin0, (size_t)add * 4);
+  up.add(m->L.epoch + (size_t)nb0 * 4, epochs.data(), (size_t)add * 4);
   if (n_node) up.add(m->L.nodes + ins.node_lo * sizeof(SkvNode), &m->nodes[ins.node_lo], n_node * sizeof(SkvNode));
   if (n_slot) up.add(m->L.slots + ins.slot_lo * sizeof(SkvSlot), &m->slots[ins.slot_lo], n_slot * sizeof(SkvSlot));
   const int rc = up.up(st);
@@ -1058,7 +1055,7 @@ extern "C" int skv_evict(skv_tree* t, int64_t n_want, const int32_t* protect_ids
     const int32_t f = nd.first + nd.n_blocks - 1;
     return Cand{epoch[f], m->canon[f], n};
   };
-  auto push_tail = [&](int32_t n) {
+  auto push_tail = [&](int32_t n) {   // (of a node whose children have all gone)
     heap.push_back(tail_of(n));
     std::push_heap(heap.begin(), heap.end(), later);
   };
@@ -1071,41 +1068,39 @@ extern "C" int skv_evict(skv_tree* t, int64_t n_want, const int32_t* protect_ids
   size_t node_lo = SIZE_MAX, node_hi = 0, slot_lo = SIZE_MAX, slot_hi = 0;
   std::vector<int32_t> gone(2 * (size_t)std::min(n_want, nb));   // record and input id of every evicted block
   int64_t done = 0;
-  bool held = false;           // `c` is the next candidate already: the block before the last one of the same node, not younger
-  Cand c{};                    // than the oldest in the heap (a node's blocks mostly go one after another)
-  while (done < n_want && (held || !heap.empty())) {
-    if (!held) {
-      std::pop_heap(heap.begin(), heap.end(), later);
-      c = heap.back();
-      heap.pop_back();
-    }
-    held = false;
+  while (done < n_want && !heap.empty()) {
+    std::pop_heap(heap.begin(), heap.end(), later);
+    const Cand c = heap.back();
+    heap.pop_back();
     SkvNode& nd = m->nodes[c.node];
-    if (prot[c.id]) {   // in use, as above
-      node_lo = std::min(node_lo, (size_t)c.node); node_hi = std::max(node_hi, (size_t)c.node + 1);
-      continue;
+    // A node's blocks mostly go one after another: from its last one up to one that is in use (the node keeps it, and with it everything
+    // above) or younger than the oldest in the heap.  How many first, and then each array in a loop of its own
+    // (a call that evicts 7.6 k of 75 k blocks 97 -> 84 us with the wait for epochs and upload, about 40 of it).
+    const int32_t first = nd.first, tail = first + nd.n_blocks - 1;
+    const int32_t least = (int32_t)std::max<int64_t>(first, tail + 1 - (n_want - done));
+    int32_t f = tail;   // the last block that stays
+    bool younger = false;
+    for (; f >= least && !prot[m->canon[f]]; --f) {
+      younger = f < tail && !heap.empty() && later(Cand{epoch[f], m->canon[f], c.node}, heap.front());
+      if (younger) break;
     }
-    const int32_t f = nd.first + nd.n_blocks - 1;
-    const int32_t page = m->page[f];
-    evicted_ids[done] = c.id;
-    evicted_pages[done] = page;
-    gone[2 * done] = f;
-    gone[2 * done + 1] = c.id;
-    ++done;
-    m->page_used[page] = 0;
-    m->canon[f] = -1;
-    m->flat_of[c.id] = -1;
-    nd.n_blocks--;
-    if (nd.n_blocks > 0) {
-      const Cand next{epoch[f - 1], m->canon[f - 1], c.node};
-      if (heap.empty() || !later(next, heap.front())) {
-        c = next;
-        held = true;
-      } else {
-        push_tail(c.node);
-      }
-      if (held && done < n_want) continue;   // (the node is noted when it is left)
+    const int32_t n = tail - f;
+    int32_t *const ids = evicted_ids + done, *const pages = evicted_pages + done, *const pairs = gone.data() + 2 * done;
+    for (int32_t i = 0; i < n; ++i) ids[i] = m->canon[tail - i];
+    for (int32_t i = 0; i < n; ++i) pages[i] = m->page[tail - i];
+    for (int32_t i = 0; i < n; ++i) {
+      pairs[2 * i] = tail - i;
+      pairs[2 * i + 1] = ids[i];
     }
+    for (int32_t i = 0; i < n; ++i) m->page_used[pages[i]] = 0;
+    for (int32_t i = 0; i < n; ++i) m->flat_of[ids[i]] = -1;
+    std::fill_n(m->canon.begin() + f + 1, n, -1);
+    done += n;
+    if (younger) {
+      heap.push_back(Cand{epoch[f], m->canon[f], c.node});
+      std::push_heap(heap.begin(), heap.end(), later);
+    }
+    nd.n_blocks = f + 1 - first;
     node_lo = std::min(node_lo, (size_t)c.node); node_hi = std::max(node_hi, (size_t)c.node + 1);
     if (nd.n_blocks > 0) continue;
     // the node is gone: its entry in the parent's table becomes a removed slot
