@@ -736,15 +736,18 @@ int64_t mean_rows(int32_t n_req, int64_t total_q_rows) { return (total_q_rows + 
 int64_t key_tiles(int64_t rows, int32_t max_blocks) { return ((int64_t)max_blocks * SKV_BLOCK_TOKENS + rows) / kBN + 1; }
 // Whether any split can come of it (the device's rule, with items of 0.7 of the longest on average): where none can neither
 // search nor merge are launched -- 3.2 us of a pass of 55.
-bool may_split(const Layout& y, int32_t n_req, int64_t total_q_rows, int32_t max_blocks) {
-  // more parts than there is room for
-  if ((total_q_rows >> y.pos_log) * y.units > kMaxSlots || (int64_t)n_req * y.units > 2 * kMaxSlots) return false;
+bool forecast_splits(const Layout& y, int32_t n_req, int64_t total_q_rows, int32_t max_blocks, float mean) {   // mean: item to the longest
   const int64_t rows = mean_rows(n_req, total_q_rows), tiles = (rows + (1 << y.pos_log) - 1) >> y.pos_log, items = n_req * tiles;
   const float kt = (float)key_tiles(rows, max_blocks);
   const int last = tile_time((int)(rows - ((tiles - 1) << y.pos_log)), y.pos_log);
-  const float share = 0.7f * n_req * y.units * ((tiles - 1) * kTileFull + last) * kt / kCus;
+  const float share = mean * n_req * y.units * ((tiles - 1) * kTileFull + last) * kt / kCus;
   return split_time(share, (float)total_q_rows / (items << y.pos_log)) <
          whole_time(items * y.units, kt * (tiles > 1 ? kTileFull : last), share);
+}
+bool may_split(const Layout& y, int32_t n_req, int64_t total_q_rows, int32_t max_blocks) {
+  // more parts than there is room for
+  if ((total_q_rows >> y.pos_log) * y.units > kMaxSlots || (int64_t)n_req * y.units > 2 * kMaxSlots) return false;
+  return forecast_splits(y, n_req, total_q_rows, max_blocks, 0.7f);
 }
 // Whether workgroups find their items themselves (plan_item): a request per lane and, where items may be split, an item per
 // lane, in one round of workgroups.  Behind the first round every workgroup, surplus ones too, would pay for it where a list is
@@ -903,6 +906,19 @@ static bool rest_rides(const SkvGather& g, const Layout& y, int64_t grid) {
   return y.units > 0 && y.max_items > 0 && g.n_req <= kSkvGatherScan && !g.large && (int64_t)g.page_vec * 16 <= 0x7fffffff && grid <= kRideRounds * kCus * (y.two ? 2 : 1);
 }
 
+// Whether it does so, too, where workgroups may split items in place, or shares the launch of the merge.  With the attention the copy fills what is
+// idle but slows the parts, whose end is everybody's; beside the merge it takes time of its own.  So with long parts, and where long items
+// are likely to stay whole, so that the merge has nothing to do.  us a pass, beside the merge / with the attention: 1 request of 256 rows
+// behind 24 k keys, 64 heads, parts of 126 key tiles 233 / 222; 900 rows behind 19 k, 164 tiles 296 / 282; 4 of 118 behind 2.2 k, whole
+// items of 46 tiles 103 / 88; 4 of 245 behind 1.5 k, 36 tiles 78 / 68.  Parts of less than 40 tiles lose by 1 to 20 %, 2.5 % on average.
+constexpr int kRidePart = 100, kRideWhole = 20;
+static bool rides_with_parts(const Layout& y, int32_t n_req, int64_t total_q_rows, int32_t max_blocks) {
+  const int64_t rows = mean_rows(n_req, total_q_rows), kt = key_tiles(rows, max_blocks);
+  const int64_t items = n_req * ((rows + (1 << y.pos_log) - 1) >> y.pos_log);
+  return kt >= kRidePart * std::max<int64_t>(1, kCus / y.units / items) ||
+         (kt >= kRideWhole && !forecast_splits(y, n_req, total_q_rows, max_blocks, 1.f));
+}
+
 // Shared by the entry points: enqueues the schedule kernel and the attention kernel on checked arguments.
 static int prefill_attn_enqueue(const skv_attn_desc* desc, int32_t n_req, const void* d_q,
                                 const void* d_knew, const void* d_vnew, const int32_t* d_q_off,
@@ -911,12 +927,14 @@ static int prefill_attn_enqueue(const skv_attn_desc* desc, int32_t n_req, const 
                                 const int32_t* d_page_table, int32_t max_blocks, void* d_out,
                                 void* d_workspace, const Layout& y, const StepExtras* x, void* stream) {
   hipStream_t st = (hipStream_t)stream;
-  // of up to kSkvGatherScan requests a plan with parts makes the suffix offsets itself, and its pages travel beside the merge
+  // of up to kSkvGatherScan requests a plan with parts makes the suffix offsets itself, and its pages travel beside the merge where
+  // they do not with the attention
   const bool plan = desc->dtype == SKV_BF16 && !y.two && plan_in_place(y, n_req) && !(y.max_parts && two_rounds(y, n_req, total_q_rows, max_blocks));
-  const bool late = x && plan && y.max_parts && !x->gather.large;
+  const bool parts = plan && y.max_parts;
   // the list holds whole items or, where anything is split, no more than max_parts records
-  const int64_t grid = (plan && y.max_parts ? kCus / y.units : std::max(y.max_items - y.max_parts, y.max_parts)) * y.units;
-  const bool ride = x && !late && rest_rides(x->gather, y, grid);
+  const int64_t grid = (parts ? kCus / y.units : std::max(y.max_items - y.max_parts, y.max_parts)) * y.units;
+  const bool ride = x && rest_rides(x->gather, y, grid) && (!parts || rides_with_parts(y, n_req, total_q_rows, max_blocks));
+  const bool late = x && parts && !ride && !x->gather.large;
   if (x && !late && !ride && desc->dtype == SKV_BF16) {
     const int rc = skv_gather_enqueue(x->gather, false, x->req_off, x->q_off, x->count, stream);
     if (rc) return rc;
@@ -964,7 +982,7 @@ static int prefill_attn_enqueue(const skv_attn_desc* desc, int32_t n_req, const 
   const int threads = y.two ? Form<true>::threads : kThreads;
   if (ride) {
     const auto kernel = y.two ? attn_rest_kernel<false, false, true>
-                        : y.max_parts ? attn_rest_kernel<true, false, false>   // (with a plan the merge carries the rest)
+                        : y.max_parts ? (plan ? attn_rest_kernel<true, true, false> : attn_rest_kernel<true, false, false>)
                                       : (plan ? attn_rest_kernel<false, true, false> : attn_rest_kernel<false, false, false>);
     const Rest rest = {x->gather, x->count, x->count.records ? n_req : 0, (int)grid};
     kernel<<<(int)grid + rest.n_count + std::min(skv_gather_blocks(x->gather), kCus), threads, 0, st>>>(p, rest);

@@ -13,6 +13,8 @@ CASES = [
     (32, 8, [17, 16, 9, 17] * 25, [2, 0, 3, 1] * 25), (32, 8, [17, 16] * 55, [2, 3] * 55),
     # eight heads and 32-row tiles; a head alone
     (64, 8, [40, 9, 33, 70] * 8, [10, 40, 3, 0] * 8), (3, 3, [130, 300, 5] * 9, [9, 0, 30] * 9),
+    # split in place: long parts, the last request without rows; long items that stay whole, the shortest such table and a shorter one
+    (32, 8, [900, 0], [1190, 70]), (64, 8, [118] * 4, [180, 0, 177, 180]), (64, 8, [118] * 4, [71] * 4), (64, 8, [118] * 4, [67, 67, 0, 67]),
     # 512 requests, 513
     (4, 1, [5, 0, 33, 2] * 128, [1, 0, 2, 1] * 128), (4, 1, [5, 0, 33] * 171, [1, 0, 2] * 171),
 ]
