@@ -1052,14 +1052,7 @@ bool large_tiles(const SkvAttnF32Params& p) {
   if (rows <= 96) return workgroups <= 512;
   return workgroups < 1024 || (int64_t)p.max_blocks * SKV_BLOCK_TOKENS + rows > 224;
 }
-// Where the items fill the chip by themselves, one wavefront takes each: four times as many at once, nothing to merge.  256 / 1000
-// requests of one row, 8 heads, d 64, behind no keys 25.7 / 84.6 us with four, 12.4 / 31.6 with one; behind 96 33.4 / 132 and 28.5 /
-// 95; behind 480 99.9 / 390 and 106 / 385, so up to two rounds the width of the table decides.  Single rows in such numbers are
-// better off without tiles: 12.7 / 20.9, 24.5 / 85, 102 / 362 (two rows each behind 96 keys: 39.3 / 135 against 28.5 / 99).
-// Where every item has a compute unit to itself eight wavefronts share its keys (d 64; at 128 a SIMD holds one): 8 requests of 72 rows
-// behind 256, 8 heads, 12.5 us with four, 11.9 with eight; one of 64 behind 2048 37.0 / 31.9, 2 of 300 behind 1000 28.4 / 25.1; 16 of 64
-// behind 256, 384 items, 16.1 / 20.7.  Up to 256 keys, a block of 32 for each of the eight, the four have two at most and fewer states to
-// merge: one of 40 behind 80 7.0 / 7.7, 16 of 33 behind 208 9.7 / 10.3 (behind 272 11.7 either way).
+
 // What a launch carries behind its attention's workgroups: the rest of a step of up to 64 requests (a lane each).  It needs nothing of the
 // attention, nor that anything of it but q_off, which the workgroups work out (Item::rows_end).  So a step has one launch less, and short
 // workgroups to fill the places that the last long ones leave: eight requests of 270 rows behind 50 keys 28.0 -> 24.7 us a pass, 64 of 1080
@@ -1101,6 +1094,14 @@ __global__ __launch_bounds__(kThreads, 2) void attn_f32_tile_kernel(SkvAttnF32Pa
 
 }  // namespace
 
+// Where the items fill the chip by themselves, one wavefront takes each: four times as many at once, nothing to merge.  256 / 1000
+// requests of one row, 8 heads, d 64, behind no keys 25.7 / 84.6 us with four, 12.4 / 31.6 with one; behind 96 33.4 / 132 and 28.5 /
+// 95; behind 480 99.9 / 390 and 106 / 385, so up to two rounds the width of the table decides.  Single rows in such numbers are
+// better off without tiles: 12.7 / 20.9, 24.5 / 85, 102 / 362 (two rows each behind 96 keys: 39.3 / 135 against 28.5 / 99).
+// Where every item has a compute unit to itself eight wavefronts share its keys (d 64; at 128 a SIMD holds one): 8 requests of 72 rows
+// behind 256, 8 heads, 12.5 us with four, 11.9 with eight; one of 64 behind 2048 37.0 / 31.9, 2 of 300 behind 1000 28.4 / 25.1; 16 of 64
+// behind 256, 384 items, 16.1 / 20.7.  Up to 256 keys, a block of 32 for each of the eight, the four have two at most and fewer states to
+// merge: one of 40 behind 80 7.0 / 7.7, 16 of 33 behind 208 9.7 / 10.3 (behind 272 11.7 either way).
 int skv_attn_f32_enqueue(const SkvAttnF32Params& params, int head_dim, const SkvStepRest* rest, void* stream) {
   const hipStream_t st = (hipStream_t)stream;
   SkvAttnF32Params p = params;

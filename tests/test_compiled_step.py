@@ -1,0 +1,33 @@
+"""Compiled assembly of the attention kernels that carry the rest of a step, for which the same holds as without: idle states behind matrix
+instructions (mfma_hazard_scan), loads to LDS by scalar descriptors, no spilled register, all forms there."""
+import re
+
+import pytest
+from mfma_hazard_scan import scan
+from test_compiled_loads import FORMS, LOAD, _compile, asm  # noqa: F401
+
+
+def _scan(text, kernel):   # (nothing runs on behind the end of a program, where the scan would read on: idle states there)
+    return scan(text.replace("\ts_endpgm\n", "\ts_endpgm\n\ts_nop 15\n\ts_nop 15\n"), kernel, 12)
+
+
+def test_forms_are_all_of_them(asm):  # noqa: F811
+    assert sorted(re.findall(r"^_ZN\S*attn_rest_kernelI(\w+E)EEv\S*:", asm, re.M)) == sorted(FORMS)
+
+
+@pytest.mark.parametrize("form", FORMS)
+def test_bf16(asm, form):  # noqa: F811
+    assert not _scan(asm, "attn_rest_kernelI" + form)
+    body = asm[re.search(r"^_ZN\S*attn_rest_kernelI" + form + r"E\S*:", asm, re.M).end():]
+    parts = re.split(r"^(\.LBB\w+):", body[:body.index(".Lfunc_end")], flags=re.M)
+    blocks = dict(zip(parts[1::2], parts[2::2]))
+    assert len(LOAD.findall("".join(parts))) >= 12
+    assert not [n for n, b in blocks.items() if LOAD.search(b) and re.search(r"s_cbranch_execnz " + re.escape(n) + r"\b", b)]
+    m = re.search(r"\.name:\s+_ZN\S*attn_rest_kernelI" + form + r".*?\.vgpr_count:\s+(\d+)\s+\.vgpr_spill_count:\s+(\d+)", asm, re.S)
+    assert int(m.group(1)) <= 256 and int(m.group(2)) == 0
+
+
+def test_f32(tmp_path_factory):
+    text = _compile("skv_attn_f32.hip", tmp_path_factory)
+    for kernel in ("attn_f32_tile_kernelILb1E", "attn_f32_kernelILi64ELi4ELb1E", "attn_f32_kernelILi64ELi8ELb1E", "attn_f32_kernelILi128ELi4ELb1E"):
+        assert not _scan(text, kernel)
