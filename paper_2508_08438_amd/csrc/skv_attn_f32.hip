@@ -770,9 +770,13 @@ __device__ __forceinline__ void attn_f32_tile(const SkvAttnF32Params& p, int blo
   };
   auto load_v = [&](const Rows& x) __attribute__((always_inline)) {
     const auto rsrc = buffer(x.v, x.bytes);
+    unsigned at = v_off;   // (the row in the lane's offset: the range check takes a scalar one off the buffer's size, which may be less)
+    asm volatile("" : "+v"(at));   // (each from the one before: eight kept through the loop would be spilled)
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
-      vraw[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc, v_off, (unsigned)((i >> 2) * 8 + (i & 3)) * row_bytes, 0));
+    for (int i = 0; i < 8; ++i) {
+      vraw[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc, at, 0, 0));
+      at += (i == 3 ? 5 : 1) * row_bytes;
+    }
   };
   // (not in front of the branches around what is done with them: everybody would wait there for what has just been requested)
   auto here = [](float (&x)[8]) __attribute__((always_inline)) {

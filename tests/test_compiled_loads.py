@@ -49,3 +49,15 @@ def test_gather_reads_offsets_with_scalar_loads(tmp_path_factory):
     m = re.search(r"^_ZN\S*gather_pages_kernelILb0ELb0E\S*:", asm, re.M)
     body = asm[m.end():asm.index(".Lfunc_end", m.end())]
     assert "global_load_dwordx4" in body and not re.search(r"global_load_dword(x2)? ", body)
+
+
+# A buffer load's range check sets what the lane's offset leaves of the buffer's size *less the scalar offset*: one that lies behind the end
+# of a short buffer (a request's last rows, an absent page) is no longer checked against anything.
+@pytest.mark.parametrize("kernel", ["attn_f32_tile_kernelILb0E", "attn_f32_tile_kernelILb1E"])
+def test_f32_rows_are_in_the_lanes_offset(kernel, tmp_path_factory):
+    asm = _compile("skv_attn_f32.hip", tmp_path_factory)
+    m = re.search(r"^_ZN\S*" + kernel + r"\S*:", asm, re.M)
+    loads = re.findall(r"buffer_load_dword\S* .*", asm[m.end():asm.index(".Lfunc_end", m.end())])
+    assert len(loads) >= 30                                              # K and V of the prologue and of either block
+    beside = [x for x in loads if not re.match(r"\S+ v\S+, v\d+, s\[\d+:\d+\], 0 offen", x)]
+    assert not beside, beside

@@ -74,3 +74,31 @@ def test_absent_pages_read_as_zeros():
     want = oracle.attention(**dict(want_c, page_table=pt), n_threads=16)
     got = run_attn(c)
     assert np.linalg.norm(got - want) <= REL * np.linalg.norm(want)
+
+
+def in_tiles(hq, S, max_blocks):
+    """Whether such a call is taken in tiles of 128 rows (large_tiles of skv_attn_f32.hip)."""
+    rows = -(-int(sum(S)) // len(S))
+    workgroups = len(S) * -(-rows // 128) * hq
+    if workgroups < 320 or rows <= 48:
+        return False
+    return workgroups <= 512 if rows <= 96 else workgroups < 1024 or max_blocks * 16 + rows > 224
+
+
+# Nothing behind a request's last key is read: new rows that end where the batch does, in the middle of 16, with NaN behind them.  A NaN
+# among the values, its weight 0, would send the tile to the form that takes its rows one by one, whose bits are others.
+@pytest.mark.parametrize("n", [1, 4, 5, 8, 11, 15])
+def test_nothing_behind_the_last_row(n):
+    S, k = [200, 330, 128 + n], [3, 0, 2]
+    c = attn_case(n, 3, 64, 4, 64, torch.float32, 3, S, k)
+    assert in_tiles(64, S, 3)
+    T, got = len(c["knew"]), {}
+    for behind in (0.0, float("nan")):
+        for x in ("knew", "vnew"):
+            full = torch.full((T + 32, *c[x].shape[1:]), behind, device="cuda:0")
+            full[:T] = c[x]
+            got[x] = full[:T]
+        got[str(behind)] = run_attn(dict(c, **{x: got[x] for x in ("knew", "vnew")}))
+    assert np.array_equal(got["0.0"], got["nan"])
+    want = oracle.attention(**c, n_threads=16)
+    assert np.linalg.norm(got["nan"] - want) <= REL * np.linalg.norm(want)
