@@ -9,6 +9,7 @@
 // times as wide the three keep that order.  The products are formed transposed, S^T = K Q^T and O^T = V^T P^T, so a query is a
 // lane column: the softmax is a register reduction plus one exchange between the halves of the wavefront, and the accumulator
 // registers of S^T are the B operand of the second product as they stand.
+#include <algorithm>
 #include <type_traits>
 
 #include "skv_gather.h"
@@ -1044,17 +1045,21 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 1) void attn_f32_rows_kerne
   one_row<D, D>(p, row);
 }
 
-// Tiles of 128 rows where their workgroups outnumber the compute units and rows fill them.  us with 32 rows to a workgroup / so, 8 heads
-// over 8: 16 requests of 200 rows behind nothing 23.2 / 18.9, behind 1024 keys 75 / 68; 32 of 100 behind 256 32.2 / 28.3; 64 of 100 behind
-// 1024 161 / 110; but 16 of 100 (128 workgroups) behind nothing 10.5 / 14.0, behind 1024 41 / 63.  Of up to 96 rows some wavefronts have none, which in one
-// round is made up for (64 of 64 behind 256 37.4 / 32.2) and in several is not (150 of 64 behind nothing 27.5 / 41.2); many rounds of
-// few keys go faster with one wavefront to an item (150 of 128 behind nothing 52 / 59).  402 calls of 2 to 300 requests of up to 1500
-// rows: time 0.979 of that of the rule before (two tiles a request, 512 in all), 0.971 were every choice right; 14 are slower by 2 % and more.
-bool large_tiles(const SkvAttnF32Params& p) {
-  const int64_t rows = (p.max_rows + p.n_req - 1) / p.n_req, workgroups = p.n_req * ((rows + kBigRows - 1) / kBigRows) * p.Hq;
-  if (workgroups < 320 || rows <= 48) return false;
-  if (rows <= 96) return workgroups <= 512;
-  return workgroups < 1024 || (int64_t)p.max_blocks * SKV_BLOCK_TOKENS + rows > 224;
+// Tiles of 128 rows (d 64; `items`: of 32 rows, `alone`: a wavefront takes one by itself).  Always where requests have two full tiles on average and
+// these fill the places of the chip: 843 such calls 0.79 of the time of 32-row items, 12 slower by 5 % and more, the worst 1.09.
+// Else 32-row items share out fewer rows than a tile holds, and few of them, better; and alone they have nothing to merge, which pays where
+// keys are few.  us with 32 rows to an item / so: 64 requests of 64 rows behind 256 keys, 8 heads over 8, 37.4 / 32.2; 8 of 140, 32 over 8, 35 / 27; 24 of 35, 4 of
+// 8, behind 2300 61 / 102 (rows); 3 of 790, 16 over 4, 1232 items, 46 / 58, 4 of 287 behind 198, 32 over 8, 1248 items, 37 / 33 (items, by keys); 49 of 203,
+// 8 over 8, 224 keys, 48 / 38, 67 of 187, 192 keys, 44 / 50, 290 of 150, 32 over 8, 176 keys, 510 / 638 (alone: keys, the more the more there are to do).
+// 1500 calls of 1 to 400 requests of 30 to 1800 rows behind up to 8192 keys, other ones than these lines were drawn from: 0.918 of the time of the kernels and the
+// rule before (two full tiles, above), 0.911 were every choice right; 15 take tiles and are slower by 5 % and more, 9 of them with lengths that differ by four times, which
+// is not known here (320 workgroups and 49 rows in place of these lines: 0.924, 103 slower).
+bool large_tiles(const SkvAttnF32Params& p, int64_t items, bool alone) {
+  const int64_t full = p.max_rows / kBigRows, rows = (p.max_rows + p.n_req - 1) / p.n_req, tiles = (rows + kBigRows - 1) / kBigRows;
+  if (full >= 2 * (int64_t)p.n_req && full * p.Hq >= 512) return true;
+  const int64_t keys = std::max<int64_t>(rows, (int64_t)p.max_blocks * SKV_BLOCK_TOKENS);
+  if (alone) return 100 * rows > 65 * kBigRows * tiles && keys > 160 + std::min<int64_t>(p.n_req * tiles * p.Hq, 4096) / 20;
+  return 2 * rows >= kBigRows * tiles && items >= (keys > 512 ? 1408 : 1088);
 }
 
 // What a launch carries behind its attention's workgroups: the rest of a step of up to 64 requests (a lane each).  It needs nothing of the
@@ -1109,15 +1114,15 @@ __global__ __launch_bounds__(kThreads, 2) void attn_f32_tile_kernel(SkvAttnF32Pa
 int skv_attn_f32_enqueue(const SkvAttnF32Params& params, int head_dim, const SkvStepRest* rest, void* stream) {
   const hipStream_t st = (hipStream_t)stream;
   SkvAttnF32Params p = params;
-  const int64_t tiles = p.max_rows / kBigRows, slots = head_dim == 64 ? 2048 : 1024;   // slots: wavefronts at once
-  const bool large = head_dim == 64 && large_tiles(p);
-  const int64_t items = ((large ? tiles : p.max_rows / kRows) + p.n_req) * p.Hq;
+  const int64_t small_items = (p.max_rows / kRows + p.n_req) * p.Hq, slots = head_dim == 64 ? 2048 : 1024;   // slots: wavefronts at once
+  const bool rows = small_items >= slots && 2 * p.max_rows <= 3 * (int64_t)p.n_req;
+  const bool alone = small_items >= 2 * slots || (small_items >= slots && p.max_blocks <= 16) || (small_items >= slots / 2 && p.max_blocks <= 2);
+  const bool large = head_dim == 64 && large_tiles(p, small_items, alone);
+  const int64_t items = large ? (p.max_rows / kBigRows + p.n_req) * p.Hq : small_items;
   if (items > 0x7fffffff) {
     const int rc = rest ? skv_gather_enqueue(*rest->gather, false, rest->req_off, rest->q_off, *rest->count, stream) : SKV_OK;
     return rc ? rc : SKV_ERANGE;
   }
-  const bool rows = items >= slots && 2 * p.max_rows <= 3 * (int64_t)p.n_req;
-  const bool alone = items >= 2 * slots || (items >= slots && p.max_blocks <= 16) || (items >= slots / 2 && p.max_blocks <= 2);
   const int row_groups = (int)((p.max_rows * p.Hq + kWaves - 1) / kWaves);   // (no more than items, where they are used)
   const bool eight = head_dim == 64 && items <= 256 && (p.max_blocks > 16 || p.max_rows > 256 * (int64_t)p.n_req);
   p.req_off = nullptr;

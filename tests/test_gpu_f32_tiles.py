@@ -1,4 +1,4 @@
-"""fp32 prefill attention in tiles of 128 rows (more than 320 workgroups, 49 rows a request and more): tiles dealt out by their number among
+"""fp32 prefill attention in tiles of 128 rows (which calls: in_tiles below): tiles dealt out by their number among
 64 requests at a time, a first tile of what a request's rows leave over, blocks of 32 keys two at a time, a reference that moves when weights
 grow.  Against the fp64 oracle; bound as in test_gpu_f32_precision.py."""
 import numpy as np
@@ -78,11 +78,30 @@ def test_absent_pages_read_as_zeros():
 
 def in_tiles(hq, S, max_blocks):
     """Whether such a call is taken in tiles of 128 rows (large_tiles of skv_attn_f32.hip)."""
-    rows = -(-int(sum(S)) // len(S))
-    workgroups = len(S) * -(-rows // 128) * hq
-    if workgroups < 320 or rows <= 48:
-        return False
-    return workgroups <= 512 if rows <= 96 else workgroups < 1024 or max_blocks * 16 + rows > 224
+    T, n = int(sum(S)), len(S)
+    rows, items = -(-T // n), (T // 32 + n) * hq
+    tiles, keys = -(-rows // 128), max(rows, 16 * max_blocks)
+    if T // 128 >= 2 * n and T // 128 * hq >= 512:
+        return True
+    if items >= 4096 or (items >= 2048 and max_blocks <= 16) or (items >= 1024 and max_blocks <= 2):
+        return 100 * rows > 65 * 128 * tiles and keys > 160 + min(n * tiles * hq, 4096) // 20
+    return rows >= 64 * tiles and items >= (1408 if keys > 512 else 1088)
+
+
+# Either side of the lines of that rule.  The rows of a call that is not in tiles have the bits that they have in a call with single rows
+# behind them, which keep the mean below any tile; those of one that is have others.
+@pytest.mark.parametrize("hq,n,rows,max_blocks,tiles", [
+    (8, 67, 187, 12, False), (8, 67, 187, 14, True), (8, 90, 160, 24, False), (8, 90, 170, 24, True), (32, 290, 150, 11, False),   # alone
+    (8, 64, 63, 20, False), (8, 64, 64, 20, True), (8, 18, 200, 20, False), (8, 19, 200, 20, True), (8, 19, 200, 33, False),
+    (16, 3, 790, 50, False), (16, 4, 790, 50, True),
+    (8, 130, 255, 16, False), (8, 130, 256, 16, True)])
+def test_which_calls(hq, n, rows, max_blocks, tiles):
+    S, more = [rows] * n, n * rows // 40
+    assert in_tiles(hq, S, max_blocks) == tiles and not in_tiles(hq, S + [1] * more, max_blocks)
+    c = attn_case(rows, n + more, hq, max(hq // 4, 1), 64, torch.float32, max_blocks, S + [1] * more, [min(2, max_blocks)] * (n + more), n_pages=2 * (n + more) + 3)
+    T, alone = n * rows, {x: c[x][:n * rows] for x in ("q", "knew", "vnew")}
+    got = run_attn(dict(c, **alone, q_off=c["q_off"][:n + 1], matched_len=c["matched_len"][:n], page_table=c["page_table"][:n]))
+    assert np.array_equal(got, run_attn(c)[:T]) != tiles
 
 
 # Nothing behind a request's last key is read: new rows that end where the batch does, in the middle of 16, with NaN behind them.  A NaN
