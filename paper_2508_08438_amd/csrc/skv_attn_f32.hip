@@ -104,32 +104,34 @@ struct Item {
     own = lane < p.n_req ? max(0, p.req_off[lane + 1] - p.req_off[lane] - p.matched_len[lane]) : 0;
     return skv_wave_scan(own);
   }
-  template <int kTileRows>
+  // kStep: q_off is being written by the same launch.  (Known at compile time: asked in every workgroup it cost each call 0.2 to 0.3 us; one row behind
+  // 16 keys 5.92 -> 5.71.)
+  template <int kTileRows, bool kStep>
   __device__ __forceinline__ bool find(const SkvAttnF32Params& p, int block) {
     const int lane = threadIdx.x & 63;
     h = block % p.Hq;
     hk = h / (p.Hq / p.Hkv);
     const int t = block / p.Hq;
     r = 0;
-    if (p.req_off) {
+    if constexpr (kStep) {
       int own;
       const int end = rows_end(p, own);
       r = __builtin_popcountll(__ballot(lane < p.n_req && (end - own) / kTileRows + lane <= t)) - 1;   // (lane 0 always counts)
       qbase = __builtin_amdgcn_readlane(end - own, r);
       S = __builtin_amdgcn_readlane(own, r);
     } else {
-    for (int n = p.n_req; n > 1;) {
-      const int step = (n + 63) / 64;
-      const int idx = r + lane * step;
-      const bool before = idx < r + n && p.q_off[idx] / kTileRows + idx <= t;
-      const int k = __builtin_popcountll(__ballot(before));   // lane 0 always counts (t is at or behind the first place)
-      const int lo = r + (k > 0 ? k - 1 : 0) * step;
-      n = min(step, r + n - lo);
-      r = lo;
-    }
-    r = __builtin_amdgcn_readfirstlane(r);
-    qbase = __builtin_amdgcn_readfirstlane(p.q_off[r]);
-    S = __builtin_amdgcn_readfirstlane(p.q_off[r + 1]) - qbase;
+      for (int n = p.n_req; n > 1;) {
+        const int step = (n + 63) / 64;
+        const int idx = r + lane * step;
+        const bool before = idx < r + n && p.q_off[idx] / kTileRows + idx <= t;
+        const int k = __builtin_popcountll(__ballot(before));   // lane 0 always counts (t is at or behind the first place)
+        const int lo = r + (k > 0 ? k - 1 : 0) * step;
+        n = min(step, r + n - lo);
+        r = lo;
+      }
+      r = __builtin_amdgcn_readfirstlane(r);
+      qbase = __builtin_amdgcn_readfirstlane(p.q_off[r]);
+      S = __builtin_amdgcn_readfirstlane(p.q_off[r + 1]) - qbase;
     }
     S = (int)min((int64_t)S, p.max_rows - qbase);
     const int n_tiles = (S + kTileRows - 1) / kTileRows;
@@ -144,14 +146,14 @@ struct Item {
   // The same places, dealt out anew among each 64 requests: of all of them the last tiles come first, by their number in the request (64
   // requests of 1070 rows over 512 places: the chip empties 1 % after the mean and not 11 %).  What a request's rows leave over is its
   // first tile, which sees the fewest keys, and so many rows more that a wavefront's start where a block of keys does.
-  template <int kTileRows>
+  template <int kTileRows, bool kStep>
   __device__ __forceinline__ bool find_by_number(const SkvAttnF32Params& p, int block) {
     const int lane = threadIdx.x & 63;
     h = block % p.Hq;
     hk = h / (p.Hq / p.Hkv);
     const int t = block / p.Hq;
-    int r0 = 0;   // first of the 64
-    for (int n = (p.n_req + 63) / 64; n > 1;) {
+    int r0 = 0;   // first of the 64 (a step has no more)
+    for (int n = kStep ? 1 : (p.n_req + 63) / 64; n > 1;) {
       const int step = (n + 63) / 64, idx = lane * step;
       const bool before = idx < n && p.q_off[r0 + 64 * idx] / kTileRows + r0 + 64 * idx <= t;
       const int k = __builtin_popcountll(__ballot(before));
@@ -162,7 +164,7 @@ struct Item {
     r0 = __builtin_amdgcn_readfirstlane(r0);
     const bool have = r0 + lane < p.n_req;
     int begin = 0, rows = 0;
-    if (p.req_off) {
+    if constexpr (kStep) {
       const int end = rows_end(p, rows);
       begin = end - rows;
     } else if (have) {
@@ -458,7 +460,7 @@ __device__ __forceinline__ void add_block(f32x16& o, const Pieces& v0, const Pie
 // W: wavefronts of a workgroup, one where the batch fills the chip by itself (the rule stands at the end).
 // Attention alone, us, on the fp32 matrix instruction -> so, four wavefronts: 8 requests of 144..320 rows, 8/8 heads, d 64: 27 -> 21; 100 of up
 // to 30 rows behind 512..2048 cached ones: 140 -> 95; the same at 8/2 heads, d 128: 225 -> 227.
-template <int D, int W>
+template <int D, int W, bool kStep>
 __device__ __forceinline__ void attn_f32_item(const SkvAttnF32Params& p, int block) {
   constexpr int kWaves = W, kThreads = 64 * W;
   constexpr int kJ = D / 8;        // 16-byte pieces of a K row per lane
@@ -477,7 +479,7 @@ __device__ __forceinline__ void attn_f32_item(const SkvAttnF32Params& p, int blo
   const int l32 = lane & 31, half = lane >> 5;
 
   Item it;
-  if (!it.find<kRows>(p, block)) return;
+  if (!it.find<kRows, kStep>(p, block)) return;
   const int h = it.h, hk = it.hk, r = it.r, qbase = it.qbase, S = it.S, L = it.L, row0 = it.row0, row1 = it.row1;
   const int key_end = L + row1;                               // keys [0, key_end) are seen by some row of the tile
   const int n_blocks = (key_end + kKeys - 1) / kKeys;
@@ -694,6 +696,7 @@ __device__ __forceinline__ void attn_f32_item(const SkvAttnF32Params& p, int blo
 // maximum per block: 641; the same with requests one after the other (Item::find): 584.  8 x 2000 rows 335 -> 253, 32 x 290 rows 64 -> 50.
 // 256 rows and eight wavefronts to a workgroup, one to a unit: 658 (a quarter of the wavefronts wait at the diagonal).
 constexpr int kBigRows = kRows * kWaves;
+template <bool kStep>
 __device__ __forceinline__ void attn_f32_tile(const SkvAttnF32Params& p, int block_id) {
   constexpr int D = 64;
   constexpr int kT = D / 16;             // steps of the score product
@@ -712,7 +715,7 @@ __device__ __forceinline__ void attn_f32_tile(const SkvAttnF32Params& p, int blo
   const int l32 = lane & 31, half = lane >> 5;
 
   Item it;
-  if (!it.find_by_number<kBigRows>(p, block_id)) return;
+  if (!it.find_by_number<kBigRows, kStep>(p, block_id)) return;
   const int h = it.h, hk = it.hk, r = it.r, qbase = it.qbase, S = it.S, L = it.L, row0 = it.row0, row1 = it.row1;
   const int key_end = L + row1;                               // keys [0, key_end) are seen by some row of the tile
   const int n_blocks = (key_end + kKeys - 1) / kKeys;
@@ -1092,13 +1095,13 @@ template <int D, int W, bool kStep>
 __global__ __launch_bounds__(64 * W, D == 64 ? 2 : 1) void attn_f32_kernel(SkvAttnF32Params p, std::conditional_t<kStep, Rest, int> x) {
   if constexpr (kStep)
     if ((int)blockIdx.x >= x.n_attn) return rest_of_step<W>(p, x, (int)blockIdx.x - x.n_attn);
-  attn_f32_item<D, W>(p, blockIdx.x);
+  attn_f32_item<D, W, kStep>(p, blockIdx.x);
 }
 template <bool kStep>
 __global__ __launch_bounds__(kThreads, 2) void attn_f32_tile_kernel(SkvAttnF32Params p, std::conditional_t<kStep, Rest, int> x) {
   if constexpr (kStep)
     if ((int)blockIdx.x >= x.n_attn) return rest_of_step<kWaves>(p, x, (int)blockIdx.x - x.n_attn);
-  attn_f32_tile(p, blockIdx.x);
+  attn_f32_tile<kStep>(p, blockIdx.x);
 }
 
 }  // namespace

@@ -44,7 +44,7 @@ struct SkvAttnF32Params {
   int n_req, max_blocks, n_pages, Hq, Hkv;
   float scale;
   int64_t max_rows;          // rows of q and out
-  const int32_t* req_off;    // not null (the enqueuing function's choice): q_off is being written, it is made from this
+  const int32_t* req_off;    // of a launch that writes q_off (the enqueuing function's choice): what that is made from
 };
 // The rest of a step, with the attention or in front of it: suffix offsets, pages, counters.
 struct SkvStepRest {

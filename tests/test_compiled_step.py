@@ -27,7 +27,22 @@ def test_bf16(asm, form):  # noqa: F811
     assert int(m.group(1)) <= 256 and int(m.group(2)) == 0
 
 
-def test_f32(tmp_path_factory):
-    text = _compile("skv_attn_f32.hip", tmp_path_factory)
-    for kernel in ("attn_f32_tile_kernelILb1E", "attn_f32_kernelILi64ELi4ELb1E", "attn_f32_kernelILi64ELi8ELb1E", "attn_f32_kernelILi128ELi4ELb1E"):
-        assert not _scan(text, kernel)
+F32_STEP = ["attn_f32_tile_kernelILb1E", "attn_f32_kernelILi64ELi4ELb1E", "attn_f32_kernelILi64ELi8ELb1E", "attn_f32_kernelILi128ELi4ELb1E"]
+
+
+@pytest.fixture(scope="module")
+def asm_f32(tmp_path_factory):
+    return _compile("skv_attn_f32.hip", tmp_path_factory)
+
+
+def test_f32(asm_f32):
+    for kernel in F32_STEP:
+        assert not _scan(asm_f32, kernel)
+
+
+def test_f32_lengths_are_scanned_in_a_step_only(asm_f32):
+    """Where q_off is there already the workgroups don't ask whether it is."""
+    kernels = {m.group(1): m.group(2) for m in re.finditer(r"^_ZN\S*?(attn_f32_(?:tile_)?kernelI\w*?Lb[01]E)\S*:(.*?)\.Lfunc_end", asm_f32, re.M | re.S)}
+    assert len(kernels) == 2 * len(F32_STEP) + 2 and all(k in kernels for k in F32_STEP)
+    for name, body in kernels.items():
+        assert ("row_bcast" in body) == (name in F32_STEP), name
