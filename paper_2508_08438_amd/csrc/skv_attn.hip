@@ -896,22 +896,35 @@ struct StepExtras {
   SkvCount count;
 };
 
-// Whether the rest of a step rides with its attention.  The copy and the counters need nothing of it, and the suffix offsets are made where
-// the items are; behind its workgroups they fill the places that the last long ones leave, and a launch in front is saved.  us a pass, in
-// front / so: 12 requests of 100 .. 300 rows behind 300 .. 700 keys 61.4 / 51.3, 24 of 50 .. 150 98.0 / 88.8, 10 of 10 .. 60 with 64 heads
-// 55.2 / 43.7.  The other arguments cost every workgroup 0.1 us of its start, so not in many rounds of them (64 of 1070 rows, 34 rounds,
-// 743 either way), nor where the copy is large.
-constexpr int kRideRounds = 4;
-static bool rest_rides(const SkvGather& g, const Layout& y, int64_t grid) {
-  return y.units > 0 && y.max_items > 0 && g.n_req <= kSkvGatherScan && !g.large && (int64_t)g.page_vec * 16 <= 0x7fffffff && grid <= kRideRounds * kCus * (y.two ? 2 : 1);
+// Whether the rest of a step rides with its attention.  The copy and the counters need nothing of it, and the suffix offsets are made where the items
+// are; behind its workgroups they fill the places that the last long ones leave, and a launch in front is saved.  us a pass, in front / so: 12
+// requests of 100 .. 300 rows behind 300 .. 700 keys 61.4 / 51.3, 24 of 50 .. 150 98.0 / 88.8, 10 of 10 .. 60 with 64 heads 55.2 / 43.7.  The other
+// arguments cost every workgroup 0.1 us of its start, so not in many rounds of them: of several hundred steps each 0.77 to 0.92 of the time in up to
+// two rounds, 0.93 to 0.95 in two to five, 0.97 in six to twelve, 1.00 in twenty and more (64 of 1070 rows, 34 rounds, 743 either way). Nor where the
+// copy is long and few rows leave it nothing to hide behind: there it has one workgroup to a compute unit at the most, and none of small pages keeps
+// enough in flight.  Workgroups of four wavefronts: 613 pages of 32 KB, 63 requests of 3 rows, 28.2 / 32.8, 1416 of 84 of 29 62.7 / 69.9; up to 12 MB
+// a pool 0.77 to 0.97; behind more than 128 rows 0.95 to 1.01 whatever its size.  Of eight, pages of 4 KB: 28.7 k of 121 of 2 rows 134 / 161, 5670 of
+// 189 of 12 36.9 / 41.3, 58.6 k of 243 of up to 2 230 / 296; up to 16 MB 0.82 to 0.93, behind more than 128 rows 0.95 (the slowest 1.04).  Of eight,
+// pages of 16 KB and more, 0.75 to 1.00 (large copies, which do not ride, 0.83 to 1.01). 4200 steps, other ones than these lines were drawn from:
+// 0.93 of the time in front, 2 slower by 5 % and more (by 5 and 7), 76 without these limits and kRideWhole's (55 of them by 10 to 23).
+constexpr int kRideRounds = 4, kRideRows = 128;
+constexpr int64_t kRideTwo = 12 << 20, kRideSmall = 16 << 20;
+static bool rest_rides(const SkvGather& g, const Layout& y, int64_t grid, int64_t rows) {   // rows: of a request
+  if (y.units == 0 || y.max_items == 0 || g.n_req > kSkvGatherScan || g.large || (int64_t)g.page_vec * 16 > 0x7fffffff) return false;
+  if (grid > kRideRounds * kCus * (y.two ? 2 : 1)) return false;
+  const int64_t page_bytes = (int64_t)g.page_vec * 16, bytes = std::min((int64_t)g.n_req * g.max_blocks, g.cap_pages) * page_bytes;
+  return rows > kRideRows || bytes < (y.two ? kRideTwo : page_bytes < 16384 ? kRideSmall : INT64_MAX);
 }
 
 // Whether it does so, too, where workgroups may split items in place, or shares the launch of the merge.  With the attention the copy fills what is
-// idle but slows the parts, whose end is everybody's; beside the merge it takes time of its own.  So with long parts, and where long items
-// are likely to stay whole, so that the merge has nothing to do.  us a pass, beside the merge / with the attention: 1 request of 256 rows
-// behind 24 k keys, 64 heads, parts of 126 key tiles 233 / 222; 900 rows behind 19 k, 164 tiles 296 / 282; 4 of 118 behind 2.2 k, whole
-// items of 46 tiles 103 / 88; 4 of 245 behind 1.5 k, 36 tiles 78 / 68.  Parts of less than 40 tiles lose by 1 to 20 %, 2.5 % on average.
-constexpr int kRidePart = 100, kRideWhole = 20;
+// idle but slows the parts, whose end is everybody's; beside the merge it takes time of its own.  So with long parts, and where long items are likely
+// to stay whole, so that the merge has nothing to do.  us a pass, beside the merge / with the attention: 1 request of 256 rows behind 24 k keys, 64
+// heads, parts of 126 key tiles 233 / 222; 900 rows behind 19 k, 164 tiles 296 / 282.  Parts, time with the attention to that beside the merge: of up
+// to 10 tiles 1.01 to 1.11, the slowest 1.33, of 10 to 20 1.00 to 1.08, of 20 to 40 1.00 to 1.04, of 40 to 60 0.98 to 1.02, of 60 to 100 0.94 to
+// 1.01, the slowest 1.08, from 100 on 0.92 to 1.01 (all the slower the larger the copy).  Whole items, 4 of 118 behind 2.2 k, 46 tiles, 103 / 88; of
+// 40 tiles and more 0.92, the slowest 1.01; of 20 to 40 0.96, but where lengths differ parts come of it all the same and one in five is slower, 13 of
+// 2 rows behind 800 .. 1600 40.6 / 46.3, 11 of 30 behind 1200 .. 2300, 37 tiles, 52.8 / 56.3.
+constexpr int kRidePart = 100, kRideWhole = 40;
 static bool rides_with_parts(const Layout& y, int32_t n_req, int64_t total_q_rows, int32_t max_blocks) {
   const int64_t rows = mean_rows(n_req, total_q_rows), kt = key_tiles(rows, max_blocks);
   const int64_t items = n_req * ((rows + (1 << y.pos_log) - 1) >> y.pos_log);
@@ -933,7 +946,7 @@ static int prefill_attn_enqueue(const skv_attn_desc* desc, int32_t n_req, const 
   const bool parts = plan && y.max_parts;
   // the list holds whole items or, where anything is split, no more than max_parts records
   const int64_t grid = (parts ? kCus / y.units : std::max(y.max_items - y.max_parts, y.max_parts)) * y.units;
-  const bool ride = x && rest_rides(x->gather, y, grid) && (!parts || rides_with_parts(y, n_req, total_q_rows, max_blocks));
+  const bool ride = x && rest_rides(x->gather, y, grid, mean_rows(n_req, total_q_rows)) && (!parts || rides_with_parts(y, n_req, total_q_rows, max_blocks));
   const bool late = x && parts && !ride && !x->gather.large;
   if (x && !late && !ride && desc->dtype == SKV_BF16) {
     const int rc = skv_gather_enqueue(x->gather, false, x->req_off, x->q_off, x->count, stream);
