@@ -1106,6 +1106,22 @@ __global__ __launch_bounds__(kThreads, 2) void attn_f32_tile_kernel(SkvAttnF32Pa
 
 }  // namespace
 
+// Whether it does.  The copy there has the attention's registers and LDS: it gets few places while the items hold most, and behind them it has fewer
+// bytes in flight than in a launch of its own.  That costs more than the launch saves where it is large and the attention is bound by memory itself,
+// with few rows.  us in front / with the attention.  Eight wavefronts to an item (256 places), up to 16 rows, pages of 8 KB: 55 requests, 224 items,
+// 4 MB a pool 17.2 / 14.1, 9 MB 21.5 / 24.5, 17 MB 33 / 38, 154 MB 194 / 224; 37, 156 items, 28 MB 49.0 / 52.5, and 0.85 of the time below that;
+// pages of 32 KB: 16, 128 items, 242 MB 267 / 222, 24, 192 items 347 / 363, 29, 232 items 403 / 450, 27, 232 items, 15 MB 23.4 / 25.3.  More rows, 8
+// KB: 13 of 121, 248 items, 33 MB 104 / 117; 32 KB 0.75 to 0.93. Four (512 places), up to 16 rows: 41, 368 items, 169 MB 201 / 163; 46, 464 items,
+// 484 MB 457 / 495, 61, 504 items, 21 MB 27 / 30; more rows 0.81 to 0.95.  3435 steps: 0.809 of the time in front with and without this rule, slower
+// by more than 2 % 6 and 45 of them, by more than 10 % 0 and 21.
+bool rest_rides(const SkvAttnF32Params& p, const SkvGather& g, int head_dim, bool large, bool eight, int64_t items) {
+  if (head_dim != 64 || large) return true;
+  const int64_t page_bytes = (int64_t)g.page_vec * 16, bytes = std::min((int64_t)p.n_req * p.max_blocks, g.cap_pages) * page_bytes;
+  const bool few = p.max_rows <= 16 * (int64_t)p.n_req, small = page_bytes < 16384;
+  if (!eight) return !few || items <= 440 || bytes < 12 << 20;
+  return items <= 160 || bytes < (small ? 6 : items <= 208 ? 48 : 12) << 20 || (!few && (!small || items <= 224));
+}
+
 // Where the items fill the chip by themselves, one wavefront takes each: four times as many at once, nothing to merge.  256 / 1000
 // requests of one row, 8 heads, d 64, behind no keys 25.7 / 84.6 us with four, 12.4 / 31.6 with one; behind 96 33.4 / 132 and 28.5 /
 // 95; behind 480 99.9 / 390 and 106 / 385, so up to two rounds the width of the table decides.  Single rows in such numbers are
@@ -1129,7 +1145,8 @@ int skv_attn_f32_enqueue(const SkvAttnF32Params& params, int head_dim, const Skv
   const int row_groups = (int)((p.max_rows * p.Hq + kWaves - 1) / kWaves);   // (no more than items, where they are used)
   const bool eight = head_dim == 64 && items <= 256 && (p.max_blocks > 16 || p.max_rows > 256 * (int64_t)p.n_req);
   p.req_off = nullptr;
-  if (rest && p.n_req <= 64 && (large || !(rows || alone)) && items + 1 + p.n_req + skv_gather_blocks(*rest->gather) <= 0x7fffffff) {
+  if (rest && p.n_req <= 64 && (large || !(rows || alone)) && rest_rides(p, *rest->gather, head_dim, large, eight, items) &&
+      items + 1 + p.n_req + skv_gather_blocks(*rest->gather) <= 0x7fffffff) {
     p.req_off = rest->req_off;
     const Rest x = {*rest->gather, rest->q_off, *rest->count, (int)items, rest->count->records ? p.n_req : 0};
     const int grid = (int)items + 1 + x.n_count + skv_gather_blocks(x.gather);
