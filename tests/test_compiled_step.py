@@ -46,3 +46,14 @@ def test_f32_lengths_are_scanned_in_a_step_only(asm_f32):
     assert len(kernels) == 2 * len(F32_STEP) + 2 and all(k in kernels for k in F32_STEP)
     for name, body in kernels.items():
         assert ("row_bcast" in body) == (name in F32_STEP), name
+
+
+@pytest.mark.parametrize("kernel", ["attn_f32_tile_kernelILb0E", "attn_f32_tile_kernelILb1E"])
+def test_f32_tiles_spill_outside_their_loop(asm_f32, kernel):
+    """The tile kernel holds all 256 registers and spills some: in front of the loop over the blocks of keys and behind it, where that is cheap."""
+    body = asm_f32[re.search(r"^_ZN\S*" + kernel + r"\S*:", asm_f32, re.M).end():]
+    lines = body[:body.index(".Lfunc_end")].split("\n")
+    label = {m.group(1): i for i, x in enumerate(lines) if (m := re.match(r"(\.LBB\w+):", x))}
+    back = [(label[m.group(1)], i) for i, x in enumerate(lines) if (m := re.search(r"s_c?branch\S* (\.LBB\w+)", x)) and label[m.group(1)] < i]
+    loops = [lines[a:b] for a, b in back if sum("v_mfma" in x for x in lines[a:b]) >= 48]
+    assert loops and not [x for loop in loops for x in loop if "scratch_" in x]

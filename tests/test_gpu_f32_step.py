@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 CASES = [
     # (query heads, kv heads, d, rows, blocks): eight wavefronts to an item, four; d 128; tiles of 128 rows, 64 requests and 65
     (8, 8, 64, [100, 7], [40, 3]), (8, 4, 64, [33] * 40, [3] * 40), (8, 2, 128, [64, 0, 130], [30, 5, 1]),
-    (8, 8, 64, [100, 0, 129] * 21 + [64], [2, 9, 0] * 21 + [1]), (8, 8, 64, [100, 60, 129] * 21 + [64, 1], [2, 9, 0] * 21 + [1, 3]),
+    (8, 8, 64, [100, 0, 129] * 21 + [64], [2, 9, 0] * 21 + [1]), (8, 8, 64, [100, 60, 129] * 21 + [64, 1], [2, 17, 0] * 21 + [1, 3]),
     # one wavefront to an item and single rows: launches of their own
     (32, 4, 64, [33, 1] * 32, [2, 1] * 32), (32, 8, 64, [1] * 64, [4] * 64),
     # nothing cached; a copy of 52 MB a pool

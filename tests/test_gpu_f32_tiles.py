@@ -15,17 +15,30 @@ G = np.random.default_rng(9)
 EDGES = [49, 127, 128, 129, 160, 161, 255, 256, 257, 31, 1, 0, 33, 384, 97, 512]
 # query / kv heads, rows and reused blocks per request
 CASES = {
-    "edges of tiles": (32, 2, EDGES, [0, 1, 2, 3, 4, 5, 6, 7, 0, 9, 1, 3, 2, 1, 13, 0]),
-    "more than 64 requests": (4, 4, G.integers(49, 140, 130), G.integers(0, 4, 130)),
-    "one of them alone in its 64": (8, 8, [60] * 64 + [130], [1] * 65),
-    "no rows among them": (16, 4, [0] * 70 + [300] * 11 + [0] * 3, [2] * 84),
+    "edges of tiles": (32, 2, EDGES, [0, 1, 2, 3, 4, 5, 6, 7, 0, 9, 1, 3, 2, 1, 20, 0]),
+    "more than 64 requests": (4, 4, G.integers(49, 160, 130), [*G.integers(0, 4, 129), 20]),
+    "one of them alone in its 64": (8, 8, [100] * 64 + [130], [1] * 64 + [20]),
+    "no rows among them": (16, 4, [0] * 70 + [700] * 11 + [0] * 3, [2] * 75 + [20] + [2] * 8),
     "pages of more than 64 blocks of keys": (64, 4, [200, 330, 70, 64], [260, 129, 128, 0]),
     "one long request": (32, 4, [1500], [5]),
 }
 
 
+def in_tiles(hq, S, max_blocks):
+    """Whether such a call is taken in tiles of 128 rows (large_tiles of skv_attn_f32.hip)."""
+    T, n = int(sum(S)), len(S)
+    rows, items = -(-T // n), (T // 32 + n) * hq
+    tiles, keys = -(-rows // 128), max(rows, 16 * max_blocks)
+    if T // 128 >= 2 * n and T // 128 * hq >= 512:
+        return True
+    if items >= 4096 or (items >= 2048 and max_blocks <= 16) or (items >= 1024 and max_blocks <= 2):
+        return 100 * rows > 65 * 128 * tiles and keys > 160 + min(n * tiles * hq, 4096) // 20
+    return rows >= 64 * tiles and items >= (1408 if keys > 512 else 1088)
+
+
 def case(name, seed=3):
     hq, hkv, S, k = CASES[name]
+    assert in_tiles(hq, S, max(max(k), 1))
     return attn_case(seed, len(S), hq, hkv, 64, torch.float32, max(max(k), 1), S, k, n_pages=int(sum(k)) + 3)
 
 
@@ -74,18 +87,6 @@ def test_absent_pages_read_as_zeros():
     want = oracle.attention(**dict(want_c, page_table=pt), n_threads=16)
     got = run_attn(c)
     assert np.linalg.norm(got - want) <= REL * np.linalg.norm(want)
-
-
-def in_tiles(hq, S, max_blocks):
-    """Whether such a call is taken in tiles of 128 rows (large_tiles of skv_attn_f32.hip)."""
-    T, n = int(sum(S)), len(S)
-    rows, items = -(-T // n), (T // 32 + n) * hq
-    tiles, keys = -(-rows // 128), max(rows, 16 * max_blocks)
-    if T // 128 >= 2 * n and T // 128 * hq >= 512:
-        return True
-    if items >= 4096 or (items >= 2048 and max_blocks <= 16) or (items >= 1024 and max_blocks <= 2):
-        return 100 * rows > 65 * 128 * tiles and keys > 160 + min(n * tiles * hq, 4096) // 20
-    return rows >= 64 * tiles and items >= (1408 if keys > 512 else 1088)
 
 
 # Either side of the lines of that rule.  The rows of a call that is not in tiles have the bits that they have in a call with single rows
