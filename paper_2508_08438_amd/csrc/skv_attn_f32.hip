@@ -310,7 +310,8 @@ struct RangeOfQ {
   }
   __device__ __forceinline__ bool odd() const { return least < ((127u - 100u) << 23) - 1u || most > (127u + 80u) << 23; }
 };
-// A sum over a column of V that small has values (or zeros) below 2^-95 only, were there 2^25 keys.
+// Where a sum over a column is that small, its values need a look (tiny_columns): of values (or zeros) below 2^-95 any is, up to 2^23 keys, whose weights are 4 on
+// average at the most (kSumLimit of a lane's 16).
 template <int kA>
 __device__ __forceinline__ bool some_small(const f32x16 (&o)[kA], float l) {
   bool small = false;
