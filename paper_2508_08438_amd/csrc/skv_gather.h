@@ -144,7 +144,8 @@ __device__ __forceinline__ void skv_gather_pages(const SkvGather& g, int block, 
   }
 }
 
-// The same copy without LDS and in few registers: beside, or in the launch of, a kernel that holds most of both.  Up to kSkvGatherScan
+// The same copy without LDS of its own and in few registers: beside a kernel that holds most of both, or in its launch.  (There every workgroup has the
+// kernel's LDS, 80 to 128 KB of the bf16 attention's: it waits until a compute unit, or half of one, is free.)  Up to kSkvGatherScan
 // requests; workgroup `block` of n_blocks takes whole pages; the first one writes the offsets.
 template <int kThreads, int kUnroll>
 __device__ __forceinline__ void skv_copy_pages(int n_req, const char* __restrict__ kpool, const char* __restrict__ vpool, int n_pages,
