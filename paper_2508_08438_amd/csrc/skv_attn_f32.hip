@@ -692,10 +692,11 @@ __device__ __forceinline__ void attn_f32_item(const SkvAttnF32Params& p, int blo
 // splitting of its weights, the output products of block i beside the splitting of K(i + 2) and V(i + 1) and the sums of the output.  Two
 // buffers of K and two of V, one barrier a block; two workgroups to a compute unit.
 // What bounds it: issue, with two wavefronts on a SIMD and their waits (48 matrix instructions, 36 reads of LDS, 310 vector and 80 scalar
-// instructions a block), and the clock under that load: 64 requests x 1070 rows x 8 heads 568 us, 470 on constant values; the six products
-// alone are 302 at the rate the instruction holds on random operands.  One block at a time, splitting between two barriers and a
-// maximum per block: 641; the same with requests one after the other (Item::find): 584.  8 x 2000 rows 335 -> 253, 32 x 290 rows 64 -> 50.
-// 256 rows and eight wavefronts to a workgroup, one to a unit: 658 (a quarter of the wavefronts wait at the diagonal).
+// instructions a block), the loads of raw rows, which are requested at the very end of a block, and the clock under that load.  64 requests x 1070
+// rows x 8 heads behind 128 keys 575 us, 656 with one block at a time, splitting between two barriers and a maximum per block; 8 x 2000 rows 260 ->
+// 190, 32 x 290 behind 256 85 -> 65.  The six products alone are 302 of 64 x 1070 at the rate the instruction holds on random operands; constant
+// values take 0.83 of the time, without loads (wrong) it is 0.76, with requests one after the other (Item::find) 1.03, with 256 rows and eight
+// wavefronts to a workgroup, one to a unit, 1.16 (a quarter of the wavefronts wait at the diagonal).
 constexpr int kBigRows = kRows * kWaves;
 template <bool kStep>
 __device__ __forceinline__ void attn_f32_tile(const SkvAttnF32Params& p, int block_id) {
@@ -1050,20 +1051,23 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 3 : 1) void attn_f32_rows_kerne
 }
 
 // Tiles of 128 rows (d 64; `items`: of 32 rows, `alone`: a wavefront takes one by itself).  Always where requests have two full tiles on average and
-// these fill the places of the chip: 843 such calls 0.79 of the time of 32-row items, 12 slower by 5 % and more, the worst 1.09.
-// Else 32-row items share out fewer rows than a tile holds, and few of them, better; and alone they have nothing to merge, which pays where
-// keys are few.  us with 32 rows to an item / so: 64 requests of 64 rows behind 256 keys, 8 heads over 8, 37.4 / 32.2; 8 of 140, 32 over 8, 35 / 27; 24 of 35, 4 of
-// 8, behind 2300 61 / 102 (rows); 3 of 790, 16 over 4, 1232 items, 46 / 58, 4 of 287 behind 198, 32 over 8, 1248 items, 37 / 33 (items, by keys); 49 of 203,
-// 8 over 8, 224 keys, 48 / 38, 67 of 187, 192 keys, 44 / 50, 290 of 150, 32 over 8, 176 keys, 510 / 638 (alone: keys, the more the more there are to do).
-// 1500 calls of 1 to 400 requests of 30 to 1800 rows behind up to 8192 keys, other ones than these lines were drawn from: 0.918 of the time of the kernels and the
-// rule before (two full tiles, above), 0.911 were every choice right; 15 take tiles and are slower by 5 % and more, 9 of them with lengths that differ by four times, which
-// is not known here (320 workgroups and 49 rows in place of these lines: 0.924, 103 slower).
+// these fill the places of the chip: 532 such calls 0.80 of the time of 32-row items, 2 slower by 2 % and more. Else 32-row items share out fewer
+// rows than a tile holds, and few of them, better; and alone they have nothing to merge, which pays where keys are few.  So for items enough whose
+// rows fill three quarters of their tiles, or half where the tiles are one round of the chip's 512 places (behind the first round half-filled tiles
+// cost most).  us with 32 rows to an item / so: 64 requests of 64 rows behind 256 keys, 8 heads over 8, 512 tiles, 37.4 / 32.2, 8 of 140, 32 over 8,
+// 35 / 27; but 55 of 64 behind up to 1500, 16 over 4, 880 tiles, 111 / 153, 66 of 87 behind 1700, 8 over 8, 528 tiles, 181 / 208 (round); 28 of 182
+// behind up to 4200, 8 over 8, 200 / 247, 24 of 35, 4 of 8, behind 2300 61 / 102 (rows); 3 of 790, 16 over 4, 1232 items, 46 / 58, 4 of 287 behind
+// 198, 32 over 8, 1248 items, 37 / 33 (items, by keys); 49 of 203, 8 over 8, 224 keys, 48 / 38, 67 of 187, 192 keys, 44 / 50, 290 of 150, 32 over 8,
+// 176 keys, 510 / 638 (alone: keys, the more the more there are to do). 3000 calls of 2 to 200 requests of 40 to 1500 rows behind up to 6000 keys,
+// other ones than these lines were drawn from: 0.935 of the time of 32-row items, 0.925 were every choice right, 8 slower by 5 % and more, 2 by 10
+// (0.938, 41 and 16 with half-filled tiles in any number); lengths that differ are not known here.
 bool large_tiles(const SkvAttnF32Params& p, int64_t items, bool alone) {
   const int64_t full = p.max_rows / kBigRows, rows = (p.max_rows + p.n_req - 1) / p.n_req, tiles = (rows + kBigRows - 1) / kBigRows;
   if (full >= 2 * (int64_t)p.n_req && full * p.Hq >= 512) return true;
-  const int64_t keys = std::max<int64_t>(rows, (int64_t)p.max_blocks * SKV_BLOCK_TOKENS);
-  if (alone) return 100 * rows > 65 * kBigRows * tiles && keys > 160 + std::min<int64_t>(p.n_req * tiles * p.Hq, 4096) / 20;
-  return 2 * rows >= kBigRows * tiles && items >= (keys > 512 ? 1408 : 1088);
+  const int64_t keys = std::max<int64_t>(rows, (int64_t)p.max_blocks * SKV_BLOCK_TOKENS), workgroups = p.n_req * tiles * p.Hq;
+  if (alone) return 100 * rows > 65 * kBigRows * tiles && keys > 160 + std::min<int64_t>(workgroups, 4096) / 20;
+  const bool round = workgroups > 448 && workgroups <= 512;
+  return (round ? 2 * rows >= kBigRows * tiles : 4 * rows >= 3 * kBigRows * tiles) && items >= (keys > 512 ? 1408 : 1088);
 }
 
 // What a launch carries behind its attention's workgroups: the rest of a step of up to 64 requests (a lane each).  It needs nothing of the

@@ -12,14 +12,14 @@ pytestmark = pytest.mark.gpu
 REL = 8 * 2.0 ** -24
 
 G = np.random.default_rng(9)
-EDGES = [49, 127, 128, 129, 160, 161, 255, 256, 257, 31, 1, 0, 33, 384, 97, 512]
+EDGES = [49, 127, 128, 129, 160, 161, 255, 256, 257, 31, 1, 0, 33, 384, 97, 1100]
 # query / kv heads, rows and reused blocks per request
 CASES = {
     "edges of tiles": (32, 2, EDGES, [0, 1, 2, 3, 4, 5, 6, 7, 0, 9, 1, 3, 2, 1, 20, 0]),
     "more than 64 requests": (4, 4, G.integers(49, 160, 130), [*G.integers(0, 4, 129), 20]),
     "one of them alone in its 64": (8, 8, [100] * 64 + [130], [1] * 64 + [20]),
     "no rows among them": (16, 4, [0] * 70 + [700] * 11 + [0] * 3, [2] * 75 + [20] + [2] * 8),
-    "pages of more than 64 blocks of keys": (64, 4, [200, 330, 70, 64], [260, 129, 128, 0]),
+    "pages of more than 64 blocks of keys": (64, 4, [200, 330, 100, 164], [260, 129, 128, 0]),
     "one long request": (32, 4, [1500], [5]),
 }
 
@@ -33,7 +33,7 @@ def in_tiles(hq, S, max_blocks):
         return True
     if items >= 4096 or (items >= 2048 and max_blocks <= 16) or (items >= 1024 and max_blocks <= 2):
         return 100 * rows > 65 * 128 * tiles and keys > 160 + min(n * tiles * hq, 4096) // 20
-    return rows >= 64 * tiles and items >= (1408 if keys > 512 else 1088)
+    return rows >= (64 if 448 < n * tiles * hq <= 512 else 96) * tiles and items >= (1408 if keys > 512 else 1088)
 
 
 def case(name, seed=3):
@@ -93,7 +93,7 @@ def test_absent_pages_read_as_zeros():
 # behind them, which keep the mean below any tile; those of one that is have others.
 @pytest.mark.parametrize("hq,n,rows,max_blocks,tiles", [
     (8, 67, 187, 12, False), (8, 67, 187, 14, True), (8, 90, 160, 24, False), (8, 90, 170, 24, True), (32, 290, 150, 11, False),   # alone
-    (8, 64, 63, 20, False), (8, 64, 64, 20, True), (8, 18, 200, 20, False), (8, 19, 200, 20, True), (8, 19, 200, 33, False),
+    (8, 64, 63, 20, False), (8, 64, 64, 20, True), (8, 65, 95, 20, False), (8, 65, 96, 20, True), (8, 56, 95, 20, False), (8, 57, 95, 20, True), (8, 18, 200, 20, False), (8, 19, 200, 20, True), (8, 19, 200, 33, False),
     (16, 3, 790, 50, False), (16, 4, 790, 50, True),
     (8, 130, 255, 16, False), (8, 130, 256, 16, True)])
 def test_which_calls(hq, n, rows, max_blocks, tiles):
