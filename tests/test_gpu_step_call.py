@@ -59,7 +59,7 @@ CASES = [
     # unsplit and with a list: 33, 64, 65 requests; 512 and 513, where the copy no longer scans
     (8, 1, 128, "bf16", [1] * 33, [60] * 33), (8, 2, 128, "bf16", [33, 70] * 32, [1, 9] * 32), (8, 2, 128, "bf16", [33] * 65, [2] * 65),
     (4, 1, 128, "bf16", [3, 0] * 256, [1, 2] * 256), (4, 1, 128, "bf16", [3] * 513, [1] * 513),
-    # fp32: the offsets with the copy; a copy with a launch of its own (48 MB a pool), in front of either type
+    # fp32: the offsets with the copy; a copy of 48 MB a pool, with the fp32 attention and in front of the bf16 one
     (8, 8, 64, "f32", [64, 1, 80], [16, 0, 3]), (4, 2, 64, "f32", [2] * 257, [1] * 257), (8, 8, 128, "f32", [9, 30], [300, 420]),
     (8, 8, 128, "bf16", [40], [1600]),
     # nothing cached, nothing new, nobody
